@@ -205,12 +205,23 @@ def run_workload(name, steps, warmup, peaks, with_optimiser=True, with_evaluatio
     if step.side is not None and occupancy is None:
         p0 = resident[0]
         n0 = (step.offsets[p0 + 1] - step.offsets[p0]) * S
-        if n0 and B.dg_hashgrid_encode_bwd_workspace_bytes(models[p0].grid, n0) <= step.ws_enc.numel() * 4:
+        order = step.layout[p0][2] if n0 else None          # samples in spatial order: only the unmerged levels are counted
+        grid0 = models[p0].grid
+        need = (B.dg_hashgrid_encode_bwd_workspace_bytes(grid0, n0) if order is None
+                else B.dg_hashgrid_encode_bwd_ordered_workspace_bytes(grid0, order, n0))
+
+        def count_sweep():
+            if order is None:
+                B.dg_hashgrid_encode_bwd_count(grid0, step.u[:n0], n0, step.ws_enc)
+            else:
+                B.dg_hashgrid_encode_bwd_ordered_count(grid0, order, step.u[:n0], n0, step.ws_enc)
+
+        if n0 and need <= step.ws_enc.numel() * 4:
             ev = [torch.cuda.Event(enable_timing=True) for _ in range(2)]
-            B.dg_hashgrid_encode_bwd_count(models[p0].grid, step.u[:n0], n0, step.ws_enc)
+            count_sweep()
             ev[0].record()
             for _ in range(3):
-                B.dg_hashgrid_encode_bwd_count(models[p0].grid, step.u[:n0], n0, step.ws_enc)
+                count_sweep()
             ev[1].record()
             ev[1].synchronize()
             count_ahead_ms = ev[0].elapsed_time(ev[1]) / 3

@@ -184,6 +184,46 @@ int dg_hashgrid_corner_indices(const dg_grid_desc *desc, const float *u, uint64_
                                uint32_t *idx, void *stream);
 
 /* ------------------------------------------------------------------------------------
+ * Samples in spatial order.  Large batches of samples are encoded faster when neighbours in
+ * memory are neighbours in space (they then share table lines), and the gradients of the coarser
+ * levels can be summed on chip, region by region, before they reach memory.  dg_order_samples sorts
+ * the samples of one sub-model; the *_ordered calls take the sorted list.  The order is a matter of
+ * speed alone, results stay those of the calls above.  Features and their gradient then are
+ * SAMPLE-MAJOR ROWS in the samples' original order: feat [N, L, F] fp16 for the *_rows network calls below.
+ * ---------------------------------------------------------------------------------- */
+typedef struct dg_order_desc {
+    uint32_t n_bricks[3], total;          /* the box cut into total = product equal bricks */
+    float    per_unit[3];                 /* bricks per unit of the unit coordinates     */
+    uint32_t n_merged;                    /* levels [0, n_merged) are summed brick by brick in the backward pass (even) */
+    uint32_t box[DG_MAX_LEVELS][3];       /* vertices of a brick at those levels         */
+    uint32_t box_first[DG_MAX_LEVELS + 1];
+} dg_order_desc;
+/* Host.  Bricks for N samples of a sub-model with this grid (L = 16, F = 2; else DG_ERR_UNSUPPORTED). */
+int dg_order_desc_init(dg_order_desc *order, const dg_grid_desc *desc, uint64_t N);
+/* ordered [N] of 16 bytes each (x, y, z fp32 and the sample's index, uint32; device, 16-byte aligned);
+ * pieces: dg_order_pieces_words(order, N) words that list which stretch of the order belongs to which brick (read by
+ * dg_hashgrid_encode_bwd_ordered; 8-byte aligned).  N < 2^32 - 1.
+ * ws: dg_order_workspace_bytes(order) bytes of device memory, 256-byte aligned. */
+size_t dg_order_workspace_bytes(const dg_order_desc *order);
+size_t dg_order_pieces_words(const dg_order_desc *order, uint64_t N);
+int dg_order_samples(const dg_order_desc *order, const float *u, uint64_t N, void *ordered, uint32_t *pieces,
+                     void *ws, size_t ws_bytes, void *stream);
+/* dg_hashgrid_encode_fwd on the sorted list: row `index` of feat [N, L*F] fp16 (16-byte aligned). */
+int dg_hashgrid_encode_fwd_ordered(const dg_grid_desc *desc, const float *table, const void *ordered, uint64_t N,
+                                   void *feat, void *stream);
+/* dg_hashgrid_encode_bwd on the sorted list.  dfeat: rows [N, 2 * n_merged] fp32 of the merged levels (16-byte aligned, in
+ * the samples' original order), then the planes [L - n_merged, N, 2] of the others -- as dg_mlp_bwd_rows writes it; u [N,3]
+ * the samples in their original order.  The merged levels are summed in fp64 per brick; the others go through the bins as
+ * in dg_hashgrid_encode_bwd, with its precision.  counted != 0: the queues have been laid out by ..._ordered_count (rules as
+ * for dg_hashgrid_encode_bwd_count). */
+size_t dg_hashgrid_encode_bwd_ordered_workspace_bytes(const dg_grid_desc *desc, const dg_order_desc *order, uint64_t N);
+int dg_hashgrid_encode_bwd_ordered_count(const dg_grid_desc *desc, const dg_order_desc *order, const float *u, uint64_t N,
+                                         void *ws, size_t ws_bytes, void *stream);
+int dg_hashgrid_encode_bwd_ordered(const dg_grid_desc *desc, const dg_order_desc *order, const void *ordered,
+                                   const uint32_t *pieces, const float *u, const float *dfeat, uint64_t N, float *dtable,
+                                   void *ws, size_t ws_bytes, uint32_t counted, void *stream);
+
+/* ------------------------------------------------------------------------------------
  * Field MLPs (Sec. 3.2: a small MLP fuses the level features; Sec. 5.1: sigmoid hidden activation in the colour
  * net, outputs of both nets clipped to [-15,15] before the output activations).
  *   density: feat[n_feat] -> n_hidden_d (ReLU) -> geo[n_geo];  sigma = exp(clip(geo[0]))
@@ -293,6 +333,21 @@ int dg_mlp_composite_fwd(const dg_mlp_desc *desc, const void *weights, const voi
                          const void *app, uint32_t S, uint32_t n_seg, const float *delta, const float *t,
                          const uint32_t *seg_ray, const uint32_t *seg_slot, uint32_t k_max, float *Ck, float *Tk,
                          float *Dk, void *stream);
+
+/* The network calls on sample-major feature rows (dg_hashgrid_encode_fwd_ordered): feat [N, 32] fp16, 16-byte aligned, else
+ * as dg_mlp_fwd_app, dg_mlp_composite_fwd and dg_mlp_bwd_app (app NULL without appearance inputs; same workspace).  The
+ * feature gradient comes as dg_hashgrid_encode_bwd_ordered reads it: rows [N, 2 * n_merged] fp32 for levels below n_merged
+ * (even; dg_order_desc.n_merged), then planes [16 - n_merged, N, 2] for the others; dfeat 16-byte aligned.
+ * DG_ERR_UNSUPPORTED unless the network is the 32-64-16 / (32 + n_app)-64-64-3 one. */
+int dg_mlp_fwd_rows(const dg_mlp_desc *desc, const void *weights, const void *feat, const void *dir_enc, const void *app,
+                    uint32_t S, uint64_t N, float *sigma, float *rgb, void *stream);
+int dg_mlp_composite_fwd_rows(const dg_mlp_desc *desc, const void *weights, const void *feat, const void *dir_enc,
+                              const void *app, uint32_t S, uint32_t n_seg, const float *delta, const float *t,
+                              const uint32_t *seg_ray, const uint32_t *seg_slot, uint32_t k_max, float *Ck, float *Tk,
+                              float *Dk, void *stream);
+int dg_mlp_bwd_rows(const dg_mlp_desc *desc, const void *weights, const void *feat, const void *dir_enc, const void *app,
+                    uint32_t S, uint64_t N, const float *dsigma, const float *drgb, float loss_scale, uint32_t n_merged,
+                    float *dfeat, float *dW, void *ws, size_t ws_bytes, void *stream);
 
 /* One Adam step (Sec. 5.1 names the optimiser; the update is Algorithm 1 of Kingma & Ba) on n fp32 values, in place:
  *   g' = g + l2 * p;  m = beta1 m + (1 - beta1) g';  v = beta2 v + (1 - beta2) g'^2;

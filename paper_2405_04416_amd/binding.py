@@ -37,6 +37,11 @@ class OccDesc(C.Structure):
     _fields_ = [("res", C.c_uint32 * 3), ("n_cells", C.c_uint32), ("scale", C.c_float * 3)]
 
 
+class OrderDesc(C.Structure):
+    _fields_ = [("n_bricks", C.c_uint32 * 3), ("total", C.c_uint32), ("per_unit", C.c_float * 3), ("n_merged", C.c_uint32),
+                ("box", (C.c_uint32 * 3) * MAX_LEVELS), ("box_first", C.c_uint32 * (MAX_LEVELS + 1))]
+
+
 class DistGridError(RuntimeError):
     pass
 
@@ -67,6 +72,16 @@ _SIGNATURES = {
     "dg_hashgrid_encode_bwd_counted": (C.c_int, [C.POINTER(GridDesc), C.c_void_p, C.c_void_p, C.c_uint64, C.c_void_p, C.c_void_p,
                                                  C.c_size_t, C.c_void_p]),
     "dg_hashgrid_corner_indices": (C.c_int, [C.POINTER(GridDesc), C.c_void_p, C.c_uint64, C.c_void_p, C.c_void_p]),
+    "dg_order_desc_init": (C.c_int, [C.POINTER(OrderDesc), C.POINTER(GridDesc), C.c_uint64]),
+    "dg_order_workspace_bytes": (C.c_size_t, [C.POINTER(OrderDesc)]),
+    "dg_order_samples": (C.c_int, [C.POINTER(OrderDesc), C.c_void_p, C.c_uint64, C.c_void_p, C.c_void_p, C.c_void_p, C.c_size_t, C.c_void_p]),
+    "dg_order_pieces_words": (C.c_size_t, [C.POINTER(OrderDesc), C.c_uint64]),
+    "dg_hashgrid_encode_bwd_ordered_workspace_bytes": (C.c_size_t, [C.POINTER(GridDesc), C.POINTER(OrderDesc), C.c_uint64]),
+    "dg_hashgrid_encode_bwd_ordered_count": (C.c_int, [C.POINTER(GridDesc), C.POINTER(OrderDesc), C.c_void_p, C.c_uint64, C.c_void_p, C.c_size_t,
+                                                       C.c_void_p]),
+    "dg_hashgrid_encode_bwd_ordered": (C.c_int, [C.POINTER(GridDesc), C.POINTER(OrderDesc)] + [C.c_void_p] * 4 + [C.c_uint64] + [C.c_void_p] * 2
+                                       + [C.c_size_t, C.c_uint32, C.c_void_p]),
+    "dg_hashgrid_encode_fwd_ordered": (C.c_int, [C.POINTER(GridDesc), C.c_void_p, C.c_void_p, C.c_uint64, C.c_void_p, C.c_void_p]),
     "dg_mlp_weight_count": (C.c_size_t, [C.POINTER(MlpDesc)]),
     "dg_mlp_fwd": (C.c_int, [C.POINTER(MlpDesc), C.c_void_p, C.c_void_p, C.c_void_p, C.c_uint32, C.c_uint64, C.c_void_p,
                              C.c_void_p, C.c_void_p]),
@@ -80,6 +95,11 @@ _SIGNATURES = {
                                  C.c_void_p, C.c_void_p, C.c_float, C.c_void_p, C.c_void_p, C.c_void_p, C.c_size_t, C.c_void_p]),
     "dg_mlp_composite_fwd": (C.c_int, [C.POINTER(MlpDesc)] + [C.c_void_p] * 4 + [C.c_uint32, C.c_uint32] + [C.c_void_p] * 4 + [C.c_uint32]
                              + [C.c_void_p] * 4),
+    "dg_mlp_fwd_rows": (C.c_int, [C.POINTER(MlpDesc)] + [C.c_void_p] * 4 + [C.c_uint32, C.c_uint64] + [C.c_void_p] * 3),
+    "dg_mlp_composite_fwd_rows": (C.c_int, [C.POINTER(MlpDesc)] + [C.c_void_p] * 4 + [C.c_uint32, C.c_uint32] + [C.c_void_p] * 4 + [C.c_uint32]
+                                  + [C.c_void_p] * 4),
+    "dg_mlp_bwd_rows": (C.c_int, [C.POINTER(MlpDesc)] + [C.c_void_p] * 4 + [C.c_uint32, C.c_uint64, C.c_void_p, C.c_void_p, C.c_float, C.c_uint32]
+                        + [C.c_void_p] * 3 + [C.c_size_t, C.c_void_p]),
     "dg_appearance_rows": (C.c_int, [C.c_void_p, C.c_void_p, C.c_void_p, C.c_uint64, C.c_uint32, C.c_void_p, C.c_void_p]),
     "dg_composite_segment_fwd": (C.c_int, [C.c_void_p] * 3 + [C.c_uint32, C.c_uint32, C.c_void_p, C.c_void_p, C.c_uint32,
                                                               C.c_void_p, C.c_void_p, C.c_void_p]),
@@ -250,6 +270,49 @@ def dg_hashgrid_corner_indices(desc, u, N, idx):
     _check(lib().dg_hashgrid_corner_indices(C.byref(desc), _ptr(u, torch.float32), N, _ptr(idx, torch.int32), _stream()))
 
 
+# ------------------------------------------------------------------ samples in spatial order
+def dg_order_desc_init(grid, N):
+    order = OrderDesc()
+    _check(lib().dg_order_desc_init(C.byref(order), C.byref(grid), N))
+    return order
+
+
+def dg_order_workspace_bytes(order):
+    return int(lib().dg_order_workspace_bytes(C.byref(order)))
+
+
+def dg_order_pieces_words(order, N):
+    return int(lib().dg_order_pieces_words(C.byref(order), N))
+
+
+def dg_order_samples(order, u, N, ordered, pieces, ws):
+    assert u.numel() >= 3 * N and ordered.numel() >= 4 * N and pieces.numel() >= dg_order_pieces_words(order, N)
+    _check(lib().dg_order_samples(C.byref(order), _ptr(u, torch.float32), N, _ptr(ordered, torch.float32), _ptr(pieces, torch.int32), _ptr(ws),
+                                  ws.numel() * ws.element_size(), _stream()))
+
+
+def dg_hashgrid_encode_fwd_ordered(desc, table, ordered, N, feat):
+    assert ordered.numel() >= 4 * N and feat.numel() >= 32 * N
+    _check(lib().dg_hashgrid_encode_fwd_ordered(C.byref(desc), _ptr(table, torch.float32), _ptr(ordered, torch.float32), N,
+                                                _ptr(feat, torch.float16), _stream()))
+
+
+def dg_hashgrid_encode_bwd_ordered_workspace_bytes(desc, order, N):
+    return int(lib().dg_hashgrid_encode_bwd_ordered_workspace_bytes(C.byref(desc), C.byref(order), N))
+
+
+def dg_hashgrid_encode_bwd_ordered_count(desc, order, u, N, ws):
+    _check(lib().dg_hashgrid_encode_bwd_ordered_count(C.byref(desc), C.byref(order), _ptr(u, torch.float32), N, _ptr(ws),
+                                                      ws.numel() * ws.element_size(), _stream()))
+
+
+def dg_hashgrid_encode_bwd_ordered(desc, order, ordered, pieces, u, dfeat, N, dtable, ws, counted=False):
+    assert ordered.numel() >= 4 * N and pieces.numel() >= dg_order_pieces_words(order, N) and u.numel() >= 3 * N and dfeat.numel() >= 32 * N
+    _check(lib().dg_hashgrid_encode_bwd_ordered(C.byref(desc), C.byref(order), _ptr(ordered, torch.float32), _ptr(pieces, torch.int32),
+                                                _ptr(u, torch.float32), _ptr(dfeat, torch.float32), N, _ptr(dtable, torch.float32), _ptr(ws),
+                                                ws.numel() * ws.element_size(), 1 if counted else 0, _stream()))
+
+
 def dg_mlp_fwd(desc, weights, feat, dir_enc, S, N, sigma, rgb):
     _check(lib().dg_mlp_fwd(C.byref(desc), _ptr(weights, torch.float16), _ptr(feat, torch.float16),
                             _ptr(dir_enc, torch.float16), S, N, _ptr(sigma, torch.float32), _ptr(rgb, torch.float32),
@@ -402,22 +465,39 @@ def dg_appearance_rows(table, image_of_ray, index, n, out):
                                     n_app, _ptr(out, torch.float16), _stream()))
 
 
-def dg_mlp_fwd_app(desc, weights, feat, dir_enc, app, S, N, sigma, rgb):
+def _mlp_fwd_app(entry, desc, weights, feat, dir_enc, app, S, N, sigma, rgb):
     rows = -(-N // S)
     assert dir_enc.numel() >= rows * desc.n_dir and (app is None or app.numel() >= rows * desc.n_app)
-    _check(lib().dg_mlp_fwd_app(C.byref(desc), _ptr(weights, torch.float16), _ptr(feat, torch.float16), _ptr(dir_enc, torch.float16),
-                                _ptr(app, torch.float16, True), S, N, _ptr(sigma, torch.float32), _ptr(rgb, torch.float32), _stream()))
+    _check(entry(C.byref(desc), _ptr(weights, torch.float16), _ptr(feat, torch.float16), _ptr(dir_enc, torch.float16),
+                 _ptr(app, torch.float16, True), S, N, _ptr(sigma, torch.float32), _ptr(rgb, torch.float32), _stream()))
 
 
-def dg_mlp_composite_fwd(desc, weights, feat, dir_enc, app, S, n_seg, delta, t, seg_ray, seg_slot, k_max, Ck, Tk, Dk):
+def dg_mlp_fwd_app(desc, weights, feat, dir_enc, app, S, N, sigma, rgb):
+    _mlp_fwd_app(lib().dg_mlp_fwd_app, desc, weights, feat, dir_enc, app, S, N, sigma, rgb)
+
+
+def dg_mlp_fwd_rows(desc, weights, feat, dir_enc, app, S, N, sigma, rgb):
+    assert feat.numel() >= N * desc.n_feat
+    _mlp_fwd_app(lib().dg_mlp_fwd_rows, desc, weights, feat, dir_enc, app, S, N, sigma, rgb)
+
+
+def _mlp_composite_fwd(entry, desc, weights, feat, dir_enc, app, S, n_seg, delta, t, seg_ray, seg_slot, k_max, Ck, Tk, Dk):
     N = n_seg * S
     assert dir_enc.numel() >= n_seg * desc.n_dir and (app is None or app.numel() >= n_seg * desc.n_app)
     assert feat.numel() >= N * desc.n_feat and delta.numel() >= N and (t is None or t.numel() >= N)
     assert min(seg_ray.numel(), seg_slot.numel()) >= n_seg
-    _check(lib().dg_mlp_composite_fwd(C.byref(desc), _ptr(weights, torch.float16), _ptr(feat, torch.float16), _ptr(dir_enc, torch.float16),
-                                      _ptr(app, torch.float16, True), S, n_seg, _ptr(delta, torch.float32), _ptr(t, torch.float32, True),
-                                      _ptr(seg_ray, torch.int32), _ptr(seg_slot, torch.int32), k_max, _ptr(Ck, torch.float32),
-                                      _ptr(Tk, torch.float32), _ptr(Dk, torch.float32, True), _stream()))
+    _check(entry(C.byref(desc), _ptr(weights, torch.float16), _ptr(feat, torch.float16), _ptr(dir_enc, torch.float16),
+                 _ptr(app, torch.float16, True), S, n_seg, _ptr(delta, torch.float32), _ptr(t, torch.float32, True),
+                 _ptr(seg_ray, torch.int32), _ptr(seg_slot, torch.int32), k_max, _ptr(Ck, torch.float32),
+                 _ptr(Tk, torch.float32), _ptr(Dk, torch.float32, True), _stream()))
+
+
+def dg_mlp_composite_fwd(desc, weights, feat, dir_enc, app, S, n_seg, delta, t, seg_ray, seg_slot, k_max, Ck, Tk, Dk):
+    _mlp_composite_fwd(lib().dg_mlp_composite_fwd, desc, weights, feat, dir_enc, app, S, n_seg, delta, t, seg_ray, seg_slot, k_max, Ck, Tk, Dk)
+
+
+def dg_mlp_composite_fwd_rows(desc, weights, feat, dir_enc, app, S, n_seg, delta, t, seg_ray, seg_slot, k_max, Ck, Tk, Dk):
+    _mlp_composite_fwd(lib().dg_mlp_composite_fwd_rows, desc, weights, feat, dir_enc, app, S, n_seg, delta, t, seg_ray, seg_slot, k_max, Ck, Tk, Dk)
 
 
 def dg_mlp_bwd_app(desc, weights, feat, dir_enc, app, S, N, dsigma, drgb, loss_scale, dfeat, dW, ws):
@@ -428,3 +508,13 @@ def dg_mlp_bwd_app(desc, weights, feat, dir_enc, app, S, N, dsigma, drgb, loss_s
                                 _ptr(app, torch.float16, True), S, N, _ptr(dsigma, torch.float32), _ptr(drgb, torch.float32),
                                 loss_scale, _ptr(dfeat, torch.float32), _ptr(dW, torch.float32), _ptr(ws),
                                 ws.numel() * ws.element_size(), _stream()))
+
+
+def dg_mlp_bwd_rows(desc, weights, feat, dir_enc, app, S, N, dsigma, drgb, loss_scale, n_merged, dfeat, dW, ws):
+    rows = -(-N // S)
+    assert dir_enc.numel() >= rows * desc.n_dir and (app is None or app.numel() >= rows * desc.n_app)
+    assert dW.numel() >= dg_mlp_weight_count(desc) and min(feat.numel(), dfeat.numel()) >= N * desc.n_feat
+    _check(lib().dg_mlp_bwd_rows(C.byref(desc), _ptr(weights, torch.float16), _ptr(feat, torch.float16), _ptr(dir_enc, torch.float16),
+                                 _ptr(app, torch.float16, True), S, N, _ptr(dsigma, torch.float32), _ptr(drgb, torch.float32),
+                                 loss_scale, n_merged, _ptr(dfeat, torch.float32), _ptr(dW, torch.float32), _ptr(ws),
+                                 ws.numel() * ws.element_size(), _stream()))

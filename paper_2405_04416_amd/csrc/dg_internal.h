@@ -33,22 +33,32 @@ inline bool aligned(const void *p, size_t a) { return (reinterpret_cast<uintptr_
 
 constexpr int kWave = 64;
 
-// binned backward of the hash-grid encode (encode_bwd_binned.hip)
-size_t encode_bwd_binned_workspace_bytes(const dg_grid_desc *d, uint64_t N);
-int encode_bwd_binned(const dg_grid_desc *d, const float *u, const float *dfeat, uint64_t N, float *dtable, void *ws,
-                      size_t ws_bytes, bool counted, hipStream_t st);
-int encode_bwd_binned_count(const dg_grid_desc *d, const float *u, uint64_t N, void *ws, size_t ws_bytes, hipStream_t st);
+// argument check shared by the encode entry points (encode.hip)
+int check_grid_desc(const dg_grid_desc *d, const char *who);
 
+// binned backward of the hash-grid encode (encode_bwd_binned.hip)
+// from_level 0: all levels; else only levels from_level and up
+size_t encode_bwd_binned_workspace_bytes(const dg_grid_desc *d, uint32_t from_level, uint64_t N);
+int encode_bwd_binned(const char *who, const dg_grid_desc *d, uint32_t from_level, const float *u, const float *dfeat, uint64_t N,
+                      float *dtable, void *ws, size_t ws_bytes, bool counted, hipStream_t st);
+int encode_bwd_binned_count(const char *who, const dg_grid_desc *d, uint32_t from_level, const float *u, uint64_t N, void *ws,
+                            size_t ws_bytes, hipStream_t st);
+
+// ordered samples: levels below order->n_merged (encode_ordered.hip)
+int brick_bwd(const char *who, const dg_grid_desc *d, const dg_order_desc *order, const uint32_t *pieces, const void *ordered,
+              const float *dfeat, uint64_t N, float *dtable, hipStream_t st);
+
+// rows: features (and the gradient of levels below n_merged) as sample-major rows instead of planes.
 // matrix-core path of the 32-64-16 / (32 + n_app)-64-64-3 field MLPs (mlp_mfma.hip); n_app = 0, 16 or 48
 size_t mlp_mfma_workspace_bytes(uint64_t N, uint32_t n_app, uint32_t S);
 size_t mlp_mfma_weight_count(uint32_t n_app);
-void mlp_mfma_fwd(const void *weights, const void *feat, const void *dir_enc, const void *app, uint32_t n_app, uint32_t S,
+void mlp_mfma_fwd(const void *weights, const void *feat, bool rows, const void *dir_enc, const void *app, uint32_t n_app, uint32_t S,
                   uint64_t N, uint32_t act_c, float *sigma, float *rgb, hipStream_t st);
-void mlp_mfma_render(const void *weights, const void *feat, const void *dir_enc, const void *app, uint32_t n_app, uint32_t S,
+void mlp_mfma_render(const void *weights, const void *feat, bool rows, const void *dir_enc, const void *app, uint32_t n_app, uint32_t S,
                      uint32_t n_seg, uint32_t act_c, const float *delta, const float *t, const uint32_t *seg_ray,
                      const uint32_t *seg_slot, uint32_t k_max, float *Ck, float *Tk, float *Dk, hipStream_t st);
-void mlp_mfma_bwd(const void *weights, const void *feat, const void *dir_enc, const void *app, uint32_t n_app, uint32_t S,
-                  uint64_t N, uint32_t act_c, const float *dsigma, const float *drgb, float loss_scale, float *dfeat, float *dW,
+void mlp_mfma_bwd(const void *weights, const void *feat, bool rows, uint32_t n_merged, const void *dir_enc, const void *app, uint32_t n_app,
+                  uint32_t S, uint64_t N, uint32_t act_c, const float *dsigma, const float *drgb, float loss_scale, float *dfeat, float *dW,
                   void *ws, hipStream_t st);
 
 }  // namespace dg

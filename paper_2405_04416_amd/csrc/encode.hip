@@ -183,7 +183,18 @@ corner_index_kernel(dg_grid_desc g, const float *__restrict__ u, uint64_t N, uin
     for (int c = 0; c < 8; ++c) idx[t * 8 + c] = lv.offset + e[c];
 }
 
-int check_desc(const dg_grid_desc *d, const char *who)
+int grid_for(uint64_t N, uint32_t n_groups, uint32_t *n_blocks, const char *who)
+{
+    const uint64_t tiles = (N + kBlock - 1) / kBlock;
+    DG_REQUIRE(tiles * n_groups <= 0x7fffffffull, DG_ERR_UNSUPPORTED, "%s: N too large for one launch", who);
+    *n_blocks = (uint32_t)(tiles * n_groups);
+    return DG_OK;
+}
+
+}  // namespace
+
+namespace dg {
+int check_grid_desc(const dg_grid_desc *d, const char *who)
 {
     DG_REQUIRE(d, DG_ERR_ARG, "%s: null descriptor", who);
     DG_REQUIRE(d->n_levels >= 1 && d->n_levels <= DG_MAX_LEVELS && d->n_features == 2 && d->log2_T <= 24,
@@ -198,21 +209,12 @@ int check_desc(const dg_grid_desc *d, const char *who)
     DG_REQUIRE(d->offset[d->n_levels] == d->n_entries, DG_ERR_ARG, "%s: n_entries disagrees with offsets", who);
     return DG_OK;
 }
-
-int grid_for(uint64_t N, uint32_t n_groups, uint32_t *n_blocks, const char *who)
-{
-    const uint64_t tiles = (N + kBlock - 1) / kBlock;
-    DG_REQUIRE(tiles * n_groups <= 0x7fffffffull, DG_ERR_UNSUPPORTED, "%s: N too large for one launch", who);
-    *n_blocks = (uint32_t)(tiles * n_groups);
-    return DG_OK;
-}
-
-}  // namespace
+}  // namespace dg
 
 extern "C" int dg_hashgrid_encode_fwd(const dg_grid_desc *desc, const float *table, const float *u, uint64_t N,
                                       void *feat, uint32_t feat_dtype, void *stream)
 {
-    if (int rc = check_desc(desc, "dg_hashgrid_encode_fwd")) return rc;
+    if (int rc = dg::check_grid_desc(desc, "dg_hashgrid_encode_fwd")) return rc;
     DG_REQUIRE(feat_dtype == DG_F32 || feat_dtype == DG_F16, DG_ERR_ARG, "dg_hashgrid_encode_fwd: bad feat_dtype");
     if (N == 0) return DG_OK;
     DG_REQUIRE(table && u && feat, DG_ERR_ARG, "dg_hashgrid_encode_fwd: null pointer");
@@ -242,32 +244,32 @@ extern "C" int dg_hashgrid_encode_fwd(const dg_grid_desc *desc, const float *tab
 
 extern "C" size_t dg_hashgrid_encode_bwd_workspace_bytes(const dg_grid_desc *desc, uint64_t N)
 {
-    if (check_desc(desc, "dg_hashgrid_encode_bwd_workspace_bytes")) return 0;
-    return dg::encode_bwd_binned_workspace_bytes(desc, N);
+    if (dg::check_grid_desc(desc, "dg_hashgrid_encode_bwd_workspace_bytes")) return 0;
+    return dg::encode_bwd_binned_workspace_bytes(desc, 0, N);
 }
 
 extern "C" int dg_hashgrid_encode_bwd_count(const dg_grid_desc *desc, const float *u, uint64_t N, void *ws, size_t ws_bytes,
                                             void *stream)
 {
-    if (int rc = check_desc(desc, "dg_hashgrid_encode_bwd_count")) return rc;
+    if (int rc = dg::check_grid_desc(desc, "dg_hashgrid_encode_bwd_count")) return rc;
     if (N == 0) return DG_OK;
     DG_REQUIRE(u && ws, DG_ERR_ARG, "dg_hashgrid_encode_bwd_count: null pointer");
     DG_REQUIRE(dg::aligned(ws, 256), DG_ERR_ARG, "dg_hashgrid_encode_bwd_count: workspace must be 256-byte aligned");
-    return dg::encode_bwd_binned_count(desc, u, N, ws, ws_bytes, (hipStream_t)stream);
+    return dg::encode_bwd_binned_count("dg_hashgrid_encode_bwd_count", desc, 0, u, N, ws, ws_bytes, (hipStream_t)stream);
 }
 
 namespace {
 int encode_bwd(const dg_grid_desc *desc, const float *u, const float *dfeat, uint64_t N, float *dtable, void *ws, size_t ws_bytes,
                bool counted, void *stream)
 {
-    if (int rc = check_desc(desc, "dg_hashgrid_encode_bwd")) return rc;
+    if (int rc = dg::check_grid_desc(desc, "dg_hashgrid_encode_bwd")) return rc;
     if (N == 0) return DG_OK;
     DG_REQUIRE(u && dfeat && dtable, DG_ERR_ARG, "dg_hashgrid_encode_bwd: null pointer");
     DG_REQUIRE(dg::aligned(dfeat, 8) && dg::aligned(dtable, 8), DG_ERR_ARG, "dg_hashgrid_encode_bwd: misaligned pointer");
     DG_REQUIRE(ws || !counted, DG_ERR_ARG, "dg_hashgrid_encode_bwd_counted: the workspace that holds the counts is missing");
     if (ws) {
         DG_REQUIRE(dg::aligned(ws, 256), DG_ERR_ARG, "dg_hashgrid_encode_bwd: workspace must be 256-byte aligned");
-        return dg::encode_bwd_binned(desc, u, dfeat, N, dtable, ws, ws_bytes, counted, (hipStream_t)stream);
+        return dg::encode_bwd_binned("dg_hashgrid_encode_bwd", desc, 0, u, dfeat, N, dtable, ws, ws_bytes, counted, (hipStream_t)stream);
     }
     const uint32_t n_groups = desc->n_levels < 8 ? desc->n_levels : 8;
     uint32_t n_blocks;
@@ -292,7 +294,7 @@ extern "C" int dg_hashgrid_encode_bwd_counted(const dg_grid_desc *desc, const fl
 extern "C" int dg_hashgrid_corner_indices(const dg_grid_desc *desc, const float *u, uint64_t N, uint32_t *idx,
                                           void *stream)
 {
-    if (int rc = check_desc(desc, "dg_hashgrid_corner_indices")) return rc;
+    if (int rc = dg::check_grid_desc(desc, "dg_hashgrid_corner_indices")) return rc;
     if (N == 0) return DG_OK;
     DG_REQUIRE(u && idx, DG_ERR_ARG, "dg_hashgrid_corner_indices: null pointer");
     const uint64_t n_blocks = (N * desc->n_levels + kBlock - 1) / kBlock;

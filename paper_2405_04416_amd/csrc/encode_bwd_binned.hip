@@ -808,11 +808,12 @@ accumulate_kernel(dg_grid_desc g, Plan plan, const uint32_t *__restrict__ binbas
     }
 }
 
-Plan make_plan(const dg_grid_desc *d)
+// from_level > 0: the caller sums the levels below it (order.hip), there is no coarse prefix
+Plan make_plan(const dg_grid_desc *d, uint32_t from_level)
 {
     Plan p{};
-    uint32_t l = 0;
-    while (l < d->n_levels && d->offset[l + 1] <= kChunk) ++l;     // coarse prefix: tables that fit LDS together
+    uint32_t l = from_level;
+    while (from_level == 0 && l < d->n_levels && d->offset[l + 1] <= kChunk) ++l;     // coarse prefix: tables that fit LDS together
     p.first_level = l;
     uint32_t key = 0;
     for (; l < d->n_levels; ++l) {
@@ -868,10 +869,10 @@ uint64_t max_batch(const dg_grid_desc *d, const Plan &p)
 
 namespace dg {
 
-size_t encode_bwd_binned_workspace_bytes(const dg_grid_desc *d, uint64_t N)
+size_t encode_bwd_binned_workspace_bytes(const dg_grid_desc *d, uint32_t from_level, uint64_t N)
 {
     using namespace dg_encode_binned;
-    const Plan p = make_plan(d);
+    const Plan p = make_plan(d, from_level);
     if (p.n_keys == 0) return 256;
     uint64_t batch = (N + kTile - 1) / kTile * kTile;
     const uint64_t cap = max_batch(d, p);
@@ -894,9 +895,9 @@ struct Prepared {
     bool narrow;
 };
 
-int prepare(const char *who, const dg_grid_desc *d, uint64_t N, void *ws, size_t ws_bytes, Prepared &q)
+int prepare(const char *who, const dg_grid_desc *d, uint32_t from_level, uint64_t N, void *ws, size_t ws_bytes, Prepared &q)
 {
-    q.p = make_plan(d);
+    q.p = make_plan(d, from_level);
     // kernels that use more LDS than a launch gets by default: asked for once per process, whichever thread comes first
     static std::once_flag lds_once;
     static hipError_t lds_status = hipSuccess;
@@ -945,11 +946,10 @@ void launch_count(const Prepared &q, const dg_grid_desc *d, const float *u, uint
 
 }  // namespace
 
-int encode_bwd_binned_count(const dg_grid_desc *d, const float *u, uint64_t N, void *ws, size_t ws_bytes, hipStream_t st)
+int encode_bwd_binned_count(const char *who, const dg_grid_desc *d, uint32_t from_level, const float *u, uint64_t N, void *ws, size_t ws_bytes, hipStream_t st)
 {
-    const char *who = "dg_hashgrid_encode_bwd_count";
     Prepared q;
-    if (int rc = prepare(who, d, N, ws, ws_bytes, q)) return rc;
+    if (int rc = prepare(who, d, from_level, N, ws, ws_bytes, q)) return rc;
     if (q.p.n_keys == 0) return DG_OK;
     if (q.L.batch < N)
         return fail(DG_ERR_WORKSPACE, "%s: counting ahead needs a workspace that holds all %llu samples in one batch (it holds %llu)", who,
@@ -958,17 +958,16 @@ int encode_bwd_binned_count(const dg_grid_desc *d, const float *u, uint64_t N, v
     return launch_status(who);
 }
 
-int encode_bwd_binned(const dg_grid_desc *d, const float *u, const float *dfeat, uint64_t N, float *dtable, void *ws,
-                      size_t ws_bytes, bool counted, hipStream_t st)
+int encode_bwd_binned(const char *who, const dg_grid_desc *d, uint32_t from_level, const float *u, const float *dfeat, uint64_t N,
+                      float *dtable, void *ws, size_t ws_bytes, bool counted, hipStream_t st)
 {
-    const char *who = "dg_hashgrid_encode_bwd";
     Prepared q;
-    if (int rc = prepare(who, d, N, ws, ws_bytes, q)) return rc;
+    if (int rc = prepare(who, d, from_level, N, ws, ws_bytes, q)) return rc;
     const Plan &p = q.p;
     if (counted && p.n_keys && q.L.batch < N)
         return fail(DG_ERR_WORKSPACE, "%s: the workspace holds %llu of %llu samples: no counts from dg_hashgrid_encode_bwd_count can be in it",
                     who, (unsigned long long)q.L.batch, (unsigned long long)N);
-    if (p.first_level > 0) {
+    if (from_level == 0 && p.first_level > 0) {
         const uint64_t tiles = (N + kCoarseBlock - 1) / kCoarseBlock;
         const uint32_t grid = (uint32_t)(tiles < kCoarseGrid ? tiles : kCoarseGrid);
         coarse_kernel<<<grid, kCoarseBlock, 2 * d->offset[p.first_level] * sizeof(double), st>>>(

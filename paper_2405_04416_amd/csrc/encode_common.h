@@ -24,22 +24,37 @@ __device__ __forceinline__ LevelGeom level_of(const dg_grid_desc &g, uint32_t l)
     return v;
 }
 
-// cell and fractional position of a sample at one level; one fp32 multiply, no contraction
-__device__ __forceinline__ void locate(const LevelGeom &lv, const float u[3], uint32_t cell[3], float frac[3])
+// cell and fractional position along one axis: one fp32 multiply, no contraction
+__device__ __forceinline__ void locate_axis(float c, float scale, uint32_t last, uint32_t &cell, float &frac)
 {
 #pragma clang fp contract(off)
+    const float pos = c * scale;
+    uint32_t i = (uint32_t)floorf(pos);
+    i = i > last ? last : i;
+    cell = i;
+    frac = pos - (float)i;
+}
+
+// the same with the cell left in floating point
+__device__ __forceinline__ void locate_axis_float(float c, float scale, float last, float &cell, float &frac)
+{
+#pragma clang fp contract(off)
+    const float pos = c * scale;
+    cell = fminf(floorf(pos), last);
+    frac = pos - cell;
+}
+
+__device__ __forceinline__ float clamp_unit(float c)
+{
+    c = c >= 0.0f ? c : 0.0f;     // NaN lands on 0 as well
+    return c > 1.0f ? 1.0f : c;
+}
+
+// cell and fractional position of a sample at one level
+__device__ __forceinline__ void locate(const LevelGeom &lv, const float u[3], uint32_t cell[3], float frac[3])
+{
 #pragma unroll
-    for (int a = 0; a < 3; ++a) {
-        float c = u[a];
-        c = c >= 0.0f ? c : 0.0f;     // NaN lands on 0 as well
-        c = c > 1.0f ? 1.0f : c;
-        const float pos = c * lv.scale[a];
-        uint32_t i = (uint32_t)floorf(pos);
-        const uint32_t last = lv.res[a] - 1u;
-        i = i > last ? last : i;
-        cell[a] = i;
-        frac[a] = pos - (float)i;
-    }
+    for (int a = 0; a < 3; ++a) locate_axis(clamp_unit(u[a]), lv.scale[a], lv.res[a] - 1u, cell[a], frac[a]);
 }
 
 // entry indices (relative to the level) of the 8 corners, corner c = cx + 2cy + 4cz
@@ -59,6 +74,12 @@ __device__ __forceinline__ void corner_entries(const LevelGeom &lv, uint32_t mas
     }
 }
 
+// entry of one vertex (relative to the level)
+__device__ __forceinline__ uint32_t vertex_entry(const LevelGeom &lv, uint32_t mask, uint32_t x, uint32_t y, uint32_t z)
+{
+    return lv.dense ? x + (lv.res[0] + 1u) * (y + (lv.res[1] + 1u) * z) : (x ^ y * kPrimeY ^ z * kPrimeZ) & mask;
+}
+
 __device__ __forceinline__ void corner_weights(const float frac[3], float w[8])
 {
     const float wx[2] = {1.0f - frac[0], frac[0]}, wy[2] = {1.0f - frac[1], frac[1]}, wz[2] = {1.0f - frac[2], frac[2]};
@@ -71,15 +92,6 @@ __device__ __forceinline__ void corner_weights(const float frac[3], float w[8])
 __device__ __forceinline__ uint32_t from_lane_below(uint32_t v)
 {
     return (uint32_t)__builtin_amdgcn_update_dpp((int)v, (int)v, 0x138 /* wave_shr:1 */, 0xF, 0xF, false);
-}
-
-// length of the longest run of lanes that share a cell, from the mask of run heads (wavefront-uniform)
-__device__ __forceinline__ int longest_run(unsigned long long heads)
-{
-    unsigned long long inner = ~heads;      // lanes that continue a run
-    int len = 1;
-    while (inner) { inner &= inner << 1; ++len; }
-    return len;
 }
 
 // ---- segmented sum over the wavefront with DPP moves (no LDS traffic, no waits) ----------------------
@@ -106,11 +118,13 @@ __device__ __forceinline__ void seg_step(float (&vx)[8], float (&vy)[8], int &f)
 __device__ __forceinline__ void segmented_sum(float (&vx)[8], float (&vy)[8], bool head, unsigned long long heads)
 {
     int f = head ? 1 : 0;
-    const int longest = longest_run(heads);         // wavefront-uniform: steps a run of that length cannot need are skipped
-    if (longest > 1) seg_step<0x111, 0xF>(vx, vy, f);
-    if (longest > 2) seg_step<0x112, 0xF>(vx, vy, f);
-    if (longest > 4) seg_step<0x114, 0xF>(vx, vy, f);
-    if (longest > 8) seg_step<0x118, 0xF>(vx, vy, f);
+    // wavefront-uniform: steps that no run needs are skipped.  Bit i of the k-th mask: the lanes up to i continue a run for
+    // at least 1, 2, 4, 8 lanes, i.e. some run is longer than that.
+    const unsigned long long r1 = ~heads, r2 = r1 & r1 << 1, r4 = r2 & r2 << 2, r8 = r4 & r4 << 4;
+    if (r1) seg_step<0x111, 0xF>(vx, vy, f);
+    if (r2) seg_step<0x112, 0xF>(vx, vy, f);
+    if (r4) seg_step<0x114, 0xF>(vx, vy, f);
+    if (r8) seg_step<0x118, 0xF>(vx, vy, f);
     if (!((heads >> 16) & 1ull) || !((heads >> 48) & 1ull)) seg_step<0x142, 0xA>(vx, vy, f);
     if (!((heads >> 32) & 1ull)) seg_step<0x143, 0xC>(vx, vy, f);
 }

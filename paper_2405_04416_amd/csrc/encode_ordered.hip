@@ -1,0 +1,340 @@
+// Hash-grid encode of samples in spatial order (order.hip): forward gather into sample-major rows, and the table gradient
+// of the coarser levels.
+#include "encode_common.h"
+#include "order_common.h"
+#include <mutex>
+
+namespace {
+
+using namespace dg_encode;
+using namespace dg_order;
+
+constexpr int kBlock = 256;
+constexpr uint32_t kXcds = 8;
+
+// Two lanes per sample (lane 2i the four corners with cx = 0, lane 2i + 1 those with cx = 1: the two entries of an x-pair
+// nearly always share a cache line, which then costs one look-up), all 16 levels.  Consecutive workgroups of an XCD take
+// consecutive samples (workgroups are handed out to the XCDs in turn), so the lines that neighbours share meet in one L2.
+// The even lane keeps levels 0..7, the odd lane levels 8..15: each writes half of the sample's row.
+// Bound by the cache lines fetched past the L2 on the levels too fine for neighbours to share them (T = 2^24, 33.5 M samples:
+// levels 13..15 take 7.3 of 10.4 ms at 51 G lines/s, levels 0..9 1.7 ms), by instructions and vector-cache look-ups on the
+// others.  Against the gather in ray order, level after level: 33.5 M samples, T = 2^24 21.6 -> 10.4 ms; 19.8 M, T = 2^24
+// 12.3 -> 6.8; 13.3 M, T = 2^19 2.38 -> 1.49; scattered rows of 64 bytes instead of planes cost 0.8, 0.47 and 0.3 ms of it.
+__global__ void __launch_bounds__(kBlock)
+encode_fwd_ordered_kernel(dg_grid_desc g, const float2 *__restrict__ table, const float4 *__restrict__ ordered, uint64_t N,
+                          uint4 *__restrict__ feat, uint32_t blocks_per_xcd)
+{
+    const uint32_t block = (blockIdx.x % kXcds) * blocks_per_xcd + blockIdx.x / kXcds;
+    const uint64_t i = (uint64_t)block * (kBlock / 2) + threadIdx.x / 2;
+    const uint32_t cx = threadIdx.x & 1u;
+    if (i >= N) return;                                   // both lanes of a pair
+    const float4 s = ordered[i];
+    const float uu[3] = {s.x, s.y, s.z};
+    const uint32_t mask = (1u << g.log2_T) - 1u;
+    uint32_t out[8];
+#pragma unroll
+    for (int l = 0; l < 16; ++l) {
+        const LevelGeom lv = level_of(g, l);
+        uint32_t cell[3], e[4];
+        float frac[3];
+        locate(lv, uu, cell, frac);
+        if (lv.dense) {
+            const uint32_t nx = lv.res[0] + 1u, nxy = nx * (lv.res[1] + 1u);
+            const uint32_t base = cell[0] + cx + nx * cell[1] + nxy * cell[2];
+#pragma unroll
+            for (int k = 0; k < 4; ++k) e[k] = base + (k & 1) * nx + (k >> 1) * nxy;
+        } else {
+            const uint32_t hy0 = cell[1] * kPrimeY, hy1 = hy0 + kPrimeY;
+            const uint32_t hz0 = cell[2] * kPrimeZ, hz1 = hz0 + kPrimeZ;
+#pragma unroll
+            for (int k = 0; k < 4; ++k) e[k] = ((cell[0] + cx) ^ ((k & 1) ? hy1 : hy0) ^ ((k & 2) ? hz1 : hz0)) & mask;
+        }
+        const float wx = cx ? frac[0] : 1.0f - frac[0];
+        const float wy[2] = {1.0f - frac[1], frac[1]}, wz[2] = {1.0f - frac[2], frac[2]};
+        float2 v[4];
+#pragma unroll
+        for (int k = 0; k < 4; ++k) v[k] = table[(size_t)lv.offset + e[k]];
+        float f0 = 0.0f, f1 = 0.0f;
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+            const float w = wx * wy[k & 1] * wz[k >> 1];
+            f0 = fmaf(w, v[k].x, f0);
+            f1 = fmaf(w, v[k].y, f1);
+        }
+        // the partner's half: lanes swapped within pairs (quad_perm 1, 0, 3, 2)
+        f0 += __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(f0), 0xB1, 0xF, 0xF, true));
+        f1 += __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(f1), 0xB1, 0xF, 0xF, true));
+        const uint32_t f = __builtin_bit_cast(uint32_t, __floats2half2_rn(f0, f1));
+        if (l < 8) out[l] = f;
+        else out[l - 8] = cx ? f : out[l - 8];
+    }
+    uint4 *half_row = feat + (size_t)__float_as_uint(s.w) * 4 + 2 * cx;
+    half_row[0] = make_uint4(out[0], out[1], out[2], out[3]);
+    half_row[1] = make_uint4(out[4], out[5], out[6], out[7]);
+}
+
+// Table gradient of levels [0, n_merged): a workgroup takes a piece of a brick and sums all its contributions in LDS -- the
+// brick's vertices at those levels, 64-bit floating point, one plane per feature -- then adds the sums to the table
+// gradient, one global add per vertex the brick touches.
+// A lane takes up to kRun consecutive samples and keeps the eight corner sums of the cell it is in in registers; only when
+// the cell changes do they go to LDS.  What the lanes hold at the end is first summed over runs of lanes in the same cell.
+// 33.5 M samples, T = 2^24, levels 0..9: 3.35 ms, of which the gradient rows (one or two random lines per sample) take 1.0,
+// the LDS adds 1.15, the sums themselves 1.2; the same levels through the coarse prefix and the bins took 8 ms.  13.3 M
+// samples, T = 2^19, levels 0..9: 1.25 ms.  Two workgroups per compute unit (512 threads, at most 80 KB of sums) and two
+// samples per lane beat four samples per lane (4.3 ms) and one workgroup of 1024 (4.3 ms).
+struct Boxes { uint32_t n_merged, dim[kMaxMerged][3], first[kMaxMerged + 1]; };
+
+constexpr int kBrickBlock = 512, kRun = 2;
+
+// First cell of brick i's box along one axis: a hair (kBoxSlack of a cell) below the brick's edge.  A sample of brick i has
+// i <= u * n < i + 1 in fp32, so its cell, floor(u * scale) in fp32, differs from what the exact edges give by less than three
+// roundings of a position of at most kMaxMergedScale cells -- 1.5e-3 cells --, and a box of floor(scale / n + 2e-2) + 3
+// vertices (dg_order_desc_init) has room for every cell the brick's samples can be in.
+constexpr float kBoxSlack = 4e-3f;
+__device__ __forceinline__ uint32_t box_low(const Bricks &b, uint32_t i, int axis, float scale)
+{
+    const float edge = (float)i / b.per_unit[axis] * scale - kBoxSlack;
+    return edge > 0.0f ? (uint32_t)edge : 0u;
+}
+
+__device__ __forceinline__ uint32_t lane_value(uint32_t v, uint32_t lane) { return (uint32_t)__builtin_amdgcn_readlane((int)v, (int)lane); }
+__device__ __forceinline__ float lane_value(float v, uint32_t lane) { return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), (int)lane)); }
+
+// What the sums of a level need, held by lane `level` of every wavefront: fetched with register moves, so that the level
+// loop has no scalar loads, whose wait would also wait for the LDS adds under way.
+struct LevelLane {
+    float scale[3], last[3];                 // last: the last cell
+    float nx, nxy, origin;                   // strides of the box; slot = x + nx y + nxy z - origin (all exact: below 2^24)
+    uint32_t first, last_slot;               // first vertex of the box among the sums; last slot whose eight corners lie in it
+};
+
+// the eight corner sums of the cell whose corner 0 is vertex d of the box
+__device__ __forceinline__ void add_to_box(double *d, uint32_t nx, uint32_t nxy, uint32_t plane, const float (&vx)[8], const float (&vy)[8])
+{
+#pragma unroll
+    for (int c = 0; c < 8; ++c) {
+        double *e = d + (c & 1) + ((c >> 1) & 1) * nx + (c >> 2) * nxy;
+        __hip_atomic_fetch_add(e, (double)vx[c], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+        __hip_atomic_fetch_add(e + plane, (double)vy[c], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+    }
+}
+
+__global__ void __launch_bounds__(kBrickBlock)
+brick_bwd_kernel(dg_grid_desc g, Bricks b, Boxes boxes, const uint2 *__restrict__ pieces, const float4 *__restrict__ ordered,
+                 const float4 *__restrict__ dfeat, float *__restrict__ dtable)
+{
+    extern __shared__ double sums[];
+    if (blockIdx.x >= pieces[0].x) return;
+    const uint2 piece = pieces[1 + blockIdx.x];
+    const uint32_t begin = piece.y, n = pieces[2 + blockIdx.x].y - begin;
+    const uint32_t n_vertices = boxes.first[boxes.n_merged];
+    for (uint32_t i = threadIdx.x; i < 2 * n_vertices; i += kBrickBlock) sums[i] = 0.0;
+    const uint32_t brick[3] = {piece.x % b.n[0], piece.x / b.n[0] % b.n[1], piece.x / (b.n[0] * b.n[1])};
+    const uint32_t mask = (1u << g.log2_T) - 1u;
+    const int lane = threadIdx.x % dg::kWave;
+    const uint32_t pairs = boxes.n_merged / 2;
+    LevelLane mine;
+    {
+        const uint32_t l = min((uint32_t)lane, boxes.n_merged - 1u);
+#pragma unroll
+        for (int a = 0; a < 3; ++a) {
+            mine.scale[a] = g.scale[l][a];
+            mine.last[a] = (float)(g.res[l][a] - 1u);
+        }
+        const uint32_t nx = boxes.dim[l][0], nxy = nx * boxes.dim[l][1];
+        mine.nx = (float)nx;
+        mine.nxy = (float)nxy;
+        mine.origin = (float)(box_low(b, brick[0], 0, mine.scale[0]) + nx * box_low(b, brick[1], 1, mine.scale[1]) + nxy * box_low(b, brick[2], 2, mine.scale[2]));
+        mine.first = boxes.first[l];
+        mine.last_slot = boxes.first[l + 1] - boxes.first[l] - 2u - nx - nxy;
+    }
+    __syncthreads();
+    for (uint32_t base = 0; base < n;) {
+        const uint32_t run = min((uint32_t)kRun, (n - base + kBrickBlock - 1u) / kBrickBlock);      // samples per lane
+        const uint32_t i0 = base + threadIdx.x * run;
+        base += run * kBrickBlock;
+        if (i0 - lane * run >= n) break;                              // the whole wavefront is past the end
+        float uu[kRun][3];
+        float4 grad[kRun][kMaxMerged / 2];
+#pragma unroll
+        for (int k = 0; k < kRun; ++k)
+            if ((uint32_t)k < run) {
+                const float4 s = ordered[begin + min(i0 + k, n - 1u)];
+                uu[k][0] = s.x; uu[k][1] = s.y; uu[k][2] = s.z;
+                const float4 *row = dfeat + (size_t)__float_as_uint(s.w) * pairs;
+#pragma unroll
+                for (int q = 0; q < kMaxMerged / 2; ++q)
+                    if ((uint32_t)q < pairs) grad[k][q] = row[q];
+                if (i0 + k >= n)
+#pragma unroll
+                    for (int q = 0; q < kMaxMerged / 2; ++q) grad[k][q] = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+#pragma unroll
+                for (int a = 0; a < 3; ++a) uu[k][a] = clamp_unit(uu[k][a]);
+            }
+        // Two levels per turn; after it the gradients move down by one place, so that every register index is a constant and
+        // the code of one turn serves all levels (all levels written out do not fit the instruction cache).
+#pragma unroll 1
+        for (uint32_t q = 0; q < pairs; ++q) {
+#pragma unroll
+            for (int which = 0; which < 2; ++which) {
+                const uint32_t l = 2 * q + which;
+                float scale[3], last[3];
+#pragma unroll
+                for (int a = 0; a < 3; ++a) { scale[a] = lane_value(mine.scale[a], l); last[a] = lane_value(mine.last[a], l); }
+                const float fnx = lane_value(mine.nx, l), fnxy = lane_value(mine.nxy, l), origin = lane_value(mine.origin, l);
+                const uint32_t nx = (uint32_t)fnx, nxy = (uint32_t)fnxy, last_slot = lane_value(mine.last_slot, l);
+                double *box = sums + lane_value(mine.first, l);
+                float vx[8], vy[8];
+                uint32_t slot = 0;                                    // of the cell whose sums vx, vy are
+#pragma unroll
+                for (int k = 0; k < kRun; ++k)
+                    if ((uint32_t)k < run) {
+                        const float gx = which ? grad[k][0].z : grad[k][0].x, gy = which ? grad[k][0].w : grad[k][0].y;
+                        float cell[3], w1[3], w0[3];
+#pragma unroll
+                        for (int a = 0; a < 3; ++a) {
+                            locate_axis_float(uu[k][a], scale[a], last[a], cell[a], w1[a]);
+                            w0[a] = 1.0f - w1[a];
+                        }
+                        // whole numbers below 2^24: exact in fp32
+                        const uint32_t now = min((uint32_t)__builtin_fmaf(cell[2], fnxy, __builtin_fmaf(cell[1], fnx, cell[0] - origin)), last_slot);
+                        if (k > 0 && now != slot) {
+                            add_to_box(box + slot, nx, nxy, n_vertices, vx, vy);
+#pragma unroll
+                            for (int c = 0; c < 8; ++c) { vx[c] = 0.0f; vy[c] = 0.0f; }
+                        }
+                        slot = now;
+                        const float px[2] = {gx * w0[0], gx * w1[0]}, py[2] = {gy * w0[0], gy * w1[0]};
+                        const float yz[4] = {w0[1] * w0[2], w1[1] * w0[2], w0[1] * w1[2], w1[1] * w1[2]};
+#pragma unroll
+                        for (int c = 0; c < 8; ++c) {
+                            vx[c] = k > 0 ? __builtin_fmaf(px[c & 1], yz[c >> 1], vx[c]) : px[c & 1] * yz[c >> 1];
+                            vy[c] = k > 0 ? __builtin_fmaf(py[c & 1], yz[c >> 1], vy[c]) : py[c & 1] * yz[c >> 1];
+                        }
+                    }
+                // the exchange comes first: every lane takes part in it
+                const uint32_t below = from_lane_below(slot);
+                const bool head = lane == 0 || below != slot;
+                const unsigned long long heads = __ballot(head);
+                if (__popcll(heads) < dg::kWave) segmented_sum(vx, vy, head, heads);
+                const bool tail = lane == dg::kWave - 1 || ((heads >> ((lane + 1) & 63)) & 1ull);
+                if (tail) add_to_box(box + slot, nx, nxy, n_vertices, vx, vy);
+            }
+#pragma unroll
+            for (int k = 0; k < kRun; ++k)
+#pragma unroll
+                for (int j = 0; j + 1 < kMaxMerged / 2; ++j) grad[k][j] = grad[k][j + 1];
+        }
+    }
+    __syncthreads();
+    for (uint32_t l = 0; l < boxes.n_merged; ++l) {
+        const LevelGeom lv = level_of(g, l);
+        uint32_t low[3];
+#pragma unroll
+        for (int a = 0; a < 3; ++a) low[a] = box_low(b, brick[a], a, lv.scale[a]);
+        const uint32_t nx = boxes.dim[l][0], ny = boxes.dim[l][1], count = boxes.first[l + 1] - boxes.first[l];
+        float *dst = dtable + 2 * (size_t)lv.offset;
+        // neighbouring lanes add the two features of neighbouring vertices: whole cache lines per instruction
+        for (uint32_t i = threadIdx.x; i < 2 * count; i += kBrickBlock) {
+            const uint32_t v = i >> 1, f = i & 1u;
+            const float sum = (float)sums[f * n_vertices + boxes.first[l] + v];
+            if (sum != 0.0f) unsafeAtomicAdd(dst + 2 * (size_t)vertex_entry(lv, mask, low[0] + v % nx, low[1] + v / nx % ny, low[2] + v / (nx * ny)) + f, sum);
+        }
+    }
+}
+
+}  // namespace
+
+namespace dg {
+
+// the merged levels of the ordered backward pass (N samples; dfeat rows of 2 * n_merged floats)
+int brick_bwd(const char *who, const dg_grid_desc *d, const dg_order_desc *order, const uint32_t *pieces, const void *ordered, const float *dfeat,
+              uint64_t N, float *dtable, hipStream_t st)
+{
+    static std::once_flag lds_once;
+    static hipError_t lds_status = hipSuccess;
+    std::call_once(lds_once, [] {
+        lds_status = hipFuncSetAttribute(reinterpret_cast<const void *>(&brick_bwd_kernel), hipFuncAttributeMaxDynamicSharedMemorySize,
+                                         (int)(kMaxBoxVertices * 2 * sizeof(double)));
+    });
+    if (lds_status != hipSuccess) return fail(DG_ERR_HIP, "%s: cannot reserve LDS: %s", who, hipGetErrorString(lds_status));
+    Boxes boxes{};
+    boxes.n_merged = order->n_merged;
+    for (uint32_t l = 0; l < order->n_merged; ++l) {
+        for (int a = 0; a < 3; ++a) boxes.dim[l][a] = order->box[l][a];
+        boxes.first[l + 1] = order->box_first[l + 1];
+    }
+    const size_t lds = (size_t)boxes.first[boxes.n_merged] * 2 * sizeof(double);
+    brick_bwd_kernel<<<(uint32_t)piece_bound(order->total, N), kBrickBlock, lds, st>>>(
+        *d, bricks_of(order), boxes, (const uint2 *)pieces, (const float4 *)ordered, (const float4 *)dfeat, dtable);
+    return launch_status(who);
+}
+
+}  // namespace dg
+
+extern "C" int dg_hashgrid_encode_fwd_ordered(const dg_grid_desc *desc, const float *table, const void *ordered, uint64_t N,
+                                              void *feat, void *stream)
+{
+    const char *who = "dg_hashgrid_encode_fwd_ordered";
+    if (int rc = dg::check_grid_desc(desc, who)) return rc;
+    DG_REQUIRE(desc->n_levels == 16, DG_ERR_UNSUPPORTED, "%s: needs 16 levels", who);
+    if (N == 0) return DG_OK;
+    DG_REQUIRE(table && ordered && feat, DG_ERR_ARG, "%s: null pointer", who);
+    DG_REQUIRE(dg::aligned(table, 8) && dg::aligned(ordered, 16) && dg::aligned(feat, 16), DG_ERR_ARG, "%s: misaligned pointer", who);
+    const uint64_t blocks = (2 * N + kBlock - 1) / kBlock, per_xcd = (blocks + kXcds - 1) / kXcds;
+    DG_REQUIRE(per_xcd * kXcds <= 0x7fffffffull, DG_ERR_UNSUPPORTED, "%s: N too large for one launch", who);
+    encode_fwd_ordered_kernel<<<(uint32_t)(per_xcd * kXcds), kBlock, 0, (hipStream_t)stream>>>(*desc, (const float2 *)table, (const float4 *)ordered, N,
+                                                                                              (uint4 *)feat, (uint32_t)per_xcd);
+    return dg::launch_status(who);
+}
+
+namespace {
+
+int ordered_ok(const char *who, const dg_grid_desc *desc, const dg_order_desc *order)
+{
+    if (int rc = dg::check_grid_desc(desc, who)) return rc;
+    if (int rc = order_ok(order, who)) return rc;
+    DG_REQUIRE(desc->n_levels == 16 && order->n_merged <= kMaxMerged && order->n_merged % 2 == 0 && order->n_merged > 0, DG_ERR_UNSUPPORTED,
+               "%s: needs 16 levels and at least two merged ones", who);
+    DG_REQUIRE(order->box_first[order->n_merged] <= kMaxBoxVertices, DG_ERR_ARG, "%s: descriptor not initialised by dg_order_desc_init", who);
+    return DG_OK;
+}
+
+int bwd_ordered(const char *who, const dg_grid_desc *desc, const dg_order_desc *order, const void *ordered, const uint32_t *pieces, const float *u,
+                const float *dfeat, uint64_t N, float *dtable, void *ws, size_t ws_bytes, bool counted, void *stream)
+{
+    if (int rc = ordered_ok(who, desc, order)) return rc;
+    if (N == 0) return DG_OK;
+    DG_REQUIRE(ordered && pieces && u && dfeat && dtable && ws, DG_ERR_ARG, "%s: null pointer", who);
+    DG_REQUIRE(dg::aligned(ordered, 16) && dg::aligned(pieces, 8) && dg::aligned(dfeat, 16) && dg::aligned(dtable, 8) && dg::aligned(ws, 256), DG_ERR_ARG,
+               "%s: misaligned pointer", who);
+    // the rows of the merged levels take the place of those levels' planes: plane l of the others lies where it always does
+    if (int rc = dg::brick_bwd(who, desc, order, pieces, ordered, dfeat, N, dtable, (hipStream_t)stream)) return rc;
+    return dg::encode_bwd_binned(who, desc, order->n_merged, u, dfeat, N, dtable, ws, ws_bytes, counted, (hipStream_t)stream);
+}
+
+}  // namespace
+
+extern "C" size_t dg_hashgrid_encode_bwd_ordered_workspace_bytes(const dg_grid_desc *desc, const dg_order_desc *order, uint64_t N)
+{
+    if (ordered_ok("dg_hashgrid_encode_bwd_ordered_workspace_bytes", desc, order)) return 0;
+    return dg::encode_bwd_binned_workspace_bytes(desc, order->n_merged, N);
+}
+
+extern "C" int dg_hashgrid_encode_bwd_ordered_count(const dg_grid_desc *desc, const dg_order_desc *order, const float *u, uint64_t N, void *ws,
+                                                    size_t ws_bytes, void *stream)
+{
+    const char *who = "dg_hashgrid_encode_bwd_ordered_count";
+    if (int rc = ordered_ok(who, desc, order)) return rc;
+    if (N == 0) return DG_OK;
+    DG_REQUIRE(u && ws, DG_ERR_ARG, "%s: null pointer", who);
+    DG_REQUIRE(dg::aligned(ws, 256), DG_ERR_ARG, "%s: workspace must be 256-byte aligned", who);
+    return dg::encode_bwd_binned_count(who, desc, order->n_merged, u, N, ws, ws_bytes, (hipStream_t)stream);
+}
+
+extern "C" int dg_hashgrid_encode_bwd_ordered(const dg_grid_desc *desc, const dg_order_desc *order, const void *ordered, const uint32_t *pieces,
+                                              const float *u, const float *dfeat, uint64_t N, float *dtable, void *ws, size_t ws_bytes,
+                                              uint32_t counted, void *stream)
+{
+    return bwd_ordered("dg_hashgrid_encode_bwd_ordered", desc, order, ordered, pieces, u, dfeat, N, dtable, ws, ws_bytes, counted != 0, stream);
+}

@@ -239,6 +239,85 @@ int which_net(const dg_mlp_desc *m, const char *who)
 
 }  // namespace
 
+namespace {
+
+// rows: sample-major features (dg_hashgrid_encode_fwd_ordered); only the matrix-core networks take them
+int mlp_fwd(const char *who, const dg_mlp_desc *desc, const void *weights, const void *feat, bool rows, const void *dir_enc, const void *app, uint32_t S,
+            uint64_t N, float *sigma, float *rgb, void *stream)
+{
+    const int net = which_net(desc, who);
+    if (net < 0) return net;
+    DG_REQUIRE(!rows || net == 1, DG_ERR_UNSUPPORTED, "%s: only the 32-64-16 / 64-64-3 networks take feature rows", who);
+    DG_REQUIRE(S >= 1, DG_ERR_ARG, "%s: S must be >= 1", who);
+    if (N == 0) return DG_OK;
+    DG_REQUIRE(weights && feat && dir_enc && sigma && rgb, DG_ERR_ARG, "%s: null pointer", who);
+    DG_REQUIRE(desc->n_app == 0 || (app && dg::aligned(app, 16)), DG_ERR_ARG, "%s: appearance rows missing or not 16-byte aligned", who);
+    const uint64_t n_blocks = (N + kFwdBlock - 1) / kFwdBlock;
+    DG_REQUIRE(n_blocks <= 0x7fffffffull, DG_ERR_UNSUPPORTED, "%s: N too large", who);
+    hipStream_t st = (hipStream_t)stream;
+    if (net == 1) {
+        DG_REQUIRE(dg::aligned(feat, rows ? 16 : 4) && dg::aligned(dir_enc, 16), DG_ERR_ARG, "%s: feat must be %d-byte, dir_enc 16-byte aligned", who,
+                   rows ? 16 : 4);
+        dg::mlp_mfma_fwd(weights, feat, rows, dir_enc, app, desc->n_app, S, N, desc->act_c, sigma, rgb, st);
+    } else
+        mlp_fwd_kernel<NetTiny><<<(uint32_t)n_blocks, kFwdBlock, 0, st>>>((const __half *)weights, (const __half *)feat,
+                                                                           (const __half *)dir_enc, S, N, desc->act_c, sigma, rgb);
+    return dg::launch_status(who);
+}
+
+int mlp_composite_fwd(const char *who, const dg_mlp_desc *desc, const void *weights, const void *feat, bool rows, const void *dir_enc, const void *app,
+                      uint32_t S, uint32_t n_seg, const float *delta, const float *t, const uint32_t *seg_ray, const uint32_t *seg_slot,
+                      uint32_t k_max, float *Ck, float *Tk, float *Dk, void *stream)
+{
+    const int net = which_net(desc, who);
+    if (net < 0) return net;
+    DG_REQUIRE(net == 1, DG_ERR_UNSUPPORTED, "%s: only the 32-64-16 / 64-64-3 networks have a fused kernel", who);
+    DG_REQUIRE(S >= 1 && S <= 64, DG_ERR_UNSUPPORTED, "%s: S=%u outside 1..64 (one wavefront renders a segment)", who, S);
+    DG_REQUIRE(k_max >= 1, DG_ERR_ARG, "%s: k_max must be >= 1", who);
+    if (n_seg == 0) return DG_OK;
+    DG_REQUIRE(weights && feat && dir_enc && delta && seg_ray && seg_slot && Ck && Tk, DG_ERR_ARG, "%s: null pointer", who);
+    DG_REQUIRE((t == nullptr) == (Dk == nullptr), DG_ERR_ARG, "%s: t and Dk go together", who);
+    DG_REQUIRE(desc->n_app == 0 || (app && dg::aligned(app, 16)), DG_ERR_ARG, "%s: appearance rows missing or not 16-byte aligned", who);
+    DG_REQUIRE(dg::aligned(feat, rows ? 16 : 4) && dg::aligned(dir_enc, 16), DG_ERR_ARG, "%s: feat must be %d-byte, dir_enc 16-byte aligned", who,
+               rows ? 16 : 4);
+    dg::mlp_mfma_render(weights, feat, rows, dir_enc, app, desc->n_app, S, n_seg, desc->act_c, delta, t, seg_ray, seg_slot, k_max, Ck, Tk, Dk,
+                        (hipStream_t)stream);
+    return dg::launch_status(who);
+}
+
+int mlp_bwd(const char *who, const dg_mlp_desc *desc, const void *weights, const void *feat, bool rows, uint32_t n_merged, const void *dir_enc,
+            const void *app, uint32_t S, uint64_t N, const float *dsigma, const float *drgb, float loss_scale, float *dfeat, float *dW, void *ws,
+            size_t ws_bytes, void *stream)
+{
+    const int net = which_net(desc, who);
+    if (net < 0) return net;
+    DG_REQUIRE(!rows || net == 1, DG_ERR_UNSUPPORTED, "%s: only the 32-64-16 / 64-64-3 networks take feature rows", who);
+    DG_REQUIRE(n_merged % 2 == 0 && n_merged <= desc->n_feat / 2, DG_ERR_ARG, "%s: n_merged=%u must be even and at most the number of levels", who, n_merged);
+    DG_REQUIRE(S >= 1 && loss_scale > 0.0f, DG_ERR_ARG, "%s: S >= 1 and loss_scale > 0 required", who);
+    if (N == 0) return DG_OK;
+    DG_REQUIRE(weights && feat && dir_enc && dsigma && drgb && dfeat && dW, DG_ERR_ARG, "%s: null pointer", who);
+    DG_REQUIRE(desc->n_app == 0 || (app && dg::aligned(app, 16)), DG_ERR_ARG, "%s: appearance rows missing or not 16-byte aligned", who);
+    DG_REQUIRE(ws && ws_bytes >= dg_mlp_bwd_app_workspace_bytes(desc, N, S), DG_ERR_WORKSPACE, "%s: workspace %zu < %zu bytes", who, ws_bytes,
+               dg_mlp_bwd_app_workspace_bytes(desc, N, S));
+    DG_REQUIRE(dg::aligned(ws, 256), DG_ERR_ARG, "%s: workspace must be 256-byte aligned", who);
+    const uint64_t n_tiles = (N + kBwdBlock - 1) / kBwdBlock;
+    const uint32_t grid = (uint32_t)(n_tiles < kBwdGrid ? n_tiles : kBwdGrid);
+    const uint32_t n_w = (uint32_t)dg_mlp_weight_count(desc);
+    hipStream_t st = (hipStream_t)stream;
+    if (net == 1) {
+        DG_REQUIRE(dg::aligned(feat, rows ? 16 : 4) && dg::aligned(dir_enc, 16) && dg::aligned(dfeat, rows ? 16 : 8), DG_ERR_ARG,
+                   "%s: feat must be %d-byte, dfeat %d-byte, dir_enc 16-byte aligned", who, rows ? 16 : 4, rows ? 16 : 8);
+        dg::mlp_mfma_bwd(weights, feat, rows, n_merged, dir_enc, app, desc->n_app, S, N, desc->act_c, dsigma, drgb, loss_scale, dfeat, dW, ws, st);
+        return dg::launch_status(who);
+    }
+    mlp_bwd_kernel<NetTiny><<<grid, kBwdBlock, 0, st>>>((const __half *)weights, (const __half *)feat, (const __half *)dir_enc,
+                                                        S, N, desc->act_c, dsigma, drgb, loss_scale, dfeat, (float *)ws);
+    fold_partials_kernel<<<(n_w + 255) / 256, 256, 0, st>>>((const float *)ws, grid, n_w, 1.0f / loss_scale, dW);
+    return dg::launch_status(who);
+}
+
+}  // namespace
+
 extern "C" int dg_mlp_fwd(const dg_mlp_desc *desc, const void *weights, const void *feat, const void *dir_enc,
                           uint32_t S, uint64_t N, float *sigma, float *rgb, void *stream)
 {
@@ -249,22 +328,13 @@ extern "C" int dg_mlp_fwd(const dg_mlp_desc *desc, const void *weights, const vo
 extern "C" int dg_mlp_fwd_app(const dg_mlp_desc *desc, const void *weights, const void *feat, const void *dir_enc,
                               const void *app, uint32_t S, uint64_t N, float *sigma, float *rgb, void *stream)
 {
-    const int net = which_net(desc, "dg_mlp_fwd");
-    if (net < 0) return net;
-    DG_REQUIRE(S >= 1, DG_ERR_ARG, "dg_mlp_fwd: S must be >= 1");
-    if (N == 0) return DG_OK;
-    DG_REQUIRE(weights && feat && dir_enc && sigma && rgb, DG_ERR_ARG, "dg_mlp_fwd: null pointer");
-    DG_REQUIRE(desc->n_app == 0 || (app && dg::aligned(app, 16)), DG_ERR_ARG, "dg_mlp_fwd: appearance rows missing or not 16-byte aligned");
-    const uint64_t n_blocks = (N + kFwdBlock - 1) / kFwdBlock;
-    DG_REQUIRE(n_blocks <= 0x7fffffffull, DG_ERR_UNSUPPORTED, "dg_mlp_fwd: N too large");
-    hipStream_t st = (hipStream_t)stream;
-    if (net == 1) {
-        DG_REQUIRE(dg::aligned(feat, 4) && dg::aligned(dir_enc, 16), DG_ERR_ARG, "dg_mlp_fwd: feat must be 4-byte, dir_enc 16-byte aligned");
-        dg::mlp_mfma_fwd(weights, feat, dir_enc, app, desc->n_app, S, N, desc->act_c, sigma, rgb, st);
-    } else
-        mlp_fwd_kernel<NetTiny><<<(uint32_t)n_blocks, kFwdBlock, 0, st>>>((const __half *)weights, (const __half *)feat,
-                                                                           (const __half *)dir_enc, S, N, desc->act_c, sigma, rgb);
-    return dg::launch_status("dg_mlp_fwd");
+    return mlp_fwd("dg_mlp_fwd", desc, weights, feat, false, dir_enc, app, S, N, sigma, rgb, stream);
+}
+
+extern "C" int dg_mlp_fwd_rows(const dg_mlp_desc *desc, const void *weights, const void *feat, const void *dir_enc,
+                               const void *app, uint32_t S, uint64_t N, float *sigma, float *rgb, void *stream)
+{
+    return mlp_fwd("dg_mlp_fwd_rows", desc, weights, feat, true, dir_enc, app, S, N, sigma, rgb, stream);
 }
 
 extern "C" int dg_mlp_composite_fwd(const dg_mlp_desc *desc, const void *weights, const void *feat, const void *dir_enc,
@@ -272,19 +342,17 @@ extern "C" int dg_mlp_composite_fwd(const dg_mlp_desc *desc, const void *weights
                                     const uint32_t *seg_ray, const uint32_t *seg_slot, uint32_t k_max, float *Ck, float *Tk,
                                     float *Dk, void *stream)
 {
-    const int net = which_net(desc, "dg_mlp_composite_fwd");
-    if (net < 0) return net;
-    DG_REQUIRE(net == 1, DG_ERR_UNSUPPORTED, "dg_mlp_composite_fwd: only the 32-64-16 / 64-64-3 networks have a fused kernel");
-    DG_REQUIRE(S >= 1 && S <= 64, DG_ERR_UNSUPPORTED, "dg_mlp_composite_fwd: S=%u outside 1..64 (one wavefront renders a segment)", S);
-    DG_REQUIRE(k_max >= 1, DG_ERR_ARG, "dg_mlp_composite_fwd: k_max must be >= 1");
-    if (n_seg == 0) return DG_OK;
-    DG_REQUIRE(weights && feat && dir_enc && delta && seg_ray && seg_slot && Ck && Tk, DG_ERR_ARG, "dg_mlp_composite_fwd: null pointer");
-    DG_REQUIRE((t == nullptr) == (Dk == nullptr), DG_ERR_ARG, "dg_mlp_composite_fwd: t and Dk go together");
-    DG_REQUIRE(desc->n_app == 0 || (app && dg::aligned(app, 16)), DG_ERR_ARG, "dg_mlp_composite_fwd: appearance rows missing or not 16-byte aligned");
-    DG_REQUIRE(dg::aligned(feat, 4) && dg::aligned(dir_enc, 16), DG_ERR_ARG, "dg_mlp_composite_fwd: feat must be 4-byte, dir_enc 16-byte aligned");
-    dg::mlp_mfma_render(weights, feat, dir_enc, app, desc->n_app, S, n_seg, desc->act_c, delta, t, seg_ray, seg_slot, k_max, Ck, Tk, Dk,
-                        (hipStream_t)stream);
-    return dg::launch_status("dg_mlp_composite_fwd");
+    return mlp_composite_fwd("dg_mlp_composite_fwd", desc, weights, feat, false, dir_enc, app, S, n_seg, delta, t, seg_ray, seg_slot, k_max, Ck, Tk, Dk,
+                             stream);
+}
+
+extern "C" int dg_mlp_composite_fwd_rows(const dg_mlp_desc *desc, const void *weights, const void *feat, const void *dir_enc,
+                                         const void *app, uint32_t S, uint32_t n_seg, const float *delta, const float *t,
+                                         const uint32_t *seg_ray, const uint32_t *seg_slot, uint32_t k_max, float *Ck, float *Tk,
+                                         float *Dk, void *stream)
+{
+    return mlp_composite_fwd("dg_mlp_composite_fwd_rows", desc, weights, feat, true, dir_enc, app, S, n_seg, delta, t, seg_ray, seg_slot, k_max, Ck, Tk,
+                             Dk, stream);
 }
 
 extern "C" size_t dg_mlp_bwd_workspace_bytes(const dg_mlp_desc *desc, uint64_t N)
@@ -313,27 +381,12 @@ extern "C" int dg_mlp_bwd_app(const dg_mlp_desc *desc, const void *weights, cons
                               const void *app, uint32_t S, uint64_t N, const float *dsigma, const float *drgb,
                               float loss_scale, float *dfeat, float *dW, void *ws, size_t ws_bytes, void *stream)
 {
-    const int net = which_net(desc, "dg_mlp_bwd");
-    if (net < 0) return net;
-    DG_REQUIRE(S >= 1 && loss_scale > 0.0f, DG_ERR_ARG, "dg_mlp_bwd: S >= 1 and loss_scale > 0 required");
-    if (N == 0) return DG_OK;
-    DG_REQUIRE(weights && feat && dir_enc && dsigma && drgb && dfeat && dW, DG_ERR_ARG, "dg_mlp_bwd: null pointer");
-    DG_REQUIRE(desc->n_app == 0 || (app && dg::aligned(app, 16)), DG_ERR_ARG, "dg_mlp_bwd: appearance rows missing or not 16-byte aligned");
-    DG_REQUIRE(ws && ws_bytes >= dg_mlp_bwd_app_workspace_bytes(desc, N, S), DG_ERR_WORKSPACE, "dg_mlp_bwd: workspace %zu < %zu bytes",
-               ws_bytes, dg_mlp_bwd_app_workspace_bytes(desc, N, S));
-    DG_REQUIRE(dg::aligned(ws, 256), DG_ERR_ARG, "dg_mlp_bwd: workspace must be 256-byte aligned");
-    const uint64_t n_tiles = (N + kBwdBlock - 1) / kBwdBlock;
-    const uint32_t grid = (uint32_t)(n_tiles < kBwdGrid ? n_tiles : kBwdGrid);
-    const uint32_t n_w = (uint32_t)dg_mlp_weight_count(desc);
-    hipStream_t st = (hipStream_t)stream;
-    if (net == 1) {
-        DG_REQUIRE(dg::aligned(feat, 4) && dg::aligned(dir_enc, 16) && dg::aligned(dfeat, 8), DG_ERR_ARG,
-                   "dg_mlp_bwd: feat must be 4-byte, dfeat 8-byte, dir_enc 16-byte aligned");
-        dg::mlp_mfma_bwd(weights, feat, dir_enc, app, desc->n_app, S, N, desc->act_c, dsigma, drgb, loss_scale, dfeat, dW, ws, st);
-        return dg::launch_status("dg_mlp_bwd");
-    }
-    mlp_bwd_kernel<NetTiny><<<grid, kBwdBlock, 0, st>>>((const __half *)weights, (const __half *)feat, (const __half *)dir_enc,
-                                                        S, N, desc->act_c, dsigma, drgb, loss_scale, dfeat, (float *)ws);
-    fold_partials_kernel<<<(n_w + 255) / 256, 256, 0, st>>>((const float *)ws, grid, n_w, 1.0f / loss_scale, dW);
-    return dg::launch_status("dg_mlp_bwd");
+    return mlp_bwd("dg_mlp_bwd", desc, weights, feat, false, 0, dir_enc, app, S, N, dsigma, drgb, loss_scale, dfeat, dW, ws, ws_bytes, stream);
+}
+
+extern "C" int dg_mlp_bwd_rows(const dg_mlp_desc *desc, const void *weights, const void *feat, const void *dir_enc,
+                               const void *app, uint32_t S, uint64_t N, const float *dsigma, const float *drgb,
+                               float loss_scale, uint32_t n_merged, float *dfeat, float *dW, void *ws, size_t ws_bytes, void *stream)
+{
+    return mlp_bwd("dg_mlp_bwd_rows", desc, weights, feat, true, n_merged, dir_enc, app, S, N, dsigma, drgb, loss_scale, dfeat, dW, ws, ws_bytes, stream);
 }

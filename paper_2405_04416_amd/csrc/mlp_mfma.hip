@@ -25,6 +25,7 @@
 // matrix-core product of the transposed delta tile with a 0/1 sample-to-row matrix and are added into a [rows, 64]
 // buffer; a small kernel contracts that buffer with the feature rows.  No accumulator registers are added.
 #include "dg_internal.h"
+#include <type_traits>
 
 namespace dg_mlp_mfma {
 
@@ -208,14 +209,16 @@ __device__ __forceinline__ void forward_tile(const __half *lds, int lane, uint32
     for (int c = 0; c < 3; ++c) { t.raw[c] = out[c]; t.rgb[c] = fast_sigmoid(clip15(out[c])); }
 }
 
-// features arrive as level-major planes [16][n_samples] of half2; slot j of k-step ks on lane half h
-// is feature 16 ks + 8 h + j, i.e. component j % 2 of level 8 ks + 4 h + j / 2
-template <int NA>
-__device__ __forceinline__ void load_inputs(const __half *feat, const __half *dir_enc, const __half *app, uint32_t S,
-                                            uint64_t n_samples, uint64_t n, bool valid, int h, Tile &t)
+// Features arrive as level-major planes [16][n_samples] of half2 -- slot j of k-step ks on lane half h is feature
+// 16 ks + 8 h + j, i.e. component j % 2 of level 8 ks + 4 h + j / 2 -- or as rows of 32 halves (ROWS).
+template <bool ROWS>
+__device__ __forceinline__ void load_features(const __half *feat, uint64_t n_samples, uint64_t n, int h, h8 x0[2])
 {
-    const h8 zero = {0, 0, 0, 0, 0, 0, 0, 0};
-    if (valid) {
+    if (ROWS) {
+        const h8 *row = reinterpret_cast<const h8 *>(feat) + 4 * n;
+#pragma unroll
+        for (int ks = 0; ks < 2; ++ks) x0[ks] = row[2 * ks + h];
+    } else {
         typedef uint32_t u4 __attribute__((ext_vector_type(4)));
         const uint32_t *planes = reinterpret_cast<const uint32_t *>(feat);
 #pragma unroll
@@ -223,8 +226,18 @@ __device__ __forceinline__ void load_inputs(const __half *feat, const __half *di
             u4 bits;
 #pragma unroll
             for (int q = 0; q < 4; ++q) bits[q] = planes[(size_t)(8 * ks + 4 * h + q) * n_samples + n];
-            t.x0[ks] = __builtin_bit_cast(h8, bits);
+            x0[ks] = __builtin_bit_cast(h8, bits);
         }
+    }
+}
+
+template <int NA, bool ROWS>
+__device__ __forceinline__ void load_inputs(const __half *feat, const __half *dir_enc, const __half *app, uint32_t S,
+                                            uint64_t n_samples, uint64_t n, bool valid, int h, Tile &t)
+{
+    const h8 zero = {0, 0, 0, 0, 0, 0, 0, 0};
+    if (valid) {
+        load_features<ROWS>(feat, n_samples, n, h, t.x0);
         t.xc[1] = reinterpret_cast<const h8 *>(dir_enc + (n / S) * ND)[h];
 #pragma unroll
         for (int ks = 0; ks < NA / 16; ++ks) t.xa[ks] = reinterpret_cast<const h8 *>(app + (n / S) * NA)[2 * ks + h];
@@ -235,7 +248,7 @@ __device__ __forceinline__ void load_inputs(const __half *feat, const __half *di
     }
 }
 
-template <int NA>
+template <int NA, bool ROWS>
 __global__ void __launch_bounds__(kBlock, 4)
 fwd_kernel(const __half *__restrict__ weights, const __half *__restrict__ feat, const __half *__restrict__ dir_enc,
            const __half *__restrict__ app, uint32_t S, uint64_t n_samples, uint32_t act_c, float *__restrict__ sigma,
@@ -253,7 +266,7 @@ fwd_kernel(const __half *__restrict__ weights, const __half *__restrict__ feat, 
         const uint64_t n = tile * 32 + (lane & 31);
         const bool valid = n < n_samples;
         Tile t;
-        load_inputs<NA>(feat, dir_enc, app, S, n_samples, n, valid, h, t);
+        load_inputs<NA, ROWS>(feat, dir_enc, app, S, n_samples, n, valid, h, t);
         forward_tile<NA>(lds, opaque(lane), act_c, t, kFwdChunks);
         if (valid && h == 0) {
             sigma[n] = t.sigma;
@@ -286,7 +299,7 @@ __device__ __forceinline__ float wave_sum(float v)
     return v;
 }
 
-template <int NA>
+template <int NA, bool ROWS>
 __global__ void __launch_bounds__(kBlock, 4)
 render_fwd_kernel(const __half *__restrict__ weights, const __half *__restrict__ feat, const __half *__restrict__ dir_enc,
                   const __half *__restrict__ app, uint32_t S, uint32_t n_seg, uint32_t act_c, const float *__restrict__ delta,
@@ -308,7 +321,7 @@ render_fwd_kernel(const __half *__restrict__ weights, const __half *__restrict__
             const uint32_t s = 32u * part + (lane & 31);
             const bool valid = s < S;
             Tile t;
-            load_inputs<NA>(feat, dir_enc, app, S, n_samples, first + (valid ? s : 0), valid, h, t);
+            load_inputs<NA, ROWS>(feat, dir_enc, app, S, n_samples, first + (valid ? s : 0), valid, h, t);
             forward_tile<NA>(lds, opaque(lane), act_c, t, kFwdChunks);
             sig[part] = t.sigma;
             col[part][0] = t.rgb[0]; col[part][1] = t.rgb[1]; col[part][2] = t.rgb[2];
@@ -391,7 +404,7 @@ __device__ __forceinline__ void store_share(float *dst, int n_in, int rows_real,
 //                already scaled and rounded to fp16, in operand order) in the workspace;
 //   density_bwd: recomputes the density hidden layer, back-propagates it from delta_geo, accumulates
 //                dWd1..2 and writes the feature gradient planes.
-template <int NA>
+template <int NA, bool ROWS>
 __global__ void __launch_bounds__(kBlock, 2)
 colour_bwd_kernel(const __half *__restrict__ weights, const __half *__restrict__ feat, const __half *__restrict__ dir_enc,
                   const __half *__restrict__ app, uint32_t S, uint64_t n_samples, uint32_t act_c,
@@ -427,7 +440,7 @@ colour_bwd_kernel(const __half *__restrict__ weights, const __half *__restrict__
         const bool valid = n < n_samples;
         const int lane = opaque(lane_fixed);
         Tile t;
-        load_inputs<NA>(feat, dir_enc, app, S, n_samples, n, valid, h, t);
+        load_inputs<NA, ROWS>(feat, dir_enc, app, S, n_samples, n, valid, h, t);
         float ds = 0.0f, dc[3] = {0.0f, 0.0f, 0.0f};
         if (valid && h == 0) {                 // issued before the forward so the latency hides behind it
             ds = dsigma[n];
@@ -554,9 +567,11 @@ colour_bwd_kernel(const __half *__restrict__ weights, const __half *__restrict__
     }
 }
 
+// ROWS: the gradient of levels [0, n_merged) goes into rows of 2 n_merged floats, that of the others into planes behind them
+template <bool ROWS>
 __global__ void __launch_bounds__(kBlock, 2)
 density_bwd_kernel(const __half *__restrict__ weights, const __half *__restrict__ feat, uint64_t n_samples,
-                   const h8 *__restrict__ dgeo, float loss_scale, float *__restrict__ dfeat, float *__restrict__ shares)
+                   const h8 *__restrict__ dgeo, float loss_scale, uint32_t n_merged, float *__restrict__ dfeat, float *__restrict__ shares)
 {
     // images: density layer 1 forward (4 chunks), Wd2^T (2), Wd1^T (4), selections (4)
     constexpr int kD1 = 0, kD2T = 4, kD1T = 6, kST = 10, kSN = 12, kChunks = 14;
@@ -584,18 +599,8 @@ density_bwd_kernel(const __half *__restrict__ weights, const __half *__restrict_
         const uint64_t n = tile * 32 + (lane & 31);
         const bool valid = n < n_samples;
         Tile t;
-        load_inputs<0>(feat, nullptr, nullptr, 1, n_samples, n, false, h, t);      // zeroes
-        if (valid) {
-            typedef uint32_t u4 __attribute__((ext_vector_type(4)));
-            const uint32_t *planes = reinterpret_cast<const uint32_t *>(feat);
-#pragma unroll
-            for (int ks = 0; ks < 2; ++ks) {
-                u4 bits;
-#pragma unroll
-                for (int q = 0; q < 4; ++q) bits[q] = planes[(size_t)(8 * ks + 4 * h + q) * n_samples + n];
-                t.x0[ks] = __builtin_bit_cast(h8, bits);
-            }
-        }
+        t.x0[0] = zero8; t.x0[1] = zero8;
+        if (valid) load_features<ROWS>(feat, n_samples, n, h, t.x0);
         const h8 dg = valid ? dgeo[2 * n + h] : zero8;
         f16v acc[2];
 #pragma unroll
@@ -637,6 +642,11 @@ density_bwd_kernel(const __half *__restrict__ weights, const __half *__restrict_
             float2 *planes = reinterpret_cast<float2 *>(dfeat);
 #pragma unroll
             for (int q = 0; q < 4; ++q) {
+                if (ROWS && 4u * q + 2u * h < n_merged) {          // n_merged is even: a lane's two levels go the same way
+                    reinterpret_cast<float4 *>(dfeat)[n * (n_merged / 2) + 2 * q + h] =
+                        make_float4(gf[4 * q] * inv_scale, gf[4 * q + 1] * inv_scale, gf[4 * q + 2] * inv_scale, gf[4 * q + 3] * inv_scale);
+                    continue;
+                }
                 planes[(size_t)(4 * q + 2 * h) * n_samples + n] = make_float2(gf[4 * q] * inv_scale, gf[4 * q + 1] * inv_scale);
                 planes[(size_t)(4 * q + 2 * h + 1) * n_samples + n] = make_float2(gf[4 * q + 2] * inv_scale, gf[4 * q + 3] * inv_scale);
             }
@@ -766,33 +776,47 @@ size_t mlp_mfma_workspace_bytes(uint64_t N, uint32_t n_app, uint32_t S)
 
 size_t mlp_mfma_weight_count(uint32_t n_app) { return (size_t)dg_mlp_mfma::kTotal + (size_t)dg_mlp_mfma::HC * n_app; }
 
-void mlp_mfma_fwd(const void *weights, const void *feat, const void *dir_enc, const void *app, uint32_t n_app, uint32_t S,
+// calls launch(appearance inputs, rows) with both as compile-time constants
+template <class F>
+static void for_shape(uint32_t n_app, bool rows, F launch)
+{
+    auto with_rows = [&](auto na) {
+        if (rows) launch(na, std::true_type{});
+        else launch(na, std::false_type{});
+    };
+    if (n_app == 0) with_rows(std::integral_constant<int, 0>{});
+    else if (n_app == 16) with_rows(std::integral_constant<int, 16>{});
+    else with_rows(std::integral_constant<int, 48>{});
+}
+
+void mlp_mfma_fwd(const void *weights, const void *feat, bool rows, const void *dir_enc, const void *app, uint32_t n_app, uint32_t S,
                   uint64_t N, uint32_t act_c, float *sigma, float *rgb, hipStream_t st)
 {
     using namespace dg_mlp_mfma;
     const uint64_t tiles = (N + 31) / 32, blocks_needed = (tiles + kWavesPerBlock - 1) / kWavesPerBlock;
     const uint32_t grid = (uint32_t)(blocks_needed < 2048 ? blocks_needed : 2048);
-    const __half *w = (const __half *)weights, *f = (const __half *)feat, *dr = (const __half *)dir_enc, *ap = (const __half *)app;
-    if (n_app == 0) fwd_kernel<0><<<grid, kBlock, 0, st>>>(w, f, dr, ap, S, N, act_c, sigma, rgb);
-    else if (n_app == 16) fwd_kernel<16><<<grid, kBlock, 0, st>>>(w, f, dr, ap, S, N, act_c, sigma, rgb);
-    else fwd_kernel<48><<<grid, kBlock, 0, st>>>(w, f, dr, ap, S, N, act_c, sigma, rgb);
+    for_shape(n_app, rows, [&](auto na, auto in_rows) {
+        fwd_kernel<decltype(na)::value, decltype(in_rows)::value><<<grid, kBlock, 0, st>>>(
+            (const __half *)weights, (const __half *)feat, (const __half *)dir_enc, (const __half *)app, S, N, act_c, sigma, rgb);
+    });
 }
 
-void mlp_mfma_render(const void *weights, const void *feat, const void *dir_enc, const void *app, uint32_t n_app, uint32_t S,
+void mlp_mfma_render(const void *weights, const void *feat, bool rows, const void *dir_enc, const void *app, uint32_t n_app, uint32_t S,
                      uint32_t n_seg, uint32_t act_c, const float *delta, const float *t, const uint32_t *seg_ray,
                      const uint32_t *seg_slot, uint32_t k_max, float *Ck, float *Tk, float *Dk, hipStream_t st)
 {
     using namespace dg_mlp_mfma;
     const uint32_t blocks_needed = (n_seg + kWavesPerBlock - 1) / kWavesPerBlock;
     const uint32_t grid = blocks_needed < 2048 ? blocks_needed : 2048;
-    const __half *w = (const __half *)weights, *f = (const __half *)feat, *dr = (const __half *)dir_enc, *ap = (const __half *)app;
-    if (n_app == 0) render_fwd_kernel<0><<<grid, kBlock, 0, st>>>(w, f, dr, ap, S, n_seg, act_c, delta, t, seg_ray, seg_slot, k_max, Ck, Tk, Dk);
-    else if (n_app == 16) render_fwd_kernel<16><<<grid, kBlock, 0, st>>>(w, f, dr, ap, S, n_seg, act_c, delta, t, seg_ray, seg_slot, k_max, Ck, Tk, Dk);
-    else render_fwd_kernel<48><<<grid, kBlock, 0, st>>>(w, f, dr, ap, S, n_seg, act_c, delta, t, seg_ray, seg_slot, k_max, Ck, Tk, Dk);
+    for_shape(n_app, rows, [&](auto na, auto in_rows) {
+        render_fwd_kernel<decltype(na)::value, decltype(in_rows)::value><<<grid, kBlock, 0, st>>>(
+            (const __half *)weights, (const __half *)feat, (const __half *)dir_enc, (const __half *)app, S, n_seg, act_c, delta, t, seg_ray,
+            seg_slot, k_max, Ck, Tk, Dk);
+    });
 }
 
-void mlp_mfma_bwd(const void *weights, const void *feat, const void *dir_enc, const void *app, uint32_t n_app, uint32_t S,
-                  uint64_t N, uint32_t act_c, const float *dsigma, const float *drgb, float loss_scale, float *dfeat, float *dW,
+void mlp_mfma_bwd(const void *weights, const void *feat, bool rows, uint32_t n_merged, const void *dir_enc, const void *app, uint32_t n_app,
+                  uint32_t S, uint64_t N, uint32_t act_c, const float *dsigma, const float *drgb, float loss_scale, float *dfeat, float *dW,
                   void *ws, hipStream_t st)
 {
     using namespace dg_mlp_mfma;
@@ -811,13 +835,12 @@ void mlp_mfma_bwd(const void *weights, const void *feat, const void *dir_enc, co
         const uint64_t n = n_rows * HC, want = (n + kBlock - 1) / kBlock;
         zero_kernel<<<(uint32_t)(want < 4096 ? want : 4096), kBlock, 0, st>>>(row_delta, n);
     }
-    if (n_app == 0)
-        colour_bwd_kernel<0><<<grid_c, kBlock, 0, st>>>(w, f, dr, ap, S, N, act_c, dsigma, drgb, loss_scale, dgeo, colour_shares, row_delta);
-    else if (n_app == 16)
-        colour_bwd_kernel<16><<<grid_c, kBlock, 0, st>>>(w, f, dr, ap, S, N, act_c, dsigma, drgb, loss_scale, dgeo, colour_shares, row_delta);
-    else
-        colour_bwd_kernel<48><<<grid_c, kBlock, 0, st>>>(w, f, dr, ap, S, N, act_c, dsigma, drgb, loss_scale, dgeo, colour_shares, row_delta);
-    density_bwd_kernel<<<grid_d, kBlock, 0, st>>>(w, f, N, dgeo, loss_scale, dfeat, density_shares);
+    for_shape(n_app, rows, [&](auto na, auto in_rows) {
+        colour_bwd_kernel<decltype(na)::value, decltype(in_rows)::value><<<grid_c, kBlock, 0, st>>>(w, f, dr, ap, S, N, act_c, dsigma, drgb, loss_scale, dgeo,
+                                                                                                   colour_shares, row_delta);
+    });
+    if (rows) density_bwd_kernel<true><<<grid_d, kBlock, 0, st>>>(w, f, N, dgeo, loss_scale, n_merged, dfeat, density_shares);
+    else density_bwd_kernel<false><<<grid_d, kBlock, 0, st>>>(w, f, N, dgeo, loss_scale, 0, dfeat, density_shares);
     fold_shares_kernel<<<(kTotal + kFoldElems - 1) / kFoldElems, kFoldElems * kFoldGroups, 0, st>>>(
         density_shares, grid_d * kWavesPerBlock, colour_shares, grid_c * kWavesPerBlock, 1.0f / loss_scale, dW);
     if (n_app) {

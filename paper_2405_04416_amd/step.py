@@ -94,17 +94,17 @@ class TrainStep:
             self.samples = {}                               # partition -> (first sample, number of samples) of this step
         self.appearance = appearance
         self.app_rows = None if appearance is None else z(self.dir_enc.shape[0], appearance[0].shape[1], dt=f16)
-        self.feat = z(n, self.n_feat, dt=f16)
+        self._feat = z(n, self.n_feat, dt=f16)
         self.sigma, self.rgb = z(n), z(n, 3)
         self.dsigma, self.drgb = z(n), z(n, 3)
-        self.dfeat = z(n, self.n_feat)
+        self._dfeat = z(n, self.n_feat)
         self.Ck, self.Tk = z(R, k_max, 3), z(R, k_max)
         self.gCk, self.gTk = z(R, k_max, 3), z(R, k_max)
         self.C, self.T, self.gC, self.gT = z(R, 3), z(R), z(R, 3), z(R)
         self.loss = z(1)
         self.ws_mlp = z(B.dg_mlp_bwd_app_workspace_bytes(any_model.mlp, n, S if occupancy is None else 1) // 4 + 64)
         # workspace of the binned table-gradient pass, capped (the call batches itself when it is smaller than ideal)
-        want = max(B.dg_hashgrid_encode_bwd_workspace_bytes(mm.grid, n) for mm in models.values())
+        want = max(self._encode_ws_bytes(mm, n) for mm in models.values())
         self.ws_enc = torch.zeros(min(want, encode_ws_cap) // 4 + 64, dtype=f32, device=self.dev) if binned_backward else None
         self.foreign_prefilled = bool(foreign_prefilled)
         # The queue sizes of the binned table-gradient pass depend on the sample coordinates alone: for the sub-model whose
@@ -115,10 +115,104 @@ class TrainStep:
         # and 40.0 against 40.0 ms per step.)
         self.side = torch.cuda.Stream(device=self.dev) if binned_backward and occupancy is None else None
         self.counted = None     # (partition, samples, event) of a count that is ahead
+        # Samples in spatial order (large batches): the sorted list of every sub-model and what its bricks hold; the scratch of
+        # the sort grows to the largest one asked for.
+        order_any = binned_backward and any(n >= self._order_min(mm) for mm in models.values())
+        self.ordered = torch.empty(n, 4, dtype=f32, device=self.dev) if order_any else None
+        self.pieces, self.ws_order = {}, None
+        self.layout = {}        # partition -> (first sample, samples, order or None) of this step
         self.offsets = None
         self.local = {}         # resident partition -> index of its first segment among the resident segments (sample buffers)
         self.t_fixed = None
         self.timings = None     # set to {} to collect (start, end) event pairs per entry point
+
+    # -- samples in spatial order ------------------------------------------------------------
+    def _order_min(self, m):
+        """Samples of a sub-model from which on they are put in spatial order.  The kernels for ordered samples serve the
+        16-level grid with the 32-64-16 / 64-64-3 networks.  The order pays once the samples lie densely enough to share table
+        lines and cells.  Whole step, plain against ordered: tables that fit the L2 (T = 2^19) 1.49 / 1.56 ms at 1.7 M samples,
+        2.63 / 2.52 at 3.3 M; larger ones (T = 2^22, four sub-models) 3.45 / 3.43 ms at 0.4 M each, 5.42 / 5.00 at 0.8 M.
+        Occupancy-guided samples lie on surfaces, ten times as densely (1.57 / 1.51 ms at 1.6 M)."""
+        if m.grid.n_levels != 16 or (m.mlp.n_feat, m.mlp.n_hidden_d, m.mlp.n_layers_c) != (32, 64, 2):
+            return 1 << 62
+        if m.grid.log2_T > 20:
+            return 1 << 19
+        return 1 << 21 if self.occ is None else 1 << 20
+
+    def _encode_ws_bytes(self, m, n):
+        """Workspace of the table-gradient pass for up to n samples.  In spatial order it holds the unmerged levels only;
+        how many levels are merged falls with the number of samples, so smaller batches are looked at too."""
+        least = self._order_min(m)
+        if n < least:
+            return B.dg_hashgrid_encode_bwd_workspace_bytes(m.grid, n)
+        sizes = [max(n * k // 10, least) for k in (10, 9, 8, 7, 6, 5)]
+        return max([B.dg_hashgrid_encode_bwd_workspace_bytes(m.grid, least)] +
+                   [B.dg_hashgrid_encode_bwd_ordered_workspace_bytes(m.grid, B.dg_order_desc_init(m.grid, k), k) for k in sizes])
+
+    def _order_of(self, m, N):
+        """Order descriptor of a batch of N samples, or None where the plain kernels serve it."""
+        return B.dg_order_desc_init(m.grid, N) if self.ordered is not None and N >= self._order_min(m) else None
+
+    def _encode_fwd(self, p, m, order, sl, N):
+        """Features of partition p's samples (their slice of the sample buffers): planes, or rows where they are sorted."""
+        self.layout[p] = (sl.start, N, order)
+        if order is not None:
+            words = B.dg_order_pieces_words(order, N)
+            if p not in self.pieces or self.pieces[p].numel() < words:
+                self.pieces[p] = torch.empty(words, dtype=torch.int32, device=self.dev)
+            need = B.dg_order_workspace_bytes(order) // 4
+            if self.ws_order is None or self.ws_order.numel() < need:
+                self.ws_order = torch.empty(need, dtype=torch.int32, device=self.dev)
+            with self._timed("dg_order_samples"):
+                B.dg_order_samples(order, self.u[sl], N, self.ordered[sl], self.pieces[p], self.ws_order)
+        with self._timed("dg_hashgrid_encode_fwd"):
+            if order is not None:
+                B.dg_hashgrid_encode_fwd_ordered(m.grid, m.table, self.ordered[sl], N, self._feat[sl])
+            else:
+                B.dg_hashgrid_encode_fwd(m.grid, m.table, self.u[sl], N, self._feat[sl])
+
+    def _mlp_fwd(self, m, order, sl, dir_enc, app, S, N):
+        call = B.dg_mlp_fwd_app if order is None else B.dg_mlp_fwd_rows
+        with self._timed("dg_mlp_fwd"):
+            call(m.mlp, m.weights, self._feat[sl], dir_enc, app, S, N, self.sigma[sl], self.rgb[sl])
+
+    def _mlp_and_encode_bwd(self, p, m, sl, dir_enc, app, S, N, counted):
+        order = self.layout[p][2]
+        with self._timed("dg_mlp_bwd"):
+            if order is None:
+                B.dg_mlp_bwd_app(m.mlp, m.weights, self._feat[sl], dir_enc, app, S, N, self.dsigma[sl], self.drgb[sl], self.loss_scale,
+                                 self._dfeat[sl], m.dW, self.ws_mlp)
+            else:
+                B.dg_mlp_bwd_rows(m.mlp, m.weights, self._feat[sl], dir_enc, app, S, N, self.dsigma[sl], self.drgb[sl], self.loss_scale,
+                                  order.n_merged, self._dfeat[sl], m.dW, self.ws_mlp)
+        with self._timed("dg_hashgrid_encode_bwd"):
+            if order is not None:
+                B.dg_hashgrid_encode_bwd_ordered(m.grid, order, self.ordered[sl], self.pieces[p], self.u[sl], self._dfeat[sl], N, m.dtable, self.ws_enc,
+                                                 counted)
+            elif counted:
+                B.dg_hashgrid_encode_bwd_counted(m.grid, self.u[sl], self._dfeat[sl], N, m.dtable, self.ws_enc)
+            else:
+                B.dg_hashgrid_encode_bwd(m.grid, self.u[sl], self._dfeat[sl], N, m.dtable, self.ws_enc)
+
+    def _as_planes(self, buf, merged_only):
+        """Copy of a feature buffer with every partition's samples as level-major planes, the layout of the plain kernels."""
+        out = buf.clone()
+        for s0, N, order in self.layout.values():
+            if order is not None:
+                M = order.n_merged if merged_only else self.n_feat // 2
+                rows = buf[s0:s0 + N].reshape(-1)[:2 * M * N].view(N, M, 2)
+                out[s0:s0 + N].view(-1, N, 2)[:M] = rows.transpose(0, 1)
+        return out
+
+    @property
+    def feat(self):
+        """Features of the last forward pass, per partition as level-major planes [L, N, 2]."""
+        return self._as_planes(self._feat, False)
+
+    @property
+    def dfeat(self):
+        """Feature gradient of the last backward pass, per partition as level-major planes [L, N, 2]."""
+        return self._as_planes(self._dfeat, True)
 
     @contextlib.contextmanager
     def _timed(self, name):
@@ -200,11 +294,13 @@ class TrainStep:
         B.dg_merge_depth(Dk, self.Tk, self.seg_count, self.R, self.k_max, D)
         return self.C, D, self.T
 
-    def _count_ahead(self, p, sl, N):
+    def _count_ahead(self, p, order, sl, N):
         """Starts the count sweep of sub-model p's table-gradient pass (and clears its gradient buffers) on the second
         stream, behind the work already queued on this one; the backward pass picks it up."""
         m = self.models[p]
-        if B.dg_hashgrid_encode_bwd_workspace_bytes(m.grid, N) > self.ws_enc.numel() * self.ws_enc.element_size():
+        need = (B.dg_hashgrid_encode_bwd_workspace_bytes(m.grid, N) if order is None
+                else B.dg_hashgrid_encode_bwd_ordered_workspace_bytes(m.grid, order, N))
+        if need > self.ws_enc.numel() * self.ws_enc.element_size():
             return                                  # the workspace would batch: counted with each batch, as usual
         here = torch.cuda.Event()
         here.record()
@@ -212,7 +308,10 @@ class TrainStep:
         with torch.cuda.stream(self.side):
             self.side.wait_event(here)
             go.record()
-            B.dg_hashgrid_encode_bwd_count(m.grid, self.u[sl], N, self.ws_enc)
+            if order is None:
+                B.dg_hashgrid_encode_bwd_count(m.grid, self.u[sl], N, self.ws_enc)
+            else:
+                B.dg_hashgrid_encode_bwd_ordered_count(m.grid, order, self.u[sl], N, self.ws_enc)
             m.dtable.zero_()
             m.dW.zero_()
             done = torch.cuda.Event()
@@ -226,6 +325,7 @@ class TrainStep:
         """Segments, and per resident sub-model: samples, encode, MLPs, local compositing into the partial slots.
         fused_depth: None, or Dk [R,k_max]: networks, compositing and depth in one call (evaluation rendering)."""
         self.counted = None
+        self.layout = {}
         S = self.S
         self.segments(o, d)
         # the sub-model whose backward pass runs first: only its counts may wait in the workspace that all share
@@ -245,21 +345,20 @@ class TrainStep:
                                      self.parts_host[p], S, self.seed, jit, self.u[sl], self.delta[sl],
                                      self.t_fixed[sl] if want_t else None)
             rows = self._rows(p)
+            order = self._order_of(m, N)
             if training and self.side is not None and p == first:
-                self._count_ahead(p, sl, N)
+                self._count_ahead(p, order, sl, N)
             with self._timed("dg_dir_encode"):
                 B.dg_dir_encode(d, self.seg_ray[b:e], n_seg, self.deg, self.dir_enc[rows])
-            with self._timed("dg_hashgrid_encode_fwd"):
-                B.dg_hashgrid_encode_fwd(m.grid, m.table, self.u[sl], N, self.feat[sl])
+            self._encode_fwd(p, m, order, sl, N)
             app = self._appearance_rows(self.seg_ray[b:e], n_seg, rows)
             if fused_depth is not None:
+                call = B.dg_mlp_composite_fwd if order is None else B.dg_mlp_composite_fwd_rows
                 with self._timed("dg_mlp_composite_fwd"):
-                    B.dg_mlp_composite_fwd(m.mlp, m.weights, self.feat[sl], self.dir_enc[rows], app, S, n_seg, self.delta[sl],
-                                           self.t_fixed[sl], self.seg_ray[b:e], self.seg_slot[b:e], self.k_max, self.Ck, self.Tk,
-                                           fused_depth)
+                    call(m.mlp, m.weights, self._feat[sl], self.dir_enc[rows], app, S, n_seg, self.delta[sl], self.t_fixed[sl], self.seg_ray[b:e],
+                         self.seg_slot[b:e], self.k_max, self.Ck, self.Tk, fused_depth)
                 continue
-            with self._timed("dg_mlp_fwd"):
-                B.dg_mlp_fwd_app(m.mlp, m.weights, self.feat[sl], self.dir_enc[rows], app, S, N, self.sigma[sl], self.rgb[sl])
+            self._mlp_fwd(m, order, sl, self.dir_enc[rows], app, S, N)
             with self._timed("dg_composite_segment_fwd"):
                 B.dg_composite_segment_fwd(self.sigma[sl], self.rgb[sl], self.delta[sl], n_seg, S, self.seg_ray[b:e],
                                            self.seg_slot[b:e], self.k_max, self.Ck, self.Tk)
@@ -299,11 +398,10 @@ class TrainStep:
             if N:
                 with self._timed("dg_dir_encode"):
                     B.dg_dir_encode(d, self.sample_ray[sl], N, self.deg, self.dir_enc[sl])
-                with self._timed("dg_hashgrid_encode_fwd"):
-                    B.dg_hashgrid_encode_fwd(m.grid, m.table, self.u[sl], N, self.feat[sl])
+                order = self._order_of(m, N)
+                self._encode_fwd(p, m, order, sl, N)
                 app = self._appearance_rows(self.sample_ray[sl], N, sl)
-                with self._timed("dg_mlp_fwd"):
-                    B.dg_mlp_fwd_app(m.mlp, m.weights, self.feat[sl], self.dir_enc[sl], app, 1, N, self.sigma[sl], self.rgb[sl])
+                self._mlp_fwd(m, order, sl, self.dir_enc[sl], app, 1, N)
             with self._timed("dg_composite_ragged_fwd"):        # also writes C_k = 0, T_k = 1 for segments that saw nothing
                 B.dg_composite_ragged_fwd(self.sigma[s0 - N:], self.rgb[s0 - N:], self.delta[s0 - N:], n_seg, first, ray, slot,
                                           self.k_max, self.Ck, self.Tk)
@@ -335,11 +433,7 @@ class TrainStep:
                 B.dg_composite_ragged_bwd(self.sigma[s0:], self.rgb[s0:], self.delta[s0:], e - b, self.first[b + p:e + p + 1],
                                           self.seg_ray[b:e], self.seg_slot[b:e], self.k_max, self.gCk, self.gTk, self.dsigma[s0:],
                                           self.drgb[s0:])
-            with self._timed("dg_mlp_bwd"):
-                B.dg_mlp_bwd_app(m.mlp, m.weights, self.feat[sl], self.dir_enc[sl], None if self.app_rows is None else self.app_rows[sl],
-                                 1, N, self.dsigma[sl], self.drgb[sl], self.loss_scale, self.dfeat[sl], m.dW, self.ws_mlp)
-            with self._timed("dg_hashgrid_encode_bwd"):
-                B.dg_hashgrid_encode_bwd(m.grid, self.u[sl], self.dfeat[sl], N, m.dtable, self.ws_enc)
+            self._mlp_and_encode_bwd(p, m, sl, self.dir_enc[sl], None if self.app_rows is None else self.app_rows[sl], 1, N, False)
 
     # -- occupancy refresh (Sec. 5.1; Instant-NGP App. E.2) -------------------------------------
     def refresh_occupancy(self, iteration, tries=32):
@@ -362,14 +456,12 @@ class TrainStep:
                 cell = self.sample_ray[:n]                      # the step's sample buffers serve as scratch
                 with self._timed("dg_occ_candidates"):
                     B.dg_occ_candidates(q.desc, q.bits, n, n_uniform, warmup, self.seed, iteration, tries, cell, self.u[:n], i0=i0)
-                with self._timed("dg_hashgrid_encode_fwd"):
-                    B.dg_hashgrid_encode_fwd(m.grid, m.table, self.u[:n], n, self.feat[:n])
+                order = None if warmup else self._order_of(m, n)        # during warm-up the candidates come cell after cell anyway
+                self._encode_fwd(p, m, order, slice(0, n), n)
                 self.dir_enc[:1].zero_()                        # the density does not depend on the direction: one zero row
                 if self.app_rows is not None:
                     self.app_rows[:1].zero_()
-                with self._timed("dg_mlp_fwd"):
-                    B.dg_mlp_fwd_app(m.mlp, m.weights, self.feat[:n], self.dir_enc[:1], None if self.app_rows is None else self.app_rows[:1],
-                                     max(n, 1), n, self.sigma[:n], self.rgb[:n])
+                self._mlp_fwd(m, order, slice(0, n), self.dir_enc[:1], None if self.app_rows is None else self.app_rows[:1], max(n, 1), n)
                 with self._timed("dg_occ_update"):
                     B.dg_occ_update(q.density, cell, self.sigma[:n], n)
             q.n_set.zero_()
@@ -404,14 +496,7 @@ class TrainStep:
                 B.dg_composite_segment_bwd(self.sigma[sl], self.rgb[sl], self.delta[sl], n_seg, S, self.seg_ray[b:e],
                                            self.seg_slot[b:e], self.k_max, self.gCk, self.gTk, self.dsigma[sl], self.drgb[sl])
             rows = self._rows(p)
-            with self._timed("dg_mlp_bwd"):
-                B.dg_mlp_bwd_app(m.mlp, m.weights, self.feat[sl], self.dir_enc[rows], None if self.app_rows is None else self.app_rows[rows],
-                                 S, N, self.dsigma[sl], self.drgb[sl], self.loss_scale, self.dfeat[sl], m.dW, self.ws_mlp)
-            with self._timed("dg_hashgrid_encode_bwd"):
-                if ahead:
-                    B.dg_hashgrid_encode_bwd_counted(m.grid, self.u[sl], self.dfeat[sl], N, m.dtable, self.ws_enc)
-                else:
-                    B.dg_hashgrid_encode_bwd(m.grid, self.u[sl], self.dfeat[sl], N, m.dtable, self.ws_enc)
+            self._mlp_and_encode_bwd(p, m, sl, self.dir_enc[rows], None if self.app_rows is None else self.app_rows[rows], S, N, ahead)
 
     def step(self, o, d, Cgt, jitter=None, foreign=None):
         self.forward(o, d, Cgt, jitter, foreign)

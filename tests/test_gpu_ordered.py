@@ -1,0 +1,139 @@
+"""Samples in spatial order: the sort, the encode into rows, the table gradient with merged levels, and the training step
+that uses them, at the sizes where they can go wrong -- one sample, one more than a wavefront or a workgroup takes, a brick
+that holds several pieces, samples on the box's faces and outside it."""
+import numpy as np
+import pytest
+import torch
+
+import dg_inputs as di
+import oracle
+from gpu_util import DEV, TOL_F16, dev, have_gpu, host, rel_err
+from paper_2405_04416_amd import binding as B
+from paper_2405_04416_amd.step import TrainStep
+
+pytestmark = [pytest.mark.gpu, pytest.mark.skipif(not have_gpu(), reason="needs a GPU")]
+
+GRIDS = {"cached": dict(log2_T=14, n_max=256, extent=[2.0, 2.0, 0.25]), "large": dict(log2_T=20, n_max=2048, extent=[1.0, 0.7, 0.3])}
+FLAVOURS = ("points", "one_spot", "faces")
+SIZES = (1, 63, 1023, 1025, 4097, 20011)
+
+
+def _grids(key):
+    q = GRIDS[key]
+    growth = B.dg_growth_factor(16, q["n_max"], 16)
+    return B.dg_grid_desc_init(16, 2, q["log2_T"], 16, growth, q["extent"]), oracle.grid_init(16, 2, q["log2_T"], 16, growth, q["extent"])
+
+
+def _coords(N, flavour):
+    u = di.make_unit_coords(N, seed=31)
+    if flavour == "one_spot":                       # everything in one brick: several pieces of it where N > 4096
+        u = (0.37 + 1e-3 * u).astype(np.float32)
+    if flavour == "faces":                          # corners, faces, and coordinates beyond the box (clamped by the encode)
+        special = np.asarray([[0, 0, 0], [1, 1, 1], [-0.3, 0.5, 2.0], [1, 0, 0.5], [0.99999994, 0.5, 0.0], [0.5, 1.0, 0.25]], np.float32)
+        n = min(N, len(special))
+        u[:n] = special[:n]
+    return u
+
+
+def _sorted(grid, u, N):
+    order = B.dg_order_desc_init(grid, N)
+    ordered = torch.full((N, 4), float("nan"), device=DEV)
+    pieces = torch.full((B.dg_order_pieces_words(order, N),), -1, dtype=torch.int32, device=DEV)
+    ws = torch.full((B.dg_order_workspace_bytes(order) // 4,), -7, dtype=torch.int32, device=DEV)
+    B.dg_order_samples(order, dev(u), N, ordered, pieces, ws)
+    return order, ordered, pieces
+
+
+@pytest.mark.parametrize("flavour", FLAVOURS)
+@pytest.mark.parametrize("N", SIZES)
+@pytest.mark.parametrize("key", list(GRIDS))
+def test_ordered_encode(key, N, flavour):
+    print("[case] ordered", key, N, flavour, flush=True)
+    grid, ref_grid = _grids(key)
+    u = _coords(N, flavour)
+    order, ordered, pieces = _sorted(grid, u, N)
+    M = order.n_merged
+    assert M >= 2 and order.total >= 1
+
+    # the sorted list is a permutation that carries the coordinates along; the pieces pave it, at most 4096 samples each
+    got = host(ordered)
+    index = got[:, 3].copy().view(np.uint32)
+    np.testing.assert_array_equal(np.sort(index), np.arange(N))
+    np.testing.assert_array_equal(got[:, :3].view(np.uint32), u[index].view(np.uint32))
+    words = host(pieces).view(np.uint32).reshape(-1, 2)
+    n_pieces = int(words[0, 0])
+    begins = words[1:2 + n_pieces, 1].astype(np.int64)
+    assert begins[0] == 0 and begins[-1] == N and np.all(np.diff(begins) > 0) and np.all(np.diff(begins) <= 4096)
+
+    # forward: rows in the original order; fp16 of an fp32 sum (bound as in the plain encode's test)
+    table = di.make_table(ref_grid.n_entries, 2, 1.0, seed=32)
+    rows = torch.full((N, 32), float("nan"), dtype=torch.float16, device=DEV)
+    B.dg_hashgrid_encode_fwd_ordered(grid, dev(table), ordered, N, rows)
+    ref = oracle.encode_fwd(ref_grid, table, u)
+    bound = oracle.encode_fwd(ref_grid, table, u, abs_terms=True)
+    assert np.all(np.abs(host(rows).astype(np.float64) - ref) <= 2.0 ** -11 * np.abs(ref) + 1e-5 * bound + 6e-8)
+
+    # backward, called twice ("+="); rows of the merged levels, then planes
+    g = (np.random.default_rng(33).standard_normal((N, 32)) * 1e-3).astype(np.float32)
+    g[::7] = 0.0
+    mixed = np.concatenate([np.ascontiguousarray(g[:, :2 * M]).ravel(), np.ascontiguousarray(g[:, 2 * M:].reshape(N, 16 - M, 2).transpose(1, 0, 2)).ravel()])
+    ud, gd = dev(u), dev(mixed)
+    dtable = torch.zeros(ref_grid.n_entries, 2, device=DEV)
+    ws = torch.zeros(B.dg_hashgrid_encode_bwd_ordered_workspace_bytes(grid, order, N) // 4 + 64, device=DEV)
+    B.dg_hashgrid_encode_bwd_ordered(grid, order, ordered, pieces, ud, gd, N, dtable, ws)
+    B.dg_hashgrid_encode_bwd_ordered_count(grid, order, ud, N, ws)
+    B.dg_hashgrid_encode_bwd_ordered(grid, order, ordered, pieces, ud, gd, N, dtable, ws, counted=True)
+    want = 2.0 * oracle.encode_bwd(ref_grid, u, g.astype(np.float64))
+    scale = 2.0 * oracle.encode_bwd(ref_grid, u, np.abs(g).astype(np.float64))          # sum of the contributions' magnitudes
+    have = host(dtable).astype(np.float64)
+    for l in range(16):
+        sl = slice(ref_grid.first[l], ref_grid.first[l + 1])
+        if l < M:
+            # a run adds up to 2 x 64 contributions in fp32, each of them four fp32 roundings deep; the rest is fp64 and a
+            # handful of fp32 adds into the table: (128 + 8) x 2^-24 of the magnitudes = 8.1e-6
+            assert np.all(np.abs(have[sl] - want[sl]) <= 1e-5 * scale[sl] + 1e-30), l
+        else:
+            assert rel_err(have[sl], want[sl]) <= TOL_F16, l                             # the binned pass, with its own bar
+    assert np.all(have[want == 0] == 0)
+
+
+def test_order_arguments():
+    grid, _ = _grids("cached")
+    order = B.dg_order_desc_init(grid, 5000)
+    u, ordered = torch.rand(5000, 3, device=DEV), torch.zeros(5000, 4, device=DEV)
+    pieces = torch.zeros(B.dg_order_pieces_words(order, 5000), dtype=torch.int32, device=DEV)
+    with pytest.raises(B.DistGridError):                                                 # workspace too small
+        B.dg_order_samples(order, u, 5000, ordered, pieces, torch.zeros(8, dtype=torch.int32, device=DEV))
+    shallow = B.dg_grid_desc_init(4, 2, 12, 16, 1.5, [1.0, 1.0, 1.0])
+    with pytest.raises(B.DistGridError):
+        B.dg_order_desc_init(shallow, 5000)
+
+
+@pytest.mark.parametrize("name,R,overrides", [("c2_ngp", 1500, {}), ("c3_2x2", 1200, dict(log2_T=16)), ("c8_app", 700, {})])
+def test_step_in_spatial_order(name, R, overrides, monkeypatch):
+    """The training step with the order forced at a small size, through every comparison of the plain step."""
+    from test_gpu_step import _compare_step
+    print("[case] step in spatial order", name, R, flush=True)
+    monkeypatch.setattr(TrainStep, "_order_min", lambda self, m: 1)
+    cfg = di.config(name)
+    cfg["grid"] = dict(cfg["grid"], **overrides)
+    step, _ = _compare_step(cfg, R, seed=2, lambda1=1e-3, loss_scale=2.0 ** 14, use_jitter_array=False, table_gain=3000.0)
+    assert all(order is not None for _, _, order in step.layout.values())
+
+
+def test_render_in_spatial_order(monkeypatch):
+    from gpu_util import gpu_models, make_step
+    import oracle.step as ostep
+    cfg = di.config("c2_ngp", table_range=0.3)
+    R = 801
+    o, d = di.make_rays(cfg, seed=5, R=R)
+    hm = ostep.make_models(cfg, seed=5)
+    plain = make_step(cfg, gpu_models(cfg, hm), R, seed=5)
+    monkeypatch.setattr(TrainStep, "_order_min", lambda self, m: 1)
+    sorted_ = make_step(cfg, gpu_models(cfg, hm), R, seed=5)
+    for fused in (None, False):
+        want = [x.clone() for x in plain.render(dev(o), dev(d), fused=fused)]
+        got = sorted_.render(dev(o), dev(d), fused=fused)
+        assert sorted_.layout[0][2] is not None
+        for a, b in zip(got, want):
+            assert rel_err(host(a), host(b)) <= TOL_F16
