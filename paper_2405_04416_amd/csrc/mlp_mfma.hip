@@ -8,15 +8,13 @@
 // layer once the registers are rounded to fp16 and packed -- the feature order this produces is
 // baked into the weight images, so layers chain with no data movement.
 //
-// Operand and result layouts (lane = 32 h + c, element j / register r):
-//   A[row c][k = 8 h + j]     B[k = 8 h + j][col c]     D[row 8 (r / 4) + 4 h + r % 4][col c]
-// "Images" are weight tiles pre-arranged in LDS so that one 16-byte read per lane yields an operand.
+// Operand layouts, images, transposes: mlp_mfma_common.h.
 //
 // Backward recomputes the forward, then walks the chain back.  Weight gradients contract over the
 // samples, so they need each (delta, activation) pair with the samples on the k axis; a product with
 // a 0/1 selection matrix on the matrix cores transposes a tile exactly (fp16 values times one,
-// summed with zeros).  Every wavefront accumulates its share of dW in registers over all its tiles,
-// writes it to the workspace once, and a second kernel folds the shares in a fixed order.
+// summed with zeros).  Every wavefront accumulates its share of dW in registers over all its tiles; the workgroup adds its
+// wavefronts' shares up, writes the sum to the workspace once, and a second kernel folds the workgroups' in a fixed order.
 //
 // Appearance features (Sec. 4.4.3: a fixed per-image vector of 16 or 48 values as extra colour-net inputs) widen the
 // first colour layer to 48 or 80 inputs.  Forward: NA / 16 more k-steps from a second row table.  Backward: the
@@ -24,13 +22,10 @@
 // sum_rows (sum of delta over the row's samples) x (row's features): the per-row delta sums come from one more
 // matrix-core product of the transposed delta tile with a 0/1 sample-to-row matrix and are added into a [rows, 64]
 // buffer; a small kernel contracts that buffer with the feature rows.  No accumulator registers are added.
-#include "dg_internal.h"
+#include "mlp_mfma_common.h"
 #include <type_traits>
 
 namespace dg_mlp_mfma {
-
-typedef _Float16 h8 __attribute__((ext_vector_type(8)));
-typedef float f16v __attribute__((ext_vector_type(16)));
 
 constexpr int NF = 32, HD = 64, NG = 16, ND = 16, HC = 64, CI = NG + ND;
 constexpr int oWd1 = 0, oWd2 = oWd1 + HD * NF, oWc1 = oWd2 + NG * HD, oWc2 = oWc1 + HC * CI, oWc3 = oWc2 + HC * HC;
@@ -39,46 +34,6 @@ constexpr int kTotal = oWc3 + 3 * HC;
 // image chunks (1 KB each: 64 lanes x 8 halves)
 constexpr int cD1 = 0, cD2 = 4, cC1 = 8, cC2 = 12, cC3 = 20, kFwdChunks = 24;
 constexpr int cC3T = 24, cC2T = 26, cC1T = 34, cD2T = 38, cD1T = 40, cSelT = 44, cSelN = 46, kAllChunks = 48;
-
-constexpr int kBlock = 256;
-constexpr int kWavesPerBlock = kBlock / 64;
-
-// feature held by slot j of lane half h in k-step ks
-__device__ __forceinline__ int feat_tiled(int ks, int h, int j) { return 32 * (ks >> 1) + 8 * (2 * (ks & 1) + (j >> 2)) + 4 * h + (j & 3); }
-__device__ __forceinline__ int feat_natural(int ks, int h, int j) { return 16 * ks + 8 * h + j; }
-
-// kind: 0 tiled, 1 natural, 2 colour-net input (k-step 0 tiled geometry, k-step 1 natural direction)
-__device__ __forceinline__ int feat_of(int kind, int ks, int h, int j)
-{
-    if (kind == 0) return feat_tiled(ks, h, j);
-    if (kind == 1) return feat_natural(ks, h, j);
-    return ks == 0 ? feat_tiled(0, h, j) : feat_natural(1, h, j);
-}
-
-// A-operand image of a weight matrix W[n_out][n_in] (row-major): rows = outputs (transpose == false)
-// or rows = inputs (transpose == true, for the data gradient)
-__device__ void build_image(__half *img, const __half *W, int n_out, int n_in, int rows_real, int k_real,
-                            int n_mt, int n_ks, int kind, bool transpose)
-{
-    for (int idx = threadIdx.x; idx < n_mt * n_ks * 512; idx += kBlock) {
-        const int j = idx & 7, lane = (idx >> 3) & 63, chunk = idx >> 9;
-        const int ks = chunk % n_ks, mt = chunk / n_ks;
-        const int row = 32 * mt + (lane & 31), k = feat_of(kind, ks, lane >> 5, j);
-        __half v = __float2half(0.0f);
-        if (row < rows_real && k < k_real) v = transpose ? W[k * n_in + row] : W[row * n_in + k];
-        img[idx] = v;
-    }
-    (void)n_out;
-}
-
-__device__ void build_selection(__half *img, int kind)
-{
-    for (int idx = threadIdx.x; idx < 2 * 512; idx += kBlock) {
-        const int j = idx & 7, lane = (idx >> 3) & 63, p = idx >> 9;
-        const int f = (kind == 0 ? feat_tiled(p, lane >> 5, j) : feat_natural(p, lane >> 5, j)) & 31;
-        img[idx] = __float2half(f == (lane & 31) ? 1.0f : 0.0f);
-    }
-}
 
 __device__ void build_forward_images(__half *lds, const __half *w)
 {
@@ -98,61 +53,6 @@ __device__ void build_backward_images(__half *lds, const __half *w)
     build_image(lds + cD1T * 512, w + oWd1, HD, NF, NF, HD, 1, 4, 0, true);
     build_selection(lds + cSelT * 512, 0);
     build_selection(lds + cSelN * 512, 1);
-}
-
-__device__ __forceinline__ h8 image(const __half *lds, int chunk, int lane)
-{
-    return reinterpret_cast<const h8 *>(lds)[chunk * 64 + lane];
-}
-
-// Returns its argument, in a way the compiler cannot see through: LDS reads indexed with the result are
-// issued where they are used, not hoisted out of the tile loop and held in registers for its whole length.
-__device__ __forceinline__ int opaque(int x)
-{
-    asm volatile("" : "+v"(x));
-    return x;
-}
-
-__device__ __forceinline__ f16v mma(h8 a, h8 b, f16v c) { return __builtin_amdgcn_mfma_f32_32x32x16_f16(a, b, c, 0, 0, 0); }
-
-__device__ __forceinline__ f16v zero16()
-{
-    f16v z;
-#pragma unroll
-    for (int i = 0; i < 16; ++i) z[i] = 0.0f;
-    return z;
-}
-
-__device__ __forceinline__ float fast_sigmoid(float x)
-{
-    return __builtin_amdgcn_rcpf(1.0f + __builtin_amdgcn_exp2f(-1.4426950408889634f * x));
-}
-__device__ __forceinline__ float clip15(float x) { return fminf(fmaxf(x, -15.0f), 15.0f); }
-
-// max(x, 0) on four pairs of halves, one instruction per pair
-__device__ __forceinline__ h8 relu_pairs(h8 x)
-{
-    typedef uint32_t u4 __attribute__((ext_vector_type(4)));
-    u4 w = __builtin_bit_cast(u4, x);
-#pragma unroll
-    for (int i = 0; i < 4; ++i) asm("v_pk_max_f16 %0, %1, 0" : "=v"(w[i]) : "v"(w[i]));
-    return __builtin_bit_cast(h8, w);
-}
-
-// registers 8p .. 8p+7 of a result tile, activated, rounded to fp16 and packed: k-step (m, p) of the next operand
-template <int ACT>   // 0 identity, 1 ReLU, 2 sigmoid
-__device__ __forceinline__ h8 pack_half(const f16v &c, int p)
-{
-    h8 out;
-#pragma unroll
-    for (int j = 0; j < 8; ++j) {
-        float v = c[8 * p + j];
-        if (ACT == 2) v = fast_sigmoid(v);
-        out[j] = (_Float16)v;
-    }
-    // ReLU after the rounding gives the same values as before it (rounding is monotone and keeps 0) and works on pairs
-    if (ACT == 1) out = relu_pairs(out);
-    return out;
 }
 
 struct Tile {
@@ -353,48 +253,6 @@ render_fwd_kernel(const __half *__restrict__ weights, const __half *__restrict__
 
 // ---------------------------------------------------------------------------------------- backward
 
-// transpose of one 32-feature tile of a packed tensor: x0 / x1 are the two k-steps that hold the tile,
-// sel0 / sel1 the matching selection images; result: the two sample k-steps of the transposed tile
-__device__ __forceinline__ void transpose_tile(h8 x0, h8 x1, h8 sel0, h8 sel1, h8 out[2])
-{
-    f16v c = zero16();
-    c = mma(x0, sel0, c);
-    c = mma(x1, sel1, c);
-    out[0] = pack_half<0>(c, 0);
-    out[1] = pack_half<0>(c, 1);
-}
-__device__ __forceinline__ void transpose_half_tile(h8 x0, h8 sel0, h8 out[2])
-{
-    f16v c = zero16();
-    c = mma(x0, sel0, c);
-    out[0] = pack_half<0>(c, 0);
-    out[1] = pack_half<0>(c, 1);
-}
-
-// delta = fp16(g * act'(a)) for one k-step; a is the packed (rounded) activation
-template <int ACT>   // 1 ReLU, 2 sigmoid
-__device__ __forceinline__ h8 delta_from(const f16v &g, int p, h8 a)
-{
-    h8 out;
-#pragma unroll
-    for (int j = 0; j < 8; ++j) {
-        const float av = (float)a[j];
-        const float d = ACT == 2 ? av * (1.0f - av) : (av > 0.0f ? 1.0f : 0.0f);
-        out[j] = (_Float16)(g[8 * p + j] * d);
-    }
-    return out;
-}
-
-__device__ __forceinline__ void store_share(float *dst, int n_in, int rows_real, int ot, int it, int lane, const f16v &acc)
-{
-    const int h = lane >> 5, i = 32 * it + (lane & 31);
-#pragma unroll
-    for (int r = 0; r < 16; ++r) {
-        const int o = 32 * ot + 8 * (r >> 2) + 4 * h + (r & 3);
-        if (o < rows_real) dst[o * n_in + i] = acc[r];
-    }
-}
-
 // The backward pass runs as two kernels so that neither has to hold all twelve dW tiles (192
 // accumulator registers) next to the activations:
 //   colour_bwd : recomputes the whole forward, back-propagates the colour net, accumulates dWc1..3
@@ -551,20 +409,31 @@ colour_bwd_kernel(const __half *__restrict__ weights, const __half *__restrict__
         if (valid) dgeo[2 * n + h] = pack_half<0>(gx, 0);
     }
 
-    float *mine = shares + wave * (kTotal - oWc1) - oWc1;       // colour shares hold elements [oWc1, kTotal)
-    const int lane = lane_fixed;
-    if (h == 0) {
+    static_assert((kTotal - oWc1) * 4 <= kAllChunks * 1024, "the share fits the space of the images");
+    write_share<kTotal - oWc1>(reinterpret_cast<float *>(lds), shares + (size_t)blockIdx.x * (kTotal - oWc1), [&](float *share, uint32_t group, bool first) {
+        const int lane = lane_fixed;
+        share -= oWc1;                                          // colour shares hold elements [oWc1, kTotal)
+        if (group < 2) {
 #pragma unroll
-        for (int it = 0; it < 2; ++it)
+            for (uint32_t ot = 0; ot < 2; ++ot)
+                if (group == ot) {
+                    add_share(share + oWc2, first, HC, HC, ot, 0, lane, gWc2[ot][0]);
+                    add_share(share + oWc2, first, HC, HC, ot, 1, lane, gWc2[ot][1]);
+                }
+        } else if (group == 2) {
 #pragma unroll
-            for (int o = 0; o < 3; ++o) mine[oWc3 + o * HC + 32 * it + (lane & 31)] = gWc3[(it * 3 + o) * 32 + (lane & 31)];
-    }
+            for (int ot = 0; ot < 2; ++ot) add_share(share + oWc1, first, CI, HC, ot, 0, lane, gWc1[ot]);
+        } else if (h == 0) {
 #pragma unroll
-    for (int ot = 0; ot < 2; ++ot) {
-        store_share(mine + oWc2, HC, HC, ot, 0, lane, gWc2[ot][0]);
-        store_share(mine + oWc2, HC, HC, ot, 1, lane, gWc2[ot][1]);
-        store_share(mine + oWc1, CI, HC, ot, 0, lane, gWc1[ot]);
-    }
+            for (int it = 0; it < 2; ++it)
+#pragma unroll
+                for (int o = 0; o < 3; ++o) {
+                    float *at = share + oWc3 + o * HC + 32 * it + (lane & 31);
+                    const float v = gWc3[(it * 3 + o) * 32 + (lane & 31)];
+                    *at = first ? v : *at + v;
+                }
+        }
+    });
 }
 
 // ROWS: the gradient of levels [0, n_merged) goes into rows of 2 n_merged floats, that of the others into planes behind them
@@ -653,46 +522,14 @@ density_bwd_kernel(const __half *__restrict__ weights, const __half *__restrict_
         }
     }
 
-    float *mine = shares + wave * oWc1;                         // density shares hold elements [0, oWc1)
+    static_assert(oWc1 * 4 <= kChunks * 1024, "the share fits the space of the images");
+    write_share<oWc1>(reinterpret_cast<float *>(lds), shares + (size_t)blockIdx.x * oWc1, [&](float *share, uint32_t group, bool first) {
 #pragma unroll
-    for (int ot = 0; ot < 2; ++ot) store_share(mine + oWd1, NF, HD, ot, 0, lane, gWd1[ot]);
-    store_share(mine + oWd2, HD, NG, 0, 0, lane, gWd2[0]);
-    store_share(mine + oWd2, HD, NG, 0, 1, lane, gWd2[1]);
-}
-
-// dW[e] += (sum of the wavefronts' shares of element e) / loss_scale, in a fixed order.  Elements below
-// oWc1 (density net) come from density_shares [n_d][oWc1], the rest from colour_shares [n_c][kTotal - oWc1].
-// A workgroup serves 64 consecutive elements; 16 groups of threads each sum every 16th share, then the 16
-// partial sums are added in a fixed order.
-constexpr int kFoldElems = 64, kFoldGroups = 16;
-static_assert(oWc1 % kFoldElems == 0, "a fold workgroup must not span both share regions");
-__global__ void __launch_bounds__(kFoldElems * kFoldGroups)
-fold_shares_kernel(const float *__restrict__ density_shares, uint32_t n_d, const float *__restrict__ colour_shares,
-                   uint32_t n_c, float inv_scale, float *__restrict__ dW)
-{
-    __shared__ float part[kFoldGroups][kFoldElems];
-    const uint32_t col = threadIdx.x % kFoldElems, group = threadIdx.x / kFoldElems;
-    const uint32_t e = blockIdx.x * kFoldElems + col;
-    float s0 = 0.0f, s1 = 0.0f;
-    if (e < (uint32_t)kTotal) {
-        const bool dens = e < (uint32_t)oWc1;
-        const float *src = dens ? density_shares + e : colour_shares + (e - oWc1);
-        const uint32_t stride = dens ? oWc1 : kTotal - oWc1, n = dens ? n_d : n_c;
-        uint32_t b = group;
-        for (; b + kFoldGroups < n; b += 2 * kFoldGroups) {
-            s0 += src[(size_t)b * stride];
-            s1 += src[(size_t)(b + kFoldGroups) * stride];
+        for (uint32_t t = 0; t < 2; ++t) {
+            if (group == t) add_share(share + oWd1, first, NF, HD, t, 0, lane, gWd1[t]);
+            if (group == 2 + t) add_share(share + oWd2, first, HD, NG, 0, t, lane, gWd2[t]);
         }
-        if (b < n) s0 += src[(size_t)b * stride];
-    }
-    part[group][col] = s0 + s1;
-    __syncthreads();
-    if (group == 0 && e < (uint32_t)kTotal) {
-        float s = 0.0f;
-#pragma unroll
-        for (int k = 0; k < kFoldGroups; ++k) s += part[k][col];
-        dW[e] += s * inv_scale;
-    }
+    });
 }
 
 // dW[kTotal + o * NA + a] += inv_scale * sum_rows row_delta[row][o] * app[row][a].  A workgroup of four row groups
@@ -759,8 +596,6 @@ zero_kernel(float *__restrict__ p, uint64_t n)
 constexpr uint32_t kGridColour = 512;      // persistent workgroups: two per compute unit of MI355X
 constexpr uint32_t kGridDensity = 512;     // the lighter kernel fits two workgroups per compute unit
 
-inline size_t align256(size_t x) { return (x + 255) / 256 * 256; }
-
 }  // namespace dg_mlp_mfma
 
 namespace dg {
@@ -769,8 +604,8 @@ size_t mlp_mfma_workspace_bytes(uint64_t N, uint32_t n_app, uint32_t S)
 {
     using namespace dg_mlp_mfma;
     const uint64_t n_rows = n_app ? (N + S - 1) / S : 0;
-    return align256((size_t)kGridDensity * kWavesPerBlock * oWc1 * sizeof(float)) +
-           align256((size_t)kGridColour * kWavesPerBlock * (kTotal - oWc1) * sizeof(float)) + align256((size_t)N * 32) +
+    return align256((size_t)kGridDensity * oWc1 * sizeof(float)) +
+           align256((size_t)kGridColour * (kTotal - oWc1) * sizeof(float)) + align256((size_t)N * 32) +
            align256((size_t)n_rows * HC * sizeof(float));
 }
 
@@ -825,9 +660,9 @@ void mlp_mfma_bwd(const void *weights, const void *feat, bool rows, uint32_t n_m
     const uint32_t grid_d = (uint32_t)(blocks_needed < kGridDensity ? blocks_needed : kGridDensity);
     char *base = static_cast<char *>(ws);
     float *density_shares = reinterpret_cast<float *>(base);
-    float *colour_shares = reinterpret_cast<float *>(base + align256((size_t)kGridDensity * kWavesPerBlock * oWc1 * sizeof(float)));
+    float *colour_shares = reinterpret_cast<float *>(base + align256((size_t)kGridDensity * oWc1 * sizeof(float)));
     h8 *dgeo = reinterpret_cast<h8 *>(reinterpret_cast<char *>(colour_shares) +
-                                      align256((size_t)kGridColour * kWavesPerBlock * (kTotal - oWc1) * sizeof(float)));
+                                      align256((size_t)kGridColour * (kTotal - oWc1) * sizeof(float)));
     float *row_delta = reinterpret_cast<float *>(reinterpret_cast<char *>(dgeo) + align256((size_t)N * 32));
     const uint64_t n_rows = n_app ? (N + S - 1) / S : 0;
     const __half *w = (const __half *)weights, *f = (const __half *)feat, *dr = (const __half *)dir_enc, *ap = (const __half *)app;
@@ -841,8 +676,9 @@ void mlp_mfma_bwd(const void *weights, const void *feat, bool rows, uint32_t n_m
     });
     if (rows) density_bwd_kernel<true><<<grid_d, kBlock, 0, st>>>(w, f, N, dgeo, loss_scale, n_merged, dfeat, density_shares);
     else density_bwd_kernel<false><<<grid_d, kBlock, 0, st>>>(w, f, N, dgeo, loss_scale, 0, dfeat, density_shares);
-    fold_shares_kernel<<<(kTotal + kFoldElems - 1) / kFoldElems, kFoldElems * kFoldGroups, 0, st>>>(
-        density_shares, grid_d * kWavesPerBlock, colour_shares, grid_c * kWavesPerBlock, 1.0f / loss_scale, dW);
+    static_assert(oWc1 % kFoldElems == 0, "a fold workgroup must not span both share regions");
+    fold_shares_kernel<<<(kTotal + kFoldElems - 1) / kFoldElems, kFoldElems * kFoldGroups, 0, st>>>(density_shares, grid_d, oWc1, colour_shares, grid_c,
+                                                                                                   kTotal, 1.0f / loss_scale, dW);
     if (n_app) {
         const uint64_t batches = (n_rows + 8 * kWgradGroups - 1) / (8 * kWgradGroups);
         const uint32_t grid_a = (uint32_t)(batches < kWgradGrid ? batches : kWgradGrid);

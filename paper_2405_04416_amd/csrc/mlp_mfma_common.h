@@ -1,0 +1,206 @@
+// Matrix-core building blocks of the field MLPs: operand images, the product, transposes on the matrix cores, weight-gradient
+// shares.  Internal, not part of the ABI.
+//
+// Operand and result layouts (lane = 32 h + c, element j / register r):
+//   A[row c][k = 8 h + j]     B[k = 8 h + j][col c]     D[row 8 (r / 4) + 4 h + r % 4][col c]
+// "Images" are weight tiles pre-arranged in LDS so that one 16-byte read per lane yields an operand.
+#pragma once
+#include "dg_internal.h"
+
+namespace dg_mlp_mfma {
+
+typedef _Float16 h8 __attribute__((ext_vector_type(8)));
+typedef float f16v __attribute__((ext_vector_type(16)));
+
+constexpr int kBlock = 256;
+constexpr int kWavesPerBlock = kBlock / 64;
+
+// feature held by slot j of lane half h in k-step ks
+__device__ __forceinline__ int feat_tiled(int ks, int h, int j) { return 32 * (ks >> 1) + 8 * (2 * (ks & 1) + (j >> 2)) + 4 * h + (j & 3); }
+__device__ __forceinline__ int feat_natural(int ks, int h, int j) { return 16 * ks + 8 * h + j; }
+
+// kind: 0 tiled, 1 natural, 2 colour-net input (k-step 0 tiled geometry, k-step 1 natural direction)
+__device__ __forceinline__ int feat_of(int kind, int ks, int h, int j)
+{
+    if (kind == 0) return feat_tiled(ks, h, j);
+    if (kind == 1) return feat_natural(ks, h, j);
+    return ks == 0 ? feat_tiled(0, h, j) : feat_natural(1, h, j);
+}
+
+// A-operand image of a weight matrix W[n_out][n_in] (row-major): rows = outputs (transpose == false)
+// or rows = inputs (transpose == true, for the data gradient)
+__device__ void build_image(__half *img, const __half *W, int n_out, int n_in, int rows_real, int k_real,
+                            int n_mt, int n_ks, int kind, bool transpose)
+{
+    for (int idx = threadIdx.x; idx < n_mt * n_ks * 512; idx += kBlock) {
+        const int j = idx & 7, lane = (idx >> 3) & 63, chunk = idx >> 9;
+        const int ks = chunk % n_ks, mt = chunk / n_ks;
+        const int row = 32 * mt + (lane & 31), k = feat_of(kind, ks, lane >> 5, j);
+        __half v = __float2half(0.0f);
+        if (row < rows_real && k < k_real) v = transpose ? W[k * n_in + row] : W[row * n_in + k];
+        img[idx] = v;
+    }
+    (void)n_out;
+}
+
+__device__ void build_selection(__half *img, int kind)
+{
+    for (int idx = threadIdx.x; idx < 2 * 512; idx += kBlock) {
+        const int j = idx & 7, lane = (idx >> 3) & 63, p = idx >> 9;
+        const int f = (kind == 0 ? feat_tiled(p, lane >> 5, j) : feat_natural(p, lane >> 5, j)) & 31;
+        img[idx] = __float2half(f == (lane & 31) ? 1.0f : 0.0f);
+    }
+}
+
+__device__ __forceinline__ h8 image(const __half *lds, int chunk, int lane)
+{
+    return reinterpret_cast<const h8 *>(lds)[chunk * 64 + lane];
+}
+
+// Returns its argument, in a way the compiler cannot see through: LDS reads indexed with the result are
+// issued where they are used, not hoisted out of the tile loop and held in registers for its whole length.
+__device__ __forceinline__ int opaque(int x)
+{
+    asm volatile("" : "+v"(x));
+    return x;
+}
+
+__device__ __forceinline__ f16v mma(h8 a, h8 b, f16v c) { return __builtin_amdgcn_mfma_f32_32x32x16_f16(a, b, c, 0, 0, 0); }
+
+__device__ __forceinline__ f16v zero16()
+{
+    f16v z;
+#pragma unroll
+    for (int i = 0; i < 16; ++i) z[i] = 0.0f;
+    return z;
+}
+
+__device__ __forceinline__ float fast_sigmoid(float x)
+{
+    return __builtin_amdgcn_rcpf(1.0f + __builtin_amdgcn_exp2f(-1.4426950408889634f * x));
+}
+__device__ __forceinline__ float clip15(float x) { return fminf(fmaxf(x, -15.0f), 15.0f); }
+
+// max(x, 0) on four pairs of halves, one instruction per pair
+__device__ __forceinline__ h8 relu_pairs(h8 x)
+{
+    typedef uint32_t u4 __attribute__((ext_vector_type(4)));
+    u4 w = __builtin_bit_cast(u4, x);
+#pragma unroll
+    for (int i = 0; i < 4; ++i) asm("v_pk_max_f16 %0, %1, 0" : "=v"(w[i]) : "v"(w[i]));
+    return __builtin_bit_cast(h8, w);
+}
+
+// registers 8p .. 8p+7 of a result tile, activated, rounded to fp16 and packed: k-step (m, p) of the next operand
+template <int ACT>   // 0 identity, 1 ReLU, 2 sigmoid
+__device__ __forceinline__ h8 pack_half(const f16v &c, int p)
+{
+    h8 out;
+#pragma unroll
+    for (int j = 0; j < 8; ++j) {
+        float v = c[8 * p + j];
+        if (ACT == 2) v = fast_sigmoid(v);
+        out[j] = (_Float16)v;
+    }
+    // ReLU after the rounding gives the same values as before it (rounding is monotone and keeps 0) and works on pairs
+    if (ACT == 1) out = relu_pairs(out);
+    return out;
+}
+
+// transpose of one 32-feature tile of a packed tensor: x0 / x1 are the two k-steps that hold the tile,
+// sel0 / sel1 the matching selection images; result: the two sample k-steps of the transposed tile
+__device__ __forceinline__ void transpose_tile(h8 x0, h8 x1, h8 sel0, h8 sel1, h8 out[2])
+{
+    f16v c = zero16();
+    c = mma(x0, sel0, c);
+    c = mma(x1, sel1, c);
+    out[0] = pack_half<0>(c, 0);
+    out[1] = pack_half<0>(c, 1);
+}
+__device__ __forceinline__ void transpose_half_tile(h8 x0, h8 sel0, h8 out[2])
+{
+    f16v c = zero16();
+    c = mma(x0, sel0, c);
+    out[0] = pack_half<0>(c, 0);
+    out[1] = pack_half<0>(c, 1);
+}
+
+// delta = fp16(g * act'(a)) for one k-step; a is the packed (rounded) activation
+template <int ACT>   // 1 ReLU, 2 sigmoid
+__device__ __forceinline__ h8 delta_from(const f16v &g, int p, h8 a)
+{
+    h8 out;
+#pragma unroll
+    for (int j = 0; j < 8; ++j) {
+        const float av = (float)a[j];
+        const float d = ACT == 2 ? av * (1.0f - av) : (av > 0.0f ? 1.0f : 0.0f);
+        out[j] = (_Float16)(g[8 * p + j] * d);
+    }
+    return out;
+}
+
+// one tile of a wavefront's weight gradient into the workgroup's share in LDS; every word belongs to one lane
+__device__ __forceinline__ void add_share(float *share, bool first, int n_in, int rows_real, int ot, int it, int lane, const f16v &acc)
+{
+    const int h = lane >> 5, i = 32 * it + (lane & 31);
+#pragma unroll
+    for (int r = 0; r < 16; ++r) {
+        const int o = 32 * ot + 8 * (r >> 2) + 4 * h + (r & 3);
+        if (o < rows_real) share[o * n_in + i] = first ? acc[r] : share[o * n_in + i] + acc[r];
+    }
+}
+
+// The wavefronts of a workgroup add their weight gradients up in LDS before the workgroup writes its share: a quarter of the
+// shares to write and to fold (fold_shares_kernel 37 -> 8 us).  The gradient comes in four groups of tiles; in turn t
+// wavefront w adds group (w + t) % 4, so that all four work at once and every word still gets its addends in a fixed order.
+// The space is that of the weight images, which nobody needs any more.
+template <int N_WORDS, class Add>
+__device__ __forceinline__ void write_share(float *share, float *__restrict__ dst, Add add)
+{
+    static_assert(kWavesPerBlock == 4, "four wavefronts, four groups");
+    const uint32_t w = threadIdx.x >> 6;
+    for (uint32_t t = 0; t < 4; ++t) {
+        __syncthreads();
+        add(share, (w + t) & 3u, t == 0);
+    }
+    __syncthreads();
+    for (int i = threadIdx.x; i < N_WORDS; i += kBlock) dst[i] = share[i];
+}
+
+// dW[e] += (sum of the workgroups' shares of element e) / loss_scale, in a fixed order, e < n_total.  Elements below n_first
+// come from first_shares [n_a][n_first], the rest from rest_shares [n_b][n_total - n_first]; n_first is n_total or a multiple
+// of kFoldElems.  A workgroup serves 64 consecutive elements; 16 groups of threads each sum every 16th share, then the 16
+// partial sums are added in a fixed order.
+constexpr int kFoldElems = 64, kFoldGroups = 16;
+static __global__ void __launch_bounds__(kFoldElems * kFoldGroups)
+fold_shares_kernel(const float *__restrict__ first_shares, uint32_t n_a, uint32_t n_first, const float *__restrict__ rest_shares, uint32_t n_b,
+                   uint32_t n_total, float inv_scale, float *__restrict__ dW)
+{
+    __shared__ float part[kFoldGroups][kFoldElems];
+    const uint32_t col = threadIdx.x % kFoldElems, group = threadIdx.x / kFoldElems;
+    const uint32_t e = blockIdx.x * kFoldElems + col;
+    float s[4] = {0.0f, 0.0f, 0.0f, 0.0f};
+    if (e < n_total) {
+        const bool in_first = e < n_first;
+        const float *src = in_first ? first_shares + e : rest_shares + (e - n_first);
+        const uint32_t stride = in_first ? n_first : n_total - n_first, n = in_first ? n_a : n_b;
+        uint32_t b = group;
+        for (; b + 3 * kFoldGroups < n; b += 4 * kFoldGroups) {
+#pragma unroll
+            for (int k = 0; k < 4; ++k) s[k] += src[(size_t)(b + k * kFoldGroups) * stride];
+        }
+        for (; b < n; b += kFoldGroups) s[0] += src[(size_t)b * stride];
+    }
+    part[group][col] = (s[0] + s[1]) + (s[2] + s[3]);
+    __syncthreads();
+    if (group == 0 && e < n_total) {
+        float sum = 0.0f;
+#pragma unroll
+        for (int k = 0; k < kFoldGroups; ++k) sum += part[k][col];
+        dW[e] += sum * inv_scale;
+    }
+}
+
+inline size_t align256(size_t x) { return (x + 255) / 256 * 256; }
+
+}  // namespace dg_mlp_mfma
