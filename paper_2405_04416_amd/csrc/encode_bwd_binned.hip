@@ -16,6 +16,7 @@
 //     accumulate in LDS (as scaled 64-bit integers: integer adds are the fastest LDS atomics) and add the
 //     finished bin into dtable with coalesced atomics.
 #include "encode_common.h"
+#include <algorithm>
 #include <mutex>
 
 namespace dg_encode_binned {
@@ -32,14 +33,21 @@ constexpr uint32_t kMaxKeys = DG_MAX_LEVELS * kMaxBins;   // (level, bin) pairs 
 constexpr int kBinGrid = 768;                      // persistent binning workgroups (three per compute unit)
 constexpr int kAccBlock = 1024;                    // threads of an accumulate workgroup (one per compute unit: its table fills LDS)
 constexpr int kAccDepth = 4;                       // records in flight per accumulate thread
-constexpr int kAccRecordsLog2 = 17;
-constexpr uint32_t kAccRecords = 1u << kAccRecordsLog2;   // an accumulate workgroup sums at least this many records of a bin (or all it has) ...
-constexpr int kAccMaxLog2 = kAccRecordsLog2 + 1;          // ... and fewer than this many: a bin is cut into floor(records / kAccRecords) equal pieces
-// pieces a bin of `total` records is cut into: a bin with less than two pieces' worth stays whole (a second workgroup
-// would clear and write out a table of its own for little)
-__host__ __device__ __forceinline__ uint32_t acc_pieces(uint32_t total) { return total == 0u ? 0u : (total >> kAccRecordsLog2 ? total >> kAccRecordsLog2 : 1u); }
+// An accumulate workgroup sums at least 2^piece_log2 records of a bin (or all it has) and fewer than twice as many: a bin is
+// cut into floor(records / 2^piece_log2) equal pieces, so a bin with less than two pieces' worth stays whole (a second
+// workgroup would clear and write out a table of its own for little).  2^17 records where there are plenty; where the bins
+// are few and the records too, pieces shrink until some 512 workgroups have one (c1's grid, 33 k samples in three bins of 131 k
+// records: 46 -> 13 us).
+constexpr int kPieceLog2Min = 13, kPieceLog2Max = 17;
+constexpr int kAccMaxLog2 = kPieceLog2Max + 1;
+__host__ __device__ __forceinline__ uint32_t acc_pieces(uint32_t total, uint32_t piece_log2) { return total == 0u ? 0u : (total >> piece_log2 ? total >> piece_log2 : 1u); }
 constexpr int kCoarseBlock = 1024;                 // coarse prefix: threads per workgroup, persistent workgroups (one per compute unit)
 constexpr int kCoarseGrid = 256;
+
+// How a sweep's workgroups share the work: `groups` groups of `width` workgroups; workgroup w of group k takes the tiles w,
+// w + width, ... at the levels first_level + k, + groups, ...  One group where there are tiles enough for every workgroup
+// (neighbouring appends then meet in L2, level after level); with few tiles several groups go through fewer levels each.
+struct Sweep { uint32_t width, groups; };
 
 struct Plan {
     uint32_t first_level;                  // levels below are accumulated directly in LDS
@@ -180,23 +188,24 @@ __device__ __forceinline__ Emission classify(const LevelGeom &lv, uint32_t mask,
 // count sweep with this workgroup's counters in LDS: one LDS add per record, no barriers inside the sweep.  Launched
 // with the fill sweep's grid and tiling: kTile threads that take one tile per step, or 2 * kTile that take two.
 __global__ void __launch_bounds__(2 * kTile)
-count_lds_kernel(dg_grid_desc g, Plan plan, const float *__restrict__ u, uint64_t n0, uint64_t nb, uint32_t *__restrict__ rows)
+count_lds_kernel(dg_grid_desc g, Plan plan, Sweep sw, const float *__restrict__ u, uint64_t n0, uint64_t nb, uint32_t *__restrict__ rows)
 {
     extern __shared__ uint32_t smem[];
     uint32_t *row = smem;                                // [n_keys]
+    const uint32_t me = blockIdx.x % sw.width, first_level = plan.first_level + blockIdx.x / sw.width;
     const uint32_t tid = threadIdx.x, in_tile = tid % kTile;
     const int lane = tid % dg::kWave;
     const uint32_t mask = (1u << g.log2_T) - 1u;
     for (uint32_t i = tid; i < plan.n_keys; i += blockDim.x) row[i] = 0u;
     __syncthreads();
     const uint64_t n_tiles = (nb + kTile - 1) / kTile;
-    const uint64_t stride = (uint64_t)(blockDim.x / kTile) * gridDim.x;
-    for (uint64_t tile = blockIdx.x + (uint64_t)(tid / kTile) * gridDim.x; tile < n_tiles; tile += stride) {
+    const uint64_t stride = (uint64_t)(blockDim.x / kTile) * sw.width;
+    for (uint64_t tile = me + (uint64_t)(tid / kTile) * sw.width; tile < n_tiles; tile += stride) {
         const uint64_t rel = tile * kTile + in_tile;
         const bool live = rel < nb;
         const uint64_t n = n0 + (live ? rel : nb - 1);
         const float uu[3] = {u[3 * n], u[3 * n + 1], u[3 * n + 2]};
-        for (uint32_t l = plan.first_level; l < g.n_levels; ++l) {
+        for (uint32_t l = first_level; l < g.n_levels; l += sw.groups) {
             const Emission em = classify(level_of(g, l), mask, uu, live, lane);
             if (em.emit) {
                 uint32_t *c = row + plan.key_base[l];
@@ -206,8 +215,9 @@ count_lds_kernel(dg_grid_desc g, Plan plan, const float *__restrict__ u, uint64_
         }
     }
     __syncthreads();
-    uint32_t *row_global = rows + (size_t)blockIdx.x * plan.n_keys;
-    for (uint32_t i = tid; i < plan.n_keys; i += blockDim.x) row_global[i] = row[i];
+    uint32_t *row_global = rows + (size_t)me * plan.n_keys;
+    for (uint32_t l = first_level; l < g.n_levels; l += sw.groups)
+        for (uint32_t i = plan.key_base[l] + tid; i < plan.key_base[l + 1]; i += blockDim.x) row_global[i] = row[i];
 }
 
 template <int CTRL, int ROW_MASK>
@@ -378,7 +388,7 @@ __device__ __forceinline__ void copy_step(uint32_t total, uint32_t tid, const ui
 }
 
 __global__ void __launch_bounds__(kNarrowThreads, 7)     // three workgroups of nine wavefronts per compute unit: seven wavefronts per SIMD
-fill_narrow_kernel(dg_grid_desc g, Plan plan, const float *__restrict__ u, const float2 *__restrict__ dfeat, uint64_t N,
+fill_narrow_kernel(dg_grid_desc g, Plan plan, Sweep sw, const float *__restrict__ u, const float2 *__restrict__ dfeat, uint64_t N,
                    uint64_t n0, uint64_t nb, const uint32_t *__restrict__ rows, const uint32_t *__restrict__ binbase,
                    uint4 *__restrict__ queue, float *__restrict__ dtable, uint32_t *__restrict__ largest_out)
 {
@@ -393,22 +403,23 @@ fill_narrow_kernel(dg_grid_desc g, Plan plan, const float *__restrict__ u, const
     const bool keeper = tid >= (uint32_t)kTile;                       // the last wavefront: kTile is a multiple of 64
     const uint32_t lane = tid % dg::kWave;
     const uint32_t mask = (1u << g.log2_T) - 1u;
-    const uint32_t *row_global = rows + (size_t)blockIdx.x * plan.n_keys;
+    const uint32_t me = blockIdx.x % sw.width, first_level = plan.first_level + blockIdx.x / sw.width;
+    const uint32_t *row_global = rows + (size_t)me * plan.n_keys;
     if (tid < 128) cnt[tid] = 0u;
     __syncthreads();
     uint32_t parity = 0, largest = 0;
     const uint64_t n_tiles = (nb + kTile - 1) / kTile;
-    const bool has_work = blockIdx.x < n_tiles;
+    const bool has_work = me < n_tiles && first_level < g.n_levels;
 
     if (keeper) {
         // lane b keeps the books of bin b: where its next append goes and how many records wait
         uint32_t pos = 0, waiting = 0;
         const uint4 zero4 = make_uint4(0u, 0u, 0u, 0u);
-        for (uint32_t l = plan.first_level; l < g.n_levels; ++l) {
+        for (uint32_t l = first_level; l < g.n_levels; l += sw.groups) {
             const uint32_t n_bins = plan.n_bins[l], key0 = plan.key_base[l];
             const bool mine = lane < n_bins;
             if (mine) pos = binbase[key0 + lane] + row_global[key0 + lane];
-            for (uint64_t tile = blockIdx.x; tile < n_tiles; tile += gridDim.x, parity ^= 1u) {
+            for (uint64_t tile = me; tile < n_tiles; tile += sw.width, parity ^= 1u) {
                 __syncthreads();                                     // ranks taken
                 // from what waits and what is fresh: how much goes out (whole granules) and how much is left; the
                 // granules of all bins laid end to end, with a table of which bin owns each
@@ -469,12 +480,12 @@ fill_narrow_kernel(dg_grid_desc g, Plan plan, const float *__restrict__ u, const
     }
 
     StepAhead ahead = {{0.0f, 0.0f, 0.0f}, make_float2(0.0f, 0.0f)};
-    if (has_work) load_ahead(ahead, u, dfeat, N, n0, nb, blockIdx.x, plan.first_level, tid);
+    if (has_work) load_ahead(ahead, u, dfeat, N, n0, nb, me, first_level, tid);
     // taken in before the loop, as every later load is before its step ends: the top of a step then waits for nothing
     asm volatile("" : "+v"(ahead.u[0]), "+v"(ahead.u[1]), "+v"(ahead.u[2]), "+v"(ahead.g.x), "+v"(ahead.g.y));
-    for (uint32_t l = plan.first_level; l < g.n_levels; ++l) {
+    for (uint32_t l = first_level; l < g.n_levels; l += sw.groups) {
         const LevelGeom lv = level_of(g, l);
-        for (uint64_t tile = blockIdx.x; tile < n_tiles; tile += gridDim.x, parity ^= 1u) {
+        for (uint64_t tile = me; tile < n_tiles; tile += sw.width, parity ^= 1u) {
             uint32_t *c_cur = cnt + 64u * parity;
             const bool live = tile * kTile + tid < nb;
             const float uu[3] = {ahead.u[0], ahead.u[1], ahead.u[2]};
@@ -483,9 +494,9 @@ fill_narrow_kernel(dg_grid_desc g, Plan plan, const float *__restrict__ u, const
             // hides their latency.  (Asked for after the copy, the wait for them would also wait for the copy's
             // stores, which have only just been issued.)
             {
-                const bool same_level = tile + gridDim.x < n_tiles;
-                const uint32_t l_next = same_level ? l : l + 1;
-                if (l_next < g.n_levels) load_ahead(ahead, u, dfeat, N, n0, nb, same_level ? tile + gridDim.x : blockIdx.x, l_next, tid);
+                const bool same_level = tile + sw.width < n_tiles;
+                const uint32_t l_next = same_level ? l : l + sw.groups;
+                if (l_next < g.n_levels) load_ahead(ahead, u, dfeat, N, n0, nb, same_level ? tile + sw.width : me, l_next, tid);
             }
             const Emission em = classify(lv, mask, uu, live, (int)lane);
             uint32_t rank[4];
@@ -542,7 +553,7 @@ constexpr int kRingThreads = 1024, kRingGrid = 256, kRingSlots = 4, kRingRounds 
 constexpr int kRingLds = kMaxBins * (kRingSlots * 16 + 4 + 4 + 2 * 2) + 16;
 
 __global__ void __launch_bounds__(kRingThreads)
-fill_ring_kernel(dg_grid_desc g, Plan plan, const float *__restrict__ u, const float2 *__restrict__ dfeat, uint64_t N,
+fill_ring_kernel(dg_grid_desc g, Plan plan, Sweep sw, const float *__restrict__ u, const float2 *__restrict__ dfeat, uint64_t N,
                  uint64_t n0, uint64_t nb, const uint32_t *__restrict__ rows, const uint32_t *__restrict__ binbase,
                  uint4 *__restrict__ queue, float *__restrict__ dtable, uint32_t *__restrict__ largest_out)
 {
@@ -557,18 +568,19 @@ fill_ring_kernel(dg_grid_desc g, Plan plan, const float *__restrict__ u, const f
     const int lane = tid % dg::kWave;
     const uint32_t half = tid / kTile, in_tile = tid % kTile;         // the workgroup takes two tiles per step
     const uint32_t mask = (1u << g.log2_T) - 1u;
-    const uint32_t *row = rows + (size_t)blockIdx.x * plan.n_keys;
+    const uint32_t me = blockIdx.x % sw.width, first_level = plan.first_level + blockIdx.x / sw.width;
+    const uint32_t *row = rows + (size_t)me * plan.n_keys;
     const uint4 zero4 = make_uint4(0u, 0u, 0u, 0u);
     uint32_t largest = 0, parity = 0;
     const uint64_t n_tiles = (nb + kTile - 1) / kTile;
-    const uint64_t stride = 2ull * gridDim.x;                         // tiles between two steps of one half
-    const uint64_t first_tile = blockIdx.x + (uint64_t)half * gridDim.x;
+    const uint64_t stride = 2ull * sw.width;                          // tiles between two steps of one half
+    const uint64_t first_tile = me + (uint64_t)half * sw.width;
     // steps of the workgroup: until its first half runs out of tiles (the second half's tiles come later in the order)
-    const uint64_t n_steps = blockIdx.x < n_tiles ? (n_tiles - blockIdx.x + stride - 1) / stride : 0;
+    const uint64_t n_steps = me < n_tiles ? (n_tiles - me + stride - 1) / stride : 0;
     StepAhead ahead = {{0.0f, 0.0f, 0.0f}, make_float2(0.0f, 0.0f)};
-    if (first_tile < n_tiles) load_ahead(ahead, u, dfeat, N, n0, nb, first_tile, plan.first_level, in_tile);
+    if (first_tile < n_tiles && first_level < g.n_levels) load_ahead(ahead, u, dfeat, N, n0, nb, first_tile, first_level, in_tile);
     if (tid < 2) n_list[tid] = 0u;
-    for (uint32_t l = plan.first_level; l < g.n_levels; ++l) {
+    for (uint32_t l = first_level; l < g.n_levels; l += sw.groups) {
         const uint32_t n_bins = plan.n_bins[l], key0 = plan.key_base[l];
         const LevelGeom lv = level_of(g, l);
         __syncthreads();                                              // the last level's books are closed
@@ -583,7 +595,7 @@ fill_ring_kernel(dg_grid_desc g, Plan plan, const float *__restrict__ u, const f
             // the next step's inputs are asked for before this step's stores (loads and stores of a wavefront retire in order)
             {
                 const bool same_level = step + 1 < n_steps;
-                const uint32_t l_next = same_level ? l : l + 1;
+                const uint32_t l_next = same_level ? l : l + sw.groups;
                 const uint64_t t_next = same_level ? tile + stride : first_tile;
                 if (l_next < g.n_levels && t_next < n_tiles) load_ahead(ahead, u, dfeat, N, n0, nb, t_next, l_next, in_tile);
             }
@@ -686,20 +698,20 @@ scan_rows_kernel(uint32_t *__restrict__ rows, uint32_t n_rows, uint32_t n_keys, 
 // first record, end) -- a bin is cut into acc_pieces of its record count, in equal shares, so that work is balanced whatever
 // the bins hold, and a workgroup finds its share with one load.  (One workgroup; n_keys is at most a few tens of thousands.)
 __global__ void __launch_bounds__(1024)
-scan_totals_kernel(const uint32_t *__restrict__ totals, uint32_t n_keys, uint32_t *__restrict__ binbase, uint4 *__restrict__ pieces)
+scan_totals_kernel(const uint32_t *__restrict__ totals, uint32_t n_keys, uint32_t piece_log2, uint32_t *__restrict__ binbase, uint4 *__restrict__ pieces)
 {
     __shared__ uint32_t wave_sum[16], wave_pieces[16];
     const uint32_t per = (n_keys + 1023) / 1024, lo = min(threadIdx.x * per, n_keys), hi = min(lo + per, n_keys);
     const uint32_t lane = threadIdx.x % dg::kWave, wave = threadIdx.x / dg::kWave;
     uint32_t s = 0, sp = 0;
-    for (uint32_t i = lo; i < hi; ++i) { s += totals[i]; sp += acc_pieces(totals[i]); }
+    for (uint32_t i = lo; i < hi; ++i) { s += totals[i]; sp += acc_pieces(totals[i], piece_log2); }
     const uint32_t incl = wave_inclusive_scan(s), incl_p = wave_inclusive_scan(sp);
     if (lane == dg::kWave - 1) { wave_sum[wave] = incl; wave_pieces[wave] = incl_p; }
     __syncthreads();
     uint32_t run = incl - s, run_p = incl_p - sp;
     for (uint32_t w = 0; w < wave; ++w) { run += wave_sum[w]; run_p += wave_pieces[w]; }
     for (uint32_t i = lo; i < hi; ++i) {
-        const uint32_t total = totals[i], n = acc_pieces(total), share = n ? (total + n - 1u) / n : 0u;
+        const uint32_t total = totals[i], n = acc_pieces(total, piece_log2), share = n ? (total + n - 1u) / n : 0u;
         binbase[i] = run;
         for (uint32_t q = 0; q < n; ++q) pieces[1 + run_p++] = make_uint4(i, run + q * share, run + min((q + 1u) * share, total), 0u);
         run += total;
@@ -828,10 +840,32 @@ struct Layout {
 // both sweeps pad every workgroup's slice of every bin to whole granules: 8 records with few bins, 4 with many
 uint32_t sweep_grid(const Plan &p) { return p.max_bins <= 64 ? (uint32_t)kBinGrid : (uint32_t)kRingGrid; }
 uint32_t slice_round(const Plan &p) { return p.max_bins <= 64 ? kSliceRound : (uint32_t)kRingSlots; }
+// width and groups of the sweeps over n_tiles tiles at n_levels levels: the split with the fewest (tile, level) steps per
+// workgroup, one group unless another saves a thirtieth.  (185 k samples at 13 levels, 361 tiles for 768 workgroups: 13 steps
+// in one group, 8 in 13 groups of 59; 830 k samples: 39 and 28.)
+Sweep choose_sweep(const Plan &p, uint32_t n_levels, uint64_t n_tiles)
+{
+    const uint32_t grid = sweep_grid(p), levels = n_levels - p.first_level, per_step = p.max_bins <= 64 ? 1u : 2u;
+    Sweep best = {grid, 1};
+    double least = 0.0;
+    for (uint32_t k = 1; k <= levels; ++k) {
+        const uint32_t width = grid / k;
+        const double steps = (double)((n_tiles + (uint64_t)per_step * width - 1) / ((uint64_t)per_step * width)) * ((levels + k - 1) / k);
+        if (k == 1 || steps < least * (29.0 / 30.0)) { best = {width, k}; least = steps; }
+    }
+    return best;
+}
 uint64_t slice_padding(const Plan &p) { return (uint64_t)sweep_grid(p) * p.n_keys * (slice_round(p) - 1u); }
 
+uint32_t piece_log2(uint64_t records)
+{
+    uint32_t k = kPieceLog2Min;
+    while (k < (uint32_t)kPieceLog2Max && records >> (k + 1) >= 512) ++k;
+    return k;
+}
+
 // accumulate workgroups that `records` records need at most
-uint32_t acc_grid(const Plan &p, uint64_t records) { return (uint32_t)(records / kAccRecords) + p.n_keys; }
+uint32_t acc_grid(const Plan &p, uint64_t records) { return (uint32_t)(records >> piece_log2(records)) + p.n_keys; }
 
 // workspace layout for a batch of `batch` samples
 Layout make_layout(const dg_grid_desc *d, const Plan &p, uint64_t batch)
@@ -842,13 +876,17 @@ Layout make_layout(const dg_grid_desc *d, const Plan &p, uint64_t batch)
     L.rows = off; off = align256(off + (size_t)sweep_grid(p) * p.n_keys * 4);
     L.totals = off; off = align256(off + (size_t)p.n_keys * 4);
     L.binbase = off; off = align256(off + (size_t)(p.n_keys + 2) * 4);      // + the largest record magnitude
-    L.pieces = off; off = align256(off + (size_t)(1 + acc_grid(p, records)) * 16);
+    // a smaller batch may have smaller pieces: never more than 1024 beyond one per bin while they are not at their largest
+    L.pieces = off; off = align256(off + (size_t)(1 + std::max(acc_grid(p, records), 1024u + p.n_keys)) * 16);
     L.queue = off; off = align256(off + records * 16);
     L.total = off;
     L.batch = batch;
     L.records = records;
     return L;
 }
+
+// records that nb samples make at most, with the padding of the slices
+uint64_t batch_records(const Plan &p, uint32_t n_levels, uint64_t nb) { return nb * 4ull * (n_levels - p.first_level) + slice_padding(p); }
 
 uint64_t max_batch(const dg_grid_desc *d, const Plan &p)
 {
@@ -883,7 +921,6 @@ struct Prepared {
     Layout L;
     uint32_t *rows, *totals, *binbase;
     uint4 *pieces, *queue;
-    uint32_t grid;
     bool narrow;
 };
 
@@ -922,7 +959,6 @@ int prepare(const char *who, const dg_grid_desc *d, uint32_t from_level, uint64_
     q.pieces = reinterpret_cast<uint4 *>(base + q.L.pieces);
     q.queue = reinterpret_cast<uint4 *>(base + q.L.queue);
     q.narrow = q.p.max_bins <= 64;                 // then n_keys <= 64 * DG_MAX_LEVELS
-    q.grid = sweep_grid(q.p);                      // persistent workgroups of the count and fill sweeps (same tiling)
     return DG_OK;
 }
 
@@ -931,12 +967,13 @@ int prepare(const char *who, const dg_grid_desc *d, uint32_t from_level, uint64_
 void launch_count(const Prepared &q, const dg_grid_desc *d, const float *u, uint64_t n0, uint64_t nb, hipStream_t st)
 {
     const Plan &p = q.p;
-    count_lds_kernel<<<q.grid, q.narrow ? kTile : kRingThreads, p.n_keys * 4, st>>>(*d, p, u, n0, nb, q.rows);
+    const Sweep sw = choose_sweep(p, d->n_levels, (nb + kTile - 1) / kTile);
+    count_lds_kernel<<<sw.width * sw.groups, q.narrow ? kTile : kRingThreads, p.n_keys * 4, st>>>(*d, p, sw, u, n0, nb, q.rows);
     const uint32_t scan_grid = (p.n_keys + kScanKeys - 1) / kScanKeys;
     static_assert(kBinGrid == 24 * kScanGroups && kRingGrid == 8 * kScanGroups, "the scan holds a group's rows in registers");
-    if (q.narrow) scan_rows_kernel<24><<<scan_grid, kScanKeys * kScanGroups, 0, st>>>(q.rows, q.grid, p.n_keys, slice_round(p), q.totals);
-    else scan_rows_kernel<8><<<scan_grid, kScanKeys * kScanGroups, 0, st>>>(q.rows, q.grid, p.n_keys, slice_round(p), q.totals);
-    scan_totals_kernel<<<1, 1024, 0, st>>>(q.totals, p.n_keys, q.binbase, q.pieces);
+    if (q.narrow) scan_rows_kernel<24><<<scan_grid, kScanKeys * kScanGroups, 0, st>>>(q.rows, sw.width, p.n_keys, slice_round(p), q.totals);
+    else scan_rows_kernel<8><<<scan_grid, kScanKeys * kScanGroups, 0, st>>>(q.rows, sw.width, p.n_keys, slice_round(p), q.totals);
+    scan_totals_kernel<<<1, 1024, 0, st>>>(q.totals, p.n_keys, piece_log2(batch_records(p, d->n_levels, nb)), q.binbase, q.pieces);
 }
 
 }  // namespace
@@ -973,13 +1010,14 @@ int encode_bwd_binned(const char *who, const dg_grid_desc *d, uint32_t from_leve
     for (uint64_t n0 = 0; n0 < N; n0 += batch) {
         const uint64_t nb = N - n0 < batch ? N - n0 : batch;
         if (!counted) launch_count(q, d, u, n0, nb, st);
+        const Sweep sw = choose_sweep(p, d->n_levels, (nb + kTile - 1) / kTile);
         if (q.narrow)
-            fill_narrow_kernel<<<kBinGrid, kNarrowThreads, kNarrowLds, st>>>(*d, p, u, (const float2 *)dfeat, N, n0, nb, q.rows, q.binbase, q.queue,
-                                                                             dtable, q.binbase + p.n_keys + 1);
+            fill_narrow_kernel<<<sw.width * sw.groups, kNarrowThreads, kNarrowLds, st>>>(*d, p, sw, u, (const float2 *)dfeat, N, n0, nb, q.rows, q.binbase,
+                                                                                        q.queue, dtable, q.binbase + p.n_keys + 1);
         else
-            fill_ring_kernel<<<q.grid, kRingThreads, p.max_bins * (kRingSlots * 16 + 12) + 16, st>>>(*d, p, u, (const float2 *)dfeat, N, n0, nb, q.rows,
-                                                                                                    q.binbase, q.queue, dtable, q.binbase + p.n_keys + 1);
-        const uint64_t records = nb * 4ull * (d->n_levels - p.first_level) + slice_padding(p);
+            fill_ring_kernel<<<sw.width * sw.groups, kRingThreads, p.max_bins * (kRingSlots * 16 + 12) + 16, st>>>(
+                *d, p, sw, u, (const float2 *)dfeat, N, n0, nb, q.rows, q.binbase, q.queue, dtable, q.binbase + p.n_keys + 1);
+        const uint64_t records = batch_records(p, d->n_levels, nb);
         accumulate_kernel<<<acc_grid(p, records), kAccBlock, 2 * kChunk * sizeof(double), st>>>(*d, p, q.binbase, q.pieces, (const u32x4 *)q.queue, dtable);
     }
     return launch_status(who);
