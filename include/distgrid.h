@@ -202,7 +202,8 @@ typedef struct dg_order_desc {
 int dg_order_desc_init(dg_order_desc *order, const dg_grid_desc *desc, uint64_t N);
 /* ordered [N] of 16 bytes each (x, y, z fp32 and the sample's index, uint32; device, 16-byte aligned);
  * pieces: dg_order_pieces_words(order, N) words that list which stretch of the order belongs to which brick (read by
- * dg_hashgrid_encode_bwd_ordered; 8-byte aligned).  N < 2^32 - 1.
+ * dg_hashgrid_encode_bwd_ordered; 8-byte aligned).  Its word 1 is set to 0 and left to the caller: room for the `largest`
+ * word of dg_mlp_bwd_rows.  N < 2^32 - 1.
  * ws: dg_order_workspace_bytes(order) bytes of device memory, 256-byte aligned. */
 size_t dg_order_workspace_bytes(const dg_order_desc *order);
 size_t dg_order_pieces_words(const dg_order_desc *order, uint64_t N);
@@ -213,15 +214,17 @@ int dg_hashgrid_encode_fwd_ordered(const dg_grid_desc *desc, const float *table,
                                    void *feat, void *stream);
 /* dg_hashgrid_encode_bwd on the sorted list.  dfeat: rows [N, 2 * n_merged] fp32 of the merged levels (16-byte aligned, in
  * the samples' original order), then the planes [L - n_merged, N, 2] of the others -- as dg_mlp_bwd_rows writes it; u [N,3]
- * the samples in their original order.  The merged levels are summed in fp64 per brick; the others go through the bins as
- * in dg_hashgrid_encode_bwd, with its precision.  counted != 0: the queues have been laid out by ..._ordered_count (rules as
+ * the samples in their original order.  *largest: device word, the bit pattern of a float that no |dfeat| exceeds.  The
+ * merged levels are summed per brick in fixed point, exactly and in quanta of 2^-37 of that magnitude or finer; the others go
+ * through the bins as in dg_hashgrid_encode_bwd, with its precision.  Where *largest is infinite or NaN every brick leaves
+ * NaN in one entry of each merged level.  counted != 0: the queues have been laid out by ..._ordered_count (rules as
  * for dg_hashgrid_encode_bwd_count). */
 size_t dg_hashgrid_encode_bwd_ordered_workspace_bytes(const dg_grid_desc *desc, const dg_order_desc *order, uint64_t N);
 int dg_hashgrid_encode_bwd_ordered_count(const dg_grid_desc *desc, const dg_order_desc *order, const float *u, uint64_t N,
                                          void *ws, size_t ws_bytes, void *stream);
 int dg_hashgrid_encode_bwd_ordered(const dg_grid_desc *desc, const dg_order_desc *order, const void *ordered,
-                                   const uint32_t *pieces, const float *u, const float *dfeat, uint64_t N, float *dtable,
-                                   void *ws, size_t ws_bytes, uint32_t counted, void *stream);
+                                   const uint32_t *pieces, const float *u, const float *dfeat, const uint32_t *largest, uint64_t N,
+                                   float *dtable, void *ws, size_t ws_bytes, uint32_t counted, void *stream);
 
 /* ------------------------------------------------------------------------------------
  * Field MLPs (Sec. 3.2: a small MLP fuses the level features; Sec. 5.1: sigmoid hidden activation in the colour
@@ -337,7 +340,8 @@ int dg_mlp_composite_fwd(const dg_mlp_desc *desc, const void *weights, const voi
 /* The network calls on sample-major feature rows (dg_hashgrid_encode_fwd_ordered): feat [N, 32] fp16, 16-byte aligned, else
  * as dg_mlp_fwd_app, dg_mlp_composite_fwd and dg_mlp_bwd_app (app NULL without appearance inputs; same workspace).  The
  * feature gradient comes as dg_hashgrid_encode_bwd_ordered reads it: rows [N, 2 * n_merged] fp32 for levels below n_merged
- * (even; dg_order_desc.n_merged), then planes [16 - n_merged, N, 2] for the others; dfeat 16-byte aligned.
+ * (even; dg_order_desc.n_merged), then planes [16 - n_merged, N, 2] for the others; dfeat 16-byte aligned.  *largest (device
+ * word) is raised to the bit pattern of the largest |dfeat| (infinity if one is NaN) if it holds less; the caller zeroes it.
  * DG_ERR_UNSUPPORTED unless the network is the 32-64-16 / (32 + n_app)-64-64-3 one. */
 int dg_mlp_fwd_rows(const dg_mlp_desc *desc, const void *weights, const void *feat, const void *dir_enc, const void *app,
                     uint32_t S, uint64_t N, float *sigma, float *rgb, void *stream);
@@ -347,7 +351,7 @@ int dg_mlp_composite_fwd_rows(const dg_mlp_desc *desc, const void *weights, cons
                               float *Dk, void *stream);
 int dg_mlp_bwd_rows(const dg_mlp_desc *desc, const void *weights, const void *feat, const void *dir_enc, const void *app,
                     uint32_t S, uint64_t N, const float *dsigma, const float *drgb, float loss_scale, uint32_t n_merged,
-                    float *dfeat, float *dW, void *ws, size_t ws_bytes, void *stream);
+                    float *dfeat, uint32_t *largest, float *dW, void *ws, size_t ws_bytes, void *stream);
 
 /* One Adam step (Sec. 5.1 names the optimiser; the update is Algorithm 1 of Kingma & Ba) on n fp32 values, in place:
  *   g' = g + l2 * p;  m = beta1 m + (1 - beta1) g';  v = beta2 v + (1 - beta2) g'^2;

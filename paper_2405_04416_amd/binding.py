@@ -79,7 +79,7 @@ _SIGNATURES = {
     "dg_hashgrid_encode_bwd_ordered_workspace_bytes": (C.c_size_t, [C.POINTER(GridDesc), C.POINTER(OrderDesc), C.c_uint64]),
     "dg_hashgrid_encode_bwd_ordered_count": (C.c_int, [C.POINTER(GridDesc), C.POINTER(OrderDesc), C.c_void_p, C.c_uint64, C.c_void_p, C.c_size_t,
                                                        C.c_void_p]),
-    "dg_hashgrid_encode_bwd_ordered": (C.c_int, [C.POINTER(GridDesc), C.POINTER(OrderDesc)] + [C.c_void_p] * 4 + [C.c_uint64] + [C.c_void_p] * 2
+    "dg_hashgrid_encode_bwd_ordered": (C.c_int, [C.POINTER(GridDesc), C.POINTER(OrderDesc)] + [C.c_void_p] * 5 + [C.c_uint64] + [C.c_void_p] * 2
                                        + [C.c_size_t, C.c_uint32, C.c_void_p]),
     "dg_hashgrid_encode_fwd_ordered": (C.c_int, [C.POINTER(GridDesc), C.c_void_p, C.c_void_p, C.c_uint64, C.c_void_p, C.c_void_p]),
     "dg_mlp_weight_count": (C.c_size_t, [C.POINTER(MlpDesc)]),
@@ -99,7 +99,7 @@ _SIGNATURES = {
     "dg_mlp_composite_fwd_rows": (C.c_int, [C.POINTER(MlpDesc)] + [C.c_void_p] * 4 + [C.c_uint32, C.c_uint32] + [C.c_void_p] * 4 + [C.c_uint32]
                                   + [C.c_void_p] * 4),
     "dg_mlp_bwd_rows": (C.c_int, [C.POINTER(MlpDesc)] + [C.c_void_p] * 4 + [C.c_uint32, C.c_uint64, C.c_void_p, C.c_void_p, C.c_float, C.c_uint32]
-                        + [C.c_void_p] * 3 + [C.c_size_t, C.c_void_p]),
+                        + [C.c_void_p] * 4 + [C.c_size_t, C.c_void_p]),
     "dg_appearance_rows": (C.c_int, [C.c_void_p, C.c_void_p, C.c_void_p, C.c_uint64, C.c_uint32, C.c_void_p, C.c_void_p]),
     "dg_composite_segment_fwd": (C.c_int, [C.c_void_p] * 3 + [C.c_uint32, C.c_uint32, C.c_void_p, C.c_void_p, C.c_uint32,
                                                               C.c_void_p, C.c_void_p, C.c_void_p]),
@@ -306,11 +306,11 @@ def dg_hashgrid_encode_bwd_ordered_count(desc, order, u, N, ws):
                                                       ws.numel() * ws.element_size(), _stream()))
 
 
-def dg_hashgrid_encode_bwd_ordered(desc, order, ordered, pieces, u, dfeat, N, dtable, ws, counted=False):
+def dg_hashgrid_encode_bwd_ordered(desc, order, ordered, pieces, u, dfeat, largest, N, dtable, ws, counted=False):
     assert ordered.numel() >= 4 * N and pieces.numel() >= dg_order_pieces_words(order, N) and u.numel() >= 3 * N and dfeat.numel() >= 32 * N
     _check(lib().dg_hashgrid_encode_bwd_ordered(C.byref(desc), C.byref(order), _ptr(ordered, torch.float32), _ptr(pieces, torch.int32),
-                                                _ptr(u, torch.float32), _ptr(dfeat, torch.float32), N, _ptr(dtable, torch.float32), _ptr(ws),
-                                                ws.numel() * ws.element_size(), 1 if counted else 0, _stream()))
+                                                _ptr(u, torch.float32), _ptr(dfeat, torch.float32), _ptr(largest, torch.int32), N, _ptr(dtable, torch.float32),
+                                                _ptr(ws), ws.numel() * ws.element_size(), 1 if counted else 0, _stream()))
 
 
 def dg_mlp_fwd(desc, weights, feat, dir_enc, S, N, sigma, rgb):
@@ -510,11 +510,11 @@ def dg_mlp_bwd_app(desc, weights, feat, dir_enc, app, S, N, dsigma, drgb, loss_s
                                 ws.numel() * ws.element_size(), _stream()))
 
 
-def dg_mlp_bwd_rows(desc, weights, feat, dir_enc, app, S, N, dsigma, drgb, loss_scale, n_merged, dfeat, dW, ws):
+def dg_mlp_bwd_rows(desc, weights, feat, dir_enc, app, S, N, dsigma, drgb, loss_scale, n_merged, dfeat, largest, dW, ws):
     rows = -(-N // S)
     assert dir_enc.numel() >= rows * desc.n_dir and (app is None or app.numel() >= rows * desc.n_app)
     assert dW.numel() >= dg_mlp_weight_count(desc) and min(feat.numel(), dfeat.numel()) >= N * desc.n_feat
     _check(lib().dg_mlp_bwd_rows(C.byref(desc), _ptr(weights, torch.float16), _ptr(feat, torch.float16), _ptr(dir_enc, torch.float16),
                                  _ptr(app, torch.float16, True), S, N, _ptr(dsigma, torch.float32), _ptr(drgb, torch.float32),
-                                 loss_scale, n_merged, _ptr(dfeat, torch.float32), _ptr(dW, torch.float32), _ptr(ws),
+                                 loss_scale, n_merged, _ptr(dfeat, torch.float32), _ptr(largest, torch.int32), _ptr(dW, torch.float32), _ptr(ws),
                                  ws.numel() * ws.element_size(), _stream()))

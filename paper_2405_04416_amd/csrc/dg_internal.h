@@ -46,7 +46,7 @@ int encode_bwd_binned_count(const char *who, const dg_grid_desc *d, uint32_t fro
 
 // ordered samples: levels below order->n_merged (encode_ordered.hip)
 int brick_bwd(const char *who, const dg_grid_desc *d, const dg_order_desc *order, const uint32_t *pieces, const void *ordered,
-              const float *dfeat, uint64_t N, float *dtable, hipStream_t st);
+              const float *dfeat, const uint32_t *largest, uint64_t N, float *dtable, hipStream_t st);
 
 // rows: features (and the gradient of levels below n_merged) as sample-major rows instead of planes.
 // matrix-core path of the 32-64-16 / (32 + n_app)-64-64-3 field MLPs (mlp_mfma.hip); n_app = 0, 16 or 48
@@ -58,8 +58,8 @@ void mlp_mfma_render(const void *weights, const void *feat, bool rows, const voi
                      uint32_t n_seg, uint32_t act_c, const float *delta, const float *t, const uint32_t *seg_ray,
                      const uint32_t *seg_slot, uint32_t k_max, float *Ck, float *Tk, float *Dk, hipStream_t st);
 void mlp_mfma_bwd(const void *weights, const void *feat, bool rows, uint32_t n_merged, const void *dir_enc, const void *app, uint32_t n_app,
-                  uint32_t S, uint64_t N, uint32_t act_c, const float *dsigma, const float *drgb, float loss_scale, float *dfeat, float *dW,
-                  void *ws, hipStream_t st);
+                  uint32_t S, uint64_t N, uint32_t act_c, const float *dsigma, const float *drgb, float loss_scale, float *dfeat, uint32_t *largest,
+                  float *dW, void *ws, hipStream_t st);
 
 }  // namespace dg
 

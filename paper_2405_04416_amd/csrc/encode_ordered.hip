@@ -74,13 +74,17 @@ encode_fwd_ordered_kernel(dg_grid_desc g, const float2 *__restrict__ table, cons
 }
 
 // Table gradient of levels [0, n_merged): a workgroup takes a piece of a brick and sums all its contributions in LDS -- the
-// brick's vertices at those levels, 64-bit floating point, one plane per feature -- then adds the sums to the table
-// gradient, one global add per vertex the brick touches.
+// brick's vertices at those levels, 64-bit fixed point, one plane per feature -- then adds the sums to the table gradient, one
+// global add per vertex the brick touches.
+// A value v becomes round(v * 2^k): the add of 1.5 * 2^52 in fp64 leaves it in the low mantissa bits, in two's complement.  k is
+// such that the magnitudes of a piece (at most 2^12 samples) sum to less than 2^50; adding the doubles' bit patterns as
+// integers adds those low bits, what happens above bit 50 is dropped when the sum is read.  (Integer adds are the fastest LDS
+// atomics: random addresses 3.6 T adds/s against 1.95 in fp64.)
 // A lane takes up to kRun consecutive samples and keeps the eight corner sums of the cell it is in in registers; only when
 // the cell changes do they go to LDS.  What the lanes hold at the end is first summed over runs of lanes in the same cell.
-// 33.5 M samples, T = 2^24, levels 0..9: 3.35 ms, of which the gradient rows (one or two random lines per sample) take 1.0,
-// the LDS adds 1.15, the sums themselves 1.2; the same levels through the coarse prefix and the bins took 8 ms.  13.3 M
-// samples, T = 2^19, levels 0..9: 1.25 ms.  Two workgroups per compute unit (512 threads, at most 80 KB of sums) and two
+// 33.5 M samples, T = 2^24, levels 0..9: 2.95 ms (3.35 with fp64 sums), of which the gradient rows (one or two random lines per
+// sample) take 1.0, the LDS adds 0.6, the sums themselves 1.2; the same levels through the coarse prefix and the bins took
+// 8 ms.  13.3 M samples, T = 2^19, levels 0..11: 1.55 ms.  Two workgroups per compute unit (512 threads, at most 80 KB of sums) and two
 // samples per lane beat four samples per lane (4.3 ms) and one workgroup of 1024 (4.3 ms).
 struct Boxes { uint32_t n_merged, dim[kMaxMerged][3], first[kMaxMerged + 1]; };
 
@@ -109,30 +113,48 @@ struct LevelLane {
 };
 
 // the eight corner sums of the cell whose corner 0 is vertex d of the box
-__device__ __forceinline__ void add_to_box(double *d, uint32_t nx, uint32_t nxy, uint32_t plane, const float (&vx)[8], const float (&vy)[8])
+__device__ __forceinline__ void add_fixed(unsigned long long *slot, float v, double to_fixed)
+{
+    __hip_atomic_fetch_add(slot, (unsigned long long)__double_as_longlong(__builtin_fma((double)v, to_fixed, 6755399441055744.0)), __ATOMIC_RELAXED,
+                           __HIP_MEMORY_SCOPE_WORKGROUP);
+}
+
+__device__ __forceinline__ void add_to_box(unsigned long long *d, double to_fixed, uint32_t nx, uint32_t nxy, uint32_t plane, const float (&vx)[8], const float (&vy)[8])
 {
 #pragma unroll
     for (int c = 0; c < 8; ++c) {
-        double *e = d + (c & 1) + ((c >> 1) & 1) * nx + (c >> 2) * nxy;
-        __hip_atomic_fetch_add(e, (double)vx[c], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
-        __hip_atomic_fetch_add(e + plane, (double)vy[c], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+        unsigned long long *e = d + (c & 1) + ((c >> 1) & 1) * nx + (c >> 2) * nxy;
+        add_fixed(e, vx[c], to_fixed);
+        add_fixed(e + plane, vy[c], to_fixed);
     }
 }
 
 __global__ void __launch_bounds__(kBrickBlock)
 brick_bwd_kernel(dg_grid_desc g, Bricks b, Boxes boxes, const uint2 *__restrict__ pieces, const float4 *__restrict__ ordered,
-                 const float4 *__restrict__ dfeat, float *__restrict__ dtable)
+                 const float4 *__restrict__ dfeat, const uint32_t *__restrict__ largest, float *__restrict__ dtable)
 {
-    extern __shared__ double sums[];
+    extern __shared__ unsigned long long sums[];
     if (blockIdx.x >= pieces[0].x) return;
     const uint2 piece = pieces[1 + blockIdx.x];
     const uint32_t begin = piece.y, n = pieces[2 + blockIdx.x].y - begin;
     const uint32_t n_vertices = boxes.first[boxes.n_merged];
-    for (uint32_t i = threadIdx.x; i < 2 * n_vertices; i += kBrickBlock) sums[i] = 0.0;
+    for (uint32_t i = threadIdx.x; i < 2 * n_vertices; i += kBrickBlock) sums[i] = 0ull;
     const uint32_t brick[3] = {piece.x % b.n[0], piece.x / b.n[0] % b.n[1], piece.x / (b.n[0] * b.n[1])};
     const uint32_t mask = (1u << g.log2_T) - 1u;
     const int lane = threadIdx.x % dg::kWave;
     const uint32_t pairs = boxes.n_merged / 2;
+    const uint32_t top = *largest >> 23;                             // biased exponent (0: no smaller k needed)
+    if (top == 255u) {      // not finite: no scale fits, the gradient is marked instead
+        for (uint32_t l = threadIdx.x; l < boxes.n_merged; l += kBrickBlock) {
+            const LevelGeom lv = level_of(g, l);
+            const uint32_t e = vertex_entry(lv, mask, box_low(b, brick[0], 0, lv.scale[0]), box_low(b, brick[1], 1, lv.scale[1]), box_low(b, brick[2], 2, lv.scale[2]));
+            dtable[2 * ((size_t)lv.offset + e)] = __uint_as_float(0x7fc00000u);
+        }
+        return;
+    }
+    static_assert(kPiece <= 1u << 12, "2^12 samples of the largest magnitude sum to less than 2^50 units");
+    const int k_scale = 50 - 12 - 1 - ((int)(top ? top : 1u) - 127);
+    const double to_fixed = __longlong_as_double((long long)(1023 + k_scale) << 52), from_fixed = __longlong_as_double((long long)(1023 - k_scale) << 52);
     LevelLane mine;
     {
         const uint32_t l = min((uint32_t)lane, boxes.n_merged - 1u);
@@ -183,7 +205,7 @@ brick_bwd_kernel(dg_grid_desc g, Bricks b, Boxes boxes, const uint2 *__restrict_
                 for (int a = 0; a < 3; ++a) { scale[a] = lane_value(mine.scale[a], l); last[a] = lane_value(mine.last[a], l); }
                 const float fnx = lane_value(mine.nx, l), fnxy = lane_value(mine.nxy, l), origin = lane_value(mine.origin, l);
                 const uint32_t nx = (uint32_t)fnx, nxy = (uint32_t)fnxy, last_slot = lane_value(mine.last_slot, l);
-                double *box = sums + lane_value(mine.first, l);
+                unsigned long long *box = sums + lane_value(mine.first, l);
                 float vx[8], vy[8];
                 uint32_t slot = 0;                                    // of the cell whose sums vx, vy are
 #pragma unroll
@@ -199,7 +221,7 @@ brick_bwd_kernel(dg_grid_desc g, Bricks b, Boxes boxes, const uint2 *__restrict_
                         // whole numbers below 2^24: exact in fp32
                         const uint32_t now = min((uint32_t)__builtin_fmaf(cell[2], fnxy, __builtin_fmaf(cell[1], fnx, cell[0] - origin)), last_slot);
                         if (k > 0 && now != slot) {
-                            add_to_box(box + slot, nx, nxy, n_vertices, vx, vy);
+                            add_to_box(box + slot, to_fixed, nx, nxy, n_vertices, vx, vy);
 #pragma unroll
                             for (int c = 0; c < 8; ++c) { vx[c] = 0.0f; vy[c] = 0.0f; }
                         }
@@ -218,7 +240,7 @@ brick_bwd_kernel(dg_grid_desc g, Bricks b, Boxes boxes, const uint2 *__restrict_
                 const unsigned long long heads = __ballot(head);
                 if (__popcll(heads) < dg::kWave) segmented_sum(vx, vy, head, heads);
                 const bool tail = lane == dg::kWave - 1 || ((heads >> ((lane + 1) & 63)) & 1ull);
-                if (tail) add_to_box(box + slot, nx, nxy, n_vertices, vx, vy);
+                if (tail) add_to_box(box + slot, to_fixed, nx, nxy, n_vertices, vx, vy);
             }
 #pragma unroll
             for (int k = 0; k < kRun; ++k)
@@ -237,7 +259,8 @@ brick_bwd_kernel(dg_grid_desc g, Bricks b, Boxes boxes, const uint2 *__restrict_
         // neighbouring lanes add the two features of neighbouring vertices: whole cache lines per instruction
         for (uint32_t i = threadIdx.x; i < 2 * count; i += kBrickBlock) {
             const uint32_t v = i >> 1, f = i & 1u;
-            const float sum = (float)sums[f * n_vertices + boxes.first[l] + v];
+            const long long bits = (long long)(sums[f * n_vertices + boxes.first[l] + v] << 13) >> 13;
+            const float sum = (float)((double)bits * from_fixed);
             if (sum != 0.0f) unsafeAtomicAdd(dst + 2 * (size_t)vertex_entry(lv, mask, low[0] + v % nx, low[1] + v / nx % ny, low[2] + v / (nx * ny)) + f, sum);
         }
     }
@@ -249,7 +272,7 @@ namespace dg {
 
 // the merged levels of the ordered backward pass (N samples; dfeat rows of 2 * n_merged floats)
 int brick_bwd(const char *who, const dg_grid_desc *d, const dg_order_desc *order, const uint32_t *pieces, const void *ordered, const float *dfeat,
-              uint64_t N, float *dtable, hipStream_t st)
+              const uint32_t *largest, uint64_t N, float *dtable, hipStream_t st)
 {
     static std::once_flag lds_once;
     static hipError_t lds_status = hipSuccess;
@@ -266,7 +289,7 @@ int brick_bwd(const char *who, const dg_grid_desc *d, const dg_order_desc *order
     }
     const size_t lds = (size_t)boxes.first[boxes.n_merged] * 2 * sizeof(double);
     brick_bwd_kernel<<<(uint32_t)piece_bound(order->total, N), kBrickBlock, lds, st>>>(
-        *d, bricks_of(order), boxes, (const uint2 *)pieces, (const float4 *)ordered, (const float4 *)dfeat, dtable);
+        *d, bricks_of(order), boxes, (const uint2 *)pieces, (const float4 *)ordered, (const float4 *)dfeat, largest, dtable);
     return launch_status(who);
 }
 
@@ -301,15 +324,15 @@ int ordered_ok(const char *who, const dg_grid_desc *desc, const dg_order_desc *o
 }
 
 int bwd_ordered(const char *who, const dg_grid_desc *desc, const dg_order_desc *order, const void *ordered, const uint32_t *pieces, const float *u,
-                const float *dfeat, uint64_t N, float *dtable, void *ws, size_t ws_bytes, bool counted, void *stream)
+                const float *dfeat, const uint32_t *largest, uint64_t N, float *dtable, void *ws, size_t ws_bytes, bool counted, void *stream)
 {
     if (int rc = ordered_ok(who, desc, order)) return rc;
     if (N == 0) return DG_OK;
-    DG_REQUIRE(ordered && pieces && u && dfeat && dtable && ws, DG_ERR_ARG, "%s: null pointer", who);
+    DG_REQUIRE(ordered && pieces && u && dfeat && largest && dtable && ws, DG_ERR_ARG, "%s: null pointer", who);
     DG_REQUIRE(dg::aligned(ordered, 16) && dg::aligned(pieces, 8) && dg::aligned(dfeat, 16) && dg::aligned(dtable, 8) && dg::aligned(ws, 256), DG_ERR_ARG,
                "%s: misaligned pointer", who);
     // the rows of the merged levels take the place of those levels' planes: plane l of the others lies where it always does
-    if (int rc = dg::brick_bwd(who, desc, order, pieces, ordered, dfeat, N, dtable, (hipStream_t)stream)) return rc;
+    if (int rc = dg::brick_bwd(who, desc, order, pieces, ordered, dfeat, largest, N, dtable, (hipStream_t)stream)) return rc;
     return dg::encode_bwd_binned(who, desc, order->n_merged, u, dfeat, N, dtable, ws, ws_bytes, counted, (hipStream_t)stream);
 }
 
@@ -333,8 +356,8 @@ extern "C" int dg_hashgrid_encode_bwd_ordered_count(const dg_grid_desc *desc, co
 }
 
 extern "C" int dg_hashgrid_encode_bwd_ordered(const dg_grid_desc *desc, const dg_order_desc *order, const void *ordered, const uint32_t *pieces,
-                                              const float *u, const float *dfeat, uint64_t N, float *dtable, void *ws, size_t ws_bytes,
-                                              uint32_t counted, void *stream)
+                                              const float *u, const float *dfeat, const uint32_t *largest, uint64_t N, float *dtable, void *ws,
+                                              size_t ws_bytes, uint32_t counted, void *stream)
 {
-    return bwd_ordered("dg_hashgrid_encode_bwd_ordered", desc, order, ordered, pieces, u, dfeat, N, dtable, ws, ws_bytes, counted != 0, stream);
+    return bwd_ordered("dg_hashgrid_encode_bwd_ordered", desc, order, ordered, pieces, u, dfeat, largest, N, dtable, ws, ws_bytes, counted != 0, stream);
 }

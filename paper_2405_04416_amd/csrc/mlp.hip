@@ -286,8 +286,8 @@ int mlp_composite_fwd(const char *who, const dg_mlp_desc *desc, const void *weig
 }
 
 int mlp_bwd(const char *who, const dg_mlp_desc *desc, const void *weights, const void *feat, bool rows, uint32_t n_merged, const void *dir_enc,
-            const void *app, uint32_t S, uint64_t N, const float *dsigma, const float *drgb, float loss_scale, float *dfeat, float *dW, void *ws,
-            size_t ws_bytes, void *stream)
+            const void *app, uint32_t S, uint64_t N, const float *dsigma, const float *drgb, float loss_scale, float *dfeat, uint32_t *largest,
+            float *dW, void *ws, size_t ws_bytes, void *stream)
 {
     const int net = which_net(desc, who);
     if (net < 0) return net;
@@ -295,7 +295,7 @@ int mlp_bwd(const char *who, const dg_mlp_desc *desc, const void *weights, const
     DG_REQUIRE(n_merged % 2 == 0 && n_merged <= desc->n_feat / 2, DG_ERR_ARG, "%s: n_merged=%u must be even and at most the number of levels", who, n_merged);
     DG_REQUIRE(S >= 1 && loss_scale > 0.0f, DG_ERR_ARG, "%s: S >= 1 and loss_scale > 0 required", who);
     if (N == 0) return DG_OK;
-    DG_REQUIRE(weights && feat && dir_enc && dsigma && drgb && dfeat && dW, DG_ERR_ARG, "%s: null pointer", who);
+    DG_REQUIRE(weights && feat && dir_enc && dsigma && drgb && dfeat && dW && (!rows || largest), DG_ERR_ARG, "%s: null pointer", who);
     DG_REQUIRE(desc->n_app == 0 || (app && dg::aligned(app, 16)), DG_ERR_ARG, "%s: appearance rows missing or not 16-byte aligned", who);
     DG_REQUIRE(ws && ws_bytes >= dg_mlp_bwd_app_workspace_bytes(desc, N, S), DG_ERR_WORKSPACE, "%s: workspace %zu < %zu bytes", who, ws_bytes,
                dg_mlp_bwd_app_workspace_bytes(desc, N, S));
@@ -307,7 +307,7 @@ int mlp_bwd(const char *who, const dg_mlp_desc *desc, const void *weights, const
     if (net == 1) {
         DG_REQUIRE(dg::aligned(feat, rows ? 16 : 4) && dg::aligned(dir_enc, 16) && dg::aligned(dfeat, rows ? 16 : 8), DG_ERR_ARG,
                    "%s: feat must be %d-byte, dfeat %d-byte, dir_enc 16-byte aligned", who, rows ? 16 : 4, rows ? 16 : 8);
-        dg::mlp_mfma_bwd(weights, feat, rows, n_merged, dir_enc, app, desc->n_app, S, N, desc->act_c, dsigma, drgb, loss_scale, dfeat, dW, ws, st);
+        dg::mlp_mfma_bwd(weights, feat, rows, n_merged, dir_enc, app, desc->n_app, S, N, desc->act_c, dsigma, drgb, loss_scale, dfeat, largest, dW, ws, st);
         return dg::launch_status(who);
     }
     mlp_bwd_kernel<NetTiny><<<grid, kBwdBlock, 0, st>>>((const __half *)weights, (const __half *)feat, (const __half *)dir_enc,
@@ -381,12 +381,13 @@ extern "C" int dg_mlp_bwd_app(const dg_mlp_desc *desc, const void *weights, cons
                               const void *app, uint32_t S, uint64_t N, const float *dsigma, const float *drgb,
                               float loss_scale, float *dfeat, float *dW, void *ws, size_t ws_bytes, void *stream)
 {
-    return mlp_bwd("dg_mlp_bwd", desc, weights, feat, false, 0, dir_enc, app, S, N, dsigma, drgb, loss_scale, dfeat, dW, ws, ws_bytes, stream);
+    return mlp_bwd("dg_mlp_bwd", desc, weights, feat, false, 0, dir_enc, app, S, N, dsigma, drgb, loss_scale, dfeat, nullptr, dW, ws, ws_bytes, stream);
 }
 
 extern "C" int dg_mlp_bwd_rows(const dg_mlp_desc *desc, const void *weights, const void *feat, const void *dir_enc,
                                const void *app, uint32_t S, uint64_t N, const float *dsigma, const float *drgb,
-                               float loss_scale, uint32_t n_merged, float *dfeat, float *dW, void *ws, size_t ws_bytes, void *stream)
+                               float loss_scale, uint32_t n_merged, float *dfeat, uint32_t *largest, float *dW, void *ws, size_t ws_bytes,
+                               void *stream)
 {
-    return mlp_bwd("dg_mlp_bwd_rows", desc, weights, feat, true, n_merged, dir_enc, app, S, N, dsigma, drgb, loss_scale, dfeat, dW, ws, ws_bytes, stream);
+    return mlp_bwd("dg_mlp_bwd_rows", desc, weights, feat, true, n_merged, dir_enc, app, S, N, dsigma, drgb, loss_scale, dfeat, largest, dW, ws, ws_bytes, stream);
 }

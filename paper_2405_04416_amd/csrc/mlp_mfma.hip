@@ -440,7 +440,8 @@ colour_bwd_kernel(const __half *__restrict__ weights, const __half *__restrict__
 template <bool ROWS>
 __global__ void __launch_bounds__(kBlock, 2)
 density_bwd_kernel(const __half *__restrict__ weights, const __half *__restrict__ feat, uint64_t n_samples,
-                   const h8 *__restrict__ dgeo, float loss_scale, uint32_t n_merged, float *__restrict__ dfeat, float *__restrict__ shares)
+                   const h8 *__restrict__ dgeo, float loss_scale, uint32_t n_merged, float *__restrict__ dfeat, uint32_t *__restrict__ largest,
+                   float *__restrict__ shares)
 {
     // images: density layer 1 forward (4 chunks), Wd2^T (2), Wd1^T (4), selections (4)
     constexpr int kD1 = 0, kD2T = 4, kD1T = 6, kST = 10, kSN = 12, kChunks = 14;
@@ -460,6 +461,7 @@ density_bwd_kernel(const __half *__restrict__ weights, const __half *__restrict_
     const h8 selN0 = image(lds, kSN, lane), selN1 = image(lds, kSN + 1, lane);
     const h8 zero8 = {0, 0, 0, 0, 0, 0, 0, 0};
 
+    float most = 0.0f;                                          // largest magnitude of the feature gradient, before the division by the loss scale
     f16v gWd2[2], gWd1[2];
 #pragma unroll
     for (int a = 0; a < 2; ++a) { gWd2[a] = zero16(); gWd1[a] = zero16(); }
@@ -506,6 +508,12 @@ density_bwd_kernel(const __half *__restrict__ weights, const __half *__restrict_
         f16v gf = zero16();
 #pragma unroll
         for (int ks = 0; ks < 4; ++ks) gf = mma(image(lds, kD1T + ks, lane), dl[ks], gf);
+        if (ROWS && valid) {
+            bool nan = false;                                   // fmaxf passes over NaN
+#pragma unroll
+            for (int k = 0; k < 16; ++k) { most = fmaxf(most, fabsf(gf[k])); nan |= gf[k] != gf[k]; }
+            if (nan) most = INFINITY;
+        }
         if (valid) {
             // registers 4q .. 4q+3 hold features 8q + 4h .. + 3: levels 4q + 2h and 4q + 2h + 1 of the planes [16][n_samples][2]
             float2 *planes = reinterpret_cast<float2 *>(dfeat);
@@ -522,6 +530,17 @@ density_bwd_kernel(const __half *__restrict__ weights, const __half *__restrict_
         }
     }
 
+    if (ROWS) {
+        // one atomic per workgroup at most: same-address atomics take turns (one per wavefront cost 15 us)
+        __shared__ uint32_t most_word;
+        if (threadIdx.x == 0) most_word = 0u;
+        __syncthreads();
+#pragma unroll
+        for (int off = 32; off > 0; off >>= 1) most = fmaxf(most, __shfl_xor(most, off, 64));
+        if (lane == 0) atomicMax(&most_word, __float_as_uint(most * inv_scale));      // bit patterns of values >= 0 order like the values
+        __syncthreads();
+        if (threadIdx.x == 0 && most_word > __hip_atomic_load(largest, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) atomicMax(largest, most_word);
+    }
     static_assert(oWc1 * 4 <= kChunks * 1024, "the share fits the space of the images");
     write_share<oWc1>(reinterpret_cast<float *>(lds), shares + (size_t)blockIdx.x * oWc1, [&](float *share, uint32_t group, bool first) {
 #pragma unroll
@@ -651,8 +670,8 @@ void mlp_mfma_render(const void *weights, const void *feat, bool rows, const voi
 }
 
 void mlp_mfma_bwd(const void *weights, const void *feat, bool rows, uint32_t n_merged, const void *dir_enc, const void *app, uint32_t n_app,
-                  uint32_t S, uint64_t N, uint32_t act_c, const float *dsigma, const float *drgb, float loss_scale, float *dfeat, float *dW,
-                  void *ws, hipStream_t st)
+                  uint32_t S, uint64_t N, uint32_t act_c, const float *dsigma, const float *drgb, float loss_scale, float *dfeat, uint32_t *largest,
+                  float *dW, void *ws, hipStream_t st)
 {
     using namespace dg_mlp_mfma;
     const uint64_t tiles = (N + 31) / 32, blocks_needed = (tiles + kWavesPerBlock - 1) / kWavesPerBlock;
@@ -674,8 +693,8 @@ void mlp_mfma_bwd(const void *weights, const void *feat, bool rows, uint32_t n_m
         colour_bwd_kernel<decltype(na)::value, decltype(in_rows)::value><<<grid_c, kBlock, 0, st>>>(w, f, dr, ap, S, N, act_c, dsigma, drgb, loss_scale, dgeo,
                                                                                                    colour_shares, row_delta);
     });
-    if (rows) density_bwd_kernel<true><<<grid_d, kBlock, 0, st>>>(w, f, N, dgeo, loss_scale, n_merged, dfeat, density_shares);
-    else density_bwd_kernel<false><<<grid_d, kBlock, 0, st>>>(w, f, N, dgeo, loss_scale, 0, dfeat, density_shares);
+    if (rows) density_bwd_kernel<true><<<grid_d, kBlock, 0, st>>>(w, f, N, dgeo, loss_scale, n_merged, dfeat, largest, density_shares);
+    else density_bwd_kernel<false><<<grid_d, kBlock, 0, st>>>(w, f, N, dgeo, loss_scale, 0, dfeat, nullptr, density_shares);
     static_assert(oWc1 % kFoldElems == 0, "a fold workgroup must not span both share regions");
     fold_shares_kernel<<<(kTotal + kFoldElems - 1) / kFoldElems, kFoldElems * kFoldGroups, 0, st>>>(density_shares, grid_d, oWc1, colour_shares, grid_c,
                                                                                                    kTotal, 1.0f / loss_scale, dW);

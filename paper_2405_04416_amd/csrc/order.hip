@@ -5,7 +5,7 @@
 // corner row costs a cache line of its own, and runs of equal cells end with the ray.  In spatial order the lines that
 // neighbours share are fetched once, and the coarser levels' gradients can be summed on chip before they go anywhere.
 //
-//   1. bricks: the box is cut into a few thousand to 2^15 equal bricks (about kPerBrick samples each).  Count, scan,
+//   1. bricks: the box is cut into a few thousand to 2^15 equal bricks (700 to 1200 samples each).  Count, scan,
 //      scatter with one persistent tiling; the counters of all bricks live in LDS, so there are no global atomics.
 //      A sample becomes 16 bytes: its coordinates and the index it came from.
 //   2. inside a brick: pencils along x (the table's contiguous direction), sorted in LDS.
@@ -80,7 +80,7 @@ brick_scan_rows_kernel(uint32_t *__restrict__ rows, uint32_t n_rows, uint32_t n_
 }
 
 // exclusive prefix over the bricks, and the list of pieces: a brick's samples in pieces of at most kPiece (one workgroup; at
-// most kMaxBricks bricks).  pieces[0] = (number of pieces, 0), then (brick, first sample) of each, then (0, N).
+// most kMaxBricks bricks).  pieces[0] = (number of pieces, 0 for the caller's use), then (brick, first sample) of each, then (0, N).
 __global__ void __launch_bounds__(1024)
 brick_scan_totals_kernel(const uint32_t *__restrict__ totals, uint32_t n_keys, uint32_t *__restrict__ first, uint2 *__restrict__ pieces)
 {
@@ -185,6 +185,51 @@ namespace {
 
 inline size_t align256(size_t x) { return (x + 255) / 256 * 256; }
 
+// bricks of about per_brick samples, and the levels that such a brick has in LDS together
+void cut_bricks(dg_order_desc *order, const dg_grid_desc *desc, uint64_t N, uint32_t per_brick)
+{
+    std::memset(order, 0, sizeof *order);
+    // the box's proportions, from the finest level's voxels along each axis
+    const float *ext = desc->scale[desc->n_levels - 1];
+    const double want = std::fmin((double)kMaxBricks, std::fmax(1.0, (double)N / per_brick));
+    const double per_side = std::cbrt(want / ((double)ext[0] * ext[1] * ext[2]));
+    uint64_t total = 1;
+    for (int a = 0; a < 3; ++a) {
+        double n = std::floor(ext[a] * per_side);
+        n = std::fmin(std::fmax(n, 1.0), 1024.0);
+        order->n_bricks[a] = (uint32_t)n;
+        total *= order->n_bricks[a];
+    }
+    while (total > kMaxBricks) {          // a flat box rounds up to one brick along its short axes: fewer along the longest
+        int a = 0;
+        for (int k = 1; k < 3; ++k) if (order->n_bricks[k] > order->n_bricks[a]) a = k;
+        order->n_bricks[a] = (order->n_bricks[a] + 1) / 2;
+        total = (uint64_t)order->n_bricks[0] * order->n_bricks[1] * order->n_bricks[2];
+    }
+    order->total = (uint32_t)total;
+    for (int a = 0; a < 3; ++a) order->per_unit[a] = (float)order->n_bricks[a];
+    // Levels summed brick by brick in the backward pass: as many as have their brick's vertices in LDS together.  A brick
+    // of width w voxels meets at most floor(w) + 2 voxels, floor(w) + 3 vertices (2e-2: room for the slack and the fp32
+    // rounding of the edges).
+    uint32_t at = 0, l = 0;
+    for (; l < kMaxMerged; ++l) {
+        uint64_t vertices = 1;
+        uint32_t box[3];
+        for (int a = 0; a < 3; ++a) {
+            box[a] = (uint32_t)std::floor((double)desc->scale[l][a] / order->n_bricks[a] + 2e-2) + 3u;
+            if (box[a] > desc->res[l][a] + 1u) box[a] = desc->res[l][a] + 1u;
+            vertices *= box[a];
+        }
+        const double finest = std::fmax(desc->scale[l][0], std::fmax(desc->scale[l][1], desc->scale[l][2]));
+        if (at + vertices > kMaxBoxVertices || finest > kMaxMergedScale) break;
+        for (int a = 0; a < 3; ++a) order->box[l][a] = box[a];
+        order->box_first[l] = at;
+        at += (uint32_t)vertices;
+        order->box_first[l + 1] = at;
+    }
+    order->n_merged = l & ~1u;
+}
+
 }  // namespace
 
 namespace dg_order {
@@ -204,46 +249,14 @@ extern "C" int dg_order_desc_init(dg_order_desc *order, const dg_grid_desc *desc
     DG_REQUIRE(order && desc, DG_ERR_ARG, "%s: null pointer", who);
     DG_REQUIRE(desc->n_levels == 16 && desc->n_features == 2, DG_ERR_UNSUPPORTED, "%s: needs L = 16, F = 2", who);
     std::memset(order, 0, sizeof *order);
-    // the box's proportions, from the finest level's voxels along each axis
-    const float *ext = desc->scale[desc->n_levels - 1];
-    const double want = std::fmin((double)kMaxBricks, std::fmax(1.0, (double)N / kPerBrick));
-    const double per_side = std::cbrt(want / ((double)ext[0] * ext[1] * ext[2]));
-    uint64_t total = 1;
-    for (int a = 0; a < 3; ++a) {
-        double n = std::floor(ext[a] * per_side);
-        n = std::fmin(std::fmax(n, 1.0), 1024.0);
-        order->n_bricks[a] = (uint32_t)n;
-        order->per_unit[a] = (float)n;
-        total *= order->n_bricks[a];
+    // Bricks of about 1200 samples, or smaller ones, down to 700, where more levels then fit LDS (two more levels summed per
+    // brick save 2 / 16 of the table-gradient pass: 13.3 M samples, T = 2^19, 9680 bricks and 10 levels 3.85 ms, 16 854 bricks and
+    // 12 levels 3.54 ms; with bricks of 500 and 350 samples 3.70 and 3.66 ms).
+    for (uint32_t per_brick = kPerBrickMax; per_brick >= kPerBrickMin; per_brick -= 100) {
+        dg_order_desc trial;
+        cut_bricks(&trial, desc, N, per_brick);
+        if (trial.n_merged > order->n_merged || order->total == 0) *order = trial;
     }
-    while (total > kMaxBricks) {          // a flat box rounds up to one brick along its short axes: fewer along the longest
-        int a = 0;
-        for (int k = 1; k < 3; ++k) if (order->n_bricks[k] > order->n_bricks[a]) a = k;
-        order->n_bricks[a] = (order->n_bricks[a] + 1) / 2;
-        order->per_unit[a] = (float)order->n_bricks[a];
-        total = (uint64_t)order->n_bricks[0] * order->n_bricks[1] * order->n_bricks[2];
-    }
-    order->total = (uint32_t)total;
-    // Levels summed brick by brick in the backward pass: as many as have their brick's vertices in LDS together.  A brick
-    // of width w voxels meets at most floor(w) + 2 voxels, floor(w) + 3 vertices (2e-2: room for the slack and the fp32 rounding of
-    // the edges).
-    uint32_t at = 0, l = 0;
-    for (; l < kMaxMerged; ++l) {
-        uint64_t vertices = 1;
-        uint32_t box[3];
-        for (int a = 0; a < 3; ++a) {
-            box[a] = (uint32_t)std::floor((double)desc->scale[l][a] / order->n_bricks[a] + 2e-2) + 3u;
-            if (box[a] > desc->res[l][a] + 1u) box[a] = desc->res[l][a] + 1u;
-            vertices *= box[a];
-        }
-        const double finest = std::fmax(desc->scale[l][0], std::fmax(desc->scale[l][1], desc->scale[l][2]));
-        if (at + vertices > kMaxBoxVertices || finest > kMaxMergedScale) break;
-        for (int a = 0; a < 3; ++a) order->box[l][a] = box[a];
-        order->box_first[l] = at;
-        at += (uint32_t)vertices;
-        order->box_first[l + 1] = at;
-    }
-    order->n_merged = l & ~1u;
     return DG_OK;
 }
 

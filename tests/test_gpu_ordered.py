@@ -80,21 +80,40 @@ def test_ordered_encode(key, N, flavour):
     ud, gd = dev(u), dev(mixed)
     dtable = torch.zeros(ref_grid.n_entries, 2, device=DEV)
     ws = torch.zeros(B.dg_hashgrid_encode_bwd_ordered_workspace_bytes(grid, order, N) // 4 + 64, device=DEV)
-    B.dg_hashgrid_encode_bwd_ordered(grid, order, ordered, pieces, ud, gd, N, dtable, ws)
+    largest = gd.abs().max().reshape(1).view(torch.int32)
+    B.dg_hashgrid_encode_bwd_ordered(grid, order, ordered, pieces, ud, gd, largest, N, dtable, ws)
     B.dg_hashgrid_encode_bwd_ordered_count(grid, order, ud, N, ws)
-    B.dg_hashgrid_encode_bwd_ordered(grid, order, ordered, pieces, ud, gd, N, dtable, ws, counted=True)
+    B.dg_hashgrid_encode_bwd_ordered(grid, order, ordered, pieces, ud, gd, largest, N, dtable, ws, counted=True)
     want = 2.0 * oracle.encode_bwd(ref_grid, u, g.astype(np.float64))
     scale = 2.0 * oracle.encode_bwd(ref_grid, u, np.abs(g).astype(np.float64))          # sum of the contributions' magnitudes
     have = host(dtable).astype(np.float64)
     for l in range(16):
         sl = slice(ref_grid.first[l], ref_grid.first[l + 1])
         if l < M:
-            # a run adds up to 2 x 64 contributions in fp32, each of them four fp32 roundings deep; the rest is fp64 and a
-            # handful of fp32 adds into the table: (128 + 8) x 2^-24 of the magnitudes = 8.1e-6
-            assert np.all(np.abs(have[sl] - want[sl]) <= 1e-5 * scale[sl] + 1e-30), l
+            # a run adds up to 2 x 64 contributions in fp32, each of them four fp32 roundings deep; the rest is exact up to its
+            # quantum (2^-37 of the largest gradient, at most one half per contribution) and a handful of fp32 adds into the
+            # table: (128 + 8) x 2^-24 of the magnitudes = 8.1e-6
+            quantum = 2.0 ** -37 * float(np.abs(g).max()) * (2 * N)
+            assert np.all(np.abs(have[sl] - want[sl]) <= 1e-5 * scale[sl] + quantum), l
         else:
             assert rel_err(have[sl], want[sl]) <= TOL_F16, l                             # the binned pass, with its own bar
     assert np.all(have[want == 0] == 0)
+
+
+def test_non_finite_gradient_is_marked():
+    """An infinite or NaN gradient (an fp16 delta that overflowed) leaves NaN in the table gradient's merged levels."""
+    grid, ref_grid = _grids("cached")
+    N = 3000
+    u = _coords(N, "points")
+    order, ordered, pieces = _sorted(grid, u, N)
+    ws = torch.zeros(B.dg_hashgrid_encode_bwd_ordered_workspace_bytes(grid, order, N) // 4 + 64, device=DEV)
+    for bad in (float("inf"), float("nan")):
+        g = torch.zeros(N * 32, device=DEV)
+        g[5] = bad
+        dtable = torch.zeros(ref_grid.n_entries, 2, device=DEV)
+        largest = torch.tensor([float("inf")], device=DEV).view(torch.int32)         # what dg_mlp_bwd_rows reports for either
+        B.dg_hashgrid_encode_bwd_ordered(grid, order, ordered, pieces, dev(u), g, largest, N, dtable, ws)
+        assert not bool(torch.isfinite(dtable).all())
 
 
 def test_order_arguments():
