@@ -61,6 +61,13 @@ void mlp_mfma_bwd(const void *weights, const void *feat, bool rows, uint32_t n_m
                   uint32_t S, uint64_t N, uint32_t act_c, const float *dsigma, const float *drgb, float loss_scale, float *dfeat, uint32_t *largest,
                   float *dW, void *ws, hipStream_t st);
 
+// the 8-32-16 / 20-32-3 networks (mlp_small.hip)
+size_t mlp_small_workspace_bytes();
+void mlp_small_fwd(const void *weights, const void *feat, const void *dir_enc, uint32_t S, uint64_t N, uint32_t act_c, float *sigma, float *rgb,
+                   hipStream_t st);
+void mlp_small_bwd(const void *weights, const void *feat, const void *dir_enc, uint32_t S, uint64_t N, uint32_t act_c, const float *dsigma,
+                   const float *drgb, float loss_scale, float *dfeat, float *dW, void *ws, hipStream_t st);
+
 }  // namespace dg
 
 #define DG_REQUIRE(cond, code, ...)                     \

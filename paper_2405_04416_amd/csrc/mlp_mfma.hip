@@ -417,12 +417,12 @@ colour_bwd_kernel(const __half *__restrict__ weights, const __half *__restrict__
 #pragma unroll
             for (uint32_t ot = 0; ot < 2; ++ot)
                 if (group == ot) {
-                    add_share(share + oWc2, first, HC, HC, ot, 0, lane, gWc2[ot][0]);
-                    add_share(share + oWc2, first, HC, HC, ot, 1, lane, gWc2[ot][1]);
+                    add_share(share + oWc2, first, HC, HC, HC, ot, 0, lane, gWc2[ot][0]);
+                    add_share(share + oWc2, first, HC, HC, HC, ot, 1, lane, gWc2[ot][1]);
                 }
         } else if (group == 2) {
 #pragma unroll
-            for (int ot = 0; ot < 2; ++ot) add_share(share + oWc1, first, CI, HC, ot, 0, lane, gWc1[ot]);
+            for (int ot = 0; ot < 2; ++ot) add_share(share + oWc1, first, CI, HC, CI, ot, 0, lane, gWc1[ot]);
         } else if (h == 0) {
 #pragma unroll
             for (int it = 0; it < 2; ++it)
@@ -545,8 +545,8 @@ density_bwd_kernel(const __half *__restrict__ weights, const __half *__restrict_
     write_share<oWc1>(reinterpret_cast<float *>(lds), shares + (size_t)blockIdx.x * oWc1, [&](float *share, uint32_t group, bool first) {
 #pragma unroll
         for (uint32_t t = 0; t < 2; ++t) {
-            if (group == t) add_share(share + oWd1, first, NF, HD, t, 0, lane, gWd1[t]);
-            if (group == 2 + t) add_share(share + oWd2, first, HD, NG, 0, t, lane, gWd2[t]);
+            if (group == t) add_share(share + oWd1, first, NF, HD, NF, t, 0, lane, gWd1[t]);
+            if (group == 2 + t) add_share(share + oWd2, first, HD, NG, HD, 0, t, lane, gWd2[t]);
         }
     });
 }

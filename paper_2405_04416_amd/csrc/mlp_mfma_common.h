@@ -140,13 +140,13 @@ __device__ __forceinline__ h8 delta_from(const f16v &g, int p, h8 a)
 }
 
 // one tile of a wavefront's weight gradient into the workgroup's share in LDS; every word belongs to one lane
-__device__ __forceinline__ void add_share(float *share, bool first, int n_in, int rows_real, int ot, int it, int lane, const f16v &acc)
+__device__ __forceinline__ void add_share(float *share, bool first, int n_in, int rows_real, int cols_real, int ot, int it, int lane, const f16v &acc)
 {
     const int h = lane >> 5, i = 32 * it + (lane & 31);
 #pragma unroll
     for (int r = 0; r < 16; ++r) {
         const int o = 32 * ot + 8 * (r >> 2) + 4 * h + (r & 3);
-        if (o < rows_real) share[o * n_in + i] = first ? acc[r] : share[o * n_in + i] + acc[r];
+        if (o < rows_real && i < cols_real) share[o * n_in + i] = first ? acc[r] : share[o * n_in + i] + acc[r];
     }
 }
 
