@@ -305,6 +305,12 @@ int dg_merge_segments_bwd(const float *Ck, const float *Tk, const uint32_t *seg_
 int dg_loss_seed(const float *C, const float *T, const float *Cgt, uint32_t R,
                  float lambda1, float *gC, float *gT, float *loss, void *stream);
 
+/* dg_merge_segments followed by dg_loss_seed, in one pass over the rays: same arguments, same results. */
+int dg_merge_loss(const float *Ck, const float *Tk, const uint32_t *seg_count, uint32_t R, uint32_t k_max, const float *Cgt,
+                  float lambda1, float *C, float *T, float *gC, float *gT, float *loss, void *stream);
+/* Clears `bytes` bytes (a multiple of 4, dst 4-byte aligned) with a kernel on the stream. */
+int dg_clear(void *dst, uint64_t bytes, void *stream);
+
 /* The same networks with appearance features (Sec. 4.4.3: a fixed vector per image, 16 or 48 values, as additional
  * inputs of the colour net): colour input = [geo | dir_enc row | app row], desc->n_app = 16 or 48 (0: app is ignored and
  * may be NULL; only the 32-64-16 / 64-64-3 shape takes appearance inputs).  app [ceil(N/S), n_app] fp16 device, 16-byte

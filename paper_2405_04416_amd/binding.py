@@ -108,6 +108,8 @@ _SIGNATURES = {
     "dg_merge_segments": (C.c_int, [C.c_void_p] * 3 + [C.c_uint32, C.c_uint32] + [C.c_void_p] * 3),
     "dg_merge_segments_bwd": (C.c_int, [C.c_void_p] * 3 + [C.c_uint32, C.c_uint32] + [C.c_void_p] * 5),
     "dg_loss_seed": (C.c_int, [C.c_void_p] * 3 + [C.c_uint32, C.c_float] + [C.c_void_p] * 4),
+    "dg_merge_loss": (C.c_int, [C.c_void_p] * 3 + [C.c_uint32, C.c_uint32, C.c_void_p, C.c_float] + [C.c_void_p] * 6),
+    "dg_clear": (C.c_int, [C.c_void_p, C.c_uint64, C.c_void_p]),
     "dg_composite_segment_depth": (C.c_int, [C.c_void_p] * 3 + [C.c_uint32, C.c_uint32, C.c_void_p, C.c_void_p, C.c_uint32, C.c_void_p, C.c_void_p]),
     "dg_merge_depth": (C.c_int, [C.c_void_p] * 3 + [C.c_uint32, C.c_uint32, C.c_void_p, C.c_void_p]),
     "dg_adam_step": (C.c_int, [C.c_void_p] * 4 + [C.c_uint64] + [C.c_float] * 4 + [C.c_uint32, C.c_float, C.c_uint32] + [C.c_void_p] * 2),
@@ -167,7 +169,8 @@ def _ptr(t, dtype=None, optional=False):
 
 
 def _stream():
-    return torch.cuda.current_stream().cuda_stream
+    """Raw handle of the current stream (building a Stream object for it costs ten times as much, on every call)."""
+    return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
 
 
 # ------------------------------------------------------------------ host helpers
@@ -257,8 +260,9 @@ def dg_hashgrid_encode_bwd(desc, u, dfeat, N, dtable, ws=None):
                                         0 if ws is None else ws.numel() * ws.element_size(), _stream()))
 
 
-def dg_hashgrid_encode_bwd_count(desc, u, N, ws):
-    _check(lib().dg_hashgrid_encode_bwd_count(C.byref(desc), _ptr(u, torch.float32), N, _ptr(ws), ws.numel() * ws.element_size(), _stream()))
+def dg_hashgrid_encode_bwd_count(desc, u, N, ws, stream=None):
+    _check(lib().dg_hashgrid_encode_bwd_count(C.byref(desc), _ptr(u, torch.float32), N, _ptr(ws), ws.numel() * ws.element_size(),
+                                              _stream() if stream is None else stream))
 
 
 def dg_hashgrid_encode_bwd_counted(desc, u, dfeat, N, dtable, ws):
@@ -301,9 +305,9 @@ def dg_hashgrid_encode_bwd_ordered_workspace_bytes(desc, order, N):
     return int(lib().dg_hashgrid_encode_bwd_ordered_workspace_bytes(C.byref(desc), C.byref(order), N))
 
 
-def dg_hashgrid_encode_bwd_ordered_count(desc, order, u, N, ws):
+def dg_hashgrid_encode_bwd_ordered_count(desc, order, u, N, ws, stream=None):
     _check(lib().dg_hashgrid_encode_bwd_ordered_count(C.byref(desc), C.byref(order), _ptr(u, torch.float32), N, _ptr(ws),
-                                                      ws.numel() * ws.element_size(), _stream()))
+                                                      ws.numel() * ws.element_size(), _stream() if stream is None else stream))
 
 
 def dg_hashgrid_encode_bwd_ordered(desc, order, ordered, pieces, u, dfeat, largest, N, dtable, ws, counted=False):
@@ -354,6 +358,16 @@ def dg_merge_segments_bwd(Ck, Tk, seg_count, R, k_max, gC, gT, gCk, gTk):
 def dg_loss_seed(Cin, Tin, Cgt, R, lambda1, gC, gT, loss=None):
     _check(lib().dg_loss_seed(_ptr(Cin, torch.float32), _ptr(Tin, torch.float32), _ptr(Cgt, torch.float32), R, lambda1,
                               _ptr(gC, torch.float32), _ptr(gT, torch.float32), _ptr(loss, torch.float32, True), _stream()))
+
+
+def dg_merge_loss(Ck, Tk, seg_count, R, k_max, Cgt, lambda1, Cout, Tout, gC, gT, loss=None):
+    _check(lib().dg_merge_loss(_ptr(Ck, torch.float32), _ptr(Tk, torch.float32), _ptr(seg_count, torch.int32), R, k_max, _ptr(Cgt, torch.float32), lambda1,
+                               _ptr(Cout, torch.float32), _ptr(Tout, torch.float32), _ptr(gC, torch.float32), _ptr(gT, torch.float32),
+                               _ptr(loss, torch.float32, True), _stream()))
+
+
+def dg_clear(t, stream=None):
+    _check(lib().dg_clear(_ptr(t), t.numel() * t.element_size(), _stream() if stream is None else stream))
 
 
 def dg_adam_step(param, grad, m, v, lr, step, beta1=0.9, beta2=0.99, eps=1e-15, l2=0.0, skip_zero_grad=False, param_half=None):

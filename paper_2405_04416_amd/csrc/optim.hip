@@ -70,7 +70,32 @@ adam_kernel(float *__restrict__ param, float *__restrict__ grad, float *__restri
     }
 }
 
+// 16 bytes per thread and turn, past the caches (what is cleared is far larger than they are, or nobody reads it soon); the first
+// threads take what lies before and behind the 16-byte words
+__global__ void __launch_bounds__(kBlock)
+clear_kernel(uint32_t *__restrict__ dst, uint64_t n_words)
+{
+    typedef uint32_t u4 __attribute__((ext_vector_type(4)));
+    const uint64_t head = (4u - (uint32_t)(reinterpret_cast<uintptr_t>(dst) / 4u % 4u)) % 4u, skip = head < n_words ? head : n_words;
+    const uint64_t n4 = (n_words - skip) / 4, tail = n_words - skip - 4 * n4;
+    const uint64_t t = (uint64_t)blockIdx.x * kBlock + threadIdx.x;
+    u4 *body = reinterpret_cast<u4 *>(dst + skip);
+    for (uint64_t i = t; i < n4; i += (uint64_t)gridDim.x * kBlock) __builtin_nontemporal_store(u4{0u, 0u, 0u, 0u}, body + i);
+    if (t < skip) dst[t] = 0u;
+    if (t < tail) dst[skip + 4 * n4 + t] = 0u;
+}
+
 }  // namespace
+
+extern "C" int dg_clear(void *dst, uint64_t bytes, void *stream)
+{
+    if (bytes == 0) return DG_OK;
+    DG_REQUIRE(dst && dg::aligned(dst, 4) && bytes % 4 == 0, DG_ERR_ARG, "dg_clear: null pointer, or not whole 4-byte words");
+    const uint64_t blocks = (bytes / 16 + kBlock - 1) / kBlock;
+    const uint32_t grid = (uint32_t)(blocks < 1 ? 1 : blocks < 8192 ? blocks : 8192);
+    clear_kernel<<<grid, kBlock, 0, (hipStream_t)stream>>>((uint32_t *)dst, bytes / 4);
+    return dg::launch_status("dg_clear");
+}
 
 extern "C" int dg_adam_step(float *param, float *grad, float *m, float *v, uint64_t n, float lr, float beta1, float beta2,
                             float eps, uint32_t step, float l2, uint32_t skip_zero_grad, void *param_half, void *stream)

@@ -178,21 +178,29 @@ composite_bwd_kernel(const float *__restrict__ sigma, const float *__restrict__ 
 
 constexpr uint32_t kMaxK = 12;
 
+__device__ __forceinline__ void merge_ray(const float *__restrict__ Ck, const float *__restrict__ Tk, const uint32_t *__restrict__ seg_count, uint32_t r,
+                                          uint32_t k_max, float (&c)[3], float &front)
+{
+    const uint32_t K = min(seg_count[r], k_max);
+    front = 1.0f;
+    c[0] = c[1] = c[2] = 0.0f;
+    for (uint32_t k = 0; k < K; ++k) {
+        const size_t i = (size_t)r * k_max + k;
+        c[0] += front * Ck[3 * i]; c[1] += front * Ck[3 * i + 1]; c[2] += front * Ck[3 * i + 2];
+        front *= Tk[i];
+    }
+}
+
 __global__ void __launch_bounds__(kBlock)
 merge_fwd_kernel(const float *__restrict__ Ck, const float *__restrict__ Tk, const uint32_t *__restrict__ seg_count,
                  uint32_t R, uint32_t k_max, float *__restrict__ C, float *__restrict__ T)
 {
     const uint32_t r = blockIdx.x * kBlock + threadIdx.x;
     if (r >= R) return;
-    const uint32_t K = min(seg_count[r], k_max);
-    float front = 1.0f, c0 = 0.0f, c1 = 0.0f, c2 = 0.0f;
-    for (uint32_t k = 0; k < K; ++k) {
-        const size_t i = (size_t)r * k_max + k;
-        c0 += front * Ck[3 * i]; c1 += front * Ck[3 * i + 1]; c2 += front * Ck[3 * i + 2];
-        front *= Tk[i];
-    }
-    C[3 * r] = c0; C[3 * r + 1] = c1; C[3 * r + 2] = c2;
-    T[r] = front;
+    float c[3], t;
+    merge_ray(Ck, Tk, seg_count, r, k_max, c, t);
+    C[3 * r] = c[0]; C[3 * r + 1] = c[1]; C[3 * r + 2] = c[2];
+    T[r] = t;
 }
 
 // depth merges like a colour channel under Eq. 5
@@ -245,35 +253,67 @@ merge_bwd_kernel(const float *__restrict__ Ck, const float *__restrict__ Tk, con
     }
 }
 
+// seeds of one ray; returns its share of the loss
+__device__ __forceinline__ float seed_ray(const float (&c)[3], float t, const float *__restrict__ Cgt, uint32_t r, uint32_t R, float lambda1,
+                                          float *__restrict__ gC, float *__restrict__ gT)
+{
+    const float inv_r = 1.0f / (float)R;
+    float mine = 0.0f;
+    for (int k = 0; k < 3; ++k) {
+        const float e = c[k] - Cgt[3 * r + k];
+        mine += e * e * inv_r;
+        gC[3 * r + k] = 2.0f * e * inv_r;
+    }
+    const float opaque = 1.0f - t;
+    const bool clamped = !(opaque >= 1e-6f);
+    gT[r] = clamped ? 0.0f : lambda1 * inv_r / opaque;
+    if (lambda1 != 0.0f) mine -= lambda1 * inv_r * logf(clamped ? 1e-6f : opaque);
+    return mine;
+}
+
+// the workgroup's share of the loss into *loss, by all its threads
+__device__ __forceinline__ void add_loss(float mine, float *__restrict__ loss)
+{
+    __shared__ float partial[kWavesPerBlock];
+    mine = group_sum<dg::kWave>(mine);
+    if (threadIdx.x % dg::kWave == 0) partial[threadIdx.x / dg::kWave] = mine;
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        float s = 0.0f;
+        for (int w = 0; w < kWavesPerBlock; ++w) s += partial[w];
+        atomicAdd(loss, s);
+    }
+}
+
 __global__ void __launch_bounds__(kBlock)
 loss_seed_kernel(const float *__restrict__ C, const float *__restrict__ T, const float *__restrict__ Cgt, uint32_t R,
                  float lambda1, float *__restrict__ gC, float *__restrict__ gT, float *__restrict__ loss)
 {
-    __shared__ float partial[kWavesPerBlock];
     const uint32_t r = blockIdx.x * kBlock + threadIdx.x;
-    const float inv_r = 1.0f / (float)R;
     float mine = 0.0f;
     if (r < R) {
-        for (int c = 0; c < 3; ++c) {
-            const float e = C[3 * r + c] - Cgt[3 * r + c];
-            mine += e * e * inv_r;
-            gC[3 * r + c] = 2.0f * e * inv_r;
-        }
-        const float opaque = 1.0f - T[r];
-        const bool clamped = !(opaque >= 1e-6f);
-        gT[r] = clamped ? 0.0f : lambda1 * inv_r / opaque;
-        if (lambda1 != 0.0f) mine -= lambda1 * inv_r * logf(clamped ? 1e-6f : opaque);
+        const float c[3] = {C[3 * r], C[3 * r + 1], C[3 * r + 2]};
+        mine = seed_ray(c, T[r], Cgt, r, R, lambda1, gC, gT);
     }
-    if (loss) {
-        mine = group_sum<dg::kWave>(mine);
-        if (threadIdx.x % dg::kWave == 0) partial[threadIdx.x / dg::kWave] = mine;
-        __syncthreads();
-        if (threadIdx.x == 0) {
-            float s = 0.0f;
-            for (int w = 0; w < kWavesPerBlock; ++w) s += partial[w];
-            atomicAdd(loss, s);
-        }
+    if (loss) add_loss(mine, loss);
+}
+
+// merge_fwd_kernel and loss_seed_kernel in one pass over the rays
+__global__ void __launch_bounds__(kBlock)
+merge_loss_kernel(const float *__restrict__ Ck, const float *__restrict__ Tk, const uint32_t *__restrict__ seg_count, uint32_t R, uint32_t k_max,
+                  const float *__restrict__ Cgt, float lambda1, float *__restrict__ C, float *__restrict__ T, float *__restrict__ gC,
+                  float *__restrict__ gT, float *__restrict__ loss)
+{
+    const uint32_t r = blockIdx.x * kBlock + threadIdx.x;
+    float mine = 0.0f;
+    if (r < R) {
+        float c[3], t;
+        merge_ray(Ck, Tk, seg_count, r, k_max, c, t);
+        C[3 * r] = c[0]; C[3 * r + 1] = c[1]; C[3 * r + 2] = c[2];
+        T[r] = t;
+        mine = seed_ray(c, t, Cgt, r, R, lambda1, gC, gT);
     }
+    if (loss) add_loss(mine, loss);
 }
 
 int seg_args_ok(uint32_t n_seg, uint32_t S, uint32_t k_max, const char *who)
@@ -405,4 +445,14 @@ extern "C" int dg_loss_seed(const float *C, const float *T, const float *Cgt, ui
     DG_REQUIRE(C && T && Cgt && gC && gT, DG_ERR_ARG, "dg_loss_seed: null pointer");
     loss_seed_kernel<<<(R + kBlock - 1) / kBlock, kBlock, 0, (hipStream_t)stream>>>(C, T, Cgt, R, lambda1, gC, gT, loss);
     return dg::launch_status("dg_loss_seed");
+}
+
+extern "C" int dg_merge_loss(const float *Ck, const float *Tk, const uint32_t *seg_count, uint32_t R, uint32_t k_max, const float *Cgt, float lambda1,
+                             float *C, float *T, float *gC, float *gT, float *loss, void *stream)
+{
+    DG_REQUIRE(k_max >= 1 && k_max <= kMaxK, DG_ERR_UNSUPPORTED, "dg_merge_loss: k_max=%u outside 1..%u", k_max, kMaxK);
+    if (R == 0) return DG_OK;
+    DG_REQUIRE(Ck && Tk && seg_count && Cgt && C && T && gC && gT, DG_ERR_ARG, "dg_merge_loss: null pointer");
+    merge_loss_kernel<<<(R + kBlock - 1) / kBlock, kBlock, 0, (hipStream_t)stream>>>(Ck, Tk, seg_count, R, k_max, Cgt, lambda1, C, T, gC, gT, loss);
+    return dg::launch_status("dg_merge_loss");
 }

@@ -59,17 +59,10 @@ __device__ __forceinline__ void insert_segment(SegmentList &L, uint32_t k_max, f
 
 // A partition covers its box minus its hole (Sec. 4.2.2: coarse sub-models cover the outer box around the inner one);
 // a ray meets such a region in up to two pieces, [t_in, hole entry] and [hole exit, t_out].
-__global__ void __launch_bounds__(kBlock)
-ray_aabb_kernel(const float *__restrict__ o, const float *__restrict__ d, uint32_t R,
-                const float *__restrict__ parts, const float *__restrict__ holes, uint32_t P, float t_min, uint32_t k_max,
-                uint32_t *__restrict__ seg_count, float *__restrict__ seg_t, int32_t *__restrict__ seg_part,
-                uint32_t *__restrict__ status)
+__device__ __forceinline__ void trace_ray(const float *__restrict__ o, const float *__restrict__ d, uint32_t r, const float *boxes, const float *hboxes,
+                                          uint32_t P, float t_min, uint32_t k_max, uint32_t *__restrict__ seg_count, float *__restrict__ seg_t,
+                                          int32_t *__restrict__ seg_part, uint32_t *__restrict__ status, uint32_t *hist)
 {
-    __shared__ float boxes[DG_MAX_PARTITIONS * 6], hboxes[DG_MAX_PARTITIONS * 6];
-    for (uint32_t i = threadIdx.x; i < P * 6; i += kBlock) { boxes[i] = parts[i]; hboxes[i] = holes ? holes[i] : 0.0f; }
-    __syncthreads();
-    const uint32_t r = blockIdx.x * kBlock + threadIdx.x;
-    if (r >= R) return;
     const float oo[3] = {o[3 * r], o[3 * r + 1], o[3 * r + 2]}, dd[3] = {d[3 * r], d[3 * r + 1], d[3 * r + 2]};
     float inv[3];
     for (int a = 0; a < 3; ++a) inv[a] = dd[a] != 0.0f ? 1.0f / dd[a] : 0.0f;
@@ -99,27 +92,30 @@ ray_aabb_kernel(const float *__restrict__ o, const float *__restrict__ d, uint32
         seg_part[(size_t)r * k_max + k] = used ? L.pid[k] : -1;
     }
     if (L.overflow) atomicOr(status, 1u);
+    for (uint32_t k = 0; k < L.cnt; ++k) atomicAdd(&hist[L.pid[k]], 1u);
+}
+
+__global__ void __launch_bounds__(kBlock)
+ray_aabb_kernel(const float *__restrict__ o, const float *__restrict__ d, uint32_t R,
+                const float *__restrict__ parts, const float *__restrict__ holes, uint32_t P, float t_min, uint32_t k_max,
+                uint32_t *__restrict__ seg_count, float *__restrict__ seg_t, int32_t *__restrict__ seg_part,
+                uint32_t *__restrict__ status, uint32_t *__restrict__ block_hist)
+{
+    __shared__ uint32_t hist[DG_MAX_PARTITIONS];      // segments per box, the first pass of their distribution (block_hist non-null)
+    if (threadIdx.x < DG_MAX_PARTITIONS) hist[threadIdx.x] = 0;
+    __shared__ float boxes[DG_MAX_PARTITIONS * 6], hboxes[DG_MAX_PARTITIONS * 6];
+    for (uint32_t i = threadIdx.x; i < P * 6; i += kBlock) { boxes[i] = parts[i]; hboxes[i] = holes ? holes[i] : 0.0f; }
+    __syncthreads();
+    const uint32_t r = blockIdx.x * kBlock + threadIdx.x;
+    if (r < R) trace_ray(o, d, r, boxes, hboxes, P, t_min, k_max, seg_count, seg_t, seg_part, status, hist);
+    if (!block_hist) return;
+    __syncthreads();
+    if (threadIdx.x < P) block_hist[(size_t)threadIdx.x * gridDim.x + blockIdx.x] = hist[threadIdx.x];
 }
 
 // ---------------------------------------------------------------- stable distribution to boxes
-// Three passes: per-block histogram, scan over blocks, scatter with in-block stable ranks.
+// Three passes: per-block histogram (in ray_aabb_kernel), scan over blocks, scatter with in-block stable ranks.
 // A ray holds at most two segments per partition (a convex box is crossed once; a box with a hole in up to two pieces).
-__global__ void __launch_bounds__(kBlock)
-bucket_count_kernel(const uint32_t *__restrict__ seg_count, const int32_t *__restrict__ seg_part, uint32_t R,
-                    uint32_t k_max, uint32_t P, uint32_t n_blocks, uint32_t *__restrict__ block_hist)
-{
-    __shared__ uint32_t hist[DG_MAX_PARTITIONS];
-    if (threadIdx.x < DG_MAX_PARTITIONS) hist[threadIdx.x] = 0;
-    __syncthreads();
-    const uint32_t r = blockIdx.x * kBlock + threadIdx.x;
-    if (r < R) {
-        const uint32_t cnt = seg_count[r];
-        for (uint32_t k = 0; k < cnt; ++k) atomicAdd(&hist[seg_part[(size_t)r * k_max + k]], 1u);
-    }
-    __syncthreads();
-    if (threadIdx.x < P) block_hist[(size_t)threadIdx.x * n_blocks + blockIdx.x] = hist[threadIdx.x];
-}
-
 // one wavefront per box at a time: exclusive scan of that box's per-block counts; then box offsets
 constexpr int kScanThreads = 1024;
 __global__ void __launch_bounds__(kScanThreads)
@@ -283,7 +279,7 @@ extern "C" size_t dg_segments_workspace_bytes(uint32_t R, uint32_t P)
 
 namespace {
 
-// shared by the two entry points below: argument checks and the four launches; hist is the [P, n_blocks] counter table
+// shared by the two entry points below: argument checks and the three launches; hist is the [P, n_blocks] counter table
 int ray_aabb_segments(const char *who, const float *o, const float *d, uint32_t R, const float *parts, const float *holes,
                       uint32_t P, float t_min, uint32_t k_max, uint32_t *seg_count, float *seg_t, int32_t *seg_part,
                       uint32_t *part_offset, uint32_t *seg_ray, uint32_t *seg_slot, uint32_t *status, uint32_t *hist,
@@ -291,11 +287,10 @@ int ray_aabb_segments(const char *who, const float *o, const float *d, uint32_t 
 {
     const uint32_t n_blocks = (R + kBlock - 1) / kBlock;
     if (R > 0) {
-        ray_aabb_kernel<<<n_blocks, kBlock, 0, st>>>(o, d, R, parts, holes, P, t_min, k_max, seg_count, seg_t, seg_part, status);
+        ray_aabb_kernel<<<n_blocks, kBlock, 0, st>>>(o, d, R, parts, holes, P, t_min, k_max, seg_count, seg_t, seg_part, status,
+                                                  part_offset ? hist : nullptr);
     }
     if (part_offset) {
-        if (R > 0)
-            bucket_count_kernel<<<n_blocks, kBlock, 0, st>>>(seg_count, seg_part, R, k_max, P, n_blocks, hist);
         bucket_scan_kernel<<<1, kScanThreads, 0, st>>>(P, n_blocks, hist, part_offset);
         if (R > 0)
             bucket_scatter_kernel<<<n_blocks, kBlock, 0, st>>>(seg_count, seg_part, R, k_max, P, n_blocks, hist,
@@ -375,7 +370,7 @@ extern "C" int dg_ray_aabb_segments_static(const float *o, const float *d, uint3
                "dg_ray_aabb_segments with a workspace", counters, kStaticCounters, R, P);
     uint32_t *hist = nullptr;
     if (int rc = static_counters(&hist)) return rc;
-    // nothing to clear: the counting kernel writes every counter [p < P, block < ceil(R/256)] the later kernels read
+    // nothing to clear: the tracing kernel writes every counter [p < P, block < ceil(R/256)] the later kernels read
     return ray_aabb_segments(who, o, d, R, parts, holes, P, t_min, k_max, seg_count, seg_t, seg_part, part_offset, seg_ray, seg_slot,
                              status, hist, (hipStream_t)stream);
 }

@@ -32,9 +32,17 @@ class SubModel:
     def __init__(self, grid_desc, mlp_desc, table, weights):
         self.grid, self.mlp = grid_desc, mlp_desc
         self.table, self.weights = table, weights
-        self.dtable = torch.zeros_like(table)
-        self.dW = torch.zeros(weights.numel(), dtype=torch.float32, device=weights.device)
+        # both gradients in one buffer, so that one launch clears them
+        buf = torch.zeros((table.numel() + 3) // 4 * 4 + weights.numel(), dtype=torch.float32, device=table.device)
+        self.dtable, self.dW = buf[:table.numel()].view(table.shape), buf[buf.numel() - weights.numel():]
+        self._grads = (buf, self.dtable, self.dW)
         self.opt = None     # optimiser state, allocated by the first optimiser step
+
+    def clear_gradients(self, stream=None):
+        """Zeroes both gradients, on the current stream or on the raw stream given."""
+        buf, dtable, dW = self._grads
+        for t in (buf,) if self.dtable is dtable and self.dW is dW else (self.dtable, self.dW):      # the caller may have put buffers of its own there
+            B.dg_clear(t, stream)
 
     def optimiser_state(self):
         """Adam moments of the table and of the weights, and the fp32 master copy of the fp16 weights."""
@@ -77,7 +85,7 @@ class TrainStep:
         cap = R * k_max if max_segments is None else max_segments
         self.cap = cap
         self.seg_count, self.seg_t, self.seg_part = z(R, dt=i32), z(R, k_max, 2), z(R, k_max, dt=i32)
-        self.part_offset, self.status = z(self.P + 1, dt=i32), z(1, dt=i32)
+        self.part_offset = z(self.P + 1, dt=i32)
         self.seg_ray, self.seg_slot = z(R * k_max, dt=i32), z(R * k_max, dt=i32)
         self.ws_seg = z(max(B.dg_segments_workspace_bytes(R, self.P) // 4, 1), dt=i32)
         self.occ = occupancy
@@ -101,7 +109,9 @@ class TrainStep:
         self.Ck, self.Tk = z(R, k_max, 3), z(R, k_max)
         self.gCk, self.gTk = z(R, k_max, 3), z(R, k_max)
         self.C, self.T, self.gC, self.gT = z(R, 3), z(R), z(R, 3), z(R)
-        self.loss = z(1)
+        # the two accumulated words, cleared together at the start of a step
+        self._words = z(2)
+        self.loss, self.status = self._words[:1], self._words[1:].view(i32)
         self.ws_mlp = z(B.dg_mlp_bwd_app_workspace_bytes(any_model.mlp, n, S if occupancy is None else 1) // 4 + 64)
         # workspace of the binned table-gradient pass, capped (the call batches itself when it is smaller than ideal)
         want = max(self._encode_ws_bytes(mm, n) for mm in models.values())
@@ -114,6 +124,7 @@ class TrainStep:
         # each in a workspace of its own, were measured on four and eight resident sub-models: no gain, 32.5 against 32.3 ms
         # and 40.0 against 40.0 ms per step.)
         self.side = torch.cuda.Stream(device=self.dev) if binned_backward and occupancy is None else None
+        self.events = tuple(torch.cuda.Event() for _ in range(3)) if self.side is not None else None
         self.counted = None     # (partition, samples, event) of a count that is ahead
         # Samples in spatial order (large batches): the sorted list of every sub-model and what its bricks hold; the scratch of
         # the sort grows to the largest one asked for.
@@ -232,8 +243,8 @@ class TrainStep:
         return {k: (len(v), sum(a.elapsed_time(b) for a, b in v)) for k, v in (self.timings or {}).items()}
 
     # -- forward ---------------------------------------------------------------------------
-    def segments(self, o, d, t_min=0.0):
-        self.status.zero_()
+    def segments(self, o, d, t_min=0.0, clear_loss=False):
+        B.dg_clear(self._words if clear_loss else self.status)
         with self._timed("dg_ray_aabb_segments"):
             B.dg_ray_aabb_segments(o, d, self.parts, t_min, self.k_max, self.seg_count, self.seg_t, self.seg_part,
                                    self.status, self.part_offset, self.seg_ray, self.seg_slot, self.ws_seg, holes=self.holes)
@@ -265,11 +276,8 @@ class TrainStep:
         self._partials(o, d, jitter, training=True)
         if foreign is not None:
             foreign(self)
-        with self._timed("dg_merge_segments"):
-            B.dg_merge_segments(self.Ck, self.Tk, self.seg_count, self.R, self.k_max, self.C, self.T)
-        self.loss.zero_()
-        with self._timed("dg_loss_seed"):
-            B.dg_loss_seed(self.C, self.T, Cgt, self.R, self.lambda1, self.gC, self.gT, self.loss)
+        with self._timed("dg_merge_loss"):
+            B.dg_merge_loss(self.Ck, self.Tk, self.seg_count, self.R, self.k_max, Cgt, self.lambda1, self.C, self.T, self.gC, self.gT, self.loss)
 
     def render(self, o, d, jitter=None, fused=None):
         """Evaluation rendering (Sec. 4.4.2): forward only, every sub-model renders its segments and the partial
@@ -302,23 +310,20 @@ class TrainStep:
                 else B.dg_hashgrid_encode_bwd_ordered_workspace_bytes(m.grid, order, N))
         if need > self.ws_enc.numel() * self.ws_enc.element_size():
             return                                  # the workspace would batch: counted with each batch, as usual
-        here = torch.cuda.Event()
-        here.record()
-        go = torch.cuda.Event()
-        with torch.cuda.stream(self.side):
-            self.side.wait_event(here)
-            go.record()
-            if order is None:
-                B.dg_hashgrid_encode_bwd_count(m.grid, self.u[sl], N, self.ws_enc)
-            else:
-                B.dg_hashgrid_encode_bwd_ordered_count(m.grid, order, self.u[sl], N, self.ws_enc)
-            m.dtable.zero_()
-            m.dW.zero_()
-            done = torch.cuda.Event()
-            done.record()
+        main, side = torch.cuda.current_stream(), self.side
+        here, go, done = self.events
+        here.record(main)
+        side.wait_event(here)
+        go.record(side)
+        if order is None:
+            B.dg_hashgrid_encode_bwd_count(m.grid, self.u[sl], N, self.ws_enc, side.cuda_stream)
+        else:
+            B.dg_hashgrid_encode_bwd_ordered_count(m.grid, order, self.u[sl], N, self.ws_enc, side.cuda_stream)
+        m.clear_gradients(side.cuda_stream)
+        done.record(side)
         # this stream goes on once the second one has got that far: the count sweep's few workgroups are then handed out
         # before the forward gather's millions arrive and fill every wavefront slot of the chip
-        torch.cuda.current_stream().wait_event(go)
+        main.wait_event(go)
         self.counted = (p, N, done)
 
     def _partials(self, o, d, jitter=None, want_t=False, fused_depth=None, training=False):
@@ -327,7 +332,7 @@ class TrainStep:
         self.counted = None
         self.layout = {}
         S = self.S
-        self.segments(o, d)
+        self.segments(o, d, clear_loss=training)
         # the sub-model whose backward pass runs first: only its counts may wait in the workspace that all share
         first = next((p for p in self.resident if self.offsets[p + 1] > self.offsets[p]), None)
         if self.occ is not None:
@@ -422,8 +427,7 @@ class TrainStep:
         for p in self.resident:
             m = self.models[p]
             with self._timed("zero_gradients"):
-                m.dtable.zero_()
-                m.dW.zero_()
+                m.clear_gradients()
             if p not in self.samples or self.samples[p][1] == 0:
                 continue
             s0, N = self.samples[p]
@@ -487,8 +491,7 @@ class TrainStep:
                 self.counted = None
             else:
                 with self._timed("zero_gradients"):
-                    m.dtable.zero_()
-                    m.dW.zero_()
+                    m.clear_gradients()
             if n_seg == 0:
                 continue
             N = n_seg * S
