@@ -193,3 +193,17 @@ def test_ragged_composite(n_seg, k_max, longest):
     mag = oracle.composite_bwd_ragged(sigma, rgb, delta, first, np.abs(gCk[ray, slot]), -np.abs(gTk[ray, slot]))[0]
     mag = np.abs(mag) + np.abs(rs)
     assert np.all(np.abs(host(dsigma)[:n] - rs) <= 20 * TOL_F32 * np.maximum(mag, np.mean(mag)))
+
+
+@pytest.mark.parametrize("n", [1, 4096, 4097, 512 * 4096, 512 * 4096 + 33])
+def test_bits_over_several_turns(n):
+    """Grids at the edge of what the workgroups of one launch take in one turn."""
+    say("occ bits n=%d" % n)
+    density = torch.rand(n, device="cuda:0")
+    bits = torch.full(((n + 31) // 32,), -1, dtype=torch.int32, device="cuda:0")
+    n_set = torch.zeros(1, dtype=torch.int32, device="cuda:0")
+    B.dg_occ_bits(density, 0.6, bits, n_set)
+    want = host(density) > np.float32(0.6)
+    got = np.unpackbits(host(bits).view(np.uint8), bitorder="little")
+    np.testing.assert_array_equal(got[:n].astype(bool), want)
+    assert not got[n:].any() and int(n_set.item()) == int(want.sum())
