@@ -200,18 +200,19 @@ typedef struct dg_order_desc {
 } dg_order_desc;
 /* Host.  Bricks for N samples of a sub-model with this grid (L = 16, F = 2; else DG_ERR_UNSUPPORTED). */
 int dg_order_desc_init(dg_order_desc *order, const dg_grid_desc *desc, uint64_t N);
-/* ordered [N] of 16 bytes each (x, y, z fp32 and the sample's index, uint32; device, 16-byte aligned);
+/* ordered [N] of 16 bytes each (x, y, z fp32 and ids[sample], uint32; ids NULL: the sample's index; device, 16-byte aligned);
  * pieces: dg_order_pieces_words(order, N) words that list which stretch of the order belongs to which brick (read by
  * dg_hashgrid_encode_bwd_ordered; 8-byte aligned).  Its word 1 is set to 0 and left to the caller: room for the `largest`
  * word of dg_mlp_bwd_rows.  N < 2^32 - 1.
  * ws: dg_order_workspace_bytes(order) bytes of device memory, 256-byte aligned. */
 size_t dg_order_workspace_bytes(const dg_order_desc *order);
 size_t dg_order_pieces_words(const dg_order_desc *order, uint64_t N);
-int dg_order_samples(const dg_order_desc *order, const float *u, uint64_t N, void *ordered, uint32_t *pieces,
+int dg_order_samples(const dg_order_desc *order, const float *u, const uint32_t *ids, uint64_t N, void *ordered, uint32_t *pieces,
                      void *ws, size_t ws_bytes, void *stream);
-/* dg_hashgrid_encode_fwd on the sorted list: row `index` of feat [N, L*F] fp16 (16-byte aligned). */
+/* dg_hashgrid_encode_fwd on the sorted list: row `index` of feat [N, L*F] fp16 (16-byte aligned), or, by_position, row i for
+ * the i-th sample of the list. */
 int dg_hashgrid_encode_fwd_ordered(const dg_grid_desc *desc, const float *table, const void *ordered, uint64_t N,
-                                   void *feat, void *stream);
+                                   uint32_t by_position, void *feat, void *stream);
 /* dg_hashgrid_encode_bwd on the sorted list.  dfeat: rows [N, 2 * n_merged] fp32 of the merged levels (16-byte aligned, in
  * the samples' original order), then the planes [L - n_merged, N, 2] of the others -- as dg_mlp_bwd_rows writes it; u [N,3]
  * the samples in their original order.  *largest: device word, the bit pattern of a float that no |dfeat| exceeds.  The
@@ -416,6 +417,11 @@ int dg_occ_decay(float *density, uint32_t n_cells, float factor, void *stream);
  * and so is a cell index >= n_cells */
 int dg_occ_update(float *density, uint32_t n_cells, const uint32_t *cell, const float *sigma, uint32_t M,
                   void *stream);
+/* The field's densities at M candidates, taken into the grid as by dg_occ_update, in one kernel: the density half of dg_mlp_fwd
+ * (the colour net is not evaluated, the densities are not written).  feat: planes [L, M, 2] fp16, or rows [M, L*F] (16-byte
+ * aligned) if rows.  The cell of candidate i is cell[i * cell_stride].  Only for the 32-64-16 density net (DG_ERR_UNSUPPORTED). */
+int dg_occ_evaluate(const dg_mlp_desc *desc, const void *weights, const void *feat, uint32_t rows, const uint32_t *cell,
+                    uint32_t cell_stride, uint64_t M, float *density, uint32_t n_cells, void *stream);
 /* bit of cell c = density[c] > threshold; *n_set (device, may be NULL) "+=" the number of set bits */
 int dg_occ_bits(const float *density, uint32_t n_cells, float threshold, uint32_t *bits, uint32_t *n_set,
                 void *stream);

@@ -74,14 +74,14 @@ _SIGNATURES = {
     "dg_hashgrid_corner_indices": (C.c_int, [C.POINTER(GridDesc), C.c_void_p, C.c_uint64, C.c_void_p, C.c_void_p]),
     "dg_order_desc_init": (C.c_int, [C.POINTER(OrderDesc), C.POINTER(GridDesc), C.c_uint64]),
     "dg_order_workspace_bytes": (C.c_size_t, [C.POINTER(OrderDesc)]),
-    "dg_order_samples": (C.c_int, [C.POINTER(OrderDesc), C.c_void_p, C.c_uint64, C.c_void_p, C.c_void_p, C.c_void_p, C.c_size_t, C.c_void_p]),
+    "dg_order_samples": (C.c_int, [C.POINTER(OrderDesc), C.c_void_p, C.c_void_p, C.c_uint64, C.c_void_p, C.c_void_p, C.c_void_p, C.c_size_t, C.c_void_p]),
     "dg_order_pieces_words": (C.c_size_t, [C.POINTER(OrderDesc), C.c_uint64]),
     "dg_hashgrid_encode_bwd_ordered_workspace_bytes": (C.c_size_t, [C.POINTER(GridDesc), C.POINTER(OrderDesc), C.c_uint64]),
     "dg_hashgrid_encode_bwd_ordered_count": (C.c_int, [C.POINTER(GridDesc), C.POINTER(OrderDesc), C.c_void_p, C.c_uint64, C.c_void_p, C.c_size_t,
                                                        C.c_void_p]),
     "dg_hashgrid_encode_bwd_ordered": (C.c_int, [C.POINTER(GridDesc), C.POINTER(OrderDesc)] + [C.c_void_p] * 5 + [C.c_uint64] + [C.c_void_p] * 2
                                        + [C.c_size_t, C.c_uint32, C.c_void_p]),
-    "dg_hashgrid_encode_fwd_ordered": (C.c_int, [C.POINTER(GridDesc), C.c_void_p, C.c_void_p, C.c_uint64, C.c_void_p, C.c_void_p]),
+    "dg_hashgrid_encode_fwd_ordered": (C.c_int, [C.POINTER(GridDesc), C.c_void_p, C.c_void_p, C.c_uint64, C.c_uint32, C.c_void_p, C.c_void_p]),
     "dg_mlp_weight_count": (C.c_size_t, [C.POINTER(MlpDesc)]),
     "dg_mlp_fwd": (C.c_int, [C.POINTER(MlpDesc), C.c_void_p, C.c_void_p, C.c_void_p, C.c_uint32, C.c_uint64, C.c_void_p,
                              C.c_void_p, C.c_void_p]),
@@ -120,6 +120,7 @@ _SIGNATURES = {
                                     C.c_void_p, C.c_void_p, C.c_void_p]),
     "dg_occ_decay": (C.c_int, [C.c_void_p, C.c_uint32, C.c_float, C.c_void_p]),
     "dg_occ_update": (C.c_int, [C.c_void_p, C.c_uint32, C.c_void_p, C.c_void_p, C.c_uint32, C.c_void_p]),
+    "dg_occ_evaluate": (C.c_int, [C.POINTER(MlpDesc), C.c_void_p, C.c_void_p, C.c_uint32, C.c_void_p, C.c_uint32, C.c_uint64, C.c_void_p, C.c_uint32, C.c_void_p]),
     "dg_occ_bits": (C.c_int, [C.c_void_p, C.c_uint32, C.c_float, C.c_void_p, C.c_void_p, C.c_void_p]),
     "dg_march_workspace_bytes": (C.c_size_t, [C.c_uint32]),
     "dg_march_segments": (C.c_int, [C.c_void_p] * 5 + [C.c_uint32, C.c_uint32, C.POINTER(C.c_float), C.POINTER(OccDesc), C.c_void_p, C.c_float,
@@ -289,15 +290,15 @@ def dg_order_pieces_words(order, N):
     return int(lib().dg_order_pieces_words(C.byref(order), N))
 
 
-def dg_order_samples(order, u, N, ordered, pieces, ws):
-    assert u.numel() >= 3 * N and ordered.numel() >= 4 * N and pieces.numel() >= dg_order_pieces_words(order, N)
-    _check(lib().dg_order_samples(C.byref(order), _ptr(u, torch.float32), N, _ptr(ordered, torch.float32), _ptr(pieces, torch.int32), _ptr(ws),
+def dg_order_samples(order, u, N, ordered, pieces, ws, ids=None):
+    assert u.numel() >= 3 * N and ordered.numel() >= 4 * N and pieces.numel() >= dg_order_pieces_words(order, N) and (ids is None or ids.numel() >= N)
+    _check(lib().dg_order_samples(C.byref(order), _ptr(u, torch.float32), None if ids is None else _ptr(ids, torch.int32), N, _ptr(ordered, torch.float32), _ptr(pieces, torch.int32), _ptr(ws),
                                   ws.numel() * ws.element_size(), _stream()))
 
 
-def dg_hashgrid_encode_fwd_ordered(desc, table, ordered, N, feat):
+def dg_hashgrid_encode_fwd_ordered(desc, table, ordered, N, feat, by_position=False):
     assert ordered.numel() >= 4 * N and feat.numel() >= 32 * N
-    _check(lib().dg_hashgrid_encode_fwd_ordered(C.byref(desc), _ptr(table, torch.float32), _ptr(ordered, torch.float32), N,
+    _check(lib().dg_hashgrid_encode_fwd_ordered(C.byref(desc), _ptr(table, torch.float32), _ptr(ordered, torch.float32), N, 1 if by_position else 0,
                                                 _ptr(feat, torch.float16), _stream()))
 
 
@@ -424,6 +425,12 @@ def dg_occ_update(density, cell, sigma, M):
     assert cell.numel() >= M and sigma.numel() >= M
     _check(lib().dg_occ_update(_ptr(density, torch.float32), density.numel(), _ptr(cell, torch.int32), _ptr(sigma, torch.float32), M,
                                _stream()))
+
+
+def dg_occ_evaluate(desc, weights, feat, rows, cell, cell_stride, M, density):
+    assert feat.numel() >= desc.n_feat * M and (M == 0 or cell.numel() > (M - 1) * cell_stride)
+    _check(lib().dg_occ_evaluate(C.byref(desc), _ptr(weights, torch.float16), _ptr(feat, torch.float16), 1 if rows else 0, _ptr(cell, torch.int32),
+                                 cell_stride, M, _ptr(density, torch.float32), density.numel(), _stream()))
 
 
 def dg_occ_bits(density, threshold, bits, n_set=None):

@@ -52,6 +52,8 @@ int brick_bwd(const char *who, const dg_grid_desc *d, const dg_order_desc *order
 // matrix-core path of the 32-64-16 / (32 + n_app)-64-64-3 field MLPs (mlp_mfma.hip); n_app = 0, 16 or 48
 size_t mlp_mfma_workspace_bytes(uint64_t N, uint32_t n_app, uint32_t S);
 size_t mlp_mfma_weight_count(uint32_t n_app);
+void mlp_mfma_density_max(const void *weights, const void *feat, bool rows, const uint32_t *cell, uint32_t cell_stride, uint64_t N, float *density,
+                          uint32_t n_cells, hipStream_t st);
 void mlp_mfma_fwd(const void *weights, const void *feat, bool rows, const void *dir_enc, const void *app, uint32_t n_app, uint32_t S,
                   uint64_t N, uint32_t act_c, float *sigma, float *rgb, hipStream_t st);
 void mlp_mfma_render(const void *weights, const void *feat, bool rows, const void *dir_enc, const void *app, uint32_t n_app, uint32_t S,

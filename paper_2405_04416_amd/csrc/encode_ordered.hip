@@ -22,7 +22,7 @@ constexpr uint32_t kXcds = 8;
 // 12.3 -> 6.8; 13.3 M, T = 2^19 2.38 -> 1.49; scattered rows of 64 bytes instead of planes cost 0.8, 0.47 and 0.3 ms of it.
 __global__ void __launch_bounds__(kBlock)
 encode_fwd_ordered_kernel(dg_grid_desc g, const float2 *__restrict__ table, const float4 *__restrict__ ordered, uint64_t N,
-                          uint4 *__restrict__ feat, uint32_t blocks_per_xcd)
+                          bool by_position, uint4 *__restrict__ feat, uint32_t blocks_per_xcd)
 {
     const uint32_t block = (blockIdx.x % kXcds) * blocks_per_xcd + blockIdx.x / kXcds;
     const uint64_t i = (uint64_t)block * (kBlock / 2) + threadIdx.x / 2;
@@ -68,7 +68,7 @@ encode_fwd_ordered_kernel(dg_grid_desc g, const float2 *__restrict__ table, cons
         if (l < 8) out[l] = f;
         else out[l - 8] = cx ? f : out[l - 8];
     }
-    uint4 *half_row = feat + (size_t)__float_as_uint(s.w) * 4 + 2 * cx;
+    uint4 *half_row = feat + (size_t)(by_position ? (uint32_t)i : __float_as_uint(s.w)) * 4 + 2 * cx;
     half_row[0] = make_uint4(out[0], out[1], out[2], out[3]);
     half_row[1] = make_uint4(out[4], out[5], out[6], out[7]);
 }
@@ -296,7 +296,7 @@ int brick_bwd(const char *who, const dg_grid_desc *d, const dg_order_desc *order
 }  // namespace dg
 
 extern "C" int dg_hashgrid_encode_fwd_ordered(const dg_grid_desc *desc, const float *table, const void *ordered, uint64_t N,
-                                              void *feat, void *stream)
+                                              uint32_t by_position, void *feat, void *stream)
 {
     const char *who = "dg_hashgrid_encode_fwd_ordered";
     if (int rc = dg::check_grid_desc(desc, who)) return rc;
@@ -306,7 +306,7 @@ extern "C" int dg_hashgrid_encode_fwd_ordered(const dg_grid_desc *desc, const fl
     DG_REQUIRE(dg::aligned(table, 8) && dg::aligned(ordered, 16) && dg::aligned(feat, 16), DG_ERR_ARG, "%s: misaligned pointer", who);
     const uint64_t blocks = (2 * N + kBlock - 1) / kBlock, per_xcd = (blocks + kXcds - 1) / kXcds;
     DG_REQUIRE(per_xcd * kXcds <= 0x7fffffffull, DG_ERR_UNSUPPORTED, "%s: N too large for one launch", who);
-    encode_fwd_ordered_kernel<<<(uint32_t)(per_xcd * kXcds), kBlock, 0, (hipStream_t)stream>>>(*desc, (const float2 *)table, (const float4 *)ordered, N,
+    encode_fwd_ordered_kernel<<<(uint32_t)(per_xcd * kXcds), kBlock, 0, (hipStream_t)stream>>>(*desc, (const float2 *)table, (const float4 *)ordered, N, by_position != 0,
                                                                                               (uint4 *)feat, (uint32_t)per_xcd);
     return dg::launch_status(who);
 }

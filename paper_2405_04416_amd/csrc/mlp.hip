@@ -163,3 +163,18 @@ extern "C" int dg_mlp_bwd_rows(const dg_mlp_desc *desc, const void *weights, con
 {
     return mlp_bwd("dg_mlp_bwd_rows", desc, weights, feat, true, n_merged, dir_enc, app, S, N, dsigma, drgb, loss_scale, dfeat, largest, dW, ws, ws_bytes, stream);
 }
+
+extern "C" int dg_occ_evaluate(const dg_mlp_desc *desc, const void *weights, const void *feat, uint32_t rows, const uint32_t *cell,
+                               uint32_t cell_stride, uint64_t M, float *density, uint32_t n_cells, void *stream)
+{
+    const char *who = "dg_occ_evaluate";
+    const int net = which_net(desc, who);
+    if (net < 0) return net;
+    DG_REQUIRE(net == 1, DG_ERR_UNSUPPORTED, "%s: only the 32-64-16 density net has this kernel", who);
+    DG_REQUIRE(cell_stride >= 1, DG_ERR_ARG, "%s: cell_stride must be >= 1", who);
+    if (M == 0) return DG_OK;
+    DG_REQUIRE(weights && feat && cell && density, DG_ERR_ARG, "%s: null pointer", who);
+    DG_REQUIRE(dg::aligned(feat, rows ? 16 : 4), DG_ERR_ARG, "%s: feat must be %d-byte aligned", who, rows ? 16 : 4);
+    dg::mlp_mfma_density_max(weights, feat, rows != 0, cell, cell_stride, M, density, n_cells, (hipStream_t)stream);
+    return dg::launch_status(who);
+}

@@ -7,7 +7,7 @@
 //
 //   1. bricks: the box is cut into a few thousand to 2^15 equal bricks (700 to 1200 samples each).  Count, scan,
 //      scatter with one persistent tiling; the counters of all bricks live in LDS, so there are no global atomics.
-//      A sample becomes 16 bytes: its coordinates and the index it came from.
+//      A sample becomes 16 bytes: its coordinates and the index it came from (or a number of the caller's).
 //   2. inside a brick: pencils along x (the table's contiguous direction), sorted in LDS.
 // The order is a matter of speed alone: any order gives the same results.
 // Bound by the scatter's lone 16-byte writes (33.5 M samples: 0.53 of 1.05 ms) and the LDS sort (0.28 ms).
@@ -112,8 +112,8 @@ brick_scan_totals_kernel(const uint32_t *__restrict__ totals, uint32_t n_keys, u
 
 // same tiling as the count: a sample takes its place with an LDS add on its brick's counter
 __global__ void __launch_bounds__(kSweepBlock)
-brick_scatter_kernel(Bricks b, const float *__restrict__ u, uint64_t N, const uint32_t *__restrict__ rows, const uint32_t *__restrict__ first,
-                     float4 *__restrict__ ordered)
+brick_scatter_kernel(Bricks b, const float *__restrict__ u, const uint32_t *__restrict__ ids, uint64_t N, const uint32_t *__restrict__ rows,
+                     const uint32_t *__restrict__ first, float4 *__restrict__ ordered)
 {
     extern __shared__ uint32_t next[];
     const uint32_t *row = rows + (size_t)blockIdx.x * b.total;
@@ -122,7 +122,7 @@ brick_scatter_kernel(Bricks b, const float *__restrict__ u, uint64_t N, const ui
     for (uint64_t n = (uint64_t)blockIdx.x * kSweepBlock + threadIdx.x; n < N; n += (uint64_t)gridDim.x * kSweepBlock) {
         const float x = u[3 * n], y = u[3 * n + 1], z = u[3 * n + 2];
         const uint32_t at = atomicAdd(&next[brick_of(b, x, y, z)], 1u);
-        ordered[at] = make_float4(x, y, z, __uint_as_float((uint32_t)n));
+        ordered[at] = make_float4(x, y, z, __uint_as_float(ids ? ids[n] : (uint32_t)n));
     }
 }
 
@@ -273,7 +273,7 @@ extern "C" size_t dg_order_pieces_words(const dg_order_desc *order, uint64_t N)
     return 2 * (2 + piece_bound(order->total, N));
 }
 
-extern "C" int dg_order_samples(const dg_order_desc *order, const float *u, uint64_t N, void *ordered, uint32_t *pieces,
+extern "C" int dg_order_samples(const dg_order_desc *order, const float *u, const uint32_t *ids, uint64_t N, void *ordered, uint32_t *pieces,
                                 void *ws, size_t ws_bytes, void *stream)
 {
     const char *who = "dg_order_samples";
@@ -304,7 +304,7 @@ extern "C" int dg_order_samples(const dg_order_desc *order, const float *u, uint
     brick_count_kernel<<<kSweepGrid, kSweepBlock, lds, st>>>(b, u, N, rows);
     brick_scan_rows_kernel<<<(b.total + kScanKeys - 1) / kScanKeys, kScanKeys * kScanGroups, 0, st>>>(rows, kSweepGrid, b.total, totals);
     brick_scan_totals_kernel<<<1, 1024, 0, st>>>(totals, b.total, first, (uint2 *)pieces);
-    brick_scatter_kernel<<<kSweepGrid, kSweepBlock, lds, st>>>(b, u, N, rows, first, (float4 *)ordered);
+    brick_scatter_kernel<<<kSweepGrid, kSweepBlock, lds, st>>>(b, u, ids, N, rows, first, (float4 *)ordered);
     brick_sort_kernel<<<(uint32_t)piece_bound(b.total, N), kSortBlock, 0, st>>>(b, (const uint2 *)pieces, (float4 *)ordered);
     return dg::launch_status(who);
 }

@@ -164,8 +164,9 @@ class TrainStep:
         """Order descriptor of a batch of N samples, or None where the plain kernels serve it."""
         return B.dg_order_desc_init(m.grid, N) if self.ordered is not None and N >= self._order_min(m) else None
 
-    def _encode_fwd(self, p, m, order, sl, N):
-        """Features of partition p's samples (their slice of the sample buffers): planes, or rows where they are sorted."""
+    def _encode_fwd(self, p, m, order, sl, N, ids=None):
+        """Features of partition p's samples (their slice of the sample buffers): planes, or rows where they are sorted.
+        ids: the number that stands beside each sorted sample in place of its index; the rows then stay in sorted order."""
         self.layout[p] = (sl.start, N, order)
         if order is not None:
             words = B.dg_order_pieces_words(order, N)
@@ -175,10 +176,10 @@ class TrainStep:
             if self.ws_order is None or self.ws_order.numel() < need:
                 self.ws_order = torch.empty(need, dtype=torch.int32, device=self.dev)
             with self._timed("dg_order_samples"):
-                B.dg_order_samples(order, self.u[sl], N, self.ordered[sl], self.pieces[p], self.ws_order)
+                B.dg_order_samples(order, self.u[sl], N, self.ordered[sl], self.pieces[p], self.ws_order, ids)
         with self._timed("dg_hashgrid_encode_fwd"):
             if order is not None:
-                B.dg_hashgrid_encode_fwd_ordered(m.grid, m.table, self.ordered[sl], N, self._feat[sl])
+                B.dg_hashgrid_encode_fwd_ordered(m.grid, m.table, self.ordered[sl], N, self._feat[sl], by_position=ids is not None)
             else:
                 B.dg_hashgrid_encode_fwd(m.grid, m.table, self.u[sl], N, self._feat[sl])
 
@@ -455,13 +456,21 @@ class TrainStep:
             M = n_cells if warmup else n_cells // 2
             n_uniform = 0 if warmup else M // 2
             piece = self.max_samples
+            density_kernel = (m.mlp.n_feat, m.mlp.n_hidden_d, m.mlp.n_layers_c) == (32, 64, 2)
             for i0 in range(0, M, piece):
                 n = min(piece, M - i0)
                 cell = self.sample_ray[:n]                      # the step's sample buffers serve as scratch
                 with self._timed("dg_occ_candidates"):
                     B.dg_occ_candidates(q.desc, q.bits, n, n_uniform, warmup, self.seed, iteration, tries, cell, self.u[:n], i0=i0)
                 order = None if warmup else self._order_of(m, n)        # during warm-up the candidates come cell after cell anyway
-                self._encode_fwd(p, m, order, slice(0, n), n)
+                self._encode_fwd(p, m, order, slice(0, n), n, None if order is None else cell)
+                if density_kernel:
+                    with self._timed("dg_occ_evaluate"):
+                        if order is None:
+                            B.dg_occ_evaluate(m.mlp, m.weights, self._feat[:n], False, cell, 1, n, q.density)
+                        else:                                   # the cells stand beside the sorted samples
+                            B.dg_occ_evaluate(m.mlp, m.weights, self._feat[:n], True, self.ordered.view(-1)[3:4 * n].view(torch.int32), 4, n, q.density)
+                    continue
                 self.dir_enc[:1].zero_()                        # the density does not depend on the direction: one zero row
                 if self.app_rows is not None:
                     self.app_rows[:1].zero_()

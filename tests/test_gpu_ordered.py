@@ -156,3 +156,39 @@ def test_render_in_spatial_order(monkeypatch):
         assert sorted_.layout[0][2] is not None
         for a, b in zip(got, want):
             assert rel_err(host(a), host(b)) <= TOL_F16
+
+
+@pytest.mark.parametrize("N", [1, 31, 33, 5003])
+def test_density_of_candidates(N):
+    """Density net and maximum in one kernel, planes and sorted rows, against the separate entry points: the same bits."""
+    print("[case] density of candidates", N, flush=True)
+    grid, ref_grid = _grids("cached")
+    mlp = B.dg_mlp_desc(32, 64, 16, 16, 64, 2, 1)
+    rng = np.random.default_rng(41)
+    table = dev(di.make_table(ref_grid.n_entries, 2, 1.0, seed=42))
+    weights = dev((rng.standard_normal(9408) * 0.2).astype(np.float16))
+    n_cells = 700
+    u, cell = dev(_coords(N, "points")), torch.from_numpy(rng.integers(0, n_cells + 50, N).astype(np.int32)).to(DEV)     # some past the grid: left out
+    planes, sigma, rgb = torch.zeros(N, 32, dtype=torch.float16, device=DEV), torch.zeros(N, device=DEV), torch.zeros(N, 3, device=DEV)
+    B.dg_hashgrid_encode_fwd(grid, table, u, N, planes)
+    B.dg_mlp_fwd(mlp, weights, planes, torch.zeros(1, 16, dtype=torch.float16, device=DEV), N, N, sigma, rgb)
+    start = torch.rand(n_cells, device=DEV)
+    want = start.clone()
+    B.dg_occ_update(want, cell, sigma, N)
+    got = start.clone()
+    B.dg_occ_evaluate(mlp, weights, planes, False, cell, 1, N, got)
+    assert torch.equal(got, want)
+    order = B.dg_order_desc_init(grid, N)
+    ordered, rows = torch.zeros(N, 4, device=DEV), torch.zeros(N, 32, dtype=torch.float16, device=DEV)
+    pieces = torch.zeros(B.dg_order_pieces_words(order, N), dtype=torch.int32, device=DEV)
+    ws = torch.zeros(B.dg_order_workspace_bytes(order) // 4, dtype=torch.int32, device=DEV)
+    B.dg_order_samples(order, u, N, ordered, pieces, ws, ids=cell)
+    assert torch.equal(ordered[:, 3].contiguous().view(torch.int32).sort().values, cell.sort().values)
+    B.dg_hashgrid_encode_fwd_ordered(grid, table, ordered, N, rows, by_position=True)
+    got = start.clone()
+    B.dg_occ_evaluate(mlp, weights, rows, True, ordered.view(-1)[3:4 * N].view(torch.int32), 4, N, got)
+    # the two encodes add a cell's corners up in another order, so features differ by fp32 rounding before theirs to fp16
+    assert rel_err(host(got), host(want)) <= TOL_F16
+    small = B.dg_mlp_desc(8, 32, 16, 4, 32, 1, 1)
+    with pytest.raises(B.DistGridError):
+        B.dg_occ_evaluate(small, weights, planes, False, cell, 1, N, got)
