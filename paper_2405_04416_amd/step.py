@@ -157,12 +157,18 @@ class TrainStep:
         if n < least:
             return B.dg_hashgrid_encode_bwd_workspace_bytes(m.grid, n)
         sizes = [max(n * k // 10, least) for k in (10, 9, 8, 7, 6, 5)]
+        orders = [(k, B.dg_order_desc_init(m.grid, k)) for k in sizes]
         return max([B.dg_hashgrid_encode_bwd_workspace_bytes(m.grid, least)] +
-                   [B.dg_hashgrid_encode_bwd_ordered_workspace_bytes(m.grid, B.dg_order_desc_init(m.grid, k), k) for k in sizes])
+                   [B.dg_hashgrid_encode_bwd_ordered_workspace_bytes(m.grid, q, k) if q.n_merged > 0 else B.dg_hashgrid_encode_bwd_workspace_bytes(m.grid, k)
+                    for k, q in orders])
 
     def _order_of(self, m, N):
-        """Order descriptor of a batch of N samples, or None where the plain kernels serve it."""
-        return B.dg_order_desc_init(m.grid, N) if self.ordered is not None and N >= self._order_min(m) else None
+        """Order descriptor of a batch of N samples, or None where the plain kernels serve it (also where not even the two
+        coarsest levels of a grid fit LDS brick by brick)."""
+        if self.ordered is None or N < self._order_min(m):
+            return None
+        order = B.dg_order_desc_init(m.grid, N)
+        return order if order.n_merged > 0 else None
 
     def _encode_fwd(self, p, m, order, sl, N, ids=None):
         """Features of partition p's samples (their slice of the sample buffers): planes, or rows where they are sorted.

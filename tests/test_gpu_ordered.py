@@ -140,6 +140,17 @@ def test_step_in_spatial_order(name, R, overrides, monkeypatch):
     assert all(order is not None for _, _, order in step.layout.values())
 
 
+def test_step_without_mergeable_levels(monkeypatch):
+    """A grid whose coarsest levels do not fit LDS brick by brick: served by the plain kernels, whatever the batch size."""
+    from test_gpu_step import _compare_step
+    print("[case] step without mergeable levels", flush=True)
+    monkeypatch.setattr(TrainStep, "_order_min", lambda self, m: 1)
+    cfg = di.config("c2_ngp")
+    cfg["grid"] = dict(cfg["grid"], n_min=600, n_max=2048, growth=None, log2_T=15)
+    step, _ = _compare_step(cfg, 300, seed=2, lambda1=1e-3, loss_scale=2.0 ** 14, use_jitter_array=False, table_gain=3000.0)
+    assert all(order is None for _, _, order in step.layout.values())
+
+
 def test_render_in_spatial_order(monkeypatch):
     from gpu_util import gpu_models, make_step
     import oracle.step as ostep
