@@ -170,17 +170,22 @@ class TrainStep:
         order = B.dg_order_desc_init(m.grid, N)
         return order if order.n_merged > 0 else None
 
+    def _grown(self, buf, words):
+        """buf if it holds that many words, otherwise a larger one.  The old one may have been allocated on another stream
+        than the current one, which may still use it."""
+        if buf is not None and buf.numel() >= words:
+            return buf
+        if buf is not None:
+            buf.record_stream(torch.cuda.current_stream())
+        return torch.empty(words, dtype=torch.int32, device=self.dev)
+
     def _encode_fwd(self, p, m, order, sl, N, ids=None):
         """Features of partition p's samples (their slice of the sample buffers): planes, or rows where they are sorted.
         ids: the number that stands beside each sorted sample in place of its index; the rows then stay in sorted order."""
         self.layout[p] = (sl.start, N, order)
         if order is not None:
-            words = B.dg_order_pieces_words(order, N)
-            if p not in self.pieces or self.pieces[p].numel() < words:
-                self.pieces[p] = torch.empty(words, dtype=torch.int32, device=self.dev)
-            need = B.dg_order_workspace_bytes(order) // 4
-            if self.ws_order is None or self.ws_order.numel() < need:
-                self.ws_order = torch.empty(need, dtype=torch.int32, device=self.dev)
+            self.pieces[p] = self._grown(self.pieces.get(p), B.dg_order_pieces_words(order, N))
+            self.ws_order = self._grown(self.ws_order, B.dg_order_workspace_bytes(order) // 4)
             with self._timed("dg_order_samples"):
                 B.dg_order_samples(order, self.u[sl], N, self.ordered[sl], self.pieces[p], self.ws_order, ids)
         with self._timed("dg_hashgrid_encode_fwd"):
