@@ -100,6 +100,28 @@ def test_ordered_encode(key, N, flavour):
     assert np.all(have[want == 0] == 0)
 
 
+@pytest.mark.parametrize("key", list(GRIDS))
+def test_ordered_backward_in_batches(key):
+    """A workspace that holds half of the samples: the unmerged levels go through it in batches, the merged ones do not use it."""
+    print("[case] ordered in batches", key, flush=True)
+    grid, ref_grid = _grids(key)
+    N = 20011
+    u = _coords(N, "points")
+    order, ordered, pieces = _sorted(grid, u, N)
+    M = order.n_merged
+    need = B.dg_hashgrid_encode_bwd_ordered_workspace_bytes(grid, order, N // 2 + 512)
+    assert need < B.dg_hashgrid_encode_bwd_ordered_workspace_bytes(grid, order, N)
+    g = (np.random.default_rng(34).standard_normal((N, 32)) * 1e-3).astype(np.float32)
+    mixed = np.concatenate([np.ascontiguousarray(g[:, :2 * M]).ravel(), np.ascontiguousarray(g[:, 2 * M:].reshape(N, 16 - M, 2).transpose(1, 0, 2)).ravel()])
+    gd = dev(mixed)
+    dtable, ws = torch.zeros(ref_grid.n_entries, 2, device=DEV), torch.zeros(need // 4, device=DEV)
+    B.dg_hashgrid_encode_bwd_ordered(grid, order, ordered, pieces, dev(u), gd, gd.abs().max().reshape(1).view(torch.int32), N, dtable, ws)
+    want, have = oracle.encode_bwd(ref_grid, u, g.astype(np.float64)), host(dtable).astype(np.float64)
+    for l in range(16):
+        sl = slice(ref_grid.first[l], ref_grid.first[l + 1])
+        assert rel_err(have[sl], want[sl]) <= TOL_F16, l
+
+
 def test_non_finite_gradient_is_marked():
     """An infinite or NaN gradient (an fp16 delta that overflowed) leaves NaN in the table gradient's merged levels."""
     grid, ref_grid = _grids("cached")
