@@ -33,12 +33,12 @@ LINE_BYTES = 128               # what one L2 miss fetches
 # over the kernels an entry point launches: (fetched, written).  Measured once per workload with the kernels as they
 # stand; the runs, their commands and the calibration are in profiles/<workload>_hbm_traffic.md.
 MEASURED_TRAFFIC_BYTES = {
-    "c5_share": {"dg_hashgrid_encode_fwd": (283.1e9, 4.295e9), "dg_hashgrid_encode_bwd": (71.77e9, 55.86e9), "dg_mlp_fwd": (4.368e9, 1.074e9),
-                 "dg_mlp_bwd": (11.96e9, 10.82e9)},
-    "c4_big": {"dg_hashgrid_encode_fwd": (82.81e9, 1.275e9), "dg_hashgrid_encode_bwd": (19.05e9, 14.98e9), "dg_mlp_fwd": (1.456e9, 0.3168e9),
-               "dg_mlp_bwd": (3.939e9, 3.247e9)},
-    "c2_ngp": {"dg_hashgrid_encode_fwd": (6.503e9, 0.854e9), "dg_hashgrid_encode_bwd": (10.91e9, 6.764e9), "dg_mlp_fwd": (0.8681e9, 0.2135e9),
-               "dg_mlp_bwd": (2.44e9, 2.214e9)},
+    "c5_share": {"dg_hashgrid_encode_fwd": (113.3e9, 4.62e9), "dg_hashgrid_encode_bwd": (45.46e9, 30.94e9), "dg_mlp_fwd": (4.367e9, 1.074e9),
+                 "dg_mlp_bwd": (11.91e9, 10.76e9)},
+    "c4_big": {"dg_hashgrid_encode_fwd": (46.06e9, 1.415e9), "dg_hashgrid_encode_bwd": (12.38e9, 10.19e9), "dg_mlp_fwd": (1.294e9, 0.317e9),
+               "dg_mlp_bwd": (3.531e9, 3.188e9)},
+    "c2_ngp": {"dg_hashgrid_encode_fwd": (8.614e9, 0.895e9), "dg_hashgrid_encode_bwd": (6.292e9, 4.062e9), "dg_mlp_fwd": (0.868e9, 0.214e9),
+               "dg_mlp_bwd": (2.382e9, 2.155e9)},
 }
 
 
