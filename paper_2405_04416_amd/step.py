@@ -206,11 +206,13 @@ class TrainStep:
                 B.dg_mlp_bwd_app(m.mlp, m.weights, self._feat[sl], dir_enc, app, S, N, self.dsigma[sl], self.drgb[sl], self.loss_scale,
                                  self._dfeat[sl], m.dW, self.ws_mlp)
             else:
+                largest = self.pieces[p][1:2]
+                B.dg_clear(largest)         # the networks only ever raise it, and a forward pass may see several backward passes
                 B.dg_mlp_bwd_rows(m.mlp, m.weights, self._feat[sl], dir_enc, app, S, N, self.dsigma[sl], self.drgb[sl], self.loss_scale,
-                                  order.n_merged, self._dfeat[sl], self.pieces[p][1:2], m.dW, self.ws_mlp)
+                                  order.n_merged, self._dfeat[sl], largest, m.dW, self.ws_mlp)
         with self._timed("dg_hashgrid_encode_bwd"):
             if order is not None:
-                B.dg_hashgrid_encode_bwd_ordered(m.grid, order, self.ordered[sl], self.pieces[p], self.u[sl], self._dfeat[sl], self.pieces[p][1:2], N, m.dtable,
+                B.dg_hashgrid_encode_bwd_ordered(m.grid, order, self.ordered[sl], self.pieces[p], self.u[sl], self._dfeat[sl], largest, N, m.dtable,
                                                  self.ws_enc, counted)
             elif counted:
                 B.dg_hashgrid_encode_bwd_counted(m.grid, self.u[sl], self._dfeat[sl], N, m.dtable, self.ws_enc)
