@@ -6,6 +6,7 @@ sub-models -> per sub-model sampling, encode, MLPs, local compositing -> merge -
 merge backward (Eq. 7-8) -> per sub-model compositing / MLP / encode backward.  Every arithmetic
 step happens inside libdistgrid; this file allocates, slices and calls.
 """
+import collections
 import contextlib
 
 import torch
@@ -59,6 +60,9 @@ class Occupancy:
     def __init__(self, desc, density, bits, dt, max_steps):
         self.desc, self.density, self.bits, self.dt, self.max_steps = desc, density, bits, float(dt), int(max_steps)
         self.n_set = torch.zeros(1, dtype=torch.int32, device=density.device)
+
+
+_Rows = collections.namedtuple("_Rows", "start N levels order by_position")     # the first `levels` levels of samples [start, start + N)
 
 
 class TrainStep:
@@ -132,6 +136,9 @@ class TrainStep:
         self.ordered = torch.empty(n, 4, dtype=f32, device=self.dev) if order_any else None
         self.pieces, self.ws_order = {}, None
         self.layout = {}        # partition -> (first sample, samples, order or None) of this step
+        # What lies in the feature buffers as rows instead of planes: partition -> _Rows.  While an entry of _feat_rows
+        # stands, the partition's stretch of `ordered` and its `pieces` are those it was written with.
+        self._feat_rows, self._dfeat_rows = {}, {}
         self.offsets = None
         self.local = {}         # resident partition -> index of its first segment among the resident segments (sample buffers)
         self.t_fixed = None
@@ -182,7 +189,7 @@ class TrainStep:
     def _encode_fwd(self, p, m, order, sl, N, ids=None):
         """Features of partition p's samples (their slice of the sample buffers): planes, or rows where they are sorted.
         ids: the number that stands beside each sorted sample in place of its index; the rows then stay in sorted order."""
-        self.layout[p] = (sl.start, N, order)
+        self._written(self._feat_rows, p, sl.start, N, self.n_feat // 2 if order is not None else 0, order, ids is not None)
         if order is not None:
             self.pieces[p] = self._grown(self.pieces.get(p), B.dg_order_pieces_words(order, N))
             self.ws_order = self._grown(self.ws_order, B.dg_order_workspace_bytes(order) // 4)
@@ -194,13 +201,26 @@ class TrainStep:
             else:
                 B.dg_hashgrid_encode_fwd(m.grid, m.table, self.u[sl], N, self._feat[sl])
 
+    @staticmethod
+    def _written(rows, p, start, N, levels, order=None, by_position=False):
+        """Books of a feature buffer: partition p's samples have been written, `levels` levels of them as rows; what lay
+        there before is gone."""
+        for q in [q for q, r in rows.items() if q == p or (r.start < start + N and start < r.start + r.N)]:
+            del rows[q]
+        if levels:
+            rows[p] = _Rows(start, N, levels, order, by_position)
+
     def _mlp_fwd(self, m, order, sl, dir_enc, app, S, N):
         call = B.dg_mlp_fwd_app if order is None else B.dg_mlp_fwd_rows
         with self._timed("dg_mlp_fwd"):
             call(m.mlp, m.weights, self._feat[sl], dir_enc, app, S, N, self.sigma[sl], self.rgb[sl])
 
     def _mlp_and_encode_bwd(self, p, m, sl, dir_enc, app, S, N, counted):
-        order = self.layout[p][2]
+        # planes also where the features have been read, replaced or overwritten since the forward pass
+        rows = self._feat_rows.get(p)
+        order = rows.order if rows is not None and (rows.start, rows.N, rows.by_position) == (sl.start, N, False) else None
+        counted = counted and order is self.layout[p][2]        # the counts were those of this order
+        self._written(self._dfeat_rows, p, sl.start, N, 0 if order is None else order.n_merged)
         with self._timed("dg_mlp_bwd"):
             if order is None:
                 B.dg_mlp_bwd_app(m.mlp, m.weights, self._feat[sl], dir_enc, app, S, N, self.dsigma[sl], self.drgb[sl], self.loss_scale,
@@ -219,25 +239,52 @@ class TrainStep:
             else:
                 B.dg_hashgrid_encode_bwd(m.grid, self.u[sl], self._dfeat[sl], N, m.dtable, self.ws_enc)
 
-    def _as_planes(self, buf, merged_only):
-        """Copy of a feature buffer with every partition's samples as level-major planes, the layout of the plain kernels."""
-        out = buf.clone()
-        for s0, N, order in self.layout.values():
-            if order is not None:
-                M = order.n_merged if merged_only else self.n_feat // 2
-                rows = buf[s0:s0 + N].reshape(-1)[:2 * M * N].view(N, M, 2)
-                out[s0:s0 + N].view(-1, N, 2)[:M] = rows.transpose(0, 1)
-        return out
+    def _as_planes(self, buf, rows):
+        """buf, with what lies in it as rows turned into level-major planes, the layout of the plain kernels."""
+        for r in rows.values():
+            flat = buf[r.start:r.start + r.N].reshape(-1)[:2 * r.levels * r.N]
+            planes = flat.view(r.N, r.levels, 2)
+            if r.by_position:
+                planes = planes[self._position_of_candidates(r)]
+            flat.copy_(planes.transpose(0, 1).reshape(-1))
+        rows.clear()
+        return buf
 
+    def _position_of_candidates(self, r):
+        """Place in the sorted list of each candidate of the last occupancy refresh.  The list holds cells in place of indices:
+        equal (coordinates, cell) are matched up, and candidates equal in all four have equal features."""
+        def ranked(*columns):
+            at = torch.arange(r.N, device=self.dev)
+            for c in columns:
+                at = at[torch.sort(c[at], stable=True).indices]
+            return at
+        bits = self.ordered[r.start:r.start + r.N].view(torch.int32)
+        u = self.u[r.start:r.start + r.N].view(torch.int32)
+        place = torch.empty(r.N, dtype=torch.int64, device=self.dev)
+        place[ranked(u[:, 0], u[:, 1], u[:, 2], self.sample_ray[:r.N])] = ranked(*bits.unbind(1))
+        return place
+
+    # The buffers themselves, as level-major planes [L, N, 2] per partition.  Large batches are kept as rows (in part, for the
+    # gradient); reading or replacing a buffer ends that, and a backward pass that follows takes the features as they then are.
     @property
     def feat(self):
-        """Features of the last forward pass, per partition as level-major planes [L, N, 2]."""
-        return self._as_planes(self._feat, False)
+        """Features of the last forward pass (or occupancy refresh), per partition as level-major planes [L, N, 2]."""
+        return self._as_planes(self._feat, self._feat_rows)
+
+    @feat.setter
+    def feat(self, buf):
+        self._feat = buf
+        self._feat_rows.clear()
 
     @property
     def dfeat(self):
         """Feature gradient of the last backward pass, per partition as level-major planes [L, N, 2]."""
-        return self._as_planes(self._dfeat, True)
+        return self._as_planes(self._dfeat, self._dfeat_rows)
+
+    @dfeat.setter
+    def dfeat(self, buf):
+        self._dfeat = buf
+        self._dfeat_rows.clear()
 
     @contextlib.contextmanager
     def _timed(self, name):
@@ -369,6 +416,7 @@ class TrainStep:
                 self._count_ahead(p, order, sl, N)
             with self._timed("dg_dir_encode"):
                 B.dg_dir_encode(d, self.seg_ray[b:e], n_seg, self.deg, self.dir_enc[rows])
+            self.layout[p] = (sl.start, N, order)
             self._encode_fwd(p, m, order, sl, N)
             app = self._appearance_rows(self.seg_ray[b:e], n_seg, rows)
             if fused_depth is not None:
@@ -418,6 +466,7 @@ class TrainStep:
                 with self._timed("dg_dir_encode"):
                     B.dg_dir_encode(d, self.sample_ray[sl], N, self.deg, self.dir_enc[sl])
                 order = self._order_of(m, N)
+                self.layout[p] = (s0 - N, N, order)
                 self._encode_fwd(p, m, order, sl, N)
                 app = self._appearance_rows(self.sample_ray[sl], N, sl)
                 self._mlp_fwd(m, order, sl, self.dir_enc[sl], app, 1, N)

@@ -1,12 +1,12 @@
 """What a step keeps between its calls: a second backward pass on one forward pass, the feature buffers as other calls
 leave them, tensors of the caller's own in place of the step's."""
-import numpy as np
 import pytest
 import torch
 
 import dg_inputs as di
 import oracle.step as ostep
-from gpu_util import TOL_F32, dev, gpu_models, have_gpu, make_step, rel_err, host
+from gpu_util import TOL_F16, TOL_F32, dev, gpu_models, gpu_occupancy, have_gpu, host, make_step, rel_err
+from paper_2405_04416_amd import binding as B
 from paper_2405_04416_amd.step import TrainStep
 
 pytestmark = [pytest.mark.gpu, pytest.mark.skipif(not have_gpu(), reason="needs a GPU")]
@@ -58,3 +58,81 @@ def test_backward_with_smaller_seeds(ordered):
     step.loss_scale *= 2.0 ** 30
     step.backward()
     assert rel_err(host(m.dtable), want) <= TOL_F32
+
+
+def test_feature_buffers_after_other_calls(ordered):
+    """Rendering other rays rewrites the features and leaves the feature gradient of the last backward pass alone."""
+    print("[case] feature buffers after a rendering", flush=True)
+    step, m, o, d, target = _step()
+    step.step(o, d, target)
+    n = step.layout[0][1]
+    want = step.dfeat.clone()
+    step.step(o, d, target)                         # the gradient lies in rows again
+    _, _, o2, d2, _ = _step(seed=9)
+    step.render(o2, d2)
+    assert step.layout[0][1] != n
+    assert rel_err(host(step.dfeat[:n]), host(want[:n])) <= 1e-6
+    k = step.layout[0][1]
+    plain = torch.zeros(k, 32, dtype=torch.float16, device=want.device)
+    B.dg_hashgrid_encode_fwd(m.grid, m.table, step.u[:k], k, plain)
+    # the two encodes add a cell's corners up in another order before the rounding to fp16
+    assert rel_err(host(step.feat[:k]), host(plain)) <= 2.0 ** -10
+
+
+def test_feature_buffers_are_live(ordered):
+    """feat and dfeat are the step's own buffers: what a caller writes or puts there between the forward and the backward
+    pass is what the backward pass takes, and both can be replaced."""
+    print("[case] feature buffers are live", flush=True)
+    step, m, o, d, target = _step()
+    step.step(o, d, target)
+    want, want_w = host(m.dtable), host(m.dW)
+    step.forward(o, d, target)
+    n = step.layout[0][1]
+    feat = step.feat
+    step.backward()                                 # read, not changed: the same gradients, by the plain kernels
+    assert rel_err(host(m.dtable), want) <= TOL_F16 and rel_err(host(m.dW), want_w) <= TOL_F16
+    dfeat = step.dfeat
+    assert feat.data_ptr() == step.feat.data_ptr() and dfeat.data_ptr() == step.dfeat.data_ptr()
+    step.forward(o, d, target)
+    step.feat[:n].zero_()
+    step.backward()
+    assert float(m.dW[:64 * 32].abs().max()) == 0.0             # the first layer saw no input
+    mine, mine_g = torch.zeros_like(feat), torch.zeros_like(dfeat)
+    step.feat, step.dfeat = mine, mine_g
+    step.step(o, d, target)
+    assert step.feat is mine and step.dfeat is mine_g
+    assert rel_err(host(m.dtable), want) <= TOL_F32 and float(mine.abs().max()) > 0 and float(mine_g.abs().max()) > 0
+
+
+def _marched(seed=7):
+    cfg = di.config("c7_occ")
+    cfg["table_range"] *= 3000.0
+    cfg["occ"] = dict(cfg["occ"], res=32)
+    o, d = di.make_rays(cfg, seed=seed, R=R)
+    models = gpu_models(cfg, ostep.make_models(cfg, seed=seed))
+    q = gpu_occupancy(cfg, ostep.make_occupancy(cfg, seed=seed))
+    step = make_step(cfg, models, R, loss_scale=2.0 ** 14, seed=seed, occupancy=q, max_samples=1 << 16)
+    return step, models[0], dev(o), dev(d), dev(di.make_targets(R, seed=seed))
+
+
+def test_feature_buffers_after_a_refresh(ordered):
+    """The occupancy refresh uses the feature buffer as scratch, in sorted order; what is read afterwards is in the order of its
+    candidates.  The gradient buffer is not touched, and a backward pass after it runs on planes."""
+    print("[case] feature buffers after a refresh", flush=True)
+    step, m, o, d, target = _marched()
+    step.step(o, d, target)
+    assert step.layout[0][2] is not None
+    n = step.layout[0][1]
+    want = step.dfeat.clone()
+    step.step(o, d, target)
+    assert step.refresh_occupancy(4096)
+    assert rel_err(host(step.dfeat[:n]), host(want[:n])) <= 1e-6
+    k = min(step.max_samples, step.occ[0].desc.n_cells // 2)
+    plain = torch.zeros(k, 32, dtype=torch.float16, device=want.device)
+    B.dg_hashgrid_encode_fwd(m.grid, m.table, step.u[:k], k, plain)
+    assert rel_err(host(step.feat[:k]), host(plain)) <= 2.0 ** -10
+    step.forward(o, d, target)
+    step.refresh_occupancy(4112)                    # scratch now: the gradients that follow mean nothing, but they are of this step
+    step.backward()
+    torch.cuda.synchronize()
+    assert bool(torch.isfinite(m.dW).all())
