@@ -188,7 +188,8 @@ int dg_hashgrid_corner_indices(const dg_grid_desc *desc, const float *u, uint64_
  * memory are neighbours in space (they then share table lines), and the gradients of the coarser
  * levels can be summed on chip, region by region, before they reach memory.  dg_order_samples sorts
  * the samples of one sub-model; the *_ordered calls take the sorted list.  The order is a matter of
- * speed alone, results stay those of the calls above.  Features and their gradient then are
+ * speed alone: results agree with those of the calls above up to fp32 rounding (corners and samples are added up in another
+ * order, which within a cell of the sort also varies from run to run).  Features and their gradient then are
  * SAMPLE-MAJOR ROWS in the samples' original order: feat [N, L, F] fp16 for the *_rows network calls below.
  * ---------------------------------------------------------------------------------- */
 typedef struct dg_order_desc {
@@ -215,9 +216,11 @@ int dg_hashgrid_encode_fwd_ordered(const dg_grid_desc *desc, const float *table,
                                    uint32_t by_position, void *feat, void *stream);
 /* dg_hashgrid_encode_bwd on the sorted list.  dfeat: rows [N, 2 * n_merged] fp32 of the merged levels (16-byte aligned, in
  * the samples' original order), then the planes [L - n_merged, N, 2] of the others -- as dg_mlp_bwd_rows writes it; u [N,3]
- * the samples in their original order.  *largest: device word, the bit pattern of a float that no |dfeat| exceeds.  The
- * merged levels are summed per brick in fixed point, exactly and in quanta of 2^-37 of that magnitude or finer; the others go
- * through the bins as in dg_hashgrid_encode_bwd, with its precision.  Where *largest is infinite or NaN every brick leaves
+ * the samples in their original order.  *largest: device word, the bit pattern of a float that no |dfeat| exceeds.
+ * Merged levels: up to 128 samples of one cell are added up in fp32, what a brick holds of such sums in 64 bits -- in fp64 at the
+ * levels whose tables together have at most 8192 entries, where the bricks' sums are added in fp64 as well, and in fixed point
+ * with quanta of 2^-37 of *largest or finer at the others, with an fp32 add into the table per brick.  The levels that are
+ * not merged go through the bins as in dg_hashgrid_encode_bwd, with its precision.  Where *largest is infinite or NaN every brick leaves
  * NaN in one entry of each merged level.  counted != 0: the queues have been laid out by ..._ordered_count (rules as
  * for dg_hashgrid_encode_bwd_count). */
 size_t dg_hashgrid_encode_bwd_ordered_workspace_bytes(const dg_grid_desc *desc, const dg_order_desc *order, uint64_t N);

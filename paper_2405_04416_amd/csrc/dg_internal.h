@@ -37,6 +37,8 @@ constexpr int kWave = 64;
 int check_grid_desc(const dg_grid_desc *d, const char *who);
 
 // binned backward of the hash-grid encode (encode_bwd_binned.hip)
+// levels whose tables fit LDS together: their gradients are summed in fp64
+uint32_t coarse_levels(const dg_grid_desc *d);
 // from_level 0: all levels; else only levels from_level and up
 size_t encode_bwd_binned_workspace_bytes(const dg_grid_desc *d, uint32_t from_level, uint64_t N);
 int encode_bwd_binned(const char *who, const dg_grid_desc *d, uint32_t from_level, const float *u, const float *dfeat, uint64_t N,
@@ -46,7 +48,7 @@ int encode_bwd_binned_count(const char *who, const dg_grid_desc *d, uint32_t fro
 
 // ordered samples: levels below order->n_merged (encode_ordered.hip)
 int brick_bwd(const char *who, const dg_grid_desc *d, const dg_order_desc *order, const uint32_t *pieces, const void *ordered,
-              const float *dfeat, const uint32_t *largest, uint64_t N, float *dtable, hipStream_t st);
+              const float *dfeat, const uint32_t *largest, uint64_t N, float *dtable, double *wide, hipStream_t st);
 
 // rows: features (and the gradient of levels below n_merged) as sample-major rows instead of planes.
 // matrix-core path of the 32-64-16 / (32 + n_app)-64-64-3 field MLPs (mlp_mfma.hip); n_app = 0, 16 or 48

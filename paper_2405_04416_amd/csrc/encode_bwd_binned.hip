@@ -59,13 +59,13 @@ struct Plan {
 
 // ------------------------------------------------------------------ coarse prefix: accumulate in LDS
 __global__ void __launch_bounds__(kCoarseBlock)
-coarse_kernel(dg_grid_desc g, uint32_t first_level, const float *__restrict__ u, const float2 *__restrict__ dfeat,
+coarse_kernel(dg_grid_desc g, uint32_t from_level, uint32_t first_level, const float *__restrict__ u, const float2 *__restrict__ dfeat,
               uint64_t N, float *__restrict__ dtable)
 {
-    // 2 sums per entry of levels [0, first_level), one plane per feature (an add instruction then spreads over all LDS
+    // 2 sums per entry of levels [from_level, first_level), one plane per feature (an add instruction then spreads over all LDS
     // banks); fp64 LDS atomics run ~7x faster than fp32 ones
     extern __shared__ double tab[];
-    const uint32_t n_entries = g.offset[first_level], n_floats = 2u * n_entries;
+    const uint32_t base = g.offset[from_level], n_entries = g.offset[first_level] - base, n_floats = 2u * n_entries;
     for (uint32_t i = threadIdx.x; i < n_floats; i += kCoarseBlock) tab[i] = 0.0;
     __syncthreads();
     const int lane = threadIdx.x % dg::kWave;
@@ -76,7 +76,7 @@ coarse_kernel(dg_grid_desc g, uint32_t first_level, const float *__restrict__ u,
         const bool live = n < N;
         const uint64_t nn = live ? n : N - 1;
         const float uu[3] = {u[3 * nn], u[3 * nn + 1], u[3 * nn + 2]};
-        for (uint32_t l = 0; l < first_level; ++l) {
+        for (uint32_t l = from_level; l < first_level; ++l) {
             const LevelGeom lv = level_of(g, l);
             uint32_t cell[3], e[8];
             float frac[3], w[8];
@@ -97,7 +97,7 @@ coarse_kernel(dg_grid_desc g, uint32_t first_level, const float *__restrict__ u,
             if (tail) {
 #pragma unroll
                 for (int c = 0; c < 8; ++c) {
-                    const uint32_t slot = lv.offset + e[c];
+                    const uint32_t slot = lv.offset - base + e[c];
                     if (vx[c] != 0.0f) __hip_atomic_fetch_add(&tab[slot], (double)vx[c], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
                     if (vy[c] != 0.0f) __hip_atomic_fetch_add(&tab[n_entries + slot], (double)vy[c], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
                 }
@@ -107,7 +107,7 @@ coarse_kernel(dg_grid_desc g, uint32_t first_level, const float *__restrict__ u,
     __syncthreads();
     for (uint32_t i = threadIdx.x; i < n_floats; i += kCoarseBlock) {
         const float v = (float)tab[(i & 1u) * n_entries + (i >> 1)];
-        if (v != 0.0f) unsafeAtomicAdd(dtable + i, v);
+        if (v != 0.0f) unsafeAtomicAdd(dtable + 2 * (size_t)base + i, v);
     }
 }
 
@@ -809,12 +809,11 @@ accumulate_kernel(dg_grid_desc g, Plan plan, const uint32_t *__restrict__ binbas
     }
 }
 
-// from_level > 0: the caller sums the levels below it (order.hip), there is no coarse prefix
+// from_level > 0: the caller sums the levels below it (brick_bwd); what is left of the coarse prefix is taken here
 Plan make_plan(const dg_grid_desc *d, uint32_t from_level)
 {
     Plan p{};
-    uint32_t l = from_level;
-    while (from_level == 0 && l < d->n_levels && d->offset[l + 1] <= kChunk) ++l;     // coarse prefix: tables that fit LDS together
+    uint32_t l = std::max(from_level, dg::coarse_levels(d));
     p.first_level = l;
     uint32_t key = 0;
     for (; l < d->n_levels; ++l) {
@@ -898,6 +897,13 @@ uint64_t max_batch(const dg_grid_desc *d, const Plan &p)
 }  // namespace dg_encode_binned
 
 namespace dg {
+
+uint32_t coarse_levels(const dg_grid_desc *d)
+{
+    uint32_t l = 0;
+    while (l < d->n_levels && d->offset[l + 1] <= dg_encode_binned::kChunk) ++l;
+    return l;
+}
 
 size_t encode_bwd_binned_workspace_bytes(const dg_grid_desc *d, uint32_t from_level, uint64_t N)
 {
@@ -999,11 +1005,11 @@ int encode_bwd_binned(const char *who, const dg_grid_desc *d, uint32_t from_leve
     if (counted && p.n_keys && q.L.batch < N)
         return fail(DG_ERR_WORKSPACE, "%s: the workspace holds %llu of %llu samples: no counts from dg_hashgrid_encode_bwd_count can be in it",
                     who, (unsigned long long)q.L.batch, (unsigned long long)N);
-    if (from_level == 0 && p.first_level > 0) {
+    if (p.first_level > from_level) {
         const uint64_t tiles = (N + kCoarseBlock - 1) / kCoarseBlock;
         const uint32_t grid = (uint32_t)(tiles < kCoarseGrid ? tiles : kCoarseGrid);
-        coarse_kernel<<<grid, kCoarseBlock, 2 * d->offset[p.first_level] * sizeof(double), st>>>(
-            *d, p.first_level, u, (const float2 *)dfeat, N, dtable);
+        coarse_kernel<<<grid, kCoarseBlock, 2 * (d->offset[p.first_level] - d->offset[from_level]) * sizeof(double), st>>>(
+            *d, from_level, p.first_level, u, (const float2 *)dfeat, N, dtable);
     }
     if (p.n_keys == 0) return launch_status(who);
     const uint64_t batch = q.L.batch;

@@ -2,6 +2,7 @@
 // of the coarser levels.
 #include "encode_common.h"
 #include "order_common.h"
+#include <algorithm>
 #include <mutex>
 
 namespace {
@@ -74,8 +75,14 @@ encode_fwd_ordered_kernel(dg_grid_desc g, const float2 *__restrict__ table, cons
 }
 
 // Table gradient of levels [0, n_merged): a workgroup takes a piece of a brick and sums all its contributions in LDS -- the
-// brick's vertices at those levels, 64-bit fixed point, one plane per feature -- then adds the sums to the table gradient, one
+// brick's vertices at those levels, in 64 bits, one plane per feature -- then adds the sums to the table gradient, one
 // global add per vertex the brick touches.
+// Levels [0, n_wide) -- the coarse levels, which ray order sums in fp64 from end to end -- are summed in fp64, here and over the
+// bricks (a vertex of the coarsest level gets hundreds of them): into `wide`, which fold_wide_kernel adds to the table.
+// The other levels, which in ray order pass through records of 27-bit values, are summed in fixed point and reach the table
+// with an fp32 add per brick.  Against 64-bit sums (33.5 M samples, 25200 bricks, 2-norm of level 0): ray order 2.3e-7, this
+// 2.4e-8; in fixed point with fp32 adds 2.6e-7 (13.3 M samples), and nothing was left of gradients below 2^-38 of the largest.
+// The fp64 adds cost 1 to 2 % of a step (13.3 M samples, T = 2^19: 7.48 -> 7.60 ms).
 // A value v becomes round(v * 2^k): the add of 1.5 * 2^52 in fp64 leaves it in the low mantissa bits, in two's complement.  k is
 // such that the magnitudes of a piece (at most 2^12 samples) sum to less than 2^50; adding the doubles' bit patterns as
 // integers adds those low bits, what happens above bit 50 is dropped when the sum is read.  (Integer adds are the fastest LDS
@@ -86,7 +93,7 @@ encode_fwd_ordered_kernel(dg_grid_desc g, const float2 *__restrict__ table, cons
 // sample) take 1.0, the LDS adds 0.6, the sums themselves 1.2; the same levels through the coarse prefix and the bins took
 // 8 ms.  13.3 M samples, T = 2^19, levels 0..11: 1.55 ms.  Two workgroups per compute unit (512 threads, at most 80 KB of sums) and two
 // samples per lane beat four samples per lane (4.3 ms) and one workgroup of 1024 (4.3 ms).
-struct Boxes { uint32_t n_merged, dim[kMaxMerged][3], first[kMaxMerged + 1]; };
+struct Boxes { uint32_t n_merged, n_wide, dim[kMaxMerged][3], first[kMaxMerged + 1]; };
 
 constexpr int kBrickBlock = 512, kRun = 2;
 
@@ -112,26 +119,37 @@ struct LevelLane {
     uint32_t first, last_slot;               // first vertex of the box among the sums; last slot whose eight corners lie in it
 };
 
-// the eight corner sums of the cell whose corner 0 is vertex d of the box
 __device__ __forceinline__ void add_fixed(unsigned long long *slot, float v, double to_fixed)
 {
     __hip_atomic_fetch_add(slot, (unsigned long long)__double_as_longlong(__builtin_fma((double)v, to_fixed, 6755399441055744.0)), __ATOMIC_RELAXED,
                            __HIP_MEMORY_SCOPE_WORKGROUP);
 }
 
-__device__ __forceinline__ void add_to_box(unsigned long long *d, double to_fixed, uint32_t nx, uint32_t nxy, uint32_t plane, const float (&vx)[8], const float (&vy)[8])
+__device__ __forceinline__ void add_wide(unsigned long long *slot, float v)
+{
+    __hip_atomic_fetch_add(reinterpret_cast<double *>(slot), (double)v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+}
+
+// the eight corner sums of the cell whose corner 0 is vertex d of the box; `wide` is the same for all lanes
+__device__ __forceinline__ void add_to_box(unsigned long long *d, bool wide, double to_fixed, uint32_t nx, uint32_t nxy, uint32_t plane, const float (&vx)[8],
+                                           const float (&vy)[8])
 {
 #pragma unroll
     for (int c = 0; c < 8; ++c) {
         unsigned long long *e = d + (c & 1) + ((c >> 1) & 1) * nx + (c >> 2) * nxy;
-        add_fixed(e, vx[c], to_fixed);
-        add_fixed(e + plane, vy[c], to_fixed);
+        if (wide) {
+            add_wide(e, vx[c]);
+            add_wide(e + plane, vy[c]);
+        } else {
+            add_fixed(e, vx[c], to_fixed);
+            add_fixed(e + plane, vy[c], to_fixed);
+        }
     }
 }
 
 __global__ void __launch_bounds__(kBrickBlock)
 brick_bwd_kernel(dg_grid_desc g, Bricks b, Boxes boxes, const uint2 *__restrict__ pieces, const float4 *__restrict__ ordered,
-                 const float4 *__restrict__ dfeat, const uint32_t *__restrict__ largest, float *__restrict__ dtable)
+                 const float4 *__restrict__ dfeat, const uint32_t *__restrict__ largest, float *__restrict__ dtable, double *__restrict__ wide_table)
 {
     extern __shared__ unsigned long long sums[];
     if (blockIdx.x >= pieces[0].x) return;
@@ -200,6 +218,7 @@ brick_bwd_kernel(dg_grid_desc g, Bricks b, Boxes boxes, const uint2 *__restrict_
 #pragma unroll
             for (int which = 0; which < 2; ++which) {
                 const uint32_t l = 2 * q + which;
+                const bool wide = l < boxes.n_wide;
                 float scale[3], last[3];
 #pragma unroll
                 for (int a = 0; a < 3; ++a) { scale[a] = lane_value(mine.scale[a], l); last[a] = lane_value(mine.last[a], l); }
@@ -221,7 +240,7 @@ brick_bwd_kernel(dg_grid_desc g, Bricks b, Boxes boxes, const uint2 *__restrict_
                         // whole numbers below 2^24: exact in fp32
                         const uint32_t now = min((uint32_t)__builtin_fmaf(cell[2], fnxy, __builtin_fmaf(cell[1], fnx, cell[0] - origin)), last_slot);
                         if (k > 0 && now != slot) {
-                            add_to_box(box + slot, to_fixed, nx, nxy, n_vertices, vx, vy);
+                            add_to_box(box + slot, wide, to_fixed, nx, nxy, n_vertices, vx, vy);
 #pragma unroll
                             for (int c = 0; c < 8; ++c) { vx[c] = 0.0f; vy[c] = 0.0f; }
                         }
@@ -240,7 +259,7 @@ brick_bwd_kernel(dg_grid_desc g, Bricks b, Boxes boxes, const uint2 *__restrict_
                 const unsigned long long heads = __ballot(head);
                 if (__popcll(heads) < dg::kWave) segmented_sum(vx, vy, head, heads);
                 const bool tail = lane == dg::kWave - 1 || ((heads >> ((lane + 1) & 63)) & 1ull);
-                if (tail) add_to_box(box + slot, to_fixed, nx, nxy, n_vertices, vx, vy);
+                if (tail) add_to_box(box + slot, wide, to_fixed, nx, nxy, n_vertices, vx, vy);
             }
 #pragma unroll
             for (int k = 0; k < kRun; ++k)
@@ -259,20 +278,42 @@ brick_bwd_kernel(dg_grid_desc g, Bricks b, Boxes boxes, const uint2 *__restrict_
         // neighbouring lanes add the two features of neighbouring vertices: whole cache lines per instruction
         for (uint32_t i = threadIdx.x; i < 2 * count; i += kBrickBlock) {
             const uint32_t v = i >> 1, f = i & 1u;
-            const long long bits = (long long)(sums[f * n_vertices + boxes.first[l] + v] << 13) >> 13;
-            const float sum = (float)((double)bits * from_fixed);
-            if (sum != 0.0f) unsafeAtomicAdd(dst + 2 * (size_t)vertex_entry(lv, mask, low[0] + v % nx, low[1] + v / nx % ny, low[2] + v / (nx * ny)) + f, sum);
+            const unsigned long long held = sums[f * n_vertices + boxes.first[l] + v];
+            const size_t at = 2 * (size_t)vertex_entry(lv, mask, low[0] + v % nx, low[1] + v / nx % ny, low[2] + v / (nx * ny)) + f;
+            if (l < boxes.n_wide) {
+                const double sum = __longlong_as_double((long long)held);
+                if (sum != 0.0) unsafeAtomicAdd(wide_table + 2 * (size_t)lv.offset + at, sum);
+            } else {
+                const float sum = (float)((double)((long long)(held << 13) >> 13) * from_fixed);
+                if (sum != 0.0f) unsafeAtomicAdd(dst + at, sum);
+            }
         }
     }
+}
+
+__global__ void __launch_bounds__(kBlock)
+fold_wide_kernel(const double *__restrict__ wide_table, uint32_t n, float *__restrict__ dtable)
+{
+    const uint32_t i = blockIdx.x * kBlock + threadIdx.x;
+    if (i >= n) return;
+    const float v = (float)wide_table[i];
+    if (v != 0.0f) dtable[i] += v;
+}
+
+// bytes of the fp64 sums of the coarse levels among the merged ones
+size_t wide_bytes(const dg_grid_desc *d, const dg_order_desc *order)
+{
+    const uint32_t n_wide = std::min(dg::coarse_levels(d), order->n_merged);
+    return (2 * (size_t)d->offset[n_wide] * sizeof(double) + 255) / 256 * 256;
 }
 
 }  // namespace
 
 namespace dg {
 
-// the merged levels of the ordered backward pass (N samples; dfeat rows of 2 * n_merged floats)
+// the merged levels of the ordered backward pass (N samples; dfeat rows of 2 * n_merged floats; wide: wide_bytes of scratch)
 int brick_bwd(const char *who, const dg_grid_desc *d, const dg_order_desc *order, const uint32_t *pieces, const void *ordered, const float *dfeat,
-              const uint32_t *largest, uint64_t N, float *dtable, hipStream_t st)
+              const uint32_t *largest, uint64_t N, float *dtable, double *wide, hipStream_t st)
 {
     static std::once_flag lds_once;
     static hipError_t lds_status = hipSuccess;
@@ -283,13 +324,17 @@ int brick_bwd(const char *who, const dg_grid_desc *d, const dg_order_desc *order
     if (lds_status != hipSuccess) return fail(DG_ERR_HIP, "%s: cannot reserve LDS: %s", who, hipGetErrorString(lds_status));
     Boxes boxes{};
     boxes.n_merged = order->n_merged;
+    boxes.n_wide = std::min(coarse_levels(d), order->n_merged);
     for (uint32_t l = 0; l < order->n_merged; ++l) {
         for (int a = 0; a < 3; ++a) boxes.dim[l][a] = order->box[l][a];
         boxes.first[l + 1] = order->box_first[l + 1];
     }
     const size_t lds = (size_t)boxes.first[boxes.n_merged] * 2 * sizeof(double);
+    const uint32_t n_wide_sums = 2 * d->offset[boxes.n_wide];
+    if (int rc = dg_clear(wide, n_wide_sums * sizeof(double), st)) return rc;
     brick_bwd_kernel<<<(uint32_t)piece_bound(order->total, N), kBrickBlock, lds, st>>>(
-        *d, bricks_of(order), boxes, (const uint2 *)pieces, (const float4 *)ordered, (const float4 *)dfeat, largest, dtable);
+        *d, bricks_of(order), boxes, (const uint2 *)pieces, (const float4 *)ordered, (const float4 *)dfeat, largest, dtable, wide);
+    if (n_wide_sums) fold_wide_kernel<<<(n_wide_sums + kBlock - 1) / kBlock, kBlock, 0, st>>>(wide, n_wide_sums, dtable);
     return launch_status(who);
 }
 
@@ -331,9 +376,11 @@ int bwd_ordered(const char *who, const dg_grid_desc *desc, const dg_order_desc *
     DG_REQUIRE(ordered && pieces && u && dfeat && largest && dtable && ws, DG_ERR_ARG, "%s: null pointer", who);
     DG_REQUIRE(dg::aligned(ordered, 16) && dg::aligned(pieces, 8) && dg::aligned(dfeat, 16) && dg::aligned(dtable, 8) && dg::aligned(ws, 256), DG_ERR_ARG,
                "%s: misaligned pointer", who);
+    const size_t wide = wide_bytes(desc, order);
+    DG_REQUIRE(ws_bytes >= wide, DG_ERR_WORKSPACE, "%s: workspace %zu bytes cannot hold the %zu of the coarse levels", who, ws_bytes, wide);
     // the rows of the merged levels take the place of those levels' planes: plane l of the others lies where it always does
-    if (int rc = dg::brick_bwd(who, desc, order, pieces, ordered, dfeat, largest, N, dtable, (hipStream_t)stream)) return rc;
-    return dg::encode_bwd_binned(who, desc, order->n_merged, u, dfeat, N, dtable, ws, ws_bytes, counted, (hipStream_t)stream);
+    if (int rc = dg::brick_bwd(who, desc, order, pieces, ordered, dfeat, largest, N, dtable, (double *)ws, (hipStream_t)stream)) return rc;
+    return dg::encode_bwd_binned(who, desc, order->n_merged, u, dfeat, N, dtable, (char *)ws + wide, ws_bytes - wide, counted, (hipStream_t)stream);
 }
 
 }  // namespace
@@ -341,7 +388,7 @@ int bwd_ordered(const char *who, const dg_grid_desc *desc, const dg_order_desc *
 extern "C" size_t dg_hashgrid_encode_bwd_ordered_workspace_bytes(const dg_grid_desc *desc, const dg_order_desc *order, uint64_t N)
 {
     if (ordered_ok("dg_hashgrid_encode_bwd_ordered_workspace_bytes", desc, order)) return 0;
-    return dg::encode_bwd_binned_workspace_bytes(desc, order->n_merged, N);
+    return wide_bytes(desc, order) + dg::encode_bwd_binned_workspace_bytes(desc, order->n_merged, N);
 }
 
 extern "C" int dg_hashgrid_encode_bwd_ordered_count(const dg_grid_desc *desc, const dg_order_desc *order, const float *u, uint64_t N, void *ws,
@@ -352,7 +399,9 @@ extern "C" int dg_hashgrid_encode_bwd_ordered_count(const dg_grid_desc *desc, co
     if (N == 0) return DG_OK;
     DG_REQUIRE(u && ws, DG_ERR_ARG, "%s: null pointer", who);
     DG_REQUIRE(dg::aligned(ws, 256), DG_ERR_ARG, "%s: workspace must be 256-byte aligned", who);
-    return dg::encode_bwd_binned_count(who, desc, order->n_merged, u, N, ws, ws_bytes, (hipStream_t)stream);
+    const size_t wide = wide_bytes(desc, order);
+    DG_REQUIRE(ws_bytes >= wide, DG_ERR_WORKSPACE, "%s: workspace %zu bytes cannot hold the %zu of the coarse levels", who, ws_bytes, wide);
+    return dg::encode_bwd_binned_count(who, desc, order->n_merged, u, N, (char *)ws + wide, ws_bytes - wide, (hipStream_t)stream);
 }
 
 extern "C" int dg_hashgrid_encode_bwd_ordered(const dg_grid_desc *desc, const dg_order_desc *order, const void *ordered, const uint32_t *pieces,

@@ -44,6 +44,11 @@ def _sorted(grid, u, N):
     return order, ordered, pieces
 
 
+def _mixed(g, M):
+    """Gradient [N, 32] as the ordered backward pass reads it: rows of the first M levels, then planes."""
+    return np.concatenate([np.ascontiguousarray(g[:, :2 * M]).ravel(), np.ascontiguousarray(g[:, 2 * M:].reshape(len(g), 16 - M, 2).transpose(1, 0, 2)).ravel()])
+
+
 @pytest.mark.parametrize("flavour", FLAVOURS)
 @pytest.mark.parametrize("N", SIZES)
 @pytest.mark.parametrize("key", list(GRIDS))
@@ -120,6 +125,34 @@ def test_ordered_backward_in_batches(key):
     for l in range(16):
         sl = slice(ref_grid.first[l], ref_grid.first[l + 1])
         assert rel_err(have[sl], want[sl]) <= TOL_F16, l
+
+
+@pytest.mark.parametrize("N", [1025, 20011])
+@pytest.mark.parametrize("key", list(GRIDS))
+def test_small_gradients_beside_a_large_one(key, N):
+    """Levels whose tables together have at most 8192 entries are summed in floating point from end to end: gradients 2^-44
+    times as large as the largest keep their fp32 precision there."""
+    print("[case] small gradients", key, N, flush=True)
+    grid, ref_grid = _grids(key)
+    u = np.minimum(_coords(N, "points"), np.float32(0.7))
+    u[0] = 0.999                                     # the large one has its cells for itself
+    g = (np.random.default_rng(35).standard_normal((N, 32)) * 2.0 ** -44).astype(np.float32)
+    g[0] = 1.0
+    order, ordered, pieces = _sorted(grid, u, N)
+    M = order.n_merged
+    gd = dev(_mixed(g, M))
+    dtable = torch.zeros(ref_grid.n_entries, 2, device=DEV)
+    ws = torch.zeros(B.dg_hashgrid_encode_bwd_ordered_workspace_bytes(grid, order, N) // 4 + 64, device=DEV)
+    B.dg_hashgrid_encode_bwd_ordered(grid, order, ordered, pieces, dev(u), gd, gd.abs().max().reshape(1).view(torch.int32), N, dtable, ws)
+    want = oracle.encode_bwd(ref_grid, u, g.astype(np.float64))
+    scale = oracle.encode_bwd(ref_grid, u, np.abs(g).astype(np.float64))
+    have = host(dtable).astype(np.float64)
+    coarse = [l for l in range(16) if ref_grid.first[l + 1] <= 8192]
+    assert len(coarse) >= 2
+    for l in coarse:
+        sl = slice(ref_grid.first[l], ref_grid.first[l + 1])
+        # a contribution is four fp32 roundings deep and goes through at most seven adds in a run; then fp64, rounded once
+        assert np.all(np.abs(have[sl] - want[sl]) <= 12 * 2.0 ** -24 * scale[sl]), l
 
 
 def test_non_finite_gradient_is_marked():
