@@ -79,6 +79,8 @@ __device__ __forceinline__ float fast_sigmoid(float x)
 {
     return __builtin_amdgcn_rcpf(1.0f + __builtin_amdgcn_exp2f(-1.4426950408889634f * x));
 }
+// the same with the library's exponential and a rounded division
+__device__ __forceinline__ float full_sigmoid(float x) { return 1.0f / (1.0f + expf(-x)); }
 __device__ __forceinline__ float clip15(float x) { return fminf(fmaxf(x, -15.0f), 15.0f); }
 
 // max(x, 0) on four pairs of halves, one instruction per pair
@@ -92,7 +94,7 @@ __device__ __forceinline__ h8 relu_pairs(h8 x)
 }
 
 // registers 8p .. 8p+7 of a result tile, activated, rounded to fp16 and packed: k-step (m, p) of the next operand
-template <int ACT>   // 0 identity, 1 ReLU, 2 sigmoid
+template <int ACT>   // 0 identity, 1 ReLU, 2 sigmoid, 3 sigmoid at full fp32 precision
 __device__ __forceinline__ h8 pack_half(const f16v &c, int p)
 {
     h8 out;
@@ -100,6 +102,7 @@ __device__ __forceinline__ h8 pack_half(const f16v &c, int p)
     for (int j = 0; j < 8; ++j) {
         float v = c[8 * p + j];
         if (ACT == 2) v = fast_sigmoid(v);
+        if (ACT == 3) v = full_sigmoid(v);
         out[j] = (_Float16)v;
     }
     // ReLU after the rounding gives the same values as before it (rounding is monotone and keeps 0) and works on pairs

@@ -68,11 +68,11 @@ __device__ __forceinline__ void small_forward(const __half *lds, int lane, uint3
     acc = mma(image(lds, iC1, lane), t.xc[0], zero16());
     acc = mma(image(lds, iC1 + 1, lane), t.xc[1], acc);
 #pragma unroll
-    for (int ks = 0; ks < 2; ++ks) t.c1[ks] = act_c ? pack_half<2>(acc, ks) : pack_half<1>(acc, ks);
+    for (int ks = 0; ks < 2; ++ks) t.c1[ks] = act_c ? pack_half<3>(acc, ks) : pack_half<1>(acc, ks);
     f16v out = mma(image(lds, iC3, lane), t.c1[0], zero16());
     out = mma(image(lds, iC3 + 1, lane), t.c1[1], out);
 #pragma unroll
-    for (int c = 0; c < 3; ++c) { t.raw[c] = out[c]; t.rgb[c] = 1.0f / (1.0f + expf(-clip15(out[c]))); }
+    for (int c = 0; c < 3; ++c) { t.raw[c] = out[c]; t.rgb[c] = full_sigmoid(clip15(out[c])); }
 }
 
 __global__ void __launch_bounds__(kBlock)

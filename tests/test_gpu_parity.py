@@ -476,6 +476,35 @@ def test_mlp_bwd_several_tiles_per_wavefront():
         pos += no * ni
 
 
+def test_small_net_sigmoid_precision():
+    """The hidden sigmoid of the 8-32-16 / 20-32-3 networks is an fp32 one before its rounding to fp16: it falls to the wrong side
+    of a rounding boundary no more often than torch's fp32 sigmoid.  Weights that bring chosen pre-activations to three hidden
+    units and make each the exponent of a colour, from which its fp16 value is read back."""
+    say("small net, hidden sigmoid against 64 bits")
+    n = 200000
+    rng = np.random.default_rng(51)
+    d = np.empty((n, 4), np.float16)
+    d[:, 0] = rng.uniform(-6.5, -2.0, n)
+    d[:, 1:] = rng.integers(-1024, 1025, (n, 3)) / 1024.0
+    Wc1, Wc3 = np.zeros((32, 20), np.float16), np.zeros((3, 32), np.float16)
+    for k in range(3):
+        Wc1[k, 16], Wc1[k, 17 + k], Wc3[k, k] = 1.0, 2.0 ** -9, 64.0
+    w = np.concatenate([np.zeros(32 * 8 + 16 * 32, np.float16), Wc1.ravel(), Wc3.ravel()])
+    x = d[:, :1].astype(np.float64) + 2.0 ** -9 * d[:, 1:].astype(np.float64)              # exact in fp32 as well
+    assert np.array_equal(x.astype(np.float32).astype(np.float64), x)
+    mdesc = gpu_mlp(di.config("c1_tiny"))
+    sigma, rgb = torch.zeros(n, device=DEV), torch.zeros(n, 3, device=DEV)
+    B.dg_mlp_fwd(mdesc, dev(w), torch.zeros(n, 8, dtype=torch.float16, device=DEV), dev(d), 1, n, sigma, rgb)
+    r = host(rgb).astype(np.float64)
+    hidden = (np.log(r / (1.0 - r)) / 64.0).astype(np.float16)          # within 2e-6 of a value whose neighbours are 1e-6 (at 1e-3) to 6e-5 away
+    exact = (1.0 / (1.0 + np.exp(-x))).astype(np.float16)
+    fp32 = host(torch.sigmoid(dev(x.astype(np.float32)))).astype(np.float16)
+    wrong, wrong_fp32 = int(np.sum(hidden != exact)), int(np.sum(fp32 != exact))
+    say("wrong side: %d of %d here, %d by torch" % (wrong, exact.size, wrong_fp32))
+    # two fp32 sigmoids may differ in the last bits: counts of the same size (a third more, and three standard deviations of it)
+    assert wrong <= wrong_fp32 * 4 / 3 + 3.0 * (wrong_fp32 * 4 / 3) ** 0.5
+
+
 @pytest.mark.parametrize("S,n_seg,n_app", [(64, 1201, 0), (48, 700, 0), (20, 333, 0), (1, 50, 0), (33, 257, 48)])
 def test_mlp_composite_fused_forward(S, n_seg, n_app):
     """Evaluation rendering (Sec. 4.4.2) with networks and local rendering in one kernel: partial colour, transmittance
