@@ -158,16 +158,35 @@ class TrainStep:
         return 1 << 21 if self.occ is None else 1 << 20
 
     def _encode_ws_bytes(self, m, n):
-        """Workspace of the table-gradient pass for up to n samples.  In spatial order it holds the unmerged levels only;
-        how many levels are merged falls with the number of samples, so smaller batches are looked at too."""
+        """Workspace of the table-gradient pass for up to n samples.  In spatial order it holds the unmerged levels only, and
+        what it needs grows with the number of samples while the merged levels stay the same and falls where there are more of
+        them: besides n, the last size before every such place counts."""
         least = self._order_min(m)
         if n < least:
             return B.dg_hashgrid_encode_bwd_workspace_bytes(m.grid, n)
-        sizes = [max(n * k // 10, least) for k in (10, 9, 8, 7, 6, 5)]
-        orders = [(k, B.dg_order_desc_init(m.grid, k)) for k in sizes]
-        return max([B.dg_hashgrid_encode_bwd_workspace_bytes(m.grid, least)] +
-                   [B.dg_hashgrid_encode_bwd_ordered_workspace_bytes(m.grid, q, k) if q.n_merged > 0 else B.dg_hashgrid_encode_bwd_workspace_bytes(m.grid, k)
-                    for k, q in orders])
+        orders = {}
+
+        def order(k):
+            if k not in orders:
+                orders[k] = B.dg_order_desc_init(m.grid, k)
+            return orders[k]
+
+        def need(k):
+            q = order(k)
+            return B.dg_hashgrid_encode_bwd_ordered_workspace_bytes(m.grid, q, k) if q.n_merged > 0 else B.dg_hashgrid_encode_bwd_workspace_bytes(m.grid, k)
+
+        def last_before_changes(a, b):
+            if order(a).n_merged == order(b).n_merged:
+                return []
+            if b - a == 1:
+                return [a]
+            mid = (a + b) // 2
+            return last_before_changes(a, mid) + last_before_changes(mid, b)
+
+        # a grid of sizes first: a flat box's bricks do not grow evenly
+        sizes = sorted({least, n} | {int(least * (n / least) ** (i / 32)) for i in range(1, 32)})
+        ends = [k for a, b in zip(sizes, sizes[1:]) for k in last_before_changes(a, b)]
+        return max(B.dg_hashgrid_encode_bwd_workspace_bytes(m.grid, least), *(need(k) for k in ends + [n]))
 
     def _order_of(self, m, N):
         """Order descriptor of a batch of N samples, or None where the plain kernels serve it (also where not even the two
