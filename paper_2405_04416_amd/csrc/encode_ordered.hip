@@ -364,8 +364,7 @@ int ordered_ok(const char *who, const dg_grid_desc *desc, const dg_order_desc *o
     if (int rc = order_ok(order, who)) return rc;
     DG_REQUIRE(desc->n_levels == 16 && order->n_merged <= kMaxMerged && order->n_merged % 2 == 0 && order->n_merged > 0, DG_ERR_UNSUPPORTED,
                "%s: needs 16 levels and at least two merged ones", who);
-    DG_REQUIRE(order->box_first[order->n_merged] <= kMaxBoxVertices, DG_ERR_ARG, "%s: descriptor not initialised by dg_order_desc_init", who);
-    return DG_OK;
+    return order_fits(order, desc, who);
 }
 
 int bwd_ordered(const char *who, const dg_grid_desc *desc, const dg_order_desc *order, const void *ordered, const uint32_t *pieces, const float *u,

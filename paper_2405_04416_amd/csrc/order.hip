@@ -185,6 +185,16 @@ namespace {
 
 inline size_t align256(size_t x) { return (x + 255) / 256 * 256; }
 
+// Vertices of a brick at one level, along one axis.  A brick of width w voxels meets at most floor(w) + 2 voxels, floor(w) + 3
+// vertices (2e-2: room for the slack and the fp32 rounding of the edges).
+uint32_t box_vertices(const dg_grid_desc *desc, uint32_t l, int a, uint32_t n_bricks)
+{
+    const uint32_t box = (uint32_t)std::floor((double)desc->scale[l][a] / n_bricks + 2e-2) + 3u;
+    return box < desc->res[l][a] + 1u ? box : desc->res[l][a] + 1u;
+}
+
+double finest_scale(const dg_grid_desc *desc, uint32_t l) { return std::fmax(desc->scale[l][0], std::fmax(desc->scale[l][1], desc->scale[l][2])); }
+
 // bricks of about per_brick samples, and the levels that such a brick has in LDS together
 void cut_bricks(dg_order_desc *order, const dg_grid_desc *desc, uint64_t N, uint32_t per_brick)
 {
@@ -208,20 +218,16 @@ void cut_bricks(dg_order_desc *order, const dg_grid_desc *desc, uint64_t N, uint
     }
     order->total = (uint32_t)total;
     for (int a = 0; a < 3; ++a) order->per_unit[a] = (float)order->n_bricks[a];
-    // Levels summed brick by brick in the backward pass: as many as have their brick's vertices in LDS together.  A brick
-    // of width w voxels meets at most floor(w) + 2 voxels, floor(w) + 3 vertices (2e-2: room for the slack and the fp32
-    // rounding of the edges).
+    // levels summed brick by brick in the backward pass: as many as have their brick's vertices in LDS together
     uint32_t at = 0, l = 0;
     for (; l < kMaxMerged; ++l) {
         uint64_t vertices = 1;
         uint32_t box[3];
         for (int a = 0; a < 3; ++a) {
-            box[a] = (uint32_t)std::floor((double)desc->scale[l][a] / order->n_bricks[a] + 2e-2) + 3u;
-            if (box[a] > desc->res[l][a] + 1u) box[a] = desc->res[l][a] + 1u;
+            box[a] = box_vertices(desc, l, a, order->n_bricks[a]);
             vertices *= box[a];
         }
-        const double finest = std::fmax(desc->scale[l][0], std::fmax(desc->scale[l][1], desc->scale[l][2]));
-        if (at + vertices > kMaxBoxVertices || finest > kMaxMergedScale) break;
+        if (at + vertices > kMaxBoxVertices || finest_scale(desc, l) > kMaxMergedScale) break;
         for (int a = 0; a < 3; ++a) order->box[l][a] = box[a];
         order->box_first[l] = at;
         at += (uint32_t)vertices;
@@ -239,6 +245,23 @@ int order_ok(const dg_order_desc *o, const char *who)
     DG_REQUIRE(o->n_bricks[0] && o->n_bricks[1] && o->n_bricks[2] && o->total <= kMaxBricks &&
                    (uint64_t)o->n_bricks[0] * o->n_bricks[1] * o->n_bricks[2] == o->total,
                DG_ERR_ARG, "%s: descriptor not initialised by dg_order_desc_init", who);
+    return DG_OK;
+}
+
+// the boxes are those of this grid: with another grid's the brick sums would land outside the levels
+int order_fits(const dg_order_desc *o, const dg_grid_desc *d, const char *who)
+{
+    bool fits = o->n_merged <= kMaxMerged && o->n_merged <= d->n_levels && o->box_first[0] == 0;
+    for (int a = 0; a < 3; ++a) fits = fits && o->per_unit[a] == (float)o->n_bricks[a];
+    for (uint32_t l = 0; fits && l < o->n_merged; ++l) {
+        uint64_t vertices = 1;
+        for (int a = 0; a < 3; ++a) {
+            fits = fits && o->box[l][a] == box_vertices(d, l, a, o->n_bricks[a]);
+            vertices *= o->box[l][a];
+        }
+        fits = fits && o->box_first[l] + vertices == o->box_first[l + 1] && o->box_first[l + 1] <= kMaxBoxVertices && finest_scale(d, l) <= kMaxMergedScale;
+    }
+    DG_REQUIRE(fits, DG_ERR_ARG, "%s: the order descriptor was made for another grid", who);
     return DG_OK;
 }
 }  // namespace dg_order

@@ -29,5 +29,6 @@ inline Bricks bricks_of(const dg_order_desc *o)
 inline uint64_t piece_bound(uint32_t n_bricks, uint64_t N) { return (uint64_t)n_bricks + N / kPiece; }
 
 int order_ok(const dg_order_desc *o, const char *who);      // order.hip
+int order_fits(const dg_order_desc *o, const dg_grid_desc *d, const char *who);
 
 }  // namespace dg_order

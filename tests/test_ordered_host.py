@@ -1,4 +1,5 @@
 """Host side of the samples in spatial order (no GPU needed): room for every batch size, argument checks, the stream handle."""
+import ctypes as C
 import random
 import types
 
@@ -33,3 +34,40 @@ def test_workspace_holds_every_smaller_batch(name, n):
     for k in sizes:
         want = _need(grid, k) if k >= least else B.dg_hashgrid_encode_bwd_workspace_bytes(grid, k)
         assert want <= room, k
+
+
+def _counts(grid, order):
+    """An ordered call on no samples: its argument checks alone."""
+    return B.lib().dg_hashgrid_encode_bwd_ordered_count(C.byref(grid), C.byref(order), None, 0, None, 0, None)
+
+
+@pytest.mark.parametrize("N", [1, 5000, 1 << 19, 13 << 20, 1 << 26])
+def test_order_of_another_grid_is_refused(N):
+    """A descriptor serves the grid it was made for (any number of samples) and is refused with a grid whose levels it does not
+    fit: the brick sums would be written outside them."""
+    names = ["c2_ngp", "c3_2x2", "c4_big", "c5_share"]
+    grids = {name: _grid(name) for name in names}
+    grids["steep"] = B.dg_grid_desc_init(16, 2, 19, 16, 1.7, [2.0, 2.0, 0.25])
+    grids["tall"] = B.dg_grid_desc_init(16, 2, 19, 16, 1.38, [0.25, 2.0, 2.0])
+    orders = {name: B.dg_order_desc_init(grid, N) for name, grid in grids.items()}
+    refused = 0
+    for a, grid in grids.items():
+        for b, order in orders.items():
+            rc = _counts(grid, order)
+            if a == b:
+                assert rc == 0, (a, b)
+            elif rc != 0:
+                refused += 1
+                assert B.dg_hashgrid_encode_bwd_ordered_workspace_bytes(grid, order, 1000) == 0
+            else:                # accepted: the boxes that this grid's own levels have for these bricks
+                assert grid.scale[0][0] / order.n_bricks[0] + 3.02 >= order.box[0][0] or order.box[0][0] == grid.res[0][0] + 1
+    assert refused >= 10
+    for field in ("per_unit", "box", "box_first"):
+        q = B.dg_order_desc_init(grids["c2_ngp"], N)
+        if field == "per_unit":
+            q.per_unit[1] *= 0.5
+        elif field == "box":
+            q.box[1][2] += 1
+        else:
+            q.box_first[2] += 1
+        assert _counts(grids["c2_ngp"], q) != 0, field
