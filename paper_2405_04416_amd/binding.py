@@ -169,9 +169,15 @@ def _ptr(t, dtype=None, optional=False):
     return t.data_ptr()
 
 
+# Raw handle of a device's current stream: building a Stream object for it costs ten times as much, on every call.  Not a public
+# name, so a torch without it gets the Stream object.
+_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+
+
 def _stream():
-    """Raw handle of the current stream (building a Stream object for it costs ten times as much, on every call)."""
-    return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
+    if _raw_stream is None:
+        return torch.cuda.current_stream().cuda_stream
+    return _raw_stream(torch.cuda.current_device())
 
 
 # ------------------------------------------------------------------ host helpers

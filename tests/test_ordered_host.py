@@ -71,3 +71,11 @@ def test_order_of_another_grid_is_refused(N):
         else:
             q.box_first[2] += 1
         assert _counts(grids["c2_ngp"], q) != 0, field
+
+
+def test_stream_handle_without_the_raw_getter(monkeypatch):
+    """A torch that does not have the getter of raw handles serves the public one."""
+    monkeypatch.setattr(B, "_raw_stream", None, raising=False)
+    monkeypatch.delattr(B.torch._C, "_cuda_getCurrentRawStream", raising=False)
+    monkeypatch.setattr(B.torch.cuda, "current_stream", lambda: types.SimpleNamespace(cuda_stream=77))
+    assert B._stream() == 77
