@@ -114,8 +114,9 @@ class TrainStep:
         self.gCk, self.gTk = z(R, k_max, 3), z(R, k_max)
         self.C, self.T, self.gC, self.gT = z(R, 3), z(R), z(R, 3), z(R)
         # the two accumulated words, cleared together at the start of a step
-        self._words = z(2)
-        self.loss, self.status = self._words[:1], self._words[1:].view(i32)
+        words = z(2)
+        self.loss, self.status = words[:1], words[1:].view(i32)
+        self._words = (words, self.loss, self.status)
         self.ws_mlp = z(B.dg_mlp_bwd_app_workspace_bytes(any_model.mlp, n, S if occupancy is None else 1) // 4 + 64)
         # workspace of the binned table-gradient pass, capped (the call batches itself when it is smaller than ideal)
         want = max(self._encode_ws_bytes(mm, n) for mm in models.values())
@@ -324,7 +325,12 @@ class TrainStep:
 
     # -- forward ---------------------------------------------------------------------------
     def segments(self, o, d, t_min=0.0, clear_loss=False):
-        B.dg_clear(self._words if clear_loss else self.status)
+        words, loss, status = self._words
+        if clear_loss and self.loss is loss and self.status is status:
+            B.dg_clear(words)
+        else:                                               # the caller may have put tensors of its own there
+            for t in (self.status, self.loss) if clear_loss else (self.status,):
+                B.dg_clear(t)
         with self._timed("dg_ray_aabb_segments"):
             B.dg_ray_aabb_segments(o, d, self.parts, t_min, self.k_max, self.seg_count, self.seg_t, self.seg_part,
                                    self.status, self.part_offset, self.seg_ray, self.seg_slot, self.ws_seg, holes=self.holes)

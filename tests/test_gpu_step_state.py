@@ -104,6 +104,22 @@ def test_feature_buffers_are_live(ordered):
     assert rel_err(host(m.dtable), want) <= TOL_F32 and float(mine.abs().max()) > 0 and float(mine_g.abs().max()) > 0
 
 
+@pytest.mark.parametrize("which", ["loss", "status", "both"])
+def test_words_of_the_caller(which):
+    """loss and status can be tensors of the caller's own: they are cleared at the start of a step as the step's are."""
+    print("[case] words of the caller", which, flush=True)
+    step, m, o, d, target = _step()
+    step.step(o, d, target)
+    want = float(step.loss)
+    if which != "status":
+        step.loss = torch.full((1,), 5.0, device=step.dev)
+    if which != "loss":
+        step.status = torch.full((1,), 7, dtype=torch.int32, device=step.dev)
+    for _ in range(2):
+        step.step(o, d, target)
+        assert float(step.loss) == pytest.approx(want, rel=TOL_F32) and int(step.status) == 0
+
+
 def _marched(seed=7):
     cfg = di.config("c7_occ")
     cfg["table_range"] *= 3000.0
