@@ -147,16 +147,52 @@ class TrainStep:
 
     # -- samples in spatial order ------------------------------------------------------------
     def _order_min(self, m):
-        """Samples of a sub-model from which on they are put in spatial order.  The kernels for ordered samples serve the
-        16-level grid with the 32-64-16 / 64-64-3 networks.  The order pays once the samples lie densely enough to share table
-        lines and cells.  Whole step, plain against ordered: tables that fit the L2 (T = 2^19) 1.49 / 1.56 ms at 1.7 M samples,
-        2.63 / 2.52 at 3.3 M; larger ones (T = 2^22, four sub-models) 3.45 / 3.43 ms at 0.4 M each, 5.42 / 5.00 at 0.8 M.
-        Occupancy-guided samples lie on surfaces, ten times as densely (1.57 / 1.51 ms at 1.6 M)."""
+        """Samples of a sub-model from which on a training step puts them in spatial order.  The kernels for ordered samples serve
+        the 16-level grid with the 32-64-16 / 64-64-3 networks.  The order pays once the samples lie densely enough to share
+        table lines and cells.  Whole step, plain / ordered in ms; what the lines below lie between:
+        T = 2^18: 1.35 / 1.36 at 1.74 M samples, 1.61 / 1.59 at 2.12 M, 2.01 / 1.87 at 2.65 M.  T = 2^17 and 2^20 gain earlier
+        (1.65 / 1.53 at 1.66 M).  T = 2^19, where the sixteen levels that the ordered gather walks at once displace each other in an L2 that
+        holds one of them: 1.65 / 1.70 at 2.10 M, 1.87 / 1.86 at 2.33 M, 2.07 / 2.05 at 2.64 M.
+        Larger tables, finest level of 2048 cells along the box: T = 2^21 0.81 / 0.81 at 0.56 M, T = 2^22 0.91 / 0.90 at 0.55 M, oblique
+        rays 3.18 / 3.28 with four sub-models of 0.40 M, 3.66 / 3.53 of 0.49 M.  With 8192 cells samples share less: T = 2^21
+        1.28 / 1.29 at 0.91 M, 1.41 / 1.41 at 1.06 M; T = 2^22 1.12 / 1.17 at 0.60 M, 1.32 / 1.31 at 0.70 M; T = 2^24 2.05 / 2.11 at 0.55 M,
+        2.28 / 2.20 at 0.71 M.
+        Occupancy-guided samples lie on surfaces, ten times as densely: T = 2^19 0.85 / 0.87 at 0.73 M, 1.07 / 1.05 at 1.01 M (with cells
+        four times as wide 1.22 / 1.23 at 1.34 M, 1.70 / 1.63 at 2.02 M); T = 2^21 0.87 / 0.87 at 0.45 M."""
         if m.grid.n_levels != 16 or (m.mlp.n_feat, m.mlp.n_hidden_d, m.mlp.n_layers_c) != (32, 64, 2):
             return 1 << 62
         if m.grid.log2_T > 20:
-            return 1 << 19
-        return 1 << 21 if self.occ is None else 1 << 20
+            if self.occ is not None or not self._fine(m):
+                return 1 << 19
+            return 1 << 20 if m.grid.log2_T == 21 else 5 << 17
+        if self.occ is not None:
+            return 1 << 20
+        return 9 << 18 if m.grid.log2_T == 19 else 1 << 21
+
+    @staticmethod
+    def _fine(m):
+        """The finest level has some 4096 cells or more along the longest side of the box."""
+        return max(m.grid.res[m.grid.n_levels - 1]) > 3 << 10
+
+    def _order_factor(self, m, use):
+        """How many times as many samples a call needs that has no backward pass to save time in: the gather alone pays for the
+        sort and for rows written one by one.  Plain / ordered in ms.
+        Rendering: T = 2^17 0.616 / 0.606 at 3.0 M samples; T = 2^18 0.82 / 0.83 at 4.0 M, 1.00 / 0.97 at 5.0 M; T = 2^19 0.73 / 0.84 at
+        3.0 M, 1.16 / 1.18 at 5.0 M, 1.38 / 1.33 at 6.0 M; T = 2^20 0.71 / 0.70 at 2.1 M.  Finest level of 2048 cells: T = 2^21
+        0.28 / 0.30 at 0.55 M, 0.37 / 0.38 at 0.80 M (oblique rays 1.57 / 1.44 with four sub-models of 0.74 M), T = 2^22 0.30 / 0.31 at 0.54 M
+        (oblique 1.18 / 1.10 with four of 0.49 M); 8192 cells: T = 2^21 1.49 / 1.50 at 3.0 M, T = 2^22 0.89 / 0.88 at 1.5 M, T = 2^23 0.71 / 0.70 at 1.1 M.
+        With occupancy-guided samples the step's own lines hold (T = 2^19 0.50 / 0.48 at 1.1 M).
+        Occupancy refresh, T = 2^19: 0.36 / 0.38 at 1.05 M candidates, 0.43 / 0.43 at 1.24 M, 0.57 / 0.55 at 1.71 M; T = 2^18 0.33 / 0.31 at 1.05 M."""
+        T = m.grid.log2_T
+        if use == "refresh":
+            return 1.25 if T == 19 else 1.0
+        if use == "step" or self.occ is not None:
+            return 1.0
+        if T <= 19:
+            return {18: 2.0, 19: 2.25}.get(T, 1.5)
+        if self._fine(m):
+            return {20: 1.0, 21: 3.0, 22: 2.25}.get(T, 1.5)
+        return 1.5 if T == 21 else 1.0
 
     def _encode_ws_bytes(self, m, n):
         """Workspace of the table-gradient pass for up to n samples.  In spatial order it holds the unmerged levels only, and
@@ -189,10 +225,10 @@ class TrainStep:
         ends = [k for a, b in zip(sizes, sizes[1:]) for k in last_before_changes(a, b)]
         return max(B.dg_hashgrid_encode_bwd_workspace_bytes(m.grid, least), *(need(k) for k in ends + [n]))
 
-    def _order_of(self, m, N):
-        """Order descriptor of a batch of N samples, or None where the plain kernels serve it (also where not even the two
-        coarsest levels of a grid fit LDS brick by brick)."""
-        if self.ordered is None or N < self._order_min(m):
+    def _order_of(self, m, N, use="step"):
+        """Order descriptor of a batch of N samples for a training step ("step"), a rendering or an occupancy refresh, or None
+        where the plain kernels serve it (also where not even the two coarsest levels of a grid fit LDS brick by brick)."""
+        if self.ordered is None or N < self._order_min(m) * self._order_factor(m, use):
             return None
         order = B.dg_order_desc_init(m.grid, N)
         return order if order.n_merged > 0 else None
@@ -421,8 +457,9 @@ class TrainStep:
         self.segments(o, d, clear_loss=training)
         # the sub-model whose backward pass runs first: only its counts may wait in the workspace that all share
         first = next((p for p in self.resident if self.offsets[p + 1] > self.offsets[p]), None)
+        use = "step" if training else "render"
         if self.occ is not None:
-            self._forward_marched(o, d)
+            self._forward_marched(o, d, use)
         for p in self.resident if self.occ is None else ():
             b, e, sl = self._slices(p)
             n_seg = e - b
@@ -436,7 +473,7 @@ class TrainStep:
                                      self.parts_host[p], S, self.seed, jit, self.u[sl], self.delta[sl],
                                      self.t_fixed[sl] if want_t else None)
             rows = self._rows(p)
-            order = self._order_of(m, N)
+            order = self._order_of(m, N, use)
             if training and self.side is not None and p == first:
                 self._count_ahead(p, order, sl, N)
             with self._timed("dg_dir_encode"):
@@ -463,7 +500,7 @@ class TrainStep:
             B.dg_appearance_rows(self.appearance[0], self.appearance[1], index, n, self.app_rows[rows])
         return self.app_rows[rows]
 
-    def _forward_marched(self, o, d):
+    def _forward_marched(self, o, d, use):
         """Per sub-model forward with occupancy-guided sampling (Sec. 3.2, Sec. 5.1): segments of different lengths,
         one direction row per sample."""
         self.samples = {}
@@ -490,7 +527,7 @@ class TrainStep:
             if N:
                 with self._timed("dg_dir_encode"):
                     B.dg_dir_encode(d, self.sample_ray[sl], N, self.deg, self.dir_enc[sl])
-                order = self._order_of(m, N)
+                order = self._order_of(m, N, use)
                 self.layout[p] = (s0 - N, N, order)
                 self._encode_fwd(p, m, order, sl, N)
                 app = self._appearance_rows(self.sample_ray[sl], N, sl)
@@ -549,7 +586,7 @@ class TrainStep:
                 cell = self.sample_ray[:n]                      # the step's sample buffers serve as scratch
                 with self._timed("dg_occ_candidates"):
                     B.dg_occ_candidates(q.desc, q.bits, n, n_uniform, warmup, self.seed, iteration, tries, cell, self.u[:n], i0=i0)
-                order = None if warmup else self._order_of(m, n)        # during warm-up the candidates come cell after cell anyway
+                order = None if warmup else self._order_of(m, n, "refresh")        # during warm-up the candidates come cell after cell anyway
                 self._encode_fwd(p, m, order, slice(0, n), n, None if order is None else cell)
                 if density_kernel:
                     with self._timed("dg_occ_evaluate"):

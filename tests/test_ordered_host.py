@@ -79,3 +79,24 @@ def test_stream_handle_without_the_raw_getter(monkeypatch):
     monkeypatch.delattr(B.torch._C, "_cuda_getCurrentRawStream", raising=False)
     monkeypatch.setattr(B.torch.cuda, "current_stream", lambda: types.SimpleNamespace(cuda_stream=77))
     assert B._stream() == 77
+
+
+@pytest.mark.parametrize("n_max", [2048, 8192])
+@pytest.mark.parametrize("log2_T", range(15, 25))
+def test_lines_of_the_order(log2_T, n_max):
+    """Where a batch changes to spatial order: at no fewer samples without a backward pass than with one, and never at a size where
+    ray order was measured to be more than 2 % faster (log2_T, n_max, use, samples)."""
+    faster_in_ray_order = [(18, 2048, "render", 3000000), (19, 2048, "step", 2103680), (19, 2048, "render", 3980000), (19, 2048, "refresh", 1048576),
+                           (21, 8192, "step", 602048), (21, 8192, "render", 2070000), (22, 8192, "step", 602560), (22, 8192, "render", 1085000),
+                           (24, 8192, "step", 554560)]
+    m = types.SimpleNamespace(grid=B.dg_grid_desc_init(16, 2, log2_T, 16, B.dg_growth_factor(16, n_max, 16), [2.0, 2.0, 0.25]),
+                              mlp=B.dg_mlp_desc(32, 64, 16, 16, 64, 2, 1))
+    for use in ("step", "render", "refresh"):
+        step = object.__new__(TrainStep)
+        step.occ, step.ordered = {} if use == "refresh" else None, True
+        line = int(step._order_min(m) * step._order_factor(m, use))
+        assert step._order_of(m, line - 1, use) is None and step._order_of(m, line, use) is not None
+        assert step._order_of(m, step._order_min(m) - 1, use) is None
+        for T, finest, what, N in faster_in_ray_order:
+            if (T, finest, what) == (log2_T, n_max, use):
+                assert step._order_of(m, N, use) is None, N
