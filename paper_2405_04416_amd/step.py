@@ -119,7 +119,8 @@ class TrainStep:
         self._words = (words, self.loss, self.status)
         self.ws_mlp = z(B.dg_mlp_bwd_app_workspace_bytes(any_model.mlp, n, S if occupancy is None else 1) // 4 + 64)
         # workspace of the binned table-gradient pass, capped (the call batches itself when it is smaller than ideal)
-        want = max(self._encode_ws_bytes(mm, n) for mm in models.values())
+        grids = {(bytes(mm.grid), bytes(mm.mlp)): mm for mm in models.values()}       # sub-models mostly share one
+        want = max(self._encode_ws_bytes(mm, n) for mm in grids.values())
         self.ws_enc = torch.zeros(min(want, encode_ws_cap) // 4 + 64, dtype=f32, device=self.dev) if binned_backward else None
         self.foreign_prefilled = bool(foreign_prefilled)
         # The queue sizes of the binned table-gradient pass depend on the sample coordinates alone: for the sub-model whose
@@ -221,7 +222,7 @@ class TrainStep:
             return last_before_changes(a, mid) + last_before_changes(mid, b)
 
         # a grid of sizes first: a flat box's bricks do not grow evenly
-        sizes = sorted({least, n} | {int(least * (n / least) ** (i / 32)) for i in range(1, 32)})
+        sizes = sorted({least, n} | {int(least * (n / least) ** (i / 12)) for i in range(1, 12)})
         ends = [k for a, b in zip(sizes, sizes[1:]) for k in last_before_changes(a, b)]
         return max(B.dg_hashgrid_encode_bwd_workspace_bytes(m.grid, least), *(need(k) for k in ends + [n]))
 
