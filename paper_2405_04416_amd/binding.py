@@ -169,15 +169,16 @@ def _ptr(t, dtype=None, optional=False):
     return t.data_ptr()
 
 
-# Raw handle of a device's current stream: building a Stream object for it costs ten times as much, on every call.  Not a public
-# name, so a torch without it gets the Stream object.
+# Raw handle of a device's current stream: building a Stream object for it costs ten times as much, on every call.  Not public
+# names, so a torch without them gets the public calls.
 _raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+_current_device = getattr(torch._C, "_cuda_getDevice", torch.cuda.current_device)
 
 
 def _stream():
     if _raw_stream is None:
         return torch.cuda.current_stream().cuda_stream
-    return _raw_stream(torch.cuda.current_device())
+    return _raw_stream(_current_device())
 
 
 # ------------------------------------------------------------------ host helpers
