@@ -191,8 +191,9 @@ fwd_kernel(const __half *__restrict__ weights, const __half *__restrict__ feat, 
 }
 
 // ---------------------------------------------------------------------------------------- densities of grid cells
-// Refresh of the occupancy grid: the density net alone, its output straight into the grid.  Densities are >= 0, so their bit
-// patterns order like unsigned integers and the maximum is one integer atomic; a density that is not > 0 (NaN) is left out.
+// Refresh of the occupancy grid: the density net alone, its output straight into the grid.  Densities are > 0 -- the clip before the
+// exponential turns a NaN of the network into -15 --, so their bit patterns order like unsigned integers and the maximum is one
+// integer atomic.
 // Bound by the rows it reads and the atomics' cache lines.  8.4 M candidates, 16.8 M cells: whole networks and a separate maximum
 // 304 + 323 us, this kernel on candidates in spatial order 215 us (neighbours' cells then share lines).
 template <bool ROWS>
@@ -214,7 +215,7 @@ density_max_kernel(const __half *__restrict__ weights, const __half *__restrict_
         load_features<ROWS>(feat, n_samples, nn, h, x0);
         const uint32_t c = cell[nn * cell_stride];
         const float sigma = __expf(clip15(density_net(lds, opaque(lane), x0)));
-        if (h == 0 && n < n_samples && c < n_cells && sigma > 0.0f) atomicMax(reinterpret_cast<unsigned int *>(density) + c, __float_as_uint(sigma));
+        if (h == 0 && n < n_samples && c < n_cells) atomicMax(reinterpret_cast<unsigned int *>(density) + c, __float_as_uint(sigma));
     }
 }
 

@@ -258,3 +258,20 @@ def test_density_of_candidates(N):
     small = B.dg_mlp_desc(8, 32, 16, 4, 32, 1, 1)
     with pytest.raises(B.DistGridError):
         B.dg_occ_evaluate(small, weights, planes, False, cell, 1, N, got)
+
+
+def test_density_of_a_nan_candidate():
+    """A NaN among the features: the clip makes the network's NaN -15, the same density as by the separate entry points."""
+    print("[case] density of a NaN candidate", flush=True)
+    N, n_cells = 40, 40
+    mlp = B.dg_mlp_desc(32, 64, 16, 16, 64, 2, 1)
+    weights = dev((np.random.default_rng(43).standard_normal(9408) * 0.2).astype(np.float16))
+    planes = torch.randn(16, N, 2, device=DEV).half()
+    planes[3, 7, 1] = planes[0, 39, 0] = float("nan")
+    cell = torch.arange(N, dtype=torch.int32, device=DEV)
+    sigma, rgb = torch.zeros(N, device=DEV), torch.zeros(N, 3, device=DEV)
+    B.dg_mlp_fwd(mlp, weights, planes, torch.zeros(1, 16, dtype=torch.float16, device=DEV), N, N, sigma, rgb)
+    want, got = torch.zeros(n_cells, device=DEV), torch.zeros(n_cells, device=DEV)
+    B.dg_occ_update(want, cell, sigma, N)
+    B.dg_occ_evaluate(mlp, weights, planes, False, cell, 1, N, got)
+    assert torch.equal(got, want) and bool((got > 0).all())
