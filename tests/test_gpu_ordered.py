@@ -155,6 +155,123 @@ def test_small_gradients_beside_a_large_one(key, N):
         assert np.all(np.abs(have[sl] - want[sl]) <= 12 * 2.0 ** -24 * scale[sl]), l
 
 
+# the cuts that batches of some millions of samples get: several bricks along every axis, up to twelve merged levels, more
+# bricks than 64 KB of LDS count
+CUTS = {"flat": dict(log2_T=19, n_max=2048, extent=[2.0, 2.0, 0.25], made_for=13300000, bricks=[53, 53, 6], n_merged=12),
+        "upright": dict(log2_T=17, n_max=2048, extent=[0.25, 2.0, 2.0], made_for=20 << 20, bricks=[6, 53, 53], n_merged=12),
+        "cube": dict(log2_T=16, n_max=1024, extent=[1.0, 1.0, 1.0], made_for=1 << 26, bricks=[31, 31, 31], n_merged=10),
+        "fine": dict(log2_T=16, n_max=8192, extent=[2.0, 2.0, 0.25], made_for=1 << 25, bricks=[60, 60, 7], n_merged=10)}
+
+
+def _beside_faces(order, N, rng):
+    """Coordinates of which three quarters lie on a brick's face along some axis, exactly or up to three roundings beside it."""
+    u = rng.random((N, 3)).astype(np.float32)
+    for n in range(0, 3 * N // 4):
+        a = n % 3
+        x = np.float32(rng.integers(1, order.n_bricks[a])) / np.float32(order.n_bricks[a])
+        for _ in range(n // 3 % 4):
+            x = np.nextafter(x, np.float32(n // 12 % 2), dtype=np.float32)
+        u[n, a] = x
+    return u
+
+
+@pytest.mark.parametrize("key", list(CUTS))
+def test_bricks_of_a_large_batch(key):
+    """The cuts of large batches on some thousand samples (the calls take a descriptor made for another N), every entry of the
+    merged levels against the oracle."""
+    print("[case] bricks of a large batch", key, flush=True)
+    q = CUTS[key]
+    growth = B.dg_growth_factor(16, q["n_max"], 16)
+    grid, ref_grid = (f(16, 2, q["log2_T"], 16, growth, q["extent"]) for f in (B.dg_grid_desc_init, oracle.grid_init))
+    order = B.dg_order_desc_init(grid, q["made_for"])
+    assert list(order.n_bricks) == q["bricks"] and order.n_merged == q["n_merged"] and order.total > 1 << 14
+    N, M = 24007, order.n_merged
+    rng = np.random.default_rng(36)
+    u = _beside_faces(order, N, rng)
+    g = (rng.standard_normal((N, 32)) * 1e-3).astype(np.float32)
+    ordered = torch.zeros(N, 4, device=DEV)
+    pieces = torch.zeros(B.dg_order_pieces_words(order, N), dtype=torch.int32, device=DEV)
+    ud, gd = dev(u), dev(_mixed(g, M))
+    B.dg_order_samples(order, ud, N, ordered, pieces, torch.zeros(B.dg_order_workspace_bytes(order) // 4, dtype=torch.int32, device=DEV))
+    assert np.array_equal(np.sort(host(ordered)[:, 3].copy().view(np.uint32)), np.arange(N))
+    dtable = torch.zeros(ref_grid.n_entries, 2, device=DEV)
+    ws = torch.zeros(B.dg_hashgrid_encode_bwd_ordered_workspace_bytes(grid, order, N) // 4 + 64, device=DEV)
+    B.dg_hashgrid_encode_bwd_ordered(grid, order, ordered, pieces, ud, gd, gd.abs().max().reshape(1).view(torch.int32), N, dtable, ws)
+    want = oracle.encode_bwd(ref_grid, u, g.astype(np.float64))
+    scale = oracle.encode_bwd(ref_grid, u, np.abs(g).astype(np.float64))
+    have = host(dtable).astype(np.float64)
+    assert np.all(have[want == 0] == 0)
+    quantum = 2.0 ** -37 * float(np.abs(g).max()) * N
+    for l in range(M):
+        sl = slice(ref_grid.first[l], ref_grid.first[l + 1])
+        assert np.all(np.abs(have[sl] - want[sl]) <= 1e-5 * scale[sl] + quantum), l           # bound as in test_ordered_encode
+    for l in range(M, 16):
+        sl = slice(ref_grid.first[l], ref_grid.first[l + 1])
+        assert rel_err(have[sl], want[sl]) <= TOL_F16, l
+
+
+@pytest.mark.parametrize("N,log2_T,n_max", [((1 << 22) + 77, 19, 2048), ((1 << 21) + 5, 22, 8192)])
+def test_ordered_gradient_at_full_size(N, log2_T, n_max):
+    """A batch of production size, level by level and entry by entry against the pass in ray order on the same gradient."""
+    print("[case] ordered gradient at full size", N, log2_T, flush=True)
+    grid = B.dg_grid_desc_init(16, 2, log2_T, 16, B.dg_growth_factor(16, n_max, 16), [2.0, 2.0, 0.25])
+    gen = torch.Generator(device=DEV)
+    gen.manual_seed(37)
+    u = torch.rand(N, 3, device=DEV, generator=gen)
+    planes = torch.randn(16, N, 2, device=DEV, generator=gen) * 1e-3
+    order = B.dg_order_desc_init(grid, N)
+    M = order.n_merged
+    ordered, pieces = torch.zeros(N, 4, device=DEV), torch.zeros(B.dg_order_pieces_words(order, N), dtype=torch.int32, device=DEV)
+    B.dg_order_samples(order, u, N, ordered, pieces, torch.zeros(B.dg_order_workspace_bytes(order) // 4, dtype=torch.int32, device=DEV))
+    mixed = torch.cat([planes[:M].transpose(0, 1).reshape(-1), planes[M:].reshape(-1)])
+    ws = torch.zeros(B.dg_hashgrid_encode_bwd_workspace_bytes(grid, N) // 4 + 64, device=DEV)
+    got, want, scale = (torch.zeros(grid.n_entries, 2, device=DEV) for _ in range(3))
+    B.dg_hashgrid_encode_bwd_ordered(grid, order, ordered, pieces, u, mixed, mixed.abs().max().reshape(1).view(torch.int32), N, got, ws)
+    B.dg_hashgrid_encode_bwd(grid, u, planes, N, want, ws)
+    B.dg_hashgrid_encode_bwd(grid, u, planes.abs(), N, scale, ws)
+    for l in range(16):
+        sl = slice(grid.offset[l], grid.offset[l + 1])
+        # in ray order a value is rounded to 2^-20 (both paths at the unmerged levels), to a quantum of 2^-31 of the largest per record
+        # and reaches the table by a handful of fp32 adds; the ordered side is below 1e-5 as in test_ordered_encode
+        assert bool(((got[sl] - want[sl]).abs() <= 1.5e-5 * scale[sl] + 2.0 ** -31 * 8e-3 * 64).all()), l
+        assert float((got[sl] - want[sl]).norm() / want[sl].norm()) <= 4 * 2.0 ** -20, l
+
+
+@pytest.mark.parametrize("bad", ["overflow", "nan", None])
+def test_largest_gradient_of_the_networks(bad):
+    """The word that the networks report for the brick sums: the largest magnitude of what they write, infinity where a delta
+    overflows fp16 or is NaN; the table gradient that follows is then marked at every merged level."""
+    print("[case] largest gradient", bad, flush=True)
+    grid, ref_grid = _grids("cached")
+    N = 3001
+    mlp = B.dg_mlp_desc(32, 64, 16, 16, 64, 2, 1)
+    rng = np.random.default_rng(44)
+    u = _coords(N, "points")
+    order, ordered, pieces = _sorted(grid, u, N)
+    M = order.n_merged
+    rows = torch.zeros(N, 32, dtype=torch.float16, device=DEV)
+    B.dg_hashgrid_encode_fwd_ordered(grid, dev(di.make_table(ref_grid.n_entries, 2, 1.0, seed=45)), ordered, N, rows)
+    dsigma, drgb = dev((rng.standard_normal(N) * 1e-4).astype(np.float32)), dev((rng.standard_normal((N, 3)) * 1e-4).astype(np.float32))
+    if bad == "nan":
+        dsigma[1234] = float("nan")
+    weights, dir_enc = dev((rng.standard_normal(9408) * 0.2).astype(np.float16)), torch.zeros(-(-N // 32), 16, dtype=torch.float16, device=DEV)
+    dfeat, dW = torch.zeros(N * 32, device=DEV), torch.zeros(9408, device=DEV)
+    largest = pieces[1:2]
+    assert int(largest) == 0
+    B.dg_mlp_bwd_rows(mlp, weights, rows, dir_enc, None, 32, N, dsigma, drgb, 2.0 ** (60 if bad == "overflow" else 12), M, dfeat, largest, dW,
+                      torch.zeros(B.dg_mlp_bwd_app_workspace_bytes(mlp, N, 32) // 4 + 64, device=DEV))
+    reported = float(largest.view(torch.float32))
+    if bad is None:
+        assert reported == float(dfeat.abs().max()) > 0
+    else:
+        assert reported == float("inf")
+    dtable = torch.zeros(ref_grid.n_entries, 2, device=DEV)
+    ws = torch.zeros(B.dg_hashgrid_encode_bwd_ordered_workspace_bytes(grid, order, N) // 4 + 64, device=DEV)
+    B.dg_hashgrid_encode_bwd_ordered(grid, order, ordered, pieces, dev(u), dfeat, largest, N, dtable, ws)
+    for l in range(M):
+        assert bool(torch.isfinite(dtable[ref_grid.first[l]:ref_grid.first[l + 1]]).all()) == (bad is None), l
+
+
 def test_non_finite_gradient_is_marked():
     """An infinite or NaN gradient (an fp16 delta that overflowed) leaves NaN in the table gradient's merged levels."""
     grid, ref_grid = _grids("cached")
@@ -193,6 +310,30 @@ def test_step_in_spatial_order(name, R, overrides, monkeypatch):
     cfg["grid"] = dict(cfg["grid"], **overrides)
     step, _ = _compare_step(cfg, R, seed=2, lambda1=1e-3, loss_scale=2.0 ** 14, use_jitter_array=False, table_gain=3000.0)
     assert all(order is not None for _, _, order in step.layout.values())
+
+
+def test_cascade_in_spatial_order(monkeypatch):
+    """The two-level cascade with the order forced: eight sub-models, regions with holes, rays that meet a sub-model twice."""
+    from test_gpu_step import _compare_step
+    print("[case] cascade in spatial order", flush=True)
+    monkeypatch.setattr(TrainStep, "_order_min", lambda self, m: 1)
+    cfg = di.config("c6_cascade")
+    cfg["grid"], cfg["grid_coarse"] = dict(cfg["grid"], log2_T=16), dict(cfg["grid_coarse"], log2_T=14)
+    step, _ = _compare_step(cfg, 700, seed=7, lambda1=1e-3, loss_scale=2.0 ** 14, use_jitter_array=False, table_gain=3000.0)
+    assert len(step.layout) == 8 and all(order is not None for _, _, order in step.layout.values())
+
+
+@pytest.mark.parametrize("name,R,room", [("c7_occ", 1100, 60000), ("c3_2x2", 800, 200000)])
+def test_occupancy_step_in_spatial_order(name, R, room, monkeypatch):
+    """Occupancy-guided samples with the order forced: segments of different lengths, one box and four."""
+    from test_gpu_step_occupancy import _compare
+    print("[case] occupancy step in spatial order", name, flush=True)
+    monkeypatch.setattr(TrainStep, "_order_min", lambda self, m: 1)
+    cfg = di.config(name)
+    cfg["occ"] = dict(res=48, max_steps=512)
+    cfg["grid"] = dict(cfg["grid"], log2_T=16)
+    step, ref = _compare(cfg, R, seed=3, lambda1=1e-3, loss_scale=2.0 ** 14, table_gain=3000.0, max_samples=room)
+    assert len(step.layout) == len(ref["per"]) and all(order is not None for _, _, order in step.layout.values())
 
 
 def test_step_without_mergeable_levels(monkeypatch):
