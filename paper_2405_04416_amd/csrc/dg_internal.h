@@ -50,8 +50,8 @@ int encode_bwd_binned_count(const char *who, const dg_grid_desc *d, uint32_t fro
 int brick_bwd(const char *who, const dg_grid_desc *d, const dg_order_desc *order, const uint32_t *pieces, const void *ordered,
               const float *dfeat, const uint32_t *largest, uint64_t N, float *dtable, double *wide, hipStream_t st);
 
-// rows: features (and the gradient of levels below n_merged) as sample-major rows instead of planes.
-// matrix-core path of the 32-64-16 / (32 + n_app)-64-64-3 field MLPs (mlp_mfma.hip); n_app = 0, 16 or 48
+// Matrix-core path of the 32-64-16 / (32 + n_app)-64-64-3 field MLPs (mlp_mfma.hip); n_app = 0, 16 or 48.
+// rows: features (and the gradient of levels below n_merged) are sample-major rows instead of planes.
 size_t mlp_mfma_workspace_bytes(uint64_t N, uint32_t n_app, uint32_t S);
 size_t mlp_mfma_weight_count(uint32_t n_app);
 void mlp_mfma_density_max(const void *weights, const void *feat, bool rows, const uint32_t *cell, uint32_t cell_stride, uint64_t N, float *density,

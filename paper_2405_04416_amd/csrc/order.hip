@@ -5,8 +5,10 @@
 // corner row costs a cache line of its own, and runs of equal cells end with the ray.  In spatial order the lines that
 // neighbours share are fetched once, and the coarser levels' gradients can be summed on chip before they go anywhere.
 //
-//   1. bricks: the box is cut into a few thousand to 2^15 equal bricks (700 to 1200 samples each).  Count, scan,
-//      scatter with one persistent tiling; the counters of all bricks live in LDS, so there are no global atomics.
+//   1. bricks: the box is cut into equal bricks.  Aimed at are 700 to 1200 samples each; the number along every axis is then
+//      rounded down and the total is at most 2^15, so that a brick holds some 700 to 2400 samples on average (2^19 samples: a few
+//      hundred bricks; the limit rules from some 39 M samples on).  Count, scan, scatter with one persistent tiling; the
+//      counters of all bricks live in LDS, so there are no global atomics.
 //      A sample becomes 16 bytes: its coordinates and the index it came from (or a number of the caller's).
 //   2. inside a brick: pencils along x (the table's contiguous direction), sorted in LDS.
 // The order is a matter of speed alone: any order gives the same results.

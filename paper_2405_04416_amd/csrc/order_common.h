@@ -5,7 +5,7 @@
 namespace dg_order {
 
 constexpr uint32_t kMaxBricks = 1u << 15;      // their counters fit LDS (128 KB)
-constexpr uint32_t kPerBrickMax = 1200, kPerBrickMin = 700;      // samples per brick aimed at
+constexpr uint32_t kPerBrickMax = 1200, kPerBrickMin = 700;      // samples per brick aimed at (rounding the number of bricks down and their limit leave up to 2400)
 
 constexpr uint32_t kPiece = 4096;               // samples of a brick that one workgroup takes at most
 constexpr int kMaxMerged = 12;                  // levels summed brick by brick at most
