@@ -37,7 +37,7 @@ constexpr int kAccDepth = 4;                       // records in flight per accu
 // cut into floor(records / 2^piece_log2) equal pieces, so a bin with less than two pieces' worth stays whole (a second
 // workgroup would clear and write out a table of its own for little).  2^17 records where there are plenty; where the bins
 // are few and the records too, pieces shrink until some 512 workgroups have one (c1's grid, 33 k samples in three bins of 131 k
-// records: 46 -> 13 us).
+// records: 46 -> 17 us).
 constexpr int kPieceLog2Min = 13, kPieceLog2Max = 17;
 constexpr int kAccMaxLog2 = kPieceLog2Max + 1;
 __host__ __device__ __forceinline__ uint32_t acc_pieces(uint32_t total, uint32_t piece_log2) { return total == 0u ? 0u : (total >> piece_log2 ? total >> piece_log2 : 1u); }

@@ -82,7 +82,7 @@ encode_fwd_ordered_kernel(dg_grid_desc g, const float2 *__restrict__ table, cons
 // The other levels, which in ray order pass through records of 27-bit values, are summed in fixed point and reach the table
 // with an fp32 add per brick.  Against 64-bit sums (33.5 M samples, 25200 bricks, 2-norm of level 0): ray order 2.3e-7, this
 // 2.4e-8; in fixed point with fp32 adds 2.6e-7 (13.3 M samples), and nothing was left of gradients below 2^-38 of the largest.
-// The fp64 adds cost 1 to 2 % of a step (13.3 M samples, T = 2^19: 7.48 -> 7.60 ms).
+// The fp64 adds take 4 % of this kernel's time (13.3 M samples, T = 2^19: 1.59 -> 1.65 ms), clearing and folding `wide` 12 us.
 // A value v becomes round(v * 2^k): the add of 1.5 * 2^52 in fp64 leaves it in the low mantissa bits, in two's complement.  k is
 // such that the magnitudes of a piece (at most 2^12 samples) sum to less than 2^50; adding the doubles' bit patterns as
 // integers adds those low bits, what happens above bit 50 is dropped when the sum is read.  (Integer adds are the fastest LDS
@@ -127,6 +127,7 @@ __device__ __forceinline__ void add_fixed(unsigned long long *slot, float v, dou
 
 __device__ __forceinline__ void add_wide(unsigned long long *slot, float v)
 {
+    asm("" : "+v"(v));          // the sixteen conversions stay on this side of the branch: ahead of it they hold 32 registers
     __hip_atomic_fetch_add(reinterpret_cast<double *>(slot), (double)v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
 }
 
@@ -134,20 +135,24 @@ __device__ __forceinline__ void add_wide(unsigned long long *slot, float v)
 __device__ __forceinline__ void add_to_box(unsigned long long *d, bool wide, double to_fixed, uint32_t nx, uint32_t nxy, uint32_t plane, const float (&vx)[8],
                                            const float (&vy)[8])
 {
+    unsigned long long *const row[4] = {d, d + nx, d + nxy, d + nx + nxy};
+    // one branch around all sixteen adds (a choice per add puts a branch between any two of them)
+    if (wide) {
 #pragma unroll
-    for (int c = 0; c < 8; ++c) {
-        unsigned long long *e = d + (c & 1) + ((c >> 1) & 1) * nx + (c >> 2) * nxy;
-        if (wide) {
-            add_wide(e, vx[c]);
-            add_wide(e + plane, vy[c]);
-        } else {
-            add_fixed(e, vx[c], to_fixed);
-            add_fixed(e + plane, vy[c], to_fixed);
+        for (int c = 0; c < 8; ++c) {
+            add_wide(row[c >> 1] + (c & 1), vx[c]);
+            add_wide(row[c >> 1] + (c & 1) + plane, vy[c]);
+        }
+    } else {
+#pragma unroll
+        for (int c = 0; c < 8; ++c) {
+            add_fixed(row[c >> 1] + (c & 1), vx[c], to_fixed);
+            add_fixed(row[c >> 1] + (c & 1) + plane, vy[c], to_fixed);
         }
     }
 }
 
-__global__ void __launch_bounds__(kBrickBlock)
+__global__ void __launch_bounds__(kBrickBlock, 4)       // two workgroups per compute unit: four wavefronts per SIMD, 128 registers
 brick_bwd_kernel(dg_grid_desc g, Bricks b, Boxes boxes, const uint2 *__restrict__ pieces, const float4 *__restrict__ ordered,
                  const float4 *__restrict__ dfeat, const uint32_t *__restrict__ largest, float *__restrict__ dtable, double *__restrict__ wide_table)
 {
