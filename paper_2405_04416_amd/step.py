@@ -262,8 +262,9 @@ class TrainStep:
     def _written(rows, p, start, N, levels, order=None, by_position=False):
         """Books of a feature buffer: partition p's samples have been written, `levels` levels of them as rows; what lay
         there before is gone."""
-        for q in [q for q, r in rows.items() if q == p or (r.start < start + N and start < r.start + r.N)]:
-            del rows[q]
+        if rows:
+            for q in [q for q, r in rows.items() if q == p or (r.start < start + N and start < r.start + r.N)]:
+                del rows[q]
         if levels:
             rows[p] = _Rows(start, N, levels, order, by_position)
 
