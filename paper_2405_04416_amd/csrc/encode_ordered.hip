@@ -77,12 +77,13 @@ encode_fwd_ordered_kernel(dg_grid_desc g, const float2 *__restrict__ table, cons
 // Table gradient of levels [0, n_merged): a workgroup takes a piece of a brick and sums all its contributions in LDS -- the
 // brick's vertices at those levels, in 64 bits, one plane per feature -- then adds the sums to the table gradient, one
 // global add per vertex the brick touches.
-// Levels [0, n_wide) -- the coarse levels, which ray order sums in fp64 from end to end -- are summed in fp64, here and over the
-// bricks (a vertex of the coarsest level gets hundreds of them): into `wide`, which fold_wide_kernel adds to the table.
-// The other levels, which in ray order pass through records of 27-bit values, are summed in fixed point and reach the table
-// with an fp32 add per brick.  Against 64-bit sums (33.5 M samples, 25200 bricks, 2-norm of level 0): ray order 2.3e-7, this
-// 2.4e-8; in fixed point with fp32 adds 2.6e-7 (13.3 M samples), and nothing was left of gradients below 2^-38 of the largest.
-// The fp64 adds take 4 % of this kernel's time (13.3 M samples, T = 2^19: 1.59 -> 1.65 ms), clearing and folding `wide` 12 us.
+// Levels [0, n_wide) -- the coarse levels, which ray order sums in fp64 -- are summed in fp64, the other levels, which in ray order
+// pass through records of 27-bit values, in fixed point.  Over the bricks levels [0, n_fold) are summed in fp64 as well (a vertex of
+// the coarsest level gets hundreds of them): into `wide`, which fold_wide_kernel adds to the table.  The others reach the table
+// with an fp32 add per brick.  Against 64-bit sums (33.5 M samples, 25200 bricks, 2-norm of levels 0 / 3 / 7): ray order 2.4e-7 / 2.0e-7 /
+// 3.3e-7, this 2.5e-8 / 2.5e-8 / 4.2e-8; level 0 in fixed point with fp32 adds 2.6e-7 (13.3 M samples), and nothing was left there of
+// gradients below 2^-38 of the largest.
+// The fp64 adds take 4 % of this kernel's time (13.3 M samples, T = 2^19: 1.59 -> 1.65 ms), clearing and folding `wide` some 12 us.
 // A value v becomes round(v * 2^k): the add of 1.5 * 2^52 in fp64 leaves it in the low mantissa bits, in two's complement.  k is
 // such that the magnitudes of a piece (at most 2^12 samples) sum to less than 2^50; adding the doubles' bit patterns as
 // integers adds those low bits, what happens above bit 50 is dropped when the sum is read.  (Integer adds are the fastest LDS
@@ -93,7 +94,7 @@ encode_fwd_ordered_kernel(dg_grid_desc g, const float2 *__restrict__ table, cons
 // sample) take 1.0, the LDS adds 0.6, the sums themselves 1.2; the same levels through the coarse prefix and the bins took
 // 8 ms.  13.3 M samples, T = 2^19, levels 0..11: 1.55 ms.  Two workgroups per compute unit (512 threads, at most 80 KB of sums) and two
 // samples per lane beat four samples per lane (4.3 ms) and one workgroup of 1024 (4.3 ms).
-struct Boxes { uint32_t n_merged, n_wide, dim[kMaxMerged][3], first[kMaxMerged + 1]; };
+struct Boxes { uint32_t n_merged, n_wide, n_fold, dim[kMaxMerged][3], first[kMaxMerged + 1]; };
 
 constexpr int kBrickBlock = 512, kRun = 2;
 
@@ -285,11 +286,12 @@ brick_bwd_kernel(dg_grid_desc g, Bricks b, Boxes boxes, const uint2 *__restrict_
             const uint32_t v = i >> 1, f = i & 1u;
             const unsigned long long held = sums[f * n_vertices + boxes.first[l] + v];
             const size_t at = 2 * (size_t)vertex_entry(lv, mask, low[0] + v % nx, low[1] + v / nx % ny, low[2] + v / (nx * ny)) + f;
-            if (l < boxes.n_wide) {
-                const double sum = __longlong_as_double((long long)held);
+            const double fixed = (double)((long long)(held << 13) >> 13) * from_fixed;
+            if (l < boxes.n_fold) {
+                const double sum = l < boxes.n_wide ? __longlong_as_double((long long)held) : fixed;
                 if (sum != 0.0) unsafeAtomicAdd(wide_table + 2 * (size_t)lv.offset + at, sum);
             } else {
-                const float sum = (float)((double)((long long)(held << 13) >> 13) * from_fixed);
+                const float sum = (float)fixed;
                 if (sum != 0.0f) unsafeAtomicAdd(dst + at, sum);
             }
         }
@@ -305,12 +307,20 @@ fold_wide_kernel(const double *__restrict__ wide_table, uint32_t n, float *__res
     if (v != 0.0f) dtable[i] += v;
 }
 
-// bytes of the fp64 sums of the coarse levels among the merged ones
-size_t wide_bytes(const dg_grid_desc *d, const dg_order_desc *order)
+// Merged levels whose bricks are summed in fp64: tables of at most 2^18 entries, which get many adds per entry -- the coarse levels
+// because many bricks share a cell, hashed ones because many vertices share an entry (some 100 with 2^18 entries and 16 000 bricks,
+// where fp32 adds are as far from 64-bit sums as ray order, 1.5e-7 in 2-norm; some 55 with 2^19, 1.1e-7 against 1.3e-7).  Up to 29 MB
+// to clear and fold.
+constexpr uint32_t kFoldEntries = 1u << 18;
+uint32_t fold_levels(const dg_grid_desc *d, const dg_order_desc *order)
 {
-    const uint32_t n_wide = std::min(dg::coarse_levels(d), order->n_merged);
-    return (2 * (size_t)d->offset[n_wide] * sizeof(double) + 255) / 256 * 256;
+    uint32_t l = 0;
+    while (l < order->n_merged && d->offset[l + 1] - d->offset[l] <= kFoldEntries) ++l;
+    return l;
 }
+
+// bytes of their sums
+size_t wide_bytes(const dg_grid_desc *d, const dg_order_desc *order) { return (2 * (size_t)d->offset[fold_levels(d, order)] * sizeof(double) + 255) / 256 * 256; }
 
 }  // namespace
 
@@ -330,12 +340,13 @@ int brick_bwd(const char *who, const dg_grid_desc *d, const dg_order_desc *order
     Boxes boxes{};
     boxes.n_merged = order->n_merged;
     boxes.n_wide = std::min(coarse_levels(d), order->n_merged);
+    boxes.n_fold = fold_levels(d, order);
     for (uint32_t l = 0; l < order->n_merged; ++l) {
         for (int a = 0; a < 3; ++a) boxes.dim[l][a] = order->box[l][a];
         boxes.first[l + 1] = order->box_first[l + 1];
     }
     const size_t lds = (size_t)boxes.first[boxes.n_merged] * 2 * sizeof(double);
-    const uint32_t n_wide_sums = 2 * d->offset[boxes.n_wide];
+    const uint32_t n_wide_sums = 2 * d->offset[boxes.n_fold];
     if (int rc = dg_clear(wide, n_wide_sums * sizeof(double), st)) return rc;
     brick_bwd_kernel<<<(uint32_t)piece_bound(order->total, N), kBrickBlock, lds, st>>>(
         *d, bricks_of(order), boxes, (const uint2 *)pieces, (const float4 *)ordered, (const float4 *)dfeat, largest, dtable, wide);
@@ -381,7 +392,7 @@ int bwd_ordered(const char *who, const dg_grid_desc *desc, const dg_order_desc *
     DG_REQUIRE(dg::aligned(ordered, 16) && dg::aligned(pieces, 8) && dg::aligned(dfeat, 16) && dg::aligned(dtable, 8) && dg::aligned(ws, 256), DG_ERR_ARG,
                "%s: misaligned pointer", who);
     const size_t wide = wide_bytes(desc, order);
-    DG_REQUIRE(ws_bytes >= wide, DG_ERR_WORKSPACE, "%s: workspace %zu bytes cannot hold the %zu of the coarse levels", who, ws_bytes, wide);
+    DG_REQUIRE(ws_bytes >= wide, DG_ERR_WORKSPACE, "%s: workspace %zu bytes cannot hold the %zu of the coarser levels", who, ws_bytes, wide);
     // the rows of the merged levels take the place of those levels' planes: plane l of the others lies where it always does
     if (int rc = dg::brick_bwd(who, desc, order, pieces, ordered, dfeat, largest, N, dtable, (double *)ws, (hipStream_t)stream)) return rc;
     return dg::encode_bwd_binned(who, desc, order->n_merged, u, dfeat, N, dtable, (char *)ws + wide, ws_bytes - wide, counted, (hipStream_t)stream);
@@ -404,7 +415,7 @@ extern "C" int dg_hashgrid_encode_bwd_ordered_count(const dg_grid_desc *desc, co
     DG_REQUIRE(u && ws, DG_ERR_ARG, "%s: null pointer", who);
     DG_REQUIRE(dg::aligned(ws, 256), DG_ERR_ARG, "%s: workspace must be 256-byte aligned", who);
     const size_t wide = wide_bytes(desc, order);
-    DG_REQUIRE(ws_bytes >= wide, DG_ERR_WORKSPACE, "%s: workspace %zu bytes cannot hold the %zu of the coarse levels", who, ws_bytes, wide);
+    DG_REQUIRE(ws_bytes >= wide, DG_ERR_WORKSPACE, "%s: workspace %zu bytes cannot hold the %zu of the coarser levels", who, ws_bytes, wide);
     return dg::encode_bwd_binned_count(who, desc, order->n_merged, u, N, (char *)ws + wide, ws_bytes - wide, (hipStream_t)stream);
 }
 

@@ -210,6 +210,30 @@ def test_bricks_of_a_large_batch(key):
         assert rel_err(have[sl], want[sl]) <= TOL_F16, l
 
 
+def test_many_bricks_to_an_entry():
+    """29 791 bricks on tables of 2^14 entries: some seventy bricks and more add to an entry.  Their sums are added in fp64, so what is
+    left are the roundings of a contribution (two products for its weight, one with the gradient, one of 1 - fraction) and that of the
+    entry: five independent ones of at most 2^-24, sqrt(5 / 3) 2^-24 = 7.7e-8 in 2-norm (with fp32 adds 1.3e-7 to 1.8e-7)."""
+    print("[case] many bricks to an entry", flush=True)
+    growth = B.dg_growth_factor(16, 1024, 16)
+    grid, ref_grid = (f(16, 2, 14, 16, growth, [1.0, 1.0, 1.0]) for f in (B.dg_grid_desc_init, oracle.grid_init))
+    order = B.dg_order_desc_init(grid, 1 << 26)
+    N, M = 200003, order.n_merged
+    assert order.total == 29791 and M >= 8
+    u = di.make_unit_coords(N, seed=38)
+    g = (np.random.default_rng(39).standard_normal((N, 32)) * 1e-3).astype(np.float32)
+    ordered, pieces = torch.zeros(N, 4, device=DEV), torch.zeros(B.dg_order_pieces_words(order, N), dtype=torch.int32, device=DEV)
+    ud, gd = dev(u), dev(_mixed(g, M))
+    B.dg_order_samples(order, ud, N, ordered, pieces, torch.zeros(B.dg_order_workspace_bytes(order) // 4, dtype=torch.int32, device=DEV))
+    dtable = torch.zeros(ref_grid.n_entries, 2, device=DEV)
+    ws = torch.zeros(B.dg_hashgrid_encode_bwd_ordered_workspace_bytes(grid, order, N) // 4 + 64, device=DEV)
+    B.dg_hashgrid_encode_bwd_ordered(grid, order, ordered, pieces, ud, gd, gd.abs().max().reshape(1).view(torch.int32), N, dtable, ws)
+    want, have = oracle.encode_bwd(ref_grid, u, g.astype(np.float64)), host(dtable).astype(np.float64)
+    off = [float(np.linalg.norm(have[a:b] - want[a:b]) / np.linalg.norm(want[a:b])) for a, b in zip(ref_grid.first[:M], ref_grid.first[1:M + 1])]
+    print("[case] 2-norms", ["%.1e" % x for x in off], flush=True)
+    assert max(off) <= (5.0 / 3.0) ** 0.5 * 2.0 ** -24
+
+
 @pytest.mark.parametrize("N,log2_T,n_max", [((1 << 22) + 77, 19, 2048), ((1 << 21) + 5, 22, 8192)])
 def test_ordered_gradient_at_full_size(N, log2_T, n_max):
     """A batch of production size, level by level and entry by entry against the pass in ray order on the same gradient."""
