@@ -10,6 +10,13 @@
 //
 // Operand layouts, images, transposes: mlp_mfma_common.h.
 //
+// What the kernels spend on a tile (13.3 M samples): forward 402 vector instructions of which 131 are transcendental and take two issue
+// slots; the vector units are busy 0.86 of the time, the matrix cores 0.31.  Colour backward: busy 0.62 and 0.42, with little overlap
+// at two wavefronts per SIMD, so it goes by the number of instructions: a compile-time choice of the activation (branches around each
+// of its uses cut the schedule into pieces), a (1 - a) as one multiply-add on halves, rows followed on the scalar unit instead of
+// divided out and images built from loads under way together took it from 1206 to 1050 us (0.65 M samples: 79 -> 65; 0.15 M: 35 -> 26),
+// the forward from 482 to 470 (40 -> 33; 17 -> 16).
+//
 // Backward recomputes the forward, then walks the chain back.  Weight gradients contract over the
 // samples, so they need each (delta, activation) pair with the samples on the k axis; a product with
 // a 0/1 selection matrix on the matrix cores transposes a tile exactly (fp16 values times one,
@@ -37,20 +44,20 @@ constexpr int cC3T = 24, cC2T = 26, cC1T = 34, cD2T = 38, cD1T = 40, cSelT = 44,
 
 __device__ void build_forward_images(__half *lds, const __half *w)
 {
-    build_image(lds + cD1 * 512, w + oWd1, HD, NF, HD, NF, 2, 2, 1, false);
-    build_image(lds + cD2 * 512, w + oWd2, NG, HD, NG, HD, 1, 4, 0, false);
-    build_image(lds + cC1 * 512, w + oWc1, HC, CI, HC, CI, 2, 2, 2, false);
-    build_image(lds + cC2 * 512, w + oWc2, HC, HC, HC, HC, 2, 4, 0, false);
-    build_image(lds + cC3 * 512, w + oWc3, 3, HC, 3, HC, 1, 4, 0, false);
+    build_image<NF, HD, NF, 2, 2, 1, false>(lds + cD1 * 512, w + oWd1);
+    build_image<HD, NG, HD, 1, 4, 0, false>(lds + cD2 * 512, w + oWd2);
+    build_image<CI, HC, CI, 2, 2, 2, false>(lds + cC1 * 512, w + oWc1);
+    build_image<HC, HC, HC, 2, 4, 0, false>(lds + cC2 * 512, w + oWc2);
+    build_image<HC, 3, HC, 1, 4, 0, false>(lds + cC3 * 512, w + oWc3);
 }
 
 __device__ void build_backward_images(__half *lds, const __half *w)
 {
-    build_image(lds + cC3T * 512, w + oWc3, 3, HC, HC, 3, 2, 1, 0, true);
-    build_image(lds + cC2T * 512, w + oWc2, HC, HC, HC, HC, 2, 4, 0, true);
-    build_image(lds + cC1T * 512, w + oWc1, HC, CI, NG, HC, 1, 4, 0, true);     // direction inputs get no gradient
-    build_image(lds + cD2T * 512, w + oWd2, NG, HD, HD, NG, 2, 1, 0, true);
-    build_image(lds + cD1T * 512, w + oWd1, HD, NF, NF, HD, 1, 4, 0, true);
+    build_image<HC, HC, 3, 2, 1, 0, true>(lds + cC3T * 512, w + oWc3);
+    build_image<HC, HC, HC, 2, 4, 0, true>(lds + cC2T * 512, w + oWc2);
+    build_image<CI, NG, HC, 1, 4, 0, true>(lds + cC1T * 512, w + oWc1);     // direction inputs get no gradient
+    build_image<HD, HD, NG, 2, 1, 0, true>(lds + cD2T * 512, w + oWd2);
+    build_image<NF, NF, HD, 1, 4, 0, true>(lds + cD1T * 512, w + oWd1);
     build_selection(lds + cSelT * 512, 0);
     build_selection(lds + cSelN * 512, 1);
 }
@@ -60,9 +67,11 @@ struct Tile {
     float geo0, sigma, raw[3], rgb[3];     // meaningful on lanes with h == 0
 };
 
-// NA: appearance inputs (0, 16 or 48); their weight images start at chunk c_app
-template <int NA>
-__device__ __forceinline__ void forward_tile(const __half *lds, int lane, uint32_t act_c, Tile &t, int c_app = 0)
+// NA: appearance inputs (0, 16 or 48); their weight images start at chunk c_app.  SIG: the colour net's hidden layers are sigmoids
+// (else ReLU); a compile-time choice, because a branch around every activation keeps the scheduler from filling the matrix
+// instructions' latency with it.
+template <int NA, bool SIG>
+__device__ __forceinline__ void forward_tile(const __half *lds, int lane, Tile &t, int c_app = 0)
 {
     f16v acc[2];
     // density layer 1: 32 -> 64, ReLU
@@ -91,7 +100,7 @@ __device__ __forceinline__ void forward_tile(const __half *lds, int lane, uint32
         for (int ks = 0; ks < NA / 16; ++ks) acc[mt] = mma(image(lds, c_app + mt * (NA / 16) + ks, lane), t.xa[ks], acc[mt]);
     }
 #pragma unroll
-    for (int ks = 0; ks < 4; ++ks) t.c1[ks] = act_c ? pack_half<2>(acc[ks >> 1], ks & 1) : pack_half<1>(acc[ks >> 1], ks & 1);
+    for (int ks = 0; ks < 4; ++ks) t.c1[ks] = pack_half<SIG ? 2 : 1>(acc[ks >> 1], ks & 1);
     // colour layer 2: 64 -> 64
 #pragma unroll
     for (int mt = 0; mt < 2; ++mt) {
@@ -100,7 +109,7 @@ __device__ __forceinline__ void forward_tile(const __half *lds, int lane, uint32
         for (int ks = 0; ks < 4; ++ks) acc[mt] = mma(image(lds, cC2 + mt * 4 + ks, lane), t.c1[ks], acc[mt]);
     }
 #pragma unroll
-    for (int ks = 0; ks < 4; ++ks) t.c2[ks] = act_c ? pack_half<2>(acc[ks >> 1], ks & 1) : pack_half<1>(acc[ks >> 1], ks & 1);
+    for (int ks = 0; ks < 4; ++ks) t.c2[ks] = pack_half<SIG ? 2 : 1>(acc[ks >> 1], ks & 1);
     // colour layer 3: 64 -> 3, raw
     f16v out = zero16();
 #pragma unroll
@@ -126,66 +135,68 @@ __device__ __forceinline__ float density_net(const __half *lds, int lane, const 
 
 // Features arrive as level-major planes [16][n_samples] of half2 -- slot j of k-step ks on lane half h is feature
 // 16 ks + 8 h + j, i.e. component j % 2 of level 8 ks + 4 h + j / 2 -- or as rows of 32 halves (ROWS).
+// base: first sample of a tile or segment, the same for the whole wavefront; s: the lane's sample from there.
 template <bool ROWS>
-__device__ __forceinline__ void load_features(const __half *feat, uint64_t n_samples, uint64_t n, int h, h8 x0[2])
+__device__ __forceinline__ void load_features(const __half *feat, uint64_t n_samples, uint64_t base, uint32_t s, int h, h8 x0[2])
 {
     if (ROWS) {
-        const h8 *row = reinterpret_cast<const h8 *>(feat) + 4 * n;
+        const h8 *row = reinterpret_cast<const h8 *>(feat) + 4 * base;
 #pragma unroll
-        for (int ks = 0; ks < 2; ++ks) x0[ks] = row[2 * ks + h];
+        for (int ks = 0; ks < 2; ++ks) x0[ks] = row[4 * s + 2 * ks + h];
     } else {
         typedef uint32_t u4 __attribute__((ext_vector_type(4)));
-        const uint32_t *planes = reinterpret_cast<const uint32_t *>(feat);
+        const uint32_t *planes = reinterpret_cast<const uint32_t *>(feat) + (size_t)(4 * h) * n_samples + s;
 #pragma unroll
         for (int ks = 0; ks < 2; ++ks) {
             u4 bits;
 #pragma unroll
-            for (int q = 0; q < 4; ++q) bits[q] = planes[(size_t)(8 * ks + 4 * h + q) * n_samples + n];
+            for (int q = 0; q < 4; ++q) bits[q] = planes[(size_t)(8 * ks + q) * n_samples + base];
             x0[ks] = __builtin_bit_cast(h8, bits);
         }
     }
 }
 
+// row: of the sample at base, r: the lane's row from there
 template <int NA, bool ROWS>
-__device__ __forceinline__ void load_inputs(const __half *feat, const __half *dir_enc, const __half *app, uint32_t S,
-                                            uint64_t n_samples, uint64_t n, bool valid, int h, Tile &t)
+__device__ __forceinline__ void load_inputs(const __half *feat, const __half *dir_enc, const __half *app, uint64_t n_samples, uint64_t base, uint32_t s,
+                                            uint64_t row, uint32_t r, int h, Tile &t)
 {
-    const h8 zero = {0, 0, 0, 0, 0, 0, 0, 0};
-    if (valid) {
-        load_features<ROWS>(feat, n_samples, n, h, t.x0);
-        t.xc[1] = reinterpret_cast<const h8 *>(dir_enc + (n / S) * ND)[h];
+    load_features<ROWS>(feat, n_samples, base, s, h, t.x0);
+    t.xc[1] = reinterpret_cast<const h8 *>(dir_enc + row * ND)[2 * r + h];
 #pragma unroll
-        for (int ks = 0; ks < NA / 16; ++ks) t.xa[ks] = reinterpret_cast<const h8 *>(app + (n / S) * NA)[2 * ks + h];
-    } else {
-        t.x0[0] = zero; t.x0[1] = zero; t.xc[1] = zero;
-#pragma unroll
-        for (int ks = 0; ks < NA / 16; ++ks) t.xa[ks] = zero;
-    }
+    for (int ks = 0; ks < NA / 16; ++ks) t.xa[ks] = reinterpret_cast<const h8 *>(app + row * NA)[NA / 8 * r + 2 * ks + h];
 }
 
+// Inputs of the walk's tile.  Lanes past the last sample read it again: no branch, and what they compute is not stored and gets no
+// gradient.  (Asked for a tile ahead: no gain at five wavefronts per SIMD forward, spills at two backward.)
 template <int NA, bool ROWS>
+__device__ __forceinline__ void load_tile(const __half *feat, const __half *dir_enc, const __half *app, const TileWalk &walk, int lane, Tile &t)
+{
+    const uint32_t s = min((uint32_t)lane & 31u, walk.count() - 1u);
+    load_inputs<NA, ROWS>(feat, dir_enc, app, walk.n_samples, walk.tile * 32, s, walk.row, walk.local_row(s), lane >> 5, t);
+}
+
+template <int NA, bool ROWS, bool SIG>
 __global__ void __launch_bounds__(kBlock, 4)
 fwd_kernel(const __half *__restrict__ weights, const __half *__restrict__ feat, const __half *__restrict__ dir_enc,
-           const __half *__restrict__ app, uint32_t S, uint64_t n_samples, uint32_t act_c, float *__restrict__ sigma,
-           float *__restrict__ rgb)
+           const __half *__restrict__ app, uint32_t S, uint64_t n_samples, float *__restrict__ sigma, float *__restrict__ rgb)
 {
     __shared__ __attribute__((aligned(16))) __half lds[(kFwdChunks + 2 * (NA / 16)) * 512];
     build_forward_images(lds, weights);
-    if (NA > 0) build_image(lds + kFwdChunks * 512, weights + kTotal, HC, NA, HC, NA, 2, NA / 16, 1, false);
+    if constexpr (NA > 0) build_image<NA, HC, NA, 2, NA / 16, 1, false>(lds + kFwdChunks * 512, weights + kTotal);
     __syncthreads();
     const int lane = threadIdx.x & 63, h = lane >> 5;
-    const uint64_t n_tiles = (n_samples + 31) / 32;
-    const uint64_t wave = (uint64_t)blockIdx.x * kWavesPerBlock + (threadIdx.x >> 6);
-    const uint64_t n_waves = (uint64_t)gridDim.x * kWavesPerBlock;
-    for (uint64_t tile = wave; tile < n_tiles; tile += n_waves) {
-        const uint64_t n = tile * 32 + (lane & 31);
-        const bool valid = n < n_samples;
+    const uint32_t s = lane & 31;
+    for (TileWalk walk(n_samples, S); walk.more(); walk.next()) {
+        const uint64_t base = walk.tile * 32;
+        const bool valid = s < walk.count();
         Tile t;
-        load_inputs<NA, ROWS>(feat, dir_enc, app, S, n_samples, n, valid, h, t);
-        forward_tile<NA>(lds, opaque(lane), act_c, t, kFwdChunks);
+        load_tile<NA, ROWS>(feat, dir_enc, app, walk, lane, t);
+        forward_tile<NA, SIG>(lds, opaque(lane), t, kFwdChunks);
         if (valid && h == 0) {
-            sigma[n] = t.sigma;
-            rgb[3 * n] = t.rgb[0]; rgb[3 * n + 1] = t.rgb[1]; rgb[3 * n + 2] = t.rgb[2];
+            (sigma + base)[s] = t.sigma;
+            float *c = rgb + 3 * base;
+            c[3 * s] = t.rgb[0]; c[3 * s + 1] = t.rgb[1]; c[3 * s + 2] = t.rgb[2];
         }
     }
 }
@@ -202,17 +213,17 @@ density_max_kernel(const __half *__restrict__ weights, const __half *__restrict_
                    uint64_t n_samples, float *__restrict__ density, uint32_t n_cells)
 {
     __shared__ __attribute__((aligned(16))) __half lds[cC1 * 512];
-    build_image(lds + cD1 * 512, weights + oWd1, HD, NF, HD, NF, 2, 2, 1, false);
-    build_image(lds + cD2 * 512, weights + oWd2, NG, HD, NG, HD, 1, 4, 0, false);
+    build_image<NF, HD, NF, 2, 2, 1, false>(lds + cD1 * 512, weights + oWd1);
+    build_image<HD, NG, HD, 1, 4, 0, false>(lds + cD2 * 512, weights + oWd2);
     __syncthreads();
     const int lane = threadIdx.x & 63, h = lane >> 5;
     const uint64_t n_tiles = (n_samples + 31) / 32;
-    const uint64_t wave = (uint64_t)blockIdx.x * kWavesPerBlock + (threadIdx.x >> 6);
+    const uint64_t wave = (uint64_t)blockIdx.x * kWavesPerBlock + (uint32_t)__builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
     const uint64_t n_waves = (uint64_t)gridDim.x * kWavesPerBlock;
     for (uint64_t tile = wave; tile < n_tiles; tile += n_waves) {
         const uint64_t n = tile * 32 + (lane & 31), nn = n < n_samples ? n : n_samples - 1;
         h8 x0[2];
-        load_features<ROWS>(feat, n_samples, nn, h, x0);
+        load_features<ROWS>(feat, n_samples, tile * 32, (uint32_t)(nn - tile * 32), h, x0);
         const uint32_t c = cell[nn * cell_stride];
         const float sigma = __expf(clip15(density_net(lds, opaque(lane), x0)));
         if (h == 0 && n < n_samples && c < n_cells) atomicMax(reinterpret_cast<unsigned int *>(density) + c, __float_as_uint(sigma));
@@ -243,20 +254,20 @@ __device__ __forceinline__ float wave_sum(float v)
     return v;
 }
 
-template <int NA, bool ROWS>
+template <int NA, bool ROWS, bool SIG>
 __global__ void __launch_bounds__(kBlock, 4)
 render_fwd_kernel(const __half *__restrict__ weights, const __half *__restrict__ feat, const __half *__restrict__ dir_enc,
-                  const __half *__restrict__ app, uint32_t S, uint32_t n_seg, uint32_t act_c, const float *__restrict__ delta,
+                  const __half *__restrict__ app, uint32_t S, uint32_t n_seg, const float *__restrict__ delta,
                   const float *__restrict__ t_samples, const uint32_t *__restrict__ seg_ray, const uint32_t *__restrict__ seg_slot,
                   uint32_t k_max, float *__restrict__ Ck, float *__restrict__ Tk, float *__restrict__ Dk)
 {
     __shared__ __attribute__((aligned(16))) __half lds[(kFwdChunks + 2 * (NA / 16)) * 512];
     build_forward_images(lds, weights);
-    if (NA > 0) build_image(lds + kFwdChunks * 512, weights + kTotal, HC, NA, HC, NA, 2, NA / 16, 1, false);
+    if constexpr (NA > 0) build_image<NA, HC, NA, 2, NA / 16, 1, false>(lds + kFwdChunks * 512, weights + kTotal);
     __syncthreads();
     const int lane = threadIdx.x & 63, h = lane >> 5;
     const uint64_t n_samples = (uint64_t)n_seg * S;
-    const uint32_t wave = blockIdx.x * kWavesPerBlock + (threadIdx.x >> 6), n_waves = gridDim.x * kWavesPerBlock;
+    const uint32_t wave = blockIdx.x * kWavesPerBlock + (uint32_t)__builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6)), n_waves = gridDim.x * kWavesPerBlock;
     for (uint32_t seg = wave; seg < n_seg; seg += n_waves) {
         const uint64_t first = (uint64_t)seg * S;
         float sig[2], col[2][3];
@@ -265,8 +276,8 @@ render_fwd_kernel(const __half *__restrict__ weights, const __half *__restrict__
             const uint32_t s = 32u * part + (lane & 31);
             const bool valid = s < S;
             Tile t;
-            load_inputs<NA, ROWS>(feat, dir_enc, app, S, n_samples, first + (valid ? s : 0), valid, h, t);
-            forward_tile<NA>(lds, opaque(lane), act_c, t, kFwdChunks);
+            load_inputs<NA, ROWS>(feat, dir_enc, app, n_samples, first, valid ? s : 0u, seg, 0u, h, t);
+            forward_tile<NA, SIG>(lds, opaque(lane), t, kFwdChunks);
             sig[part] = t.sigma;
             col[part][0] = t.rgb[0]; col[part][1] = t.rgb[1]; col[part][2] = t.rgb[2];
         }
@@ -306,10 +317,10 @@ render_fwd_kernel(const __half *__restrict__ weights, const __half *__restrict__
 //                already scaled and rounded to fp16, in operand order) in the workspace;
 //   density_bwd: recomputes the density hidden layer, back-propagates it from delta_geo, accumulates
 //                dWd1..2 and writes the feature gradient planes.
-template <int NA, bool ROWS>
+template <int NA, bool ROWS, bool SIG>
 __global__ void __launch_bounds__(kBlock, 2)
 colour_bwd_kernel(const __half *__restrict__ weights, const __half *__restrict__ feat, const __half *__restrict__ dir_enc,
-                  const __half *__restrict__ app, uint32_t S, uint64_t n_samples, uint32_t act_c,
+                  const __half *__restrict__ app, uint32_t S, uint64_t n_samples,
                   const float *__restrict__ dsigma, const float *__restrict__ drgb, float loss_scale, h8 *__restrict__ dgeo,
                   float *__restrict__ shares, float *__restrict__ row_delta)
 {
@@ -317,12 +328,9 @@ colour_bwd_kernel(const __half *__restrict__ weights, const __half *__restrict__
     __shared__ float acc3[kWavesPerBlock * 2 * 3 * 32];
     build_forward_images(lds, weights);
     build_backward_images(lds, weights);
-    if (NA > 0) build_image(lds + kAllChunks * 512, weights + kTotal, HC, NA, HC, NA, 2, NA / 16, 1, false);
+    if constexpr (NA > 0) build_image<NA, HC, NA, 2, NA / 16, 1, false>(lds + kAllChunks * 512, weights + kTotal);
     __syncthreads();
     const int lane_fixed = threadIdx.x & 63, h = lane_fixed >> 5;
-    const uint64_t n_tiles = (n_samples + 31) / 32;
-    const uint64_t wave = (uint64_t)blockIdx.x * kWavesPerBlock + (threadIdx.x >> 6);
-    const uint64_t n_waves = (uint64_t)gridDim.x * kWavesPerBlock;
     const h8 zero8 = {0, 0, 0, 0, 0, 0, 0, 0};
 
     f16v gWc2[2][2], gWc1[2];               // [output tile][input tile]
@@ -337,18 +345,20 @@ colour_bwd_kernel(const __half *__restrict__ weights, const __half *__restrict__
         for (int k = 0; k < 6; ++k) gWc3[k * 32 + (lane_fixed & 31)] = 0.0f;
     }
 
-    for (uint64_t tile = wave; tile < n_tiles; tile += n_waves) {
-        const uint64_t n = tile * 32 + (lane_fixed & 31);
-        const bool valid = n < n_samples;
+    const uint32_t s = lane_fixed & 31;
+    for (TileWalk walk(n_samples, S); walk.more(); walk.next()) {
+        const uint64_t base = walk.tile * 32;
+        const bool valid = s < walk.count();
         const int lane = opaque(lane_fixed);
         Tile t;
-        load_inputs<NA, ROWS>(feat, dir_enc, app, S, n_samples, n, valid, h, t);
+        load_tile<NA, ROWS>(feat, dir_enc, app, walk, lane_fixed, t);
         float ds = 0.0f, dc[3] = {0.0f, 0.0f, 0.0f};
         if (valid && h == 0) {                 // issued before the forward so the latency hides behind it
-            ds = dsigma[n];
-            dc[0] = drgb[3 * n]; dc[1] = drgb[3 * n + 1]; dc[2] = drgb[3 * n + 2];
+            const float *c = drgb + 3 * base;
+            ds = (dsigma + base)[s];
+            dc[0] = c[3 * s]; dc[1] = c[3 * s + 1]; dc[2] = c[3 * s + 2];
         }
-        forward_tile<NA>(lds, lane, act_c, t, kAllChunks);
+        forward_tile<NA, SIG>(lds, lane, t, kAllChunks);
         const h8 selT0 = image(lds, cSelT, lane), selT1 = image(lds, cSelT + 1, lane);
 
         // ---- output layer of the colour net
@@ -380,7 +390,7 @@ colour_bwd_kernel(const __half *__restrict__ weights, const __half *__restrict__
         // ---- second hidden layer of the colour net
         h8 dl[4];
 #pragma unroll
-        for (int ks = 0; ks < 4; ++ks) dl[ks] = act_c ? delta_from<2>(g[ks >> 1], ks & 1, t.c2[ks]) : delta_from<1>(g[ks >> 1], ks & 1, t.c2[ks]);
+        for (int ks = 0; ks < 4; ++ks) dl[ks] = delta_from<SIG ? 2 : 1>(g[ks >> 1], ks & 1, t.c2[ks]);
         transpose_tile(dl[0], dl[1], selT0, selT1, td[0]);
         transpose_tile(dl[2], dl[3], selT0, selT1, td[1]);
         transpose_tile(t.c1[0], t.c1[1], selT0, selT1, ta[0]);
@@ -400,7 +410,7 @@ colour_bwd_kernel(const __half *__restrict__ weights, const __half *__restrict__
 
         // ---- first hidden layer of the colour net
 #pragma unroll
-        for (int ks = 0; ks < 4; ++ks) dl[ks] = act_c ? delta_from<2>(g[ks >> 1], ks & 1, t.c1[ks]) : delta_from<1>(g[ks >> 1], ks & 1, t.c1[ks]);
+        for (int ks = 0; ks < 4; ++ks) dl[ks] = delta_from<SIG ? 2 : 1>(g[ks >> 1], ks & 1, t.c1[ks]);
         transpose_tile(dl[0], dl[1], selT0, selT1, td[0]);
         transpose_tile(dl[2], dl[3], selT0, selT1, td[1]);
         transpose_tile(t.xc[0], t.xc[1], selT0, image(lds, cSelN + 1, lane), ta[0]);
@@ -411,31 +421,19 @@ colour_bwd_kernel(const __half *__restrict__ weights, const __half *__restrict__
         if (NA > 0) {
             // per-row sums of delta for the appearance columns: delta^T (features x samples) times the 0/1 matrix
             // "sample s lies in the tile's local row c"; column c of the result is the sum over that row's samples
-            const uint64_t n0 = tile * 32;
-            const uint64_t row0 = n0 / S;                                             // row of the tile's first sample
-            const uint32_t rem0 = (uint32_t)(n0 - row0 * S), c = lane_fixed & 31;
-            // local row of sample s of the tile: rows of 32 or more samples change at most once, at sample `turn`;
-            // shorter rows: (rem0 + s) / S on integers below 64, exact through a float reciprocal
-            const bool wide = S >= 32;
-            const uint32_t turn = S - rem0;
-            const float inv_S = 1.0f / (float)S;
-            auto local_row = [&](uint32_t smp) {
-                return wide ? (smp >= turn ? 1u : 0u) : (uint32_t)((float)(rem0 + smp) * inv_S + 1e-3f);
-            };
-            const uint32_t last = (uint32_t)(n_samples - 1 - n0 < 31 ? n_samples - 1 - n0 : 31);
-            const uint32_t n_local = local_row(last) + 1u;                            // rows with samples in this tile
+            const uint32_t c = s, n_local = walk.local_row(walk.count() - 1u) + 1u;   // rows with samples in this tile
             h8 in_row[2];
 #pragma unroll
             for (int p = 0; p < 2; ++p)
 #pragma unroll
                 for (int j = 0; j < 8; ++j)      // slot j of k-step p holds sample feat_tiled(p, h, j) of the tile, as in td
-                    in_row[p][j] = (_Float16)(local_row((uint32_t)feat_tiled(p, h, j)) == c ? 1.0f : 0.0f);
+                    in_row[p][j] = (_Float16)(walk.local_row((uint32_t)feat_tiled(p, h, j)) == c ? 1.0f : 0.0f);
 #pragma unroll
             for (int ot = 0; ot < 2; ++ot) {
                 f16v sums = mma(td[ot][0], in_row[0], zero16());
                 sums = mma(td[ot][1], in_row[1], sums);
                 if (c < n_local) {
-                    float *dst = row_delta + (row0 + c) * HC + 32 * ot + 4 * h;
+                    float *dst = row_delta + (walk.row + c) * HC + 32 * ot + 4 * h;
 #pragma unroll
                     for (int r = 0; r < 16; ++r) unsafeAtomicAdd(dst + 8 * (r >> 2) + (r & 3), sums[r]);
                 }
@@ -450,7 +448,7 @@ colour_bwd_kernel(const __half *__restrict__ weights, const __half *__restrict__
             const bool pass0 = t.geo0 >= -15.0f && t.geo0 <= 15.0f;
             gx[0] += pass0 ? loss_scale * ds * t.sigma : 0.0f;
         }
-        if (valid) dgeo[2 * n + h] = pack_half<0>(gx, 0);
+        if (valid) (dgeo + 2 * base)[2 * s + h] = pack_half<0>(gx, 0);
     }
 
     static_assert((kTotal - oWc1) * 4 <= kAllChunks * 1024, "the share fits the space of the images");
@@ -490,15 +488,15 @@ density_bwd_kernel(const __half *__restrict__ weights, const __half *__restrict_
     // images: density layer 1 forward (4 chunks), Wd2^T (2), Wd1^T (4), selections (4)
     constexpr int kD1 = 0, kD2T = 4, kD1T = 6, kST = 10, kSN = 12, kChunks = 14;
     __shared__ __attribute__((aligned(16))) __half lds[kChunks * 512];
-    build_image(lds + kD1 * 512, weights + oWd1, HD, NF, HD, NF, 2, 2, 1, false);
-    build_image(lds + kD2T * 512, weights + oWd2, NG, HD, HD, NG, 2, 1, 0, true);
-    build_image(lds + kD1T * 512, weights + oWd1, HD, NF, NF, HD, 1, 4, 0, true);
+    build_image<NF, HD, NF, 2, 2, 1, false>(lds + kD1 * 512, weights + oWd1);
+    build_image<HD, HD, NG, 2, 1, 0, true>(lds + kD2T * 512, weights + oWd2);
+    build_image<NF, NF, HD, 1, 4, 0, true>(lds + kD1T * 512, weights + oWd1);
     build_selection(lds + kST * 512, 0);
     build_selection(lds + kSN * 512, 1);
     __syncthreads();
     const int lane = threadIdx.x & 63, h = lane >> 5;
     const uint64_t n_tiles = (n_samples + 31) / 32;
-    const uint64_t wave = (uint64_t)blockIdx.x * kWavesPerBlock + (threadIdx.x >> 6);
+    const uint64_t wave = (uint64_t)blockIdx.x * kWavesPerBlock + (uint32_t)__builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
     const uint64_t n_waves = (uint64_t)gridDim.x * kWavesPerBlock;
     const float inv_scale = 1.0f / loss_scale;
     const h8 selT0 = image(lds, kST, lane), selT1 = image(lds, kST + 1, lane);
@@ -510,13 +508,21 @@ density_bwd_kernel(const __half *__restrict__ weights, const __half *__restrict_
 #pragma unroll
     for (int a = 0; a < 2; ++a) { gWd2[a] = zero16(); gWd1[a] = zero16(); }
 
+    h8 x_next[2], dg_next;
+    auto load = [&](uint64_t tile) {            // lanes past the last sample read it again; their gradient is set to zero below
+        const uint64_t base = tile * 32, left = n_samples - base;
+        const uint32_t s = min((uint32_t)lane & 31u, left < 32 ? (uint32_t)left - 1u : 31u);
+        load_features<ROWS>(feat, n_samples, base, s, h, x_next);
+        dg_next = (dgeo + 2 * base)[2 * s + h];
+    };
+    if (wave < n_tiles) load(wave);
     for (uint64_t tile = wave; tile < n_tiles; tile += n_waves) {
         const uint64_t n = tile * 32 + (lane & 31);
         const bool valid = n < n_samples;
         Tile t;
-        t.x0[0] = zero8; t.x0[1] = zero8;
-        if (valid) load_features<ROWS>(feat, n_samples, n, h, t.x0);
-        const h8 dg = valid ? dgeo[2 * n + h] : zero8;
+        t.x0[0] = x_next[0]; t.x0[1] = x_next[1];
+        const h8 dg = valid ? dg_next : zero8;
+        if (tile + n_waves < n_tiles) load(tile + n_waves);         // a tile ahead
         f16v acc[2];
 #pragma unroll
         for (int mt = 0; mt < 2; ++mt) {
@@ -656,6 +662,9 @@ zero_kernel(float *__restrict__ p, uint64_t n)
     for (uint64_t i = (uint64_t)blockIdx.x * kBlock + threadIdx.x; i < n; i += (uint64_t)gridDim.x * kBlock) p[i] = 0.0f;
 }
 
+// Forward: five workgroups per compute unit, all resident at once.  0.65 M samples: 33 us against 36 with 2048 workgroups, each of which
+// builds the weight images; 13.3 M samples: the same within 1 %.
+constexpr uint32_t kGridForward = 1280;
 constexpr uint32_t kGridColour = 512;      // persistent workgroups: two per compute unit of MI355X
 constexpr uint32_t kGridDensity = 512;     // the lighter kernel fits two workgroups per compute unit
 
@@ -674,13 +683,17 @@ size_t mlp_mfma_workspace_bytes(uint64_t N, uint32_t n_app, uint32_t S)
 
 size_t mlp_mfma_weight_count(uint32_t n_app) { return (size_t)dg_mlp_mfma::kTotal + (size_t)dg_mlp_mfma::HC * n_app; }
 
-// calls launch(appearance inputs, rows) with both as compile-time constants
+// calls launch(appearance inputs, rows, sigmoid) with all three as compile-time constants
 template <class F>
-static void for_shape(uint32_t n_app, bool rows, F launch)
+static void for_shape(uint32_t n_app, bool rows, uint32_t act_c, F launch)
 {
+    auto with_act = [&](auto na, auto in_rows) {
+        if (act_c) launch(na, in_rows, std::true_type{});
+        else launch(na, in_rows, std::false_type{});
+    };
     auto with_rows = [&](auto na) {
-        if (rows) launch(na, std::true_type{});
-        else launch(na, std::false_type{});
+        if (rows) with_act(na, std::true_type{});
+        else with_act(na, std::false_type{});
     };
     if (n_app == 0) with_rows(std::integral_constant<int, 0>{});
     else if (n_app == 16) with_rows(std::integral_constant<int, 16>{});
@@ -692,10 +705,10 @@ void mlp_mfma_fwd(const void *weights, const void *feat, bool rows, const void *
 {
     using namespace dg_mlp_mfma;
     const uint64_t tiles = (N + 31) / 32, blocks_needed = (tiles + kWavesPerBlock - 1) / kWavesPerBlock;
-    const uint32_t grid = (uint32_t)(blocks_needed < 2048 ? blocks_needed : 2048);
-    for_shape(n_app, rows, [&](auto na, auto in_rows) {
-        fwd_kernel<decltype(na)::value, decltype(in_rows)::value><<<grid, kBlock, 0, st>>>(
-            (const __half *)weights, (const __half *)feat, (const __half *)dir_enc, (const __half *)app, S, N, act_c, sigma, rgb);
+    const uint32_t grid = (uint32_t)(blocks_needed < kGridForward ? blocks_needed : kGridForward);
+    for_shape(n_app, rows, act_c, [&](auto na, auto in_rows, auto sig) {
+        fwd_kernel<decltype(na)::value, decltype(in_rows)::value, decltype(sig)::value><<<grid, kBlock, 0, st>>>(
+            (const __half *)weights, (const __half *)feat, (const __half *)dir_enc, (const __half *)app, S, N, sigma, rgb);
     });
 }
 
@@ -717,9 +730,9 @@ void mlp_mfma_render(const void *weights, const void *feat, bool rows, const voi
     using namespace dg_mlp_mfma;
     const uint32_t blocks_needed = (n_seg + kWavesPerBlock - 1) / kWavesPerBlock;
     const uint32_t grid = blocks_needed < 2048 ? blocks_needed : 2048;
-    for_shape(n_app, rows, [&](auto na, auto in_rows) {
-        render_fwd_kernel<decltype(na)::value, decltype(in_rows)::value><<<grid, kBlock, 0, st>>>(
-            (const __half *)weights, (const __half *)feat, (const __half *)dir_enc, (const __half *)app, S, n_seg, act_c, delta, t, seg_ray,
+    for_shape(n_app, rows, act_c, [&](auto na, auto in_rows, auto sig) {
+        render_fwd_kernel<decltype(na)::value, decltype(in_rows)::value, decltype(sig)::value><<<grid, kBlock, 0, st>>>(
+            (const __half *)weights, (const __half *)feat, (const __half *)dir_enc, (const __half *)app, S, n_seg, delta, t, seg_ray,
             seg_slot, k_max, Ck, Tk, Dk);
     });
 }
@@ -744,8 +757,8 @@ void mlp_mfma_bwd(const void *weights, const void *feat, bool rows, uint32_t n_m
         const uint64_t n = n_rows * HC, want = (n + kBlock - 1) / kBlock;
         zero_kernel<<<(uint32_t)(want < 4096 ? want : 4096), kBlock, 0, st>>>(row_delta, n);
     }
-    for_shape(n_app, rows, [&](auto na, auto in_rows) {
-        colour_bwd_kernel<decltype(na)::value, decltype(in_rows)::value><<<grid_c, kBlock, 0, st>>>(w, f, dr, ap, S, N, act_c, dsigma, drgb, loss_scale, dgeo,
+    for_shape(n_app, rows, act_c, [&](auto na, auto in_rows, auto sig) {
+        colour_bwd_kernel<decltype(na)::value, decltype(in_rows)::value, decltype(sig)::value><<<grid_c, kBlock, 0, st>>>(w, f, dr, ap, S, N, dsigma, drgb, loss_scale, dgeo,
                                                                                                    colour_shares, row_delta);
     });
     if (rows) density_bwd_kernel<true><<<grid_d, kBlock, 0, st>>>(w, f, N, dgeo, loss_scale, n_merged, dfeat, largest, density_shares);

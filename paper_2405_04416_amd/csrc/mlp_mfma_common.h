@@ -28,28 +28,41 @@ __device__ __forceinline__ int feat_of(int kind, int ks, int h, int j)
 }
 
 // A-operand image of a weight matrix W[n_out][n_in] (row-major): rows = outputs (transpose == false)
-// or rows = inputs (transpose == true, for the data gradient)
-__device__ void build_image(__half *img, const __half *W, int n_out, int n_in, int rows_real, int k_real,
-                            int n_mt, int n_ks, int kind, bool transpose)
+// or rows = inputs (transpose == true, for the data gradient).  A thread makes whole operands of 8 halves, whose loads are under way
+// together: the images are built once per workgroup, and with few tiles per workgroup the kernels wait for little else.
+template <int N_IN, int ROWS_REAL, int K_REAL, int N_MT, int N_KS, int KIND, bool TRANSPOSE>
+__device__ __forceinline__ void build_image(__half *img, const __half *__restrict__ W)
 {
-    for (int idx = threadIdx.x; idx < n_mt * n_ks * 512; idx += kBlock) {
-        const int j = idx & 7, lane = (idx >> 3) & 63, chunk = idx >> 9;
-        const int ks = chunk % n_ks, mt = chunk / n_ks;
-        const int row = 32 * mt + (lane & 31), k = feat_of(kind, ks, lane >> 5, j);
-        __half v = __float2half(0.0f);
-        if (row < rows_real && k < k_real) v = transpose ? W[k * n_in + row] : W[row * n_in + k];
-        img[idx] = v;
+#pragma unroll
+    for (int i = 0; i < (N_MT * N_KS * 64 + kBlock - 1) / kBlock; ++i) {
+        const int slot = i * kBlock + threadIdx.x;
+        if (N_MT * N_KS * 64 % kBlock != 0 && slot >= N_MT * N_KS * 64) break;
+        const int lane = slot & 63, chunk = slot >> 6, ks = chunk % N_KS, mt = chunk / N_KS;
+        const int row = 32 * mt + (lane & 31);
+        const _Float16 *w = reinterpret_cast<const _Float16 *>(W);
+        h8 v;
+#pragma unroll
+        for (int j = 0; j < 8; ++j) {
+            const int k = feat_of(KIND, ks, lane >> 5, j);
+            const bool real = (ROWS_REAL >= 32 * N_MT || row < ROWS_REAL) && (K_REAL >= 16 * N_KS || k < K_REAL);
+            v[j] = real ? (TRANSPOSE ? w[k * N_IN + row] : w[row * N_IN + k]) : (_Float16)0.0f;
+        }
+        reinterpret_cast<h8 *>(img)[slot] = v;
     }
-    (void)n_out;
 }
 
-__device__ void build_selection(__half *img, int kind)
+__device__ __forceinline__ void build_selection(__half *img, int kind)
 {
-    for (int idx = threadIdx.x; idx < 2 * 512; idx += kBlock) {
-        const int j = idx & 7, lane = (idx >> 3) & 63, p = idx >> 9;
+    const int slot = threadIdx.x;
+    if (slot >= 2 * 64) return;
+    const int lane = slot & 63, p = slot >> 6;
+    h8 v;
+#pragma unroll
+    for (int j = 0; j < 8; ++j) {
         const int f = (kind == 0 ? feat_tiled(p, lane >> 5, j) : feat_natural(p, lane >> 5, j)) & 31;
-        img[idx] = __float2half(f == (lane & 31) ? 1.0f : 0.0f);
+        v[j] = (_Float16)(f == (lane & 31) ? 1.0f : 0.0f);
     }
+    reinterpret_cast<h8 *>(img)[slot] = v;
 }
 
 __device__ __forceinline__ h8 image(const __half *lds, int chunk, int lane)
@@ -107,6 +120,8 @@ __device__ __forceinline__ h8 pack_half(const f16v &c, int p)
     }
     // ReLU after the rounding gives the same values as before it (rounding is monotone and keeps 0) and works on pairs
     if (ACT == 1) out = relu_pairs(out);
+    // the packed halves are what later uses read: without this the compiler rounds every value a second time, unpacked
+    if (ACT >= 2) asm("" : "+v"(out));
     return out;
 }
 
@@ -132,12 +147,22 @@ __device__ __forceinline__ void transpose_half_tile(h8 x0, h8 sel0, h8 out[2])
 template <int ACT>   // 1 ReLU, 2 sigmoid
 __device__ __forceinline__ h8 delta_from(const f16v &g, int p, h8 a)
 {
+    typedef float f2 __attribute__((ext_vector_type(2)));
+    typedef _Float16 h2 __attribute__((ext_vector_type(2)));
     h8 out;
 #pragma unroll
-    for (int j = 0; j < 8; ++j) {
-        const float av = (float)a[j];
-        const float d = ACT == 2 ? av * (1.0f - av) : (av > 0.0f ? 1.0f : 0.0f);
-        out[j] = (_Float16)(g[8 * p + j] * d);
+    for (int j = 0; j < 8; j += 2) {
+        f2 v;
+#pragma unroll
+        for (int k = 0; k < 2; ++k) {
+            const float av = (float)a[j + k];
+            // a (1 - a) as one multiply-add on the halves: 1 - a is exact in fp32 for all but the smallest a, so this rounds the
+            // same value once
+            v[k] = g[8 * p + j + k] * (ACT == 2 ? __builtin_fmaf(-av, av, av) : (av > 0.0f ? 1.0f : 0.0f));
+        }
+        const h2 r = __builtin_convertvector(v, h2);
+        out[j] = r[0];
+        out[j + 1] = r[1];
     }
     return out;
 }
@@ -203,6 +228,42 @@ fold_shares_kernel(const float *__restrict__ first_shares, uint32_t n_a, uint32_
         dW[e] += sum * inv_scale;
     }
 }
+
+// Tiles of 32 samples that a wavefront takes, w, w + n_waves, ..., and where the tile lies in the rows of S samples each.  All of it is
+// the same for the whole wavefront and lives in scalar registers: rows are followed instead of divided out, and addresses are a
+// scalar base plus a lane's constant offset.
+struct TileWalk {
+    uint64_t tile, n_tiles, n_waves, n_samples, row, rem, row_step, rem_step;       // row, rem: row of the tile's first sample, and its place in that row
+    uint32_t S;
+
+    __device__ __forceinline__ TileWalk(uint64_t N, uint32_t S_) : n_samples(N), S(S_)
+    {
+        n_tiles = (N + 31) / 32;
+        n_waves = (uint64_t)gridDim.x * kWavesPerBlock;
+        tile = (uint64_t)blockIdx.x * kWavesPerBlock + (uint32_t)__builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+        row = tile * 32 / S;
+        rem = tile * 32 - row * S;
+        row_step = n_waves * 32 / S;
+        rem_step = n_waves * 32 - row_step * S;
+    }
+    __device__ __forceinline__ bool more() const { return tile < n_tiles; }
+    __device__ __forceinline__ void next()
+    {
+        tile += n_waves;
+        row += row_step;
+        rem += rem_step;
+        if (rem >= S) { rem -= S; ++row; }
+    }
+    // samples of the tile
+    __device__ __forceinline__ uint32_t count() const { return n_samples - tile * 32 < 32 ? (uint32_t)(n_samples - tile * 32) : 32u; }
+    // row of sample s of the tile (s < 32), counted from `row`: rows of 32 or more samples change at most once; shorter ones:
+    // integers below 63 divided through a float reciprocal, which the slack of 1e-3 makes exact
+    __device__ __forceinline__ uint32_t local_row(uint32_t s) const
+    {
+        if (S >= 32) return s >= S - rem ? 1u : 0u;
+        return (uint32_t)((float)((uint32_t)rem + s) * (1.0f / (float)S) + 1e-3f);
+    }
+};
 
 inline size_t align256(size_t x) { return (x + 255) / 256 * 256; }
 

@@ -19,18 +19,18 @@ constexpr int iC3T = 7, iC1T = 8, iD2T = 10, iD1T = 11, iSelT = 13, iSelN = 15, 
 
 __device__ void build_small_forward(__half *lds, const __half *w)
 {
-    build_image(lds + iD1 * 512, w + pWd1, sHD, sNF, sHD, sNF, 1, 1, 1, false);
-    build_image(lds + iD2 * 512, w + pWd2, sNG, sHD, sNG, sHD, 1, 2, 0, false);
-    build_image(lds + iC1 * 512, w + pWc1, sHC, sCI, sHC, sCI, 1, 2, 2, false);
-    build_image(lds + iC3 * 512, w + pWc3, 3, sHC, 3, sHC, 1, 2, 0, false);
+    build_image<sNF, sHD, sNF, 1, 1, 1, false>(lds + iD1 * 512, w + pWd1);
+    build_image<sHD, sNG, sHD, 1, 2, 0, false>(lds + iD2 * 512, w + pWd2);
+    build_image<sCI, sHC, sCI, 1, 2, 2, false>(lds + iC1 * 512, w + pWc1);
+    build_image<sHC, 3, sHC, 1, 2, 0, false>(lds + iC3 * 512, w + pWc3);
 }
 
 __device__ void build_small_backward(__half *lds, const __half *w)
 {
-    build_image(lds + iC3T * 512, w + pWc3, 3, sHC, sHC, 3, 1, 1, 0, true);
-    build_image(lds + iC1T * 512, w + pWc1, sHC, sCI, sNG, sHC, 1, 2, 0, true);        // direction inputs get no gradient
-    build_image(lds + iD2T * 512, w + pWd2, sNG, sHD, sHD, sNG, 1, 1, 0, true);
-    build_image(lds + iD1T * 512, w + pWd1, sHD, sNF, sNF, sHD, 1, 2, 0, true);
+    build_image<sHC, sHC, 3, 1, 1, 0, true>(lds + iC3T * 512, w + pWc3);
+    build_image<sCI, sNG, sHC, 1, 2, 0, true>(lds + iC1T * 512, w + pWc1);        // direction inputs get no gradient
+    build_image<sHD, sHD, sNG, 1, 1, 0, true>(lds + iD2T * 512, w + pWd2);
+    build_image<sNF, sNF, sHD, 1, 2, 0, true>(lds + iD1T * 512, w + pWd1);
     build_selection(lds + iSelT * 512, 0);
     build_selection(lds + iSelN * 512, 1);
 }
