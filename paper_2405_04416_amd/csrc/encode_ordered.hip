@@ -4,6 +4,7 @@
 #include "order_common.h"
 #include <algorithm>
 #include <mutex>
+#include <type_traits>
 
 namespace {
 
@@ -83,20 +84,28 @@ encode_fwd_ordered_kernel(dg_grid_desc g, const float2 *__restrict__ table, cons
 // with an fp32 add per brick.  Against 64-bit sums (33.5 M samples, 25200 bricks, 2-norm of levels 0 / 3 / 7): ray order 2.4e-7 / 2.0e-7 /
 // 3.3e-7, this 2.5e-8 / 2.5e-8 / 4.2e-8; level 0 in fixed point with fp32 adds 2.6e-7 (13.3 M samples), and nothing was left there of
 // gradients below 2^-38 of the largest.
-// The fp64 adds take 4 % of this kernel's time (13.3 M samples, T = 2^19: 1.59 -> 1.65 ms), clearing and folding `wide` some 12 us.
+// Clearing and folding `wide` takes some 12 us.
 // A value v becomes round(v * 2^k): the add of 1.5 * 2^52 in fp64 leaves it in the low mantissa bits, in two's complement.  k is
 // such that the magnitudes of a piece (at most 2^12 samples) sum to less than 2^50; adding the doubles' bit patterns as
 // integers adds those low bits, what happens above bit 50 is dropped when the sum is read.  (Integer adds are the fastest LDS
 // atomics: random addresses 3.6 T adds/s against 1.95 in fp64.)
-// A lane takes up to kRun consecutive samples and keeps the eight corner sums of the cell it is in in registers; only when
-// the cell changes do they go to LDS.  What the lanes hold at the end is first summed over runs of lanes in the same cell.
-// 33.5 M samples, T = 2^24, levels 0..9: 2.95 ms (3.35 with fp64 sums), of which the gradient rows (one or two random lines per
-// sample) take 1.0, the LDS adds 0.6, the sums themselves 1.2; the same levels through the coarse prefix and the bins took
-// 8 ms.  13.3 M samples, T = 2^19, levels 0..11: 1.55 ms.  Two workgroups per compute unit (512 threads, at most 80 KB of sums) and two
-// samples per lane beat four samples per lane (4.3 ms) and one workgroup of 1024 (4.3 ms).
+// A lane takes two levels and a run of consecutive samples: the eight corner sums of the cell that the run is in stay in registers and
+// go to LDS when it leaves the cell.  Neighbouring lanes take the same samples at the neighbouring levels, so that what they read of
+// a sample's row of the gradient lies side by side and costs the vector cache one or two look-ups, not one per lane.  Two or three of
+// the eight wavefronts share the lower half of the levels, whose runs seldom leave a cell, the others the upper half.
+// What a level needs is worked out once per workgroup and kept in LDS; the write-out takes 25 vector instructions per 64 sums.
+// 13.3 M samples, T = 2^19, levels 0..11: 1.23 ms (vector units busy 0.64, LDS 0.67); 33.5 M, T = 2^24, levels 0..9: 2.15 ms, of which the
+// rows, some 1.6 random lines each, take 0.9 at the rate of the fabric.  Measured on the way:
+// - every wavefront at all levels of an eighth of the samples, two samples per lane at a time: 1.66 and 3.01 ms (the sums over lanes
+//   and the adds to LDS come every other sample, and every level is set up eight times for the write-out);
+// - a wavefront per pair of levels, every lane at a row of its own: 1.27 and 2.95 ms, of which the loads alone 0.94 and 2.3;
+// - as it stands without the sums over lanes at the end: 1.28 and 2.43 ms (adds to one address take turns);
+// - one and two wavefronts at the lower half: 1.46 and 3.10 ms, three and four: 1.30 and 2.46 ms;
+// - 80 registers for six wavefronts per SIMD: 2.4 and 4.9 ms (spills).
 struct Boxes { uint32_t n_merged, n_wide, n_fold, dim[kMaxMerged][3], first[kMaxMerged + 1]; };
 
-constexpr int kBrickBlock = 512, kRun = 2;
+constexpr int kBrickWaves = 8;
+static_assert(kMaxMerged <= 12, "at most three pairs of levels to a wavefront");
 
 // First cell of brick i's box along one axis: a hair (kBoxSlack of a cell) below the brick's edge.  A sample of brick i has
 // i <= u * n < i + 1 in fp32, so its cell, floor(u * scale) in fp32, differs from what the exact edges give by less than three
@@ -109,16 +118,31 @@ __device__ __forceinline__ uint32_t box_low(const Bricks &b, uint32_t i, int axi
     return edge > 0.0f ? (uint32_t)edge : 0u;
 }
 
-__device__ __forceinline__ uint32_t lane_value(uint32_t v, uint32_t lane) { return (uint32_t)__builtin_amdgcn_readlane((int)v, (int)lane); }
-__device__ __forceinline__ float lane_value(float v, uint32_t lane) { return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), (int)lane)); }
-
-// What the sums of a level need, held by lane `level` of every wavefront: fetched with register moves, so that the level
-// loop has no scalar loads, whose wait would also wait for the LDS adds under way.
-struct LevelLane {
-    float scale[3], last[3];                 // last: the last cell
+// What the sums of a level need, worked out once per workgroup.
+struct LevelBox {
+    float scale[3];
+    uint32_t first;                          // first vertex of the box among the sums
+    float last[3];                           // the last cell
+    uint32_t last_slot;                      // last slot whose eight corners lie in the box
     float nx, nxy, origin;                   // strides of the box; slot = x + nx y + nxy z - origin (all exact: below 2^24)
-    uint32_t first, last_slot;               // first vertex of the box among the sums; last slot whose eight corners lie in it
+    uint32_t wide;
+    uint32_t low[3], count;                  // first cell of the box; its vertices
+    float per_nx, per_nxy;                   // reciprocals of the strides
+    uint32_t unused[2];
 };
+
+// clamp_unit and locate_axis_float in one instruction per clamp: the middle of three values, which takes NaN for the smallest
+__device__ __forceinline__ float unit(float c) { return __builtin_amdgcn_fmed3f(c, 0.0f, 1.0f); }
+__device__ __forceinline__ void locate_unit(float c, float scale, float last, float &cell, float &frac)
+{
+#pragma clang fp contract(off)
+    const float pos = c * scale;
+    cell = __builtin_amdgcn_fmed3f(floorf(pos), 0.0f, last);
+    frac = pos - cell;
+}
+
+__device__ __forceinline__ uint32_t uniform(uint32_t v) { return (uint32_t)__builtin_amdgcn_readfirstlane((int)v); }
+__device__ __forceinline__ float uniform(float v) { return __int_as_float(__builtin_amdgcn_readfirstlane(__float_as_int(v))); }
 
 __device__ __forceinline__ void add_fixed(unsigned long long *slot, float v, double to_fixed)
 {
@@ -132,7 +156,15 @@ __device__ __forceinline__ void add_wide(unsigned long long *slot, float v)
     __hip_atomic_fetch_add(reinterpret_cast<double *>(slot), (double)v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
 }
 
-// the eight corner sums of the cell whose corner 0 is vertex d of the box; `wide` is the same for all lanes
+// the whole number, less than 2^50 in magnitude, that the low 51 bits of a sum of doubles' bit patterns hold in two's complement
+__device__ __forceinline__ double from_low_bits(unsigned long long held)
+{
+    // shifted up by 2^50 the number is the low mantissa bits of a double from 2^52 on; the upper bits of `held` go
+    const uint32_t high = (((uint32_t)(held >> 32) + (1u << 18)) & ((1u << 19) - 1u)) | 0x43300000u;
+    return __longlong_as_double((long long)((unsigned long long)high << 32 | (uint32_t)held)) - 0x1.4p52;
+}
+
+// the eight corner sums of the cell whose corner 0 is vertex d of the box
 __device__ __forceinline__ void add_to_box(unsigned long long *d, bool wide, double to_fixed, uint32_t nx, uint32_t nxy, uint32_t plane, const float (&vx)[8],
                                            const float (&vy)[8])
 {
@@ -153,23 +185,76 @@ __device__ __forceinline__ void add_to_box(unsigned long long *d, bool wide, dou
     }
 }
 
-__global__ void __launch_bounds__(kBrickBlock, 4)       // two workgroups per compute unit: four wavefronts per SIMD, 128 registers
+// Adds the sums that lanes hold at the end of their runs; lanes STRIDE apart are at the same levels.  A segmented sum along those lanes
+// within each row of 16 (a run of lanes in the same cell starts where `head` is set), then its last lane adds.
+template <int STRIDE, int STEP>
+__device__ __forceinline__ void row_step(float (&vx)[8], float (&vy)[8], int &f)
+{
+    if constexpr (STRIDE * STEP < 16) seg_step<0x110 + STRIDE * STEP, 0xF>(vx, vy, f);
+}
+
+template <int STRIDE>
+__device__ __forceinline__ void finish_runs(unsigned long long *sums, const LevelBox (&box)[2], const uint32_t (&slot)[2], float (&vx)[2][8], float (&vy)[2][8],
+                                            bool live, int lane, double to_fixed, uint32_t plane)
+{
+    static_assert(STRIDE <= 3, "steps of 1, 2, 4 and 8 runs cover a row");
+#pragma unroll
+    for (int which = 0; which < 2; ++which) {
+        const uint32_t mine = live ? slot[which] : ~0u;               // lanes without samples are runs of their own
+        const uint32_t before = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)mine, 0x110 + STRIDE, 0xF, 0xF, true);
+        const int head = (lane & 15) < STRIDE || before != mine ? 1 : 0;
+        const int next = __builtin_amdgcn_update_dpp(1, head, 0x100 + STRIDE, 0xF, 0xF, false);        // of the lane STRIDE above; 1 past the row's end
+        int f = head;
+        row_step<STRIDE, 1>(vx[which], vy[which], f);
+        row_step<STRIDE, 2>(vx[which], vy[which], f);
+        row_step<STRIDE, 4>(vx[which], vy[which], f);
+        row_step<STRIDE, 8>(vx[which], vy[which], f);
+        if (live && next) {
+            const LevelBox &v = box[which];
+            add_to_box(sums + v.first + slot[which], v.wide, to_fixed, (uint32_t)v.nx, (uint32_t)v.nxy, plane, vx[which], vy[which]);
+        }
+    }
+}
+
+__global__ void __launch_bounds__(kBrickWaves * 64, 4)       // two workgroups per compute unit: four wavefronts per SIMD, 128 registers
 brick_bwd_kernel(dg_grid_desc g, Bricks b, Boxes boxes, const uint2 *__restrict__ pieces, const float4 *__restrict__ ordered,
                  const float4 *__restrict__ dfeat, const uint32_t *__restrict__ largest, float *__restrict__ dtable, double *__restrict__ wide_table)
 {
-    extern __shared__ unsigned long long sums[];
+    extern __shared__ __attribute__((aligned(16))) unsigned long long sums[];
+    __shared__ LevelBox levels[kMaxMerged];
     if (blockIdx.x >= pieces[0].x) return;
     const uint2 piece = pieces[1 + blockIdx.x];
     const uint32_t begin = piece.y, n = pieces[2 + blockIdx.x].y - begin;
     const uint32_t n_vertices = boxes.first[boxes.n_merged];
-    for (uint32_t i = threadIdx.x; i < 2 * n_vertices; i += kBrickBlock) sums[i] = 0ull;
     const uint32_t brick[3] = {piece.x % b.n[0], piece.x / b.n[0] % b.n[1], piece.x / (b.n[0] * b.n[1])};
+    if (threadIdx.x < boxes.n_merged) {
+        const uint32_t l = threadIdx.x, nx = boxes.dim[l][0], nxy = nx * boxes.dim[l][1];
+        LevelBox v;
+#pragma unroll
+        for (int a = 0; a < 3; ++a) {
+            v.scale[a] = g.scale[l][a];
+            v.last[a] = (float)(g.res[l][a] - 1u);
+            v.low[a] = box_low(b, brick[a], a, v.scale[a]);
+        }
+        v.first = boxes.first[l];
+        v.count = boxes.first[l + 1] - v.first;
+        v.last_slot = v.count - 2u - nx - nxy;
+        v.nx = (float)nx;
+        v.nxy = (float)nxy;
+        v.origin = (float)(v.low[0] + nx * v.low[1] + nxy * v.low[2]);
+        v.wide = l < boxes.n_wide;
+        v.per_nx = 1.0f / v.nx;
+        v.per_nxy = 1.0f / v.nxy;
+        levels[l] = v;
+    }
+    uint4 *const clear = reinterpret_cast<uint4 *>(sums);
+    for (uint32_t i = threadIdx.x; i < n_vertices; i += blockDim.x) clear[i] = make_uint4(0u, 0u, 0u, 0u);
     const uint32_t mask = (1u << g.log2_T) - 1u;
     const int lane = threadIdx.x % dg::kWave;
     const uint32_t pairs = boxes.n_merged / 2;
     const uint32_t top = *largest >> 23;                             // biased exponent (0: no smaller k needed)
     if (top == 255u) {      // not finite: no scale fits, the gradient is marked instead
-        for (uint32_t l = threadIdx.x; l < boxes.n_merged; l += kBrickBlock) {
+        for (uint32_t l = threadIdx.x; l < boxes.n_merged; l += blockDim.x) {
             const LevelGeom lv = level_of(g, l);
             const uint32_t e = vertex_entry(lv, mask, box_low(b, brick[0], 0, lv.scale[0]), box_low(b, brick[1], 1, lv.scale[1]), box_low(b, brick[2], 2, lv.scale[2]));
             dtable[2 * ((size_t)lv.offset + e)] = __uint_as_float(0x7fc00000u);
@@ -179,121 +264,107 @@ brick_bwd_kernel(dg_grid_desc g, Bricks b, Boxes boxes, const uint2 *__restrict_
     static_assert(kPiece <= 1u << 12, "2^12 samples of the largest magnitude sum to less than 2^50 units");
     const int k_scale = 50 - 12 - 1 - ((int)(top ? top : 1u) - 127);
     const double to_fixed = __longlong_as_double((long long)(1023 + k_scale) << 52), from_fixed = __longlong_as_double((long long)(1023 - k_scale) << 52);
-    LevelLane mine;
-    {
-        const uint32_t l = min((uint32_t)lane, boxes.n_merged - 1u);
-#pragma unroll
-        for (int a = 0; a < 3; ++a) {
-            mine.scale[a] = g.scale[l][a];
-            mine.last[a] = (float)(g.res[l][a] - 1u);
-        }
-        const uint32_t nx = boxes.dim[l][0], nxy = nx * boxes.dim[l][1];
-        mine.nx = (float)nx;
-        mine.nxy = (float)nxy;
-        mine.origin = (float)(box_low(b, brick[0], 0, mine.scale[0]) + nx * box_low(b, brick[1], 1, mine.scale[1]) + nxy * box_low(b, brick[2], 2, mine.scale[2]));
-        mine.first = boxes.first[l];
-        mine.last_slot = boxes.first[l + 1] - boxes.first[l] - 2u - nx - nxy;
-    }
     __syncthreads();
-    for (uint32_t base = 0; base < n;) {
-        const uint32_t run = min((uint32_t)kRun, (n - base + kBrickBlock - 1u) / kBrickBlock);      // samples per lane
-        const uint32_t i0 = base + threadIdx.x * run;
-        base += run * kBrickBlock;
-        if (i0 - lane * run >= n) break;                              // the whole wavefront is past the end
-        float uu[kRun][3];
-        float4 grad[kRun][kMaxMerged / 2];
+    {
+        const char *const list = reinterpret_cast<const char *>(ordered + begin);
+        const uint32_t wave = (uint32_t)__builtin_amdgcn_readfirstlane((int)(threadIdx.x / dg::kWave));
+        const uint32_t lower = pairs / 2, lower_waves = lower == 0u ? 0u : lower < pairs - lower ? 2u : 3u;
+        const bool is_lower = wave < lower_waves;
+        const uint32_t here = is_lower ? lower : pairs - lower, per_wave = dg::kWave / here;            // pairs of levels, runs per wavefront
+        const uint32_t runs = (is_lower ? lower_waves : kBrickWaves - lower_waves) * per_wave;
+        const uint32_t in_wave = lane / here, q = (is_lower ? 0u : lower) + lane % here;
+        const uint32_t run = (n + runs - 1u) / runs;                                                    // samples per lane
+        // lanes that are left over start past the end
+        const uint32_t i0 = in_wave < per_wave ? ((is_lower ? wave : wave - lower_waves) * per_wave + in_wave) * run : n;
+        const LevelBox box[2] = {levels[2 * q], levels[2 * q + 1]};
+        float vx[2][8], vy[2][8];
+        uint32_t slot[2] = {0u, 0u};                                  // of the cells whose sums vx, vy are
 #pragma unroll
-        for (int k = 0; k < kRun; ++k)
-            if ((uint32_t)k < run) {
-                const float4 s = ordered[begin + min(i0 + k, n - 1u)];
-                uu[k][0] = s.x; uu[k][1] = s.y; uu[k][2] = s.z;
-                const float4 *row = dfeat + (size_t)__float_as_uint(s.w) * pairs;
+        for (int which = 0; which < 2; ++which)
 #pragma unroll
-                for (int q = 0; q < kMaxMerged / 2; ++q)
-                    if ((uint32_t)q < pairs) grad[k][q] = row[q];
-                if (i0 + k >= n)
-#pragma unroll
-                    for (int q = 0; q < kMaxMerged / 2; ++q) grad[k][q] = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
-#pragma unroll
-                for (int a = 0; a < 3; ++a) uu[k][a] = clamp_unit(uu[k][a]);
-            }
-        // Two levels per turn; after it the gradients move down by one place, so that every register index is a constant and
-        // the code of one turn serves all levels (all levels written out do not fit the instruction cache).
+            for (int c = 0; c < 8; ++c) { vx[which][c] = 0.0f; vy[which][c] = 0.0f; }
+        // a sample's coordinates are asked for two samples ahead, its row of the gradient one ahead
+        const uint32_t last = (n - 1u) * (uint32_t)sizeof(float4);
+        uint32_t at = i0 * (uint32_t)sizeof(float4);
+        auto sample = [&](uint32_t offset) { return *reinterpret_cast<const float4 *>(list + min(offset, last)); };
+        float4 s = sample(at), s_next = sample(at + (uint32_t)sizeof(float4));
+        float4 row = dfeat[(size_t)__float_as_uint(s.w) * pairs + q];
 #pragma unroll 1
-        for (uint32_t q = 0; q < pairs; ++q) {
+        for (uint32_t k = 0; k < run; ++k, at += (uint32_t)sizeof(float4)) {
+            const float uu[3] = {unit(s.x), unit(s.y), unit(s.z)}, gx[2] = {row.x, row.z}, gy[2] = {row.y, row.w};
+            s = s_next;
+            row = dfeat[(size_t)__float_as_uint(s.w) * pairs + q];
+            s_next = sample(at + 2u * (uint32_t)sizeof(float4));
+            if (at > last) continue;                                  // past the end of the piece
 #pragma unroll
             for (int which = 0; which < 2; ++which) {
-                const uint32_t l = 2 * q + which;
-                const bool wide = l < boxes.n_wide;
-                float scale[3], last[3];
+                const LevelBox &v = box[which];
+                float cell[3], w1[3], w0[3];
 #pragma unroll
-                for (int a = 0; a < 3; ++a) { scale[a] = lane_value(mine.scale[a], l); last[a] = lane_value(mine.last[a], l); }
-                const float fnx = lane_value(mine.nx, l), fnxy = lane_value(mine.nxy, l), origin = lane_value(mine.origin, l);
-                const uint32_t nx = (uint32_t)fnx, nxy = (uint32_t)fnxy, last_slot = lane_value(mine.last_slot, l);
-                unsigned long long *box = sums + lane_value(mine.first, l);
-                float vx[8], vy[8];
-                uint32_t slot = 0;                                    // of the cell whose sums vx, vy are
+                for (int a = 0; a < 3; ++a) {
+                    locate_unit(uu[a], v.scale[a], v.last[a], cell[a], w1[a]);
+                    w0[a] = 1.0f - w1[a];
+                }
+                // whole numbers below 2^24: exact in fp32
+                const uint32_t now = min((uint32_t)__builtin_fmaf(cell[2], v.nxy, __builtin_fmaf(cell[1], v.nx, cell[0] - v.origin)), v.last_slot);
+                if (k > 0 && now != slot[which]) {
+                    add_to_box(sums + v.first + slot[which], v.wide, to_fixed, (uint32_t)v.nx, (uint32_t)v.nxy, n_vertices, vx[which], vy[which]);
 #pragma unroll
-                for (int k = 0; k < kRun; ++k)
-                    if ((uint32_t)k < run) {
-                        const float gx = which ? grad[k][0].z : grad[k][0].x, gy = which ? grad[k][0].w : grad[k][0].y;
-                        float cell[3], w1[3], w0[3];
+                    for (int c = 0; c < 8; ++c) { vx[which][c] = 0.0f; vy[which][c] = 0.0f; }
+                }
+                slot[which] = now;
+                const float px[2] = {gx[which] * w0[0], gx[which] * w1[0]}, py[2] = {gy[which] * w0[0], gy[which] * w1[0]};
+                const float yz[4] = {w0[1] * w0[2], w1[1] * w0[2], w0[1] * w1[2], w1[1] * w1[2]};
 #pragma unroll
-                        for (int a = 0; a < 3; ++a) {
-                            locate_axis_float(uu[k][a], scale[a], last[a], cell[a], w1[a]);
-                            w0[a] = 1.0f - w1[a];
-                        }
-                        // whole numbers below 2^24: exact in fp32
-                        const uint32_t now = min((uint32_t)__builtin_fmaf(cell[2], fnxy, __builtin_fmaf(cell[1], fnx, cell[0] - origin)), last_slot);
-                        if (k > 0 && now != slot) {
-                            add_to_box(box + slot, wide, to_fixed, nx, nxy, n_vertices, vx, vy);
-#pragma unroll
-                            for (int c = 0; c < 8; ++c) { vx[c] = 0.0f; vy[c] = 0.0f; }
-                        }
-                        slot = now;
-                        const float px[2] = {gx * w0[0], gx * w1[0]}, py[2] = {gy * w0[0], gy * w1[0]};
-                        const float yz[4] = {w0[1] * w0[2], w1[1] * w0[2], w0[1] * w1[2], w1[1] * w1[2]};
-#pragma unroll
-                        for (int c = 0; c < 8; ++c) {
-                            vx[c] = k > 0 ? __builtin_fmaf(px[c & 1], yz[c >> 1], vx[c]) : px[c & 1] * yz[c >> 1];
-                            vy[c] = k > 0 ? __builtin_fmaf(py[c & 1], yz[c >> 1], vy[c]) : py[c & 1] * yz[c >> 1];
-                        }
-                    }
-                // the exchange comes first: every lane takes part in it
-                const uint32_t below = from_lane_below(slot);
-                const bool head = lane == 0 || below != slot;
-                const unsigned long long heads = __ballot(head);
-                if (__popcll(heads) < dg::kWave) segmented_sum(vx, vy, head, heads);
-                const bool tail = lane == dg::kWave - 1 || ((heads >> ((lane + 1) & 63)) & 1ull);
-                if (tail) add_to_box(box + slot, wide, to_fixed, nx, nxy, n_vertices, vx, vy);
+                for (int c = 0; c < 8; ++c) {
+                    vx[which][c] = __builtin_fmaf(px[c & 1], yz[c >> 1], vx[which][c]);
+                    vy[which][c] = __builtin_fmaf(py[c & 1], yz[c >> 1], vy[which][c]);
+                }
             }
-#pragma unroll
-            for (int k = 0; k < kRun; ++k)
-#pragma unroll
-                for (int j = 0; j + 1 < kMaxMerged / 2; ++j) grad[k][j] = grad[k][j + 1];
         }
+        // what the lanes hold at the end, first summed over the lanes of a row of 16 that are in the same cell: on the coarser levels
+        // these are most of them, and adds to one address take turns
+        if (here == 1u) finish_runs<1>(sums, box, slot, vx, vy, i0 < n, lane, to_fixed, n_vertices);
+        else if (here == 2u) finish_runs<2>(sums, box, slot, vx, vy, i0 < n, lane, to_fixed, n_vertices);
+        else finish_runs<3>(sums, box, slot, vx, vy, i0 < n, lane, to_fixed, n_vertices);
     }
     __syncthreads();
     for (uint32_t l = 0; l < boxes.n_merged; ++l) {
         const LevelGeom lv = level_of(g, l);
-        uint32_t low[3];
-#pragma unroll
-        for (int a = 0; a < 3; ++a) low[a] = box_low(b, brick[a], a, lv.scale[a]);
-        const uint32_t nx = boxes.dim[l][0], ny = boxes.dim[l][1], count = boxes.first[l + 1] - boxes.first[l];
-        float *dst = dtable + 2 * (size_t)lv.offset;
+        const LevelBox &v = levels[l];
+        const uint32_t low[3] = {uniform(v.low[0]), uniform(v.low[1]), uniform(v.low[2])}, first = uniform(v.first), count = uniform(v.count);
+        const float fnx = uniform(v.nx), fnxy = uniform(v.nxy), per_nx = uniform(v.per_nx), per_nxy = uniform(v.per_nxy);
+        const uint32_t origin = lv.dense ? vertex_entry(lv, mask, low[0], low[1], low[2]) : 0u, ny1 = lv.res[1] + 1u, nx1 = lv.res[0] + 1u;
         // neighbouring lanes add the two features of neighbouring vertices: whole cache lines per instruction
-        for (uint32_t i = threadIdx.x; i < 2 * count; i += kBrickBlock) {
-            const uint32_t v = i >> 1, f = i & 1u;
-            const unsigned long long held = sums[f * n_vertices + boxes.first[l] + v];
-            const size_t at = 2 * (size_t)vertex_entry(lv, mask, low[0] + v % nx, low[1] + v / nx % ny, low[2] + v / (nx * ny)) + f;
-            const double fixed = (double)((long long)(held << 13) >> 13) * from_fixed;
-            if (l < boxes.n_fold) {
-                const double sum = l < boxes.n_wide ? __longlong_as_double((long long)held) : fixed;
-                if (sum != 0.0) unsafeAtomicAdd(wide_table + 2 * (size_t)lv.offset + at, sum);
-            } else {
-                const float sum = (float)fixed;
-                if (sum != 0.0f) unsafeAtomicAdd(dst + at, sum);
+        auto write_out = [&](auto dense, auto add) {
+            const uint32_t f = threadIdx.x & 1u;                     // blockDim.x is even
+            const unsigned long long *from = sums + f * n_vertices + first;
+            for (uint32_t v = threadIdx.x >> 1; v < count; v += blockDim.x >> 1) {
+                // quotients of v + 1/2: a whole number below 2^13 is half a unit from the next multiple, far more than the products' rounding
+                const float fv = (float)v, fz = floorf(__builtin_fmaf(fv, per_nxy, 0.5f * per_nxy)), in_z = __builtin_fmaf(-fz, fnxy, fv);
+                const float fy = floorf(__builtin_fmaf(in_z, per_nx, 0.5f * per_nx));
+                const uint32_t x = (uint32_t)__builtin_fmaf(-fy, fnx, in_z), y = (uint32_t)fy, z = (uint32_t)fz;
+                const uint32_t e = dense ? origin + x + nx1 * (y + ny1 * z) : ((low[0] + x) ^ (low[1] + y) * kPrimeY ^ (low[2] + z) * kPrimeZ) & mask;
+                add(from[v], 2u * e + f);                            // below 2^25
             }
+        };
+        auto write_level = [&](auto add) {
+            if (lv.dense) write_out(std::true_type{}, add);
+            else write_out(std::false_type{}, add);
+        };
+        if (l < boxes.n_fold) {
+            double *dst = wide_table + 2 * (size_t)lv.offset;
+            const bool wide = l < boxes.n_wide;
+            write_level([&](unsigned long long held, uint32_t at) {
+                const double sum = wide ? __longlong_as_double((long long)held) : from_low_bits(held) * from_fixed;
+                if (sum != 0.0) unsafeAtomicAdd(dst + at, sum);
+            });
+        } else {
+            float *dst = dtable + 2 * (size_t)lv.offset;
+            write_level([&](unsigned long long held, uint32_t at) {
+                const float sum = (float)(from_low_bits(held) * from_fixed);
+                if (sum != 0.0f) unsafeAtomicAdd(dst + at, sum);
+            });
         }
     }
 }
@@ -348,7 +419,7 @@ int brick_bwd(const char *who, const dg_grid_desc *d, const dg_order_desc *order
     const size_t lds = (size_t)boxes.first[boxes.n_merged] * 2 * sizeof(double);
     const uint32_t n_wide_sums = 2 * d->offset[boxes.n_fold];
     if (int rc = dg_clear(wide, n_wide_sums * sizeof(double), st)) return rc;
-    brick_bwd_kernel<<<(uint32_t)piece_bound(order->total, N), kBrickBlock, lds, st>>>(
+    brick_bwd_kernel<<<(uint32_t)piece_bound(order->total, N), kBrickWaves * 64, lds, st>>>(
         *d, bricks_of(order), boxes, (const uint2 *)pieces, (const float4 *)ordered, (const float4 *)dfeat, largest, dtable, wide);
     if (n_wide_sums) fold_wide_kernel<<<(n_wide_sums + kBlock - 1) / kBlock, kBlock, 0, st>>>(wide, n_wide_sums, dtable);
     return launch_status(who);

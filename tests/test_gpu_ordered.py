@@ -210,6 +210,40 @@ def test_bricks_of_a_large_batch(key):
         assert rel_err(have[sl], want[sl]) <= TOL_F16, l
 
 
+@pytest.mark.parametrize("N", [1, 21, 64, 127, 1009, 4099])
+@pytest.mark.parametrize("n_merged", [2, 4, 6, 8, 10, 12])
+def test_every_number_of_merged_levels(n_merged, N):
+    """One to six pairs of levels share the wavefronts of a workgroup in different ways, and fewer samples than lanes, one more than a
+    piece and everything between divides among them differently.  Three quarters of the samples lie in one brick."""
+    print("[case] merged levels", n_merged, N, flush=True)
+    q = CUTS["flat"]
+    growth = B.dg_growth_factor(16, q["n_max"], 16)
+    grid, ref_grid = (f(16, 2, q["log2_T"], 16, growth, q["extent"]) for f in (B.dg_grid_desc_init, oracle.grid_init))
+    order = B.dg_order_desc_init(grid, q["made_for"])
+    order.n_merged = n_merged
+    u = di.make_unit_coords(N, seed=46)
+    u[:3 * N // 4] = (np.asarray([0.5, 0.3, 0.4]) + 0.018 * (u[:3 * N // 4] - 0.5)).astype(np.float32)
+    g = (np.random.default_rng(47).standard_normal((N, 32)) * 1e-3).astype(np.float32)
+    ordered, pieces = torch.zeros(N, 4, device=DEV), torch.zeros(B.dg_order_pieces_words(order, N), dtype=torch.int32, device=DEV)
+    ud, gd = dev(u), dev(_mixed(g, n_merged))
+    B.dg_order_samples(order, ud, N, ordered, pieces, torch.zeros(B.dg_order_workspace_bytes(order) // 4, dtype=torch.int32, device=DEV))
+    dtable = torch.zeros(ref_grid.n_entries, 2, device=DEV)
+    ws = torch.zeros(B.dg_hashgrid_encode_bwd_ordered_workspace_bytes(grid, order, N) // 4 + 64, device=DEV)
+    B.dg_hashgrid_encode_bwd_ordered(grid, order, ordered, pieces, ud, gd, gd.abs().max().reshape(1).view(torch.int32), N, dtable, ws)
+    want, have = oracle.encode_bwd(ref_grid, u, g.astype(np.float64)), host(dtable).astype(np.float64)
+    scale = oracle.encode_bwd(ref_grid, u, np.abs(g).astype(np.float64))
+    assert np.all(have[want == 0] == 0)
+    # four roundings in a contribution, at most 66 adds in a lane's run (4096 samples on 63 lanes), four over lanes, a few into the table
+    quantum = 2.0 ** -37 * float(np.abs(g).max()) * N
+    for l in range(n_merged):
+        sl = slice(ref_grid.first[l], ref_grid.first[l + 1])
+        assert np.all(np.abs(have[sl] - want[sl]) <= 80 * 2.0 ** -24 * scale[sl] + quantum), l
+    for l in range(n_merged, 16):
+        # not the brick sums: records rounded to 2^-20
+        sl = slice(ref_grid.first[l], ref_grid.first[l + 1])
+        assert np.linalg.norm(have[sl] - want[sl]) <= 4 * 2.0 ** -20 * np.linalg.norm(want[sl]), l
+
+
 def test_many_bricks_to_an_entry():
     """29 791 bricks on tables of 2^14 entries: some seventy bricks and more add to an entry.  Their sums are added in fp64, so what is
     left are the roundings of a contribution (two products for its weight, one with the gradient, one of 1 - fraction) and that of the
