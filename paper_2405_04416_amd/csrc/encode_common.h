@@ -88,6 +88,14 @@ __device__ __forceinline__ void corner_weights(const float frac[3], float w[8])
 }
 
 
+// the whole number, less than 2^50 in magnitude, that the low 51 bits of a sum of doubles' bit patterns hold in two's complement
+__device__ __forceinline__ double from_low_bits(unsigned long long held)
+{
+    // shifted up by 2^50 the number is the low mantissa bits of a double from 2^52 on; the upper bits of `held` go
+    const uint32_t high = (((uint32_t)(held >> 32) + (1u << 18)) & ((1u << 19) - 1u)) | 0x43300000u;
+    return __longlong_as_double((long long)((unsigned long long)high << 32 | (uint32_t)held)) - 0x1.4p52;
+}
+
 // value of the lane below (lane - 1) in the wavefront; lane 0 gets its own.  A DPP move: no LDS traffic, no wait.
 __device__ __forceinline__ uint32_t from_lane_below(uint32_t v)
 {

@@ -156,14 +156,6 @@ __device__ __forceinline__ void add_wide(unsigned long long *slot, float v)
     __hip_atomic_fetch_add(reinterpret_cast<double *>(slot), (double)v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
 }
 
-// the whole number, less than 2^50 in magnitude, that the low 51 bits of a sum of doubles' bit patterns hold in two's complement
-__device__ __forceinline__ double from_low_bits(unsigned long long held)
-{
-    // shifted up by 2^50 the number is the low mantissa bits of a double from 2^52 on; the upper bits of `held` go
-    const uint32_t high = (((uint32_t)(held >> 32) + (1u << 18)) & ((1u << 19) - 1u)) | 0x43300000u;
-    return __longlong_as_double((long long)((unsigned long long)high << 32 | (uint32_t)held)) - 0x1.4p52;
-}
-
 // the eight corner sums of the cell whose corner 0 is vertex d of the box
 __device__ __forceinline__ void add_to_box(unsigned long long *d, bool wide, double to_fixed, uint32_t nx, uint32_t nxy, uint32_t plane, const float (&vx)[8],
                                            const float (&vy)[8])

@@ -150,6 +150,8 @@ GRIDS = {
     # T = 2^21: a dense level of 34 bins and hashed levels of 256 bins (more than one wavefront's worth)
     "wide": lambda: (None, dict(L=4, F=2, log2_T=21, n_min=64, growth=2.0, extent=[1.0, 1.0, 1.0])),
     # T = 2^24, three hashed levels: 6144 (level, bin) pairs, too many for the counters to sit in LDS
+    # 5, 34 and 263 bins of dense levels, which get many records each, and three times 1024 of hashed ones, which get few
+    "sparse": lambda: (None, dict(L=6, F=2, log2_T=23, n_min=32, growth=2.0, extent=[1.0, 1.0, 1.0])),
     "huge": lambda: (None, dict(L=3, F=2, log2_T=24, n_min=512, growth=2.0, extent=[1.0, 1.0, 1.0])),
 }
 
@@ -323,6 +325,35 @@ def test_encode_bwd_binned_marks_non_finite_gradients(bad):
     B.dg_hashgrid_encode_bwd(g, dev(u), dev(to_planes(dfeat)), N, dtable, ws)
     torch.cuda.synchronize()
     assert not bool(torch.isfinite(dtable).all())
+
+
+@pytest.mark.parametrize("bad", [None, np.inf])
+@pytest.mark.parametrize("N", [1, 513, 50011])
+def test_encode_bwd_many_sparse_bins(N, bad):
+    """More bins than 2048 and fewer records than entries: workgroups that take bin after bin, bins that are one workgroup's alone and
+    bins cut into pieces.  One count serves two passes, the second onto what the first has left."""
+    say("encode bwd sparse bins N=%d %s" % (N, bad))
+    g, r, _ = _both_grids("sparse")
+    u = _coords(N, "rays", seed=55)
+    dfeat = (np.random.default_rng(56).standard_normal((N, 2 * g.n_levels)) * 1e-3).astype(np.float32)
+    if bad is not None:
+        dfeat[N // 2, 3] = bad
+    ud, dd = dev(u), dev(to_planes(dfeat))
+    ws = torch.full((B.dg_hashgrid_encode_bwd_workspace_bytes(g, N) // 4 + 64,), float("nan"), device=DEV)
+    dtable = torch.zeros(r.n_entries, 2, device=DEV)
+    B.dg_hashgrid_encode_bwd_count(g, ud, N, ws)
+    for _ in range(2):
+        B.dg_hashgrid_encode_bwd_counted(g, ud, dd, N, dtable, ws)
+    if bad is not None:
+        for l in range(g.n_levels):
+            assert not bool(torch.isfinite(dtable[r.first[l]:r.first[l + 1]]).all()), l
+        return
+    ref, got = 2.0 * oracle.encode_bwd(r, u, dfeat.astype(np.float64)), host(dtable).astype(np.float64)
+    for l in range(g.n_levels):
+        sl = slice(r.first[l], r.first[l + 1])
+        # records rounded to 2^-20, sums rounded to fp32
+        assert np.linalg.norm(got[sl] - ref[sl]) <= 4 * 2.0 ** -20 * np.linalg.norm(ref[sl]), l
+    assert np.all(got[ref == 0] == 0)
 
 
 @pytest.mark.parametrize("with_ws", [False, True])
