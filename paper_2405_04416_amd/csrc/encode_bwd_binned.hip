@@ -57,26 +57,38 @@ struct Plan {
     uint32_t max_bins;
 };
 
-// ------------------------------------------------------------------ coarse prefix: accumulate in LDS
+// ------------------------------------------------------------------ accumulate in LDS directly
+// Groups of `width` workgroups, each for a table region that fits LDS: the coarse prefix, and with `bins` every bin of the other
+// levels.  A group's workgroups sweep all samples at their region's levels and add what falls into it.
 __global__ void __launch_bounds__(kCoarseBlock)
-coarse_kernel(dg_grid_desc g, uint32_t from_level, uint32_t first_level, const float *__restrict__ u, const float2 *__restrict__ dfeat,
+coarse_kernel(dg_grid_desc g, Plan plan, uint32_t from_level, uint32_t width, const float *__restrict__ u, const float2 *__restrict__ dfeat,
               uint64_t N, float *__restrict__ dtable)
 {
-    // 2 sums per entry of levels [from_level, first_level), one plane per feature (an add instruction then spreads over all LDS
-    // banks); fp64 LDS atomics run ~7x faster than fp32 ones
+    // 2 sums per entry of the region, one plane per feature (an add instruction then spreads over all LDS banks); fp64 LDS atomics
+    // run ~7x faster than fp32 ones
     extern __shared__ double tab[];
-    const uint32_t base = g.offset[from_level], n_entries = g.offset[first_level] - base, n_floats = 2u * n_entries;
+    const uint32_t group = blockIdx.x / width, me = blockIdx.x % width, prefix = plan.first_level > from_level ? 1u : 0u;
+    uint32_t first = from_level, end = plan.first_level, base = g.offset[first], n_entries = g.offset[end] - base;      // levels, entries
+    if (group >= prefix) {
+        const uint32_t key = group - prefix;
+        first = plan.first_level;
+        while (first + 1 < g.n_levels && key >= plan.key_base[first + 1]) ++first;
+        end = first + 1;
+        base = g.offset[first] + (key - plan.key_base[first]) * kChunk;
+        n_entries = min(kChunk, g.offset[end] - base);
+    }
+    const uint32_t n_floats = 2u * n_entries;
     for (uint32_t i = threadIdx.x; i < n_floats; i += kCoarseBlock) tab[i] = 0.0;
     __syncthreads();
     const int lane = threadIdx.x % dg::kWave;
     const uint32_t mask = (1u << g.log2_T) - 1u;
     const uint64_t n_tiles = (N + kCoarseBlock - 1) / kCoarseBlock;
-    for (uint64_t tile = blockIdx.x; tile < n_tiles; tile += gridDim.x) {
+    for (uint64_t tile = me; tile < n_tiles; tile += width) {
         const uint64_t n = tile * kCoarseBlock + threadIdx.x;
         const bool live = n < N;
         const uint64_t nn = live ? n : N - 1;
         const float uu[3] = {u[3 * nn], u[3 * nn + 1], u[3 * nn + 2]};
-        for (uint32_t l = from_level; l < first_level; ++l) {
+        for (uint32_t l = first; l < end; ++l) {
             const LevelGeom lv = level_of(g, l);
             uint32_t cell[3], e[8];
             float frac[3], w[8];
@@ -97,7 +109,8 @@ coarse_kernel(dg_grid_desc g, uint32_t from_level, uint32_t first_level, const f
             if (tail) {
 #pragma unroll
                 for (int c = 0; c < 8; ++c) {
-                    const uint32_t slot = lv.offset - base + e[c];
+                    const uint32_t slot = lv.offset + e[c] - base;
+                    if (slot >= n_entries) continue;                 // another bin's
                     if (vx[c] != 0.0f) __hip_atomic_fetch_add(&tab[slot], (double)vx[c], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
                     if (vy[c] != 0.0f) __hip_atomic_fetch_add(&tab[n_entries + slot], (double)vy[c], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
                 }
@@ -966,6 +979,17 @@ uint32_t piece_log2(uint64_t records)
 // accumulate workgroups that `records` records need at most
 uint32_t acc_grid(const Plan &p, uint64_t records) { return (uint32_t)(records >> piece_log2(records)) + p.n_keys; }
 
+// All bins summed in LDS directly, in the sweep that serves the coarse prefix (coarse_kernel): one launch instead of six and no queue,
+// but every bin's workgroups go through all samples: 8 us + 12.6 ps per sample and bin against some 45 us + 34 ps per sample and level
+// through the queues, which the line below follows.  In us, direct / queues: 6 bins in 3 levels 33 k samples 18 / 52, 1.6 M 129 / 186,
+// 4 M 326 / 567; 17 bins in 3 levels 0.3 M 70 / 120, 3 M 618 / 425; 30 bins in 15 levels 30 k 23 / 76, 3 M 1086 / 1796; 58 bins in 13
+// levels 30 k 31 / 73, 0.3 M 219 / 247, 3 M 2203 / 1625.  At most as many bins as workgroups are resident at once.
+bool direct_bins(const Plan &p, uint32_t n_levels, uint64_t N)
+{
+    const uint64_t free = 5ull * (n_levels - p.first_level) / 2;
+    return p.n_keys < (uint32_t)kCoarseGrid && (p.n_keys <= free || N * (p.n_keys - free) < 5000000ull);
+}
+
 // Many bins with fewer records than entries: accumulate_sparse_kernel.  Its time against accumulate_kernel's in us, with `bins` bins and
 // `records` records per bin at most: 4080 bins, 5300 records 183 / 245; 3900, 5000 198 / 270; 2560, 2100 134 / 144; 2560, 1600 131 / 141;
 // 13 900, 1400 1000 / 1010.  Few bins: 1380, 5700 101 / 73; 830, 4700 55 / 55; 830, 9100 65 / 62; 830, 14 000 71 / 60.  Many records: 3500
@@ -1102,6 +1126,7 @@ int encode_bwd_binned_count(const char *who, const dg_grid_desc *d, uint32_t fro
     if (q.L.batch < N)
         return fail(DG_ERR_WORKSPACE, "%s: counting ahead needs a workspace that holds all %llu samples in one batch (it holds %llu)", who,
                     (unsigned long long)N, (unsigned long long)q.L.batch);
+    if (direct_bins(q.p, d->n_levels, N)) return DG_OK;                  // no queues to size
     launch_count(q, d, u, 0, N, st);
     return launch_status(who);
 }
@@ -1115,13 +1140,15 @@ int encode_bwd_binned(const char *who, const dg_grid_desc *d, uint32_t from_leve
     if (counted && p.n_keys && q.L.batch < N)
         return fail(DG_ERR_WORKSPACE, "%s: the workspace holds %llu of %llu samples: no counts from dg_hashgrid_encode_bwd_count can be in it",
                     who, (unsigned long long)q.L.batch, (unsigned long long)N);
-    if (p.first_level > from_level) {
+    const bool direct = direct_bins(p, d->n_levels, N);
+    const uint32_t groups = (p.first_level > from_level ? 1u : 0u) + (direct ? p.n_keys : 0u);
+    if (groups) {
         const uint64_t tiles = (N + kCoarseBlock - 1) / kCoarseBlock;
-        const uint32_t grid = (uint32_t)(tiles < kCoarseGrid ? tiles : kCoarseGrid);
-        coarse_kernel<<<grid, kCoarseBlock, 2 * (d->offset[p.first_level] - d->offset[from_level]) * sizeof(double), st>>>(
-            *d, from_level, p.first_level, u, (const float2 *)dfeat, N, dtable);
+        const uint32_t width = std::max(1u, (uint32_t)std::min<uint64_t>(tiles, kCoarseGrid / groups));
+        const uint32_t entries = direct && p.n_keys ? kChunk : d->offset[p.first_level] - d->offset[from_level];
+        coarse_kernel<<<groups * width, kCoarseBlock, 2 * entries * sizeof(double), st>>>(*d, p, from_level, width, u, (const float2 *)dfeat, N, dtable);
     }
-    if (p.n_keys == 0) return launch_status(who);
+    if (p.n_keys == 0 || direct) return launch_status(who);
     const uint64_t batch = q.L.batch;
     for (uint64_t n0 = 0; n0 < N; n0 += batch) {
         const uint64_t nb = N - n0 < batch ? N - n0 : batch;

@@ -327,6 +327,36 @@ def test_encode_bwd_binned_marks_non_finite_gradients(bad):
     assert not bool(torch.isfinite(dtable).all())
 
 
+@pytest.mark.parametrize("log2_T,n_bins", [(11, 0), (12, 2), (14, 6), (16, 17)])
+@pytest.mark.parametrize("N", [1, 63, 1025, 100003])
+def test_encode_bwd_few_bins(N, log2_T, n_bins):
+    """So few bins that every one is summed in LDS directly, the last of a level partly filled: fp64 from the wavefront's runs to the
+    workgroup's sum, then one fp32 add per workgroup."""
+    say("encode bwd few bins N=%d T=2^%d" % (N, log2_T))
+    g, r = (f(4, 2, log2_T, 16, 1.5, [1.0, 1.0, 1.0]) for f in (B.dg_grid_desc_init, oracle.grid_init))
+    prefix = max(l for l in range(5) if r.first[l] <= 8192)
+    assert sum(-(-(r.first[l + 1] - r.first[l]) // 8192) for l in range(prefix, 4)) == n_bins
+    u = _coords(N, "rays", seed=65)
+    u[:2] = [[1, 1, 1], [-0.3, 0.5, 2.0]][:N]
+    dfeat = (np.random.default_rng(66).standard_normal((N, 8)) * 1e-3).astype(np.float32)
+    ud, dd = dev(u), dev(to_planes(dfeat))
+    ws = torch.full((B.dg_hashgrid_encode_bwd_workspace_bytes(g, N) // 4 + 64,), float("nan"), device=DEV)
+    dtable = torch.zeros(r.n_entries, 2, device=DEV)
+    B.dg_hashgrid_encode_bwd(g, ud, dd, N, dtable, ws)
+    B.dg_hashgrid_encode_bwd_count(g, ud, N, ws)
+    B.dg_hashgrid_encode_bwd_counted(g, ud, dd, N, dtable, ws)
+    ref, scale = (2.0 * oracle.encode_bwd(r, u, x.astype(np.float64)) for x in (dfeat, np.abs(dfeat)))
+    got = host(dtable).astype(np.float64)
+    # four roundings in a contribution, six adds over a run of lanes, and the workgroups' adds of both passes
+    adds = 2 * min(-(-N // 1024), 256 // (n_bins + (1 if prefix else 0)))
+    assert np.all(np.abs(got - ref) <= (10 + adds) * 2.0 ** -24 * scale)
+    assert np.all(got[ref == 0] == 0)
+    dd[1, 0, 0] = float("inf")                           # shows in the gradient of that level, and only there
+    dtable.zero_()
+    B.dg_hashgrid_encode_bwd(g, ud, dd, N, dtable, ws)
+    assert [bool(torch.isfinite(dtable[r.first[l]:r.first[l + 1]]).all()) for l in range(4)] == [True, False, True, True]
+
+
 @pytest.mark.parametrize("bad", [None, np.inf])
 @pytest.mark.parametrize("N", [1, 513, 50011])
 def test_encode_bwd_many_sparse_bins(N, bad):
