@@ -315,6 +315,37 @@ int dg_merge_loss(const float *Ck, const float *Tk, const uint32_t *seg_count, u
 /* Clears `bytes` bytes (a multiple of 4, dst 4-byte aligned) with a kernel on the stream. */
 int dg_clear(void *dst, uint64_t bytes, void *stream);
 
+/* One sub-model's share of a training step, each way in one call: what the entry points named below do, in that order, on the
+ * sub-model's n_seg segments of S samples each (N = n_seg * S, level-major features).  For callers whose step is bound by the
+ * launching, not by the work.  All pointers as in those entry points, each at the sub-model's first segment or sample; the code of the
+ * first call that fails is returned, those before it have been launched.
+ *   dg_field_fwd: dg_sample_segments, dg_dir_encode, dg_hashgrid_encode_fwd (fp16), dg_mlp_fwd, dg_composite_segment_fwd
+ *   dg_field_bwd: dg_clear of the gradients (two stretches, either may be empty), dg_composite_segment_bwd, dg_mlp_bwd,
+ *                 dg_hashgrid_encode_bwd */
+typedef struct {
+    const dg_grid_desc *grid;
+    const dg_mlp_desc *mlp;
+    uint32_t n_seg, S, k_max, degree;
+    uint64_t seed;
+    float box[6], loss_scale;
+    uint32_t reserved;                                           /* 0 */
+    const uint32_t *seg_ray, *seg_slot;
+    const float *o, *d, *seg_t;                                  /* forward */
+    const float *table;
+    const void *weights;
+    float *u, *delta;
+    void *dir_enc, *feat;
+    float *sigma, *rgb, *Ck, *Tk;
+    const float *gCk, *gTk;                                      /* backward */
+    float *dsigma, *drgb, *dfeat, *dtable, *dW;
+    void *clear[2];
+    uint64_t clear_bytes[2];
+    void *ws_mlp, *ws_enc;                                       /* ws_enc NULL: no workspace */
+    uint64_t ws_mlp_bytes, ws_enc_bytes;
+} dg_field_call;
+int dg_field_fwd(const dg_field_call *call, void *stream);
+int dg_field_bwd(const dg_field_call *call, void *stream);
+
 /* The same networks with appearance features (Sec. 4.4.3: a fixed vector per image, 16 or 48 values, as additional
  * inputs of the colour net): colour input = [geo | dir_enc row | app row], desc->n_app = 16 or 48 (0: app is ignored and
  * may be NULL; only the 32-64-16 / 64-64-3 shape takes appearance inputs).  app [ceil(N/S), n_app] fp16 device, 16-byte

@@ -42,6 +42,17 @@ class OrderDesc(C.Structure):
                 ("box", (C.c_uint32 * 3) * MAX_LEVELS), ("box_first", C.c_uint32 * (MAX_LEVELS + 1))]
 
 
+_POINTERS_1 = ("seg_ray", "seg_slot", "o", "d", "seg_t", "table", "weights", "u", "delta", "dir_enc", "feat", "sigma", "rgb", "Ck", "Tk", "gCk", "gTk",
+               "dsigma", "drgb", "dfeat", "dtable", "dW")
+
+
+class FieldCall(C.Structure):
+    _fields_ = ([("grid", C.c_void_p), ("mlp", C.c_void_p)] + [(n, C.c_uint32) for n in ("n_seg", "S", "k_max", "degree")]
+                + [("seed", C.c_uint64), ("box", C.c_float * 6), ("loss_scale", C.c_float), ("reserved", C.c_uint32)]
+                + [(n, C.c_void_p) for n in _POINTERS_1] + [("clear", C.c_void_p * 2), ("clear_bytes", C.c_uint64 * 2), ("ws_mlp", C.c_void_p),
+                                                            ("ws_enc", C.c_void_p), ("ws_mlp_bytes", C.c_uint64), ("ws_enc_bytes", C.c_uint64)])
+
+
 class DistGridError(RuntimeError):
     pass
 
@@ -110,6 +121,8 @@ _SIGNATURES = {
     "dg_loss_seed": (C.c_int, [C.c_void_p] * 3 + [C.c_uint32, C.c_float] + [C.c_void_p] * 4),
     "dg_merge_loss": (C.c_int, [C.c_void_p] * 3 + [C.c_uint32, C.c_uint32, C.c_void_p, C.c_float] + [C.c_void_p] * 6),
     "dg_clear": (C.c_int, [C.c_void_p, C.c_uint64, C.c_void_p]),
+    "dg_field_fwd": (C.c_int, [C.POINTER(FieldCall), C.c_void_p]),
+    "dg_field_bwd": (C.c_int, [C.POINTER(FieldCall), C.c_void_p]),
     "dg_composite_segment_depth": (C.c_int, [C.c_void_p] * 3 + [C.c_uint32, C.c_uint32, C.c_void_p, C.c_void_p, C.c_uint32, C.c_void_p, C.c_void_p]),
     "dg_merge_depth": (C.c_int, [C.c_void_p] * 3 + [C.c_uint32, C.c_uint32, C.c_void_p, C.c_void_p]),
     "dg_adam_step": (C.c_int, [C.c_void_p] * 4 + [C.c_uint64] + [C.c_float] * 4 + [C.c_uint32, C.c_float, C.c_uint32] + [C.c_void_p] * 2),
@@ -280,6 +293,52 @@ def dg_hashgrid_encode_bwd_counted(desc, u, dfeat, N, dtable, ws):
 
 def dg_hashgrid_corner_indices(desc, u, N, idx):
     _check(lib().dg_hashgrid_corner_indices(C.byref(desc), _ptr(u, torch.float32), N, _ptr(idx, torch.int32), _stream()))
+
+
+# ------------------------------------------------------------------ a sub-model's share of a step in one call
+def _part(t, dtype, first, count):
+    """Pointer to element `first` of a contiguous tensor that holds `count` elements from there."""
+    if t.numel() < first + count:
+        raise DistGridError("tensor of %d elements is too small for %d from element %d on" % (t.numel(), count, first))
+    return _ptr(t, dtype) + first * t.element_size()
+
+
+def _field_call(grid, mlp, first, n_seg, S, degree, seg_first, seg_ray, seg_slot, k_max, weights, u, delta, dir_enc, feat, sigma, rgb):
+    """What both ways share.  first: index of the sub-model's first segment in the sample buffers, seg_first: in seg_ray / seg_slot."""
+    f32, f16, i32 = torch.float32, torch.float16, torch.int32
+    N, n0, rows = n_seg * S, first * S, degree * degree
+    c = FieldCall(grid=C.addressof(grid), mlp=C.addressof(mlp), n_seg=n_seg, S=S, k_max=k_max, degree=degree)
+    c.seg_ray, c.seg_slot = _part(seg_ray, i32, seg_first, n_seg), _part(seg_slot, i32, seg_first, n_seg)
+    c.weights, c.dir_enc = _ptr(weights, f16), _part(dir_enc, f16, first * rows, n_seg * rows)
+    c.u, c.delta, c.feat = _part(u, f32, 3 * n0, 3 * N), _part(delta, f32, n0, N), _part(feat, f16, mlp.n_feat * n0, mlp.n_feat * N)
+    c.sigma, c.rgb = _part(sigma, f32, n0, N), _part(rgb, f32, 3 * n0, 3 * N)
+    return c
+
+
+def dg_field_fwd(common, box, seed, o, d, seg_t, table, Ck, Tk):
+    """common: the arguments of _field_call."""
+    f32 = torch.float32
+    c = _field_call(*common)
+    c.seed, c.box = seed, (C.c_float * 6)(*box)
+    c.o, c.d, c.seg_t, c.table, c.Ck, c.Tk = _ptr(o, f32), _ptr(d, f32), _ptr(seg_t, f32), _ptr(table, f32), _ptr(Ck, f32), _ptr(Tk, f32)
+    _check(lib().dg_field_fwd(C.byref(c), _stream()))
+
+
+def dg_field_bwd(common, loss_scale, gCk, gTk, dsigma, drgb, dfeat, dtable, dW, clear, ws_mlp, ws_enc):
+    """clear: at most two tensors to zero first."""
+    f32 = torch.float32
+    c = _field_call(*common)
+    first, N, n_feat = common[2] * common[4], c.n_seg * c.S, common[1].n_feat
+    c.loss_scale = loss_scale
+    c.gCk, c.gTk = _ptr(gCk, f32), _ptr(gTk, f32)
+    c.dsigma, c.drgb, c.dfeat = _part(dsigma, f32, first, N), _part(drgb, f32, 3 * first, 3 * N), _part(dfeat, f32, n_feat * first, n_feat * N)
+    c.dtable, c.dW = _ptr(dtable, f32), _ptr(dW, f32)
+    for i, t in enumerate(clear):
+        c.clear[i], c.clear_bytes[i] = _ptr(t), t.numel() * t.element_size()
+    c.ws_mlp, c.ws_mlp_bytes = _ptr(ws_mlp), ws_mlp.numel() * ws_mlp.element_size()
+    if ws_enc is not None:
+        c.ws_enc, c.ws_enc_bytes = _ptr(ws_enc), ws_enc.numel() * ws_enc.element_size()
+    _check(lib().dg_field_bwd(C.byref(c), _stream()))
 
 
 # ------------------------------------------------------------------ samples in spatial order

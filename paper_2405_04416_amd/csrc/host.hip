@@ -1,4 +1,4 @@
-// Host-side parts of libdistgrid: error slot, grid descriptor (Sec. 3.2, Sec. 4.1), weight counts.
+// Host-side parts of libdistgrid: error slot, grid descriptor (Sec. 3.2, Sec. 4.1), weight counts, a sub-model's share of a step in one call.
 #include "dg_internal.h"
 #include <cmath>
 #include <cstring>
@@ -68,4 +68,34 @@ extern "C" size_t dg_mlp_weight_count(const dg_mlp_desc *m)
     if (m->n_layers_c == 2) c += (size_t)m->n_hidden_c * m->n_hidden_c;
     c += (size_t)m->n_hidden_c * m->n_app;      // the appearance columns of the first colour layer, packed last
     return c;
+}
+
+extern "C" int dg_field_fwd(const dg_field_call *c, void *stream)
+{
+    const char *who = "dg_field_fwd";
+    DG_REQUIRE(c && c->grid && c->mlp, DG_ERR_ARG, "%s: null pointer", who);
+    DG_REQUIRE(c->reserved == 0, DG_ERR_ARG, "%s: the reserved word must be 0", who);
+    const uint64_t N = (uint64_t)c->n_seg * c->S;
+    if (int rc = dg_sample_segments(c->o, c->d, c->seg_t, c->seg_ray, c->seg_slot, c->n_seg, c->k_max, c->box, c->S, c->seed, nullptr, c->u, c->delta, nullptr, stream))
+        return rc;
+    if (int rc = dg_dir_encode(c->d, c->seg_ray, c->n_seg, c->degree, c->dir_enc, stream)) return rc;
+    if (int rc = dg_hashgrid_encode_fwd(c->grid, c->table, c->u, N, c->feat, DG_F16, stream)) return rc;
+    if (int rc = dg_mlp_fwd(c->mlp, c->weights, c->feat, c->dir_enc, c->S, N, c->sigma, c->rgb, stream)) return rc;
+    return dg_composite_segment_fwd(c->sigma, c->rgb, c->delta, c->n_seg, c->S, c->seg_ray, c->seg_slot, c->k_max, c->Ck, c->Tk, stream);
+}
+
+extern "C" int dg_field_bwd(const dg_field_call *c, void *stream)
+{
+    const char *who = "dg_field_bwd";
+    DG_REQUIRE(c && c->grid && c->mlp, DG_ERR_ARG, "%s: null pointer", who);
+    DG_REQUIRE(c->reserved == 0, DG_ERR_ARG, "%s: the reserved word must be 0", who);
+    const uint64_t N = (uint64_t)c->n_seg * c->S;
+    for (int i = 0; i < 2; ++i)
+        if (c->clear_bytes[i])
+            if (int rc = dg_clear(c->clear[i], c->clear_bytes[i], stream)) return rc;
+    if (int rc = dg_composite_segment_bwd(c->sigma, c->rgb, c->delta, c->n_seg, c->S, c->seg_ray, c->seg_slot, c->k_max, c->gCk, c->gTk, c->dsigma, c->drgb, stream))
+        return rc;
+    if (int rc = dg_mlp_bwd(c->mlp, c->weights, c->feat, c->dir_enc, c->S, N, c->dsigma, c->drgb, c->loss_scale, c->dfeat, c->dW, c->ws_mlp, c->ws_mlp_bytes, stream))
+        return rc;
+    return dg_hashgrid_encode_bwd(c->grid, c->u, c->dfeat, N, c->dtable, c->ws_enc, c->ws_enc_bytes, stream);
 }

@@ -152,3 +152,42 @@ def test_feature_buffers_after_a_refresh(ordered):
     step.backward()
     torch.cuda.synchronize()
     assert bool(torch.isfinite(m.dW).all())
+
+
+@pytest.mark.parametrize("name,R", [("c1_tiny", 257), ("c2_ngp", 1), ("c2_ngp", 700), ("c3_2x2", 500), ("c6_cascade", 300)])
+def test_one_call_each_way(name, R, monkeypatch):
+    """A sub-model's share of a step in one library call each way and by the single entry points: the same numbers.  The table gradient
+    adds up in no fixed order; the caller's own gradient buffers are the ones that are cleared and filled."""
+    cfg = di.config(name, table_range=0.3)
+    for key in ("grid", "grid_coarse"):
+        if key in cfg:
+            cfg[key] = dict(cfg[key], log2_T=min(cfg[key]["log2_T"], 16))
+    o, d = di.make_rays(cfg, seed=5, R=R)
+    target, hm = dev(di.make_targets(R, seed=5)), ostep.make_models(cfg, seed=5)
+    steps = [make_step(cfg, gpu_models(cfg, hm), R, seed=5) for _ in range(2)]
+    took = []
+    one_call = TrainStep._one_call
+    for step, allowed in zip(steps, (True, False)):
+        monkeypatch.setattr(TrainStep, "_one_call", lambda self, order, N: took.append((allowed, one_call(self, order, N))) or (allowed and took[-1][1]))
+        for m in step.models.values():
+            m.dtable, m.dW = torch.full_like(m.dtable, 7.0), torch.full_like(m.dW, 7.0)
+        for _ in range(2):
+            step.step(dev(o), dev(d), target)
+    assert all(yes for allowed, yes in took) and any(allowed for allowed, _ in took)
+    a, b = steps
+    for x, y in ((a.C, b.C), (a.T, b.T), (a.gCk, b.gCk)):
+        assert torch.equal(x, y)
+    assert float(a.loss) == pytest.approx(float(b.loss), rel=1e-6)
+    for p in a.models:
+        assert float((a.models[p].dW - b.models[p].dW).norm()) <= 1e-6 * float(b.models[p].dW.norm())
+        assert float((a.models[p].dtable - b.models[p].dtable).norm()) <= 1e-6 * float(b.models[p].dtable.norm())
+
+
+def test_one_call_refuses_buffers_that_are_too_small():
+    cfg = di.config("c1_tiny")
+    R = 64
+    o, d = di.make_rays(cfg, seed=6, R=R)
+    step = make_step(cfg, gpu_models(cfg, ostep.make_models(cfg, seed=6)), R, seed=6)
+    step.feat = step.feat[:5]
+    with pytest.raises(B.DistGridError):
+        step.step(dev(o), dev(d), dev(di.make_targets(R, seed=6)))
