@@ -11,16 +11,14 @@
 // Operand layouts, images, transposes: mlp_mfma_common.h.
 //
 // What the kernels spend on a tile (13.3 M samples): forward 402 vector instructions of which 131 are transcendental and take two issue
-// slots; the vector units are busy 0.86 of the time, the matrix cores 0.31.  Colour backward: busy 0.62 and 0.42, with little overlap
+// slots; the vector units are busy 0.86 of the time, the matrix cores 0.31.  Colour backward: busy 0.6 and 0.4, with little overlap
 // at two wavefronts per SIMD, so it goes by the number of instructions: a compile-time choice of the activation (branches around each
 // of its uses cut the schedule into pieces), a (1 - a) as one multiply-add on halves, rows followed on the scalar unit instead of
 // divided out and images built from loads under way together took it from 1206 to 1050 us (0.65 M samples: 79 -> 65; 0.15 M: 35 -> 26),
 // the forward from 482 to 470 (40 -> 33; 17 -> 16).
 //
 // Backward recomputes the forward, then walks the chain back.  Weight gradients contract over the
-// samples, so they need each (delta, activation) pair with the samples on the k axis; a product with
-// a 0/1 selection matrix on the matrix cores transposes a tile exactly (fp16 values times one,
-// summed with zeros).  Every wavefront accumulates its share of dW in registers over all its tiles; the workgroup adds its
+// samples, so they need each (delta, activation) pair with the samples on the k axis: tiles are transposed through LDS.  Every wavefront accumulates its share of dW in registers over all its tiles; the workgroup adds its
 // wavefronts' shares up, writes the sum to the workspace once, and a second kernel folds the workgroups' in a fixed order.
 //
 // Appearance features (Sec. 4.4.3: a fixed per-image vector of 16 or 48 values as extra colour-net inputs) widen the
@@ -40,7 +38,7 @@ constexpr int kTotal = oWc3 + 3 * HC;
 
 // image chunks (1 KB each: 64 lanes x 8 halves)
 constexpr int cD1 = 0, cD2 = 4, cC1 = 8, cC2 = 12, cC3 = 20, kFwdChunks = 24;
-constexpr int cC3T = 24, cC2T = 26, cC1T = 34, cD2T = 38, cD1T = 40, cSelT = 44, cSelN = 46, kAllChunks = 48;
+constexpr int cC3T = 24, cC2T = 26, cC1T = 34, kAllChunks = 38;
 
 __device__ void build_forward_images(__half *lds, const __half *w)
 {
@@ -56,10 +54,6 @@ __device__ void build_backward_images(__half *lds, const __half *w)
     build_image<HC, HC, 3, 2, 1, 0, true>(lds + cC3T * 512, w + oWc3);
     build_image<HC, HC, HC, 2, 4, 0, true>(lds + cC2T * 512, w + oWc2);
     build_image<CI, NG, HC, 1, 4, 0, true>(lds + cC1T * 512, w + oWc1);     // direction inputs get no gradient
-    build_image<HD, HD, NG, 2, 1, 0, true>(lds + cD2T * 512, w + oWd2);
-    build_image<NF, NF, HD, 1, 4, 0, true>(lds + cD1T * 512, w + oWd1);
-    build_selection(lds + cSelT * 512, 0);
-    build_selection(lds + cSelN * 512, 1);
 }
 
 struct Tile {
@@ -326,6 +320,7 @@ colour_bwd_kernel(const __half *__restrict__ weights, const __half *__restrict__
 {
     __shared__ __attribute__((aligned(16))) __half lds[(kAllChunks + 2 * (NA / 16)) * 512];
     __shared__ float acc3[kWavesPerBlock * 2 * 3 * 32];
+    __shared__ __attribute__((aligned(16))) _Float16 scratch[kWavesPerBlock * kScratchHalves];
     build_forward_images(lds, weights);
     build_backward_images(lds, weights);
     if constexpr (NA > 0) build_image<NA, HC, NA, 2, NA / 16, 1, false>(lds + kAllChunks * 512, weights + kTotal);
@@ -340,6 +335,7 @@ colour_bwd_kernel(const __half *__restrict__ weights, const __half *__restrict__
     // registers next to the others.  Each wavefront keeps those 3 x 64 sums in LDS words of its own (one owner lane
     // per word, plain read-add-write, so the order of the additions is fixed).
     float *gWc3 = acc3 + (threadIdx.x >> 6) * (2 * 3 * 32);      // [input tile][row][column]
+    _Float16 *const tile0 = scratch + (threadIdx.x >> 6) * kScratchHalves, *const tile1 = tile0 + kTileHalves;
     if (h == 0) {
 #pragma unroll
         for (int k = 0; k < 6; ++k) gWc3[k * 32 + (lane_fixed & 31)] = 0.0f;
@@ -359,7 +355,6 @@ colour_bwd_kernel(const __half *__restrict__ weights, const __half *__restrict__
             dc[0] = c[3 * s]; dc[1] = c[3 * s + 1]; dc[2] = c[3 * s + 2];
         }
         forward_tile<NA, SIG>(lds, lane, t, kAllChunks);
-        const h8 selT0 = image(lds, cSelT, lane), selT1 = image(lds, cSelT + 1, lane);
 
         // ---- output layer of the colour net
         h8 d3 = zero8;
@@ -371,9 +366,9 @@ colour_bwd_kernel(const __half *__restrict__ weights, const __half *__restrict__
             }
         }
         h8 td[2][2], ta[2][2];      // transposed delta / activation: [feature tile][sample k-step]
-        transpose_half_tile(d3, selT0, td[0]);
-        transpose_tile(t.c2[0], t.c2[1], selT0, selT1, ta[0]);
-        transpose_tile(t.c2[2], t.c2[3], selT0, selT1, ta[1]);
+        transpose_half_tile(tile0, lane, d3, td[0]);
+        transpose_tile(tile1, lane, t.c2[0], t.c2[1], ta[0]);
+        transpose_tile(tile0, lane, t.c2[2], t.c2[3], ta[1]);
 #pragma unroll
         for (int it = 0; it < 2; ++it) {
             f16v part = mma(td[0][0], ta[it][0], zero16());
@@ -391,10 +386,10 @@ colour_bwd_kernel(const __half *__restrict__ weights, const __half *__restrict__
         h8 dl[4];
 #pragma unroll
         for (int ks = 0; ks < 4; ++ks) dl[ks] = delta_from<SIG ? 2 : 1>(g[ks >> 1], ks & 1, t.c2[ks]);
-        transpose_tile(dl[0], dl[1], selT0, selT1, td[0]);
-        transpose_tile(dl[2], dl[3], selT0, selT1, td[1]);
-        transpose_tile(t.c1[0], t.c1[1], selT0, selT1, ta[0]);
-        transpose_tile(t.c1[2], t.c1[3], selT0, selT1, ta[1]);
+        transpose_tile(tile0, lane, t.c1[0], t.c1[1], ta[0]);
+        transpose_tile(tile1, lane, t.c1[2], t.c1[3], ta[1]);
+        transpose_tile(tile0, lane, dl[0], dl[1], td[0]);
+        transpose_tile(tile1, lane, dl[2], dl[3], td[1]);
 #pragma unroll
         for (int ot = 0; ot < 2; ++ot)
 #pragma unroll
@@ -411,9 +406,9 @@ colour_bwd_kernel(const __half *__restrict__ weights, const __half *__restrict__
         // ---- first hidden layer of the colour net
 #pragma unroll
         for (int ks = 0; ks < 4; ++ks) dl[ks] = delta_from<SIG ? 2 : 1>(g[ks >> 1], ks & 1, t.c1[ks]);
-        transpose_tile(dl[0], dl[1], selT0, selT1, td[0]);
-        transpose_tile(dl[2], dl[3], selT0, selT1, td[1]);
-        transpose_tile(t.xc[0], t.xc[1], selT0, image(lds, cSelN + 1, lane), ta[0]);
+        transpose_tile<kTiled, kNatural>(tile0, lane, t.xc[0], t.xc[1], ta[0]);
+        transpose_tile(tile1, lane, dl[0], dl[1], td[0]);
+        transpose_tile(tile0, lane, dl[2], dl[3], td[1]);
 #pragma unroll
         for (int ot = 0; ot < 2; ++ot)
 #pragma unroll
@@ -485,22 +480,20 @@ density_bwd_kernel(const __half *__restrict__ weights, const __half *__restrict_
                    const h8 *__restrict__ dgeo, float loss_scale, uint32_t n_merged, float *__restrict__ dfeat, uint32_t *__restrict__ largest,
                    float *__restrict__ shares)
 {
-    // images: density layer 1 forward (4 chunks), Wd2^T (2), Wd1^T (4), selections (4)
-    constexpr int kD1 = 0, kD2T = 4, kD1T = 6, kST = 10, kSN = 12, kChunks = 14;
+    // images: density layer 1 forward (4 chunks), Wd2^T (2), Wd1^T (4); the share of the weight gradient takes their place
+    constexpr int kD1 = 0, kD2T = 4, kD1T = 6, kChunks = 12;
     __shared__ __attribute__((aligned(16))) __half lds[kChunks * 512];
+    __shared__ __attribute__((aligned(16))) _Float16 scratch[kWavesPerBlock * kScratchHalves];
     build_image<NF, HD, NF, 2, 2, 1, false>(lds + kD1 * 512, weights + oWd1);
     build_image<HD, HD, NG, 2, 1, 0, true>(lds + kD2T * 512, weights + oWd2);
     build_image<NF, NF, HD, 1, 4, 0, true>(lds + kD1T * 512, weights + oWd1);
-    build_selection(lds + kST * 512, 0);
-    build_selection(lds + kSN * 512, 1);
     __syncthreads();
     const int lane = threadIdx.x & 63, h = lane >> 5;
     const uint64_t n_tiles = (n_samples + 31) / 32;
     const uint64_t wave = (uint64_t)blockIdx.x * kWavesPerBlock + (uint32_t)__builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
     const uint64_t n_waves = (uint64_t)gridDim.x * kWavesPerBlock;
     const float inv_scale = 1.0f / loss_scale;
-    const h8 selT0 = image(lds, kST, lane), selT1 = image(lds, kST + 1, lane);
-    const h8 selN0 = image(lds, kSN, lane), selN1 = image(lds, kSN + 1, lane);
+    _Float16 *const tile0 = scratch + (threadIdx.x >> 6) * kScratchHalves, *const tile1 = tile0 + kTileHalves;
     const h8 zero8 = {0, 0, 0, 0, 0, 0, 0, 0};
 
     float most = 0.0f;                                          // largest magnitude of the feature gradient, before the division by the loss scale
@@ -534,9 +527,9 @@ density_bwd_kernel(const __half *__restrict__ weights, const __half *__restrict_
         for (int ks = 0; ks < 4; ++ks) t.h1[ks] = pack_half<1>(acc[ks >> 1], ks & 1);
 
         h8 td[2][2], ta[2][2];
-        transpose_half_tile(dg, selT0, td[0]);
-        transpose_tile(t.h1[0], t.h1[1], selT0, selT1, ta[0]);
-        transpose_tile(t.h1[2], t.h1[3], selT0, selT1, ta[1]);
+        transpose_half_tile(tile0, lane, dg, td[0]);
+        transpose_tile(tile1, lane, t.h1[0], t.h1[1], ta[0]);
+        transpose_tile(tile0, lane, t.h1[2], t.h1[3], ta[1]);
 #pragma unroll
         for (int it = 0; it < 2; ++it)
 #pragma unroll
@@ -548,9 +541,9 @@ density_bwd_kernel(const __half *__restrict__ weights, const __half *__restrict_
         h8 dl[4];
 #pragma unroll
         for (int ks = 0; ks < 4; ++ks) dl[ks] = delta_from<1>(g[ks >> 1], ks & 1, t.h1[ks]);
-        transpose_tile(dl[0], dl[1], selT0, selT1, td[0]);
-        transpose_tile(dl[2], dl[3], selT0, selT1, td[1]);
-        transpose_tile(t.x0[0], t.x0[1], selN0, selN1, ta[0]);
+        transpose_tile<kNatural>(tile1, lane, t.x0[0], t.x0[1], ta[0]);
+        transpose_tile(tile0, lane, dl[0], dl[1], td[0]);
+        transpose_tile(tile1, lane, dl[2], dl[3], td[1]);
 #pragma unroll
         for (int ot = 0; ot < 2; ++ot)
 #pragma unroll

@@ -1,4 +1,4 @@
-// Matrix-core building blocks of the field MLPs: operand images, the product, transposes on the matrix cores, weight-gradient
+// Matrix-core building blocks of the field MLPs: operand images, the product, transposes, weight-gradient
 // shares.  Internal, not part of the ABI.
 //
 // Operand and result layouts (lane = 32 h + c, element j / register r):
@@ -49,20 +49,6 @@ __device__ __forceinline__ void build_image(__half *img, const __half *__restric
         }
         reinterpret_cast<h8 *>(img)[slot] = v;
     }
-}
-
-__device__ __forceinline__ void build_selection(__half *img, int kind)
-{
-    const int slot = threadIdx.x;
-    if (slot >= 2 * 64) return;
-    const int lane = slot & 63, p = slot >> 6;
-    h8 v;
-#pragma unroll
-    for (int j = 0; j < 8; ++j) {
-        const int f = (kind == 0 ? feat_tiled(p, lane >> 5, j) : feat_natural(p, lane >> 5, j)) & 31;
-        v[j] = (_Float16)(f == (lane & 31) ? 1.0f : 0.0f);
-    }
-    reinterpret_cast<h8 *>(img)[slot] = v;
 }
 
 __device__ __forceinline__ h8 image(const __half *lds, int chunk, int lane)
@@ -125,22 +111,57 @@ __device__ __forceinline__ h8 pack_half(const f16v &c, int p)
     return out;
 }
 
-// transpose of one 32-feature tile of a packed tensor: x0 / x1 are the two k-steps that hold the tile,
-// sel0 / sel1 the matching selection images; result: the two sample k-steps of the transposed tile
-__device__ __forceinline__ void transpose_tile(h8 x0, h8 x1, h8 sel0, h8 sel1, h8 out[2])
+// Transposes of 32-feature tiles through LDS, for the weight gradients, which need the samples on the k axis.  A wavefront writes a tile
+// as rows of a sample's features (a lane holds eight of them per k-step, in two stretches of four) and reads columns: the
+// transposing read gives a lane four samples of one feature.  What the lane then holds in slot j of sample k-step p is sample
+// feat_tiled(p, h, j) of feature lane & 31.  LDS operations of a wavefront stay in order, so a tile's place can be used again at once.
+// Rows are 72 bytes apart: writes of 32 samples fall on different banks.
+// (Products with 0/1 selection matrices on the matrix cores do the same, 19 of then 73 in the colour kernel, with a result tile to round
+// and pack for each: 0.65 M samples, colour and density kernel 65 + 32 us against 64 + 30; 5.1 M with 48 appearance inputs 548 + 228 against
+// 530 + 222.  The colour kernel's chain of dependent products and LDS round trips at two wavefronts per SIMD bounds both forms: as
+// straight-line code without the branches around its loads and its output layer it is slower, 1050 against 1018 us at 13.3 M samples.)
+constexpr int kTileRow = 36, kTileHalves = 32 * kTileRow, kScratchHalves = 2 * kTileHalves;       // two tiles per wavefront
+
+typedef _Float16 h4 __attribute__((ext_vector_type(4)));
+enum TileKind { kTiled, kNatural };
+
+// k-step ks of a packed tensor (its features 16 ks .. 16 ks + 15) into a tile
+template <TileKind KIND>
+__device__ __forceinline__ void put_step(_Float16 *tile, int lane, int ks, h8 x)
 {
-    f16v c = zero16();
-    c = mma(x0, sel0, c);
-    c = mma(x1, sel1, c);
-    out[0] = pack_half<0>(c, 0);
-    out[1] = pack_half<0>(c, 1);
+    _Float16 *row = tile + (lane & 31) * kTileRow + 16 * ks + (KIND == kTiled ? 4 : 8) * (lane >> 5);
+    *reinterpret_cast<h4 *>(row) = __builtin_shufflevector(x, x, 0, 1, 2, 3);
+    *reinterpret_cast<h4 *>(row + (KIND == kTiled ? 8 : 4)) = __builtin_shufflevector(x, x, 4, 5, 6, 7);
 }
-__device__ __forceinline__ void transpose_half_tile(h8 x0, h8 sel0, h8 out[2])
+
+// the two sample k-steps of the transposed tile
+__device__ __forceinline__ void get_transposed(const _Float16 *tile, int lane, h8 out[2])
 {
-    f16v c = zero16();
-    c = mma(x0, sel0, c);
-    out[0] = pack_half<0>(c, 0);
-    out[1] = pack_half<0>(c, 1);
+    typedef __fp16 g4 __attribute__((ext_vector_type(4)));
+    typedef __attribute__((address_space(3))) g4 *lds_g4;
+    const int i = lane & 15;
+    const _Float16 *at = tile + (4 * (lane >> 5) + (i >> 2)) * kTileRow + (lane & 16) + 4 * (i & 3);
+#pragma unroll
+    for (int p = 0; p < 2; ++p) {
+        const h4 lo = __builtin_bit_cast(h4, __builtin_amdgcn_ds_read_tr16_b64_v4f16((lds_g4)(at + 16 * p * kTileRow)));
+        const h4 hi = __builtin_bit_cast(h4, __builtin_amdgcn_ds_read_tr16_b64_v4f16((lds_g4)(at + (16 * p + 8) * kTileRow)));
+        out[p] = __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7);
+    }
+}
+
+template <TileKind KIND0 = kTiled, TileKind KIND1 = KIND0>
+__device__ __forceinline__ void transpose_tile(_Float16 *tile, int lane, h8 x0, h8 x1, h8 out[2])
+{
+    put_step<KIND0>(tile, lane, 0, x0);
+    put_step<KIND1>(tile, lane, 1, x1);
+    get_transposed(tile, lane, out);
+}
+// features 16..31 of the result are whatever the tile held: rows or columns of a weight gradient that nobody reads
+template <TileKind KIND = kTiled>
+__device__ __forceinline__ void transpose_half_tile(_Float16 *tile, int lane, h8 x0, h8 out[2])
+{
+    put_step<KIND>(tile, lane, 0, x0);
+    get_transposed(tile, lane, out);
 }
 
 // delta = fp16(g * act'(a)) for one k-step; a is the packed (rounded) activation

@@ -13,9 +13,9 @@ using namespace dg_mlp_mfma;
 constexpr int sNF = 8, sHD = 32, sNG = 16, sND = 4, sHC = 32, sCI = sNG + sND;
 constexpr int pWd1 = 0, pWd2 = pWd1 + sHD * sNF, pWc1 = pWd2 + sNG * sHD, pWc3 = pWc1 + sHC * sCI, sTotal = pWc3 + 3 * sHC;
 
-// image chunks: forward, then the transposed weights and the selections of the backward pass
+// image chunks: forward, then the transposed weights of the backward pass
 constexpr int iD1 = 0, iD2 = 1, iC1 = 3, iC3 = 5, kFwdImages = 7;
-constexpr int iC3T = 7, iC1T = 8, iD2T = 10, iD1T = 11, iSelT = 13, iSelN = 15, kAllImages = 17;
+constexpr int iC3T = 7, iC1T = 8, iD2T = 10, iD1T = 11, kAllImages = 13;
 
 __device__ void build_small_forward(__half *lds, const __half *w)
 {
@@ -31,8 +31,6 @@ __device__ void build_small_backward(__half *lds, const __half *w)
     build_image<sCI, sNG, sHC, 1, 2, 0, true>(lds + iC1T * 512, w + pWc1);        // direction inputs get no gradient
     build_image<sHD, sHD, sNG, 1, 1, 0, true>(lds + iD2T * 512, w + pWd2);
     build_image<sNF, sNF, sHD, 1, 2, 0, true>(lds + iD1T * 512, w + pWd1);
-    build_selection(lds + iSelT * 512, 0);
-    build_selection(lds + iSelN * 512, 1);
 }
 
 struct SmallTile {
@@ -103,13 +101,14 @@ small_bwd_kernel(const __half *__restrict__ weights, const __half *__restrict__ 
                  float *__restrict__ shares)
 {
     __shared__ __attribute__((aligned(16))) __half lds[kAllImages * 512];
+    __shared__ __attribute__((aligned(16))) _Float16 scratch[kWavesPerBlock * kScratchHalves];
     build_small_forward(lds, weights);
     build_small_backward(lds, weights);
     __syncthreads();
     const int lane = threadIdx.x & 63, h = lane >> 5;
     const uint64_t n_tiles = (n_samples + 31) / 32, n_waves = (uint64_t)gridDim.x * kWavesPerBlock;
     const float inv_scale = 1.0f / loss_scale;
-    const h8 selT0 = image(lds, iSelT, lane), selT1 = image(lds, iSelT + 1, lane), selN0 = image(lds, iSelN, lane), selN1 = image(lds, iSelN + 1, lane);
+    _Float16 *const tile0 = scratch + (threadIdx.x >> 6) * kScratchHalves, *const tile1 = tile0 + kTileHalves;
     f16v gWd1 = zero16(), gWd2 = zero16(), gWc1 = zero16(), gWc3 = zero16();
     for (uint64_t tile = (uint64_t)blockIdx.x * kWavesPerBlock + (threadIdx.x >> 6); tile < n_tiles; tile += n_waves) {
         const uint64_t n = tile * 32 + (lane & 31);
@@ -132,8 +131,8 @@ small_bwd_kernel(const __half *__restrict__ weights, const __half *__restrict__ 
             }
         }
         h8 td[2], ta[2];                        // transposed delta / activation: samples on the k axis
-        transpose_half_tile(d3, selT0, td);
-        transpose_tile(t.c1[0], t.c1[1], selT0, selT1, ta);
+        transpose_half_tile(tile0, lane, d3, td);
+        transpose_tile(tile1, lane, t.c1[0], t.c1[1], ta);
         gWc3 = mma(td[0], ta[0], gWc3);
         gWc3 = mma(td[1], ta[1], gWc3);
         f16v g = mma(image(lds, iC3T, lane), d3, zero16());
@@ -141,8 +140,8 @@ small_bwd_kernel(const __half *__restrict__ weights, const __half *__restrict__ 
         h8 dl[2];
 #pragma unroll
         for (int ks = 0; ks < 2; ++ks) dl[ks] = act_c ? delta_from<2>(g, ks, t.c1[ks]) : delta_from<1>(g, ks, t.c1[ks]);
-        transpose_tile(dl[0], dl[1], selT0, selT1, td);
-        transpose_tile(t.xc[0], t.xc[1], selT0, selN1, ta);
+        transpose_tile(tile0, lane, dl[0], dl[1], td);
+        transpose_tile<kTiled, kNatural>(tile1, lane, t.xc[0], t.xc[1], ta);
         gWc1 = mma(td[0], ta[0], gWc1);
         gWc1 = mma(td[1], ta[1], gWc1);
         f16v gx = mma(image(lds, iC1T, lane), dl[0], zero16());
@@ -153,16 +152,16 @@ small_bwd_kernel(const __half *__restrict__ weights, const __half *__restrict__ 
             gx[0] += pass0 ? loss_scale * ds * t.sigma : 0.0f;
         }
         const h8 dgeo = pack_half<0>(gx, 0);
-        transpose_half_tile(dgeo, selT0, td);
-        transpose_tile(t.h1[0], t.h1[1], selT0, selT1, ta);
+        transpose_half_tile(tile0, lane, dgeo, td);
+        transpose_tile(tile1, lane, t.h1[0], t.h1[1], ta);
         gWd2 = mma(td[0], ta[0], gWd2);
         gWd2 = mma(td[1], ta[1], gWd2);
         g = mma(image(lds, iD2T, lane), dgeo, zero16());
         // hidden layer of the density net
 #pragma unroll
         for (int ks = 0; ks < 2; ++ks) dl[ks] = delta_from<1>(g, ks, t.h1[ks]);
-        transpose_tile(dl[0], dl[1], selT0, selT1, td);
-        transpose_half_tile(t.x0, selN0, ta);
+        transpose_tile(tile0, lane, dl[0], dl[1], td);
+        transpose_half_tile<kNatural>(tile1, lane, t.x0, ta);
         gWd1 = mma(td[0], ta[0], gWd1);
         gWd1 = mma(td[1], ta[1], gWd1);
         f16v gf = mma(image(lds, iD1T, lane), dl[0], zero16());
