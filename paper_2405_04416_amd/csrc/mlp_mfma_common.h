@@ -82,15 +82,9 @@ __device__ __forceinline__ float fast_sigmoid(float x)
 __device__ __forceinline__ float full_sigmoid(float x) { return 1.0f / (1.0f + expf(-x)); }
 __device__ __forceinline__ float clip15(float x) { return fminf(fmaxf(x, -15.0f), 15.0f); }
 
-// max(x, 0) on four pairs of halves, one instruction per pair
-__device__ __forceinline__ h8 relu_pairs(h8 x)
-{
-    typedef uint32_t u4 __attribute__((ext_vector_type(4)));
-    u4 w = __builtin_bit_cast(u4, x);
-#pragma unroll
-    for (int i = 0; i < 4; ++i) asm("v_pk_max_f16 %0, %1, 0" : "=v"(w[i]) : "v"(w[i]));
-    return __builtin_bit_cast(h8, w);
-}
+// max(x, 0) on four pairs of halves, one instruction per pair.  Not in inline assembly: the compiler keeps two wait states between a vector
+// instruction and a matrix instruction that reads its result, and does not see one that stands there.
+__device__ __forceinline__ h8 relu_pairs(h8 x) { return __builtin_elementwise_max(x, (h8)(_Float16)0.0f); }
 
 // registers 8p .. 8p+7 of a result tile, activated, rounded to fp16 and packed: k-step (m, p) of the next operand
 template <int ACT>   // 0 identity, 1 ReLU, 2 sigmoid, 3 sigmoid at full fp32 precision
