@@ -214,6 +214,12 @@ int dg_order_samples(const dg_order_desc *order, const float *u, const uint32_t 
  * the i-th sample of the list. */
 int dg_hashgrid_encode_fwd_ordered(const dg_grid_desc *desc, const float *table, const void *ordered, uint64_t N,
                                    uint32_t by_position, void *feat, void *stream);
+/* The same, split: rows [N, DG_SPLIT_LEVELS * F] of the first DG_SPLIT_LEVELS levels, then the planes [L - DG_SPLIT_LEVELS, N, F] of the
+ * others, each where it lies among planes of all levels; by_position the planes are in the list's order too, else from u [N,3] in
+ * the samples' own. */
+#define DG_SPLIT_LEVELS 12
+int dg_hashgrid_encode_fwd_split(const dg_grid_desc *desc, const float *table, const void *ordered, const float *u, uint64_t N,
+                                 uint32_t by_position, void *feat, void *stream);
 /* dg_hashgrid_encode_bwd on the sorted list.  dfeat: rows [N, 2 * n_merged] fp32 of the merged levels (16-byte aligned, in
  * the samples' original order), then the planes [L - n_merged, N, 2] of the others -- as dg_mlp_bwd_rows writes it; u [N,3]
  * the samples in their original order.  *largest: device word, the bit pattern of a float that no |dfeat| exceeds.
@@ -393,6 +399,12 @@ int dg_mlp_composite_fwd_rows(const dg_mlp_desc *desc, const void *weights, cons
 int dg_mlp_bwd_rows(const dg_mlp_desc *desc, const void *weights, const void *feat, const void *dir_enc, const void *app,
                     uint32_t S, uint64_t N, const float *dsigma, const float *drgb, float loss_scale, uint32_t n_merged,
                     float *dfeat, uint32_t *largest, float *dW, void *ws, size_t ws_bytes, void *stream);
+/* dg_mlp_fwd_rows and dg_mlp_bwd_rows on features as dg_hashgrid_encode_fwd_split writes them. */
+int dg_mlp_fwd_split(const dg_mlp_desc *desc, const void *weights, const void *feat, const void *dir_enc, const void *app,
+                     uint32_t S, uint64_t N, float *sigma, float *rgb, void *stream);
+int dg_mlp_bwd_split(const dg_mlp_desc *desc, const void *weights, const void *feat, const void *dir_enc, const void *app,
+                     uint32_t S, uint64_t N, const float *dsigma, const float *drgb, float loss_scale, uint32_t n_merged,
+                     float *dfeat, uint32_t *largest, float *dW, void *ws, size_t ws_bytes, void *stream);
 
 /* One Adam step (Sec. 5.1 names the optimiser; the update is Algorithm 1 of Kingma & Ba) on n fp32 values, in place:
  *   g' = g + l2 * p;  m = beta1 m + (1 - beta1) g';  v = beta2 v + (1 - beta2) g'^2;
@@ -456,6 +468,9 @@ int dg_occ_update(float *density, uint32_t n_cells, const uint32_t *cell, const 
  * aligned) if rows.  The cell of candidate i is cell[i * cell_stride].  Only for the 32-64-16 density net (DG_ERR_UNSUPPORTED). */
 int dg_occ_evaluate(const dg_mlp_desc *desc, const void *weights, const void *feat, uint32_t rows, const uint32_t *cell,
                     uint32_t cell_stride, uint64_t M, float *density, uint32_t n_cells, void *stream);
+/* The same on features as dg_hashgrid_encode_fwd_split writes them. */
+int dg_occ_evaluate_split(const dg_mlp_desc *desc, const void *weights, const void *feat, const uint32_t *cell,
+                          uint32_t cell_stride, uint64_t M, float *density, uint32_t n_cells, void *stream);
 /* bit of cell c = density[c] > threshold; *n_set (device, may be NULL) "+=" the number of set bits */
 int dg_occ_bits(const float *density, uint32_t n_cells, float threshold, uint32_t *bits, uint32_t *n_set,
                 void *stream);

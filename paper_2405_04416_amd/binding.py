@@ -109,6 +109,11 @@ _SIGNATURES = {
     "dg_mlp_fwd_rows": (C.c_int, [C.POINTER(MlpDesc)] + [C.c_void_p] * 4 + [C.c_uint32, C.c_uint64] + [C.c_void_p] * 3),
     "dg_mlp_composite_fwd_rows": (C.c_int, [C.POINTER(MlpDesc)] + [C.c_void_p] * 4 + [C.c_uint32, C.c_uint32] + [C.c_void_p] * 4 + [C.c_uint32]
                                   + [C.c_void_p] * 4),
+    "dg_hashgrid_encode_fwd_split": (C.c_int, [C.POINTER(GridDesc)] + [C.c_void_p] * 3 + [C.c_uint64, C.c_uint32, C.c_void_p, C.c_void_p]),
+    "dg_mlp_fwd_split": (C.c_int, [C.POINTER(MlpDesc)] + [C.c_void_p] * 4 + [C.c_uint32, C.c_uint64] + [C.c_void_p] * 3),
+    "dg_mlp_bwd_split": (C.c_int, [C.POINTER(MlpDesc)] + [C.c_void_p] * 4 + [C.c_uint32, C.c_uint64, C.c_void_p, C.c_void_p, C.c_float, C.c_uint32]
+                         + [C.c_void_p] * 4 + [C.c_size_t, C.c_void_p]),
+    "dg_occ_evaluate_split": (C.c_int, [C.POINTER(MlpDesc), C.c_void_p, C.c_void_p, C.c_void_p, C.c_uint32, C.c_uint64, C.c_void_p, C.c_uint32, C.c_void_p]),
     "dg_mlp_bwd_rows": (C.c_int, [C.POINTER(MlpDesc)] + [C.c_void_p] * 4 + [C.c_uint32, C.c_uint64, C.c_void_p, C.c_void_p, C.c_float, C.c_uint32]
                         + [C.c_void_p] * 4 + [C.c_size_t, C.c_void_p]),
     "dg_appearance_rows": (C.c_int, [C.c_void_p, C.c_void_p, C.c_void_p, C.c_uint64, C.c_uint32, C.c_void_p, C.c_void_p]),
@@ -368,6 +373,15 @@ def dg_hashgrid_encode_fwd_ordered(desc, table, ordered, N, feat, by_position=Fa
                                                 _ptr(feat, torch.float16), _stream()))
 
 
+SPLIT_LEVELS = 12
+
+
+def dg_hashgrid_encode_fwd_split(desc, table, ordered, u, N, feat, by_position=False):
+    assert ordered.numel() >= 4 * N and u.numel() >= 3 * N and feat.numel() >= 32 * N
+    _check(lib().dg_hashgrid_encode_fwd_split(C.byref(desc), _ptr(table, torch.float32), _ptr(ordered, torch.float32), _ptr(u, torch.float32), N,
+                                              1 if by_position else 0, _ptr(feat, torch.float16), _stream()))
+
+
 def dg_hashgrid_encode_bwd_ordered_workspace_bytes(desc, order, N):
     return int(lib().dg_hashgrid_encode_bwd_ordered_workspace_bytes(C.byref(desc), C.byref(order), N))
 
@@ -499,6 +513,12 @@ def dg_occ_evaluate(desc, weights, feat, rows, cell, cell_stride, M, density):
                                  cell_stride, M, _ptr(density, torch.float32), density.numel(), _stream()))
 
 
+def dg_occ_evaluate_split(desc, weights, feat, cell, cell_stride, M, density):
+    assert feat.numel() >= desc.n_feat * M and (M == 0 or cell.numel() > (M - 1) * cell_stride)
+    _check(lib().dg_occ_evaluate_split(C.byref(desc), _ptr(weights, torch.float16), _ptr(feat, torch.float16), _ptr(cell, torch.int32), cell_stride, M,
+                                       _ptr(density, torch.float32), density.numel(), _stream()))
+
+
 def dg_occ_bits(density, threshold, bits, n_set=None):
     assert bits.numel() >= (density.numel() + 31) // 32
     _check(lib().dg_occ_bits(_ptr(density, torch.float32), density.numel(), threshold, _ptr(bits, torch.int32),
@@ -568,6 +588,11 @@ def dg_mlp_fwd_rows(desc, weights, feat, dir_enc, app, S, N, sigma, rgb):
     _mlp_fwd_app(lib().dg_mlp_fwd_rows, desc, weights, feat, dir_enc, app, S, N, sigma, rgb)
 
 
+def dg_mlp_fwd_split(desc, weights, feat, dir_enc, app, S, N, sigma, rgb):
+    assert feat.numel() >= N * desc.n_feat
+    _mlp_fwd_app(lib().dg_mlp_fwd_split, desc, weights, feat, dir_enc, app, S, N, sigma, rgb)
+
+
 def _mlp_composite_fwd(entry, desc, weights, feat, dir_enc, app, S, n_seg, delta, t, seg_ray, seg_slot, k_max, Ck, Tk, Dk):
     N = n_seg * S
     assert dir_enc.numel() >= n_seg * desc.n_dir and (app is None or app.numel() >= n_seg * desc.n_app)
@@ -597,11 +622,19 @@ def dg_mlp_bwd_app(desc, weights, feat, dir_enc, app, S, N, dsigma, drgb, loss_s
                                 ws.numel() * ws.element_size(), _stream()))
 
 
-def dg_mlp_bwd_rows(desc, weights, feat, dir_enc, app, S, N, dsigma, drgb, loss_scale, n_merged, dfeat, largest, dW, ws):
+def _mlp_bwd_rows(entry, desc, weights, feat, dir_enc, app, S, N, dsigma, drgb, loss_scale, n_merged, dfeat, largest, dW, ws):
     rows = -(-N // S)
     assert dir_enc.numel() >= rows * desc.n_dir and (app is None or app.numel() >= rows * desc.n_app)
     assert dW.numel() >= dg_mlp_weight_count(desc) and min(feat.numel(), dfeat.numel()) >= N * desc.n_feat
-    _check(lib().dg_mlp_bwd_rows(C.byref(desc), _ptr(weights, torch.float16), _ptr(feat, torch.float16), _ptr(dir_enc, torch.float16),
+    _check(entry(C.byref(desc), _ptr(weights, torch.float16), _ptr(feat, torch.float16), _ptr(dir_enc, torch.float16),
                                  _ptr(app, torch.float16, True), S, N, _ptr(dsigma, torch.float32), _ptr(drgb, torch.float32),
                                  loss_scale, n_merged, _ptr(dfeat, torch.float32), _ptr(largest, torch.int32), _ptr(dW, torch.float32), _ptr(ws),
                                  ws.numel() * ws.element_size(), _stream()))
+
+
+def dg_mlp_bwd_rows(*args):
+    _mlp_bwd_rows(lib().dg_mlp_bwd_rows, *args)
+
+
+def dg_mlp_bwd_split(*args):
+    _mlp_bwd_rows(lib().dg_mlp_bwd_split, *args)

@@ -33,6 +33,11 @@ inline bool aligned(const void *p, size_t a) { return (reinterpret_cast<uintptr_
 
 constexpr int kWave = 64;
 
+// How the features of a batch lie in memory: level-major planes, rows of all levels of a sample, or rows of the first kSplitLevels
+// levels followed by the planes of the others (plane l lies where it always does)
+enum FeatureLayout { kPlanes, kRows, kSplit };
+constexpr int kSplitLevels = DG_SPLIT_LEVELS;
+
 // argument check shared by the encode entry points (encode.hip)
 int check_grid_desc(const dg_grid_desc *d, const char *who);
 
@@ -51,17 +56,17 @@ int brick_bwd(const char *who, const dg_grid_desc *d, const dg_order_desc *order
               const float *dfeat, const uint32_t *largest, uint64_t N, float *dtable, double *wide, hipStream_t st);
 
 // Matrix-core path of the 32-64-16 / (32 + n_app)-64-64-3 field MLPs (mlp_mfma.hip); n_app = 0, 16 or 48.
-// rows: features (and the gradient of levels below n_merged) are sample-major rows instead of planes.
+// layout: of the features; other than kPlanes, the gradient of levels below n_merged comes as sample-major rows.
 size_t mlp_mfma_workspace_bytes(uint64_t N, uint32_t n_app, uint32_t S);
 size_t mlp_mfma_weight_count(uint32_t n_app);
-void mlp_mfma_density_max(const void *weights, const void *feat, bool rows, const uint32_t *cell, uint32_t cell_stride, uint64_t N, float *density,
+void mlp_mfma_density_max(const void *weights, const void *feat, FeatureLayout layout, const uint32_t *cell, uint32_t cell_stride, uint64_t N, float *density,
                           uint32_t n_cells, hipStream_t st);
-void mlp_mfma_fwd(const void *weights, const void *feat, bool rows, const void *dir_enc, const void *app, uint32_t n_app, uint32_t S,
+void mlp_mfma_fwd(const void *weights, const void *feat, FeatureLayout layout, const void *dir_enc, const void *app, uint32_t n_app, uint32_t S,
                   uint64_t N, uint32_t act_c, float *sigma, float *rgb, hipStream_t st);
-void mlp_mfma_render(const void *weights, const void *feat, bool rows, const void *dir_enc, const void *app, uint32_t n_app, uint32_t S,
+void mlp_mfma_render(const void *weights, const void *feat, FeatureLayout layout, const void *dir_enc, const void *app, uint32_t n_app, uint32_t S,
                      uint32_t n_seg, uint32_t act_c, const float *delta, const float *t, const uint32_t *seg_ray,
                      const uint32_t *seg_slot, uint32_t k_max, float *Ck, float *Tk, float *Dk, hipStream_t st);
-void mlp_mfma_bwd(const void *weights, const void *feat, bool rows, uint32_t n_merged, const void *dir_enc, const void *app, uint32_t n_app,
+void mlp_mfma_bwd(const void *weights, const void *feat, FeatureLayout layout, uint32_t n_merged, const void *dir_enc, const void *app, uint32_t n_app,
                   uint32_t S, uint64_t N, uint32_t act_c, const float *dsigma, const float *drgb, float loss_scale, float *dfeat, uint32_t *largest,
                   float *dW, void *ws, hipStream_t st);
 

@@ -56,42 +56,12 @@ encode_fwd_pair_kernel(dg_grid_desc g, const float2 *__restrict__ table, const f
     const bool live = s < N;
     const uint64_t n = live ? s : N - 1;                 // every lane stays in for the exchange
     const float uu[3] = {u[3 * n], u[3 * n + 1], u[3 * n + 2]};
-    const uint32_t mask = (1u << g.log2_T) - 1u;
-    const LevelGeom lv = level_of(g, l);
-    uint32_t cell[3], e[4];
-    float frac[3];
-    locate(lv, uu, cell, frac);
-    if (lv.dense) {
-        const uint32_t nx = lv.res[0] + 1u, nxy = nx * (lv.res[1] + 1u);
-        const uint32_t base = cell[0] + cx + nx * cell[1] + nxy * cell[2];
-#pragma unroll
-        for (int k = 0; k < 4; ++k) e[k] = base + (k & 1) * nx + (k >> 1) * nxy;
-    } else {
-        const uint32_t hy0 = cell[1] * kPrimeY, hy1 = hy0 + kPrimeY;
-        const uint32_t hz0 = cell[2] * kPrimeZ, hz1 = hz0 + kPrimeZ;
-#pragma unroll
-        for (int k = 0; k < 4; ++k) e[k] = ((cell[0] + cx) ^ ((k & 1) ? hy1 : hy0) ^ ((k & 2) ? hz1 : hz0)) & mask;
-    }
-    const float wx = cx ? frac[0] : 1.0f - frac[0];
-    const float wy[2] = {1.0f - frac[1], frac[1]}, wz[2] = {1.0f - frac[2], frac[2]};
-    float2 v[4];
-#pragma unroll
-    for (int k = 0; k < 4; ++k) v[k] = table[(size_t)lv.offset + e[k]];
-    float f0 = 0.0f, f1 = 0.0f;
-#pragma unroll
-    for (int k = 0; k < 4; ++k) {
-        const float w = wx * wy[k & 1] * wz[k >> 1];
-        f0 = fmaf(w, v[k].x, f0);
-        f1 = fmaf(w, v[k].y, f1);
-    }
-    // the partner's half: lanes swapped within pairs (quad_perm 1, 0, 3, 2)
-    f0 += __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(f0), 0xB1, 0xF, 0xF, true));
-    f1 += __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(f1), 0xB1, 0xF, 0xF, true));
+    const float2 f = gather_pair(level_of(g, l), (1u << g.log2_T) - 1u, table, uu, cx);
     if (!live || cx) return;
     if (kHalf) {
-        reinterpret_cast<__half2 *>(feat)[(size_t)l * N + n] = __floats2half2_rn(f0, f1);
+        reinterpret_cast<__half2 *>(feat)[(size_t)l * N + n] = __floats2half2_rn(f.x, f.y);
     } else {
-        reinterpret_cast<float2 *>(feat)[(size_t)l * N + n] = make_float2(f0, f1);
+        reinterpret_cast<float2 *>(feat)[(size_t)l * N + n] = f;
     }
 }
 

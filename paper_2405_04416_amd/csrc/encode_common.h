@@ -96,6 +96,42 @@ __device__ __forceinline__ double from_low_bits(unsigned long long held)
     return __longlong_as_double((long long)((unsigned long long)high << 32 | (uint32_t)held)) - 0x1.4p52;
 }
 
+// Features of one sample at one level by two lanes: cx = 0 takes the four corners with x of the cell, its neighbour cx = 1 those with x + 1
+// -- the two entries of an x-pair nearly always share a cache line, which then costs one look-up -- and a DPP move adds the halves.
+__device__ __forceinline__ float2 gather_pair(const LevelGeom &lv, uint32_t mask, const float2 *__restrict__ table, const float (&uu)[3], uint32_t cx)
+{
+    uint32_t cell[3], e[4];
+    float frac[3];
+    locate(lv, uu, cell, frac);
+    if (lv.dense) {
+        const uint32_t nx = lv.res[0] + 1u, nxy = nx * (lv.res[1] + 1u);
+        const uint32_t base = cell[0] + cx + nx * cell[1] + nxy * cell[2];
+#pragma unroll
+        for (int k = 0; k < 4; ++k) e[k] = base + (k & 1) * nx + (k >> 1) * nxy;
+    } else {
+        const uint32_t hy0 = cell[1] * kPrimeY, hy1 = hy0 + kPrimeY;
+        const uint32_t hz0 = cell[2] * kPrimeZ, hz1 = hz0 + kPrimeZ;
+#pragma unroll
+        for (int k = 0; k < 4; ++k) e[k] = ((cell[0] + cx) ^ ((k & 1) ? hy1 : hy0) ^ ((k & 2) ? hz1 : hz0)) & mask;
+    }
+    const float wx = cx ? frac[0] : 1.0f - frac[0];
+    const float wy[2] = {1.0f - frac[1], frac[1]}, wz[2] = {1.0f - frac[2], frac[2]};
+    float2 v[4];
+#pragma unroll
+    for (int k = 0; k < 4; ++k) v[k] = table[(size_t)lv.offset + e[k]];
+    float f0 = 0.0f, f1 = 0.0f;
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+        const float w = wx * wy[k & 1] * wz[k >> 1];
+        f0 = fmaf(w, v[k].x, f0);
+        f1 = fmaf(w, v[k].y, f1);
+    }
+    // the partner's half: lanes swapped within pairs (quad_perm 1, 0, 3, 2)
+    f0 += __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(f0), 0xB1, 0xF, 0xF, true));
+    f1 += __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(f1), 0xB1, 0xF, 0xF, true));
+    return make_float2(f0, f1);
+}
+
 // value of the lane below (lane - 1) in the wavefront; lane 0 gets its own.  A DPP move: no LDS traffic, no wait.
 __device__ __forceinline__ uint32_t from_lane_below(uint32_t v)
 {

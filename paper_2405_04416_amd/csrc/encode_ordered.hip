@@ -10,21 +10,23 @@ namespace {
 
 using namespace dg_encode;
 using namespace dg_order;
+using dg::kSplitLevels;
 
 constexpr int kBlock = 256;
 constexpr uint32_t kXcds = 8;
 
-// Two lanes per sample (lane 2i the four corners with cx = 0, lane 2i + 1 those with cx = 1: the two entries of an x-pair
-// nearly always share a cache line, which then costs one look-up), all 16 levels.  Consecutive workgroups of an XCD take
+// Two lanes per sample (gather_pair), level after level of the same sample.  Consecutive workgroups of an XCD take
 // consecutive samples (workgroups are handed out to the XCDs in turn), so the lines that neighbours share meet in one L2.
-// The even lane keeps levels 0..7, the odd lane levels 8..15: each writes half of the sample's row.
+// The even lane keeps the lower half of the levels, the odd lane the upper half: each writes half of the sample's row.
 // Bound by the cache lines fetched past the L2 on the levels too fine for neighbours to share them (T = 2^24, 33.5 M samples:
 // levels 13..15 take 7.3 of 10.4 ms at 51 G lines/s, levels 0..9 1.7 ms), by instructions and vector-cache look-ups on the
 // others.  Against the gather in ray order, level after level: 33.5 M samples, T = 2^24 21.6 -> 10.4 ms; 19.8 M, T = 2^24
 // 12.3 -> 6.8; 13.3 M, T = 2^19 2.38 -> 1.49; scattered rows of 64 bytes instead of planes cost 0.8, 0.47 and 0.3 ms of it.
+// LEVELS: 16, or 12 where the finer levels go through encode_planes_kernel; a row is LEVELS x 4 bytes.
+template <int LEVELS>
 __global__ void __launch_bounds__(kBlock)
 encode_fwd_ordered_kernel(dg_grid_desc g, const float2 *__restrict__ table, const float4 *__restrict__ ordered, uint64_t N,
-                          bool by_position, uint4 *__restrict__ feat, uint32_t blocks_per_xcd)
+                          bool by_position, uint32_t *__restrict__ feat, uint32_t blocks_per_xcd)
 {
     const uint32_t block = (blockIdx.x % kXcds) * blocks_per_xcd + blockIdx.x / kXcds;
     const uint64_t i = (uint64_t)block * (kBlock / 2) + threadIdx.x / 2;
@@ -33,46 +35,42 @@ encode_fwd_ordered_kernel(dg_grid_desc g, const float2 *__restrict__ table, cons
     const float4 s = ordered[i];
     const float uu[3] = {s.x, s.y, s.z};
     const uint32_t mask = (1u << g.log2_T) - 1u;
-    uint32_t out[8];
+    constexpr int kHalfRow = LEVELS / 2;
+    uint32_t out[kHalfRow];
 #pragma unroll
-    for (int l = 0; l < 16; ++l) {
-        const LevelGeom lv = level_of(g, l);
-        uint32_t cell[3], e[4];
-        float frac[3];
-        locate(lv, uu, cell, frac);
-        if (lv.dense) {
-            const uint32_t nx = lv.res[0] + 1u, nxy = nx * (lv.res[1] + 1u);
-            const uint32_t base = cell[0] + cx + nx * cell[1] + nxy * cell[2];
-#pragma unroll
-            for (int k = 0; k < 4; ++k) e[k] = base + (k & 1) * nx + (k >> 1) * nxy;
-        } else {
-            const uint32_t hy0 = cell[1] * kPrimeY, hy1 = hy0 + kPrimeY;
-            const uint32_t hz0 = cell[2] * kPrimeZ, hz1 = hz0 + kPrimeZ;
-#pragma unroll
-            for (int k = 0; k < 4; ++k) e[k] = ((cell[0] + cx) ^ ((k & 1) ? hy1 : hy0) ^ ((k & 2) ? hz1 : hz0)) & mask;
-        }
-        const float wx = cx ? frac[0] : 1.0f - frac[0];
-        const float wy[2] = {1.0f - frac[1], frac[1]}, wz[2] = {1.0f - frac[2], frac[2]};
-        float2 v[4];
-#pragma unroll
-        for (int k = 0; k < 4; ++k) v[k] = table[(size_t)lv.offset + e[k]];
-        float f0 = 0.0f, f1 = 0.0f;
-#pragma unroll
-        for (int k = 0; k < 4; ++k) {
-            const float w = wx * wy[k & 1] * wz[k >> 1];
-            f0 = fmaf(w, v[k].x, f0);
-            f1 = fmaf(w, v[k].y, f1);
-        }
-        // the partner's half: lanes swapped within pairs (quad_perm 1, 0, 3, 2)
-        f0 += __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(f0), 0xB1, 0xF, 0xF, true));
-        f1 += __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(f1), 0xB1, 0xF, 0xF, true));
-        const uint32_t f = __builtin_bit_cast(uint32_t, __floats2half2_rn(f0, f1));
-        if (l < 8) out[l] = f;
-        else out[l - 8] = cx ? f : out[l - 8];
+    for (int l = 0; l < LEVELS; ++l) {
+        const float2 v = gather_pair(level_of(g, l), mask, table, uu, cx);
+        const uint32_t f = __builtin_bit_cast(uint32_t, __floats2half2_rn(v.x, v.y));
+        if (l < kHalfRow) out[l] = f;
+        else out[l - kHalfRow] = cx ? f : out[l - kHalfRow];
     }
-    uint4 *half_row = feat + (size_t)(by_position ? (uint32_t)i : __float_as_uint(s.w)) * 4 + 2 * cx;
-    half_row[0] = make_uint4(out[0], out[1], out[2], out[3]);
-    half_row[1] = make_uint4(out[4], out[5], out[6], out[7]);
+    uint32_t *half_row = feat + (size_t)(by_position ? (uint32_t)i : __float_as_uint(s.w)) * LEVELS + kHalfRow * cx;
+    if constexpr (kHalfRow % 4 == 0) {
+#pragma unroll
+        for (int k = 0; k < kHalfRow; k += 4) *reinterpret_cast<uint4 *>(half_row + k) = make_uint4(out[k], out[k + 1], out[k + 2], out[k + 3]);
+    } else {
+#pragma unroll
+        for (int k = 0; k < kHalfRow; k += 2) *reinterpret_cast<uint2 *>(half_row + k) = make_uint2(out[k], out[k + 1]);
+    }
+}
+
+// Levels 12..15 as planes, level after level, so that one level's table at a time lies in the L2s: SORTED from the sorted list, in its
+// order, else in ray order.  With T = 2^19 the sixteen levels that the ordered gather walks at once fetch 5 lines per sample past an L2 that
+// holds one of them, at the rate of the fabric; the finer ones are most of it, and below some 6 M samples neighbours share few of their
+// lines.  T = 2^19, 3.3 M samples: 612 us with all levels in one walk, 186 + 262 this way; 13.3 M: 1471 against 789 + 1023.  Refresh of an
+// occupancy grid, 8.4 M sorted candidates: 1190 against 472 + 485.  T = 2^18, 3.3 M: 441 against 178 + 206.
+template <bool SORTED>
+__global__ void __launch_bounds__(kBlock)
+encode_planes_kernel(dg_grid_desc g, const float2 *__restrict__ table, const float *__restrict__ u, uint64_t N, uint32_t *__restrict__ feat, uint32_t n_tiles)
+{
+    const uint32_t l = kSplitLevels + blockIdx.x / n_tiles;
+    const uint64_t s = (uint64_t)(blockIdx.x % n_tiles) * (kBlock / 2) + threadIdx.x / 2;
+    const uint32_t cx = threadIdx.x & 1u;
+    if (s >= N) return;                                   // both lanes of a pair
+    const float *at = u + (SORTED ? 4 : 3) * s;
+    const float uu[3] = {at[0], at[1], at[2]};
+    const float2 f = gather_pair(level_of(g, l), (1u << g.log2_T) - 1u, table, uu, cx);
+    if (cx == 0u) feat[(size_t)l * N + s] = __builtin_bit_cast(uint32_t, __floats2half2_rn(f.x, f.y));
 }
 
 // Table gradient of levels [0, n_merged): a workgroup takes a piece of a brick and sums all its contributions in LDS -- the
@@ -430,8 +428,28 @@ extern "C" int dg_hashgrid_encode_fwd_ordered(const dg_grid_desc *desc, const fl
     DG_REQUIRE(dg::aligned(table, 8) && dg::aligned(ordered, 16) && dg::aligned(feat, 16), DG_ERR_ARG, "%s: misaligned pointer", who);
     const uint64_t blocks = (2 * N + kBlock - 1) / kBlock, per_xcd = (blocks + kXcds - 1) / kXcds;
     DG_REQUIRE(per_xcd * kXcds <= 0x7fffffffull, DG_ERR_UNSUPPORTED, "%s: N too large for one launch", who);
-    encode_fwd_ordered_kernel<<<(uint32_t)(per_xcd * kXcds), kBlock, 0, (hipStream_t)stream>>>(*desc, (const float2 *)table, (const float4 *)ordered, N, by_position != 0,
-                                                                                              (uint4 *)feat, (uint32_t)per_xcd);
+    encode_fwd_ordered_kernel<16><<<(uint32_t)(per_xcd * kXcds), kBlock, 0, (hipStream_t)stream>>>(
+        *desc, (const float2 *)table, (const float4 *)ordered, N, by_position != 0, (uint32_t *)feat, (uint32_t)per_xcd);
+    return dg::launch_status(who);
+}
+
+extern "C" int dg_hashgrid_encode_fwd_split(const dg_grid_desc *desc, const float *table, const void *ordered, const float *u, uint64_t N,
+                                            uint32_t by_position, void *feat, void *stream)
+{
+    const char *who = "dg_hashgrid_encode_fwd_split";
+    if (int rc = dg::check_grid_desc(desc, who)) return rc;
+    DG_REQUIRE(desc->n_levels == 16, DG_ERR_UNSUPPORTED, "%s: needs 16 levels", who);
+    if (N == 0) return DG_OK;
+    DG_REQUIRE(table && ordered && feat && (u || by_position), DG_ERR_ARG, "%s: null pointer", who);
+    DG_REQUIRE(dg::aligned(table, 8) && dg::aligned(ordered, 16) && dg::aligned(feat, 16), DG_ERR_ARG, "%s: misaligned pointer", who);
+    const uint64_t blocks = (2 * N + kBlock - 1) / kBlock, per_xcd = (blocks + kXcds - 1) / kXcds;
+    DG_REQUIRE(per_xcd * kXcds <= 0x7fffffffull && (16 - kSplitLevels) * blocks <= 0x7fffffffull, DG_ERR_UNSUPPORTED, "%s: N too large for one launch", who);
+    hipStream_t st = (hipStream_t)stream;
+    encode_fwd_ordered_kernel<kSplitLevels><<<(uint32_t)(per_xcd * kXcds), kBlock, 0, st>>>(*desc, (const float2 *)table, (const float4 *)ordered, N, by_position != 0,
+                                                                                           (uint32_t *)feat, (uint32_t)per_xcd);
+    const uint32_t grid = (uint32_t)((16 - kSplitLevels) * blocks);
+    if (by_position) encode_planes_kernel<true><<<grid, kBlock, 0, st>>>(*desc, (const float2 *)table, (const float *)ordered, N, (uint32_t *)feat, (uint32_t)blocks);
+    else encode_planes_kernel<false><<<grid, kBlock, 0, st>>>(*desc, (const float2 *)table, u, N, (uint32_t *)feat, (uint32_t)blocks);
     return dg::launch_status(who);
 }
 

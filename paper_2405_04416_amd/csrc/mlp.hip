@@ -22,28 +22,28 @@ int which_net(const dg_mlp_desc *m, const char *who)
 
 namespace {
 
-// rows: sample-major features (dg_hashgrid_encode_fwd_ordered); only the matrix-core networks take them
-int mlp_fwd(const char *who, const dg_mlp_desc *desc, const void *weights, const void *feat, bool rows, const void *dir_enc, const void *app, uint32_t S,
+// layout: of the features; only the matrix-core networks take other than planes
+int mlp_fwd(const char *who, const dg_mlp_desc *desc, const void *weights, const void *feat, dg::FeatureLayout layout, const void *dir_enc, const void *app, uint32_t S,
             uint64_t N, float *sigma, float *rgb, void *stream)
 {
     const int net = which_net(desc, who);
     if (net < 0) return net;
-    DG_REQUIRE(!rows || net == 1, DG_ERR_UNSUPPORTED, "%s: only the 32-64-16 / 64-64-3 networks take feature rows", who);
+    DG_REQUIRE(layout == dg::kPlanes || net == 1, DG_ERR_UNSUPPORTED, "%s: only the 32-64-16 / 64-64-3 networks take feature rows", who);
     DG_REQUIRE(S >= 1, DG_ERR_ARG, "%s: S must be >= 1", who);
     if (N == 0) return DG_OK;
     DG_REQUIRE(weights && feat && dir_enc && sigma && rgb, DG_ERR_ARG, "%s: null pointer", who);
     DG_REQUIRE(desc->n_app == 0 || (app && dg::aligned(app, 16)), DG_ERR_ARG, "%s: appearance rows missing or not 16-byte aligned", who);
     hipStream_t st = (hipStream_t)stream;
     if (net == 1) {
-        DG_REQUIRE(dg::aligned(feat, rows ? 16 : 4) && dg::aligned(dir_enc, 16), DG_ERR_ARG, "%s: feat must be %d-byte, dir_enc 16-byte aligned", who,
-                   rows ? 16 : 4);
-        dg::mlp_mfma_fwd(weights, feat, rows, dir_enc, app, desc->n_app, S, N, desc->act_c, sigma, rgb, st);
+        DG_REQUIRE(dg::aligned(feat, layout != dg::kPlanes ? 16 : 4) && dg::aligned(dir_enc, 16), DG_ERR_ARG, "%s: feat must be %d-byte, dir_enc 16-byte aligned", who,
+                   layout != dg::kPlanes ? 16 : 4);
+        dg::mlp_mfma_fwd(weights, feat, layout, dir_enc, app, desc->n_app, S, N, desc->act_c, sigma, rgb, st);
     } else
         dg::mlp_small_fwd(weights, feat, dir_enc, S, N, desc->act_c, sigma, rgb, st);
     return dg::launch_status(who);
 }
 
-int mlp_composite_fwd(const char *who, const dg_mlp_desc *desc, const void *weights, const void *feat, bool rows, const void *dir_enc, const void *app,
+int mlp_composite_fwd(const char *who, const dg_mlp_desc *desc, const void *weights, const void *feat, dg::FeatureLayout layout, const void *dir_enc, const void *app,
                       uint32_t S, uint32_t n_seg, const float *delta, const float *t, const uint32_t *seg_ray, const uint32_t *seg_slot,
                       uint32_t k_max, float *Ck, float *Tk, float *Dk, void *stream)
 {
@@ -56,33 +56,33 @@ int mlp_composite_fwd(const char *who, const dg_mlp_desc *desc, const void *weig
     DG_REQUIRE(weights && feat && dir_enc && delta && seg_ray && seg_slot && Ck && Tk, DG_ERR_ARG, "%s: null pointer", who);
     DG_REQUIRE((t == nullptr) == (Dk == nullptr), DG_ERR_ARG, "%s: t and Dk go together", who);
     DG_REQUIRE(desc->n_app == 0 || (app && dg::aligned(app, 16)), DG_ERR_ARG, "%s: appearance rows missing or not 16-byte aligned", who);
-    DG_REQUIRE(dg::aligned(feat, rows ? 16 : 4) && dg::aligned(dir_enc, 16), DG_ERR_ARG, "%s: feat must be %d-byte, dir_enc 16-byte aligned", who,
-               rows ? 16 : 4);
-    dg::mlp_mfma_render(weights, feat, rows, dir_enc, app, desc->n_app, S, n_seg, desc->act_c, delta, t, seg_ray, seg_slot, k_max, Ck, Tk, Dk,
+    DG_REQUIRE(dg::aligned(feat, layout != dg::kPlanes ? 16 : 4) && dg::aligned(dir_enc, 16), DG_ERR_ARG, "%s: feat must be %d-byte, dir_enc 16-byte aligned", who,
+               layout != dg::kPlanes ? 16 : 4);
+    dg::mlp_mfma_render(weights, feat, layout, dir_enc, app, desc->n_app, S, n_seg, desc->act_c, delta, t, seg_ray, seg_slot, k_max, Ck, Tk, Dk,
                         (hipStream_t)stream);
     return dg::launch_status(who);
 }
 
-int mlp_bwd(const char *who, const dg_mlp_desc *desc, const void *weights, const void *feat, bool rows, uint32_t n_merged, const void *dir_enc,
+int mlp_bwd(const char *who, const dg_mlp_desc *desc, const void *weights, const void *feat, dg::FeatureLayout layout, uint32_t n_merged, const void *dir_enc,
             const void *app, uint32_t S, uint64_t N, const float *dsigma, const float *drgb, float loss_scale, float *dfeat, uint32_t *largest,
             float *dW, void *ws, size_t ws_bytes, void *stream)
 {
     const int net = which_net(desc, who);
     if (net < 0) return net;
-    DG_REQUIRE(!rows || net == 1, DG_ERR_UNSUPPORTED, "%s: only the 32-64-16 / 64-64-3 networks take feature rows", who);
+    DG_REQUIRE(layout == dg::kPlanes || net == 1, DG_ERR_UNSUPPORTED, "%s: only the 32-64-16 / 64-64-3 networks take feature rows", who);
     DG_REQUIRE(n_merged % 2 == 0 && n_merged <= desc->n_feat / 2, DG_ERR_ARG, "%s: n_merged=%u must be even and at most the number of levels", who, n_merged);
     DG_REQUIRE(S >= 1 && loss_scale > 0.0f, DG_ERR_ARG, "%s: S >= 1 and loss_scale > 0 required", who);
     if (N == 0) return DG_OK;
-    DG_REQUIRE(weights && feat && dir_enc && dsigma && drgb && dfeat && dW && (!rows || largest), DG_ERR_ARG, "%s: null pointer", who);
+    DG_REQUIRE(weights && feat && dir_enc && dsigma && drgb && dfeat && dW && (layout == dg::kPlanes || largest), DG_ERR_ARG, "%s: null pointer", who);
     DG_REQUIRE(desc->n_app == 0 || (app && dg::aligned(app, 16)), DG_ERR_ARG, "%s: appearance rows missing or not 16-byte aligned", who);
     DG_REQUIRE(ws && ws_bytes >= dg_mlp_bwd_app_workspace_bytes(desc, N, S), DG_ERR_WORKSPACE, "%s: workspace %zu < %zu bytes", who, ws_bytes,
                dg_mlp_bwd_app_workspace_bytes(desc, N, S));
     DG_REQUIRE(dg::aligned(ws, 256), DG_ERR_ARG, "%s: workspace must be 256-byte aligned", who);
     hipStream_t st = (hipStream_t)stream;
     if (net == 1) {
-        DG_REQUIRE(dg::aligned(feat, rows ? 16 : 4) && dg::aligned(dir_enc, 16) && dg::aligned(dfeat, rows ? 16 : 8), DG_ERR_ARG,
-                   "%s: feat must be %d-byte, dfeat %d-byte, dir_enc 16-byte aligned", who, rows ? 16 : 4, rows ? 16 : 8);
-        dg::mlp_mfma_bwd(weights, feat, rows, n_merged, dir_enc, app, desc->n_app, S, N, desc->act_c, dsigma, drgb, loss_scale, dfeat, largest, dW, ws, st);
+        DG_REQUIRE(dg::aligned(feat, layout != dg::kPlanes ? 16 : 4) && dg::aligned(dir_enc, 16) && dg::aligned(dfeat, layout != dg::kPlanes ? 16 : 8), DG_ERR_ARG,
+                   "%s: feat must be %d-byte, dfeat %d-byte, dir_enc 16-byte aligned", who, layout != dg::kPlanes ? 16 : 4, layout != dg::kPlanes ? 16 : 8);
+        dg::mlp_mfma_bwd(weights, feat, layout, n_merged, dir_enc, app, desc->n_app, S, N, desc->act_c, dsigma, drgb, loss_scale, dfeat, largest, dW, ws, st);
         return dg::launch_status(who);
     }
     dg::mlp_small_bwd(weights, feat, dir_enc, S, N, desc->act_c, dsigma, drgb, loss_scale, dfeat, dW, ws, st);
@@ -101,13 +101,13 @@ extern "C" int dg_mlp_fwd(const dg_mlp_desc *desc, const void *weights, const vo
 extern "C" int dg_mlp_fwd_app(const dg_mlp_desc *desc, const void *weights, const void *feat, const void *dir_enc,
                               const void *app, uint32_t S, uint64_t N, float *sigma, float *rgb, void *stream)
 {
-    return mlp_fwd("dg_mlp_fwd", desc, weights, feat, false, dir_enc, app, S, N, sigma, rgb, stream);
+    return mlp_fwd("dg_mlp_fwd", desc, weights, feat, dg::kPlanes, dir_enc, app, S, N, sigma, rgb, stream);
 }
 
 extern "C" int dg_mlp_fwd_rows(const dg_mlp_desc *desc, const void *weights, const void *feat, const void *dir_enc,
                                const void *app, uint32_t S, uint64_t N, float *sigma, float *rgb, void *stream)
 {
-    return mlp_fwd("dg_mlp_fwd_rows", desc, weights, feat, true, dir_enc, app, S, N, sigma, rgb, stream);
+    return mlp_fwd("dg_mlp_fwd_rows", desc, weights, feat, dg::kRows, dir_enc, app, S, N, sigma, rgb, stream);
 }
 
 extern "C" int dg_mlp_composite_fwd(const dg_mlp_desc *desc, const void *weights, const void *feat, const void *dir_enc,
@@ -115,7 +115,7 @@ extern "C" int dg_mlp_composite_fwd(const dg_mlp_desc *desc, const void *weights
                                     const uint32_t *seg_ray, const uint32_t *seg_slot, uint32_t k_max, float *Ck, float *Tk,
                                     float *Dk, void *stream)
 {
-    return mlp_composite_fwd("dg_mlp_composite_fwd", desc, weights, feat, false, dir_enc, app, S, n_seg, delta, t, seg_ray, seg_slot, k_max, Ck, Tk, Dk,
+    return mlp_composite_fwd("dg_mlp_composite_fwd", desc, weights, feat, dg::kPlanes, dir_enc, app, S, n_seg, delta, t, seg_ray, seg_slot, k_max, Ck, Tk, Dk,
                              stream);
 }
 
@@ -124,7 +124,7 @@ extern "C" int dg_mlp_composite_fwd_rows(const dg_mlp_desc *desc, const void *we
                                          const uint32_t *seg_ray, const uint32_t *seg_slot, uint32_t k_max, float *Ck, float *Tk,
                                          float *Dk, void *stream)
 {
-    return mlp_composite_fwd("dg_mlp_composite_fwd_rows", desc, weights, feat, true, dir_enc, app, S, n_seg, delta, t, seg_ray, seg_slot, k_max, Ck, Tk,
+    return mlp_composite_fwd("dg_mlp_composite_fwd_rows", desc, weights, feat, dg::kRows, dir_enc, app, S, n_seg, delta, t, seg_ray, seg_slot, k_max, Ck, Tk,
                              Dk, stream);
 }
 
@@ -153,7 +153,7 @@ extern "C" int dg_mlp_bwd_app(const dg_mlp_desc *desc, const void *weights, cons
                               const void *app, uint32_t S, uint64_t N, const float *dsigma, const float *drgb,
                               float loss_scale, float *dfeat, float *dW, void *ws, size_t ws_bytes, void *stream)
 {
-    return mlp_bwd("dg_mlp_bwd", desc, weights, feat, false, 0, dir_enc, app, S, N, dsigma, drgb, loss_scale, dfeat, nullptr, dW, ws, ws_bytes, stream);
+    return mlp_bwd("dg_mlp_bwd", desc, weights, feat, dg::kPlanes, 0, dir_enc, app, S, N, dsigma, drgb, loss_scale, dfeat, nullptr, dW, ws, ws_bytes, stream);
 }
 
 extern "C" int dg_mlp_bwd_rows(const dg_mlp_desc *desc, const void *weights, const void *feat, const void *dir_enc,
@@ -161,20 +161,49 @@ extern "C" int dg_mlp_bwd_rows(const dg_mlp_desc *desc, const void *weights, con
                                float loss_scale, uint32_t n_merged, float *dfeat, uint32_t *largest, float *dW, void *ws, size_t ws_bytes,
                                void *stream)
 {
-    return mlp_bwd("dg_mlp_bwd_rows", desc, weights, feat, true, n_merged, dir_enc, app, S, N, dsigma, drgb, loss_scale, dfeat, largest, dW, ws, ws_bytes, stream);
+    return mlp_bwd("dg_mlp_bwd_rows", desc, weights, feat, dg::kRows, n_merged, dir_enc, app, S, N, dsigma, drgb, loss_scale, dfeat, largest, dW, ws, ws_bytes, stream);
 }
 
-extern "C" int dg_occ_evaluate(const dg_mlp_desc *desc, const void *weights, const void *feat, uint32_t rows, const uint32_t *cell,
-                               uint32_t cell_stride, uint64_t M, float *density, uint32_t n_cells, void *stream)
+extern "C" int dg_mlp_fwd_split(const dg_mlp_desc *desc, const void *weights, const void *feat, const void *dir_enc,
+                                const void *app, uint32_t S, uint64_t N, float *sigma, float *rgb, void *stream)
 {
-    const char *who = "dg_occ_evaluate";
+    return mlp_fwd("dg_mlp_fwd_split", desc, weights, feat, dg::kSplit, dir_enc, app, S, N, sigma, rgb, stream);
+}
+
+extern "C" int dg_mlp_bwd_split(const dg_mlp_desc *desc, const void *weights, const void *feat, const void *dir_enc,
+                                const void *app, uint32_t S, uint64_t N, const float *dsigma, const float *drgb,
+                                float loss_scale, uint32_t n_merged, float *dfeat, uint32_t *largest, float *dW, void *ws, size_t ws_bytes,
+                                void *stream)
+{
+    return mlp_bwd("dg_mlp_bwd_split", desc, weights, feat, dg::kSplit, n_merged, dir_enc, app, S, N, dsigma, drgb, loss_scale, dfeat, largest, dW, ws, ws_bytes, stream);
+}
+
+namespace {
+
+int occ_evaluate(const char *who, const dg_mlp_desc *desc, const void *weights, const void *feat, dg::FeatureLayout layout, const uint32_t *cell,
+                 uint32_t cell_stride, uint64_t M, float *density, uint32_t n_cells, void *stream)
+{
     const int net = which_net(desc, who);
     if (net < 0) return net;
     DG_REQUIRE(net == 1, DG_ERR_UNSUPPORTED, "%s: only the 32-64-16 density net has this kernel", who);
     DG_REQUIRE(cell_stride >= 1, DG_ERR_ARG, "%s: cell_stride must be >= 1", who);
     if (M == 0) return DG_OK;
     DG_REQUIRE(weights && feat && cell && density, DG_ERR_ARG, "%s: null pointer", who);
-    DG_REQUIRE(dg::aligned(feat, rows ? 16 : 4), DG_ERR_ARG, "%s: feat must be %d-byte aligned", who, rows ? 16 : 4);
-    dg::mlp_mfma_density_max(weights, feat, rows != 0, cell, cell_stride, M, density, n_cells, (hipStream_t)stream);
+    DG_REQUIRE(dg::aligned(feat, layout != dg::kPlanes ? 16 : 4), DG_ERR_ARG, "%s: feat must be %d-byte aligned", who, layout != dg::kPlanes ? 16 : 4);
+    dg::mlp_mfma_density_max(weights, feat, layout, cell, cell_stride, M, density, n_cells, (hipStream_t)stream);
     return dg::launch_status(who);
+}
+
+}  // namespace
+
+extern "C" int dg_occ_evaluate(const dg_mlp_desc *desc, const void *weights, const void *feat, uint32_t rows, const uint32_t *cell,
+                               uint32_t cell_stride, uint64_t M, float *density, uint32_t n_cells, void *stream)
+{
+    return occ_evaluate("dg_occ_evaluate", desc, weights, feat, rows ? dg::kRows : dg::kPlanes, cell, cell_stride, M, density, n_cells, stream);
+}
+
+extern "C" int dg_occ_evaluate_split(const dg_mlp_desc *desc, const void *weights, const void *feat, const uint32_t *cell,
+                                     uint32_t cell_stride, uint64_t M, float *density, uint32_t n_cells, void *stream)
+{
+    return occ_evaluate("dg_occ_evaluate_split", desc, weights, feat, dg::kSplit, cell, cell_stride, M, density, n_cells, stream);
 }

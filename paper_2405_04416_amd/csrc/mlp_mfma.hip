@@ -15,11 +15,12 @@
 // at two wavefronts per SIMD, so it goes by the number of instructions: a compile-time choice of the activation (branches around each
 // of its uses cut the schedule into pieces), a (1 - a) as one multiply-add on halves, rows followed on the scalar unit instead of
 // divided out and images built from loads under way together took it from 1206 to 1050 us (0.65 M samples: 79 -> 65; 0.15 M: 35 -> 26),
-// the forward from 482 to 470 (40 -> 33; 17 -> 16).
+// transposes through LDS instead of products with selection matrices to 1020; the forward went from 482 to 470 (40 -> 33; 17 -> 16).
 //
 // Backward recomputes the forward, then walks the chain back.  Weight gradients contract over the
-// samples, so they need each (delta, activation) pair with the samples on the k axis: tiles are transposed through LDS.  Every wavefront accumulates its share of dW in registers over all its tiles; the workgroup adds its
-// wavefronts' shares up, writes the sum to the workspace once, and a second kernel folds the workgroups' in a fixed order.
+// samples, so they need each (delta, activation) pair with the samples on the k axis: tiles are transposed through LDS.  Every
+// wavefront accumulates its share of dW in registers over all its tiles; the workgroup adds its wavefronts' shares up, writes the
+// sum to the workspace once, and a second kernel folds the workgroups' in a fixed order.
 //
 // Appearance features (Sec. 4.4.3: a fixed per-image vector of 16 or 48 values as extra colour-net inputs) widen the
 // first colour layer to 48 or 80 inputs.  Forward: NA / 16 more k-steps from a second row table.  Backward: the
@@ -31,6 +32,12 @@
 #include <type_traits>
 
 namespace dg_mlp_mfma {
+
+using dg::FeatureLayout;
+using dg::kPlanes;
+using dg::kRows;
+using dg::kSplit;
+using dg::kSplitLevels;
 
 constexpr int NF = 32, HD = 64, NG = 16, ND = 16, HC = 64, CI = NG + ND;
 constexpr int oWd1 = 0, oWd2 = oWd1 + HD * NF, oWc1 = oWd2 + NG * HD, oWc2 = oWc1 + HC * CI, oWc3 = oWc2 + HC * HC;
@@ -128,18 +135,19 @@ __device__ __forceinline__ float density_net(const __half *lds, int lane, const 
 }
 
 // Features arrive as level-major planes [16][n_samples] of half2 -- slot j of k-step ks on lane half h is feature
-// 16 ks + 8 h + j, i.e. component j % 2 of level 8 ks + 4 h + j / 2 -- or as rows of 32 halves (ROWS).
+// 16 ks + 8 h + j, i.e. component j % 2 of level 8 ks + 4 h + j / 2 -- as rows of 32 halves, or as rows of 24 halves and the planes of levels 12..15.
 // base: first sample of a tile or segment, the same for the whole wavefront; s: the lane's sample from there.
-template <bool ROWS>
+template <FeatureLayout LAYOUT>
 __device__ __forceinline__ void load_features(const __half *feat, uint64_t n_samples, uint64_t base, uint32_t s, int h, h8 x0[2])
 {
-    if (ROWS) {
+    typedef uint32_t u4 __attribute__((ext_vector_type(4)));
+    const uint32_t *words = reinterpret_cast<const uint32_t *>(feat);
+    if (LAYOUT == kRows) {
         const h8 *row = reinterpret_cast<const h8 *>(feat) + 4 * base;
 #pragma unroll
         for (int ks = 0; ks < 2; ++ks) x0[ks] = row[4 * s + 2 * ks + h];
-    } else {
-        typedef uint32_t u4 __attribute__((ext_vector_type(4)));
-        const uint32_t *planes = reinterpret_cast<const uint32_t *>(feat) + (size_t)(4 * h) * n_samples + s;
+    } else if (LAYOUT == kPlanes) {
+        const uint32_t *planes = words + (size_t)(4 * h) * n_samples + s;
 #pragma unroll
         for (int ks = 0; ks < 2; ++ks) {
             u4 bits;
@@ -147,15 +155,28 @@ __device__ __forceinline__ void load_features(const __half *feat, uint64_t n_sam
             for (int q = 0; q < 4; ++q) bits[q] = planes[(size_t)(8 * ks + q) * n_samples + base];
             x0[ks] = __builtin_bit_cast(h8, bits);
         }
+    } else {
+        static_assert(kSplitLevels == 12, "a row is three operands, the fourth comes from planes");
+        const h8 *row = reinterpret_cast<const h8 *>(feat) + 3 * base;
+        x0[0] = row[3 * s + h];
+        if (h == 0) {
+            x0[1] = row[3 * s + 2];
+        } else {
+            const uint32_t *planes = words + base;
+            u4 bits;
+#pragma unroll
+            for (int q = 0; q < 4; ++q) bits[q] = (planes + (size_t)(12 + q) * n_samples)[s];
+            x0[1] = __builtin_bit_cast(h8, bits);
+        }
     }
 }
 
 // row: of the sample at base, r: the lane's row from there
-template <int NA, bool ROWS>
+template <int NA, FeatureLayout LAYOUT>
 __device__ __forceinline__ void load_inputs(const __half *feat, const __half *dir_enc, const __half *app, uint64_t n_samples, uint64_t base, uint32_t s,
                                             uint64_t row, uint32_t r, int h, Tile &t)
 {
-    load_features<ROWS>(feat, n_samples, base, s, h, t.x0);
+    load_features<LAYOUT>(feat, n_samples, base, s, h, t.x0);
     t.xc[1] = reinterpret_cast<const h8 *>(dir_enc + row * ND)[2 * r + h];
 #pragma unroll
     for (int ks = 0; ks < NA / 16; ++ks) t.xa[ks] = reinterpret_cast<const h8 *>(app + row * NA)[NA / 8 * r + 2 * ks + h];
@@ -163,14 +184,14 @@ __device__ __forceinline__ void load_inputs(const __half *feat, const __half *di
 
 // Inputs of the walk's tile.  Lanes past the last sample read it again: no branch, and what they compute is not stored and gets no
 // gradient.  (Asked for a tile ahead: no gain at five wavefronts per SIMD forward, spills at two backward.)
-template <int NA, bool ROWS>
+template <int NA, FeatureLayout LAYOUT>
 __device__ __forceinline__ void load_tile(const __half *feat, const __half *dir_enc, const __half *app, const TileWalk &walk, int lane, Tile &t)
 {
     const uint32_t s = min((uint32_t)lane & 31u, walk.count() - 1u);
-    load_inputs<NA, ROWS>(feat, dir_enc, app, walk.n_samples, walk.tile * 32, s, walk.row, walk.local_row(s), lane >> 5, t);
+    load_inputs<NA, LAYOUT>(feat, dir_enc, app, walk.n_samples, walk.tile * 32, s, walk.row, walk.local_row(s), lane >> 5, t);
 }
 
-template <int NA, bool ROWS, bool SIG>
+template <int NA, FeatureLayout LAYOUT, bool SIG>
 __global__ void __launch_bounds__(kBlock, 4)
 fwd_kernel(const __half *__restrict__ weights, const __half *__restrict__ feat, const __half *__restrict__ dir_enc,
            const __half *__restrict__ app, uint32_t S, uint64_t n_samples, float *__restrict__ sigma, float *__restrict__ rgb)
@@ -185,7 +206,7 @@ fwd_kernel(const __half *__restrict__ weights, const __half *__restrict__ feat, 
         const uint64_t base = walk.tile * 32;
         const bool valid = s < walk.count();
         Tile t;
-        load_tile<NA, ROWS>(feat, dir_enc, app, walk, lane, t);
+        load_tile<NA, LAYOUT>(feat, dir_enc, app, walk, lane, t);
         forward_tile<NA, SIG>(lds, opaque(lane), t, kFwdChunks);
         if (valid && h == 0) {
             (sigma + base)[s] = t.sigma;
@@ -201,7 +222,7 @@ fwd_kernel(const __half *__restrict__ weights, const __half *__restrict__ feat, 
 // integer atomic.
 // Bound by the rows it reads and the atomics' cache lines.  8.4 M candidates, 16.8 M cells: whole networks and a separate maximum
 // 304 + 323 us, this kernel on candidates in spatial order 215 us (neighbours' cells then share lines).
-template <bool ROWS>
+template <FeatureLayout LAYOUT>
 __global__ void __launch_bounds__(kBlock, 8)
 density_max_kernel(const __half *__restrict__ weights, const __half *__restrict__ feat, const uint32_t *__restrict__ cell, uint32_t cell_stride,
                    uint64_t n_samples, float *__restrict__ density, uint32_t n_cells)
@@ -217,7 +238,7 @@ density_max_kernel(const __half *__restrict__ weights, const __half *__restrict_
     for (uint64_t tile = wave; tile < n_tiles; tile += n_waves) {
         const uint64_t n = tile * 32 + (lane & 31), nn = n < n_samples ? n : n_samples - 1;
         h8 x0[2];
-        load_features<ROWS>(feat, n_samples, tile * 32, (uint32_t)(nn - tile * 32), h, x0);
+        load_features<LAYOUT>(feat, n_samples, tile * 32, (uint32_t)(nn - tile * 32), h, x0);
         const uint32_t c = cell[nn * cell_stride];
         const float sigma = __expf(clip15(density_net(lds, opaque(lane), x0)));
         if (h == 0 && n < n_samples && c < n_cells) atomicMax(reinterpret_cast<unsigned int *>(density) + c, __float_as_uint(sigma));
@@ -248,7 +269,7 @@ __device__ __forceinline__ float wave_sum(float v)
     return v;
 }
 
-template <int NA, bool ROWS, bool SIG>
+template <int NA, FeatureLayout LAYOUT, bool SIG>
 __global__ void __launch_bounds__(kBlock, 4)
 render_fwd_kernel(const __half *__restrict__ weights, const __half *__restrict__ feat, const __half *__restrict__ dir_enc,
                   const __half *__restrict__ app, uint32_t S, uint32_t n_seg, const float *__restrict__ delta,
@@ -270,7 +291,7 @@ render_fwd_kernel(const __half *__restrict__ weights, const __half *__restrict__
             const uint32_t s = 32u * part + (lane & 31);
             const bool valid = s < S;
             Tile t;
-            load_inputs<NA, ROWS>(feat, dir_enc, app, n_samples, first, valid ? s : 0u, seg, 0u, h, t);
+            load_inputs<NA, LAYOUT>(feat, dir_enc, app, n_samples, first, valid ? s : 0u, seg, 0u, h, t);
             forward_tile<NA, SIG>(lds, opaque(lane), t, kFwdChunks);
             sig[part] = t.sigma;
             col[part][0] = t.rgb[0]; col[part][1] = t.rgb[1]; col[part][2] = t.rgb[2];
@@ -311,7 +332,7 @@ render_fwd_kernel(const __half *__restrict__ weights, const __half *__restrict__
 //                already scaled and rounded to fp16, in operand order) in the workspace;
 //   density_bwd: recomputes the density hidden layer, back-propagates it from delta_geo, accumulates
 //                dWd1..2 and writes the feature gradient planes.
-template <int NA, bool ROWS, bool SIG>
+template <int NA, FeatureLayout LAYOUT, bool SIG>
 __global__ void __launch_bounds__(kBlock, 2)
 colour_bwd_kernel(const __half *__restrict__ weights, const __half *__restrict__ feat, const __half *__restrict__ dir_enc,
                   const __half *__restrict__ app, uint32_t S, uint64_t n_samples,
@@ -347,7 +368,7 @@ colour_bwd_kernel(const __half *__restrict__ weights, const __half *__restrict__
         const bool valid = s < walk.count();
         const int lane = opaque(lane_fixed);
         Tile t;
-        load_tile<NA, ROWS>(feat, dir_enc, app, walk, lane_fixed, t);
+        load_tile<NA, LAYOUT>(feat, dir_enc, app, walk, lane_fixed, t);
         float ds = 0.0f, dc[3] = {0.0f, 0.0f, 0.0f};
         if (valid && h == 0) {                 // issued before the forward so the latency hides behind it
             const float *c = drgb + 3 * base;
@@ -473,14 +494,15 @@ colour_bwd_kernel(const __half *__restrict__ weights, const __half *__restrict__
     });
 }
 
-// ROWS: the gradient of levels [0, n_merged) goes into rows of 2 n_merged floats, that of the others into planes behind them
-template <bool ROWS>
+// Other than with planes, the gradient of levels [0, n_merged) goes into rows of 2 n_merged floats, that of the others into planes behind them
+template <FeatureLayout LAYOUT>
 __global__ void __launch_bounds__(kBlock, 2)
 density_bwd_kernel(const __half *__restrict__ weights, const __half *__restrict__ feat, uint64_t n_samples,
                    const h8 *__restrict__ dgeo, float loss_scale, uint32_t n_merged, float *__restrict__ dfeat, uint32_t *__restrict__ largest,
                    float *__restrict__ shares)
 {
     // images: density layer 1 forward (4 chunks), Wd2^T (2), Wd1^T (4); the share of the weight gradient takes their place
+    constexpr bool kGradRows = LAYOUT != kPlanes;
     constexpr int kD1 = 0, kD2T = 4, kD1T = 6, kChunks = 12;
     __shared__ __attribute__((aligned(16))) __half lds[kChunks * 512];
     __shared__ __attribute__((aligned(16))) _Float16 scratch[kWavesPerBlock * kScratchHalves];
@@ -505,7 +527,7 @@ density_bwd_kernel(const __half *__restrict__ weights, const __half *__restrict_
     auto load = [&](uint64_t tile) {            // lanes past the last sample read it again; their gradient is set to zero below
         const uint64_t base = tile * 32, left = n_samples - base;
         const uint32_t s = min((uint32_t)lane & 31u, left < 32 ? (uint32_t)left - 1u : 31u);
-        load_features<ROWS>(feat, n_samples, base, s, h, x_next);
+        load_features<LAYOUT>(feat, n_samples, base, s, h, x_next);
         dg_next = (dgeo + 2 * base)[2 * s + h];
     };
     if (wave < n_tiles) load(wave);
@@ -551,7 +573,7 @@ density_bwd_kernel(const __half *__restrict__ weights, const __half *__restrict_
         f16v gf = zero16();
 #pragma unroll
         for (int ks = 0; ks < 4; ++ks) gf = mma(image(lds, kD1T + ks, lane), dl[ks], gf);
-        if (ROWS && valid) {
+        if (kGradRows && valid) {
             bool nan = false;                                   // fmaxf passes over NaN
 #pragma unroll
             for (int k = 0; k < 16; ++k) { most = fmaxf(most, fabsf(gf[k])); nan |= gf[k] != gf[k]; }
@@ -562,7 +584,7 @@ density_bwd_kernel(const __half *__restrict__ weights, const __half *__restrict_
             float2 *planes = reinterpret_cast<float2 *>(dfeat);
 #pragma unroll
             for (int q = 0; q < 4; ++q) {
-                if (ROWS && 4u * q + 2u * h < n_merged) {          // n_merged is even: a lane's two levels go the same way
+                if (kGradRows && 4u * q + 2u * h < n_merged) {          // n_merged is even: a lane's two levels go the same way
                     reinterpret_cast<float4 *>(dfeat)[n * (n_merged / 2) + 2 * q + h] =
                         make_float4(gf[4 * q] * inv_scale, gf[4 * q + 1] * inv_scale, gf[4 * q + 2] * inv_scale, gf[4 * q + 3] * inv_scale);
                     continue;
@@ -573,7 +595,7 @@ density_bwd_kernel(const __half *__restrict__ weights, const __half *__restrict_
         }
     }
 
-    if (ROWS) {
+    if (kGradRows) {
         // one atomic per workgroup at most: same-address atomics take turns (one per wavefront cost 15 us)
         __shared__ uint32_t most_word;
         if (threadIdx.x == 0) most_word = 0u;
@@ -676,61 +698,64 @@ size_t mlp_mfma_workspace_bytes(uint64_t N, uint32_t n_app, uint32_t S)
 
 size_t mlp_mfma_weight_count(uint32_t n_app) { return (size_t)dg_mlp_mfma::kTotal + (size_t)dg_mlp_mfma::HC * n_app; }
 
-// calls launch(appearance inputs, rows, sigmoid) with all three as compile-time constants
+// calls launch(appearance inputs, layout of the features, sigmoid) with all three as compile-time constants
 template <class F>
-static void for_shape(uint32_t n_app, bool rows, uint32_t act_c, F launch)
+static void for_shape(uint32_t n_app, FeatureLayout layout, uint32_t act_c, F launch)
 {
     auto with_act = [&](auto na, auto in_rows) {
         if (act_c) launch(na, in_rows, std::true_type{});
         else launch(na, in_rows, std::false_type{});
     };
     auto with_rows = [&](auto na) {
-        if (rows) with_act(na, std::true_type{});
-        else with_act(na, std::false_type{});
+        if (layout == kPlanes) with_act(na, std::integral_constant<FeatureLayout, kPlanes>{});
+        else if (layout == kRows) with_act(na, std::integral_constant<FeatureLayout, kRows>{});
+        else with_act(na, std::integral_constant<FeatureLayout, kSplit>{});
     };
     if (n_app == 0) with_rows(std::integral_constant<int, 0>{});
     else if (n_app == 16) with_rows(std::integral_constant<int, 16>{});
     else with_rows(std::integral_constant<int, 48>{});
 }
 
-void mlp_mfma_fwd(const void *weights, const void *feat, bool rows, const void *dir_enc, const void *app, uint32_t n_app, uint32_t S,
+void mlp_mfma_fwd(const void *weights, const void *feat, FeatureLayout layout, const void *dir_enc, const void *app, uint32_t n_app, uint32_t S,
                   uint64_t N, uint32_t act_c, float *sigma, float *rgb, hipStream_t st)
 {
     using namespace dg_mlp_mfma;
     const uint64_t tiles = (N + 31) / 32, blocks_needed = (tiles + kWavesPerBlock - 1) / kWavesPerBlock;
     const uint32_t grid = (uint32_t)(blocks_needed < kGridForward ? blocks_needed : kGridForward);
-    for_shape(n_app, rows, act_c, [&](auto na, auto in_rows, auto sig) {
+    for_shape(n_app, layout, act_c, [&](auto na, auto in_rows, auto sig) {
         fwd_kernel<decltype(na)::value, decltype(in_rows)::value, decltype(sig)::value><<<grid, kBlock, 0, st>>>(
             (const __half *)weights, (const __half *)feat, (const __half *)dir_enc, (const __half *)app, S, N, sigma, rgb);
     });
 }
 
-void mlp_mfma_density_max(const void *weights, const void *feat, bool rows, const uint32_t *cell, uint32_t cell_stride, uint64_t N, float *density,
+void mlp_mfma_density_max(const void *weights, const void *feat, FeatureLayout layout, const uint32_t *cell, uint32_t cell_stride, uint64_t N, float *density,
                           uint32_t n_cells, hipStream_t st)
 {
     using namespace dg_mlp_mfma;
     const uint64_t tiles = (N + 31) / 32, blocks_needed = (tiles + kWavesPerBlock - 1) / kWavesPerBlock;
     const uint32_t grid = (uint32_t)(blocks_needed < 2048 ? blocks_needed : 2048);
     const __half *w = (const __half *)weights, *f = (const __half *)feat;
-    if (rows) density_max_kernel<true><<<grid, kBlock, 0, st>>>(w, f, cell, cell_stride, N, density, n_cells);
-    else density_max_kernel<false><<<grid, kBlock, 0, st>>>(w, f, cell, cell_stride, N, density, n_cells);
+    if (layout == kPlanes) density_max_kernel<kPlanes><<<grid, kBlock, 0, st>>>(w, f, cell, cell_stride, N, density, n_cells);
+    else if (layout == kRows) density_max_kernel<kRows><<<grid, kBlock, 0, st>>>(w, f, cell, cell_stride, N, density, n_cells);
+    else density_max_kernel<kSplit><<<grid, kBlock, 0, st>>>(w, f, cell, cell_stride, N, density, n_cells);
 }
 
-void mlp_mfma_render(const void *weights, const void *feat, bool rows, const void *dir_enc, const void *app, uint32_t n_app, uint32_t S,
+void mlp_mfma_render(const void *weights, const void *feat, FeatureLayout layout, const void *dir_enc, const void *app, uint32_t n_app, uint32_t S,
                      uint32_t n_seg, uint32_t act_c, const float *delta, const float *t, const uint32_t *seg_ray,
                      const uint32_t *seg_slot, uint32_t k_max, float *Ck, float *Tk, float *Dk, hipStream_t st)
 {
     using namespace dg_mlp_mfma;
     const uint32_t blocks_needed = (n_seg + kWavesPerBlock - 1) / kWavesPerBlock;
     const uint32_t grid = blocks_needed < 2048 ? blocks_needed : 2048;
-    for_shape(n_app, rows, act_c, [&](auto na, auto in_rows, auto sig) {
-        render_fwd_kernel<decltype(na)::value, decltype(in_rows)::value, decltype(sig)::value><<<grid, kBlock, 0, st>>>(
-            (const __half *)weights, (const __half *)feat, (const __half *)dir_enc, (const __half *)app, S, n_seg, delta, t, seg_ray,
-            seg_slot, k_max, Ck, Tk, Dk);
+    for_shape(n_app, layout, act_c, [&](auto na, auto in_rows, auto sig) {
+        if constexpr (decltype(in_rows)::value != kSplit)              // views take planes or rows
+            render_fwd_kernel<decltype(na)::value, decltype(in_rows)::value, decltype(sig)::value><<<grid, kBlock, 0, st>>>(
+                (const __half *)weights, (const __half *)feat, (const __half *)dir_enc, (const __half *)app, S, n_seg, delta, t, seg_ray,
+                seg_slot, k_max, Ck, Tk, Dk);
     });
 }
 
-void mlp_mfma_bwd(const void *weights, const void *feat, bool rows, uint32_t n_merged, const void *dir_enc, const void *app, uint32_t n_app,
+void mlp_mfma_bwd(const void *weights, const void *feat, FeatureLayout layout, uint32_t n_merged, const void *dir_enc, const void *app, uint32_t n_app,
                   uint32_t S, uint64_t N, uint32_t act_c, const float *dsigma, const float *drgb, float loss_scale, float *dfeat, uint32_t *largest,
                   float *dW, void *ws, hipStream_t st)
 {
@@ -750,12 +775,13 @@ void mlp_mfma_bwd(const void *weights, const void *feat, bool rows, uint32_t n_m
         const uint64_t n = n_rows * HC, want = (n + kBlock - 1) / kBlock;
         zero_kernel<<<(uint32_t)(want < 4096 ? want : 4096), kBlock, 0, st>>>(row_delta, n);
     }
-    for_shape(n_app, rows, act_c, [&](auto na, auto in_rows, auto sig) {
+    for_shape(n_app, layout, act_c, [&](auto na, auto in_rows, auto sig) {
         colour_bwd_kernel<decltype(na)::value, decltype(in_rows)::value, decltype(sig)::value><<<grid_c, kBlock, 0, st>>>(w, f, dr, ap, S, N, dsigma, drgb, loss_scale, dgeo,
                                                                                                    colour_shares, row_delta);
     });
-    if (rows) density_bwd_kernel<true><<<grid_d, kBlock, 0, st>>>(w, f, N, dgeo, loss_scale, n_merged, dfeat, largest, density_shares);
-    else density_bwd_kernel<false><<<grid_d, kBlock, 0, st>>>(w, f, N, dgeo, loss_scale, 0, dfeat, nullptr, density_shares);
+    if (layout == kPlanes) density_bwd_kernel<kPlanes><<<grid_d, kBlock, 0, st>>>(w, f, N, dgeo, loss_scale, 0, dfeat, nullptr, density_shares);
+    else if (layout == kRows) density_bwd_kernel<kRows><<<grid_d, kBlock, 0, st>>>(w, f, N, dgeo, loss_scale, n_merged, dfeat, largest, density_shares);
+    else density_bwd_kernel<kSplit><<<grid_d, kBlock, 0, st>>>(w, f, N, dgeo, loss_scale, n_merged, dfeat, largest, density_shares);
     static_assert(oWc1 % kFoldElems == 0, "a fold workgroup must not span both share regions");
     fold_shares_kernel<<<(kTotal + kFoldElems - 1) / kFoldElems, kFoldElems * kFoldGroups, 0, st>>>(density_shares, grid_d, oWc1, colour_shares, grid_c,
                                                                                                    kTotal, 1.0f / loss_scale, dW);

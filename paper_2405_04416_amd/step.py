@@ -154,25 +154,27 @@ class TrainStep:
     def _order_min(self, m):
         """Samples of a sub-model from which on a training step puts them in spatial order.  The kernels for ordered samples serve
         the 16-level grid with the 32-64-16 / 64-64-3 networks.  The order pays once the samples lie densely enough to share
-        table lines and cells.  Whole step, plain / ordered in ms; what the lines below lie between:
-        T = 2^18: 1.35 / 1.36 at 1.74 M samples, 1.61 / 1.59 at 2.12 M, 2.01 / 1.87 at 2.65 M.  T = 2^17 and 2^20 gain earlier
-        (1.65 / 1.53 at 1.66 M).  T = 2^19, where the sixteen levels that the ordered gather walks at once displace each other in an L2 that
-        holds one of them: 1.65 / 1.70 at 2.10 M, 1.87 / 1.86 at 2.33 M, 2.07 / 2.05 at 2.64 M.
-        Larger tables, finest level of 2048 cells along the box: T = 2^21 0.81 / 0.81 at 0.56 M, T = 2^22 0.91 / 0.90 at 0.55 M, oblique
-        rays 3.18 / 3.28 with four sub-models of 0.40 M, 3.66 / 3.53 of 0.49 M.  With 8192 cells samples share less: T = 2^21
-        1.28 / 1.29 at 0.91 M, 1.41 / 1.41 at 1.06 M; T = 2^22 1.12 / 1.17 at 0.60 M, 1.32 / 1.31 at 0.70 M; T = 2^24 2.05 / 2.11 at 0.55 M,
-        2.28 / 2.20 at 0.71 M.
-        Occupancy-guided samples lie on surfaces, ten times as densely: T = 2^19 0.85 / 0.87 at 0.73 M, 1.07 / 1.05 at 1.01 M (with cells
-        four times as wide 1.22 / 1.23 at 1.34 M, 1.70 / 1.63 at 2.02 M); T = 2^21 0.87 / 0.87 at 0.45 M."""
+        table lines and cells.  Whole step, plain / ordered in us; what the lines below lie between:
+        T = 2^17 739 / 808 at 0.81 M samples, 1050 / 1006 at 1.22 M, 1279 / 1244 at 1.63 M.  T = 2^18 990 / 994 at 1.22 M, 1290 / 1272 at 1.63 M.
+        T = 2^19 1137 / 1028 against 1062 at 1.22 M and 1419 / 1277 against 1362 at 1.63 M, where the features are and are not split: the line stays
+        where the ordered gather breaks even without that, 1.65 / 1.70 ms at 2.10 M, 1.87 / 1.86 at 2.33 M.  T = 2^20 661 / 676 at 0.50 M, 911 / 873 at 0.81 M; oblique rays 2183 / 2205 with
+        four sub-models of 0.40 M, 3679 / 3275 of 0.80 M.
+        Larger tables, finest level of 2048 cells along the box: T = 2^21 685 / 713 at 0.41 M, 850 / 830 at 0.62 M; T = 2^22 739 / 754 at 0.41 M,
+        989 / 999 at 0.61 M, oblique 2855 / 2812 with four of 0.40 M, 4842 / 4156 of 0.79 M.  With 8192 cells samples share less: T = 2^21
+        797 / 790 at 0.44 M, 1058 / 1054 at 0.69 M, 1390 / 1336 at 1.0 M; T = 2^22 863 / 878 at 0.44 M, 1302 / 1261 at 0.69 M; T = 2^24 1898 / 1897 at
+        0.44 M, 2115 / 2095 at 0.69 M.
+        Occupancy-guided samples lie on surfaces, ten times as densely: T = 2^18 673 / 678 at 0.56 M, 901 / 847 at 0.79 M; T = 2^19 704 / 707 and
+        920 / 855; T = 2^20 539 / 537 at 0.28 M, 815 / 760 at 0.56 M; with cells four times as wide T = 2^19 1893 / 1715 at 2.2 M."""
         if m.grid.n_levels != 16 or (m.mlp.n_feat, m.mlp.n_hidden_d, m.mlp.n_layers_c) != (32, 64, 2):
             return 1 << 62
-        if m.grid.log2_T > 20:
-            if self.occ is not None or not self._fine(m):
-                return 1 << 19
-            return 1 << 20 if m.grid.log2_T == 21 else 5 << 17
+        T = m.grid.log2_T
         if self.occ is not None:
-            return 1 << 20
-        return 9 << 18 if m.grid.log2_T == 19 else 1 << 21
+            return 3 << 18 if T <= 19 else 1 << 19
+        if T <= 20:
+            return {17: 5 << 18, 18: 3 << 19, 19: 9 << 18, 20: 3 << 18}.get(T, 1 << 21)
+        if not self._fine(m):
+            return 1 << 19
+        return 3 << 18 if T == 21 else 5 << 17
 
     @staticmethod
     def _fine(m):
@@ -186,18 +188,39 @@ class TrainStep:
         3.0 M, 1.16 / 1.18 at 5.0 M, 1.38 / 1.33 at 6.0 M; T = 2^20 0.71 / 0.70 at 2.1 M.  Finest level of 2048 cells: T = 2^21
         0.28 / 0.30 at 0.55 M, 0.37 / 0.38 at 0.80 M (oblique rays 1.57 / 1.44 with four sub-models of 0.74 M), T = 2^22 0.30 / 0.31 at 0.54 M
         (oblique 1.18 / 1.10 with four of 0.49 M); 8192 cells: T = 2^21 1.49 / 1.50 at 3.0 M, T = 2^22 0.89 / 0.88 at 1.5 M, T = 2^23 0.71 / 0.70 at 1.1 M.
-        With occupancy-guided samples the step's own lines hold (T = 2^19 0.50 / 0.48 at 1.1 M).
+        With occupancy-guided samples from 2^20 on (T = 2^19 0.50 / 0.48 at 1.1 M).
         Occupancy refresh, T = 2^19: 0.36 / 0.38 at 1.05 M candidates, 0.43 / 0.43 at 1.24 M, 0.57 / 0.55 at 1.71 M; T = 2^18 0.33 / 0.31 at 1.05 M."""
         T = m.grid.log2_T
-        if use == "refresh":
-            return 1.25 if T == 19 else 1.0
-        if use == "step" or self.occ is not None:
+        if use == "step":
             return 1.0
-        if T <= 19:
-            return {18: 2.0, 19: 2.25}.get(T, 1.5)
+        if self.occ is not None:
+            from_2_20 = 4 / 3 if T <= 19 else 2.0 if T == 20 else 1.0
+            return 1.25 * from_2_20 if use == "refresh" and T == 19 else from_2_20
+        if T <= 20:
+            return {17: 2.4, 18: 8 / 3, 19: 2.25, 20: 8 / 3}.get(T, 1.5)
         if self._fine(m):
-            return {20: 1.0, 21: 3.0, 22: 2.25}.get(T, 1.5)
+            return {21: 4.0, 22: 2.25}.get(T, 1.5)
         return 1.5 if T == 21 else 1.0
+
+    def _split(self, m, N, use):
+        """Whether the features of samples in spatial order are split: rows of the first levels, planes of the finer ones, which are
+        gathered level after level.  Pays where an XCD's L2 holds much of one level's table but not of the sixteen that the ordered gather
+        walks at once, and while neighbours share few of the finer levels' lines.  One walk / split in us:
+        step, T = 2^17 1400 / 1381 at 2.0 M samples, 1979 / 1995 at 3.3 M; T = 2^18 2045 / 1990 at 3.3 M, 2663 / 2667 at 4.6 M; T = 2^19 1137 / 1028 at
+        1.2 M, 2849 / 2747 at 4.6 M, 3862 / 3870 at 6.6 M; T = 2^20 1655 / 1604 at 2.0 M, 2385 / 2385 at 3.3 M; T = 2^21 1304 / 1276 at 1.2 M, 2062 / 2134 at
+        2.5 M, with 8192 cells along the box 1422 / 1336 at 1.0 M, 4793 / 4424 at 4.7 M; T = 2^22 with 2048 cells 4156 / 4285 (four of 0.79 M), with 8192
+        1603 / 1550 at 1.0 M, 5070 / 4947 at 4.7 M; T = 2^24 2100 / 2095 at 0.69 M, 4136 / 4156 at 2.8 M.
+        Occupancy-guided steps, whose samples share more, lose or gain little: T = 2^19 1009 / 1027 at 1.0 M.
+        Refresh, pieces of 8.4 M, 4.2 M and 2.1 M candidates: T = 2^17 1383 / 1403, -, 1723 / 1591; T = 2^18 1478 / 1421, 1639 / 1422, 2061 / 1628;
+        T = 2^19 1693 / 1597, 2051 / 1627, 2546 / 1851; T = 2^20 1821 / 1948, 2231 / 2074, 2756 / 2393."""
+        T = m.grid.log2_T
+        if use == "refresh":
+            return N < {17: 3 << 20, 18: 10 << 20, 19: 10 << 20, 20: 6 << 20}.get(T, 0)
+        if use != "step" or self.occ is not None:
+            return False
+        if T > 20 and self._fine(m):
+            return N < {21: 5 << 20, 22: 5 << 20}.get(T, 0)
+        return N < {17: 5 << 19, 18: 1 << 22, 19: 23 << 18, 20: 5 << 19, 21: 3 << 19}.get(T, 0)
 
     def _encode_ws_bytes(self, m, n):
         """Workspace of the table-gradient pass for up to n samples.  In spatial order it holds the unmerged levels only, and
@@ -247,17 +270,21 @@ class TrainStep:
             buf.record_stream(torch.cuda.current_stream())
         return torch.empty(words, dtype=torch.int32, device=self.dev)
 
-    def _encode_fwd(self, p, m, order, sl, N, ids=None):
-        """Features of partition p's samples (their slice of the sample buffers): planes, or rows where they are sorted.
-        ids: the number that stands beside each sorted sample in place of its index; the rows then stay in sorted order."""
-        self._written(self._feat_rows, p, sl.start, N, self.n_feat // 2 if order is not None else 0, order, ids is not None)
+    def _encode_fwd(self, p, m, order, sl, N, use, ids=None):
+        """Features of partition p's samples (their slice of the sample buffers): planes, or rows, of all levels or of the first ones, where
+        they are sorted.
+        ids: the number that stands beside each sorted sample in place of its index; the features then stay in sorted order."""
+        split = order is not None and self._split(m, N, use)
+        self._written(self._feat_rows, p, sl.start, N, 0 if order is None else B.SPLIT_LEVELS if split else self.n_feat // 2, order, ids is not None)
         if order is not None:
             self.pieces[p] = self._grown(self.pieces.get(p), B.dg_order_pieces_words(order, N))
             self.ws_order = self._grown(self.ws_order, B.dg_order_workspace_bytes(order) // 4)
             with self._timed("dg_order_samples"):
                 B.dg_order_samples(order, self.u[sl], N, self.ordered[sl], self.pieces[p], self.ws_order, ids)
         with self._timed("dg_hashgrid_encode_fwd"):
-            if order is not None:
+            if split:
+                B.dg_hashgrid_encode_fwd_split(m.grid, m.table, self.ordered[sl], self.u[sl], N, self._feat[sl], by_position=ids is not None)
+            elif order is not None:
                 B.dg_hashgrid_encode_fwd_ordered(m.grid, m.table, self.ordered[sl], N, self._feat[sl], by_position=ids is not None)
             else:
                 B.dg_hashgrid_encode_fwd(m.grid, m.table, self.u[sl], N, self._feat[sl])
@@ -272,8 +299,11 @@ class TrainStep:
         if levels:
             rows[p] = _Rows(start, N, levels, order, by_position)
 
-    def _mlp_fwd(self, m, order, sl, dir_enc, app, S, N):
-        call = B.dg_mlp_fwd_app if order is None else B.dg_mlp_fwd_rows
+    def _is_split(self, p):
+        return p in self._feat_rows and self._feat_rows[p].levels == B.SPLIT_LEVELS
+
+    def _mlp_fwd(self, p, m, order, sl, dir_enc, app, S, N):
+        call = B.dg_mlp_fwd_app if order is None else B.dg_mlp_fwd_split if self._is_split(p) else B.dg_mlp_fwd_rows
         with self._timed("dg_mlp_fwd"):
             call(m.mlp, m.weights, self._feat[sl], dir_enc, app, S, N, self.sigma[sl], self.rgb[sl])
 
@@ -290,8 +320,9 @@ class TrainStep:
             else:
                 largest = self.pieces[p][1:2]
                 B.dg_clear(largest)         # the networks only ever raise it, and a forward pass may see several backward passes
-                B.dg_mlp_bwd_rows(m.mlp, m.weights, self._feat[sl], dir_enc, app, S, N, self.dsigma[sl], self.drgb[sl], self.loss_scale,
-                                  order.n_merged, self._dfeat[sl], largest, m.dW, self.ws_mlp)
+                call = B.dg_mlp_bwd_split if rows.levels == B.SPLIT_LEVELS else B.dg_mlp_bwd_rows
+                call(m.mlp, m.weights, self._feat[sl], dir_enc, app, S, N, self.dsigma[sl], self.drgb[sl], self.loss_scale,
+                     order.n_merged, self._dfeat[sl], largest, m.dW, self.ws_mlp)
         with self._timed("dg_hashgrid_encode_bwd"):
             if order is not None:
                 B.dg_hashgrid_encode_bwd_ordered(m.grid, order, self.ordered[sl], self.pieces[p], self.u[sl], self._dfeat[sl], largest, N, m.dtable,
@@ -307,7 +338,10 @@ class TrainStep:
             flat = buf[r.start:r.start + r.N].reshape(-1)[:2 * r.levels * r.N]
             planes = flat.view(r.N, r.levels, 2)
             if r.by_position:
-                planes = planes[self._position_of_candidates(r)]
+                place = self._position_of_candidates(r)
+                planes = planes[place]
+                rest = buf[r.start:r.start + r.N].reshape(-1)[2 * r.levels * r.N:].view(-1, r.N, 2)
+                rest.copy_(rest[:, place])
             flat.copy_(planes.transpose(0, 1).reshape(-1))
         rows.clear()
         return buf
@@ -490,7 +524,7 @@ class TrainStep:
             with self._timed("dg_dir_encode"):
                 B.dg_dir_encode(d, self.seg_ray[b:e], n_seg, self.deg, self.dir_enc[rows])
             self.layout[p] = (sl.start, N, order)
-            self._encode_fwd(p, m, order, sl, N)
+            self._encode_fwd(p, m, order, sl, N, use)
             app = self._appearance_rows(self.seg_ray[b:e], n_seg, rows)
             if fused_depth is not None:
                 call = B.dg_mlp_composite_fwd if order is None else B.dg_mlp_composite_fwd_rows
@@ -498,7 +532,7 @@ class TrainStep:
                     call(m.mlp, m.weights, self._feat[sl], self.dir_enc[rows], app, S, n_seg, self.delta[sl], self.t_fixed[sl], self.seg_ray[b:e],
                          self.seg_slot[b:e], self.k_max, self.Ck, self.Tk, fused_depth)
                 continue
-            self._mlp_fwd(m, order, sl, self.dir_enc[rows], app, S, N)
+            self._mlp_fwd(p, m, order, sl, self.dir_enc[rows], app, S, N)
             with self._timed("dg_composite_segment_fwd"):
                 B.dg_composite_segment_fwd(self.sigma[sl], self.rgb[sl], self.delta[sl], n_seg, S, self.seg_ray[b:e],
                                            self.seg_slot[b:e], self.k_max, self.Ck, self.Tk)
@@ -554,9 +588,9 @@ class TrainStep:
                     B.dg_dir_encode(d, self.sample_ray[sl], N, self.deg, self.dir_enc[sl])
                 order = self._order_of(m, N, use)
                 self.layout[p] = (s0 - N, N, order)
-                self._encode_fwd(p, m, order, sl, N)
+                self._encode_fwd(p, m, order, sl, N, use)
                 app = self._appearance_rows(self.sample_ray[sl], N, sl)
-                self._mlp_fwd(m, order, sl, self.dir_enc[sl], app, 1, N)
+                self._mlp_fwd(p, m, order, sl, self.dir_enc[sl], app, 1, N)
             with self._timed("dg_composite_ragged_fwd"):        # also writes C_k = 0, T_k = 1 for segments that saw nothing
                 B.dg_composite_ragged_fwd(self.sigma[s0 - N:], self.rgb[s0 - N:], self.delta[s0 - N:], n_seg, first, ray, slot,
                                           self.k_max, self.Ck, self.Tk)
@@ -612,18 +646,22 @@ class TrainStep:
                 with self._timed("dg_occ_candidates"):
                     B.dg_occ_candidates(q.desc, q.bits, n, n_uniform, warmup, self.seed, iteration, tries, cell, self.u[:n], i0=i0)
                 order = None if warmup else self._order_of(m, n, "refresh")        # during warm-up the candidates come cell after cell anyway
-                self._encode_fwd(p, m, order, slice(0, n), n, None if order is None else cell)
+                self._encode_fwd(p, m, order, slice(0, n), n, "refresh", None if order is None else cell)
                 if density_kernel:
                     with self._timed("dg_occ_evaluate"):
                         if order is None:
                             B.dg_occ_evaluate(m.mlp, m.weights, self._feat[:n], False, cell, 1, n, q.density)
                         else:                                   # the cells stand beside the sorted samples
-                            B.dg_occ_evaluate(m.mlp, m.weights, self._feat[:n], True, self.ordered.view(-1)[3:4 * n].view(torch.int32), 4, n, q.density)
+                            cells = self.ordered.view(-1)[3:4 * n].view(torch.int32)
+                            if self._is_split(p):
+                                B.dg_occ_evaluate_split(m.mlp, m.weights, self._feat[:n], cells, 4, n, q.density)
+                            else:
+                                B.dg_occ_evaluate(m.mlp, m.weights, self._feat[:n], True, cells, 4, n, q.density)
                     continue
                 self.dir_enc[:1].zero_()                        # the density does not depend on the direction: one zero row
                 if self.app_rows is not None:
                     self.app_rows[:1].zero_()
-                self._mlp_fwd(m, order, slice(0, n), self.dir_enc[:1], None if self.app_rows is None else self.app_rows[:1], max(n, 1), n)
+                self._mlp_fwd(p, m, order, slice(0, n), self.dir_enc[:1], None if self.app_rows is None else self.app_rows[:1], max(n, 1), n)
                 with self._timed("dg_occ_update"):
                     B.dg_occ_update(q.density, cell, self.sigma[:n], n)
             q.n_set.zero_()

@@ -459,6 +459,84 @@ def test_density_of_candidates(N):
         B.dg_occ_evaluate(small, weights, planes, False, cell, 1, N, got)
 
 
+@pytest.mark.parametrize("n_app", [0, 48])
+@pytest.mark.parametrize("key,N", [(key, N) for key in GRIDS for N in (1, 31, 63, 1025, 20011)])
+def test_split_features(key, N, n_app):
+    """Features as rows of twelve levels and planes of four: the ordered gather's features level by level, and from them the networks'
+    results of the features in rows, forward, backward and of candidates."""
+    print("[case] split features", key, N, n_app, flush=True)
+    grid, ref_grid = _grids(key)
+    rng = np.random.default_rng(46)
+    u = _coords(N, "faces")
+    order, ordered, _ = _sorted(grid, u, N)
+    table, ud = dev(di.make_table(ref_grid.n_entries, 2, 1.0, seed=47)), dev(u)
+    rows, split = (torch.full((N, 32), float("nan"), dtype=torch.float16, device=DEV) for _ in range(2))
+    for by_position in (True, False):                   # the last one's are the samples' own order
+        B.dg_hashgrid_encode_fwd_ordered(grid, table, ordered, N, rows, by_position=by_position)
+        B.dg_hashgrid_encode_fwd_split(grid, table, ordered, ud, N, split, by_position=by_position)
+        flat, n_rows = split.view(-1), 2 * B.SPLIT_LEVELS * N
+        assert torch.equal(flat[:n_rows].view(N, -1), rows[:, :2 * B.SPLIT_LEVELS])
+        assert torch.equal(flat[n_rows:].view(-1, N, 2).transpose(0, 1).reshape(N, -1), rows[:, 2 * B.SPLIT_LEVELS:])
+        if by_position:
+            mlp = B.dg_mlp_desc(32, 64, 16, 16, 64, 2, 1)
+            weights = dev((rng.standard_normal(9408) * 0.2).astype(np.float16))
+            cell, got, want = torch.arange(N, dtype=torch.int32, device=DEV), torch.zeros(N, device=DEV), torch.zeros(N, device=DEV)
+            B.dg_occ_evaluate_split(mlp, weights, split, cell, 1, N, got)
+            B.dg_occ_evaluate(mlp, weights, rows, True, cell, 1, N, want)
+            assert torch.equal(got, want)
+
+    mlp, S = B.dg_mlp_desc(32, 64, 16, 16, 64, 2, 1, n_app=n_app), 37
+    weights = dev((rng.standard_normal(B.dg_mlp_weight_count(mlp)) * 0.2).astype(np.float16))
+    n_dir = -(-N // S)
+    dir_enc = dev(rng.standard_normal((n_dir, 16)).astype(np.float16))
+    app = dev(rng.standard_normal((n_dir, n_app)).astype(np.float16)) if n_app else None
+    dsigma, drgb = dev((rng.standard_normal(N) * 1e-4).astype(np.float32)), dev((rng.standard_normal((N, 3)) * 1e-4).astype(np.float32))
+    ws = torch.zeros(B.dg_mlp_bwd_app_workspace_bytes(mlp, N, S) // 4 + 64, device=DEV)
+    results = []
+    for fwd, bwd, feat in ((B.dg_mlp_fwd_rows, B.dg_mlp_bwd_rows, rows), (B.dg_mlp_fwd_split, B.dg_mlp_bwd_split, split)):
+        sigma, rgb, dfeat = torch.zeros(N, device=DEV), torch.zeros(N, 3, device=DEV), torch.zeros(N * 32, device=DEV)
+        dW, largest = torch.zeros(B.dg_mlp_weight_count(mlp), device=DEV), torch.zeros(1, dtype=torch.int32, device=DEV)
+        fwd(mlp, weights, feat, dir_enc, app, S, N, sigma, rgb)
+        bwd(mlp, weights, feat, dir_enc, app, S, N, dsigma, drgb, 4096.0, order.n_merged, dfeat, largest, dW, ws)
+        results.append((sigma, rgb, dfeat, largest, dW[:9408], dW[9408:]))
+    for a, b in list(zip(*results))[:5]:                # one kernel on the same numbers read from other places
+        assert torch.equal(a, b)
+    # the appearance columns' sums go out by fp32 atomics, one per column and tile, in any order: each add rounds by 2^-24 of a partial sum
+    # no larger than sqrt(tiles) typical terms in random signs, tiles of them
+    assert not n_app or rel_err(host(results[1][5]), host(results[0][5])) <= 2.0 ** -24 * max(-(-N // 32), 1)
+
+
+@pytest.mark.parametrize("name", ["c2_ngp", "c3_2x2", "c8_app"])
+def test_step_with_split_features(name, monkeypatch):
+    """The training step in spatial order with split features, through every comparison of the plain step; what a caller reads as
+    step.feat is planes."""
+    from test_gpu_step import _compare_step
+    print("[case] step with split features", name, flush=True)
+    monkeypatch.setattr(TrainStep, "_order_min", lambda self, m: 1)
+    split = []
+    monkeypatch.setattr(TrainStep, "_split", lambda self, m, N, use: split.append(N) or True)
+    cfg = di.config(name)
+    cfg["grid"] = dict(cfg["grid"], log2_T=16)
+    _compare_step(cfg, 700, seed=2, lambda1=1e-3, loss_scale=2.0 ** 14, use_jitter_array=False, table_gain=3000.0)
+    assert split
+
+
+def test_refresh_with_split_features(monkeypatch):
+    """The refresh of an occupancy grid from split features: the bits of the one from rows, and the candidates' planes for a caller."""
+    from test_gpu_step_state import _marched
+    print("[case] refresh with split features", flush=True)
+    monkeypatch.setattr(TrainStep, "_order_min", lambda self, m: 1)
+    seen = []
+    for split in (False, True):
+        monkeypatch.setattr(TrainStep, "_split", lambda self, m, N, use: split)
+        step = _marched()[0]
+        assert step.refresh_occupancy(4096) and step._feat_rows[0].levels == (B.SPLIT_LEVELS if split else 16)
+        k = min(step.max_samples, step.occ[0].desc.n_cells // 2)
+        seen.append((step.occ[0].density.clone(), step.feat[:k].clone()))
+    for a, b in zip(*seen):
+        assert torch.equal(a, b)
+
+
 def test_density_of_a_nan_candidate():
     """A NaN among the features: the clip makes the network's NaN -15, the same density as by the separate entry points."""
     print("[case] density of a NaN candidate", flush=True)
