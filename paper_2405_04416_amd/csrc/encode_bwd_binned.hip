@@ -15,6 +15,8 @@
 //     bin receives contiguous runs.  Then workgroups balanced by record count stream the queue,
 //     accumulate in LDS (as scaled 64-bit integers: integer adds are the fastest LDS atomics) and add the
 //     finished bin into dtable with coalesced atomics.
+//     Many bins of few records are taken by workgroups that stay (sparse_bins).
+// Where there are few bins altogether, all of them are accumulated directly, without queues (direct_bins).
 #include "encode_common.h"
 #include <algorithm>
 #include <mutex>

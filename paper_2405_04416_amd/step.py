@@ -169,7 +169,7 @@ class TrainStep:
             return 1 << 62
         T = m.grid.log2_T
         if self.occ is not None:
-            return 3 << 18 if T <= 19 else 1 << 19
+            return 1 << 20 if T < 18 else 3 << 18 if T <= 19 else 1 << 19
         if T <= 20:
             return {17: 5 << 18, 18: 3 << 19, 19: 9 << 18, 20: 3 << 18}.get(T, 1 << 21)
         if not self._fine(m):
@@ -194,7 +194,7 @@ class TrainStep:
         if use == "step":
             return 1.0
         if self.occ is not None:
-            from_2_20 = 4 / 3 if T <= 19 else 2.0 if T == 20 else 1.0
+            from_2_20 = {18: 4 / 3, 19: 4 / 3, 20: 2.0}.get(T, 1.0)
             return 1.25 * from_2_20 if use == "refresh" and T == 19 else from_2_20
         if T <= 20:
             return {17: 2.4, 18: 8 / 3, 19: 2.25, 20: 8 / 3}.get(T, 1.5)
