@@ -324,7 +324,8 @@ int dg_clear(void *dst, uint64_t bytes, void *stream);
 /* One sub-model's share of a training step, each way in one call: what the entry points named below do, in that order, on the
  * sub-model's n_seg segments of S samples each (N = n_seg * S, level-major features).  For callers whose step is bound by the
  * launching, not by the work.  All pointers as in those entry points, each at the sub-model's first segment or sample; the code of the
- * first call that fails is returned, those before it have been launched.
+ * first call that fails is returned, those before it have been launched.  A degree whose square is less than the networks' n_dir is
+ * refused (DG_ERR_ARG) before anything is launched.
  *   dg_field_fwd: dg_sample_segments, dg_dir_encode, dg_hashgrid_encode_fwd (fp16), dg_mlp_fwd, dg_composite_segment_fwd
  *   dg_field_bwd: dg_clear of the gradients (two stretches, either may be empty), dg_composite_segment_bwd, dg_mlp_bwd,
  *                 dg_hashgrid_encode_bwd */

@@ -312,6 +312,7 @@ def _field_call(grid, mlp, first, n_seg, S, degree, seg_first, seg_ray, seg_slot
     """What both ways share.  first: index of the sub-model's first segment in the sample buffers, seg_first: in seg_ray / seg_slot."""
     f32, f16, i32 = torch.float32, torch.float16, torch.int32
     N, n0, rows = n_seg * S, first * S, degree * degree
+    assert rows >= mlp.n_dir                # the networks read n_dir values per segment
     c = FieldCall(grid=C.addressof(grid), mlp=C.addressof(mlp), n_seg=n_seg, S=S, k_max=k_max, degree=degree)
     c.seg_ray, c.seg_slot = _part(seg_ray, i32, seg_first, n_seg), _part(seg_slot, i32, seg_first, n_seg)
     c.weights, c.dir_enc = _ptr(weights, f16), _part(dir_enc, f16, first * rows, n_seg * rows)
@@ -334,6 +335,7 @@ def dg_field_bwd(common, loss_scale, gCk, gTk, dsigma, drgb, dfeat, dtable, dW, 
     f32 = torch.float32
     c = _field_call(*common)
     first, N, n_feat = common[2] * common[4], c.n_seg * c.S, common[1].n_feat
+    assert dW.numel() >= dg_mlp_weight_count(common[1])
     c.loss_scale = loss_scale
     c.gCk, c.gTk = _ptr(gCk, f32), _ptr(gTk, f32)
     c.dsigma, c.drgb, c.dfeat = _part(dsigma, f32, first, N), _part(drgb, f32, 3 * first, 3 * N), _part(dfeat, f32, n_feat * first, n_feat * N)

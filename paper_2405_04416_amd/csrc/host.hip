@@ -70,11 +70,22 @@ extern "C" size_t dg_mlp_weight_count(const dg_mlp_desc *m)
     return c;
 }
 
-extern "C" int dg_field_fwd(const dg_field_call *c, void *stream)
+namespace {
+
+int check_field_call(const dg_field_call *c, const char *who)
 {
-    const char *who = "dg_field_fwd";
     DG_REQUIRE(c && c->grid && c->mlp, DG_ERR_ARG, "%s: null pointer", who);
     DG_REQUIRE(c->reserved == 0, DG_ERR_ARG, "%s: the reserved word must be 0", who);
+    DG_REQUIRE((uint64_t)c->degree * c->degree >= c->mlp->n_dir, DG_ERR_ARG, "%s: %u direction inputs per segment, but degree %u gives fewer", who,
+               c->mlp->n_dir, c->degree);
+    return DG_OK;
+}
+
+}  // namespace
+
+extern "C" int dg_field_fwd(const dg_field_call *c, void *stream)
+{
+    if (int rc = check_field_call(c, "dg_field_fwd")) return rc;
     const uint64_t N = (uint64_t)c->n_seg * c->S;
     if (int rc = dg_sample_segments(c->o, c->d, c->seg_t, c->seg_ray, c->seg_slot, c->n_seg, c->k_max, c->box, c->S, c->seed, nullptr, c->u, c->delta, nullptr, stream))
         return rc;
@@ -86,9 +97,7 @@ extern "C" int dg_field_fwd(const dg_field_call *c, void *stream)
 
 extern "C" int dg_field_bwd(const dg_field_call *c, void *stream)
 {
-    const char *who = "dg_field_bwd";
-    DG_REQUIRE(c && c->grid && c->mlp, DG_ERR_ARG, "%s: null pointer", who);
-    DG_REQUIRE(c->reserved == 0, DG_ERR_ARG, "%s: the reserved word must be 0", who);
+    if (int rc = check_field_call(c, "dg_field_bwd")) return rc;
     const uint64_t N = (uint64_t)c->n_seg * c->S;
     for (int i = 0; i < 2; ++i)
         if (c->clear_bytes[i])

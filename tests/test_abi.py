@@ -129,3 +129,54 @@ def test_bench_refuses_more_than_one_gpu():
     import sys
     res = subprocess.run([sys.executable, os.path.join(ROOT, "bench.py"), "--gpus", "2"], capture_output=True, text=True)
     assert res.returncode != 0 and "ONE GPU" in res.stderr
+
+
+def _field_arguments(degree, n_dir, short_dW):
+    """Arguments of the two one-call bindings for 3 segments of 5 samples, on host tensors."""
+    import torch
+    z = lambda *s, dt=torch.float32: torch.zeros(*s, dtype=dt)
+    i32, f16 = torch.int32, torch.float16
+    grid, mlp = B.dg_grid_desc_init(4, 2, 12, 16, 1.5, [1.0] * 3), B.dg_mlp_desc(8, 32, 16, n_dir, 32, 1)
+    n_seg, S = 3, 5
+    N, n_w = n_seg * S, B.dg_mlp_weight_count(mlp)
+    common = (grid, mlp, 0, n_seg, S, degree, 0, z(n_seg, dt=i32), z(n_seg, dt=i32), 1, z(n_w, dt=f16), z(N, 3), z(N), z(n_seg, degree * degree, dt=f16),
+              z(N, 8, dt=f16), z(N), z(N, 3))
+    table, Ck, Tk, dW = z(grid.n_entries, 2), z(n_seg, 1, 3), z(n_seg, 1), z(n_w - short_dW)
+    return ((common, [0.0] * 6, 1, z(n_seg, 3), z(n_seg, 3), z(n_seg, 1, 2), table, Ck, Tk),
+            (common, 1.0, Ck, Tk, z(N), z(N, 3), z(N, 8), table, dW, (table, dW), z(64), z(64)))
+
+
+@pytest.mark.parametrize("degree,n_dir,short_dW,refused", [(2, 4, 0, ()), (2, 16, 0, ("fwd", "bwd")), (3, 16, 0, ("fwd", "bwd")), (2, 4, 1, ("bwd",))])
+def test_one_call_bindings_refuse_what_the_single_ones_refuse(degree, n_dir, short_dW, refused, monkeypatch):
+    """Rows of the direction table shorter than the networks read them, a weight gradient shorter than the networks write it: the
+    bindings dg_mlp_fwd_app and dg_mlp_bwd_app refuse both.  The launching calls are replaced, nothing runs."""
+    real, launched = B.lib(), []
+
+    class Stub:
+        def __getattr__(self, name):
+            if name in ("dg_field_fwd", "dg_field_bwd"):
+                return lambda *a: launched.append(name[-3:]) or 0
+            return getattr(real, name)
+
+    fwd, bwd = _field_arguments(degree, n_dir, short_dW)
+    monkeypatch.setattr(B, "lib", lambda: Stub())
+    monkeypatch.setattr(B, "_ptr", lambda t, dtype=None, optional=False: t.data_ptr())
+    monkeypatch.setattr(B, "_stream", lambda: 0)
+    for way, call, args in (("fwd", B.dg_field_fwd, fwd), ("bwd", B.dg_field_bwd, bwd)):
+        launched.clear()
+        if way in refused:
+            with pytest.raises(AssertionError):
+                call(*args)
+            assert not launched
+        else:
+            call(*args)
+            assert launched == [way]
+
+
+@pytest.mark.parametrize("name", ["dg_field_fwd", "dg_field_bwd"])
+def test_one_call_refuses_short_direction_rows(name):
+    """The library looks at it before all else (every pointer of the call is NULL, nothing could be launched)."""
+    grid, mlp = B.dg_grid_desc_init(16, 2, 14, 16, 1.4, [1.0] * 3), B.dg_mlp_desc(32, 64, 16, 16, 64, 2)
+    call = B.FieldCall(grid=C.addressof(grid), mlp=C.addressof(mlp), n_seg=3, S=5, k_max=1, degree=2)
+    assert getattr(B.lib(), name)(C.byref(call), None) != 0
+    assert b"direction inputs" in B.lib().dg_last_error()
