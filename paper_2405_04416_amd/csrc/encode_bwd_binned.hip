@@ -712,7 +712,7 @@ scan_rows_kernel(uint32_t *__restrict__ rows, uint32_t n_rows, uint32_t n_keys, 
 }
 
 // binbase = exclusive scan of totals, and the list of pieces the accumulate workgroups take: pieces[0].x of them, each (key,
-// first record, end, whether it is the whole bin) -- a bin is cut into acc_pieces of its record count, in equal shares, so that work is balanced whatever
+// first record, end) -- a bin is cut into acc_pieces of its record count, in equal shares, so that work is balanced whatever
 // the bins hold, and a workgroup finds its share with one load.  (One workgroup; n_keys is at most a few tens of thousands.)
 __global__ void __launch_bounds__(1024)
 scan_totals_kernel(const uint32_t *__restrict__ totals, uint32_t n_keys, uint32_t piece_log2, uint32_t *__restrict__ binbase, uint4 *__restrict__ pieces)
@@ -730,7 +730,7 @@ scan_totals_kernel(const uint32_t *__restrict__ totals, uint32_t n_keys, uint32_
     for (uint32_t i = lo; i < hi; ++i) {
         const uint32_t total = totals[i], n = acc_pieces(total, piece_log2), share = n ? (total + n - 1u) / n : 0u;
         binbase[i] = run;
-        for (uint32_t q = 0; q < n; ++q) pieces[1 + run_p++] = make_uint4(i, run + q * share, run + min((q + 1u) * share, total), n == 1u ? 1u : 0u);
+        for (uint32_t q = 0; q < n; ++q) pieces[1 + run_p++] = make_uint4(i, run + q * share, run + min((q + 1u) * share, total), 0u);
         run += total;
     }
     if (threadIdx.x == 1023) {
@@ -823,9 +823,10 @@ accumulate_kernel(dg_grid_desc g, Plan plan, const uint32_t *__restrict__ binbas
 // The same for bins of few records, which are bound not by the queue but by the chain of a bin -- its piece, the first records from
 // memory, the adds, the table's way in and out -- in a compute unit that one table fills.  One workgroup per compute unit stays
 // and takes piece after piece from a common counter: the next piece's first records are on their way while the table goes out,
-// which also clears it.  A bin that comes in one piece is its workgroup's alone, so what the gradient holds there is asked for
-// during the adds and stored with the sums added, instead of adding with atomics.
-// Where it serves: sparse_bins.  Eight sub-models, four of them with 4080 bins of 5 k records: 245 -> 183 us each.
+// which also clears it.
+// Where it serves: sparse_bins.  Eight sub-models, four of them with 4074 bins of 5.7 k records: 243 -> 219 us each.  (Bins that come in one piece
+// stored instead, with what the gradient held added: 183 us, but then an add of another stream to the same gradient is lost.)
+
 // kAccDepth records per thread from `at` on of the n of a piece, several in flight so that the queue streams at memory speed: the loads are unconditional
 // (index clamped into the piece) so that they issue back to back
 __device__ __forceinline__ void load_records(u32x4 (&rec)[kAccDepth], const u32x4 *__restrict__ records, uint32_t at, uint32_t n)
@@ -877,12 +878,6 @@ accumulate_sparse_kernel(dg_grid_desc g, Plan plan, const uint32_t *__restrict__
         while (l + 1 < g.n_levels && key >= plan.key_base[l + 1]) ++l;
         const uint32_t first = (key - plan.key_base[l]) * kChunk, n_values = 2 * min(kChunk, g.offset[l + 1] - g.offset[l] - first);
         float *dst = dtable + 2 * ((size_t)g.offset[l] + first);
-        // a bin that comes in one piece is this workgroup's alone: what the table holds is asked for now and stored with the sums added
-        const bool whole = piece.w != 0u;
-        float held[kPerThread];
-        if (whole)
-#pragma unroll
-            for (int j = 0; j < kPerThread; ++j) held[j] = dst[min(j * kAccBlock + threadIdx.x, n_values - 1u)];
         for (uint32_t done = 0;; done += kAccDepth * kAccBlock) {
             u32x4 now[kAccDepth];
 #pragma unroll
@@ -916,8 +911,7 @@ accumulate_sparse_kernel(dg_grid_desc g, Plan plan, const uint32_t *__restrict__
             const unsigned long long bits = from[i >> 1];
             from[i >> 1] = 0ull;
             const float sum = (float)(from_low_bits(bits) * inv_scale);
-            if (whole) dst[i] = held[j] + sum;
-            else if (sum != 0.0f) unsafeAtomicAdd(dst + i, sum);
+            if (sum != 0.0f) unsafeAtomicAdd(dst + i, sum);
         }
         if (!another) break;
         __syncthreads();
@@ -993,9 +987,9 @@ bool direct_bins(const Plan &p, uint32_t n_levels, uint64_t N)
 }
 
 // Many bins with fewer records than entries: accumulate_sparse_kernel.  Its time against accumulate_kernel's in us, with `bins` bins and
-// `records` records per bin at most: 4080 bins, 5300 records 183 / 245; 3900, 5000 198 / 270; 2560, 2100 134 / 144; 2560, 1600 131 / 141;
-// 13 900, 1400 1000 / 1010.  Few bins: 1380, 5700 101 / 73; 830, 4700 55 / 55; 830, 9100 65 / 62; 830, 14 000 71 / 60.  Many records: 3500
-// bins, 22 000 351 / 325; 14 000, 34 000 1750 / 1656.
+// `records` records per bin at most: 4074 bins, 5700 records 219 / 243; 4566, 4600 241 / 278; 3731, 5600 207 / 213; 2238, 2600 129 / 145; 2047, 2000
+// 128 / 140; 15 923, 1300 955 / 1014.  Few bins: 1123, 7200 97 / 73; 611, 6400 57 / 54; 611, 12 300 65 / 63.  Many records: 15 900, 10 000 1065 / 1146;
+// 4560, 13 200 334 / 345; 3730, 13 900 281 / 263.
 bool sparse_bins(const Plan &p, uint32_t n_levels, uint64_t nb)
 {
     return p.n_keys >= 2048u && nb * 4ull * (n_levels - p.first_level) < (uint64_t)p.n_keys * kChunk;

@@ -365,7 +365,7 @@ fold_wide_kernel(const double *__restrict__ wide_table, uint32_t n, float *__res
     const uint32_t i = blockIdx.x * kBlock + threadIdx.x;
     if (i >= n) return;
     const float v = (float)wide_table[i];
-    if (v != 0.0f) dtable[i] += v;
+    if (v != 0.0f) unsafeAtomicAdd(dtable + i, v);
 }
 
 // Merged levels whose bricks are summed in fp64: tables of at most 2^18 entries, which get many adds per entry -- the coarse levels

@@ -244,6 +244,32 @@ def test_every_number_of_merged_levels(n_merged, N):
         assert np.linalg.norm(have[sl] - want[sl]) <= 4 * 2.0 ** -20 * np.linalg.norm(want[sl]), l
 
 
+def test_ordered_gradients_of_two_streams_into_one_table():
+    """dtable "+=": two streams, each with a workspace of its own, add to one gradient at the same time and nothing of either is lost."""
+    print("[case] ordered gradients of two streams", flush=True)
+    grid, ref_grid = _grids("large")
+    N, passes = 20011, 4
+    u = _coords(N, "points")
+    order, ordered, pieces = _sorted(grid, u, N)
+    g = (np.random.default_rng(48).standard_normal((N, 32)) * 1e-3).astype(np.float32)
+    ud, gd = dev(u), dev(_mixed(g, order.n_merged))
+    largest = gd.abs().max().reshape(1).view(torch.int32)
+    need = B.dg_hashgrid_encode_bwd_ordered_workspace_bytes(grid, order, N) // 4 + 64
+    streams, ws = [torch.cuda.Stream() for _ in range(2)], [torch.zeros(need, device=DEV) for _ in range(2)]
+    dtable = torch.zeros(ref_grid.n_entries, 2, device=DEV)
+    torch.cuda.synchronize()
+    for _ in range(passes):
+        for s, w in zip(streams, ws):
+            with torch.cuda.stream(s):
+                B.dg_hashgrid_encode_bwd_ordered(grid, order, ordered, pieces, ud, gd, largest, N, dtable, w)
+    torch.cuda.synchronize()
+    want, have = 2.0 * passes * oracle.encode_bwd(ref_grid, u, g.astype(np.float64)), host(dtable).astype(np.float64)
+    for l in range(16):
+        # records rounded to 2^-20, sums rounded to fp32, eight fp32 adds of them
+        sl = slice(ref_grid.first[l], ref_grid.first[l + 1])
+        assert np.linalg.norm(have[sl] - want[sl]) <= 4 * 2.0 ** -20 * np.linalg.norm(want[sl]), l
+
+
 def test_many_bricks_to_an_entry():
     """29 791 bricks on tables of 2^14 entries: some seventy bricks and more add to an entry.  Their sums are added in fp64, so what is
     left are the roundings of a contribution (two products for its weight, one with the gradient, one of 1 - fraction) and that of the

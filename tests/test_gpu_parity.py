@@ -386,6 +386,31 @@ def test_encode_bwd_many_sparse_bins(N, bad):
     assert np.all(got[ref == 0] == 0)
 
 
+def test_encode_bwd_of_two_streams_into_one_gradient():
+    """dtable "+=": two streams, each with a workspace of its own, add to one gradient at the same time and nothing of either is lost."""
+    say("encode bwd of two streams")
+    g, r, _ = _both_grids("sparse")
+    N, passes = 50011, 4
+    u = _coords(N, "rays", seed=75)
+    dfeat = (np.random.default_rng(76).standard_normal((N, 2 * g.n_levels)) * 1e-3).astype(np.float32)
+    ud, dd = dev(u), dev(to_planes(dfeat))
+    need = B.dg_hashgrid_encode_bwd_workspace_bytes(g, N) // 4 + 64
+    streams, ws = [torch.cuda.Stream() for _ in range(2)], [torch.zeros(need, device=DEV) for _ in range(2)]
+    dtable = torch.zeros(r.n_entries, 2, device=DEV)
+    torch.cuda.synchronize()
+    for _ in range(passes):
+        for s, w in zip(streams, ws):
+            with torch.cuda.stream(s):
+                B.dg_hashgrid_encode_bwd(g, ud, dd, N, dtable, w)
+    torch.cuda.synchronize()
+    ref, got = 2.0 * passes * oracle.encode_bwd(r, u, dfeat.astype(np.float64)), host(dtable).astype(np.float64)
+    for l in range(g.n_levels):
+        sl = slice(r.first[l], r.first[l + 1])
+        # records rounded to 2^-20, sums rounded to fp32, eight fp32 adds of them
+        assert np.linalg.norm(got[sl] - ref[sl]) <= 4 * 2.0 ** -20 * np.linalg.norm(ref[sl]), l
+    assert np.all(got[ref == 0] == 0)
+
+
 @pytest.mark.parametrize("with_ws", [False, True])
 def test_encode_bwd_empty_batch(with_ws):
     """N = 0 adds nothing, with and without a workspace."""

@@ -17,3 +17,13 @@ def test_no_instruction_in_inline_assembly(path):
     text = re.sub(r"//.*", "", open(path).read())
     for body in re.findall(r"\basm\b\s*(?:volatile\s*)?\(\s*\"([^\"]*)\"", text):
         assert body.strip() == "", body
+
+
+@pytest.mark.parametrize("path", [p for p in SOURCES if os.path.basename(p).startswith("encode")], ids=os.path.basename)
+def test_table_gradients_are_only_added_to(path):
+    """dtable "+=": other streams may add to the same gradient, so every add of a kernel is atomic.  A plain store is a NaN that marks
+    the gradient."""
+    for function in re.sub(r"//.*", "", open(path).read()).split("\n}\n"):
+        names = "|".join(["dtable"] + re.findall(r"\*\s*(\w+)\s*=\s*dtable\b", function))
+        for store in re.findall(r"\b(?:%s)\s*\[[^;=]*\]\s*[-+]?=[^=][^;]*;" % names, function):
+            assert "__uint_as_float(0x7fc00000u)" in store, store
