@@ -223,7 +223,7 @@ int dg_hashgrid_encode_fwd_split(const dg_grid_desc *desc, const float *table, c
 /* dg_hashgrid_encode_bwd on the sorted list.  dfeat: rows [N, 2 * n_merged] fp32 of the merged levels (16-byte aligned, in
  * the samples' original order), then the planes [L - n_merged, N, 2] of the others -- as dg_mlp_bwd_rows writes it; u [N,3]
  * the samples in their original order.  *largest: device word, the bit pattern of a float that no |dfeat| exceeds.
- * Merged levels: up to 128 samples of one cell are added up in fp32, what a brick holds of such sums in 64 bits: in fp64 at the
+ * Merged levels: up to 96 samples of one cell are added up in fp32, what a brick holds of such sums in 64 bits: in fp64 at the
  * levels whose tables together have at most 8192 entries, in fixed point with quanta of 2^-37 of *largest or finer at the others.
  * The bricks' sums are added in fp64 at levels of at most 2^18 entries, in fp32 at larger ones.  The levels that are
  * not merged go through the bins as in dg_hashgrid_encode_bwd, with its precision.  Where *largest is infinite or NaN every brick leaves

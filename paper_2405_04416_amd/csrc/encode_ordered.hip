@@ -88,18 +88,21 @@ encode_planes_kernel(dg_grid_desc g, const float2 *__restrict__ table, const flo
 // integers adds those low bits, what happens above bit 50 is dropped when the sum is read.  (Integer adds are the fastest LDS
 // atomics: random addresses 3.6 T adds/s against 1.95 in fp64.)
 // A lane takes two levels and a run of consecutive samples: the eight corner sums of the cell that the run is in stay in registers and
-// go to LDS when it leaves the cell.  Neighbouring lanes take the same samples at the neighbouring levels, so that what they read of
+// go to LDS when it leaves the cell, and every eight (six) samples together with those of its neighbours in the same cell: at most 96
+// samples of a cell are added up in fp32.  Neighbouring lanes take the same samples at the neighbouring levels, so that what they read of
 // a sample's row of the gradient lies side by side and costs the vector cache one or two look-ups, not one per lane.  Two or three of
 // the eight wavefronts share the lower half of the levels, whose runs seldom leave a cell, the others the upper half.
 // What a level needs is worked out once per workgroup and kept in LDS; the write-out takes 25 vector instructions per 64 sums.
-// 13.3 M samples, T = 2^19, levels 0..11: 1.23 ms (vector units busy 0.64, LDS 0.67); 33.5 M, T = 2^24, levels 0..9: 2.15 ms, of which the
-// rows, some 1.6 random lines each, take 0.9 at the rate of the fabric.  Measured on the way:
+// 13.3 M samples, T = 2^19, levels 0..11: 1.27 ms; 33.5 M, T = 2^24, levels 0..9: 2.33 ms, of which the rows, some 1.6 random lines each,
+// take 0.9 at the rate of the fabric.  Full pieces in one cell, terms of either sign: 8.2e-8 from 64-bit sums.  Measured on the way:
+// - runs of up to 66 samples and then sums over lanes, up to 512 samples of a cell in fp32: 1.23 and 2.21 ms, but 1.2e-7 from 64-bit sums
+//   (pairs of samples and sums over 64 lanes: 8.6e-8); sixteen samples at a time 1.18 and 2.21 ms, 9.3e-8, twelve 1.25 and 2.27 ms, 8.8e-8;
+// - eight samples at a time without sums over lanes: 1.40 and 2.79 ms (adds to one address take turns);
 // - every wavefront at all levels of an eighth of the samples, two samples per lane at a time: 1.66 and 3.01 ms (the sums over lanes
 //   and the adds to LDS come every other sample, and every level is set up eight times for the write-out);
 // - a wavefront per pair of levels, every lane at a row of its own: 1.27 and 2.95 ms, of which the loads alone 0.94 and 2.3;
-// - as it stands without the sums over lanes at the end: 1.28 and 2.43 ms (adds to one address take turns);
-// - one and two wavefronts at the lower half: 1.46 and 3.10 ms, three and four: 1.30 and 2.46 ms;
-// - 80 registers for six wavefronts per SIMD: 2.4 and 4.9 ms (spills).
+// - and with whole runs: one and two wavefronts at the lower half 1.46 and 3.10 ms, three and four 1.30 and 2.46 ms; 80 registers for six
+//   wavefronts per SIMD 2.4 and 4.9 ms (spills).
 struct Boxes { uint32_t n_merged, n_wide, n_fold, dim[kMaxMerged][3], first[kMaxMerged + 1]; };
 
 constexpr int kBrickWaves = 8;
@@ -175,7 +178,7 @@ __device__ __forceinline__ void add_to_box(unsigned long long *d, bool wide, dou
     }
 }
 
-// Adds the sums that lanes hold at the end of their runs; lanes STRIDE apart are at the same levels.  A segmented sum along those lanes
+// Adds the sums that lanes hold; lanes STRIDE apart are at the same levels.  A segmented sum along those lanes
 // within each row of 16 (a run of lanes in the same cell starts where `head` is set), then its last lane adds.
 template <int STRIDE, int STEP>
 __device__ __forceinline__ void row_step(float (&vx)[8], float (&vy)[8], int &f)
@@ -269,54 +272,62 @@ brick_bwd_kernel(dg_grid_desc g, Bricks b, Boxes boxes, const uint2 *__restrict_
         const LevelBox box[2] = {levels[2 * q], levels[2 * q + 1]};
         float vx[2][8], vy[2][8];
         uint32_t slot[2] = {0u, 0u};                                  // of the cells whose sums vx, vy are
-#pragma unroll
-        for (int which = 0; which < 2; ++which)
-#pragma unroll
-            for (int c = 0; c < 8; ++c) { vx[which][c] = 0.0f; vy[which][c] = 0.0f; }
         // a sample's coordinates are asked for two samples ahead, its row of the gradient one ahead
         const uint32_t last = (n - 1u) * (uint32_t)sizeof(float4);
         uint32_t at = i0 * (uint32_t)sizeof(float4);
         auto sample = [&](uint32_t offset) { return *reinterpret_cast<const float4 *>(list + min(offset, last)); };
         float4 s = sample(at), s_next = sample(at + (uint32_t)sizeof(float4));
         float4 row = dfeat[(size_t)__float_as_uint(s.w) * pairs + q];
+        // samples that a lane adds up in fp32 before the sums over lanes, which take four steps with runs next to one another, else three: on
+        // average 7.5 roundings per sample either way
+        const uint32_t in_fp32 = here == 1u ? 6u : 8u;
 #pragma unroll 1
-        for (uint32_t k = 0; k < run; ++k, at += (uint32_t)sizeof(float4)) {
-            const float uu[3] = {unit(s.x), unit(s.y), unit(s.z)}, gx[2] = {row.x, row.z}, gy[2] = {row.y, row.w};
-            s = s_next;
-            row = dfeat[(size_t)__float_as_uint(s.w) * pairs + q];
-            s_next = sample(at + 2u * (uint32_t)sizeof(float4));
-            if (at > last) continue;                                  // past the end of the piece
+        for (uint32_t k0 = 0; k0 < run; k0 += in_fp32) {
+            const bool live = at <= last;                                 // the lane has samples among these
 #pragma unroll
-            for (int which = 0; which < 2; ++which) {
-                const LevelBox &v = box[which];
-                float cell[3], w1[3], w0[3];
+            for (int which = 0; which < 2; ++which)
 #pragma unroll
-                for (int a = 0; a < 3; ++a) {
-                    locate_unit(uu[a], v.scale[a], v.last[a], cell[a], w1[a]);
-                    w0[a] = 1.0f - w1[a];
-                }
-                // whole numbers below 2^24: exact in fp32
-                const uint32_t now = min((uint32_t)__builtin_fmaf(cell[2], v.nxy, __builtin_fmaf(cell[1], v.nx, cell[0] - v.origin)), v.last_slot);
-                if (k > 0 && now != slot[which]) {
-                    add_to_box(sums + v.first + slot[which], v.wide, to_fixed, (uint32_t)v.nx, (uint32_t)v.nxy, n_vertices, vx[which], vy[which]);
+                for (int c = 0; c < 8; ++c) { vx[which][c] = 0.0f; vy[which][c] = 0.0f; }
+            const uint32_t k1 = min(k0 + in_fp32, run);
+#pragma unroll 1
+            for (uint32_t k = k0; k < k1; ++k, at += (uint32_t)sizeof(float4)) {
+                const float uu[3] = {unit(s.x), unit(s.y), unit(s.z)}, gx[2] = {row.x, row.z}, gy[2] = {row.y, row.w};
+                s = s_next;
+                row = dfeat[(size_t)__float_as_uint(s.w) * pairs + q];
+                s_next = sample(at + 2u * (uint32_t)sizeof(float4));
+                if (at > last) continue;                                  // past the end of the piece
 #pragma unroll
-                    for (int c = 0; c < 8; ++c) { vx[which][c] = 0.0f; vy[which][c] = 0.0f; }
-                }
-                slot[which] = now;
-                const float px[2] = {gx[which] * w0[0], gx[which] * w1[0]}, py[2] = {gy[which] * w0[0], gy[which] * w1[0]};
-                const float yz[4] = {w0[1] * w0[2], w1[1] * w0[2], w0[1] * w1[2], w1[1] * w1[2]};
+                for (int which = 0; which < 2; ++which) {
+                    const LevelBox &v = box[which];
+                    float cell[3], w1[3], w0[3];
 #pragma unroll
-                for (int c = 0; c < 8; ++c) {
-                    vx[which][c] = __builtin_fmaf(px[c & 1], yz[c >> 1], vx[which][c]);
-                    vy[which][c] = __builtin_fmaf(py[c & 1], yz[c >> 1], vy[which][c]);
+                    for (int a = 0; a < 3; ++a) {
+                        locate_unit(uu[a], v.scale[a], v.last[a], cell[a], w1[a]);
+                        w0[a] = 1.0f - w1[a];
+                    }
+                    // whole numbers below 2^24: exact in fp32
+                    const uint32_t now = min((uint32_t)__builtin_fmaf(cell[2], v.nxy, __builtin_fmaf(cell[1], v.nx, cell[0] - v.origin)), v.last_slot);
+                    if (k > k0 && now != slot[which]) {
+                        add_to_box(sums + v.first + slot[which], v.wide, to_fixed, (uint32_t)v.nx, (uint32_t)v.nxy, n_vertices, vx[which], vy[which]);
+#pragma unroll
+                        for (int c = 0; c < 8; ++c) { vx[which][c] = 0.0f; vy[which][c] = 0.0f; }
+                    }
+                    slot[which] = now;
+                    const float px[2] = {gx[which] * w0[0], gx[which] * w1[0]}, py[2] = {gy[which] * w0[0], gy[which] * w1[0]};
+                    const float yz[4] = {w0[1] * w0[2], w1[1] * w0[2], w0[1] * w1[2], w1[1] * w1[2]};
+#pragma unroll
+                    for (int c = 0; c < 8; ++c) {
+                        vx[which][c] = __builtin_fmaf(px[c & 1], yz[c >> 1], vx[which][c]);
+                        vy[which][c] = __builtin_fmaf(py[c & 1], yz[c >> 1], vy[which][c]);
+                    }
                 }
             }
+            // what the lanes then hold, first summed over the lanes of a row of 16 that are in the same cell: on the coarser levels
+            // these are most of them, and adds to one address take turns
+            if (here == 1u) finish_runs<1>(sums, box, slot, vx, vy, live, lane, to_fixed, n_vertices);
+            else if (here == 2u) finish_runs<2>(sums, box, slot, vx, vy, live, lane, to_fixed, n_vertices);
+            else finish_runs<3>(sums, box, slot, vx, vy, live, lane, to_fixed, n_vertices);
         }
-        // what the lanes hold at the end, first summed over the lanes of a row of 16 that are in the same cell: on the coarser levels
-        // these are most of them, and adds to one address take turns
-        if (here == 1u) finish_runs<1>(sums, box, slot, vx, vy, i0 < n, lane, to_fixed, n_vertices);
-        else if (here == 2u) finish_runs<2>(sums, box, slot, vx, vy, i0 < n, lane, to_fixed, n_vertices);
-        else finish_runs<3>(sums, box, slot, vx, vy, i0 < n, lane, to_fixed, n_vertices);
     }
     __syncthreads();
     for (uint32_t l = 0; l < boxes.n_merged; ++l) {

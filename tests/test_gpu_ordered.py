@@ -233,11 +233,11 @@ def test_every_number_of_merged_levels(n_merged, N):
     want, have = oracle.encode_bwd(ref_grid, u, g.astype(np.float64)), host(dtable).astype(np.float64)
     scale = oracle.encode_bwd(ref_grid, u, np.abs(g).astype(np.float64))
     assert np.all(have[want == 0] == 0)
-    # four roundings in a contribution, at most 66 adds in a lane's run (4096 samples on 63 lanes), four over lanes, a few into the table
+    # four roundings in a contribution, at most eight adds in a lane's run, four over lanes, up to sixteen bricks' into the table
     quantum = 2.0 ** -37 * float(np.abs(g).max()) * N
     for l in range(n_merged):
         sl = slice(ref_grid.first[l], ref_grid.first[l + 1])
-        assert np.all(np.abs(have[sl] - want[sl]) <= 80 * 2.0 ** -24 * scale[sl] + quantum), l
+        assert np.all(np.abs(have[sl] - want[sl]) <= 32 * 2.0 ** -24 * scale[sl] + quantum), l
     for l in range(n_merged, 16):
         # not the brick sums: records rounded to 2^-20
         sl = slice(ref_grid.first[l], ref_grid.first[l + 1])
@@ -268,6 +268,39 @@ def test_ordered_gradients_of_two_streams_into_one_table():
         # records rounded to 2^-20, sums rounded to fp32, eight fp32 adds of them
         sl = slice(ref_grid.first[l], ref_grid.first[l + 1])
         assert np.linalg.norm(have[sl] - want[sl]) <= 4 * 2.0 ** -20 * np.linalg.norm(want[sl]), l
+
+
+@pytest.mark.parametrize("n_merged", [4, 8, 12])
+def test_full_pieces_in_one_cell(n_merged):
+    """256 bricks whose 4096 samples each lie in one cell of the coarser levels, of either sign: what is added up in fp32 before it
+    reaches 64 bits shows here, where no rounding at the end hides it."""
+    print("[case] full pieces in one cell", n_merged, flush=True)
+    q = CUTS["flat"]
+    growth = B.dg_growth_factor(16, q["n_max"], 16)
+    grid, ref_grid = (f(16, 2, q["log2_T"], 16, growth, q["extent"]) for f in (B.dg_grid_desc_init, oracle.grid_init))
+    order = B.dg_order_desc_init(grid, q["made_for"])
+    order.n_merged = n_merged
+    rng = np.random.default_rng(49)
+    N, bricks = 256 * 4096, rng.choice(order.total, 256, replace=False)
+    nx, ny, nz = order.n_bricks
+    middle = (np.stack([bricks % nx, bricks // nx % ny, bricks // (nx * ny)], 1) + 0.5) / np.asarray([nx, ny, nz])
+    u = (np.repeat(middle, 4096, 0) + 1e-3 * (rng.random((N, 3)) - 0.5)).astype(np.float32)
+    g = np.zeros((N, 32), np.float32)
+    g[:, :2 * n_merged] = rng.standard_normal((N, 2 * n_merged)) * 1e-3
+    ordered, pieces = torch.zeros(N, 4, device=DEV), torch.zeros(B.dg_order_pieces_words(order, N), dtype=torch.int32, device=DEV)
+    ud, gd = dev(u), dev(_mixed(g, n_merged))
+    B.dg_order_samples(order, ud, N, ordered, pieces, torch.zeros(B.dg_order_workspace_bytes(order) // 4, dtype=torch.int32, device=DEV))
+    assert int(pieces[0]) == 256
+    dtable = torch.zeros(ref_grid.n_entries, 2, device=DEV)
+    ws = torch.zeros(B.dg_hashgrid_encode_bwd_ordered_workspace_bytes(grid, order, N) // 4 + 64, device=DEV)
+    B.dg_hashgrid_encode_bwd_ordered(grid, order, ordered, pieces, ud, gd, gd.abs().max().reshape(1).view(torch.int32), N, dtable, ws)
+    want, have = oracle.encode_bwd(ref_grid, u, g.astype(np.float64)), host(dtable).astype(np.float64)
+    for l in range(n_merged):
+        sl = slice(ref_grid.first[l], ref_grid.first[l + 1])
+        # terms of either sign: roundings add up in quadrature, and so do the terms to `want`.  Per sample four in the contribution, 7.5 on
+        # average in the sums over samples and lanes, and the last to fp32 and its adds: 13 of 0.42 x 2^-24 each (a rounding is uniform
+        # over an ulp, which is 2^-24 to 2^-23 of the value), 9.0e-8; 512 bricks and features to average over: 11 % for three deviations
+        assert np.linalg.norm(have[sl] - want[sl]) <= 1.0e-7 * np.linalg.norm(want[sl]), l
 
 
 def test_many_bricks_to_an_entry():
