@@ -119,6 +119,14 @@ constexpr int kTileRow = 36, kTileHalves = 32 * kTileRow, kScratchHalves = 2 * k
 typedef _Float16 h4 __attribute__((ext_vector_type(4)));
 enum TileKind { kTiled, kNatural };
 
+// What a lane reads of a tile, other lanes wrote.  The hardware keeps a wavefront's LDS operations in order, but the compiler sees
+// only that a lane's own addresses differ: this keeps it from moving LDS accesses of one side to the other.  Emits no instruction.
+__device__ __forceinline__ void tile_exchange()
+{
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront", "local");
+    __builtin_amdgcn_wave_barrier();
+}
+
 // k-step ks of a packed tensor (its features 16 ks .. 16 ks + 15) into a tile
 template <TileKind KIND>
 __device__ __forceinline__ void put_step(_Float16 *tile, int lane, int ks, h8 x)
@@ -128,19 +136,21 @@ __device__ __forceinline__ void put_step(_Float16 *tile, int lane, int ks, h8 x)
     *reinterpret_cast<h4 *>(row + (KIND == kTiled ? 8 : 4)) = __builtin_shufflevector(x, x, 4, 5, 6, 7);
 }
 
-// the two sample k-steps of the transposed tile
+// the two sample k-steps of the transposed tile, whose place can be written again at once
 __device__ __forceinline__ void get_transposed(const _Float16 *tile, int lane, h8 out[2])
 {
     typedef __fp16 g4 __attribute__((ext_vector_type(4)));
     typedef __attribute__((address_space(3))) g4 *lds_g4;
     const int i = lane & 15;
     const _Float16 *at = tile + (4 * (lane >> 5) + (i >> 2)) * kTileRow + (lane & 16) + 4 * (i & 3);
+    tile_exchange();
 #pragma unroll
     for (int p = 0; p < 2; ++p) {
         const h4 lo = __builtin_bit_cast(h4, __builtin_amdgcn_ds_read_tr16_b64_v4f16((lds_g4)(at + 16 * p * kTileRow)));
         const h4 hi = __builtin_bit_cast(h4, __builtin_amdgcn_ds_read_tr16_b64_v4f16((lds_g4)(at + (16 * p + 8) * kTileRow)));
         out[p] = __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7);
     }
+    tile_exchange();
 }
 
 template <TileKind KIND0 = kTiled, TileKind KIND1 = KIND0>

@@ -27,3 +27,17 @@ def test_table_gradients_are_only_added_to(path):
         names = "|".join(["dtable"] + re.findall(r"\*\s*(\w+)\s*=\s*dtable\b", function))
         for store in re.findall(r"\b(?:%s)\s*\[[^;=]*\]\s*[-+]?=[^=][^;]*;" % names, function):
             assert "__uint_as_float(0x7fc00000u)" in store, store
+
+
+@pytest.mark.parametrize("path", SOURCES, ids=os.path.basename)
+def test_transposing_reads_are_fenced(path):
+    """A transposing LDS read returns what other lanes stored, which the compiler cannot see: a function that reads so keeps it behind
+    the stores before and ahead of those that follow."""
+    text = re.sub(r"//.*", "", open(path).read())
+    fences = [name for name, body in re.findall(r"\bvoid (\w+)\(\)\s*\{(.*?)\n\}", text, re.S)
+              if "__builtin_amdgcn_fence" in body and "__builtin_amdgcn_wave_barrier" in body]
+    for function in text.split("\n}\n"):
+        reads = [m.start() for m in re.finditer(r"__builtin_amdgcn_ds_read_tr", function)]
+        if reads:
+            calls = [m.start() for name in fences for m in re.finditer(r"\b%s\(\);" % name, function)]
+            assert calls and min(calls) < reads[0] and max(calls) > reads[-1], function
