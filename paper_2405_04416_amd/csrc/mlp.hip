@@ -58,9 +58,8 @@ int mlp_composite_fwd(const char *who, const dg_mlp_desc *desc, const void *weig
     DG_REQUIRE(desc->n_app == 0 || (app && dg::aligned(app, 16)), DG_ERR_ARG, "%s: appearance rows missing or not 16-byte aligned", who);
     DG_REQUIRE(dg::aligned(feat, layout != dg::kPlanes ? 16 : 4) && dg::aligned(dir_enc, 16), DG_ERR_ARG, "%s: feat must be %d-byte, dir_enc 16-byte aligned", who,
                layout != dg::kPlanes ? 16 : 4);
-    dg::mlp_mfma_render(weights, feat, layout, dir_enc, app, desc->n_app, S, n_seg, desc->act_c, delta, t, seg_ray, seg_slot, k_max, Ck, Tk, Dk,
-                        (hipStream_t)stream);
-    return dg::launch_status(who);
+    return dg::mlp_mfma_render(who, weights, feat, layout, dir_enc, app, desc->n_app, S, n_seg, desc->act_c, delta, t, seg_ray, seg_slot, k_max, Ck, Tk, Dk,
+                               (hipStream_t)stream);
 }
 
 int mlp_bwd(const char *who, const dg_mlp_desc *desc, const void *weights, const void *feat, dg::FeatureLayout layout, uint32_t n_merged, const void *dir_enc,

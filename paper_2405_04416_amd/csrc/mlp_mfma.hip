@@ -740,19 +740,21 @@ void mlp_mfma_density_max(const void *weights, const void *feat, FeatureLayout l
     else density_max_kernel<kSplit><<<grid, kBlock, 0, st>>>(w, f, cell, cell_stride, N, density, n_cells);
 }
 
-void mlp_mfma_render(const void *weights, const void *feat, FeatureLayout layout, const void *dir_enc, const void *app, uint32_t n_app, uint32_t S,
-                     uint32_t n_seg, uint32_t act_c, const float *delta, const float *t, const uint32_t *seg_ray,
-                     const uint32_t *seg_slot, uint32_t k_max, float *Ck, float *Tk, float *Dk, hipStream_t st)
+int mlp_mfma_render(const char *who, const void *weights, const void *feat, FeatureLayout layout, const void *dir_enc, const void *app, uint32_t n_app, uint32_t S,
+                    uint32_t n_seg, uint32_t act_c, const float *delta, const float *t, const uint32_t *seg_ray,
+                    const uint32_t *seg_slot, uint32_t k_max, float *Ck, float *Tk, float *Dk, hipStream_t st)
 {
     using namespace dg_mlp_mfma;
+    DG_REQUIRE(layout != kSplit, DG_ERR_UNSUPPORTED, "%s: views take planes or rows, not split features", who);
     const uint32_t blocks_needed = (n_seg + kWavesPerBlock - 1) / kWavesPerBlock;
     const uint32_t grid = blocks_needed < 2048 ? blocks_needed : 2048;
     for_shape(n_app, layout, act_c, [&](auto na, auto in_rows, auto sig) {
-        if constexpr (decltype(in_rows)::value != kSplit)              // views take planes or rows
+        if constexpr (decltype(in_rows)::value != kSplit)              // refused above
             render_fwd_kernel<decltype(na)::value, decltype(in_rows)::value, decltype(sig)::value><<<grid, kBlock, 0, st>>>(
                 (const __half *)weights, (const __half *)feat, (const __half *)dir_enc, (const __half *)app, S, n_seg, delta, t, seg_ray,
                 seg_slot, k_max, Ck, Tk, Dk);
     });
+    return launch_status(who);
 }
 
 void mlp_mfma_bwd(const void *weights, const void *feat, FeatureLayout layout, uint32_t n_merged, const void *dir_enc, const void *app, uint32_t n_app,

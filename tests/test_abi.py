@@ -180,3 +180,14 @@ def test_one_call_refuses_short_direction_rows(name):
     call = B.FieldCall(grid=C.addressof(grid), mlp=C.addressof(mlp), n_seg=3, S=5, k_max=1, degree=2)
     assert getattr(B.lib(), name)(C.byref(call), None) != 0
     assert b"direction inputs" in B.lib().dg_last_error()
+
+
+def test_fused_rendering_refuses_split_features():
+    """No entry point passes them; the function behind dg_mlp_composite_fwd has no kernel for them and says so instead of returning
+    success (n_seg = 0 and NULL pointers: nothing could be launched)."""
+    render = getattr(B.lib(), "_ZN2dg15mlp_mfma_renderEPKcPKvS3_NS_13FeatureLayoutES3_S3_jjjjPKfS6_PKjS8_jPfS9_S9_P12ihipStream_t")
+    p, u = C.c_void_p, C.c_uint32
+    render.restype, render.argtypes = C.c_int, [C.c_char_p, p, p, C.c_int, p, p, u, u, u, u, p, p, p, p, u, p, p, p, p]
+    kSplit = 2
+    assert render(b"views", None, None, kSplit, None, None, 0, 64, 0, 1, None, None, None, None, 1, None, None, None, None) != 0
+    assert b"split" in B.lib().dg_last_error()
