@@ -143,15 +143,17 @@ GRIDS = {
     "c2": lambda: (di.config("c2_ngp"), None),
     "mixed_small": lambda: (None, dict(L=6, F=2, log2_T=10, n_min=4, growth=1.7, extent=[1.0, 2.0, 0.5])),
     "one_level_dense": lambda: (None, dict(L=1, F=2, log2_T=12, n_min=15, growth=1.0, extent=[1.0, 1.0, 1.0])),
-    # 37^3 vertices in one dense level: 7 bins of 8192 entries, odd row length, so x-pairs straddle bin boundaries
+    # 37^3 vertices in one dense level: 7 bins of 8192 entries, odd row length, so x-pairs straddle bin boundaries (summed directly below 1 M samples)
     "dense_odd": lambda: (None, dict(L=1, F=2, log2_T=16, n_min=36, growth=1.0, extent=[1.0, 1.0, 1.0])),
-    # two dense levels of 18^3 = 5832 entries: the first fits the LDS prefix, the second is binned and is a single bin
+    # the same in two levels of 63^3 vertices, 31 bins each: through the queues from 88 k samples on
+    "dense_odd_many": lambda: (None, dict(L=2, F=2, log2_T=18, n_min=62, growth=1.0, extent=[1.0, 1.0, 1.0])),
+    # two dense levels of 18^3 = 5832 entries: the first fits the LDS prefix, the second is a single bin, which is always summed directly
     "one_bin": lambda: (None, dict(L=2, F=2, log2_T=16, n_min=17, growth=1.0, extent=[1.0, 1.0, 1.0])),
     # T = 2^21: a dense level of 34 bins and hashed levels of 256 bins (more than one wavefront's worth)
     "wide": lambda: (None, dict(L=4, F=2, log2_T=21, n_min=64, growth=2.0, extent=[1.0, 1.0, 1.0])),
-    # T = 2^24, three hashed levels: 6144 (level, bin) pairs, too many for the counters to sit in LDS
     # 5, 34 and 263 bins of dense levels, which get many records each, and three times 1024 of hashed ones, which get few
     "sparse": lambda: (None, dict(L=6, F=2, log2_T=23, n_min=32, growth=2.0, extent=[1.0, 1.0, 1.0])),
+    # T = 2^24, three hashed levels: 6144 (level, bin) pairs, too many for the counters to sit in LDS
     "huge": lambda: (None, dict(L=3, F=2, log2_T=24, n_min=512, growth=2.0, extent=[1.0, 1.0, 1.0])),
 }
 
@@ -207,10 +209,21 @@ def test_encode_fwd_and_indices(key, N):
     assert np.all(err16 <= 2.0 ** -11 * np.abs(ref) + TOL_F32 * bound + 6e-8)
 
 
+def _through_queues(g, r, u, dfeat, ws):
+    """Whether a call with these inputs bins records: an infinite gradient at the first level then marks every level whose bins have
+    records.  Bins that are summed directly show it at the first level only."""
+    dd = dev(to_planes(dfeat))
+    dd[0, 0, 0] = float("inf")
+    marked = torch.zeros(r.n_entries, 2, device=DEV)
+    B.dg_hashgrid_encode_bwd(g, dev(u), dd, u.shape[0], marked, ws)
+    return not bool(torch.isfinite(marked[r.first[g.n_levels - 1]:]).all())
+
+
 @pytest.mark.parametrize("mode", ["atomic", "binned", "binned_batched"])
 @pytest.mark.parametrize("key,N,flavour", [("c1", 32768, "points"), ("c2", 10007, "points"), ("mixed_small", 3333, "points"),
                                            ("one_level_dense", 700, "points"), ("c2", 20011, "rays"),
                                            ("dense_odd", 150001, "points"), ("dense_odd", 30000, "rays"),
+                                           ("dense_odd_many", 90011, "points"), ("dense_odd_many", 90011, "rays"),
                                            ("wide", 20011, "points"), ("wide", 9000, "rays"), ("huge", 20011, "points"),
                                            ("c2", 1, "points"), ("c2", 7, "rays"), ("c2", 513, "rays"), ("c2", 2048 * 3 + 5, "rays"),
                                            ("one_bin", 60011, "rays"), ("one_bin", 3001, "points"),
@@ -230,6 +243,7 @@ def test_encode_bwd(key, N, flavour, mode):
         if mode == "binned_batched":                                   # room for a few tiles only: several batches
             need = B.dg_hashgrid_encode_bwd_workspace_bytes(g, 2048)
         ws = torch.zeros(need // 4 + 64, device=DEV)
+        assert key != "dense_odd_many" or _through_queues(g, r, u, dfeat, ws)
     B.dg_hashgrid_encode_bwd(g, dev(u), dev(to_planes(dfeat)), N, dtable, ws)
     B.dg_hashgrid_encode_bwd(g, dev(u), dev(to_planes(dfeat)), N, dtable, ws)   # "+=": twice gives twice
     ref = 2.0 * oracle.encode_bwd(r, u, dfeat.astype(np.float64))
@@ -244,23 +258,28 @@ def test_encode_bwd(key, N, flavour, mode):
 # level at most; these give it several, element by element against the oracle: records that wait for a full granule
 # from one step to the next and the two halves of the waiting slots (narrow sweep, c2), queue cursors that advance step
 # after step (sweep for many bins: wide, huge), bins whose records are split over several accumulating workgroups
-# (one_bin: 3.2 M records in one bin), and a capped workspace that makes two batches of two tiles per workgroup each.
+# (dense_odd_many with all samples in the layers that one bin of each level covers, in one batch and in two), a bin that is
+# summed directly (one_bin), and a capped workspace that makes two batches of two tiles per workgroup each.
 STEADY = 2 * 768 * 512
 
 
 @pytest.mark.parametrize("key,N,capped", [("c2", STEADY + 12345, False), ("c2", 2 * STEADY, True), ("wide", STEADY + 777, False),
-                                          ("huge", STEADY + 777, False), ("one_bin", STEADY + 13579, False)])
+                                          ("huge", STEADY + 777, False), ("one_bin", STEADY + 13579, False),
+                                          ("dense_odd_many", STEADY + 13579, False), ("dense_odd_many", STEADY + 13579, True)])
 def test_encode_bwd_several_tiles_per_workgroup(key, N, capped):
     say("encode bwd steady state %s N=%d capped=%s" % (key, N, capped))
     g, r, _ = _both_grids(key)
     L = g.n_levels
     u = _coords(N, "rays", seed=25)
+    if key == "dense_odd_many":
+        u[:, 2] *= np.float32(0.9 / 62)                  # two layers of 63 x 63 vertices: entries 0..7937 of the 8192 of a bin
     dfeat = (np.random.default_rng(26).standard_normal((N, 2 * L)) * 1e-3).astype(np.float32)
     dfeat[::11] = 0.0
     dtable = torch.zeros(r.n_entries, 2, device=DEV)
     need = B.dg_hashgrid_encode_bwd_workspace_bytes(g, N // 2 + 512 if capped else N)
     assert not capped or need < B.dg_hashgrid_encode_bwd_workspace_bytes(g, N)
     ws = torch.zeros(need // 4 + 64, device=DEV)
+    assert key != "dense_odd_many" or _through_queues(g, r, u, dfeat, ws)
     B.dg_hashgrid_encode_bwd(g, dev(u), dev(to_planes(dfeat)), N, dtable, ws)
     torch.cuda.synchronize()
     ref = oracle.encode_bwd(r, u, dfeat.astype(np.float64))
