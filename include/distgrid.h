@@ -160,9 +160,12 @@ int dg_hashgrid_encode_fwd(const dg_grid_desc *desc, const float *table, const f
  * summed exactly (in fixed point scaled to the batch's largest magnitude: a contribution below 2^-32 of that magnitude
  * adds nothing).  If any contribution of the batch is infinite or NaN the sums cannot be formed: every table region
  * that received contributions then gets NaN in its first entry, so the gradient is visibly non-finite as it would be
- * with fp32 atomics.  ws must be 256-byte aligned; a smaller workspace is accepted and makes the call run
- * in batches, DG_ERR_WORKSPACE if it cannot hold one tile of 512 samples (16 bytes per sample, level
- * and pair of corners, plus bookkeeping). */
+ * with fp32 atomics.  The coarse levels whose tables together have at most 8192 entries, and all levels of a grid with so few
+ * regions of 8192 entries (two or three per level, or up to 255 where N is small) that binning would take longer, are summed in fp64
+ * without bins: nothing is rounded to 18 bits there, and an infinite or NaN contribution shows in the entries it touches.
+ * All adds to dtable are atomic: other streams may add to it at the same time, each call with a workspace of its own.
+ * ws must be 256-byte aligned; a smaller workspace is accepted and makes the call run in batches, DG_ERR_WORKSPACE if it
+ * cannot hold one tile of 512 samples (16 bytes per sample, level and pair of corners, plus bookkeeping). */
 size_t dg_hashgrid_encode_bwd_workspace_bytes(const dg_grid_desc *desc, uint64_t N);
 int dg_hashgrid_encode_bwd(const dg_grid_desc *desc, const float *u, const float *dfeat,
                            uint64_t N, float *dtable, void *ws, size_t ws_bytes, void *stream);

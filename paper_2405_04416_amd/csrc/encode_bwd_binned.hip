@@ -60,8 +60,9 @@ struct Plan {
 };
 
 // ------------------------------------------------------------------ accumulate in LDS directly
-// Groups of `width` workgroups, each for a table region that fits LDS: the coarse prefix, and with `bins` every bin of the other
-// levels.  A group's workgroups sweep all samples at their region's levels and add what falls into it.
+// Groups of `width` workgroups, each for a table region that fits LDS: the coarse prefix, if there is one, and then every bin of the
+// other levels where direct_bins takes this way.  A group's workgroups sweep all samples at their region's levels and add what falls
+// into it.
 __global__ void __launch_bounds__(kCoarseBlock)
 coarse_kernel(dg_grid_desc g, Plan plan, uint32_t from_level, uint32_t width, const float *__restrict__ u, const float2 *__restrict__ dfeat,
               uint64_t N, float *__restrict__ dtable)
@@ -820,21 +821,20 @@ accumulate_kernel(dg_grid_desc g, Plan plan, const uint32_t *__restrict__ binbas
     }
 }
 
-// The same for bins of few records, which are bound not by the queue but by the chain of a bin -- its piece, the first records from
-// memory, the adds, the table's way in and out -- in a compute unit that one table fills.  One workgroup per compute unit stays
-// and takes piece after piece from a common counter: the next piece's first records are on their way while the table goes out,
-// which also clears it.
-// Where it serves: sparse_bins.  Eight sub-models, four of them with 4074 bins of 5.7 k records: 243 -> 219 us each.  (Bins that come in one piece
-// stored instead, with what the gradient held added: 183 us, but then an add of another stream to the same gradient is lost.)
-
 // kAccDepth records per thread from `at` on of the n of a piece, several in flight so that the queue streams at memory speed: the loads are unconditional
-// (index clamped into the piece) so that they issue back to back
+// (index clamped into the piece) so that they issue back to back.
 __device__ __forceinline__ void load_records(u32x4 (&rec)[kAccDepth], const u32x4 *__restrict__ records, uint32_t at, uint32_t n)
 {
 #pragma unroll
     for (int k = 0; k < kAccDepth; ++k) rec[k] = __builtin_nontemporal_load(records + min(at + k * kAccBlock, n - 1u));      // read once: streams faster past the caches (measured)
 }
 
+// The same for bins of few records, which are bound not by the queue but by the chain of a bin -- its piece, the first records from
+// memory, the adds, the table's way in and out -- in a compute unit that one table fills.  One workgroup per compute unit stays
+// and takes piece after piece from a common counter: the next piece's first records are on their way while the table goes out,
+// which also clears it.
+// Where it serves: sparse_bins.  Eight sub-models, four of them with 4074 bins of 5.7 k records: 243 -> 219 us each.  (Bins that come in one piece
+// stored instead, with what the gradient held added: 183 us, but then an add of another stream to the same gradient is lost.)
 __global__ void __launch_bounds__(kAccBlock)
 accumulate_sparse_kernel(dg_grid_desc g, Plan plan, const uint32_t *__restrict__ binbase, const uint4 *__restrict__ pieces,
                   const u32x4 *__restrict__ queue, float *__restrict__ dtable, uint32_t *__restrict__ taken)
