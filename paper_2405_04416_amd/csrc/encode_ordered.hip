@@ -79,8 +79,8 @@ encode_planes_kernel(dg_grid_desc g, const float2 *__restrict__ table, const flo
 // Levels [0, n_wide) -- the coarse levels, which ray order sums in fp64 -- are summed in fp64, the other levels, which in ray order
 // pass through records of 27-bit values, in fixed point.  Over the bricks levels [0, n_fold) are summed in fp64 as well (a vertex of
 // the coarsest level gets hundreds of them): into `wide`, which fold_wide_kernel adds to the table.  The others reach the table
-// with an fp32 add per brick.  Against 64-bit sums (33.5 M samples, 25200 bricks, 2-norm of levels 0 / 3 / 7): ray order 2.4e-7 / 2.0e-7 /
-// 3.3e-7, this 2.5e-8 / 2.5e-8 / 4.2e-8; level 0 in fixed point with fp32 adds 2.6e-7 (13.3 M samples), and nothing was left there of
+// with an fp32 add per brick.  Against 64-bit sums (33.5 M samples, 25200 bricks, 2-norm of levels 0 / 3 / 7): ray order 2.3e-7 / 1.9e-7 /
+// 2.5e-7, this 2.6e-8 / 2.5e-8 / 3.9e-8; level 0 in fixed point with fp32 adds 2.6e-7 (13.3 M samples), and nothing was left there of
 // gradients below 2^-38 of the largest.
 // Clearing and folding `wide` takes some 12 us.
 // A value v becomes round(v * 2^k): the add of 1.5 * 2^52 in fp64 leaves it in the low mantissa bits, in two's complement.  k is

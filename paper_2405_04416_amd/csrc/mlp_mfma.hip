@@ -10,8 +10,8 @@
 //
 // Operand layouts, images, transposes: mlp_mfma_common.h.
 //
-// What the kernels spend on a tile (13.3 M samples): forward 402 vector instructions of which 131 are transcendental and take two issue
-// slots; the vector units are busy 0.86 of the time, the matrix cores 0.31.  Colour backward: busy 0.6 and 0.4, with little overlap
+// What the kernels spend on a tile (13.3 M samples): forward 394 vector instructions of which 135 are transcendental and take two issue
+// slots; the vector units are busy 0.84 of the time, the matrix cores 0.30.  Colour backward: busy 0.60 and 0.33, with little overlap
 // at two wavefronts per SIMD, so it goes by the number of instructions: a compile-time choice of the activation (branches around each
 // of its uses cut the schedule into pieces), a (1 - a) as one multiply-add on halves, rows followed on the scalar unit instead of
 // divided out and images built from loads under way together took it from 1206 to 1050 us (0.65 M samples: 79 -> 65; 0.15 M: 35 -> 26),

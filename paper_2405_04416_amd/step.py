@@ -212,7 +212,8 @@ class TrainStep:
         1603 / 1550 at 1.0 M, 5070 / 4947 at 4.7 M; T = 2^24 2100 / 2095 at 0.69 M, 4136 / 4156 at 2.8 M.
         Occupancy-guided steps, whose samples share more, lose or gain little: T = 2^19 1009 / 1027 at 1.0 M.
         Refresh, pieces of 8.4 M, 4.2 M and 2.1 M candidates: T = 2^17 1383 / 1403, -, 1723 / 1591; T = 2^18 1478 / 1421, 1639 / 1422, 2061 / 1628;
-        T = 2^19 1693 / 1597, 2051 / 1627, 2546 / 1851; T = 2^20 1821 / 1948, 2231 / 2074, 2756 / 2393."""
+        T = 2^19 1693 / 1597, 2051 / 1627, 2546 / 1851; T = 2^20 1821 / 1948, 2231 / 2074, 2756 / 2393.
+        Tables that are not named (T = 2^23, and below 2^17) were not measured and keep the one walk."""
         T = m.grid.log2_T
         if use == "refresh":
             return N < {17: 3 << 20, 18: 10 << 20, 19: 10 << 20, 20: 6 << 20}.get(T, 0)
