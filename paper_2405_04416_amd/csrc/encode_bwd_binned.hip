@@ -17,47 +17,11 @@
 //     finished bin into dtable with coalesced atomics.
 //     Many bins of few records are taken by workgroups that stay (sparse_bins).
 // Where there are few bins altogether, all of them are accumulated directly, without queues (direct_bins).
-#include "encode_common.h"
+#include "encode_binned_common.h"
 #include <algorithm>
 #include <mutex>
 
 namespace dg_encode_binned {
-
-using namespace dg_encode;
-
-constexpr int kChunkLog2 = 13;
-constexpr uint32_t kChunk = 1u << kChunkLog2;      // entries per bin
-constexpr int kMaxBins = 2048;                     // per level: 2^24 entries / 8192
-constexpr int kTile = 512;                         // samples per tile == threads per binning workgroup
-constexpr int kKeeper = 64;                        // narrow fill sweep: one more wavefront, which keeps the books of the 64 bins
-constexpr int kPairs = kTile * 4;                  // records staged per (tile, level): one per pair of corners along x
-constexpr uint32_t kMaxKeys = DG_MAX_LEVELS * kMaxBins;   // (level, bin) pairs at most: the count sweep keeps one counter each in LDS (128 KB)
-constexpr int kBinGrid = 768;                      // persistent binning workgroups (three per compute unit)
-constexpr int kAccBlock = 1024, kAccGrid = 256;    // threads of an accumulate workgroup (one per compute unit: its table fills LDS), compute units
-constexpr int kAccDepth = 4;                       // records in flight per accumulate thread
-// An accumulate workgroup sums at least 2^piece_log2 records of a bin (or all it has) and fewer than twice as many: a bin is
-// cut into floor(records / 2^piece_log2) equal pieces, so a bin with less than two pieces' worth stays whole (a second
-// workgroup would clear and write out a table of its own for little).  2^17 records where there are plenty; where the bins
-// are few and the records too, pieces shrink until some 512 workgroups have one (c1's grid, 33 k samples in three bins of 131 k
-// records: 46 -> 17 us).
-constexpr int kPieceLog2Min = 13, kPieceLog2Max = 17;
-constexpr int kAccMaxLog2 = kPieceLog2Max + 1;
-__host__ __device__ __forceinline__ uint32_t acc_pieces(uint32_t total, uint32_t piece_log2) { return total == 0u ? 0u : (total >> piece_log2 ? total >> piece_log2 : 1u); }
-constexpr int kCoarseBlock = 1024;                 // coarse prefix: threads per workgroup, persistent workgroups (one per compute unit)
-constexpr int kCoarseGrid = 256;
-
-// How a sweep's workgroups share the work: `groups` groups of `width` workgroups; workgroup w of group k takes the tiles w,
-// w + width, ... at the levels first_level + k, + groups, ...  One group where there are tiles enough for every workgroup
-// (neighbouring appends then meet in L2, level after level); with few tiles several groups go through fewer levels each.
-struct Sweep { uint32_t width, groups; };
-
-struct Plan {
-    uint32_t first_level;                  // levels below are accumulated directly in LDS
-    uint32_t n_keys;                       // (level, bin) pairs of the binned levels
-    uint32_t key_base[DG_MAX_LEVELS + 1];  // first key of each level
-    uint32_t n_bins[DG_MAX_LEVELS];
-    uint32_t max_bins;
-};
 
 // ------------------------------------------------------------------ accumulate in LDS directly
 // Groups of `width` workgroups, each for a table region that fits LDS: the coarse prefix, if there is one, and then every bin of the
@@ -236,34 +200,6 @@ count_lds_kernel(dg_grid_desc g, Plan plan, Sweep sw, const float *__restrict__ 
         for (uint32_t i = plan.key_base[l] + tid; i < plan.key_base[l + 1]; i += blockDim.x) row_global[i] = row[i];
 }
 
-template <int CTRL, int ROW_MASK>
-__device__ __forceinline__ void scan_step(uint32_t &v)
-{
-    v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, CTRL, ROW_MASK, 0xF, true);
-}
-
-// inclusive prefix sum over the wavefront (DPP moves: rows of 16 lanes, then across rows)
-__device__ __forceinline__ uint32_t wave_inclusive_scan(uint32_t v)
-{
-    scan_step<0x111, 0xF>(v);
-    scan_step<0x112, 0xF>(v);
-    scan_step<0x114, 0xF>(v);
-    scan_step<0x118, 0xF>(v);
-    scan_step<0x142, 0xA>(v);
-    scan_step<0x143, 0xC>(v);
-    return v;
-}
-
-// inclusive running maximum over the wavefront, same moves (a lane that receives nothing takes 0)
-__device__ __forceinline__ uint32_t wave_inclusive_max(uint32_t v)
-{
-#define DG_MAX_STEP(CTRL, ROW_MASK) v = max(v, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, CTRL, ROW_MASK, 0xF, true))
-    DG_MAX_STEP(0x111, 0xF); DG_MAX_STEP(0x112, 0xF); DG_MAX_STEP(0x114, 0xF); DG_MAX_STEP(0x118, 0xF);
-    DG_MAX_STEP(0x142, 0xA); DG_MAX_STEP(0x143, 0xC);
-#undef DG_MAX_STEP
-    return v;
-}
-
 // Fill sweep.  Per step (one tile at one level): every emitting lane takes a rank in its records' bins (LDS
 // counters), the counters are scanned into staging offsets, the records are staged in LDS sorted by bin and then
 // copied to the queues, so that every bin receives contiguous runs.  A workgroup goes level after level, and
@@ -271,19 +207,6 @@ __device__ __forceinline__ uint32_t wave_inclusive_max(uint32_t v)
 // cache lines at their ends are completed while they still sit in L2.
 // Loads are requested one step ahead: memory operations of a wavefront retire in order, so a load issued right
 // after queue stores could only be awaited together with their acknowledgements.
-
-struct StepAhead {
-    float u[3];
-    float2 g;
-};
-
-__device__ __forceinline__ void load_ahead(StepAhead &a, const float *__restrict__ u, const float2 *__restrict__ dfeat, uint64_t N,
-                                           uint64_t n0, uint64_t nb, uint64_t tile, uint32_t l, uint32_t tid)
-{
-    const uint64_t rel = tile * kTile + tid, n = n0 + (rel < nb ? rel : nb - 1);
-    a.u[0] = u[3 * n]; a.u[1] = u[3 * n + 1]; a.u[2] = u[3 * n + 2];
-    a.g = dfeat[(size_t)l * N + n];
-}
 
 // values of the 8 corners of one sample at one level, runs merged where the emission says so; `largest` follows the
 // largest magnitude (as the bit pattern of |v|, which orders like the value) of anything a lane emits
@@ -303,19 +226,6 @@ __device__ __forceinline__ void corner_values(const Emission &em, float2 gfe, fl
     // fmaxf passes over NaN: a NaN gradient is reported as such (its bit pattern orders above infinity's), by whichever
     // lane holds it, whether or not that lane emits
     if (gfe.x != gfe.x || gfe.y != gfe.y) largest = max(largest, 0x7fc00000u);
-}
-
-// largest over the workgroup -> *dst (one atomic per workgroup); `word` is an LDS word nobody else uses any more
-__device__ __forceinline__ void publish_largest(uint32_t largest, uint32_t *word, uint32_t *__restrict__ dst)
-{
-    __syncthreads();
-    if (threadIdx.x == 0) *word = 0u;
-    __syncthreads();
-#pragma unroll
-    for (int off = dg::kWave / 2; off > 0; off >>= 1) largest = max(largest, (uint32_t)__shfl_xor((int)largest, off, dg::kWave));
-    if (threadIdx.x % dg::kWave == 0 && largest) atomicMax(word, largest);
-    __syncthreads();
-    if (threadIdx.x == 0 && *word) atomicMax(dst, *word);
 }
 
 // the record of pair p; a pair that straddles a bin boundary (or, against every expectation, differs in some other way
@@ -346,8 +256,6 @@ __device__ __forceinline__ uint4 make_record(const Emission &em, int p, const fl
 // instruction covers whole cache lines, while the book-keeping wavefront puts together what waits from here on.  Two
 // barriers per step.  At the end of a level the book-keeper writes the waiting records out and pads this workgroup's
 // slice of each bin to kSliceRound records with zero records, which add nothing.
-__device__ __forceinline__ uint32_t lane_value(uint32_t v, uint32_t lane) { return (uint32_t)__builtin_amdgcn_readlane((int)v, (int)lane); }
-
 constexpr uint32_t kCarry = kGran - 1;
 // append granules a step can hold: its records plus what waits in the 64 bins
 constexpr uint32_t kOwner = ((kPairs + 64 * kCarry) / kGran + 1 + 3) / 4 * 4;
@@ -716,7 +624,7 @@ scan_rows_kernel(uint32_t *__restrict__ rows, uint32_t n_rows, uint32_t n_keys, 
 // first record, end) -- a bin is cut into acc_pieces of its record count, in equal shares, so that work is balanced whatever
 // the bins hold, and a workgroup finds its share with one load.  (One workgroup; n_keys is at most a few tens of thousands.)
 __global__ void __launch_bounds__(1024)
-scan_totals_kernel(const uint32_t *__restrict__ totals, uint32_t n_keys, uint32_t piece_log2, uint32_t *__restrict__ binbase, uint4 *__restrict__ pieces)
+scan_totals_kernel(const uint32_t *__restrict__ totals, uint32_t n_keys, uint32_t piece_log2, uint32_t round, uint32_t *__restrict__ binbase, uint4 *__restrict__ pieces)
 {
     __shared__ uint32_t wave_sum[16], wave_pieces[16];
     const uint32_t per = (n_keys + 1023) / 1024, lo = min(threadIdx.x * per, n_keys), hi = min(lo + per, n_keys);
@@ -729,9 +637,9 @@ scan_totals_kernel(const uint32_t *__restrict__ totals, uint32_t n_keys, uint32_
     uint32_t run = incl - s, run_p = incl_p - sp;
     for (uint32_t w = 0; w < wave; ++w) { run += wave_sum[w]; run_p += wave_pieces[w]; }
     for (uint32_t i = lo; i < hi; ++i) {
-        const uint32_t total = totals[i], n = acc_pieces(total, piece_log2), share = n ? (total + n - 1u) / n : 0u;
+        const uint32_t total = totals[i], n = acc_pieces(total, piece_log2), share = n ? ((total + n - 1u) / n + round - 1u) / round * round : 0u;
         binbase[i] = run;
-        for (uint32_t q = 0; q < n; ++q) pieces[1 + run_p++] = make_uint4(i, run + q * share, run + min((q + 1u) * share, total), 0u);
+        for (uint32_t q = 0; q < n; ++q) pieces[1 + run_p++] = make_uint4(i, run + (uint32_t)min((uint64_t)q * share, (uint64_t)total), run + (uint32_t)min((q + 1ull) * share, (uint64_t)total), 0u);
         run += total;
     }
     if (threadIdx.x == 1023) {
@@ -755,17 +663,101 @@ __device__ __forceinline__ void add_fixed(unsigned long long *slot, float v, dou
                            __HIP_MEMORY_SCOPE_WORKGROUP);
 }
 
+// The two kinds of records in the queues.  A thread takes kDepth records at a time, kAccBlock apart, 64 bytes.
+struct PairRecords {
+    static constexpr int kDepth = 4;
+    typedef u32x4 Record;
+    static __device__ __forceinline__ uint32_t offset(uint32_t i) { return i * 16u; }                  // of record i, in bytes
+    static __device__ __forceinline__ uint32_t slot(uint32_t entry, uint32_t feature) { return feature * kChunk + entry; }      // of the sum
+    // records that fill a slice up are zero: they would all add to one sum in turn
+    static __device__ __forceinline__ bool empty(const Record &rec) { return (rec.x >> 17 | rec.y | rec.z | rec.w) == 0u; }
+    static __device__ __forceinline__ void add(unsigned long long *tab, const Record &rec, double scale)
+    {
+        uint32_t ea, eb;
+        float v0, v1, v2, v3;
+        unpack_record(rec, ea, eb, v0, v1, v2, v3);
+        add_fixed(&tab[ea], v0, scale);
+        add_fixed(&tab[kChunk + ea], v1, scale);
+        add_fixed(&tab[eb], v2, scale);
+        add_fixed(&tab[kChunk + eb], v3, scale);
+    }
+};
+// slot of the entry's sums (slot_of, 14 bits), pair_code (4 bits), gradient times y and z weights (27-bit floats), x fraction in units of 2^-23
+struct CompactRecords {
+    static constexpr int kDepth = kLineRecords;
+    typedef uint32_t Record __attribute__((ext_vector_type(3), aligned(4)));
+    static __device__ __forceinline__ uint32_t offset(uint32_t i) { return i / kLineRecords * 64u + i % kLineRecords * 12u; }
+    static __device__ __forceinline__ uint32_t slot(uint32_t entry, uint32_t feature)
+    {
+        return (entry & (kChunk / 2 - 1u)) | (entry & kChunk / 2) << 1 | feature * (kChunk / 2);
+    }
+    static __device__ __forceinline__ bool empty(const Record &rec) { return ((rec.y | rec.z) & 0x7ffffffu) == 0u; }
+    static __device__ __forceinline__ void add(unsigned long long *tab, const Record &rec, double scale)
+    {
+        const uint32_t a = (rec.x & 0x3fffu) << 3, b = a ^ ((1u << (rec.x >> 14 & 15u)) - 1u) << 3;
+        const uint32_t fx = __builtin_amdgcn_alignbit(__builtin_amdgcn_alignbit(rec.z >> 27, rec.y, 27u), rec.x, 18u);
+        const double at1 = (double)fx, at0 = 8388608.0 - at1, unit = scale * 0x1p-23;
+        const double gx = (double)__uint_as_float(rec.y << 5) * unit, gy = (double)__uint_as_float(rec.z << 5) * unit;
+        char *const sums = reinterpret_cast<char *>(tab);
+        add_scaled(sums + a, gx, at0);
+        add_scaled(sums + a + kChunk / 2 * 8, gy, at0);
+        add_scaled(sums + b, gx, at1);
+        add_scaled(sums + b + kChunk / 2 * 8, gy, at1);
+    }
+    // adds round(v * w)
+    static __device__ __forceinline__ void add_scaled(char *sum, double v, double w)
+    {
+        __hip_atomic_fetch_add(reinterpret_cast<unsigned long long *>(sum), (unsigned long long)__double_as_longlong(__builtin_fma(v, w, 6755399441055744.0 /* 1.5 * 2^52 */)),
+                               __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+    }
+};
+
+// A thread's records of a piece: several in flight so that the queue streams at memory speed.  The loads are unconditional (clamped to the
+// piece's last record) so that they issue back to back, and non-temporal: what is read once streams faster past the caches (measured).
+template <class R>
+struct PieceReader {
+    static constexpr uint32_t kStride = R::kDepth * kAccBlock;           // records per turn of the workgroup
+    static constexpr uint32_t kStrideBytes = 64u * kAccBlock;
+    uint32_t offset[R::kDepth];
+    __device__ __forceinline__ PieceReader()
+    {
+#pragma unroll
+        for (int j = 0; j < R::kDepth; ++j) offset[j] = R::offset(j * kAccBlock + threadIdx.x);
+    }
+    // the records of turn `turn` of a piece whose last record lies at `last`
+    __device__ __forceinline__ void load(typename R::Record (&rec)[R::kDepth], const char *piece, uint32_t turn, uint32_t last) const
+    {
+#pragma unroll
+        for (int j = 0; j < R::kDepth; ++j)
+            rec[j] = __builtin_nontemporal_load(reinterpret_cast<const typename R::Record *>(piece + min(turn * kStrideBytes + offset[j], last)));
+    }
+    // adds them, n records in the piece
+    __device__ __forceinline__ void add(unsigned long long *tab, const typename R::Record (&rec)[R::kDepth], uint32_t turn, uint32_t n, double scale) const
+    {
+#pragma unroll
+        for (int j = 0; j < R::kDepth; ++j)
+            if (turn * kStride + j * kAccBlock + threadIdx.x < n && !R::empty(rec[j])) R::add(tab, rec[j], scale);
+    }
+};
+static_assert(PairRecords::kDepth * 16 == 64 && CompactRecords::kDepth == kLineRecords, "a thread takes 64 bytes of the queue per turn");
+
+template <class R>
+__device__ __forceinline__ const char *piece_records(const char *queue, uint32_t first)
+{
+    return queue + (R::kDepth == kLineRecords ? (size_t)(first / kLineRecords) * 64 : (size_t)first * 16);
+}
+
+template <class R>
 __global__ void __launch_bounds__(kAccBlock)
 accumulate_kernel(dg_grid_desc g, Plan plan, const uint32_t *__restrict__ binbase, const uint4 *__restrict__ pieces,
-                  const u32x4 *__restrict__ queue, float *__restrict__ dtable)
+                  const char *__restrict__ queue, float *__restrict__ dtable)
 {
     // [2][kChunk] sums, one plane per feature: an add instruction then spreads over all LDS banks instead of every other pair
     extern __shared__ unsigned long long acc_tab[];
     unsigned long long *tab = acc_tab;
     const uint4 piece = pieces[1 + blockIdx.x];                           // the list has room for every workgroup of the grid
     if (blockIdx.x >= pieces[0].x) return;
-    const uint32_t key = piece.x;
-    const size_t begin = piece.y, end = piece.z;                          // fewer than 2^kAccMaxLog2 records
+    const uint32_t key = piece.x, n = piece.z - piece.y;                  // fewer than 2^kAccMaxLog2 records
     // 2^k with k = 50 - kAccMaxLog2 - 1 - (exponent of the largest magnitude): 2^kAccMaxLog2 values of that size sum to < 2^50
     const uint32_t top = binbase[plan.n_keys + 1] >> 23;                 // biased exponent (0 for zero / denormal: no smaller k needed)
     const int k = 50 - kAccMaxLog2 - 1 - ((int)(top ? top : 1u) - 127);
@@ -775,7 +767,7 @@ accumulate_kernel(dg_grid_desc g, Plan plan, const uint32_t *__restrict__ binbas
         // an infinite or NaN contribution somewhere in the batch: the scale above means nothing and integer sums cannot
         // carry it.  The gradient is marked instead: every bin that has records gets NaN in its first entry, as sums
         // with fp32 atomics would end up non-finite too.
-        if (threadIdx.x == 0 && begin < end) {
+        if (threadIdx.x == 0 && n) {
             uint32_t lv = plan.first_level;
             while (lv + 1 < g.n_levels && key >= plan.key_base[lv + 1]) ++lv;
             dtable[2 * ((size_t)g.offset[lv] + (size_t)(key - plan.key_base[lv]) * kChunk)] = __uint_as_float(0x7fc00000u);
@@ -784,28 +776,18 @@ accumulate_kernel(dg_grid_desc g, Plan plan, const uint32_t *__restrict__ binbas
     }
     for (uint32_t i = threadIdx.x; i < 2 * kChunk; i += kAccBlock) tab[i] = 0ull;
     __syncthreads();
-    // several records in flight per thread so that the queue streams at memory speed: the loads are unconditional
-    // (index clamped into the range) so that they issue back to back; a clamped duplicate adds 0
-    if (begin < end) {
-        const size_t last = end - 1;
-        for (size_t i0 = begin + threadIdx.x; i0 < end; i0 += kAccDepth * kAccBlock) {
-            u32x4 rec[kAccDepth];
+    if (n) {
+        const PieceReader<R> reader;
+        const char *records = piece_records<R>(queue, piece.y);
+        const uint32_t last = R::offset(n - 1u);
+        typename R::Record rec[R::kDepth];
+        reader.load(rec, records, 0u, last);
+        for (uint32_t turn = 0; turn * PieceReader<R>::kStride < n; ++turn) {
+            typename R::Record now[R::kDepth];
 #pragma unroll
-            for (int k2 = 0; k2 < kAccDepth; ++k2) {
-                const size_t want = i0 + (size_t)k2 * kAccBlock, i = want < last ? want : last;
-                rec[k2] = __builtin_nontemporal_load(queue + i);      // read once: streams faster past the caches (measured)
-            }
-#pragma unroll
-            for (int k2 = 0; k2 < kAccDepth; ++k2) {
-                if (!(i0 + (size_t)k2 * kAccBlock < end)) rec[k2] = u32x4{0u, 0u, 0u, 0u};      // a clamped duplicate: the zero record
-                uint32_t ea, eb;
-                float v0, v1, v2, v3;
-                unpack_record(rec[k2], ea, eb, v0, v1, v2, v3);
-                add_fixed(&tab[ea], v0, scale);
-                add_fixed(&tab[kChunk + ea], v1, scale);
-                add_fixed(&tab[eb], v2, scale);
-                add_fixed(&tab[kChunk + eb], v3, scale);
-            }
+            for (int j = 0; j < R::kDepth; ++j) now[j] = rec[j];
+            reader.load(rec, records, turn + 1u, last);
+            reader.add(tab, now, turn, n, scale);
         }
     }
     __syncthreads();
@@ -816,17 +798,9 @@ accumulate_kernel(dg_grid_desc g, Plan plan, const uint32_t *__restrict__ binbas
     const uint32_t first = bin * kChunk, n_valid = min(kChunk, level_len - first);
     float *dst = dtable + 2 * ((size_t)g.offset[l] + first);
     for (uint32_t i = threadIdx.x; i < 2 * n_valid; i += kAccBlock) {
-        const float sum = (float)(from_low_bits(tab[(i & 1u) * kChunk + (i >> 1)]) * inv_scale);
+        const float sum = (float)(from_low_bits(tab[R::slot(i >> 1, i & 1u)]) * inv_scale);
         if (sum != 0.0f) unsafeAtomicAdd(dst + i, sum);
     }
-}
-
-// kAccDepth records per thread from `at` on of the n of a piece, several in flight so that the queue streams at memory speed: the loads are unconditional
-// (index clamped into the piece) so that they issue back to back.
-__device__ __forceinline__ void load_records(u32x4 (&rec)[kAccDepth], const u32x4 *__restrict__ records, uint32_t at, uint32_t n)
-{
-#pragma unroll
-    for (int k = 0; k < kAccDepth; ++k) rec[k] = __builtin_nontemporal_load(records + min(at + k * kAccBlock, n - 1u));      // read once: streams faster past the caches (measured)
 }
 
 // The same for bins of few records, which are bound not by the queue but by the chain of a bin -- its piece, the first records from
@@ -835,9 +809,10 @@ __device__ __forceinline__ void load_records(u32x4 (&rec)[kAccDepth], const u32x
 // which also clears it.
 // Where it serves: sparse_bins.  Eight sub-models, four of them with 4074 bins of 5.7 k records: 243 -> 219 us each.  (Bins that come in one piece
 // stored instead, with what the gradient held added: 183 us, but then an add of another stream to the same gradient is lost.)
+template <class R>
 __global__ void __launch_bounds__(kAccBlock)
 accumulate_sparse_kernel(dg_grid_desc g, Plan plan, const uint32_t *__restrict__ binbase, const uint4 *__restrict__ pieces,
-                  const u32x4 *__restrict__ queue, float *__restrict__ dtable, uint32_t *__restrict__ taken)
+                  const char *__restrict__ queue, float *__restrict__ dtable, uint32_t *__restrict__ taken)
 {
     // [2][kChunk] sums, one plane per feature: an add instruction then spreads over all LDS banks instead of every other pair
     extern __shared__ __attribute__((aligned(16))) unsigned long long acc_tab[];
@@ -864,36 +839,28 @@ accumulate_sparse_kernel(dg_grid_desc g, Plan plan, const uint32_t *__restrict__
         return;
     }
     if (index >= n_pieces) return;
+    const PieceReader<R> reader;
     uint4 piece = pieces[1 + index];                                     // key, first record, end: fewer than 2^kAccMaxLog2 records, at least one
-    u32x4 rec[kAccDepth];
-    load_records(rec, queue + piece.y, threadIdx.x, piece.z - piece.y);
+    typename R::Record rec[R::kDepth];
+    reader.load(rec, piece_records<R>(queue, piece.y), 0u, R::offset(piece.z - piece.y - 1u));
     uint4 *const clear = reinterpret_cast<uint4 *>(tab);
     for (uint32_t i = threadIdx.x; i < kChunk; i += kAccBlock) clear[i] = make_uint4(0u, 0u, 0u, 0u);
     __syncthreads();
     for (;;) {
-        const uint32_t key = piece.x, n = piece.z - piece.y;
-        const u32x4 *const records = queue + piece.y;
+        const uint32_t key = piece.x, n = piece.z - piece.y, last = R::offset(n - 1u);
+        const char *const records = piece_records<R>(queue, piece.y);
         if (threadIdx.x == 0) next_piece = gridDim.x + atomicAdd(taken, 1u);
         uint32_t l = plan.first_level;
         while (l + 1 < g.n_levels && key >= plan.key_base[l + 1]) ++l;
         const uint32_t first = (key - plan.key_base[l]) * kChunk, n_values = 2 * min(kChunk, g.offset[l + 1] - g.offset[l] - first);
         float *dst = dtable + 2 * ((size_t)g.offset[l] + first);
-        for (uint32_t done = 0;; done += kAccDepth * kAccBlock) {
-            u32x4 now[kAccDepth];
+        for (uint32_t turn = 0;; ++turn) {
+            typename R::Record now[R::kDepth];
 #pragma unroll
-            for (int j = 0; j < kAccDepth; ++j) now[j] = done + j * kAccBlock + threadIdx.x < n ? rec[j] : u32x4{0u, 0u, 0u, 0u};        // a clamped duplicate: the zero record
-            const bool more = done + kAccDepth * kAccBlock < n;
-            if (more) load_records(rec, records, done + kAccDepth * kAccBlock + threadIdx.x, n);
-#pragma unroll
-            for (int j = 0; j < kAccDepth; ++j) {
-                uint32_t ea, eb;
-                float v0, v1, v2, v3;
-                unpack_record(now[j], ea, eb, v0, v1, v2, v3);
-                add_fixed(&tab[ea], v0, scale);
-                add_fixed(&tab[kChunk + ea], v1, scale);
-                add_fixed(&tab[eb], v2, scale);
-                add_fixed(&tab[kChunk + eb], v3, scale);
-            }
+            for (int j = 0; j < R::kDepth; ++j) now[j] = rec[j];
+            const bool more = (turn + 1u) * PieceReader<R>::kStride < n;
+            if (more) reader.load(rec, records, turn + 1u, last);
+            reader.add(tab, now, turn, n, scale);
             if (!more) break;
         }
         __syncthreads();
@@ -901,15 +868,15 @@ accumulate_sparse_kernel(dg_grid_desc g, Plan plan, const uint32_t *__restrict__
         const bool another = index < n_pieces;
         if (another) {
             piece = pieces[1 + index];
-            load_records(rec, queue + piece.y, threadIdx.x, piece.z - piece.y);
+            reader.load(rec, piece_records<R>(queue, piece.y), 0u, R::offset(piece.z - piece.y - 1u));
         }
-        unsigned long long *from = tab + (threadIdx.x & 1u) * kChunk;
 #pragma unroll
         for (int j = 0; j < kPerThread; ++j) {
             const uint32_t i = j * kAccBlock + threadIdx.x;
             if (i >= n_values) continue;
-            const unsigned long long bits = from[i >> 1];
-            from[i >> 1] = 0ull;
+            unsigned long long *from = tab + R::slot(i >> 1, i & 1u);
+            const unsigned long long bits = *from;
+            *from = 0ull;
             const float sum = (float)(from_low_bits(bits) * inv_scale);
             if (sum != 0.0f) unsafeAtomicAdd(dst + i, sum);
         }
@@ -931,7 +898,8 @@ Plan make_plan(const dg_grid_desc *d, uint32_t from_level)
         key += p.n_bins[l];
         if (p.n_bins[l] > p.max_bins) p.max_bins = p.n_bins[l];
     }
-    p.max_bins = (p.max_bins + 63) / 64 * 64;
+    if (from_level > 0u) set_compact(p);
+    else p.max_bins = (p.max_bins + 63) / 64 * 64;
     p.key_base[d->n_levels] = key;
     p.n_keys = key;
     return p;
@@ -946,14 +914,22 @@ struct Layout {
 };
 
 // both sweeps pad every workgroup's slice of every bin to whole granules: 8 records with few bins, 4 with many
-uint32_t sweep_grid(const Plan &p) { return p.max_bins <= 64 ? (uint32_t)kBinGrid : (uint32_t)kRingGrid; }
-uint32_t slice_round(const Plan &p) { return p.max_bins <= 64 ? kSliceRound : (uint32_t)kRingSlots; }
+uint32_t sweep_grid(const Plan &p)
+{
+    if (p.compact) return (uint32_t)kCompactGrid;
+    return p.max_bins <= 64 ? (uint32_t)kBinGrid : (uint32_t)kRingGrid;
+}
+uint32_t slice_round(const Plan &p)
+{
+    if (p.compact) return p.compact;
+    return p.max_bins <= 64 ? kSliceRound : (uint32_t)kRingSlots;
+}
 // width and groups of the sweeps over n_tiles tiles at n_levels levels: the split with the fewest (tile, level) steps per
 // workgroup, one group unless another saves a thirtieth.  (185 k samples at 13 levels, 361 tiles for 768 workgroups: 13 steps
 // in one group, 8 in 13 groups of 59; 830 k samples: 39 and 28.)
 Sweep choose_sweep(const Plan &p, uint32_t n_levels, uint64_t n_tiles)
 {
-    const uint32_t grid = sweep_grid(p), levels = n_levels - p.first_level, per_step = p.max_bins <= 64 ? 1u : 2u;
+    const uint32_t grid = sweep_grid(p), levels = n_levels - p.first_level, per_step = p.max_bins <= 64 || p.compact ? 1u : 2u;
     Sweep best = {grid, 1};
     double least = 0.0;
     for (uint32_t k = 1; k <= levels; ++k) {
@@ -962,6 +938,11 @@ Sweep choose_sweep(const Plan &p, uint32_t n_levels, uint64_t n_tiles)
         if (k == 1 || steps < least * (29.0 / 30.0)) { best = {width, k}; least = steps; }
     }
     return best;
+}
+uint64_t tiles_of(const Plan &p, uint64_t n)
+{
+    const uint64_t tile = p.compact ? kCompactTile : kTile;
+    return (n + tile - 1) / tile;
 }
 uint64_t slice_padding(const Plan &p) { return (uint64_t)sweep_grid(p) * p.n_keys * (slice_round(p) - 1u); }
 
@@ -986,27 +967,26 @@ bool direct_bins(const Plan &p, uint32_t n_levels, uint64_t N)
     return p.n_keys < (uint32_t)kCoarseGrid && (p.n_keys <= free || N * (p.n_keys - free) < 5000000ull);
 }
 
-// Many bins with fewer records than entries: accumulate_sparse_kernel.  Its time against accumulate_kernel's in us, with `bins` bins and
-// `records` records per bin at most: 4074 bins, 5700 records 219 / 243; 4566, 4600 241 / 278; 3731, 5600 207 / 213; 2238, 2600 129 / 145; 2047, 2000
-// 128 / 140; 15 923, 1300 955 / 1014.  Few bins: 1123, 7200 97 / 73; 611, 6400 57 / 54; 611, 12 300 65 / 63.  Many records: 15 900, 10 000 1065 / 1146;
-// 4560, 13 200 334 / 345; 3730, 13 900 281 / 263.
+// Many bins: accumulate_sparse_kernel.  Its time against accumulate_kernel's in us, with `bins` bins and `records` records per bin at most.  Compact records:
+// 12 288 bins, 65 500 records 2212 / 2275; 12 288, 38 700 1426 / 1466; four calls of 3072, 25 400 1068 / 1122; few bins: 256 bins, 832 000 records 519 / 522; 390,
+// 203 000 281 / 239; 512, 97 000 171 / 166.  Records of 16 bytes: 4074, 5700 211 / 243; 15 923, 1300 955 / 1014; 611, 4800 49 / 47.
 bool sparse_bins(const Plan &p, uint32_t n_levels, uint64_t nb)
 {
-    return p.n_keys >= 2048u && nb * 4ull * (n_levels - p.first_level) < (uint64_t)p.n_keys * kChunk;
+    return p.n_keys >= 2048u;
 }
 
 // workspace layout for a batch of `batch` samples
 Layout make_layout(const dg_grid_desc *d, const Plan &p, uint64_t batch)
 {
     Layout L{};
-    const uint64_t records = (batch * 4ull * (d->n_levels - p.first_level) + slice_padding(p) + 15ull) / 16ull * 16ull;
+    const uint64_t records = (batch * 4ull * (d->n_levels - p.first_level) + slice_padding(p) + 79ull) / 80ull * 80ull;
     size_t off = 0;
     L.rows = off; off = align256(off + (size_t)sweep_grid(p) * p.n_keys * 4);
     L.totals = off; off = align256(off + (size_t)p.n_keys * 4);
     L.binbase = off; off = align256(off + (size_t)(p.n_keys + 3) * 4);      // + the largest record magnitude, the pieces taken
     // a smaller batch may have smaller pieces: never more than 1024 beyond one per bin while they are not at their largest
     L.pieces = off; off = align256(off + (size_t)(1 + std::max(acc_grid(p, records), 1024u + p.n_keys)) * 16);
-    L.queue = off; off = align256(off + records * 16);
+    L.queue = off; off = align256(off + (p.compact ? records / kLineRecords * 64 : records * 16));
     L.total = off;
     L.batch = batch;
     L.records = records;
@@ -1020,7 +1000,8 @@ uint64_t max_batch(const dg_grid_desc *d, const Plan &p)
 {
     const uint64_t per_sample = 4ull * (d->n_levels - p.first_level);
     if (per_sample == 0) return ~0ull;
-    return ((0xffffffffull - slice_padding(p) - 16ull) / per_sample) / kTile * kTile;           // record offsets stay below 2^32
+    const uint64_t batch = ((0xffffffffull - slice_padding(p) - 80ull) / per_sample) / kTile * kTile;           // record offsets stay below 2^32
+    return p.compact ? std::min(batch, kCompactBatch) : batch;
 }
 
 }  // namespace dg_encode_binned
@@ -1055,7 +1036,8 @@ struct Prepared {
     Plan p;
     Layout L;
     uint32_t *rows, *totals, *binbase;
-    uint4 *pieces, *queue;
+    uint4 *pieces;
+    char *queue;
     bool narrow;
 };
 
@@ -1067,12 +1049,15 @@ int prepare(const char *who, const dg_grid_desc *d, uint32_t from_level, uint64_
     static hipError_t lds_status = hipSuccess;
     std::call_once(lds_once, [] {
         const int acc_lds = 2 * kChunk * (int)sizeof(double), count_lds = (int)kMaxKeys * 4;
-        const hipError_t e[6] = {
+        const hipError_t e[] = {
+            (hipError_t)reserve_compact(),
             hipFuncSetAttribute(reinterpret_cast<const void *>(&fill_ring_kernel), hipFuncAttributeMaxDynamicSharedMemorySize, kRingLds),
             hipFuncSetAttribute(reinterpret_cast<const void *>(&count_lds_kernel), hipFuncAttributeMaxDynamicSharedMemorySize, count_lds),
             hipFuncSetAttribute(reinterpret_cast<const void *>(&fill_narrow_kernel), hipFuncAttributeMaxDynamicSharedMemorySize, kNarrowLds),
-            hipFuncSetAttribute(reinterpret_cast<const void *>(&accumulate_kernel), hipFuncAttributeMaxDynamicSharedMemorySize, acc_lds),
-            hipFuncSetAttribute(reinterpret_cast<const void *>(&accumulate_sparse_kernel), hipFuncAttributeMaxDynamicSharedMemorySize, acc_lds),
+            hipFuncSetAttribute(reinterpret_cast<const void *>(&accumulate_kernel<PairRecords>), hipFuncAttributeMaxDynamicSharedMemorySize, acc_lds),
+            hipFuncSetAttribute(reinterpret_cast<const void *>(&accumulate_kernel<CompactRecords>), hipFuncAttributeMaxDynamicSharedMemorySize, acc_lds),
+            hipFuncSetAttribute(reinterpret_cast<const void *>(&accumulate_sparse_kernel<PairRecords>), hipFuncAttributeMaxDynamicSharedMemorySize, acc_lds),
+            hipFuncSetAttribute(reinterpret_cast<const void *>(&accumulate_sparse_kernel<CompactRecords>), hipFuncAttributeMaxDynamicSharedMemorySize, acc_lds),
             hipFuncSetAttribute(reinterpret_cast<const void *>(&coarse_kernel), hipFuncAttributeMaxDynamicSharedMemorySize, acc_lds)};
         for (const hipError_t x : e)
             if (x != hipSuccess) lds_status = x;
@@ -1093,8 +1078,8 @@ int prepare(const char *who, const dg_grid_desc *d, uint32_t from_level, uint64_
     q.totals = reinterpret_cast<uint32_t *>(base + q.L.totals);
     q.binbase = reinterpret_cast<uint32_t *>(base + q.L.binbase);
     q.pieces = reinterpret_cast<uint4 *>(base + q.L.pieces);
-    q.queue = reinterpret_cast<uint4 *>(base + q.L.queue);
-    q.narrow = q.p.max_bins <= 64;                 // then n_keys <= 64 * DG_MAX_LEVELS
+    q.queue = base + q.L.queue;
+    q.narrow = q.p.max_bins <= 64 && !q.p.compact; // then n_keys <= 64 * DG_MAX_LEVELS
     return DG_OK;
 }
 
@@ -1103,13 +1088,14 @@ int prepare(const char *who, const dg_grid_desc *d, uint32_t from_level, uint64_
 void launch_count(const Prepared &q, const dg_grid_desc *d, const float *u, uint64_t n0, uint64_t nb, hipStream_t st)
 {
     const Plan &p = q.p;
-    const Sweep sw = choose_sweep(p, d->n_levels, (nb + kTile - 1) / kTile);
-    count_lds_kernel<<<sw.width * sw.groups, q.narrow ? kTile : kRingThreads, p.n_keys * 4, st>>>(*d, p, sw, u, n0, nb, q.rows);
+    const Sweep sw = choose_sweep(p, d->n_levels, tiles_of(p, nb));
+    if (p.compact) count_compact(d, p, sw, u, n0, nb, q.rows, st);
+    else count_lds_kernel<<<sw.width * sw.groups, q.narrow ? kTile : kRingThreads, p.n_keys * 4, st>>>(*d, p, sw, u, n0, nb, q.rows);
     const uint32_t scan_grid = (p.n_keys + kScanKeys - 1) / kScanKeys;
     static_assert(kBinGrid == 24 * kScanGroups && kRingGrid == 8 * kScanGroups, "the scan holds a group's rows in registers");
     if (q.narrow) scan_rows_kernel<24><<<scan_grid, kScanKeys * kScanGroups, 0, st>>>(q.rows, sw.width, p.n_keys, slice_round(p), q.totals);
     else scan_rows_kernel<8><<<scan_grid, kScanKeys * kScanGroups, 0, st>>>(q.rows, sw.width, p.n_keys, slice_round(p), q.totals);
-    scan_totals_kernel<<<1, 1024, 0, st>>>(q.totals, p.n_keys, piece_log2(batch_records(p, d->n_levels, nb)), q.binbase, q.pieces);
+    scan_totals_kernel<<<1, 1024, 0, st>>>(q.totals, p.n_keys, piece_log2(batch_records(p, d->n_levels, nb)), p.compact ? slice_round(p) : 1u, q.binbase, q.pieces);
 }
 
 }  // namespace
@@ -1149,20 +1135,27 @@ int encode_bwd_binned(const char *who, const dg_grid_desc *d, uint32_t from_leve
     for (uint64_t n0 = 0; n0 < N; n0 += batch) {
         const uint64_t nb = N - n0 < batch ? N - n0 : batch;
         if (!counted) launch_count(q, d, u, n0, nb, st);
-        const Sweep sw = choose_sweep(p, d->n_levels, (nb + kTile - 1) / kTile);
-        if (q.narrow)
+        const Sweep sw = choose_sweep(p, d->n_levels, tiles_of(p, nb));
+        if (p.compact)
+            fill_compact(d, p, sw, u, dfeat, N, n0, nb, q.rows, q.binbase, q.queue, dtable, st);
+        else if (q.narrow)
             fill_narrow_kernel<<<sw.width * sw.groups, kNarrowThreads, kNarrowLds, st>>>(*d, p, sw, u, (const float2 *)dfeat, N, n0, nb, q.rows, q.binbase,
-                                                                                        q.queue, dtable, q.binbase + p.n_keys + 1);
+                                                                                        (uint4 *)q.queue, dtable, q.binbase + p.n_keys + 1);
         else
             fill_ring_kernel<<<sw.width * sw.groups, kRingThreads, p.max_bins * (kRingSlots * 16 + 12) + 16, st>>>(
-                *d, p, sw, u, (const float2 *)dfeat, N, n0, nb, q.rows, q.binbase, q.queue, dtable, q.binbase + p.n_keys + 1);
+                *d, p, sw, u, (const float2 *)dfeat, N, n0, nb, q.rows, q.binbase, (uint4 *)q.queue, dtable, q.binbase + p.n_keys + 1);
         const uint64_t records = batch_records(p, d->n_levels, nb);
         const uint32_t grid = acc_grid(p, records);
         constexpr size_t table = 2 * kChunk * sizeof(double);
-        if (sparse_bins(p, d->n_levels, nb))
-            accumulate_sparse_kernel<<<std::min(grid, (uint32_t)kAccGrid), kAccBlock, table, st>>>(*d, p, q.binbase, q.pieces, (const u32x4 *)q.queue, dtable,
-                                                                                                  q.binbase + p.n_keys + 2);
-        else accumulate_kernel<<<grid, kAccBlock, table, st>>>(*d, p, q.binbase, q.pieces, (const u32x4 *)q.queue, dtable);
+        auto accumulate = [&](auto kind) {
+            typedef decltype(kind) R;
+            if (sparse_bins(p, d->n_levels, nb))
+                accumulate_sparse_kernel<R><<<std::min(grid, (uint32_t)kAccGrid), kAccBlock, table, st>>>(*d, p, q.binbase, q.pieces, q.queue, dtable,
+                                                                                                         q.binbase + p.n_keys + 2);
+            else accumulate_kernel<R><<<grid, kAccBlock, table, st>>>(*d, p, q.binbase, q.pieces, q.queue, dtable);
+        };
+        if (p.compact) accumulate(CompactRecords{});
+        else accumulate(PairRecords{});
     }
     return launch_status(who);
 }

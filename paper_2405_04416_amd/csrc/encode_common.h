@@ -7,6 +7,11 @@ namespace dg_encode {
 
 constexpr uint32_t kPrimeY = 2654435761u, kPrimeZ = 805459861u;   // Instant-NGP Eq. 4 (x prime is 1)
 
+// Products with the hash's primes, as far as an index of at most 24 bits needs them: one full-rate instruction where a 32-bit product takes
+// four times as long
+__device__ __forceinline__ uint32_t hash_y(uint32_t y) { return __umul24(y, kPrimeY & 0xffffffu); }
+__device__ __forceinline__ uint32_t hash_z(uint32_t z) { return __umul24(z, kPrimeZ & 0xffffffu); }
+
 struct LevelGeom {
     uint32_t res[3];
     uint32_t dense;
@@ -48,6 +53,16 @@ __device__ __forceinline__ float clamp_unit(float c)
 {
     c = c >= 0.0f ? c : 0.0f;     // NaN lands on 0 as well
     return c > 1.0f ? 1.0f : c;
+}
+
+// clamp_unit and locate_axis_float in one instruction per clamp: the middle of three values, which takes NaN for the smallest
+__device__ __forceinline__ float unit(float c) { return __builtin_amdgcn_fmed3f(c, 0.0f, 1.0f); }
+__device__ __forceinline__ void locate_unit(float c, float scale, float last, float &cell, float &frac)
+{
+#pragma clang fp contract(off)
+    const float pos = c * scale;
+    cell = __builtin_amdgcn_fmed3f(floorf(pos), 0.0f, last);
+    frac = pos - cell;
 }
 
 // cell and fractional position of a sample at one level

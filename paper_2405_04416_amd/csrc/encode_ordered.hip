@@ -132,16 +132,6 @@ struct LevelBox {
     uint32_t unused[2];
 };
 
-// clamp_unit and locate_axis_float in one instruction per clamp: the middle of three values, which takes NaN for the smallest
-__device__ __forceinline__ float unit(float c) { return __builtin_amdgcn_fmed3f(c, 0.0f, 1.0f); }
-__device__ __forceinline__ void locate_unit(float c, float scale, float last, float &cell, float &frac)
-{
-#pragma clang fp contract(off)
-    const float pos = c * scale;
-    cell = __builtin_amdgcn_fmed3f(floorf(pos), 0.0f, last);
-    frac = pos - cell;
-}
-
 __device__ __forceinline__ uint32_t uniform(uint32_t v) { return (uint32_t)__builtin_amdgcn_readfirstlane((int)v); }
 __device__ __forceinline__ float uniform(float v) { return __int_as_float(__builtin_amdgcn_readfirstlane(__float_as_int(v))); }
 

@@ -327,6 +327,38 @@ def test_many_bricks_to_an_entry():
     assert max(off) <= (5.0 / 3.0) ** 0.5 * 2.0 ** -24
 
 
+@pytest.mark.parametrize("flavour", FLAVOURS)
+@pytest.mark.parametrize("log2_T", [11, 14, 17, 20, 22, 23, 24])
+def test_unmerged_levels_of_every_table_size(log2_T, flavour):
+    """Levels of one to 2048 bins, whose queues are filled from rings of 2048 lines to one, several steps per workgroup, the last one partly
+    filled; with all samples in a few cells most records find their ring full.  Pairs whose entries lie in different bins are among them."""
+    print("[case] unmerged levels", log2_T, flavour, flush=True)
+    growth = B.dg_growth_factor(16, 1024, 16)
+    grid, ref_grid = (f(16, 2, log2_T, 16, growth, [1.0, 0.9, 0.5]) for f in (B.dg_grid_desc_init, oracle.grid_init))
+    N = 150001
+    u = _coords(N, flavour)
+    order, ordered, pieces = _sorted(grid, u, N)
+    M = order.n_merged
+    assert M < 12 and max(ref_grid.first[l + 1] - ref_grid.first[l] for l in range(M, 16)) == 1 << log2_T
+    g = (np.random.default_rng(50).standard_normal((N, 32)) * 1e-3).astype(np.float32)
+    g[5::11] = 0.0
+    gd = dev(_mixed(g, M))
+    dtable = torch.zeros(ref_grid.n_entries, 2, device=DEV)
+    ws = torch.full((B.dg_hashgrid_encode_bwd_ordered_workspace_bytes(grid, order, N) // 4 + 64,), float("nan"), device=DEV)
+    B.dg_hashgrid_encode_bwd_ordered(grid, order, ordered, pieces, dev(u), gd, gd.abs().max().reshape(1).view(torch.int32), N, dtable, ws)
+    want, have = oracle.encode_bwd(ref_grid, u, g.astype(np.float64)), host(dtable).astype(np.float64)
+    scale = oracle.encode_bwd(ref_grid, u, np.abs(g).astype(np.float64))
+    for l in range(M, 16):
+        # every contribution is rounded to 2^-19 of itself at most and is four fp32 roundings deep, an x fraction to 2^-24, the sum to fp32.  Samples
+        # all over the box also average: a rounding is uniform, 2^-19 / sqrt(3) = 1.1e-6 in 2-norm, and few terms meet in an entry
+        sl = slice(ref_grid.first[l], ref_grid.first[l + 1])
+        off = np.linalg.norm(have[sl] - want[sl])
+        assert np.all(have[sl][want[sl] == 0] == 0), l
+        assert off <= (2.0 ** -19 + 8 * 2.0 ** -24) * np.linalg.norm(scale[sl]), l
+        if flavour == "points":
+            assert off <= 1.2e-6 * np.linalg.norm(want[sl]), l
+
+
 @pytest.mark.parametrize("N,log2_T,n_max", [((1 << 22) + 77, 19, 2048), ((1 << 21) + 5, 22, 8192)])
 def test_ordered_gradient_at_full_size(N, log2_T, n_max):
     """A batch of production size, level by level and entry by entry against the pass in ray order on the same gradient."""
