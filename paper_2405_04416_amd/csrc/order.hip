@@ -12,7 +12,7 @@
 //      A sample becomes 16 bytes: its coordinates and the index it came from (or a number of the caller's).
 //   2. inside a brick: pencils along x (the table's contiguous direction), sorted in LDS.
 // The order is a matter of speed alone: any order gives the same results.
-// Bound by the scatter's lone 16-byte writes (33.5 M samples: 0.53 of 1.05 ms) and the LDS sort (0.28 ms).
+// Bound by the scatter's lone 16-byte writes (33.5 M samples: 0.53 of 1.05 ms) and the LDS sort.
 #include "order_common.h"
 #include <cmath>
 #include <cstring>
@@ -128,57 +128,67 @@ brick_scatter_kernel(Bricks b, const float *__restrict__ u, const uint32_t *__re
     }
 }
 
-// Inside a brick: 16 x 8 x 8 cells, x fastest.  A brick is taken in pieces of at most kPiece samples, each sorted by
-// itself in LDS (a brick that holds many more samples than the average is only sorted piece by piece).
-constexpr int kSortBlock = 512, kCells = 1024, kPerThread = (int)kPiece / kSortBlock;
+// Inside a brick: 16 x 8 x 8 cells, x fastest.  A piece is sorted in LDS, up to kSortRun samples at a time (a brick that holds many more
+// samples than the average is only sorted run by run).  Bound by the chain from the loads over the counts to the stores, so the runs are as short
+// as the bricks of most batches and four workgroups fit a compute unit: 13.3 M samples 82 us, 19.8 M 152
+// (4096 samples, two workgroups: 137 and 410).
+constexpr int kSortBlock = 512, kCells = 1024, kSortRun = 2048, kPerThread = kSortRun / kSortBlock;
 __global__ void __launch_bounds__(kSortBlock)
 brick_sort_kernel(Bricks b, const uint2 *__restrict__ pieces, float4 *__restrict__ ordered)
 {
-    __shared__ float4 stage[kPiece];
+    __shared__ float4 stage[kSortRun];
     __shared__ uint32_t count[kCells];
     __shared__ uint32_t wave_sum[kSortBlock / dg::kWave];
     if (blockIdx.x >= pieces[0].x) return;
     const uint32_t lane = threadIdx.x % dg::kWave, wave = threadIdx.x / dg::kWave;
-    const uint32_t base = pieces[1 + blockIdx.x].y, n = pieces[2 + blockIdx.x].y - base;
-    for (uint32_t i = threadIdx.x; i < kCells; i += kSortBlock) count[i] = 0u;
-    __syncthreads();
-    float4 s[kPerThread];
-    uint32_t place[kPerThread];
+    const uint32_t end = pieces[2 + blockIdx.x].y;
+    for (uint32_t base = pieces[1 + blockIdx.x].y; base < end; base += kSortRun) {
+        const uint32_t n = min(end - base, (uint32_t)kSortRun);
+        float4 s[kPerThread];
+        uint32_t place[kPerThread];
 #pragma unroll
-    for (int k = 0; k < kPerThread; ++k) {
-        const uint32_t i = k * kSortBlock + threadIdx.x;
-        if (i >= n) continue;
-        s[k] = ordered[base + i];
-        // sixteenths and eighths of the brick (the brick's own number drops out of the low bits)
-        const uint32_t cx = (uint32_t)(unit(s[k].x) * b.per_unit[0] * 16.0f) & 15u, cy = (uint32_t)(unit(s[k].y) * b.per_unit[1] * 8.0f) & 7u,
-                       cz = (uint32_t)(unit(s[k].z) * b.per_unit[2] * 8.0f) & 7u;
-        const uint32_t yz = (cy & 1u) | (cz & 1u) << 1 | (cy & 2u) << 1 | (cz & 2u) << 2 | (cy & 4u) << 2 | (cz & 4u) << 3;
-        const uint32_t cell = yz << 4 | cx;
-        place[k] = cell << 16 | atomicAdd(&count[cell], 1u);
-    }
-    __syncthreads();
-    // exclusive scan of the cell counts, two per thread
-    const uint32_t c0 = count[2 * threadIdx.x], c1 = count[2 * threadIdx.x + 1];
-    uint32_t incl = c0 + c1;
+        for (int k = 0; k < kPerThread; ++k) {
+            const uint32_t i = k * kSortBlock + threadIdx.x;
+            if (i < n) s[k] = ordered[base + i];
+        }
+        for (uint32_t i = threadIdx.x; i < kCells; i += kSortBlock) count[i] = 0u;
+        __syncthreads();
 #pragma unroll
-    for (int off = 1; off < dg::kWave; off <<= 1) {
-        const uint32_t up = __shfl_up(incl, off, dg::kWave);
-        if ((int)lane >= off) incl += up;
-    }
-    if (lane == dg::kWave - 1) wave_sum[wave] = incl;
-    __syncthreads();
-    uint32_t run = incl - c0 - c1;
-    for (uint32_t w = 0; w < wave; ++w) run += wave_sum[w];
-    count[2 * threadIdx.x] = run;
-    count[2 * threadIdx.x + 1] = run + c0;
-    __syncthreads();
+        for (int k = 0; k < kPerThread; ++k) {
+            const uint32_t i = k * kSortBlock + threadIdx.x;
+            if (i >= n) continue;
+            // sixteenths and eighths of the brick (the brick's own number drops out of the low bits)
+            const uint32_t cx = (uint32_t)(unit(s[k].x) * b.per_unit[0] * 16.0f) & 15u, cy = (uint32_t)(unit(s[k].y) * b.per_unit[1] * 8.0f) & 7u,
+                           cz = (uint32_t)(unit(s[k].z) * b.per_unit[2] * 8.0f) & 7u;
+            const uint32_t yz = (cy & 1u) | (cz & 1u) << 1 | (cy & 2u) << 1 | (cz & 2u) << 2 | (cy & 4u) << 2 | (cz & 4u) << 3;
+            const uint32_t cell = yz << 4 | cx;
+            place[k] = cell << 16 | atomicAdd(&count[cell], 1u);
+        }
+        __syncthreads();
+        // exclusive scan of the cell counts, two per thread
+        const uint32_t c0 = count[2 * threadIdx.x], c1 = count[2 * threadIdx.x + 1];
+        uint32_t incl = c0 + c1;
 #pragma unroll
-    for (int k = 0; k < kPerThread; ++k) {
-        const uint32_t i = k * kSortBlock + threadIdx.x;
-        if (i < n) stage[count[place[k] >> 16] + (place[k] & 0xffffu)] = s[k];
+        for (int off = 1; off < dg::kWave; off <<= 1) {
+            const uint32_t up = __shfl_up(incl, off, dg::kWave);
+            if ((int)lane >= off) incl += up;
+        }
+        if (lane == dg::kWave - 1) wave_sum[wave] = incl;
+        __syncthreads();
+        uint32_t run = incl - c0 - c1;
+        for (uint32_t w = 0; w < wave; ++w) run += wave_sum[w];
+        count[2 * threadIdx.x] = run;
+        count[2 * threadIdx.x + 1] = run + c0;
+        __syncthreads();
+#pragma unroll
+        for (int k = 0; k < kPerThread; ++k) {
+            const uint32_t i = k * kSortBlock + threadIdx.x;
+            if (i < n) stage[count[place[k] >> 16] + (place[k] & 0xffffu)] = s[k];
+        }
+        __syncthreads();
+        for (uint32_t i = threadIdx.x; i < n; i += kSortBlock) ordered[base + i] = stage[i];
+        __syncthreads();                                                  // counts and sums of the next run
     }
-    __syncthreads();
-    for (uint32_t i = threadIdx.x; i < n; i += kSortBlock) ordered[base + i] = stage[i];
 }
 
 }  // namespace
