@@ -103,6 +103,27 @@ def _march_gpu(o, d, seg_t, seg_ray, seg_slot, begin, end, box, g, bits, dt, max
     return host(first).view(np.uint32), host(u), host(delta), host(t), host(ray).view(np.uint32), int(host(status)[0])
 
 
+@pytest.mark.parametrize("n_strata", [1, 15, 16, 17, 31, 32, 33, 255, 256, 257, 289, 1003])
+def test_march_numbers_of_strata(n_strata):
+    """Segments of as many strata as a pass, a word of kept bits and all words hold, one less and one more, and of more than the bits reach:
+    sample by sample as the oracle's, with half of the cells occupied at random."""
+    say("march n_strata=%d" % n_strata)
+    cfg = di.config("c3_2x2")
+    o, d, seg_t, off, seg_ray, seg_slot = _segments(cfg, 61, seed=6)
+    box, begin, end = cfg["parts"][0], int(off[0]), int(off[1])
+    ext = di.box_extent(box)
+    g_ref, g = oracle.occ_init(96, ext), B.dg_occ_desc_init(96, ext)
+    bits = np.random.default_rng(7).integers(0, 1 << 32, (g_ref.n_cells + 31) // 32, dtype=np.uint64).astype(np.uint32)
+    dt = np.float32(1e-6)                             # finer than any segment needs: every one is cut into max_steps strata
+    rf, ru, rd, rt, rr = oracle.march_segments(o, d, seg_t, seg_ray, seg_slot, begin, end, box, g_ref, bits, dt, n_strata, seed=23)
+    n = int(rf[-1])
+    assert end - begin > 16 and n > 0
+    first, u, delta, t, ray, status = _march_gpu(o, d, seg_t, seg_ray, seg_slot, begin, end, box, g, bits, dt, n_strata, 23, n)
+    assert status == 0
+    for got, ref in ((first, rf), (u[:n], ru), (delta[:n], rd), (t[:n], rt), (ray[:n], rr)):
+        np.testing.assert_array_equal(got, ref)
+
+
 @pytest.mark.parametrize("name,R,N,max_steps,fill", [("c2_ngp", 3000, 64, 4096, "scene"), ("c2_ngp", 700, 512, 4096, "scene"),
                                                       ("c3_2x2", 2001, 48, 4096, "scene"), ("c2_ngp", 500, 64, 4096, "full"),
                                                       ("c2_ngp", 500, 64, 4096, "empty"), ("c2_ngp", 900, 64, 37, "scene"),
