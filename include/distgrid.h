@@ -223,6 +223,10 @@ int dg_hashgrid_encode_fwd_ordered(const dg_grid_desc *desc, const float *table,
 #define DG_SPLIT_LEVELS 12
 int dg_hashgrid_encode_fwd_split(const dg_grid_desc *desc, const float *table, const void *ordered, const float *u, uint64_t N,
                                  uint32_t by_position, void *feat, void *stream);
+/* What dg_hashgrid_encode_fwd_split gives, with the levels below order->n_merged gathered brick by brick from on-chip memory:
+ * order and pieces are those that `ordered` was made with (dg_order_samples). */
+int dg_hashgrid_encode_fwd_bricks(const dg_grid_desc *desc, const dg_order_desc *order, const float *table, const void *ordered,
+                                  const uint32_t *pieces, const float *u, uint64_t N, uint32_t by_position, void *feat, void *stream);
 /* dg_hashgrid_encode_bwd on the sorted list.  dfeat: rows [N, 2 * n_merged] fp32 of the merged levels (16-byte aligned, in
  * the samples' original order), then the planes [L - n_merged, N, 2] of the others -- as dg_mlp_bwd_rows writes it; u [N,3]
  * the samples in their original order.  *largest: device word, the bit pattern of a float that no |dfeat| exceeds.

@@ -109,6 +109,7 @@ _SIGNATURES = {
     "dg_mlp_fwd_rows": (C.c_int, [C.POINTER(MlpDesc)] + [C.c_void_p] * 4 + [C.c_uint32, C.c_uint64] + [C.c_void_p] * 3),
     "dg_mlp_composite_fwd_rows": (C.c_int, [C.POINTER(MlpDesc)] + [C.c_void_p] * 4 + [C.c_uint32, C.c_uint32] + [C.c_void_p] * 4 + [C.c_uint32]
                                   + [C.c_void_p] * 4),
+    "dg_hashgrid_encode_fwd_bricks": (C.c_int, [C.POINTER(GridDesc), C.POINTER(OrderDesc)] + [C.c_void_p] * 4 + [C.c_uint64, C.c_uint32, C.c_void_p, C.c_void_p]),
     "dg_hashgrid_encode_fwd_split": (C.c_int, [C.POINTER(GridDesc)] + [C.c_void_p] * 3 + [C.c_uint64, C.c_uint32, C.c_void_p, C.c_void_p]),
     "dg_mlp_fwd_split": (C.c_int, [C.POINTER(MlpDesc)] + [C.c_void_p] * 4 + [C.c_uint32, C.c_uint64] + [C.c_void_p] * 3),
     "dg_mlp_bwd_split": (C.c_int, [C.POINTER(MlpDesc)] + [C.c_void_p] * 4 + [C.c_uint32, C.c_uint64, C.c_void_p, C.c_void_p, C.c_float, C.c_uint32]
@@ -382,6 +383,12 @@ def dg_hashgrid_encode_fwd_split(desc, table, ordered, u, N, feat, by_position=F
     assert ordered.numel() >= 4 * N and u.numel() >= 3 * N and feat.numel() >= 32 * N
     _check(lib().dg_hashgrid_encode_fwd_split(C.byref(desc), _ptr(table, torch.float32), _ptr(ordered, torch.float32), _ptr(u, torch.float32), N,
                                               1 if by_position else 0, _ptr(feat, torch.float16), _stream()))
+
+
+def dg_hashgrid_encode_fwd_bricks(desc, order, table, ordered, pieces, u, N, feat, by_position=False):
+    assert ordered.numel() >= 4 * N and u.numel() >= 3 * N and feat.numel() >= 32 * N and pieces.numel() >= dg_order_pieces_words(order, N)
+    _check(lib().dg_hashgrid_encode_fwd_bricks(C.byref(desc), C.byref(order), _ptr(table, torch.float32), _ptr(ordered, torch.float32), _ptr(pieces, torch.int32),
+                                               _ptr(u, torch.float32), N, 1 if by_position else 0, _ptr(feat, torch.float16), _stream()))
 
 
 def dg_hashgrid_encode_bwd_ordered_workspace_bytes(desc, order, N):

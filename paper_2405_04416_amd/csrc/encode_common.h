@@ -111,40 +111,64 @@ __device__ __forceinline__ double from_low_bits(unsigned long long held)
     return __longlong_as_double((long long)((unsigned long long)high << 32 | (uint32_t)held)) - 0x1.4p52;
 }
 
+// value of the other lane of a pair (quad_perm 1, 0, 3, 2)
+__device__ __forceinline__ uint32_t from_pair(uint32_t v) { return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0xB1, 0xF, 0xF, true); }
+
 // Features of one sample at one level by two lanes: cx = 0 takes the four corners with x of the cell, its neighbour cx = 1 those with x + 1
 // -- the two entries of an x-pair nearly always share a cache line, which then costs one look-up -- and a DPP move adds the halves.
-__device__ __forceinline__ float2 gather_pair(const LevelGeom &lv, uint32_t mask, const float2 *__restrict__ table, const float (&uu)[3], uint32_t cx)
-{
-    uint32_t cell[3], e[4];
+struct PairCorners {
+    float2 v[4];
     float frac[3];
-    locate(lv, uu, cell, frac);
+};
+
+// asks for the lane's four corners; uu within [0, 1]
+__device__ __forceinline__ PairCorners ask_pair(const LevelGeom &lv, uint32_t mask, const float2 *__restrict__ table, const float (&uu)[3], uint32_t cx)
+{
+    PairCorners q;
+    float at[3];
+    uint32_t cell[3], e[4];
+#pragma unroll
+    for (int a = 0; a < 3; ++a) {
+        locate_unit(uu[a], lv.scale[a], (float)(lv.res[a] - 1u), at[a], q.frac[a]);
+        cell[a] = (uint32_t)at[a];
+    }
     if (lv.dense) {
         const uint32_t nx = lv.res[0] + 1u, nxy = nx * (lv.res[1] + 1u);
         const uint32_t base = cell[0] + cx + nx * cell[1] + nxy * cell[2];
 #pragma unroll
         for (int k = 0; k < 4; ++k) e[k] = base + (k & 1) * nx + (k >> 1) * nxy;
     } else {
-        const uint32_t hy0 = cell[1] * kPrimeY, hy1 = hy0 + kPrimeY;
-        const uint32_t hz0 = cell[2] * kPrimeZ, hz1 = hz0 + kPrimeZ;
+        const uint32_t hy0 = hash_y(cell[1]), hy1 = hy0 + kPrimeY;
+        const uint32_t hz0 = hash_z(cell[2]), hz1 = hz0 + kPrimeZ;
 #pragma unroll
         for (int k = 0; k < 4; ++k) e[k] = ((cell[0] + cx) ^ ((k & 1) ? hy1 : hy0) ^ ((k & 2) ? hz1 : hz0)) & mask;
     }
-    const float wx = cx ? frac[0] : 1.0f - frac[0];
-    const float wy[2] = {1.0f - frac[1], frac[1]}, wz[2] = {1.0f - frac[2], frac[2]};
-    float2 v[4];
 #pragma unroll
-    for (int k = 0; k < 4; ++k) v[k] = table[(size_t)lv.offset + e[k]];
+    for (int k = 0; k < 4; ++k) q.v[k] = table[(size_t)lv.offset + e[k]];
+    return q;
+}
+
+// both lanes get the sum
+__device__ __forceinline__ float2 finish_pair(const PairCorners &q, uint32_t cx)
+{
+    const float wx = cx ? q.frac[0] : 1.0f - q.frac[0];
+    const float wy[2] = {1.0f - q.frac[1], q.frac[1]}, wz[2] = {1.0f - q.frac[2], q.frac[2]};
     float f0 = 0.0f, f1 = 0.0f;
 #pragma unroll
     for (int k = 0; k < 4; ++k) {
         const float w = wx * wy[k & 1] * wz[k >> 1];
-        f0 = fmaf(w, v[k].x, f0);
-        f1 = fmaf(w, v[k].y, f1);
+        f0 = fmaf(w, q.v[k].x, f0);
+        f1 = fmaf(w, q.v[k].y, f1);
     }
-    // the partner's half: lanes swapped within pairs (quad_perm 1, 0, 3, 2)
-    f0 += __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(f0), 0xB1, 0xF, 0xF, true));
-    f1 += __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(f1), 0xB1, 0xF, 0xF, true));
+    f0 += __uint_as_float(from_pair(__float_as_uint(f0)));
+    f1 += __uint_as_float(from_pair(__float_as_uint(f1)));
     return make_float2(f0, f1);
+}
+
+__device__ __forceinline__ float2 gather_pair(const LevelGeom &lv, uint32_t mask, const float2 *__restrict__ table, const float (&uu)[3], uint32_t cx)
+{
+    const float at[3] = {unit(uu[0]), unit(uu[1]), unit(uu[2])};
+    return finish_pair(ask_pair(lv, mask, table, at, cx), cx);
 }
 
 // value of the lane below (lane - 1) in the wavefront; lane 0 gets its own.  A DPP move: no LDS traffic, no wait.

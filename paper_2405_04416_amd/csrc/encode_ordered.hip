@@ -360,6 +360,168 @@ brick_bwd_kernel(dg_grid_desc g, Bricks b, Boxes boxes, const uint2 *__restrict_
     }
 }
 
+// ---- forward, brick by brick
+constexpr int kFwdThreads = 1024;
+constexpr uint32_t kFwdChunk = 16;
+
+// what a gather from the brick's box of a level needs
+struct FwdBox {
+    float scale[3], origin;                  // slot = x + nx y + nxy z - origin (all exact: below 2^24)
+    float last[3], nx;
+    float nxy;
+    uint32_t first, last_slot, nx_bytes;     // first: of the level's sums, in bytes; last_slot: whose eight corners lie in the box
+    uint32_t nxy_bytes, unused[3];
+};
+// and what filling it does: its place in the grid and in the table
+struct FwdFill {
+    float nx, nxy, per_nx, per_nxy;
+    uint32_t low[3], dense;
+    uint32_t res[3], offset;                 // offset: of the level's entries in the table
+};
+
+// Rows of the first kSplitLevels levels, the finer ones of which come as planes (encode_planes_kernel).  What bounds the walk above is the vector cache,
+// a look-up per clock and compute unit, whatever the walk finds there.  Here a workgroup takes a piece of a brick and first copies the
+// brick's vertices at the merged levels to LDS -- 5000 of them, where its samples make 30 000 look-ups --; a sample's two lanes then take half of these
+// levels each, eight corners from LDS.  Levels between the merged and the split ones are gathered as above, asked for before the others' arithmetic.
+// 3.3 M samples, T = 2^19, ten levels of twelve merged 213 -> 134 us; 8.4 M 473 -> 280.  Rows of all sixteen levels this way are no faster: the finer levels
+// bound them, and the LDS of the boxes leaves room for fewer wavefronts to wait for their lines (13.3 M, T = 2^19 1486 / 1512 us; 33.5 M,
+// T = 2^24 10.3 / 10.4 ms; 1.55 M with eight merged levels 177 / 348 us).  Boxes filled level by level, without loads under way together: 147 us
+// instead of 138; equal numbers of pieces to every XCD in one stretch: 16.4 ms instead of 10.7, as one gets the crowded side of the box.
+template <int MERGED>
+__global__ void __launch_bounds__(kFwdThreads)
+encode_fwd_bricks_kernel(dg_grid_desc g, Bricks b, Boxes boxes, const uint2 *__restrict__ pieces, const float2 *__restrict__ table,
+                         const float4 *__restrict__ ordered, bool by_position, uint32_t *__restrict__ feat)
+{
+    constexpr int LEVELS = kSplitLevels;
+    extern __shared__ __attribute__((aligned(16))) float2 box[];
+    __shared__ __attribute__((aligned(16))) FwdBox levels[MERGED];
+    __shared__ __attribute__((aligned(16))) FwdFill fills[MERGED];
+    // an XCD takes kFwdChunk consecutive pieces, the next one the next: neighbours meet in one L2, and no XCD gets the empty side of the box
+    const uint32_t in_xcd = blockIdx.x / kXcds, index = (in_xcd / kFwdChunk * kXcds + blockIdx.x % kXcds) * kFwdChunk + in_xcd % kFwdChunk;
+    if (index >= pieces[0].x) return;
+    const uint2 piece = pieces[1 + index];
+    const uint32_t begin = piece.y, n = pieces[2 + index].y - begin;
+    const uint32_t mask = (1u << g.log2_T) - 1u;
+    if (threadIdx.x < MERGED) {
+        const uint32_t l = threadIdx.x, nx = boxes.dim[l][0], nxy = nx * boxes.dim[l][1], count = boxes.first[l + 1] - boxes.first[l];
+        const uint32_t brick[3] = {piece.x % b.n[0], piece.x / b.n[0] % b.n[1], piece.x / (b.n[0] * b.n[1])};
+        FwdBox v{};
+        FwdFill w;
+#pragma unroll
+        for (int a = 0; a < 3; ++a) {
+            v.scale[a] = g.scale[l][a];
+            v.last[a] = (float)(g.res[l][a] - 1u);
+            w.low[a] = box_low(b, brick[a], a, v.scale[a]);
+            w.res[a] = g.res[l][a];
+        }
+        v.origin = (float)(w.low[0] + nx * w.low[1] + nxy * w.low[2]);
+        v.nx = w.nx = (float)nx;
+        v.nxy = w.nxy = (float)nxy;
+        v.first = boxes.first[l] * (uint32_t)sizeof(float2);
+        v.last_slot = count - 2u - nx - nxy;
+        v.nx_bytes = nx * (uint32_t)sizeof(float2);
+        v.nxy_bytes = nxy * (uint32_t)sizeof(float2);
+        w.per_nx = 1.0f / w.nx;
+        w.per_nxy = 1.0f / w.nxy;
+        w.dense = g.dense[l];
+        w.offset = g.offset[l];
+        levels[l] = v;
+        fills[l] = w;
+    }
+    __syncthreads();
+    // The boxes of all levels in one go: a thread's vertices are asked for before the first of them is waited for
+    {
+        constexpr int kPer = (int)((kMaxBoxVertices + kFwdThreads - 1) / kFwdThreads);
+        const uint32_t n_vertices = boxes.first[MERGED];
+        float2 entry[kPer];
+#pragma unroll
+        for (int k = 0; k < kPer; ++k) {
+            const uint32_t at = min(k * kFwdThreads + threadIdx.x, n_vertices - 1u);
+            uint32_t l = 0, first = 0;
+#pragma unroll
+            for (int m = 1; m < MERGED; ++m)
+                if (at >= boxes.first[m]) { l = m; first = boxes.first[m]; }
+            const FwdFill w = fills[l];
+            // quotients as in brick_bwd_kernel; vertices beyond the grid, which no cell has, repeat the last one
+            const float fv = (float)(at - first), fz = floorf(__builtin_fmaf(fv, w.per_nxy, 0.5f * w.per_nxy)), in_z = __builtin_fmaf(-fz, w.nxy, fv);
+            const float fy = floorf(__builtin_fmaf(in_z, w.per_nx, 0.5f * w.per_nx));
+            const uint32_t x = min(w.low[0] + (uint32_t)__builtin_fmaf(-fy, w.nx, in_z), w.res[0]), y = min(w.low[1] + (uint32_t)fy, w.res[1]),
+                           z = min(w.low[2] + (uint32_t)fz, w.res[2]);
+            // indices of at most 24 bits
+            const uint32_t e = w.dense ? x + __umul24(w.res[0] + 1u, y + __umul24(w.res[1] + 1u, z)) : (x ^ hash_y(y) ^ hash_z(z)) & mask;
+            entry[k] = table[(size_t)w.offset + e];
+        }
+#pragma unroll
+        for (int k = 0; k < kPer; ++k)
+            if (k * kFwdThreads + threadIdx.x < n_vertices) box[k * kFwdThreads + threadIdx.x] = entry[k];
+    }
+    __syncthreads();
+    const uint32_t odd = threadIdx.x & 1u;
+    for (uint32_t i = threadIdx.x / 2; i < n; i += kFwdThreads / 2) {
+        const float4 s = ordered[begin + i];
+        const float uu[3] = {unit(s.x), unit(s.y), unit(s.z)};
+        // the finer levels' corners are asked for first, and waited for last
+        PairCorners finer[LEVELS > MERGED ? LEVELS - MERGED : 1];
+#pragma unroll
+        for (int l = MERGED; l < LEVELS; ++l) finer[l - MERGED] = ask_pair(level_of(g, l), mask, table, uu, odd);
+        __builtin_amdgcn_sched_barrier(0);
+        uint32_t mine[MERGED / 2];                           // levels 0 .. MERGED / 2 - 1 on the even lane, the others on the odd one
+        // read where it is used: held in registers for all levels it would leave no room for the wavefronts
+        uint32_t from = odd * (MERGED / 2);
+        asm volatile("" : "+v"(from));
+        const FwdBox *const here = levels + from;
+#pragma unroll
+        for (int l = 0; l < MERGED / 2; ++l) {
+            const FwdBox q = here[l];
+            float cell[3], w1[3], w0[3];
+#pragma unroll
+            for (int a = 0; a < 3; ++a) {
+                locate_unit(uu[a], q.scale[a], q.last[a], cell[a], w1[a]);
+                w0[a] = 1.0f - w1[a];
+            }
+            // whole numbers below 2^24: exact in fp32
+            const uint32_t slot = min((uint32_t)__builtin_fmaf(cell[2], q.nxy, __builtin_fmaf(cell[1], q.nx, cell[0] - q.origin)), q.last_slot);
+            const char *const at = reinterpret_cast<const char *>(box) + q.first + slot * (uint32_t)sizeof(float2);
+            float2 v[8];
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {
+                const float2 *row = reinterpret_cast<const float2 *>(at + ((r & 1) ? q.nx_bytes : 0u) + ((r & 2) ? q.nxy_bytes : 0u));
+                v[2 * r] = row[0];
+                v[2 * r + 1] = row[1];
+            }
+            const float yz[4] = {w0[1] * w0[2], w1[1] * w0[2], w0[1] * w1[2], w1[1] * w1[2]};
+            float f0 = 0.0f, f1 = 0.0f;
+#pragma unroll
+            for (int c = 0; c < 8; ++c) {
+                const float w = (c & 1 ? w1[0] : w0[0]) * yz[c >> 1];
+                f0 = __builtin_fmaf(w, v[c].x, f0);
+                f1 = __builtin_fmaf(w, v[c].y, f1);
+            }
+            mine[l] = __builtin_bit_cast(uint32_t, __floats2half2_rn(f0, f1));
+            asm volatile("" : "+v"(mine[l]));                // done here: put off to where the rows are written, all levels' corners would wait for it
+        }
+        // half of the sample's row per lane
+        constexpr int kHalfRow = LEVELS / 2;
+        uint32_t out[kHalfRow];
+#pragma unroll
+        for (int l = 0; l < LEVELS; ++l) {
+            uint32_t f;
+            if (l < MERGED / 2) f = mine[l];
+            else if (l < MERGED) f = l < kHalfRow ? from_pair(mine[l - MERGED / 2]) : mine[l - MERGED / 2];
+            else {
+                const float2 v = finish_pair(finer[l - MERGED], odd);
+                f = __builtin_bit_cast(uint32_t, __floats2half2_rn(v.x, v.y));
+            }
+            if (l < kHalfRow) out[l] = f;
+            else out[l - kHalfRow] = odd ? f : out[l - kHalfRow];
+        }
+        uint32_t *half_row = feat + (size_t)(by_position ? begin + i : __float_as_uint(s.w)) * LEVELS + kHalfRow * odd;
+        static_assert(kHalfRow % 2 == 0, "halves of rows are written in steps of 8 bytes");
+#pragma unroll
+        for (int k = 0; k < kHalfRow; k += 2) *reinterpret_cast<uint2 *>(half_row + k) = make_uint2(out[k], out[k + 1]);
+    }
+}
+
 __global__ void __launch_bounds__(kBlock)
 fold_wide_kernel(const double *__restrict__ wide_table, uint32_t n, float *__restrict__ dtable)
 {
@@ -367,6 +529,17 @@ fold_wide_kernel(const double *__restrict__ wide_table, uint32_t n, float *__res
     if (i >= n) return;
     const float v = (float)wide_table[i];
     if (v != 0.0f) unsafeAtomicAdd(dtable + i, v);
+}
+
+Boxes boxes_of(const dg_order_desc *order)
+{
+    Boxes boxes{};
+    boxes.n_merged = order->n_merged;
+    for (uint32_t l = 0; l < order->n_merged; ++l) {
+        for (int a = 0; a < 3; ++a) boxes.dim[l][a] = order->box[l][a];
+        boxes.first[l + 1] = order->box_first[l + 1];
+    }
+    return boxes;
 }
 
 // Merged levels whose bricks are summed in fp64: tables of at most 2^18 entries, which get many adds per entry -- the coarse levels
@@ -399,14 +572,9 @@ int brick_bwd(const char *who, const dg_grid_desc *d, const dg_order_desc *order
                                          (int)(kMaxBoxVertices * 2 * sizeof(double)));
     });
     if (lds_status != hipSuccess) return fail(DG_ERR_HIP, "%s: cannot reserve LDS: %s", who, hipGetErrorString(lds_status));
-    Boxes boxes{};
-    boxes.n_merged = order->n_merged;
+    Boxes boxes = boxes_of(order);
     boxes.n_wide = std::min(coarse_levels(d), order->n_merged);
     boxes.n_fold = fold_levels(d, order);
-    for (uint32_t l = 0; l < order->n_merged; ++l) {
-        for (int a = 0; a < 3; ++a) boxes.dim[l][a] = order->box[l][a];
-        boxes.first[l + 1] = order->box_first[l + 1];
-    }
     const size_t lds = (size_t)boxes.first[boxes.n_merged] * 2 * sizeof(double);
     const uint32_t n_wide_sums = 2 * d->offset[boxes.n_fold];
     if (int rc = dg_clear(wide, n_wide_sums * sizeof(double), st)) return rc;
@@ -434,6 +602,15 @@ extern "C" int dg_hashgrid_encode_fwd_ordered(const dg_grid_desc *desc, const fl
     return dg::launch_status(who);
 }
 
+namespace {
+void launch_planes(const dg_grid_desc &d, const float *table, const void *ordered, const float *u, uint64_t N, uint32_t by_position, void *feat, hipStream_t st)
+{
+    const uint32_t blocks = (uint32_t)((2 * N + kBlock - 1) / kBlock), grid = (16 - kSplitLevels) * blocks;
+    if (by_position) encode_planes_kernel<true><<<grid, kBlock, 0, st>>>(d, (const float2 *)table, (const float *)ordered, N, (uint32_t *)feat, blocks);
+    else encode_planes_kernel<false><<<grid, kBlock, 0, st>>>(d, (const float2 *)table, u, N, (uint32_t *)feat, blocks);
+}
+}  // namespace
+
 extern "C" int dg_hashgrid_encode_fwd_split(const dg_grid_desc *desc, const float *table, const void *ordered, const float *u, uint64_t N,
                                             uint32_t by_position, void *feat, void *stream)
 {
@@ -448,9 +625,7 @@ extern "C" int dg_hashgrid_encode_fwd_split(const dg_grid_desc *desc, const floa
     hipStream_t st = (hipStream_t)stream;
     encode_fwd_ordered_kernel<kSplitLevels><<<(uint32_t)(per_xcd * kXcds), kBlock, 0, st>>>(*desc, (const float2 *)table, (const float4 *)ordered, N, by_position != 0,
                                                                                            (uint32_t *)feat, (uint32_t)per_xcd);
-    const uint32_t grid = (uint32_t)((16 - kSplitLevels) * blocks);
-    if (by_position) encode_planes_kernel<true><<<grid, kBlock, 0, st>>>(*desc, (const float2 *)table, (const float *)ordered, N, (uint32_t *)feat, (uint32_t)blocks);
-    else encode_planes_kernel<false><<<grid, kBlock, 0, st>>>(*desc, (const float2 *)table, u, N, (uint32_t *)feat, (uint32_t)blocks);
+    launch_planes(*desc, table, ordered, u, N, by_position, feat, st);
     return dg::launch_status(who);
 }
 
@@ -506,4 +681,28 @@ extern "C" int dg_hashgrid_encode_bwd_ordered(const dg_grid_desc *desc, const dg
                                               size_t ws_bytes, uint32_t counted, void *stream)
 {
     return bwd_ordered("dg_hashgrid_encode_bwd_ordered", desc, order, ordered, pieces, u, dfeat, largest, N, dtable, ws, ws_bytes, counted != 0, stream);
+}
+
+extern "C" int dg_hashgrid_encode_fwd_bricks(const dg_grid_desc *desc, const dg_order_desc *order, const float *table, const void *ordered,
+                                             const uint32_t *pieces, const float *u, uint64_t N, uint32_t by_position, void *feat, void *stream)
+{
+    const char *who = "dg_hashgrid_encode_fwd_bricks";
+    if (int rc = ordered_ok(who, desc, order)) return rc;
+    if (N == 0) return DG_OK;
+    DG_REQUIRE(table && ordered && pieces && feat && (u || by_position), DG_ERR_ARG, "%s: null pointer", who);
+    DG_REQUIRE(dg::aligned(table, 8) && dg::aligned(ordered, 16) && dg::aligned(pieces, 8) && dg::aligned(feat, 16), DG_ERR_ARG, "%s: misaligned pointer", who);
+    DG_REQUIRE((16 - kSplitLevels) * ((2 * N + kBlock - 1) / kBlock) <= 0x7fffffffull, DG_ERR_UNSUPPORTED, "%s: N too large for one launch", who);
+    hipStream_t st = (hipStream_t)stream;
+    const Boxes boxes = boxes_of(order);
+    auto launch = [&](auto kernel) {
+        const uint64_t stretch = kXcds * kFwdChunk, grid = (piece_bound(order->total, N) + stretch - 1) / stretch * stretch;
+        kernel<<<(uint32_t)grid, kFwdThreads, boxes.first[boxes.n_merged] * sizeof(float2), st>>>(
+            *desc, bricks_of(order), boxes, (const uint2 *)pieces, (const float2 *)table, (const float4 *)ordered, by_position != 0, (uint32_t *)feat);
+    };
+    if (order->n_merged == 12) launch(encode_fwd_bricks_kernel<12>);
+    else if (order->n_merged == 10) launch(encode_fwd_bricks_kernel<10>);
+    else if (order->n_merged == 8) launch(encode_fwd_bricks_kernel<8>);
+    else return dg_hashgrid_encode_fwd_split(desc, table, ordered, u, N, by_position, feat, stream);
+    launch_planes(*desc, table, ordered, u, N, by_position, feat, st);
+    return dg::launch_status(who);
 }

@@ -204,24 +204,25 @@ class TrainStep:
 
     def _split(self, m, N, use):
         """Whether the features of samples in spatial order are split: rows of the first levels, planes of the finer ones, which are
-        gathered level after level.  Pays where an XCD's L2 holds much of one level's table but not of the sixteen that the ordered gather
-        walks at once, and while neighbours share few of the finer levels' lines.  One walk / split in us:
-        step, T = 2^17 1400 / 1381 at 2.0 M samples, 1979 / 1995 at 3.3 M; T = 2^18 2045 / 1990 at 3.3 M, 2663 / 2667 at 4.6 M; T = 2^19 1137 / 1028 at
-        1.2 M, 2849 / 2747 at 4.6 M, 3862 / 3870 at 6.6 M; T = 2^20 1655 / 1604 at 2.0 M, 2385 / 2385 at 3.3 M; T = 2^21 1304 / 1276 at 1.2 M, 2062 / 2134 at
-        2.5 M, with 8192 cells along the box 1422 / 1336 at 1.0 M, 4793 / 4424 at 4.7 M; T = 2^22 with 2048 cells 4156 / 4285 (four of 0.79 M), with 8192
-        1603 / 1550 at 1.0 M, 5070 / 4947 at 4.7 M; T = 2^24 2100 / 2095 at 0.69 M, 4136 / 4156 at 2.8 M.
-        Occupancy-guided steps, whose samples share more, lose or gain little: T = 2^19 1009 / 1027 at 1.0 M.
-        Refresh, pieces of 8.4 M, 4.2 M and 2.1 M candidates: T = 2^17 1383 / 1403, -, 1723 / 1591; T = 2^18 1478 / 1421, 1639 / 1422, 2061 / 1628;
-        T = 2^19 1693 / 1597, 2051 / 1627, 2546 / 1851; T = 2^20 1821 / 1948, 2231 / 2074, 2756 / 2393.
-        Tables that are not named (T = 2^23, and below 2^17) were not measured and keep the one walk."""
+        gathered level after level; the rows' merged levels come brick by brick from LDS.  Pays where an XCD's L2 holds much of one level's
+        table but not of the sixteen that the ordered gather walks at once, and while neighbours share few of the finer levels' lines.  One
+        walk / split in us:
+        step, T = 2^17 1315 / 1284 at 2.0 M samples, 2260 / 2222 at 4.1 M, 6592 / 6733 at 13.3 M; T = 2^18 2344 / 2272 at 4.1 M, 3594 / 3564 at 6.6 M, 6574 / 6693 at
+        13.3 M; T = 2^19 3830 / 3730 at 6.6 M, 5038 / 5020 at 9.2 M, 6737 / 6912 at 13.3 M; T = 2^20 1353 / 1284 at 1.5 M, 2096 / 2016 at 3.1 M, 3972 / 4151 at 6.6 M;
+        T = 2^21 1111 / 1092 at 1.0 M, 2236 / 2329 at 3.1 M; T = 2^22 with 2048 cells 4614 / 4825 (four of 1.0 M), with 8192 cells 1590 / 1541 at 1.1 M, 4706 / 4550 at
+        4.9 M, 9932 / 9725 at 11.3 M, 11344 / 11124 at 12.8 M; T = 2^23 11645 / 12166 at 12.8 M; T = 2^24 2395 / 2406 at 1.1 M.  T = 2^21 with 8192 cells was measured with
+        the walk for both: 1422 / 1336 at 1.0 M, 4793 / 4424 at 4.7 M.
+        Occupancy-guided steps, whose samples share more: T = 2^18 1172 / 1189 at 1.5 M, T = 2^19 1196 / 1229, T = 2^20 1251 / 1363.
+        Refresh, pieces of 8.4 M and 2.1 M candidates: T = 2^17 1344 / 1167; T = 2^18 1411 / 1205; T = 2^19 1646 / 1373, 2525 / 1680; T = 2^20 1789 / 1756, 2751 / 2204.
+        Tables that are not named (below 2^17) were not measured and keep the one walk."""
         T = m.grid.log2_T
         if use == "refresh":
-            return N < {17: 3 << 20, 18: 10 << 20, 19: 10 << 20, 20: 6 << 20}.get(T, 0)
+            return N < {17: 10 << 20, 18: 10 << 20, 19: 10 << 20, 20: 10 << 20}.get(T, 0)
         if use != "step" or self.occ is not None:
             return False
         if T > 20 and self._fine(m):
-            return N < {21: 5 << 20, 22: 5 << 20}.get(T, 0)
-        return N < {17: 5 << 19, 18: 1 << 22, 19: 23 << 18, 20: 5 << 19, 21: 3 << 19}.get(T, 0)
+            return N < {21: 5 << 20, 22: 13 << 20}.get(T, 0)
+        return N < {17: 5 << 20, 18: 7 << 20, 19: 9 << 20, 20: 1 << 22, 21: 3 << 19}.get(T, 0)
 
     def _encode_ws_bytes(self, m, n):
         """Workspace of the table-gradient pass for up to n samples.  In spatial order it holds the unmerged levels only, and
@@ -284,7 +285,8 @@ class TrainStep:
                 B.dg_order_samples(order, self.u[sl], N, self.ordered[sl], self.pieces[p], self.ws_order, ids)
         with self._timed("dg_hashgrid_encode_fwd"):
             if split:
-                B.dg_hashgrid_encode_fwd_split(m.grid, m.table, self.ordered[sl], self.u[sl], N, self._feat[sl], by_position=ids is not None)
+                B.dg_hashgrid_encode_fwd_bricks(m.grid, order, m.table, self.ordered[sl], self.pieces[p], self.u[sl], N, self._feat[sl],
+                                                by_position=ids is not None)
             elif order is not None:
                 B.dg_hashgrid_encode_fwd_ordered(m.grid, m.table, self.ordered[sl], N, self._feat[sl], by_position=ids is not None)
             else:

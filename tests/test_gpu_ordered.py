@@ -597,6 +597,33 @@ def test_split_features(key, N, n_app):
     assert not n_app or rel_err(host(results[1][5]), host(results[0][5])) <= 2.0 ** -24 * max(-(-N // 32), 1)
 
 
+@pytest.mark.parametrize("by_position", [False, True])
+@pytest.mark.parametrize("n_merged", [6, 8, 10, 12])
+@pytest.mark.parametrize("key,N", [(key, N) for key in ("flat", "cube", "upright") for N in (1, 513, 4097, 24007)])
+def test_features_brick_by_brick(key, N, n_merged, by_position):
+    """Levels gathered from a brick's vertices in LDS: samples on the bricks' faces and up to three roundings beside them, in corners of the box
+    and outside it, and one brick that holds several pieces."""
+    print("[case] features brick by brick", key, N, n_merged, by_position, flush=True)
+    q = CUTS[key]
+    growth = B.dg_growth_factor(16, q["n_max"], 16)
+    grid, ref_grid = (f(16, 2, q["log2_T"], 16, growth, q["extent"]) for f in (B.dg_grid_desc_init, oracle.grid_init))
+    order = B.dg_order_desc_init(grid, q["made_for"])
+    order.n_merged = min(n_merged, order.n_merged)
+    u = _beside_faces(order, N, np.random.default_rng(51))
+    u[:5] = np.asarray([[0, 0, 0], [1, 1, 1], [-0.3, 0.5, 2.0], [1, 0, 0.5], [0.99999994, 0.5, 0.0]], np.float32)[:N]
+    u[N // 2:] = (np.asarray([0.5, 0.3, 0.4]) + 4e-3 * (u[N // 2:] - 0.5)).astype(np.float32)          # half of them in one brick or two
+    ordered, pieces = torch.zeros(N, 4, device=DEV), torch.zeros(B.dg_order_pieces_words(order, N), dtype=torch.int32, device=DEV)
+    ud, table = dev(u), di.make_table(ref_grid.n_entries, 2, 1.0, seed=52)
+    B.dg_order_samples(order, ud, N, ordered, pieces, torch.zeros(B.dg_order_workspace_bytes(order) // 4, dtype=torch.int32, device=DEV))
+    feat = torch.full((N, 32), float("nan"), dtype=torch.float16, device=DEV)
+    B.dg_hashgrid_encode_fwd_bricks(grid, order, dev(table), ordered, pieces, ud, N, feat, by_position=by_position)
+    flat, n_rows = host(feat).reshape(-1), 2 * B.SPLIT_LEVELS * N
+    got = np.concatenate([flat[:n_rows].reshape(N, -1), flat[n_rows:].reshape(-1, N, 2).transpose(1, 0, 2).reshape(N, -1)], 1).astype(np.float64)
+    at = host(ordered)[:, 3].copy().view(np.uint32) if by_position else np.arange(N)
+    ref, bound = oracle.encode_fwd(ref_grid, table, u)[at], oracle.encode_fwd(ref_grid, table, u, abs_terms=True)[at]
+    assert np.all(np.abs(got - ref) <= 2.0 ** -11 * np.abs(ref) + 1e-5 * bound + 6e-8)          # as in test_ordered_encode
+
+
 @pytest.mark.parametrize("name", ["c2_ngp", "c3_2x2", "c8_app"])
 def test_step_with_split_features(name, monkeypatch):
     """The training step in spatial order with split features, through every comparison of the plain step; what a caller reads as
