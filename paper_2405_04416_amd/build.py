@@ -11,7 +11,7 @@ OBJ_DIR = os.path.join(HERE, "_build")
 LIB_PATH = os.path.join(HERE, "libdistgrid.so")
 PEAKS_PATH = os.path.join(HERE, "libdgpeaks.so")     # yardstick kernels of the benchmark, not part of the library
 
-SOURCES = ["host.hip", "segments.hip", "encode.hip", "encode_bwd_binned.hip", "encode_bwd_compact.hip", "order.hip", "encode_ordered.hip", "mlp.hip", "mlp_mfma.hip", "mlp_small.hip", "render.hip", "optim.hip", "occupancy.hip"]
+SOURCES = ["host.hip", "segments.hip", "encode.hip", "encode_bwd_binned.hip", "encode_bwd_fill.hip", "order.hip", "encode_ordered.hip", "mlp.hip", "mlp_mfma.hip", "mlp_small.hip", "render.hip", "optim.hip", "occupancy.hip"]
 COMMON = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-Wall", "-Wno-unused-function",
           # packed fp32 instructions are kept out of every kernel of this library
           "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",

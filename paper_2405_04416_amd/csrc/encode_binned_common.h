@@ -1,4 +1,4 @@
-// What the table-gradient passes that go through bins share: bins, plans of a sweep, the sweeps' look-ahead.  Internal, not part of the ABI.
+// What the parts of the table-gradient pass that goes through bins share: bins, plans of a sweep, queue lines.  Internal, not part of the ABI.
 #pragma once
 #include "encode_common.h"
 
@@ -9,11 +9,8 @@ using namespace dg_encode;
 constexpr int kChunkLog2 = 13;
 constexpr uint32_t kChunk = 1u << kChunkLog2;      // entries per bin
 constexpr int kMaxBins = 2048;                     // per level: 2^24 entries / 8192
-constexpr int kTile = 512;                         // samples per tile == threads per binning workgroup
-constexpr int kKeeper = 64;                        // narrow fill sweep: one more wavefront, which keeps the books of the 64 bins
-constexpr int kPairs = kTile * 4;                  // records staged per (tile, level): one per pair of corners along x
+constexpr int kTile = 512;                         // batches are multiples of this many samples
 constexpr uint32_t kMaxKeys = DG_MAX_LEVELS * kMaxBins;   // (level, bin) pairs at most: the count sweep keeps one counter each in LDS (128 KB)
-constexpr int kBinGrid = 768;                      // persistent binning workgroups (three per compute unit)
 constexpr int kAccBlock = 1024, kAccGrid = 256;    // threads of an accumulate workgroup (one per compute unit: its table fills LDS), compute units
 // An accumulate workgroup sums at least 2^piece_log2 records of a bin (or all it has) and fewer than twice as many: a bin is
 // cut into floor(records / 2^piece_log2) equal pieces, so a bin with less than two pieces' worth stays whole (a second
@@ -36,24 +33,31 @@ struct Plan {
     uint32_t n_keys;                       // (level, bin) pairs of the binned levels
     uint32_t key_base[DG_MAX_LEVELS + 1];  // first key of each level
     uint32_t n_bins[DG_MAX_LEVELS];
-    uint32_t max_bins;                     // of a level: rounded up to a multiple of 64, or a power of two where records are compact
-    uint32_t compact;                      // 0, or records of an append where records are compact (encode_bwd_compact.hip)
+    uint32_t max_bins;                     // of a level, rounded up to a power of two
+    uint32_t compact;                      // compact records
+    uint32_t per_unit;                     // workgroups of a sweep per compute unit: 1 or 2
 };
 
-// Queues of compact records: lines of 64 bytes, five records and a spare word.
-constexpr uint32_t kLineRecords = 5;
-constexpr int kCompactTile = 1024;                 // samples that a workgroup takes per step == its threads
-constexpr int kCompactGrid = 256;                  // persistent workgroups, one per compute unit: their rings fill LDS
-constexpr uint32_t kRingLinesLog2 = 11, kRingLines = 1u << kRingLinesLog2;
-constexpr uint64_t kCompactBatch = 1ull << 28;     // samples: their coordinates' offsets stay below 2^32 bytes
-inline size_t compact_lds(uint32_t max_bins) { return 64 * kRingLines + (max_bins * 13 + 16 + 15) / 16 * 16; }
+// Queues are lines of 64 bytes: four records, or five compact ones and a spare word.  The sweeps that fill them (encode_bwd_fill.hip):
+constexpr uint32_t kPairLine = 4, kCompactLine = 5;
+constexpr int kFillTile = 1024;                    // samples that a workgroup takes per step == its threads
+constexpr int kUnits = 256;                        // compute units, one or two persistent workgroups each, whose rings of lines fill LDS
+__host__ __device__ constexpr int ring_lines_log2(int per_unit) { return per_unit == 1 ? 11 : 10; }
+constexpr uint64_t kFillBatch = 0xffffffffull / 12 / kTile * kTile;         // samples: their coordinates' offsets stay below 2^32 bytes
+inline uint32_t line_records(const Plan &p) { return p.compact ? kCompactLine : kPairLine; }
+inline uint32_t append_lines(uint32_t max_bins) { return max_bins <= 512u ? 2u : 1u; }      // lines of an append: two where rings have at least four
+inline uint32_t slice_round(const Plan &p) { return line_records(p) * append_lines(p.max_bins); }       // a workgroup's slice of a bin is padded to this many records
+// Workgroups per compute unit.  A second one hides barriers and latency, but its rings are half as long and appends of two lines need two of them.
+// Merged records, whose arithmetic takes longer than the writes, fill pass in us with one / two: 8 sub-models, T = 2^19 and 2^22, 0.4 M samples each
+// 1402 / 1218, 80 k samples, T = 2^19 41.9 / 39.0 (four of 512 threads 49.7).  Compact ones are bound by the writes: T = 2^19, 13.3 M samples 751 / 808.
+inline uint32_t per_unit(const Plan &p) { return p.compact || p.max_bins > 512u ? 1u : 2u; }
+inline uint32_t fill_grid(const Plan &p) { return kUnits * p.per_unit; }
 
-void set_compact(Plan &p);                 // p.max_bins: of a level
-int reserve_compact();                     // sets the kernels' LDS limits; returns a hipError_t
+int reserve_fill();                        // sets the kernels' LDS limits; returns a hipError_t
 // the sweeps over samples [n0, n0 + nb)
-void count_compact(const dg_grid_desc *d, const Plan &p, const Sweep &sw, const float *u, uint64_t n0, uint64_t nb, uint32_t *rows, hipStream_t st);
-void fill_compact(const dg_grid_desc *d, const Plan &p, const Sweep &sw, const float *u, const float *dfeat, uint64_t N, uint64_t n0, uint64_t nb,
-                  const uint32_t *rows, uint32_t *binbase, void *queue, float *dtable, hipStream_t st);
+void count_records(const dg_grid_desc *d, const Plan &p, const Sweep &sw, const float *u, uint64_t n0, uint64_t nb, uint32_t *rows, hipStream_t st);
+void fill_queues(const dg_grid_desc *d, const Plan &p, const Sweep &sw, const float *u, const float *dfeat, uint64_t N, uint64_t n0, uint64_t nb,
+                 const uint32_t *rows, uint32_t *binbase, void *queue, float *dtable, hipStream_t st);
 
 template <int CTRL, int ROW_MASK>
 __device__ __forceinline__ void scan_step(uint32_t &v)
@@ -73,30 +77,7 @@ __device__ __forceinline__ uint32_t wave_inclusive_scan(uint32_t v)
     return v;
 }
 
-// inclusive running maximum over the wavefront, same moves (a lane that receives nothing takes 0)
-__device__ __forceinline__ uint32_t wave_inclusive_max(uint32_t v)
-{
-#define DG_MAX_STEP(CTRL, ROW_MASK) v = max(v, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, CTRL, ROW_MASK, 0xF, true))
-    DG_MAX_STEP(0x111, 0xF); DG_MAX_STEP(0x112, 0xF); DG_MAX_STEP(0x114, 0xF); DG_MAX_STEP(0x118, 0xF);
-    DG_MAX_STEP(0x142, 0xA); DG_MAX_STEP(0x143, 0xC);
-#undef DG_MAX_STEP
-    return v;
-}
-
 __device__ __forceinline__ uint32_t lane_value(uint32_t v, uint32_t lane) { return (uint32_t)__builtin_amdgcn_readlane((int)v, (int)lane); }
-
-struct StepAhead {
-    float u[3];
-    float2 g;
-};
-
-__device__ __forceinline__ void load_ahead(StepAhead &a, const float *__restrict__ u, const float2 *__restrict__ dfeat, uint64_t N,
-                                           uint64_t n0, uint64_t nb, uint64_t tile, uint32_t l, uint32_t tid)
-{
-    const uint64_t rel = tile * kTile + tid, n = n0 + (rel < nb ? rel : nb - 1);
-    a.u[0] = u[3 * n]; a.u[1] = u[3 * n + 1]; a.u[2] = u[3 * n + 2];
-    a.g = dfeat[(size_t)l * N + n];
-}
 
 // largest over the workgroup -> *dst (one atomic per workgroup); `word` is an LDS word nobody else uses any more
 __device__ __forceinline__ void publish_largest(uint32_t largest, uint32_t *word, uint32_t *__restrict__ dst)

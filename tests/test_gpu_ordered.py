@@ -359,6 +359,31 @@ def test_unmerged_levels_of_every_table_size(log2_T, flavour):
             assert off <= 1.2e-6 * np.linalg.norm(want[sl]), l
 
 
+@pytest.mark.parametrize("flavour", FLAVOURS)
+@pytest.mark.parametrize("log2_T", [14, 20, 22, 23, 24])
+def test_ray_order_queues_of_every_table_size(log2_T, flavour):
+    """The same sizes for samples in the order of their rays: records of merged runs, four in a line, and rings of half as many lines for up to 512
+    bins."""
+    print("[case] ray order", log2_T, flavour, flush=True)
+    growth = B.dg_growth_factor(16, 1024, 16)
+    grid, ref_grid = (f(16, 2, log2_T, 16, growth, [1.0, 0.9, 0.5]) for f in (B.dg_grid_desc_init, oracle.grid_init))
+    N = 150001
+    u = _coords(N, flavour)
+    g = (np.random.default_rng(51).standard_normal((N, 32)) * 1e-3).astype(np.float32)
+    g[5::11] = 0.0
+    gd = dev(np.ascontiguousarray(g.reshape(N, 16, 2).transpose(1, 0, 2)))
+    dtable = torch.zeros(ref_grid.n_entries, 2, device=DEV)
+    ws = torch.full((B.dg_hashgrid_encode_bwd_workspace_bytes(grid, N) // 4 + 64,), float("nan"), device=DEV)
+    B.dg_hashgrid_encode_bwd(grid, dev(u), gd, N, dtable, ws)
+    want, have = oracle.encode_bwd(ref_grid, u, g.astype(np.float64)), host(dtable).astype(np.float64)
+    scale = oracle.encode_bwd(ref_grid, u, np.abs(g).astype(np.float64))
+    for l in range(16):
+        # a contribution is four fp32 roundings deep, a run of up to 64 adds six more, a record rounds to 2^-19 at most, and the bin's flush to fp32
+        sl = slice(ref_grid.first[l], ref_grid.first[l + 1])
+        assert np.all(have[sl][want[sl] == 0] == 0), l
+        assert np.linalg.norm(have[sl] - want[sl]) <= (2.0 ** -19 + 14 * 2.0 ** -24) * np.linalg.norm(scale[sl]), l
+
+
 @pytest.mark.parametrize("N,log2_T,n_max", [((1 << 22) + 77, 19, 2048), ((1 << 21) + 5, 22, 8192)])
 def test_ordered_gradient_at_full_size(N, log2_T, n_max):
     """A batch of production size, level by level and entry by entry against the pass in ray order on the same gradient."""

@@ -254,10 +254,9 @@ def test_encode_bwd(key, N, flavour, mode):
     assert np.all(got[ref == 0] == 0)                                 # untouched entries stay untouched
 
 
-# The binned pass runs 768 persistent workgroups over tiles of 512 samples.  The cases above give a workgroup one tile per
-# level at most; these give it several, element by element against the oracle: records that wait for a full granule
-# from one step to the next and the two halves of the waiting slots (narrow sweep, c2), queue cursors that advance step
-# after step (sweep for many bins: wide, huge), bins whose records are split over several accumulating workgroups
+# The binned pass runs 256 or 512 persistent workgroups over tiles of 1024 samples.  The cases above give a workgroup one tile per
+# level at most; these give it several, element by element against the oracle: records that wait in LDS for a full unit of lines
+# from one step to the next (c2), rings of one line (wide, huge), bins whose records are split over several accumulating workgroups
 # (dense_odd_many with all samples in the layers that one bin of each level covers, in one batch and in two), a bin that is
 # summed directly (one_bin), and a capped workspace that makes two batches of two tiles per workgroup each.
 STEADY = 2 * 768 * 512
