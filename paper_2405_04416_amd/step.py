@@ -155,14 +155,14 @@ class TrainStep:
         """Samples of a sub-model from which on a training step puts them in spatial order.  The kernels for ordered samples serve
         the 16-level grid with the 32-64-16 / 64-64-3 networks.  The order pays once the samples lie densely enough to share
         table lines and cells.  Whole step, plain / ordered in us; what the lines below lie between:
-        T = 2^17 739 / 808 at 0.81 M samples, 1050 / 1006 at 1.22 M, 1279 / 1244 at 1.63 M.  T = 2^18 990 / 994 at 1.22 M, 1290 / 1272 at 1.63 M.
-        T = 2^19 1137 / 1028 against 1062 at 1.22 M and 1419 / 1277 against 1362 at 1.63 M, where the features are and are not split: the line stays
-        where the ordered gather breaks even without that, 1.65 / 1.70 ms at 2.10 M, 1.87 / 1.86 at 2.33 M.  T = 2^20 661 / 676 at 0.50 M, 911 / 873 at 0.81 M; oblique rays 2183 / 2205 with
-        four sub-models of 0.40 M, 3679 / 3275 of 0.80 M.
-        Larger tables, finest level of 2048 cells along the box: T = 2^21 685 / 713 at 0.41 M, 850 / 830 at 0.62 M; T = 2^22 739 / 754 at 0.41 M,
-        989 / 999 at 0.61 M, oblique 2855 / 2812 with four of 0.40 M, 4842 / 4156 of 0.79 M.  With 8192 cells samples share less: T = 2^21
-        797 / 790 at 0.44 M, 1058 / 1054 at 0.69 M, 1390 / 1336 at 1.0 M; T = 2^22 863 / 878 at 0.44 M, 1302 / 1261 at 0.69 M; T = 2^24 1898 / 1897 at
-        0.44 M, 2115 / 2095 at 0.69 M.
+        T = 2^17 644 / 721 at 0.83 M samples, 969 / 960 at 1.30 M.  T = 2^18 899 / 942 at 1.25 M, 1160 / 1137 at 1.66 M.  T = 2^19 1197 / 1217 at 1.66 M,
+        1720 / 1522 at 2.48 M; the line stays where the ordered gather breaks even by itself, 1.65 / 1.70 ms at 2.10 M.  T = 2^20 757 / 824 at 0.83 M,
+        1039 / 1083 at 1.26 M, 1324 / 1328 at 1.68 M, but oblique rays, whose neighbours share less, with four sub-models 2069 / 2260 of 0.40 M, 2729 / 2723 of 0.61 M,
+        3432 / 3228 of 0.81 M.
+        Larger tables, finest level of 2048 cells along the box: T = 2^21 757 / 799 at 0.65 M, 1174 / 1191 at 1.25 M, 1466 / 1459 at 1.67 M, oblique 2437 / 2617 with four
+        of 0.40 M, 3241 / 3155 of 0.61 M; T = 2^22 754 / 780 at 0.49 M, 893 / 907 at 0.65 M, 1164 / 1133 at 0.98 M, oblique 3049 / 3030 with four of 0.41 M, 3842 / 3593 of
+        0.61 M.  With 8192 cells samples share less: T = 2^21 845 / 900 at 0.64 M, 1121 / 1136 at 0.96 M; T = 2^22 875 / 928 at 0.48 M, 1209 / 1210 at 0.81 M;
+        T = 2^23 1159 / 1163 at 0.48 M, 1531 / 1488 at 0.81 M; T = 2^24 1467 / 1500 at 0.49 M, 1709 / 1676 at 0.65 M.
         Occupancy-guided samples lie on surfaces, ten times as densely: T = 2^18 673 / 678 at 0.56 M, 901 / 847 at 0.79 M; T = 2^19 704 / 707 and
         920 / 855; T = 2^20 539 / 537 at 0.28 M, 815 / 760 at 0.56 M; with cells four times as wide T = 2^19 1893 / 1715 at 2.2 M."""
         if m.grid.n_levels != 16 or (m.mlp.n_feat, m.mlp.n_hidden_d, m.mlp.n_layers_c) != (32, 64, 2):
@@ -235,7 +235,7 @@ class TrainStep:
 
         def order(k):
             if k not in orders:
-                orders[k] = B.dg_order_desc_init(m.grid, k)
+                orders[k] = self._order_desc(m, k)
             return orders[k]
 
         def need(k):
@@ -260,8 +260,23 @@ class TrainStep:
         where the plain kernels serve it (also where not even the two coarsest levels of a grid fit LDS brick by brick)."""
         if self.ordered is None or N < self._order_min(m) * self._order_factor(m, use):
             return None
-        order = B.dg_order_desc_init(m.grid, N)
+        order = self._order_desc(m, N, use)
         return order if order.n_merged > 0 else None
+
+    def _order_desc(self, m, N, use="step"):
+        """The bricks of a batch of N samples.  Their number, and how many levels are merged brick by brick, follow the number of samples as if these
+        filled the box evenly.  Occupancy-guided samples lie on surfaces: bricks that hold some hold several times as many, and are cut as for 3 N
+        samples.  Whole step in us at 1, 2, 3, 4 N: T = 2^18 3477, 3458, 3293, 3327 at 5.9 M; T = 2^19 1207, 1130, 1121, 1140 at 1.5 M, 3500, 3448, 3337, 3351 at
+        5.9 M, 6727, 6274, 6310, 6319 at 11.7 M; T = 2^22 1401, 1302, 1305, 1319 at 1.5 M; T = 2^24 2213, 2109, 2115, 2101 at 1.9 M; but T = 2^17 1425, 1430,
+        1442, 1443 at 2.2 M.  With tables of a few of an XCD's L2 the ninth and tenth level are cheaper merged from fewer samples on: at 1, 1.4, 2 N T = 2^21 1519, 1459, 1450 at
+        1.7 M, 2400, 2412, 2394 at 3.3 M; T = 2^22 1625, 1535, 1534 at 1.7 M, 9647, 9688, 9757 with four sub-models of 3.2 M; T = 2^23 3562, 3621, 3602 at 3.3 M; T = 2^19 1915, -, 1967 at 3.3 M."""
+        T = m.grid.log2_T
+        factor = 1.0
+        if self.occ is not None and use != "refresh":
+            factor = 3.0 if T >= 18 else 1.0
+        elif use != "refresh" and T in (21, 22):
+            factor = max(1.0, min(1.4, (1 << 21) / max(N, 1)))
+        return B.dg_order_desc_init(m.grid, int(N * factor))
 
     def _grown(self, buf, words):
         """buf if it holds that many words, otherwise a larger one.  The old one may have been allocated on another stream

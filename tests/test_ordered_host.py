@@ -100,3 +100,23 @@ def test_lines_of_the_order(log2_T, n_max):
         for T, finest, what, N in faster_in_ray_order:
             if (T, finest, what) == (log2_T, n_max, use):
                 assert step._order_of(m, N, use) is None, N
+
+
+@pytest.mark.parametrize("log2_T,occ,use,factor", [(17, True, "step", 1.0), (18, True, "step", 3.0), (24, True, "render", 3.0), (19, True, "refresh", 1.0),
+                                                   (20, False, "step", 1.0), (21, False, "step", 1.4), (22, False, "render", 1.4), (22, False, "refresh", 1.0),
+                                                   (23, False, "step", 1.0)])
+def test_bricks_follow_the_density_of_the_samples(log2_T, occ, use, factor):
+    """The bricks are those of the stated multiple of the samples, and the table-gradient workspace that a capacity gets serves every smaller batch."""
+    m = types.SimpleNamespace(grid=B.dg_grid_desc_init(16, 2, log2_T, 16, B.dg_growth_factor(16, 2048, 16), [2.0, 2.0, 0.25]),
+                              mlp=B.dg_mlp_desc(32, 64, 16, 16, 64, 2, 1))
+    step = object.__new__(TrainStep)
+    step.occ, step.ordered = {} if occ else None, True
+    most = 6000000
+    for N in (most, 4000001, 1999999, 1400003):
+        if N >= step._order_min(m) * step._order_factor(m, use):
+            many = max(N, min(int(N * factor), 1 << 21)) if factor == 1.4 else int(N * factor)
+            assert bytes(step._order_of(m, N, use)) == bytes(B.dg_order_desc_init(m.grid, many))
+    if use == "step":
+        room = step._encode_ws_bytes(m, most)
+        for N in range(int(step._order_min(m)), most, 99991):
+            assert B.dg_hashgrid_encode_bwd_ordered_workspace_bytes(m.grid, step._order_of(m, N), N) <= room, N
