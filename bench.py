@@ -33,11 +33,11 @@ LINE_BYTES = 128               # what one L2 miss fetches
 # over the kernels an entry point launches: (fetched, written).  Measured once per workload with the kernels as they
 # stand; the runs, their commands and the calibration are in profiles/<workload>_hbm_traffic.md.
 MEASURED_TRAFFIC_BYTES = {
-    "c5_share": {"dg_hashgrid_encode_fwd": (113.0e9, 4.635e9), "dg_hashgrid_encode_bwd": (53.92e9, 30.96e9), "dg_mlp_fwd": (4.368e9, 1.074e9),
+    "c5_share": {"dg_hashgrid_encode_fwd": (116.1e9, 4.606e9), "dg_hashgrid_encode_bwd": (49.66e9, 23.61e9), "dg_mlp_fwd": (4.368e9, 1.074e9),
                  "dg_mlp_bwd": (11.9e9, 10.76e9)},
-    "c4_big": {"dg_hashgrid_encode_fwd": (45.94e9, 1.426e9), "dg_hashgrid_encode_bwd": (12.86e9, 10.21e9), "dg_mlp_fwd": (1.294e9, 0.317e9),
+    "c4_big": {"dg_hashgrid_encode_fwd": (45.98e9, 1.416e9), "dg_hashgrid_encode_bwd": (11.52e9, 8.048e9), "dg_mlp_fwd": (1.294e9, 0.317e9),
                "dg_mlp_bwd": (3.531e9, 3.188e9)},
-    "c2_ngp": {"dg_hashgrid_encode_fwd": (8.701e9, 0.907e9), "dg_hashgrid_encode_bwd": (6.671e9, 4.082e9), "dg_mlp_fwd": (0.868e9, 0.214e9),
+    "c2_ngp": {"dg_hashgrid_encode_fwd": (8.568e9, 0.892e9), "dg_hashgrid_encode_bwd": (6.133e9, 3.522e9), "dg_mlp_fwd": (0.868e9, 0.214e9),
                "dg_mlp_bwd": (2.382e9, 2.155e9)},
 }
 

@@ -43,7 +43,6 @@ constexpr uint32_t kPairLine = 4, kCompactLine = 5;
 constexpr int kFillTile = 1024;                    // samples that a workgroup takes per step == its threads
 constexpr int kUnits = 256;                        // compute units, one or two persistent workgroups each, whose rings of lines fill LDS
 __host__ __device__ constexpr int ring_lines_log2(int per_unit) { return per_unit == 1 ? 11 : 10; }
-constexpr uint64_t kFillBatch = 0xffffffffull / 12 / kTile * kTile;         // samples: their coordinates' offsets stay below 2^32 bytes
 inline uint32_t line_records(const Plan &p) { return p.compact ? kCompactLine : kPairLine; }
 inline uint32_t append_lines(uint32_t max_bins) { return max_bins <= 512u ? 2u : 1u; }      // lines of an append: two where rings have at least four
 inline uint32_t slice_round(const Plan &p) { return line_records(p) * append_lines(p.max_bins); }       // a workgroup's slice of a bin is padded to this many records

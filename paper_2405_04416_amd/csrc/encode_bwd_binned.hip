@@ -502,8 +502,7 @@ uint64_t max_batch(const dg_grid_desc *d, const Plan &p)
 {
     const uint64_t per_sample = 4ull * (d->n_levels - p.first_level);
     if (per_sample == 0) return ~0ull;
-    const uint64_t batch = ((0xffffffffull - slice_padding(p) - 80ull) / per_sample) / kTile * kTile;           // record offsets stay below 2^32
-    return std::min(batch, kFillBatch);
+    return ((0xffffffffull - slice_padding(p) - 80ull) / per_sample) / kTile * kTile;           // record offsets stay below 2^32
 }
 
 }  // namespace dg_encode_binned

@@ -305,12 +305,12 @@ fill_kernel(dg_grid_desc g, Plan plan, Sweep sw, const float *__restrict__ u, co
     uint32_t largest = 0;                                             // bits of the largest magnitude; infinity or more where a gradient is not a number
     const uint32_t n_tiles = (nb + kFillTile - 1u) / kFillTile;
     StepAhead ahead = {{0.0f, 0.0f, 0.0f}, make_float2(0.0f, 0.0f)};
-    // 12 and 8 bytes a sample: below 2^32 for the samples of a batch
+    // the tile's addresses are the same for all lanes, a lane's offset in it fits 32 bits
     auto load = [&](uint32_t tile, uint32_t l) {
-        const uint32_t n = min(tile * kFillTile + tid, nb - 1u);
-        const float *at = reinterpret_cast<const float *>(reinterpret_cast<const char *>(u) + n * 12u);
+        const uint32_t n = min(tid, nb - 1u - tile * kFillTile);
+        const float *at = reinterpret_cast<const float *>(reinterpret_cast<const char *>(u + (size_t)tile * (3 * kFillTile)) + n * 12u);
         ahead.u[0] = at[0]; ahead.u[1] = at[1]; ahead.u[2] = at[2];
-        ahead.g = *reinterpret_cast<const float2 *>(reinterpret_cast<const char *>(dfeat + (size_t)l * N) + n * 8u);
+        ahead.g = *reinterpret_cast<const float2 *>(reinterpret_cast<const char *>(dfeat + (size_t)l * N + (size_t)tile * kFillTile) + n * 8u);
     };
     const bool has_work = me < n_tiles && first_level < g.n_levels;
     if (has_work) load(me, first_level);
