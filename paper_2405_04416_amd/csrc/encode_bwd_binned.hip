@@ -446,7 +446,12 @@ Sweep choose_sweep(const Plan &p, uint32_t n_levels, uint64_t nb)
     }
     return best;
 }
-uint64_t slice_padding(const Plan &p) { return (uint64_t)fill_grid(p) * p.n_keys * (slice_round(p) - 1u); }
+// Zero records that fill up the slices of nb samples, at most: a workgroup without a tile has no records and no slice.  (A level of 512 bins is
+// 512 workgroups' appends of 128 bytes, 29 MB of padding a level where all have tiles, 57 KB where one tile is all a workspace has room for.)
+uint64_t slice_padding(const Plan &p, uint64_t nb)
+{
+    return std::min<uint64_t>(fill_grid(p), (nb + kFillTile - 1) / kFillTile) * p.n_keys * (slice_round(p) - 1u);
+}
 
 uint32_t piece_log2(uint64_t records)
 {
@@ -477,11 +482,14 @@ bool sparse_bins(const Plan &p, uint32_t n_levels, uint64_t nb)
     return p.n_keys >= 2048u;
 }
 
+// records that nb samples make at most, with the padding of the slices
+uint64_t batch_records(const Plan &p, uint32_t n_levels, uint64_t nb) { return nb * 4ull * (n_levels - p.first_level) + slice_padding(p, nb); }
+
 // workspace layout for a batch of `batch` samples
 Layout make_layout(const dg_grid_desc *d, const Plan &p, uint64_t batch)
 {
     Layout L{};
-    const uint64_t records = (batch * 4ull * (d->n_levels - p.first_level) + slice_padding(p) + 79ull) / 80ull * 80ull;
+    const uint64_t records = (batch_records(p, d->n_levels, batch) + 79ull) / 80ull * 80ull;
     size_t off = 0;
     L.rows = off; off = align256(off + (size_t)fill_grid(p) * p.n_keys * 4);
     L.totals = off; off = align256(off + (size_t)p.n_keys * 4);
@@ -495,14 +503,11 @@ Layout make_layout(const dg_grid_desc *d, const Plan &p, uint64_t batch)
     return L;
 }
 
-// records that nb samples make at most, with the padding of the slices
-uint64_t batch_records(const Plan &p, uint32_t n_levels, uint64_t nb) { return nb * 4ull * (n_levels - p.first_level) + slice_padding(p); }
-
 uint64_t max_batch(const dg_grid_desc *d, const Plan &p)
 {
     const uint64_t per_sample = 4ull * (d->n_levels - p.first_level);
     if (per_sample == 0) return ~0ull;
-    return ((0xffffffffull - slice_padding(p) - 80ull) / per_sample) / kTile * kTile;           // record offsets stay below 2^32
+    return ((0xffffffffull - slice_padding(p, ~0ull / 2) - 80ull) / per_sample) / kTile * kTile;           // record offsets stay below 2^32
 }
 
 }  // namespace dg_encode_binned

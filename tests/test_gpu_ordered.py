@@ -384,6 +384,36 @@ def test_ray_order_queues_of_every_table_size(log2_T, flavour):
         assert np.linalg.norm(have[sl] - want[sl]) <= (2.0 ** -19 + 14 * 2.0 ** -24) * np.linalg.norm(scale[sl]), l
 
 
+@pytest.mark.parametrize("spatial", [False, True])
+@pytest.mark.parametrize("log2_T,n_max,room", [(20, 2048, 18933760), (22, 2048, 64 << 20), (22, 8192, 64 << 20)])
+def test_gradient_through_a_small_workspace(log2_T, n_max, room, spatial):
+    """Levels of 128 and of 512 bins in less room than all workgroups' slices of them would take up with their last lines alone: batches, the last
+    one partly filled, against the sums of one batch."""
+    print("[case] small workspace", log2_T, n_max, room, spatial, flush=True)
+    growth = B.dg_growth_factor(16, n_max, 16)
+    grid, ref_grid = (f(16, 2, log2_T, 16, growth, [2.0, 2.0, 0.25]) for f in (B.dg_grid_desc_init, oracle.grid_init))
+    N = 150001
+    u = _coords(N, "points")
+    order, ordered, pieces = _sorted(grid, u, N)
+    M = order.n_merged if spatial else 0
+    g = (np.random.default_rng(52).standard_normal((N, 32)) * 1e-3).astype(np.float32)
+    gd = dev(_mixed(g, M))
+    dtable, ws = torch.zeros(ref_grid.n_entries, 2, device=DEV), torch.full((room // 4,), float("nan"), device=DEV)
+    if spatial:
+        assert room < B.dg_hashgrid_encode_bwd_ordered_workspace_bytes(grid, order, N)
+        B.dg_hashgrid_encode_bwd_ordered(grid, order, ordered, pieces, dev(u), gd, gd.abs().max().reshape(1).view(torch.int32), N, dtable, ws)
+    else:
+        assert room < B.dg_hashgrid_encode_bwd_workspace_bytes(grid, N)
+        B.dg_hashgrid_encode_bwd(grid, dev(u), gd, N, dtable, ws)
+    want, have = oracle.encode_bwd(ref_grid, u, g.astype(np.float64)), host(dtable).astype(np.float64)
+    scale = oracle.encode_bwd(ref_grid, u, np.abs(g).astype(np.float64))
+    for l in range(16):
+        # as for one batch (test_ray_order_queues_of_every_table_size), and each of up to sixteen batches adds to an entry in fp32
+        sl = slice(ref_grid.first[l], ref_grid.first[l + 1])
+        assert np.all(have[sl][want[sl] == 0] == 0), l
+        assert np.linalg.norm(have[sl] - want[sl]) <= (2.0 ** -19 + 30 * 2.0 ** -24) * np.linalg.norm(scale[sl]), l
+
+
 @pytest.mark.parametrize("N,log2_T,n_max", [((1 << 22) + 77, 19, 2048), ((1 << 21) + 5, 22, 8192)])
 def test_ordered_gradient_at_full_size(N, log2_T, n_max):
     """A batch of production size, level by level and entry by entry against the pass in ray order on the same gradient."""

@@ -120,3 +120,26 @@ def test_bricks_follow_the_density_of_the_samples(log2_T, occ, use, factor):
         room = step._encode_ws_bytes(m, most)
         for N in range(int(step._order_min(m)), most, 99991):
             assert B.dg_hashgrid_encode_bwd_ordered_workspace_bytes(m.grid, step._order_of(m, N), N) <= room, N
+
+
+# Bytes that the table-gradient pass has been content with since its queues exist: T = 2^14 .. 2^24, finest level of 2048 and of 8192 cells; samples
+# in ray order and in spatial order with the bricks of 2^20 and of 2^25 samples.
+SMALLEST_WORKSPACE = {
+    2048: [(2759680, 3085568, 3290112), (4898304, 5536768, 6077184), (8819200, 9961216, 11172864), (16037120, 17867776, 20422144),
+           (29493504, 32284672, 37524480), (54890240, 50903040, 27959296), (15419136, 18933760, 11974656), (27741440, 31256064, 18802688),
+           (50199552, 53713920, 32458752), (91167744, 94682112, 59770880), (159821056, 163335936, 114395136)],
+    8192: [(2970624, 3098880, 3303424), (5287424, 5544448, 6084864), (9564928, 10157824, 11369216), (17674496, 18673920, 21228288),
+           (33357824, 35028992, 40268800), (62140928, 59350528, 36406784), (18145536, 19295232, 12429824), (33508608, 34658304, 22671872),
+           (62795008, 63944448, 43155968), (117419264, 118568704, 84124160), (217825536, 218975232, 166060544)],
+}
+
+
+@pytest.mark.parametrize("n_max", [2048, 8192])
+@pytest.mark.parametrize("log2_T", range(14, 25))
+def test_smallest_workspace(log2_T, n_max):
+    """A workspace in which a call could run in batches stays one: what one tile of 512 samples needs is the least that is accepted."""
+    grid = B.dg_grid_desc_init(16, 2, log2_T, 16, B.dg_growth_factor(16, n_max, 16), [2.0, 2.0, 0.25])
+    orders = [B.dg_order_desc_init(grid, N) for N in (1 << 20, 1 << 25)]
+    least = [B.dg_hashgrid_encode_bwd_workspace_bytes(grid, 512)] + [B.dg_hashgrid_encode_bwd_ordered_workspace_bytes(grid, q, 512) for q in orders]
+    for have, most in zip(least, SMALLEST_WORKSPACE[n_max][log2_T - 14]):
+        assert 0 < have <= most
