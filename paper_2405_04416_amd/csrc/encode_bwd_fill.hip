@@ -16,7 +16,7 @@
 // (T = 2^19, 13.3 M samples, levels 12..15: 4 % of the lanes; T = 2^24, levels 10..15: 1 %), so nothing is merged, and what a pair of corners along x gets
 // is one gradient times the weights 1 - fx and fx.  A record is 12 bytes (struct Compact): where the sums of corner 0 lie in its bin's table (14 bits),
 // how corner 1's entry differs (4 bits), the two gradient values times their y and z weights (27-bit floats, as in the other queues) and fx in units of
-// 2^-23 (24 bits: exact but for the first cell along x).  Five records and a spare word make a queue line of 64 bytes.
+// 2^-23 (24 bits: exact but for the first cell along x, see values).  Five records and a spare word make a queue line of 64 bytes.
 // Bound by the writes: T = 2^19, 13.3 M samples, 4 levels 0.75 ms, 57 G lines/s (records of 16 bytes sorted in LDS: 0.88); four sub-models, T = 2^22,
 // 13 M samples, 6 levels 1.31 ms (granules of four 16-byte records: 2.14);
 // T = 2^24, 33.5 M samples, 6 levels 4.43 ms (6.10).  Measured on the way, T = 2^19: a ring per wavefront, without barriers, nine wavefronts per
@@ -39,7 +39,7 @@ namespace dg_encode_binned {
 // bits: the two differ in their k low bits, all of them -- x and x + 1 do, and both index forms keep that: a sum of
 // x with multiples of the resolution, or an exclusive-or of x with hashes of y and z) and the pair's four values as
 // 27-bit floats (sign, 8 exponent bits, 18 mantissa bits: fp32 rounded to nearest at bit 5, relative error at most
-// 2^-20 per value, the same for both signs).  Four of them make a queue line of 64 bytes.  (With 20-byte records of fp32 values, probes
+// 2^-19 per value, the same for both signs).  Four of them make a queue line of 64 bytes.  (With 20-byte records of fp32 values, probes
 // of the store side alone measured 3.0 ms for 9.1 GB appended as it comes and 1.8 ms in whole lines.)
 // k such that eb == ea ^ (2^k - 1), or 15 when the two do not differ that way (ea, eb < 2^13)
 __device__ __forceinline__ uint32_t pair_code(uint32_t ea, uint32_t eb)
@@ -184,8 +184,8 @@ struct Compact {
         return live;
     }
     __device__ __forceinline__ uint32_t entry(int p) const { return e[p]; }
-    // A pair's entries may lie in different bins or halves of one (one in thousands): its corner 1 then goes to the table directly, and the
-    // record's second entry is corner 0 again, whose value the record's two shares add up to
+    // A pair's entries may lie in different bins or halves of one (one in thousands), or the x fraction may not fit the record: corner 1 then
+    // goes to the table directly, and the record's second entry is corner 0 again, whose value the record's two shares add up to
     __device__ __forceinline__ void apart(int p, uint32_t other, const LevelGeom &lv, float *__restrict__ dtable)
     {
         float *dst = dtable + 2 * ((size_t)lv.offset + other);
@@ -207,23 +207,27 @@ struct Compact {
         }
         largest = max(largest, __float_as_uint(most));
         if (gfe.x != gfe.x || gfe.y != gfe.y) largest = 0x7fc00000u;                  // fmaxf passes over NaN
+        // In a level's first cell along x fractions have more bits than units of 2^-23 can say; rounded, next to a face of the cell a share
+        // would lose all of them.  One sample in hundreds: ordered pass, 13.3 M samples, T = 2^19 2.593 / 2.591 ms without and with this, 3.3 M 780 / 795 us.
+        const float units = frac[0] * 0x1p23f;
+        fx = (uint32_t)(units + 0.5f);
+        const bool finer = units != (float)fx;
         codes = 0u;
         if (lv.dense) {
 #pragma unroll
             for (int p = 0; p < 4; ++p) {
                 const uint32_t differ = e[p] ^ (e[p] + 1u);
-                if (differ < kChunk / 2) codes |= (uint32_t)__popc(differ) << (14 + 4 * p);
+                if (differ < kChunk / 2 && !finer) codes |= (uint32_t)__popc(differ) << (14 + 4 * p);
                 else if (live) apart(p, e[p] + 1u, lv, dtable);
             }
         } else {
             const uint32_t differ = (x ^ (x + 1u)) & mask;
-            if (differ < kChunk / 2) codes = (uint32_t)__popc(differ) * 0x4444000u;
+            if (differ < kChunk / 2 && !finer) codes = (uint32_t)__popc(differ) * 0x4444000u;
             else if (live) {
 #pragma unroll
                 for (int p = 0; p < 4; ++p) apart(p, e[p] ^ differ, lv, dtable);
             }
         }
-        fx = (uint32_t)(frac[0] * 8388608.0f + 0.5f);
     }
     __device__ __forceinline__ Record record(int p, const LevelGeom &, float *) const
     {
