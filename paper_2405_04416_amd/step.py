@@ -255,25 +255,39 @@ class TrainStep:
         ends = [k for a, b in zip(sizes, sizes[1:]) for k in last_before_changes(a, b)]
         return max(B.dg_hashgrid_encode_bwd_workspace_bytes(m.grid, least), *(need(k) for k in ends + [n]))
 
-    def _order_of(self, m, N, use="step"):
+    def _order_of(self, m, N, use="step", full=False):
         """Order descriptor of a batch of N samples for a training step ("step"), a rendering or an occupancy refresh, or None
-        where the plain kernels serve it (also where not even the two coarsest levels of a grid fit LDS brick by brick)."""
+        where the plain kernels serve it (also where not even the two coarsest levels of a grid fit LDS brick by brick).
+        full: occupancy-guided samples that fill the box (_fill_the_box)."""
         if self.ordered is None or N < self._order_min(m) * self._order_factor(m, use):
             return None
-        order = self._order_desc(m, N, use)
+        order = self._order_desc(m, N, use, full)
+        # fewer merged levels need more room in the table-gradient pass, whose workspace is made for those of thin samples
+        if full and use == "step" and B.dg_hashgrid_encode_bwd_ordered_workspace_bytes(m.grid, order, N) > self.ws_enc.numel() * self.ws_enc.element_size():
+            order = self._order_desc(m, N, use)
         return order if order.n_merged > 0 else None
 
-    def _order_desc(self, m, N, use="step"):
+    def _fill_the_box(self, p, N, n_seg):
+        """Whether N occupancy-guided samples of n_seg segments lie all over partition p's box, as with a grid that has not been thinned out yet,
+        and not on surfaces: they take up more than a third of the length that as many chords of the box have on average (four times its volume over
+        its surface; a full grid of 512 x 512 x 64 cells under a camera 0.64 of it, one of which half the layers are set 0.32, surfaces 0.05)."""
+        ext = [hi - lo for lo, hi in zip(self.parts_host[p][:3], self.parts_host[p][3:])]
+        chord = 2.0 / sum(1.0 / e for e in ext)
+        return 3.0 * N * self.occ[p].dt > n_seg * chord
+
+    def _order_desc(self, m, N, use="step", full=False):
         """The bricks of a batch of N samples.  Their number, and how many levels are merged brick by brick, follow the number of samples as if these
         filled the box evenly.  Occupancy-guided samples lie on surfaces: bricks that hold some hold several times as many, and are cut as for 3 N
         samples.  Whole step in us at 1, 2, 3, 4 N: T = 2^18 3477, 3458, 3293, 3327 at 5.9 M; T = 2^19 1207, 1130, 1121, 1140 at 1.5 M, 3500, 3448, 3337, 3351 at
         5.9 M, 6727, 6274, 6310, 6319 at 11.7 M; T = 2^22 1401, 1302, 1305, 1319 at 1.5 M; T = 2^24 2213, 2109, 2115, 2101 at 1.9 M; but T = 2^17 1425, 1430,
-        1442, 1443 at 2.2 M.  With tables of a few of an XCD's L2 the ninth and tenth level are cheaper merged from fewer samples on: at 1, 1.4, 2 N T = 2^21 1519, 1459, 1450 at
+        1442, 1443 at 2.2 M.  Down from grids of which half the layers are set 3 N is the best or within 0.5 % of it.  Guided samples that fill the box (full) are cut as for
+        1.5 N; at 1, 1.5, 3 N: T = 2^18 1437, 1429, 1459 at 2.0 M, 3485, 3484, 3646 at 6.0 M; T = 2^19 1295, 1243, 1254 at 1.6 M, 2055, 2065, 2090 at 3.0 M; T = 2^20
+        1550, 1534, 1587 at 2.0 M; T = 2^22 1724, 1713, 1782 at 2.0 M, 2340, 2324, 2402 at 3.0 M; T = 2^24 2329, 2315, 2396 at 2.0 M.  With tables of a few of an XCD's L2 the ninth and tenth level are cheaper merged from fewer samples on: at 1, 1.4, 2 N T = 2^21 1519, 1459, 1450 at
         1.7 M, 2400, 2412, 2394 at 3.3 M; T = 2^22 1625, 1535, 1534 at 1.7 M, 9647, 9688, 9757 with four sub-models of 3.2 M; T = 2^23 3562, 3621, 3602 at 3.3 M; T = 2^19 1915, -, 1967 at 3.3 M."""
         T = m.grid.log2_T
         factor = 1.0
         if self.occ is not None and use != "refresh":
-            factor = 3.0 if T >= 18 else 1.0
+            factor = 1.0 if T < 18 else 1.5 if full else 3.0
         elif use != "refresh" and T in (21, 22):
             factor = max(1.0, min(1.4, (1 << 21) / max(N, 1)))
         return B.dg_order_desc_init(m.grid, int(N * factor))
@@ -604,7 +618,7 @@ class TrainStep:
             if N:
                 with self._timed("dg_dir_encode"):
                     B.dg_dir_encode(d, self.sample_ray[sl], N, self.deg, self.dir_enc[sl])
-                order = self._order_of(m, N, use)
+                order = self._order_of(m, N, use, self._fill_the_box(p, N, n_seg))
                 self.layout[p] = (s0 - N, N, order)
                 self._encode_fwd(p, m, order, sl, N, use)
                 app = self._appearance_rows(self.sample_ray[sl], N, sl)

@@ -13,6 +13,8 @@ import oracle.step as ostep
 
 from gpu_util import (DEV, TOL_F16, TOL_F32, assert_close_robust, dev, from_planes, gpu_models, gpu_occupancy, have_gpu, host,
                       make_step, rel_err, split_appearance_weights)
+from paper_2405_04416_amd import binding as B
+from paper_2405_04416_amd.step import TrainStep
 
 pytestmark = [pytest.mark.gpu, pytest.mark.skipif(not have_gpu(), reason="needs a GPU")]
 
@@ -110,6 +112,34 @@ def test_step_occupancy_with_appearance_features():
     cfg["mlp"] = dict(cfg["mlp"], n_app=16)
     cfg["occ"] = dict(res=64, max_steps=1024)
     _compare(cfg, 1000, seed=4, lambda1=1e-3, loss_scale=2.0 ** 14, table_gain=3000.0, max_samples=60000)
+
+
+@pytest.mark.parametrize("full,factor", [(False, 3.0), (True, 1.5)])
+def test_bricks_of_guided_samples(monkeypatch, full, factor):
+    """Samples on surfaces are put in bricks for three times their number; those of a grid that is set all over fill the box and are not.  Where the
+    workspace is too small for the levels that are then left unmerged, the bricks are those of samples on surfaces."""
+    say("bricks of occupancy-guided samples, grid full: %s" % full)
+    monkeypatch.setattr(TrainStep, "_order_min", lambda self, m: 1)
+    cfg = di.config("c7_occ")
+    cfg["grid"] = dict(cfg["grid"], log2_T=18)
+    cfg["occ"] = dict(cfg["occ"], res=64)
+    R = 20000
+    o, d = di.make_rays(cfg, seed=5, R=R)
+    hm, ho = ostep.make_models(cfg, seed=5), ostep.make_occupancy(cfg, seed=5)
+    if full:
+        ho[0]["bits"] = ~np.zeros_like(ho[0]["bits"])
+    gm = gpu_models(cfg, hm)
+    step = make_step(cfg, gm, R, loss_scale=2.0 ** 14, seed=5, occupancy=gpu_occupancy(cfg, ho), max_samples=100 * R)
+    step.step(dev(o), dev(d), dev(di.make_targets(R, seed=5)))
+    N = step.samples[0][1]
+    assert N > (50 if full else 3) * R // 2
+    assert bytes(step.layout[0][2]) == bytes(B.dg_order_desc_init(gm[0].grid, int(factor * N)))
+    if full:
+        step.ws_enc = step.ws_enc[:B.dg_hashgrid_encode_bwd_ordered_workspace_bytes(gm[0].grid, step.layout[0][2], N) // 4 - 64]
+        step.step(dev(o), dev(d), dev(di.make_targets(R, seed=5)))
+        assert bytes(step.layout[0][2]) == bytes(B.dg_order_desc_init(gm[0].grid, 3 * N))
+    torch.cuda.synchronize()
+    assert bool(torch.isfinite(gm[0].dtable).all()) and bool(gm[0].dtable.any())
 
 
 def test_sample_capacity_is_enforced():
