@@ -330,8 +330,9 @@ def test_many_bricks_to_an_entry():
 @pytest.mark.parametrize("flavour", FLAVOURS)
 @pytest.mark.parametrize("log2_T", [11, 14, 17, 20, 22, 23, 24])
 def test_unmerged_levels_of_every_table_size(log2_T, flavour):
-    """Levels of one to 2048 bins, whose queues are filled from rings of 2048 lines to one, several steps per workgroup, the last one partly
-    filled; with all samples in a few cells most records find their ring full.  Pairs whose entries lie in different bins are among them."""
+    """Levels of up to 2048 bins, the last step partly filled; with all samples in a few cells most records find their ring full.  Pairs whose
+    entries lie in different bins are among them.  T = 2^11 and 2^14 have so few bins that all are summed directly; from 2^17 on queues are
+    filled from rings of 128 lines to one (test_queues_of_few_bins: longer ones)."""
     print("[case] unmerged levels", log2_T, flavour, flush=True)
     growth = B.dg_growth_factor(16, 1024, 16)
     grid, ref_grid = (f(16, 2, log2_T, 16, growth, [1.0, 0.9, 0.5]) for f in (B.dg_grid_desc_init, oracle.grid_init))
@@ -403,8 +404,8 @@ def test_fractions_finer_than_a_record(log2_T):
 @pytest.mark.parametrize("flavour", FLAVOURS)
 @pytest.mark.parametrize("log2_T", [14, 20, 22, 23, 24])
 def test_ray_order_queues_of_every_table_size(log2_T, flavour):
-    """The same sizes for samples in the order of their rays: records of merged runs, four in a line, and rings of half as many lines for up to 512
-    bins."""
+    """The same for samples in the order of their rays: records of merged runs, four in a line, and rings of half as many lines for up to 512
+    bins.  T = 2^14 is summed directly."""
     print("[case] ray order", log2_T, flavour, flush=True)
     growth = B.dg_growth_factor(16, 1024, 16)
     grid, ref_grid = (f(16, 2, log2_T, 16, growth, [1.0, 0.9, 0.5]) for f in (B.dg_grid_desc_init, oracle.grid_init))
@@ -420,6 +421,47 @@ def test_ray_order_queues_of_every_table_size(log2_T, flavour):
     scale = oracle.encode_bwd(ref_grid, u, np.abs(g).astype(np.float64))
     for l in range(16):
         # a contribution is four fp32 roundings deep, a run of up to 64 adds six more, a record rounds to 2^-19 at most, and the bin's flush to fp32
+        sl = slice(ref_grid.first[l], ref_grid.first[l + 1])
+        assert np.all(have[sl][want[sl] == 0] == 0), l
+        assert np.linalg.norm(have[sl] - want[sl]) <= (2.0 ** -19 + 14 * 2.0 ** -24) * np.linalg.norm(scale[sl]), l
+
+
+@pytest.mark.parametrize("flavour", FLAVOURS)
+@pytest.mark.parametrize("spatial", [False, True])
+@pytest.mark.parametrize("log2_T,n_max,N,merged,fewest,most", [(18, 64, 150001, 2, 1, 16), (15, 1024, 400001, None, 4, 4)])
+def test_queues_of_few_bins(log2_T, n_max, N, merged, fewest, most, spatial, flavour):
+    """Levels of one to sixteen bins and of four that go through queues all the same: rings of 2048 (in ray order 1024) lines to 128 (64), written out by as
+    many groups of lanes to a bin as there are."""
+    print("[case] few bins", log2_T, n_max, spatial, flavour, flush=True)
+    extent, growth = [1.0, 0.9, 0.5], B.dg_growth_factor(16, n_max, 16)
+    grid, ref_grid = (f(16, 2, log2_T, 16, growth, extent) for f in (B.dg_grid_desc_init, oracle.grid_init))
+    u = _coords(N, flavour)
+    order, ordered, pieces = _sorted(grid, u, N)
+    if merged is not None:
+        order.n_merged = merged
+    M = order.n_merged if spatial else 0
+    first = max(M, sum(e <= 8192 for e in ref_grid.first[1:17]))            # the levels below have a way of their own
+    have_bins = [-((ref_grid.first[l] - ref_grid.first[l + 1]) // 8192) for l in range(first, 16)]
+    assert min(have_bins) <= fewest and max(have_bins) == most
+    g = (np.random.default_rng(54).standard_normal((N, 32)) * 1e-3).astype(np.float32)
+    ud, need = dev(u), (B.dg_hashgrid_encode_bwd_ordered_workspace_bytes(grid, order, N) if spatial else B.dg_hashgrid_encode_bwd_workspace_bytes(grid, N))
+
+    def gradient(planes_of):
+        gd, dtable, ws = dev(_mixed(planes_of, M)), torch.zeros(ref_grid.n_entries, 2, device=DEV), torch.full((need // 4 + 64,), float("nan"), device=DEV)
+        if spatial:
+            B.dg_hashgrid_encode_bwd_ordered(grid, order, ordered, pieces, ud, gd, dev(np.abs(g).max().reshape(1)).view(torch.int32), N, dtable, ws)
+        else:
+            B.dg_hashgrid_encode_bwd(grid, ud, gd, N, dtable, ws)
+        return host(dtable)
+
+    # an infinite gradient at the first of these levels marks every bin of a queue, and its own entries alone where bins are summed directly
+    marked = g.copy()
+    marked[0, 2 * first] = np.inf
+    assert not np.isfinite(gradient(marked)[ref_grid.first[15]:]).all()
+    want, have = oracle.encode_bwd(ref_grid, u, g.astype(np.float64)), gradient(g).astype(np.float64)
+    scale = oracle.encode_bwd(ref_grid, u, np.abs(g).astype(np.float64))
+    for l in range(first, 16):
+        # as in test_ray_order_queues_of_every_table_size; half a quantum of 2^-31 of the largest sum of a run, which some thousands of records share
         sl = slice(ref_grid.first[l], ref_grid.first[l + 1])
         assert np.all(have[sl][want[sl] == 0] == 0), l
         assert np.linalg.norm(have[sl] - want[sl]) <= (2.0 ** -19 + 14 * 2.0 ** -24) * np.linalg.norm(scale[sl]), l
