@@ -476,11 +476,9 @@ bool direct_bins(const Plan &p, uint32_t n_levels, uint64_t N)
 
 // Many bins: accumulate_sparse_kernel.  Its time against accumulate_kernel's in us, with `bins` bins and `records` records per bin at most.  Compact records:
 // 12 288 bins, 65 500 records 2212 / 2275; 12 288, 38 700 1426 / 1466; four calls of 3072, 25 400 1068 / 1122; few bins: 256 bins, 832 000 records 519 / 522; 390,
-// 203 000 281 / 239; 512, 97 000 171 / 166.  Records of 16 bytes: 4074, 5700 211 / 243; 15 923, 1300 955 / 1014; 611, 4800 49 / 47.
-bool sparse_bins(const Plan &p, uint32_t n_levels, uint64_t nb)
-{
-    return p.n_keys >= 2048u;
-}
+// 203 000 281 / 239; 512, 97 000 171 / 166.  Records of 16 bytes: 4074, 5700 211 / 243; 15 923, 1300 955 / 1014; 611, 4800 49 / 47; the whole pass, for more records
+// than entries: 3731, 8500 438 / 427; 3731, 17 000 645 / 669; 3731, 113 000 3720 / 3733; 4566, 23 000 1124 / 1157; 8662, 48 000 4148 / 4174; 15 923, 53 000 9037 / 9126.
+bool sparse_bins(const Plan &p) { return p.n_keys >= 2048u; }
 
 // records that nb samples make at most, with the padding of the slices
 uint64_t batch_records(const Plan &p, uint32_t n_levels, uint64_t nb) { return nb * 4ull * (n_levels - p.first_level) + slice_padding(p, nb); }
@@ -642,7 +640,7 @@ int encode_bwd_binned(const char *who, const dg_grid_desc *d, uint32_t from_leve
         constexpr size_t table = 2 * kChunk * sizeof(double);
         auto accumulate = [&](auto kind) {
             typedef decltype(kind) R;
-            if (sparse_bins(p, d->n_levels, nb))
+            if (sparse_bins(p))
                 accumulate_sparse_kernel<R><<<std::min(grid, (uint32_t)kAccGrid), kAccBlock, table, st>>>(*d, p, q.binbase, q.pieces, q.queue, dtable,
                                                                                                          q.binbase + p.n_keys + 2);
             else accumulate_kernel<R><<<grid, kAccBlock, table, st>>>(*d, p, q.binbase, q.pieces, q.queue, dtable);

@@ -40,22 +40,14 @@ __device__ __forceinline__ void locate_axis(float c, float scale, uint32_t last,
     frac = pos - (float)i;
 }
 
-// the same with the cell left in floating point
-__device__ __forceinline__ void locate_axis_float(float c, float scale, float last, float &cell, float &frac)
-{
-#pragma clang fp contract(off)
-    const float pos = c * scale;
-    cell = fminf(floorf(pos), last);
-    frac = pos - cell;
-}
-
 __device__ __forceinline__ float clamp_unit(float c)
 {
     c = c >= 0.0f ? c : 0.0f;     // NaN lands on 0 as well
     return c > 1.0f ? 1.0f : c;
 }
 
-// clamp_unit and locate_axis_float in one instruction per clamp: the middle of three values, which takes NaN for the smallest
+// clamp_unit, and locate_axis with the cell left in floating point, in one instruction per clamp: the middle of three values, which takes NaN for
+// the smallest
 __device__ __forceinline__ float unit(float c) { return __builtin_amdgcn_fmed3f(c, 0.0f, 1.0f); }
 __device__ __forceinline__ void locate_unit(float c, float scale, float last, float &cell, float &frac)
 {
