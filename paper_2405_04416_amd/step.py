@@ -154,27 +154,31 @@ class TrainStep:
     def _order_min(self, m):
         """Samples of a sub-model from which on a training step puts them in spatial order.  The kernels for ordered samples serve
         the 16-level grid with the 32-64-16 / 64-64-3 networks.  The order pays once the samples lie densely enough to share
-        table lines and cells.  Whole step, plain / ordered in us; what the lines below lie between:
-        T = 2^17 644 / 721 at 0.83 M samples, 969 / 960 at 1.30 M.  T = 2^18 899 / 942 at 1.25 M, 1160 / 1137 at 1.66 M.  T = 2^19 1197 / 1217 at 1.66 M,
-        1720 / 1522 at 2.48 M; the line stays where the ordered gather breaks even by itself, 1.65 / 1.70 ms at 2.10 M.  T = 2^20 757 / 824 at 0.83 M,
-        1039 / 1083 at 1.26 M, 1324 / 1328 at 1.68 M, but oblique rays, whose neighbours share less, with four sub-models 2069 / 2260 of 0.40 M, 2729 / 2723 of 0.61 M,
-        3432 / 3228 of 0.81 M.
-        Larger tables, finest level of 2048 cells along the box: T = 2^21 757 / 799 at 0.65 M, 1174 / 1191 at 1.25 M, 1466 / 1459 at 1.67 M, oblique 2437 / 2617 with four
-        of 0.40 M, 3241 / 3155 of 0.61 M; T = 2^22 754 / 780 at 0.49 M, 893 / 907 at 0.65 M, 1164 / 1133 at 0.98 M, oblique 3049 / 3030 with four of 0.41 M, 3842 / 3593 of
-        0.61 M.  With 8192 cells samples share less: T = 2^21 845 / 900 at 0.64 M, 1121 / 1136 at 0.96 M; T = 2^22 875 / 928 at 0.48 M, 1209 / 1210 at 0.81 M;
-        T = 2^23 1159 / 1163 at 0.48 M, 1531 / 1488 at 0.81 M; T = 2^24 1467 / 1500 at 0.49 M, 1709 / 1676 at 0.65 M.
-        Occupancy-guided samples lie on surfaces, ten times as densely: T = 2^18 673 / 678 at 0.56 M, 901 / 847 at 0.79 M; T = 2^19 704 / 707 and
-        920 / 855; T = 2^20 539 / 537 at 0.28 M, 815 / 760 at 0.56 M; with cells four times as wide T = 2^19 1893 / 1715 at 2.2 M."""
+        table lines and cells: with oblique rays, whose neighbours share less in ray order, earlier than under a camera; the lines lie where views from above
+        break even or (T = 2^20 to 2^22) a little earlier.  Whole step, plain / ordered in us, of one box seen from above; oblique rays, and four
+        sub-models that they cross, where stated:
+        T = 2^17 728 / 771 at 0.91 M samples, 852 / 851 at 1.11 M, 909 / 899 at 1.19 M, oblique 870 / 828 at 1.0 M.  T = 2^18 823 / 842 at 1.03 M, 886 / 885 at 1.14 M,
+        953 / 935 at 1.24 M, oblique 802 / 775 at 0.90 M.  T = 2^19 766 / 784 at 0.89 M, 863 / 864 at 1.04 M, 962 / 944 at 1.19 M, 1279 / 1191 at 1.66 M, oblique 906 / 861 at
+        1.0 M, 1809 / 1434 at 2.2 M, four sub-models 2392 / 2470 of 0.61 M, 2925 / 2857 of 0.79 M, 4377 / 4036 of 1.28 M, with 48 appearance inputs 1148 / 1111 at 1.20 M.
+        T = 2^20 818 / 855 at 0.84 M, 946 / 943 at 1.00 M, 1130 / 1104 at 1.25 M, oblique 920 / 894 at 0.85 M, four sub-models 2071 / 2278 of 0.41 M, 2758 / 2750 of
+        0.61 M, 3467 / 3290 of 0.82 M.
+        Larger tables, finest level of 2048 cells along the box: T = 2^21 684 / 707 at 0.52 M, 796 / 819 at 0.65 M, 917 / 891 at 0.80 M, oblique 883 / 851 at 0.65 M, four
+        sub-models 2463 / 2622 of 0.41 M, 3264 / 3200 of 0.61 M; T = 2^22 698 / 732 at 0.38 M, 832 / 830 at 0.52 M, 941 / 927 at 0.64 M, four 3025 / 3041 of 0.42 M.
+        With 8192 cells samples share less: T = 2^21 860 / 874 at 0.60 M, 1001 / 993 at 0.75 M, 1148 / 1125 at 0.91 M; T = 2^22 916 / 925 at 0.46 M, 1083 / 1071 at
+        0.62 M, 1261 / 1203 at 0.77 M, oblique 1016 / 1020 at 0.50 M; T = 2^23 999 / 1032 at 0.32 M, 1126 / 1137 at 0.40 M, 1253 / 1182 at 0.45 M, oblique 1264 / 1176 at 0.40 M;
+        T = 2^24 1419 / 1454 at 0.40 M, 1607 / 1481 at 0.46 M, 1710 / 1632 at 0.55 M, oblique 1577 / 1515 at 0.40 M.
+        Occupancy-guided samples lie on surfaces, ten times as densely: T = 2^17 604 / 608 at 0.56 M, 1008 / 934 at 1.12 M; T = 2^18 612 / 603 at 0.56 M, 783 / 710 at
+        0.78 M; T = 2^19 642 / 630 and 808 / 728; T = 2^20 559 / 560 at 0.39 M, 708 / 672 at 0.56 M; with cells four times as wide T = 2^19 1893 / 1715 at 2.2 M."""
         if m.grid.n_levels != 16 or (m.mlp.n_feat, m.mlp.n_hidden_d, m.mlp.n_layers_c) != (32, 64, 2):
             return 1 << 62
         T = m.grid.log2_T
         if self.occ is not None:
             return 1 << 20 if T < 18 else 3 << 18 if T <= 19 else 1 << 19
         if T <= 20:
-            return {17: 5 << 18, 18: 3 << 19, 19: 9 << 18, 20: 3 << 18}.get(T, 1 << 21)
+            return {17: 9 << 17, 18: 9 << 17, 19: 9 << 17, 20: 3 << 18}.get(T, 1 << 21)
         if not self._fine(m):
             return 1 << 19
-        return 3 << 18 if T == 21 else 5 << 17
+        return {21: 3 << 18, 22: 5 << 17}.get(T, 7 << 16)
 
     @staticmethod
     def _fine(m):
@@ -184,10 +188,11 @@ class TrainStep:
     def _order_factor(self, m, use):
         """How many times as many samples a call needs that has no backward pass to save time in: the gather alone pays for the
         sort and for rows written one by one.  Plain / ordered in ms.
-        Rendering: T = 2^17 0.616 / 0.606 at 3.0 M samples; T = 2^18 0.82 / 0.83 at 4.0 M, 1.00 / 0.97 at 5.0 M; T = 2^19 0.73 / 0.84 at
-        3.0 M, 1.16 / 1.18 at 5.0 M, 1.38 / 1.33 at 6.0 M; T = 2^20 0.71 / 0.70 at 2.1 M.  Finest level of 2048 cells: T = 2^21
-        0.28 / 0.30 at 0.55 M, 0.37 / 0.38 at 0.80 M (oblique rays 1.57 / 1.44 with four sub-models of 0.74 M), T = 2^22 0.30 / 0.31 at 0.54 M
-        (oblique 1.18 / 1.10 with four of 0.49 M); 8192 cells: T = 2^21 1.49 / 1.50 at 3.0 M, T = 2^22 0.89 / 0.88 at 1.5 M, T = 2^23 0.71 / 0.70 at 1.1 M.
+        Rendering: T = 2^17 0.616 / 0.606 at 3.0 M samples; T = 2^18 0.66 / 0.69 at 3.2 M, 1.00 / 0.97 at 5.0 M; T = 2^19 0.59 / 0.70 at 2.4 M, 0.93 / 0.99 at
+        4.0 M, 1.10 / 1.13 at 4.8 M, 1.38 / 1.33 at 6.0 M; T = 2^20 0.61 / 0.64 at 1.8 M, 0.75 / 0.74 at 2.2 M.  Finest level of 2048 cells: T = 2^21
+        0.35 / 0.36 at 0.68 M, 0.42 / 0.42 at 0.87 M, 0.54 / 0.52 at 1.2 M (oblique rays 1.57 / 1.44 with four sub-models of 0.74 M), T = 2^22 0.26 / 0.27 at 0.40 M,
+        0.33 / 0.33 at 0.56 M, 0.39 / 0.37 at 0.72 M; 8192 cells: T = 2^21 1.06 / 1.09 at 1.9 M, 1.53 / 1.52 at 2.8 M, T = 2^22 0.66 / 0.66 at 0.95 M, 0.94 / 0.90 at
+        1.4 M, T = 2^23 0.56 / 0.56 at 0.75 M, 0.74 / 0.71 at 1.0 M.
         With occupancy-guided samples from 2^20 on (T = 2^19 0.50 / 0.48 at 1.1 M).
         Occupancy refresh, T = 2^19: 0.36 / 0.38 at 1.05 M candidates, 0.43 / 0.43 at 1.24 M, 0.57 / 0.55 at 1.71 M; T = 2^18 0.33 / 0.31 at 1.05 M."""
         T = m.grid.log2_T
@@ -197,9 +202,9 @@ class TrainStep:
             from_2_20 = {18: 4 / 3, 19: 4 / 3, 20: 2.0}.get(T, 1.0)
             return 1.25 * from_2_20 if use == "refresh" and T == 19 else from_2_20
         if T <= 20:
-            return {17: 2.4, 18: 8 / 3, 19: 2.25, 20: 8 / 3}.get(T, 1.5)
+            return {17: 8 / 3, 18: 32 / 9, 19: 4.5, 20: 8 / 3}.get(T, 1.5)
         if self._fine(m):
-            return {21: 4.0, 22: 2.25}.get(T, 1.5)
+            return {21: 4.0, 22: 2.25}.get(T, 15 / 7)
         return 1.5 if T == 21 else 1.0
 
     def _split(self, m, N, use):
