@@ -281,6 +281,9 @@ struct StepAhead {
 // UNIT: lines of an append.  A step's records go in ROUNDS rounds, each followed by its own write-out: the fewer records a bin gets per round, the
 // less often its ring overflows.  LIST: bins that have a unit are listed, otherwise all are looked at.  WAIT: where a ring is a single line, records
 // beyond it wait for the write-out.
+// Merged records, of which a step has fewer, take one round.  The pass on samples in ray order, four rounds (two with 1024 bins) and lists at all levels / one and lists where
+// there are more than 128 bins, in us: T = 2^24, oblique rays, 25.6 M samples 17 291 / 13 530, 5.1 M 4080 / 3246, views from above 16.1 M 8980 / 7970, 0.5 M 877 / 827;
+// T = 2^23, 0.64 M 1141 / 724, 6.4 M 4190 / 3600.
 template <class K, int PER_UNIT, int UNIT, int ROUNDS, bool LIST, bool WAIT>
 __global__ void __launch_bounds__(kFillTile, PER_UNIT == 1 ? 4 : 8)          // wavefronts per SIMD
 fill_kernel(dg_grid_desc g, Plan plan, Sweep sw, const float *__restrict__ u, const float2 *__restrict__ dfeat, uint64_t N, uint32_t nb,
@@ -337,9 +340,13 @@ fill_kernel(dg_grid_desc g, Plan plan, Sweep sw, const float *__restrict__ u, co
         // a bin's units are written out by groups of lanes that sit in one wavefront, several where there are more groups than bins
         const bool wait = WAIT && lines_log2 == 0u;
         constexpr uint32_t kGroupsLog2 = 31 - __builtin_clz(kGroups), kPerWaveLog2 = 31 - __builtin_clz(dg::kWave / kLanes);
-        const uint32_t subs_log2 = min(kPerWaveLog2, bins_log2 < kGroupsLog2 ? kGroupsLog2 - bins_log2 : 0u);
-        const uint32_t group = tid / kLanes, sub = LIST ? 0u : group & ((1u << subs_log2) - 1u), subs = LIST ? 1u : 1u << subs_log2;
-        const uint32_t first_group = LIST ? group : group >> subs_log2, group_step = LIST ? kGroups : kGroups >> subs_log2;
+        // A level of few bins is not listed: a bin that gets hundreds of lines a round would have one group of lanes to write them.  (Compact records come from
+        // finer levels, where all bins are listed.)
+        constexpr bool kChoose = LIST && kLine == kPairLine;
+        const uint32_t subs_log2 = LIST && !kChoose ? 0u : min(kPerWaveLog2, bins_log2 < kGroupsLog2 ? kGroupsLog2 - bins_log2 : 0u);
+        const bool listed = LIST && (!kChoose || subs_log2 == 0u);
+        const uint32_t group = tid / kLanes, sub = group & ((1u << subs_log2) - 1u), subs = 1u << subs_log2;
+        const uint32_t first_group = group >> subs_log2, group_step = kGroups >> subs_log2;
         for (uint32_t tile = me; tile < n_tiles; tile += sw.width) {
             const bool live = tile * kFillTile + tid < nb;
             const float uu[3] = {ahead.u[0], ahead.u[1], ahead.u[2]};
@@ -353,6 +360,7 @@ fill_kernel(dg_grid_desc g, Plan plan, Sweep sw, const float *__restrict__ u, co
 #pragma unroll
             for (int round = 0; round < ROUNDS; ++round, parity ^= 1u) {
                 uint32_t at[kPer], bin[kPer];                         // place of each record in its bin's ring
+                typename K::Record rec[kPer];
                 uint32_t beyond[kPer];                                // queue line of the ring's first, of records that found their ring full
                 auto to_queue = [&](uint32_t line, uint32_t place, const typename K::Record &rec) {
                     const uint32_t q = K::line_of(place);
@@ -369,12 +377,13 @@ fill_kernel(dg_grid_desc g, Plan plan, Sweep sw, const float *__restrict__ u, co
                         const uint32_t head = at[k] >> 16;
                         at[k] &= 0xffffu;
                         const uint32_t q = K::line_of(at[k]), in_line = kWords * (at[k] - kLine * q);
-                        if (at[k] < room) *reinterpret_cast<typename K::Record *>(ring + ((((bin[k] << lines_log2) + ((head + q) & line_mask)) << 4) + in_line)) = k0.record(p, lv, dtable);
+                        rec[k] = k0.record(p, lv, dtable);
+                        if (at[k] < room) *reinterpret_cast<typename K::Record *>(ring + ((((bin[k] << lines_log2) + ((head + q) & line_mask)) << 4) + in_line)) = rec[k];
                         else if (wait) beyond[k] = line0[bin[k]];
-                        else to_queue(line0[bin[k]], at[k], k0.record(p, lv, dtable));
+                        else to_queue(line0[bin[k]], at[k], rec[k]);
                     }
                 }
-                if constexpr (LIST) {
+                if (listed) {
                     // bins that get their first whole unit go into the list: one LDS add per wavefront and pair of corners
 #pragma unroll
                     for (int k = 0; k < kPer; ++k) {
@@ -389,9 +398,9 @@ fill_kernel(dg_grid_desc g, Plan plan, Sweep sw, const float *__restrict__ u, co
                     }
                 }
                 __syncthreads();                                      // records placed, list complete
-                const uint32_t n = LIST ? n_list[parity] : n_bins, c = tid % kLanes;
+                const uint32_t n = listed ? n_list[parity] : n_bins, c = tid % kLanes;
                 for (uint32_t i = first_group; i < n; i += group_step) {
-                    const uint32_t bin = LIST ? list[parity * cap + i] : i;
+                    const uint32_t bin = listed ? list[parity * cap + i] : i;
                     const uint32_t book = books[bin], total = book & 0xffffu, head = book >> 16;
                     const uint32_t units = K::line_of(min(total, room)) / UNIT;
                     if (!units) continue;
@@ -425,9 +434,8 @@ fill_kernel(dg_grid_desc g, Plan plan, Sweep sw, const float *__restrict__ u, co
 #pragma unroll
                     for (int k = 0; k < kPer; ++k) {
                         if (!wait || !emit || at[k] < room) continue;
-                        const typename K::Record rec = k0.record(kPer * round + k, lv, dtable);
-                        if (kept[bin[k]] & kDirect) to_queue(beyond[k], at[k], rec);
-                        else *reinterpret_cast<typename K::Record *>(ring + 16u * bin[k] + kWords * (at[k] - room)) = rec;
+                        if (kept[bin[k]] & kDirect) to_queue(beyond[k], at[k], rec[k]);
+                        else *reinterpret_cast<typename K::Record *>(ring + 16u * bin[k] + kWords * (at[k] - room)) = rec[k];
                     }
                 }
             }
@@ -460,8 +468,8 @@ auto with_kernel(const Plan &p, F f)
         return f(fill_kernel<Compact, 1, 1, 4, true, true>);
     }
     if (p.per_unit == 2u) return f(fill_kernel<Merged, 2, 2, 1, false, false>);
-    if (p.max_bins <= 1024u) return f(fill_kernel<Merged, 1, 1, 2, true, false>);
-    return f(fill_kernel<Merged, 1, 1, 4, true, true>);
+    if (p.max_bins <= 1024u) return f(fill_kernel<Merged, 1, 1, 1, true, false>);
+    return f(fill_kernel<Merged, 1, 1, 1, true, true>);
 }
 
 // rings, the books of the bins (13 bytes each) and the lists' lengths
