@@ -155,7 +155,7 @@ class TrainStep:
         """Samples of a sub-model from which on a training step puts them in spatial order.  The kernels for ordered samples serve
         the 16-level grid with the 32-64-16 / 64-64-3 networks.  The order pays once the samples lie densely enough to share
         table lines and cells: with oblique rays, whose neighbours share less in ray order, earlier than under a camera; the lines lie where views from above
-        break even or (T = 2^20 to 2^22) a little earlier.  Whole step, plain / ordered in us, of one box seen from above; oblique rays, and four
+        break even or (T = 2^20 to 2^23) a little earlier.  Whole step, plain / ordered in us, of one box seen from above; oblique rays, and four
         sub-models that they cross, where stated:
         T = 2^17 728 / 771 at 0.91 M samples, 852 / 851 at 1.11 M, 909 / 899 at 1.19 M, oblique 870 / 828 at 1.0 M.  T = 2^18 823 / 842 at 1.03 M, 886 / 885 at 1.14 M,
         953 / 935 at 1.24 M, oblique 802 / 775 at 0.90 M.  T = 2^19 766 / 784 at 0.89 M, 863 / 864 at 1.04 M, 962 / 944 at 1.19 M, 1279 / 1191 at 1.66 M, oblique 906 / 861 at
@@ -165,8 +165,8 @@ class TrainStep:
         Larger tables, finest level of 2048 cells along the box: T = 2^21 684 / 707 at 0.52 M, 796 / 819 at 0.65 M, 917 / 891 at 0.80 M, oblique 883 / 851 at 0.65 M, four
         sub-models 2463 / 2622 of 0.41 M, 3264 / 3200 of 0.61 M; T = 2^22 698 / 732 at 0.38 M, 832 / 830 at 0.52 M, 941 / 927 at 0.64 M, four 3025 / 3041 of 0.42 M.
         With 8192 cells samples share less: T = 2^21 860 / 874 at 0.60 M, 1001 / 993 at 0.75 M, 1148 / 1125 at 0.91 M; T = 2^22 916 / 925 at 0.46 M, 1083 / 1071 at
-        0.62 M, 1261 / 1203 at 0.77 M, oblique 1016 / 1020 at 0.50 M; T = 2^23 999 / 1032 at 0.32 M, 1126 / 1137 at 0.40 M, 1253 / 1182 at 0.45 M, oblique 1264 / 1176 at 0.40 M;
-        T = 2^24 1419 / 1454 at 0.40 M, 1607 / 1481 at 0.46 M, 1710 / 1632 at 0.55 M, oblique 1577 / 1515 at 0.40 M.
+        0.62 M, 1261 / 1203 at 0.77 M, oblique 1016 / 1020 at 0.50 M; T = 2^23 1086 / 1138 at 0.40 M, 1348 / 1374 at 0.60 M, 1463 / 1491 at 0.70 M, oblique 1274 / 1303 at
+        0.50 M, 1469 / 1413 at 0.64 M; T = 2^24 1397 / 1475 at 0.40 M, 1658 / 1683 at 0.56 M, 1831 / 1831 at 0.65 M, oblique 1590 / 1640 at 0.50 M, 1830 / 1821 at 0.64 M.
         Occupancy-guided samples lie on surfaces, ten times as densely: T = 2^17 604 / 608 at 0.56 M, 1008 / 934 at 1.12 M; T = 2^18 612 / 603 at 0.56 M, 783 / 710 at
         0.78 M; T = 2^19 642 / 630 and 808 / 728; T = 2^20 559 / 560 at 0.39 M, 708 / 672 at 0.56 M; with cells four times as wide T = 2^19 1893 / 1715 at 2.2 M."""
         if m.grid.n_levels != 16 or (m.mlp.n_feat, m.mlp.n_hidden_d, m.mlp.n_layers_c) != (32, 64, 2):
@@ -178,7 +178,7 @@ class TrainStep:
             return {17: 9 << 17, 18: 9 << 17, 19: 9 << 17, 20: 3 << 18}.get(T, 1 << 21)
         if not self._fine(m):
             return 1 << 19
-        return {21: 3 << 18, 22: 5 << 17}.get(T, 7 << 16)
+        return 3 << 18 if T == 21 else 5 << 17
 
     @staticmethod
     def _fine(m):
@@ -204,7 +204,7 @@ class TrainStep:
         if T <= 20:
             return {17: 8 / 3, 18: 32 / 9, 19: 4.5, 20: 8 / 3}.get(T, 1.5)
         if self._fine(m):
-            return {21: 4.0, 22: 2.25}.get(T, 15 / 7)
+            return {21: 4.0, 22: 2.25}.get(T, 1.5)
         return 1.5 if T == 21 else 1.0
 
     def _split(self, m, N, use):

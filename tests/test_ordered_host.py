@@ -91,11 +91,11 @@ def test_lines_of_the_order(log2_T, n_max):
     faster_in_ray_order = [(18, 2048, "render", 3000000), (19, 2048, "render", 3980000), (19, 2048, "refresh", 1048576), (21, 8192, "step", 602048),
                            (21, 8192, "render", 2070000), (22, 8192, "step", 602560), (22, 8192, "render", 1085000), (17, 2048, "step", 912000),
                            (18, 2048, "step", 1030976), (19, 2048, "step", 891008), (20, 2048, "step", 678528), (21, 2048, "step", 516864),
-                           (22, 2048, "step", 379968), (23, 8192, "step", 397440), (24, 8192, "step", 399696), (18, 2048, "render", 3171456),
+                           (22, 2048, "step", 379968), (23, 8192, "step", 596448), (24, 8192, "step", 554560), (18, 2048, "render", 3171456),
                            (19, 2048, "render", 4756096), (20, 2048, "render", 1750656), (21, 2048, "render", 675648), (22, 2048, "render", 396224)]
     faster_in_order = [(17, 2048, "step", 1293312), (18, 2048, "step", 1240000), (19, 2048, "step", 1188608), (20, 2048, "step", 1197760),
                        (21, 2048, "step", 795968), (22, 2048, "step", 796608), (21, 8192, "step", 905136), (22, 8192, "step", 768432),
-                       (23, 8192, "step", 613920), (24, 8192, "step", 551280), (21, 2048, "render", 1193472), (22, 2048, "render", 717824)]
+                       (21, 2048, "render", 1193472), (22, 2048, "render", 717824)]
     m = types.SimpleNamespace(grid=B.dg_grid_desc_init(16, 2, log2_T, 16, B.dg_growth_factor(16, n_max, 16), [2.0, 2.0, 0.25]),
                               mlp=B.dg_mlp_desc(32, 64, 16, 16, 64, 2, 1))
     for use in ("step", "render", "refresh"):
