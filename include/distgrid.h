@@ -206,7 +206,7 @@ typedef struct dg_order_desc {
 int dg_order_desc_init(dg_order_desc *order, const dg_grid_desc *desc, uint64_t N);
 /* ordered [N] of 16 bytes each (x, y, z fp32 and ids[sample], uint32; ids NULL: the sample's index; device, 16-byte aligned);
  * pieces: dg_order_pieces_words(order, N) words that list which stretch of the order belongs to which brick (read by
- * dg_hashgrid_encode_bwd_ordered; 8-byte aligned).  Its word 1 is set to 0 and left to the caller: room for the `largest`
+ * dg_hashgrid_encode_fwd_bricks and dg_hashgrid_encode_bwd_ordered; 8-byte aligned).  Its word 1 is set to 0 and left to the caller: room for the `largest`
  * word of dg_mlp_bwd_rows.  N < 2^32 - 1.
  * ws: dg_order_workspace_bytes(order) bytes of device memory, 256-byte aligned. */
 size_t dg_order_workspace_bytes(const dg_order_desc *order);
@@ -233,7 +233,8 @@ int dg_hashgrid_encode_fwd_bricks(const dg_grid_desc *desc, const dg_order_desc 
  * Merged levels: up to 96 samples of one cell are added up in fp32, what a brick holds of such sums in 64 bits: in fp64 at the
  * levels whose tables together have at most 8192 entries, in fixed point with quanta of 2^-37 of *largest or finer at the others.
  * The bricks' sums are added in fp64 at levels of at most 2^18 entries, in fp32 at larger ones.  The levels that are
- * not merged go through the bins as in dg_hashgrid_encode_bwd, with its precision.  Where *largest is infinite or NaN every brick leaves
+ * not merged go through the bins as in dg_hashgrid_encode_bwd, with its precision (in a level's first cell along x 2^-21 of a contribution
+ * more).  Where *largest is infinite or NaN every brick leaves
  * NaN in one entry of each merged level.  counted != 0: the queues have been laid out by ..._ordered_count (rules as
  * for dg_hashgrid_encode_bwd_count). */
 size_t dg_hashgrid_encode_bwd_ordered_workspace_bytes(const dg_grid_desc *desc, const dg_order_desc *order, uint64_t N);

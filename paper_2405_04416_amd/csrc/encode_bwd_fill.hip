@@ -207,11 +207,13 @@ struct Compact {
         }
         largest = max(largest, __float_as_uint(most));
         if (gfe.x != gfe.x || gfe.y != gfe.y) largest = 0x7fc00000u;                  // fmaxf passes over NaN
-        // In a level's first cell along x fractions have more bits than units of 2^-23 can say; rounded, next to a face of the cell a share
-        // would lose all of them.  One sample in hundreds: ordered pass, 13.3 M samples, T = 2^19 2.593 / 2.591 ms without and with this, 3.3 M 780 / 795 us.
+        // In a level's first cell along x fractions have more bits than units of 2^-23 can say.  Rounded to these a share is off by 2^-21 of itself at most while
+        // the fraction lies in [1/8, 7/8], a quarter of what its 27-bit value may be off; nearer to a face of the cell it could lose all of its bits, and the
+        // pair goes apart: one sample in hundreds.  Ordered pass without and with this, T = 2^19, 13.3 M samples 2600 / 2599 us, 3.3 M 780 / 788 (798 if
+        // pairs went apart all over the cell); half a million with a sixth of all in the first cell 282 / 366.
         const float units = frac[0] * 0x1p23f;
         fx = (uint32_t)(units + 0.5f);
-        const bool finer = units != (float)fx;
+        const bool finer = units != (float)fx && fabsf(units - 0x1p22f) > 0x1.8p21f;
         codes = 0u;
         if (lv.dense) {
 #pragma unroll
