@@ -2,7 +2,7 @@
 // Sec. 4.1: the grid is deformable like the hash grid; Sec. 5.1: its hyper-parameters; refresh rule of
 // Instant-NGP App. E.2: decay, candidate cells, maximum, threshold).
 //
-// Marching: sixteen lanes per segment, one stratum per lane and pass.  The lanes of a pass lie next to
+// Marching: sixteen lanes per segment (64 where there are few), one stratum per lane and pass.  The lanes of a pass lie next to
 // each other on the ray, so their bit lookups fall into a few cache lines of a bit field that stays in L2
 // (512 x 512 x 64 cells are 2 MiB).  Segments are placed by an exclusive scan over their sample counts, so the layout is
 // deterministic: count, scan, write.
@@ -13,6 +13,7 @@
 #include "sample_common.h"
 #include <cmath>
 #include <cstring>
+#include <type_traits>
 
 #pragma clang fp contract(off)
 
@@ -148,11 +149,14 @@ bits_kernel(const float *__restrict__ density, uint32_t n_cells, float threshold
 // ---------------------------------------------------------------- marching
 struct MarchOut { float *u, *delta, *t; uint32_t *sample_ray; };
 
-// Segments are short (some eighty strata where the box is flat): kSegLanes lanes take one, four to a wavefront, so that few lanes run past its end.
+// Segments are short (some eighty strata where the box is flat): sixteen lanes take one, four to a wavefront, so that few lanes run past its end.
 // The counting pass is bound by its look-ups, a cache line of the bit field per stratum, and by the arithmetic, two 64-bit products for the jitter and
 // the cell; what it finds out about the first kMaskStrata strata stays in the workspace as bits, and the writing pass works on the kept ones
 // alone.  208 k segments, 1.55 M of 16 M strata kept: 57 + 23 us (a wavefront per segment, both passes over all strata: 76 + 79).
-constexpr uint32_t kSegLanes = 16, kSegPerBlock = kBlock / kSegLanes;
+// Where there are few, little more than the 8192 wavefronts that the chip holds, each gets one: what counts is then the chain along a segment.  The whole march with sixteen / 64 lanes, in us: flat box, tenth of the cells
+// set 4000 segments 24 / 23, 10 000 26.5 / 25.9, 20 000 31 / 34, 260 000 141 / 217; cube, some 400 strata a segment, a layer set 1000 segments 36 / 22, 4000 38 / 28, 10 000 49 / 41,
+// 20 000 64 / 61, 60 000 130 / 135; cube, all cells set 1000 44 / 25, 4000 53 / 35.
+constexpr uint32_t kFewSegments = 10240, kFewLanes = dg::kWave, kManyLanes = 16;
 constexpr uint32_t kMaskWords = 8, kMaskStrata = 32 * kMaskWords;
 
 struct MarchIn {
@@ -199,26 +203,32 @@ struct Strata {
 };
 
 // `on` of the lane's segment, as its low bits
-__device__ __forceinline__ uint32_t segment_ballot(bool on, uint32_t lane) { return (uint32_t)(__ballot(on) >> (lane & ~(kSegLanes - 1u))) & ((1u << kSegLanes) - 1u); }
-
-__global__ void __launch_bounds__(kBlock)
-march_count_kernel(MarchIn in, OccArgs occ, const uint32_t *__restrict__ bits, uint32_t *__restrict__ first, uint32_t *__restrict__ masks)
+template <uint32_t LANES>
+__device__ __forceinline__ uint64_t segment_ballot(bool on, uint32_t lane)
 {
-    const uint32_t j = blockIdx.x * kSegPerBlock + threadIdx.x / kSegLanes, lane = threadIdx.x % dg::kWave, in_seg = threadIdx.x % kSegLanes;
+    const uint64_t wave = __ballot(on);
+    return LANES == dg::kWave ? wave : (wave >> (lane & ~(LANES - 1u))) & ((1ull << (LANES % dg::kWave)) - 1ull);
+}
+
+template <uint32_t LANES>
+__global__ void __launch_bounds__(kBlock)
+march_count_kernel(MarchIn in, OccArgs occ, const uint32_t *__restrict__ bits, uint32_t *__restrict__ first, uint64_t *__restrict__ masks)
+{
+    const uint32_t j = blockIdx.x * (kBlock / LANES) + threadIdx.x / LANES, lane = threadIdx.x % dg::kWave, in_seg = threadIdx.x % LANES;
     if (blockIdx.x == 0 && threadIdx.x == 0) first[in.n_seg] = 0;            // the scan turns it into the total
     if (j >= in.n_seg) return;                                              // all lanes of a segment
     const Strata strata(in, j);
-    uint32_t kept = 0, word = 0u;
-    uint64_t z = strata.jitter + kGolden * in_seg;
-    for (uint32_t base = 0; base < strata.n; base += kSegLanes, z += kGolden * kSegLanes) {
+    uint32_t kept = 0;
+    uint64_t z = strata.jitter + kGolden * in_seg, word = 0u;
+    for (uint32_t base = 0; base < strata.n; base += LANES, z += kGolden * LANES) {
         float u[3];
         const uint32_t s = base + in_seg;
         strata.sample(in, s, z, u);
-        const uint32_t mask = segment_ballot(s < strata.n && bit_of(bits, cell_of(occ, u)), lane);      // empty space is skipped
-        kept += (uint32_t)__popc(mask);
-        word |= mask << (base % 32u);
-        if ((base + kSegLanes) % 32u == 0u || base + kSegLanes >= strata.n) {
-            if (in_seg == 0 && base < kMaskStrata) masks[(size_t)kMaskWords * j + base / 32u] = word;
+        const uint64_t mask = segment_ballot<LANES>(s < strata.n && bit_of(bits, cell_of(occ, u)), lane);      // empty space is skipped
+        kept += (uint32_t)__popcll(mask);
+        word |= mask << (base % 64u);
+        if ((base + LANES) % 64u == 0u || base + LANES >= strata.n) {
+            if (in_seg == 0 && base < kMaskStrata) masks[(size_t)(kMaskWords / 2) * j + base / 64u] = word;
             word = 0u;
         }
     }
@@ -240,11 +250,12 @@ __device__ __forceinline__ uint32_t select_bit(uint32_t x, uint32_t rank)
     return at;
 }
 
+template <uint32_t LANES>
 __global__ void __launch_bounds__(kBlock)
 march_write_kernel(MarchIn in, OccArgs occ, const uint32_t *__restrict__ bits, uint32_t capacity, const uint32_t *__restrict__ first,
                    const uint32_t *__restrict__ masks, MarchOut out, uint32_t *__restrict__ status)
 {
-    const uint32_t j = blockIdx.x * kSegPerBlock + threadIdx.x / kSegLanes, lane = threadIdx.x % dg::kWave, in_seg = threadIdx.x % kSegLanes;
+    const uint32_t j = blockIdx.x * (kBlock / LANES) + threadIdx.x / LANES, lane = threadIdx.x % dg::kWave, in_seg = threadIdx.x % LANES;
     if (j >= in.n_seg) return;                                              // all lanes of a segment
     const uint32_t begin = first[j], total = first[j + 1] - begin;
     if (total == 0u) return;
@@ -269,7 +280,7 @@ march_write_kernel(MarchIn in, OccArgs occ, const uint32_t *__restrict__ bits, u
         word[w] = 32u * w < strata.n ? masks[(size_t)kMaskWords * j + w] : 0u;
         below[w + 1] = below[w] + (uint32_t)__popc(word[w]);
     }
-    for (uint32_t i = in_seg; i < below[kMaskWords]; i += kSegLanes) {
+    for (uint32_t i = in_seg; i < below[kMaskWords]; i += LANES) {
         uint32_t mine = word[0], rank = i, base = 0;
 #pragma unroll
         for (uint32_t w = 1; w < kMaskWords; ++w)
@@ -278,14 +289,14 @@ march_write_kernel(MarchIn in, OccArgs occ, const uint32_t *__restrict__ bits, u
     }
     // strata that the bits do not reach are looked at again
     uint32_t kept = below[kMaskWords];
-    for (uint32_t base = kMaskStrata; base < strata.n; base += kSegLanes) {
+    for (uint32_t base = kMaskStrata; base < strata.n; base += LANES) {
         float u[3];
         const uint32_t s = base + in_seg;
         strata.sample(in, s, strata.jitter + kGolden * s, u);
         const bool keep = s < strata.n && bit_of(bits, cell_of(occ, u));
-        const uint32_t mask = segment_ballot(keep, lane);
-        if (keep) write(kept + (uint32_t)__popc(mask & ((1u << in_seg) - 1u)), s);
-        kept += (uint32_t)__popc(mask);
+        const uint64_t mask = segment_ballot<LANES>(keep, lane);
+        if (keep) write(kept + (uint32_t)__popcll(mask & ((1ull << in_seg) - 1ull)), s);
+        kept += (uint32_t)__popcll(mask);
     }
     if (dropped) atomicOr(status, 2u);
 }
@@ -497,14 +508,19 @@ extern "C" int dg_march_segments(const float *o, const float *d, const float *se
     const OccArgs g = occ_args(occ);
     const MarchOut out = {u, delta, t, sample_ray};
     const MarchIn in = {o, d, seg_t, seg_ray, seg_slot, n_seg, k_max, b, dt, max_steps, seed};
-    const uint32_t seg_blocks = n_seg ? (uint32_t)(((uint64_t)n_seg + kSegPerBlock - 1) / kSegPerBlock) : 1u;
     uint32_t *sums = (uint32_t *)ws;
     uint32_t *masks = sums + march_sums_bytes(n_seg) / sizeof(uint32_t);
     const uint32_t n_vals = n_seg + 1u, n_tiles = scan_tiles(n_vals);
-    march_count_kernel<<<seg_blocks, kBlock, 0, st>>>(in, g, bits, first, masks);
-    scan_tile_sums_kernel<<<n_tiles, kBlock, 0, st>>>(first, n_vals, sums);
-    scan_sums_kernel<<<1, kSumsBlock, 0, st>>>(sums, n_tiles);
-    scan_apply_kernel<<<n_tiles, kBlock, 0, st>>>(first, n_vals, sums);
-    if (n_seg) march_write_kernel<<<seg_blocks, kBlock, 0, st>>>(in, g, bits, capacity, first, masks, out, status);
+    auto march = [&](auto lanes) {
+        constexpr uint32_t kLanes = decltype(lanes)::value;
+        const uint32_t blocks = (uint32_t)(((uint64_t)n_seg * kLanes + kBlock - 1) / kBlock);
+        march_count_kernel<kLanes><<<blocks ? blocks : 1u, kBlock, 0, st>>>(in, g, bits, first, (uint64_t *)masks);
+        scan_tile_sums_kernel<<<n_tiles, kBlock, 0, st>>>(first, n_vals, sums);
+        scan_sums_kernel<<<1, kSumsBlock, 0, st>>>(sums, n_tiles);
+        scan_apply_kernel<<<n_tiles, kBlock, 0, st>>>(first, n_vals, sums);
+        if (n_seg) march_write_kernel<kLanes><<<blocks, kBlock, 0, st>>>(in, g, bits, capacity, first, masks, out, status);
+    };
+    if (n_seg <= kFewSegments) march(std::integral_constant<uint32_t, kFewLanes>{});
+    else march(std::integral_constant<uint32_t, kManyLanes>{});
     return dg::launch_status("dg_march_segments");
 }

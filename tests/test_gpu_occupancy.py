@@ -103,13 +103,14 @@ def _march_gpu(o, d, seg_t, seg_ray, seg_slot, begin, end, box, g, bits, dt, max
     return host(first).view(np.uint32), host(u), host(delta), host(t), host(ray).view(np.uint32), int(host(status)[0])
 
 
-@pytest.mark.parametrize("n_strata", [1, 15, 16, 17, 31, 32, 33, 255, 256, 257, 289, 1003])
-def test_march_numbers_of_strata(n_strata):
+@pytest.mark.parametrize("R,n_strata", [(61, n) for n in (1, 15, 16, 17, 31, 32, 33, 63, 64, 65, 255, 256, 257, 289, 1003)] +
+                                       [(50000, n) for n in (1, 15, 16, 17, 31, 32, 33, 63, 64, 65, 255, 256, 257, 289)])
+def test_march_numbers_of_strata(R, n_strata):
     """Segments of as many strata as a pass, a word of kept bits and all words hold, one less and one more, and of more than the bits reach:
-    sample by sample as the oracle's, with half of the cells occupied at random."""
+    sample by sample as the oracle's, with half of the cells occupied at random; few segments, which a wavefront takes each, and more than 10240."""
     say("march n_strata=%d" % n_strata)
     cfg = di.config("c3_2x2")
-    o, d, seg_t, off, seg_ray, seg_slot = _segments(cfg, 61, seed=6)
+    o, d, seg_t, off, seg_ray, seg_slot = _segments(cfg, R, seed=6)
     box, begin, end = cfg["parts"][0], int(off[0]), int(off[1])
     ext = di.box_extent(box)
     g_ref, g = oracle.occ_init(96, ext), B.dg_occ_desc_init(96, ext)
@@ -117,7 +118,7 @@ def test_march_numbers_of_strata(n_strata):
     dt = np.float32(1e-6)                             # finer than any segment needs: every one is cut into max_steps strata
     rf, ru, rd, rt, rr = oracle.march_segments(o, d, seg_t, seg_ray, seg_slot, begin, end, box, g_ref, bits, dt, n_strata, seed=23)
     n = int(rf[-1])
-    assert end - begin > 16 and n > 0
+    assert (end - begin > 10240 if R > 61 else end - begin > 16) and n > 0
     first, u, delta, t, ray, status = _march_gpu(o, d, seg_t, seg_ray, seg_slot, begin, end, box, g, bits, dt, n_strata, 23, n)
     assert status == 0
     for got, ref in ((first, rf), (u[:n], ru), (delta[:n], rd), (t[:n], rt), (ray[:n], rr)):
