@@ -444,6 +444,7 @@ Sweep choose_sweep(const Plan &p, uint32_t n_levels, uint64_t nb)
         const double steps = ((double)((n_tiles + width - 1) / width) + 0.5) * ((levels + k - 1) / k);
         if (k == 1 || steps < least * (29.0 / 30.0)) { best = {width, k}; least = steps; }
     }
+    best.width = (uint32_t)std::min<uint64_t>(best.width, n_tiles);          // the others would have no tile, but counters to clear and rows to scan
     return best;
 }
 // Zero records that fill up the slices of nb samples, at most: a workgroup without a tile has no records and no slice.  (A level of 512 bins is
