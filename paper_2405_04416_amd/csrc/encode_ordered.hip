@@ -683,6 +683,11 @@ extern "C" int dg_hashgrid_encode_bwd_ordered(const dg_grid_desc *desc, const dg
     return bwd_ordered("dg_hashgrid_encode_bwd_ordered", desc, order, ordered, pieces, u, dfeat, largest, N, dtable, ws, ws_bytes, counted != 0, stream);
 }
 
+// With eight merged levels the corners of four more are under way, 96 registers a lane, which leave room for one workgroup per compute unit: enough while the L2s
+// hold those levels' tables.  Rows walked / from bricks, with the planes, in us: T = 2^17, 1.2 M samples 154 / 147, T = 2^18 152 / 149, T = 2^19 179 / 181,
+// T = 2^20, 0.8 M 186 / 200, T = 2^21 (2048 cells) 233 / 241, T = 2^21 and 2^22 (8192 cells), 4.0 M and 2.5 M 1316 / 1417 and 1048 / 1116.
+constexpr uint32_t kBricks8Log2T = 18;
+
 extern "C" int dg_hashgrid_encode_fwd_bricks(const dg_grid_desc *desc, const dg_order_desc *order, const float *table, const void *ordered,
                                              const uint32_t *pieces, const float *u, uint64_t N, uint32_t by_position, void *feat, void *stream)
 {
@@ -701,7 +706,7 @@ extern "C" int dg_hashgrid_encode_fwd_bricks(const dg_grid_desc *desc, const dg_
     };
     if (order->n_merged == 12) launch(encode_fwd_bricks_kernel<12>);
     else if (order->n_merged == 10) launch(encode_fwd_bricks_kernel<10>);
-    else if (order->n_merged == 8) launch(encode_fwd_bricks_kernel<8>);
+    else if (order->n_merged == 8 && desc->log2_T <= kBricks8Log2T) launch(encode_fwd_bricks_kernel<8>);
     else return dg_hashgrid_encode_fwd_split(desc, table, ordered, u, N, by_position, feat, stream);
     launch_planes(*desc, table, ordered, u, N, by_position, feat, st);
     return dg::launch_status(who);

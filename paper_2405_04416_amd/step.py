@@ -209,14 +209,14 @@ class TrainStep:
 
     def _split(self, m, N, use):
         """Whether the features of samples in spatial order are split: rows of the first levels, planes of the finer ones, which are
-        gathered level after level; the rows' merged levels come brick by brick from LDS.  Pays where an XCD's L2 holds much of one level's
+        gathered level after level; the rows' merged levels come brick by brick from LDS where that is faster.  Pays where an XCD's L2 holds much of one level's
         table but not of the sixteen that the ordered gather walks at once, and while neighbours share few of the finer levels' lines.  One
         walk / split in us:
         step, T = 2^17 1315 / 1284 at 2.0 M samples, 2260 / 2222 at 4.1 M, 6592 / 6733 at 13.3 M; T = 2^18 2344 / 2272 at 4.1 M, 3594 / 3564 at 6.6 M, 6574 / 6693 at
         13.3 M; T = 2^19 3830 / 3730 at 6.6 M, 5038 / 5020 at 9.2 M, 6737 / 6912 at 13.3 M; T = 2^20 1353 / 1284 at 1.5 M, 2096 / 2016 at 3.1 M, 3972 / 4151 at 6.6 M;
-        T = 2^21 1111 / 1092 at 1.0 M, 2236 / 2329 at 3.1 M; T = 2^22 with 2048 cells 4614 / 4825 (four of 1.0 M), with 8192 cells 1590 / 1541 at 1.1 M, 4706 / 4550 at
-        4.9 M, 9932 / 9725 at 11.3 M, 11344 / 11124 at 12.8 M; T = 2^23 11645 / 12166 at 12.8 M; T = 2^24 2395 / 2406 at 1.1 M.  T = 2^21 with 8192 cells was measured with
-        the walk for both: 1422 / 1336 at 1.0 M, 4793 / 4424 at 4.7 M.
+        T = 2^21 1111 / 1092 at 1.0 M, 2236 / 2329 at 3.1 M; T = 2^22 with 2048 cells 4614 / 4825 (four of 1.0 M), with 8192 cells 1257 / 1220 at 0.76 M, 2501 / 2395 at 2.3 M,
+        4768 / 4507 at 4.9 M, 8513 / 8501 at 9.8 M, 10 679 / 10 692 at 12.5 M; T = 2^23 11645 / 12166 at 12.8 M; T = 2^24 2395 / 2406 at 1.1 M.  T = 2^21 with 8192 cells 1116 / 1058 at
+        0.83 M, 2316 / 2081 at 2.3 M, 4320 / 3992 at 4.9 M.
         Occupancy-guided steps, whose samples share more: T = 2^18 1172 / 1189 at 1.5 M, T = 2^19 1196 / 1229, T = 2^20 1251 / 1363.
         Refresh, pieces of 8.4 M and 2.1 M candidates: T = 2^17 1344 / 1167; T = 2^18 1411 / 1205; T = 2^19 1646 / 1373, 2525 / 1680; T = 2^20 1789 / 1756, 2751 / 2204.
         Tables that are not named (below 2^17) were not measured and keep the one walk."""
