@@ -9,7 +9,7 @@
 //
 // Samples in the order of their rays: 16-byte records of pairs of corners along x, runs of lanes that share a cell in one (struct Merged).  Bound by
 // the arithmetic (some 490 vector instructions per wavefront and level), below 0.1 M samples by the steps' latency.  Whole training steps with appends sorted through LDS tiles (up to 64
-// bins) or one queue granule per bin (above) / now: eight sub-models, T = 2^19 and 2^22, 0.4 M samples each 6.20 / 6.11 ms; T = 2^23, 0.32 M 1.08 / 0.91;
+// bins) or one queue granule per bin (above) / rings as first built: eight sub-models, T = 2^19 and 2^22, 0.4 M samples each 6.20 / 6.11 ms; T = 2^23, 0.32 M 1.08 / 0.91;
 // T = 2^24, 0.37 M 1.75 / 1.27, 27 k 1.12 / 0.55.
 //
 // Samples in spatial order, the levels above those that are summed brick by brick: their cells are so small that few neighbours along a ray share one
