@@ -212,7 +212,7 @@ __device__ __forceinline__ uint64_t segment_ballot(bool on, uint32_t lane)
 
 template <uint32_t LANES>
 __global__ void __launch_bounds__(kBlock)
-march_count_kernel(MarchIn in, OccArgs occ, const uint32_t *__restrict__ bits, uint32_t *__restrict__ first, uint64_t *__restrict__ masks)
+march_count_kernel(MarchIn in, OccArgs occ, const uint32_t *__restrict__ bits, uint32_t *__restrict__ first, uint32_t *__restrict__ masks)
 {
     const uint32_t j = blockIdx.x * (kBlock / LANES) + threadIdx.x / LANES, lane = threadIdx.x % dg::kWave, in_seg = threadIdx.x % LANES;
     if (blockIdx.x == 0 && threadIdx.x == 0) first[in.n_seg] = 0;            // the scan turns it into the total
@@ -228,7 +228,11 @@ march_count_kernel(MarchIn in, OccArgs occ, const uint32_t *__restrict__ bits, u
         kept += (uint32_t)__popcll(mask);
         word |= mask << (base % 64u);
         if ((base + LANES) % 64u == 0u || base + LANES >= strata.n) {
-            if (in_seg == 0 && base < kMaskStrata) masks[(size_t)(kMaskWords / 2) * j + base / 64u] = word;
+            if (in_seg == 0 && base < kMaskStrata) {                        // words: the workspace may be aligned for no more
+                uint32_t *at = masks + (size_t)kMaskWords * j + base / 64u * 2u;
+                at[0] = (uint32_t)word;
+                at[1] = (uint32_t)(word >> 32);
+            }
             word = 0u;
         }
     }
@@ -514,7 +518,7 @@ extern "C" int dg_march_segments(const float *o, const float *d, const float *se
     auto march = [&](auto lanes) {
         constexpr uint32_t kLanes = decltype(lanes)::value;
         const uint32_t blocks = (uint32_t)(((uint64_t)n_seg * kLanes + kBlock - 1) / kBlock);
-        march_count_kernel<kLanes><<<blocks ? blocks : 1u, kBlock, 0, st>>>(in, g, bits, first, (uint64_t *)masks);
+        march_count_kernel<kLanes><<<blocks ? blocks : 1u, kBlock, 0, st>>>(in, g, bits, first, masks);
         scan_tile_sums_kernel<<<n_tiles, kBlock, 0, st>>>(first, n_vals, sums);
         scan_sums_kernel<<<1, kSumsBlock, 0, st>>>(sums, n_tiles);
         scan_apply_kernel<<<n_tiles, kBlock, 0, st>>>(first, n_vals, sums);
